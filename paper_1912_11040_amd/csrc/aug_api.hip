@@ -68,8 +68,7 @@ struct ScratchLayout {
     static constexpr size_t dct = window + align256(sizeof(float) * 2048);                      // float [128][128]
     static constexpr size_t offsets = dct + align256(sizeof(float) * AUG_MAX_MEL * AUG_MAX_MEL);
     static constexpr size_t frame_offsets = offsets + align256(sizeof(int64_t) * (AUG_STATIC_MAX_UTT + 1));
-    static constexpr size_t frame_first = frame_offsets + align256(sizeof(int64_t) * (AUG_STATIC_MAX_UTT + 1));
-    static constexpr size_t frame_items = frame_first + align256(sizeof(int) * (AUG_STATIC_MAX_UTT + 1));
+    static constexpr size_t frame_items = frame_offsets + align256(sizeof(int64_t) * (AUG_STATIC_MAX_UTT + 1));
     static constexpr size_t mel_tab = frame_items + align256(sizeof(int2) * AUG_STATIC_MAX_ROW_GROUPS);
     static constexpr size_t mel_tab_bytes = sizeof(float2) * (size_t)AUG_STATIC_MAX_UTT * (512 / 2 + 1 + 9);
     static constexpr size_t end = mel_tab + align256(mel_tab_bytes);
@@ -169,53 +168,81 @@ int grow(aug_ctx* ctx, DeviceBuffer& b, size_t bytes, const char* what) {
     return AUG_OK;
 }
 
-// Pinned staging slots of at least `entries` int64 each, with their events.
-int ring_reserve(aug_ctx* ctx, size_t entries) {
+// Bytes of a staging slot for n_utt + 1 = n entries: two int64 and two int arrays.
+size_t ring_bytes(size_t n) { return n * (2 * sizeof(int64_t) + 2 * sizeof(int)); }
+
+// Pinned staging slots of at least `bytes` each, with their events.
+int ring_reserve(aug_ctx* ctx, size_t bytes) {
     aug::HostRing& r = ctx->ring;
-    if (entries <= r.cap) return AUG_OK;
-    for (int i = 0; i < aug::HostRing::kSlots; ++i) {
-        if (r.done[i]) AUG_HIP(hipEventSynchronize(r.done[i]), "staging event wait");
-        if (r.slot[i]) {
-            AUG_HIP(hipHostFree(r.slot[i]), "staging free");
-            r.slot[i] = nullptr;
-        }
+    if (bytes <= r.bytes) return AUG_OK;
+    AUG_HIP(hipStreamSynchronize(ctx->stream), "stream synchronize");       // kernels still read the old slots
+    if (r.host) {
+        AUG_HIP(hipHostFree(r.host), "staging free");
+        r.host = nullptr;
     }
-    r.cap = 0;
-    const size_t want = entries + entries / 4 + 64;
-    for (int i = 0; i < aug::HostRing::kSlots; ++i) {
-        AUG_HIP(hipHostMalloc(reinterpret_cast<void**>(&r.slot[i]), want * sizeof(int64_t), hipHostMallocDefault),
-                "pinned staging buffer");
-        if (!r.done[i]) AUG_HIP(hipEventCreateWithFlags(&r.done[i], hipEventDisableTiming), "staging event");
-    }
-    r.cap = want;
+    r.bytes = 0;
+    const size_t want = (bytes + bytes / 4 + 4095) & ~(size_t)4095;
+    AUG_HIP(hipHostMalloc(reinterpret_cast<void**>(&r.host), want * aug::HostRing::kSlots, hipHostMallocDefault),
+            "pinned staging buffer");
+    AUG_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&r.device), r.host, 0), "pinned staging address");
+    for (hipEvent_t& e : r.done)
+        if (!e) AUG_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming), "staging event");
+    r.bytes = want;
     return AUG_OK;
 }
 
-// Copy up to two host arrays of n int64 each to the device through the next staging slot, without waiting
-// for the stream: the slot is reused only after this copy has run (its event).  A null array is skipped.
-int upload_offsets(aug_ctx* ctx, size_t n, const int64_t* a, int64_t* d_a, const int64_t* b, int64_t* d_b) {
+// Write a batch's arrays into the next staging slot and enqueue the packing kernel on them, without waiting for
+// the stream.  conv_block / frames_per_group > 0 ask for that table; upload_offsets is false where the device
+// already holds these offsets.  The slot's arrays: offsets, frame offsets, block prefix, group prefix.
+int upload_packing(aug_ctx* ctx, aug::PackArgs pa, const int64_t* offsets, bool upload_offsets, int conv_block,
+                   const int64_t* frame_offsets) {
     aug::HostRing& r = ctx->ring;
-    const int i = r.next;
-    AUG_HIP(hipEventSynchronize(r.done[i]), "staging event wait");     // an unrecorded event counts as complete
-    if (a) {
-        memcpy(r.slot[i], a, n * sizeof(int64_t));
-        AUG_HIP(hipMemcpyAsync(d_a, r.slot[i], n * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream), "offsets copy");
+    const int i = r.next, e = i / aug::HostRing::kPerEvent;
+    if (i % aug::HostRing::kPerEvent == 0)
+        AUG_HIP(hipEventSynchronize(r.done[e]), "staging event wait");      // an unrecorded event counts as complete
+    const size_t n = (size_t)pa.n_utt + 1, i64 = n * sizeof(int64_t);
+    unsigned char* const h = r.host + (size_t)i * r.bytes;
+    unsigned char* const d = r.device + (size_t)i * r.bytes;
+    pa.offsets = nullptr;
+    pa.frame_offsets = nullptr;
+    pa.conv_first = pa.frame_first = nullptr;
+    if (upload_offsets) {
+        memcpy(h, offsets, i64);
+        pa.offsets = reinterpret_cast<const int64_t*>(d);
     }
-    if (b) {
-        memcpy(r.slot[i] + n, b, n * sizeof(int64_t));
-        AUG_HIP(hipMemcpyAsync(d_b, r.slot[i] + n, n * sizeof(int64_t), hipMemcpyHostToDevice, ctx->stream),
-                "frame offsets copy");
+    if (frame_offsets) {
+        memcpy(h + i64, frame_offsets, i64);
+        pa.frame_offsets = reinterpret_cast<const int64_t*>(d + i64);
+        int* const first = reinterpret_cast<int*>(h + 2 * i64 + n * sizeof(int));
+        int at = 0;
+        for (int u = 0; u < pa.n_utt; ++u) {
+            first[u] = at;
+            at += (int)((frame_offsets[u + 1] - frame_offsets[u] + pa.frames_per_group - 1) / pa.frames_per_group);
+        }
+        first[pa.n_utt] = at;
+        pa.frame_first = reinterpret_cast<const int*>(d + 2 * i64 + n * sizeof(int));
     }
-    AUG_HIP(hipEventRecord(r.done[i], ctx->stream), "staging event record");
+    if (conv_block > 0) {
+        int* const first = reinterpret_cast<int*>(h + 2 * i64);
+        int at = 0;
+        for (int u = 0; u < pa.n_utt; ++u) {
+            first[u] = at;
+            at += (int)((offsets[u + 1] - offsets[u] + conv_block - 1) / conv_block);
+        }
+        first[pa.n_utt] = at;
+        pa.conv_first = reinterpret_cast<const int*>(d + 2 * i64);
+    }
+    AUG_HIP(aug::launch_pack(ctx->stream, pa), "packing kernel");
+    if (i % aug::HostRing::kPerEvent == aug::HostRing::kPerEvent - 1)
+        AUG_HIP(hipEventRecord(r.done[e], ctx->stream), "staging event record");
     r.next = (i + 1) % aug::HostRing::kSlots;
     return AUG_OK;
 }
 
 // Device copies of the offsets and the (utterance, block) / (utterance, frame group) tables.  When the host
 // arrays equal the previous call's nothing is done (a steady-state call is kernel launches only).  Otherwise
-// the arrays go to the device through pinned staging with asynchronous copies and the tables are rebuilt
-// there by two small kernels, all in stream order behind the earlier calls' kernels: the call does not
-// wait for the stream.  The host only counts the items (one pass over the utterances) to size the grids.
+// the arrays go through pinned staging and one kernel rebuilds the tables, in stream order behind the earlier
+// calls' kernels: the call does not wait for the stream.
 int sync_packing(aug_ctx* ctx, int n_utt, const int64_t* offsets, const int64_t* frame_offsets,
                  int conv_block, int frames_per_group) {
     aug::Packing& pk = ctx->packing;
@@ -249,18 +276,18 @@ int sync_packing(aug_ctx* ctx, int n_utt, const int64_t* offsets, const int64_t*
     }
     if (need_fr) {
         AUG_TRY(grow(ctx, ctx->d_frame_offsets, n * sizeof(int64_t), "frame offsets buffer"));
-        AUG_TRY(grow(ctx, ctx->d_frame_first, n * sizeof(int), "frame group prefix table"));
         AUG_TRY(grow(ctx, ctx->d_frame_items, (size_t)std::max<int64_t>(n_groups, 1) * sizeof(int2), "frame group table"));
     }
-    AUG_TRY(ring_reserve(ctx, 2 * n));
-    if (!same_off || need_fr)
-        AUG_TRY(upload_offsets(ctx, n, same_off ? nullptr : offsets, ctx->d_offsets.as<int64_t>(),
-                               need_fr ? frame_offsets : nullptr, ctx->d_frame_offsets.as<int64_t>()));
-    AUG_HIP(aug::launch_pack(ctx->stream, n_utt, ctx->d_offsets.as<int64_t>(), ctx->d_frame_offsets.as<int64_t>(),
-                             conv_block, frames_per_group,
-                             need_conv ? ctx->d_conv_first.as<int>() : nullptr, ctx->d_conv_items.as<int2>(), n_conv,
-                             need_fr ? ctx->d_frame_first.as<int>() : nullptr, ctx->d_frame_items.as<int2>(), n_groups),
-            "packing kernels");
+    AUG_TRY(ring_reserve(ctx, ring_bytes(n)));
+    aug::PackArgs pa{};
+    pa.n_utt = n_utt;
+    pa.frames_per_group = frames_per_group;
+    pa.d_offsets = ctx->d_offsets.as<int64_t>();
+    pa.d_frame_offsets = ctx->d_frame_offsets.as<int64_t>();
+    pa.d_conv_first = ctx->d_conv_first.as<int>();
+    pa.conv_items = ctx->d_conv_items.as<int2>();
+    pa.frame_items = ctx->d_frame_items.as<int2>();
+    AUG_TRY(upload_packing(ctx, pa, offsets, !same_off, need_conv ? conv_block : 0, need_fr ? frame_offsets : nullptr));
 
     if (!same_off) {
         pk.offsets.assign(offsets, offsets + n);
@@ -547,7 +574,7 @@ int aug_create(aug_ctx** out, int device_id, void* hip_stream) {
         }
         ctx->scratch = g_scratch[device_id];
     }
-    if (ring_reserve(ctx, 2 * ((size_t)AUG_STATIC_MAX_UTT + 1)) != AUG_OK) {
+    if (ring_reserve(ctx, ring_bytes((size_t)AUG_STATIC_MAX_UTT + 1)) != AUG_OK) {
         aug_destroy(ctx);
         return AUG_ERR_NOMEM;
     }
@@ -563,16 +590,15 @@ int aug_destroy(aug_ctx* ctx) {
         rc = AUG_ERR_HIP;
     }
     DeviceBuffer* bufs[] = {&ctx->d_offsets, &ctx->d_frame_offsets, &ctx->d_conv_items, &ctx->d_frame_items,
-                            &ctx->d_conv_first, &ctx->d_frame_first,
+                            &ctx->d_conv_first,
                             &ctx->rir_items, &ctx->rir_ctrl, &ctx->mic_rows, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->gains, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab,
                             &ctx->window};
     for (DeviceBuffer* b : bufs) b->release();
     for (DeviceBuffer& b : ctx->twiddle) b.release();
     for (auto& m : ctx->marks) (void)hipEventDestroy(m.first);
-    for (int i = 0; i < aug::HostRing::kSlots; ++i) {
-        if (ctx->ring.done[i]) (void)hipEventDestroy(ctx->ring.done[i]);
-        if (ctx->ring.slot[i]) (void)hipHostFree(ctx->ring.slot[i]);
-    }
+    for (hipEvent_t e : ctx->ring.done)
+        if (e) (void)hipEventDestroy(e);
+    if (ctx->ring.host) (void)hipHostFree(ctx->ring.host);
     delete ctx;
     return rc;
 }
@@ -721,21 +747,24 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     if (n_utt == 0 || n_groups == 0) return AUG_OK;
     unsigned char* const base = ctx->scratch;            // the device address, not the array's name
     if (!base) return fail(ctx, AUG_ERR_HIP, "the static scratch array is not available on this device");
-    if (ctx->ring.cap < 2 * ((size_t)n_utt + 1)) return fail(ctx, AUG_ERR_HIP, "staging ring missing");
+    if (ctx->ring.bytes < ring_bytes((size_t)n_utt + 1)) return fail(ctx, AUG_ERR_HIP, "staging ring missing");
 
     float2* const tw = reinterpret_cast<float2*>(base + ScratchLayout::twiddle);
     float* const window = reinterpret_cast<float*>(base + ScratchLayout::window);
     float* const dct = reinterpret_cast<float*>(base + ScratchLayout::dct);
     int64_t* const d_off = reinterpret_cast<int64_t*>(base + ScratchLayout::offsets);
     int64_t* const d_foff = reinterpret_cast<int64_t*>(base + ScratchLayout::frame_offsets);
-    int* const d_first = reinterpret_cast<int*>(base + ScratchLayout::frame_first);
     int2* const d_items = reinterpret_cast<int2*>(base + ScratchLayout::frame_items);
     float2* const mel_tab = reinterpret_cast<float2*>(base + ScratchLayout::mel_tab);
 
     // Everything the kernels read from the array is rewritten here, in stream order, by this call.
-    AUG_TRY(upload_offsets(ctx, (size_t)n_utt + 1, offsets, d_off, frame_offsets, d_foff));
-    AUG_HIP(aug::launch_pack(ctx->stream, n_utt, d_off, d_foff, 0, fpg, nullptr, nullptr, 0, d_first, d_items, n_groups),
-            "packing kernels");
+    aug::PackArgs pa{};
+    pa.n_utt = n_utt;
+    pa.frames_per_group = fpg;
+    pa.d_offsets = d_off;
+    pa.d_frame_offsets = d_foff;
+    pa.frame_items = d_items;
+    AUG_TRY(upload_packing(ctx, pa, offsets, true, 0, frame_offsets));
     AUG_HIP(aug::launch_twiddle(ctx->stream, cfg->nfft / 2, tw), "twiddle kernel");
     AUG_HIP(aug::launch_window(ctx->stream, cfg->win, window), "window kernel");
     if (cfg->feature == AUG_FEAT_MFCC)

@@ -32,14 +32,16 @@ struct Packing {
     int64_t n_frame_groups = 0;
 };
 
-// Pinned host staging for the offset arrays: a call copies its arrays into the next slot and enqueues an
-// asynchronous copy from there, so the caller's arrays are free when the call returns and nothing waits for
-// the stream.  A slot is reused only after the copy that read it has completed (its event).
+// Pinned host staging for the offset arrays: a call writes its arrays into the next slot and the packing kernel
+// reads them there, so the caller's arrays are free when the call returns and nothing waits for the stream.
+// A slot is reused only after the kernel that read it has finished: one event for every kPerEvent slots in
+// turn, recorded behind the last of them and waited for before the first is written again.
 struct HostRing {
-    static constexpr int kSlots = 4;
-    int64_t* slot[kSlots] = {nullptr, nullptr, nullptr, nullptr};
-    hipEvent_t done[kSlots] = {nullptr, nullptr, nullptr, nullptr};
-    size_t cap = 0;                      // int64 entries per slot
+    static constexpr int kSlots = 16, kPerEvent = 4;
+    unsigned char* host = nullptr;       // kSlots slots of `bytes` each
+    unsigned char* device = nullptr;     // the same memory as the device addresses it
+    hipEvent_t done[kSlots / kPerEvent] = {};
+    size_t bytes = 0;
     int next = 0;
 };
 
@@ -57,7 +59,6 @@ struct aug_ctx {
     aug::DeviceBuffer d_conv_items;      // int2 [n_conv_blocks]: (utterance, block)
     aug::DeviceBuffer d_frame_items;     // int2 [n_frame_groups]: (utterance, first frame)
     aug::DeviceBuffer d_conv_first;      // int [n_utt+1]: blocks of the utterances before u
-    aug::DeviceBuffer d_frame_first;     // int [n_utt+1]: frame groups of the utterances before u
     aug::HostRing ring;
     unsigned char* scratch = nullptr;    // this device's copy of the library's static scratch array
 
@@ -198,12 +199,23 @@ hipError_t launch_vtlp_table(hipStream_t s, int n_utt, const float* alpha, float
 hipError_t launch_vtlp_resynth(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t max_len,
                                const float* wave, const float2* tab, const float2* twiddle, float* out);
 
-// Exclusive prefix sums of the per-utterance item counts (blocks of conv_block samples; groups of
-// frames_per_group output rows) and the item tables (utterance, block) / (utterance, first row), all from the
-// device copies of the offsets.  A null `*_first` skips that table.  The item counts are the host's.
-hipError_t launch_pack(hipStream_t s, int n_utt, const int64_t* d_offsets, const int64_t* d_frame_offsets,
-                       int conv_block, int frames_per_group, int* conv_first, int2* conv_items, int64_t n_conv_items,
-                       int* frame_first, int2* frame_items, int64_t n_frame_items);
+// Device copies of a batch's offsets and its item tables, from the arrays that the host has left in pinned
+// memory: offsets, frame offsets and the exclusive prefix sums of the items per utterance (blocks of the
+// convolution; groups of frames_per_group output rows), n_utt + 1 entries each.  A null source is skipped.
+struct PackArgs {
+    int n_utt;
+    int frames_per_group;
+    const int64_t* offsets;          // pinned host memory, as the device sees it
+    const int64_t* frame_offsets;
+    const int* conv_first;
+    const int* frame_first;
+    int64_t* d_offsets;              // device
+    int64_t* d_frame_offsets;
+    int* d_conv_first;
+    int2* conv_items;                // (utterance, block)
+    int2* frame_items;               // (utterance, first row)
+};
+hipError_t launch_pack(hipStream_t s, const PackArgs& a);
 
 // fill n 32-bit words with a value (used instead of memset so that calls stay graph-capturable)
 hipError_t launch_fill_u32(hipStream_t s, void* p, uint32_t v, int64_t n);
