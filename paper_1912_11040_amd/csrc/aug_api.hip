@@ -63,14 +63,14 @@ std::mutex g_scratch_mutex;
 constexpr size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 // byte offsets of the tables inside the array
 struct ScratchLayout {
-    static constexpr size_t twiddle = 0;                                                        // float2 [393]
-    static constexpr size_t window = twiddle + align256(sizeof(float2) * 512);                  // float [<= 2048]
+    static constexpr size_t lane_consts = 0;                                                    // float [mel_lane_floats()]
+    static constexpr size_t window = 12288;                                                     // float [<= 2048]
     static constexpr size_t dct = window + align256(sizeof(float) * 2048);                      // float [128][128]
     static constexpr size_t offsets = dct + align256(sizeof(float) * AUG_MAX_MEL * AUG_MAX_MEL);
     static constexpr size_t frame_offsets = offsets + align256(sizeof(int64_t) * (AUG_STATIC_MAX_UTT + 1));
     static constexpr size_t frame_items = frame_offsets + align256(sizeof(int64_t) * (AUG_STATIC_MAX_UTT + 1));
     static constexpr size_t mel_tab = frame_items + align256(sizeof(int2) * AUG_STATIC_MAX_ROW_GROUPS);
-    static constexpr size_t mel_tab_bytes = sizeof(float2) * (size_t)AUG_STATIC_MAX_UTT * (512 / 2 + 1 + 9);
+    static constexpr size_t mel_tab_bytes = sizeof(float2) * (size_t)AUG_STATIC_MAX_UTT * (512 / 2 + 1 + 21);
     static constexpr size_t end = mel_tab + align256(mel_tab_bytes);
 };
 static_assert(ScratchLayout::end <= AUG_STATIC_SCRATCH_BYTES, "the tables fit the static array");
@@ -375,6 +375,10 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
 int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
     if (n_utt == 0 || ctx->packing.n_frame_groups == 0) return AUG_OK;
     AUG_TRY(grow(ctx, ctx->window, sizeof(float) * (size_t)cfg->win, "window table"));
+    if (!ctx->mel_lanes.ptr) {
+        AUG_TRY(grow(ctx, ctx->mel_lanes, sizeof(float) * (size_t)aug::mel_lane_floats(), "lane constants"));
+        AUG_HIP(aug::launch_mel_lanes(ctx->stream, ctx->mel_lanes.as<float>()), "lane constants kernel");
+    }
     if (cfg->feature == AUG_FEAT_MFCC)
         AUG_TRY(grow(ctx, ctx->dct, sizeof(float) * (size_t)cfg->n_ceps * cfg->n_mel, "cosine table"));
     AUG_TRY(grow(ctx, ctx->mel_tab, sizeof(float2) * (size_t)n_utt * aug::mel_table_stride(cfg->nfft), "mel table"));
@@ -461,15 +465,26 @@ int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, 
     return AUG_OK;
 }
 
+// The mel table kernel's arguments; the band edges are kept from call to call of one configuration.
+const aug::MelTableArgs& mel_table_args(aug_ctx* ctx, const aug_frontend_cfg* cfg, const float* alpha, float2* tab) {
+    aug::MelTableArgs& a = ctx->mel_args;
+    if (!ctx->have_mel_args || a.cfg.n_mel != cfg->n_mel || a.cfg.f_lo != cfg->f_lo || a.cfg.f_hi != cfg->f_hi) {
+        aug::mel_edges(*cfg, a);
+        ctx->have_mel_args = true;
+    }
+    a.cfg = *cfg;
+    a.alpha = alpha;
+    a.tab = tab;
+    return a;
+}
+
 // n_extra > 0: the analysed signal is wave + sum_j gains[u][j] extra[j * extra_stride + .] (mixed on the fly)
 int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const float* alpha, const aug_frontend_cfg* cfg,
             float* feats_out, int n_extra = 0, const float* extra = nullptr, int64_t extra_stride = 0,
             const float* gains = nullptr) {
     const aug::Packing& pk = ctx->packing;
     if (n_utt == 0 || pk.n_frame_groups == 0) return AUG_OK;
-    const float2* tw = nullptr;
     AUG_TRY(prepare_mel(ctx, n_utt, cfg));
-    AUG_TRY(ensure_twiddle(ctx, cfg->nfft / 2, &tw));
     if (ctx->window_n != cfg->win) {
         AUG_HIP(aug::launch_window(ctx->stream, cfg->win, ctx->window.as<float>()), "window kernel");
         ctx->window_n = cfg->win;
@@ -484,7 +499,8 @@ int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const float* alpha, cons
         dct = ctx->dct.as<float>();
     }
     AUG_TRY(mark(ctx, -1));
-    AUG_HIP(aug::launch_mel_table(ctx->stream, n_utt, alpha, *cfg, ctx->mel_tab.as<float2>()), "mel table kernel");
+    AUG_HIP(aug::launch_mel_table(ctx->stream, n_utt, mel_table_args(ctx, cfg, alpha, ctx->mel_tab.as<float2>())),
+            "mel table kernel");
     aug::MelArgs ma;
     ma.offsets = ctx->d_offsets.as<int64_t>();
     ma.frame_offsets = ctx->d_frame_offsets.as<int64_t>();
@@ -499,7 +515,7 @@ int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const float* alpha, cons
     ma.mel_tab = ctx->mel_tab.as<float2>();
     ma.dct = dct;
     ma.window = ctx->window.as<float>();
-    ma.twiddle = tw;
+    ma.lane_consts = ctx->mel_lanes.as<float>();
     ma.cfg = *cfg;
     ma.feats = feats_out;
     AUG_HIP(aug::launch_mel(ctx->stream, ma), "mel kernel");
@@ -591,7 +607,7 @@ int aug_destroy(aug_ctx* ctx) {
     }
     DeviceBuffer* bufs[] = {&ctx->d_offsets, &ctx->d_frame_offsets, &ctx->d_conv_items, &ctx->d_frame_items,
                             &ctx->d_conv_first,
-                            &ctx->rir_items, &ctx->rir_ctrl, &ctx->mic_rows, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->gains, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab,
+                            &ctx->rir_items, &ctx->rir_ctrl, &ctx->mic_rows, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->gains, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab, &ctx->mel_lanes,
                             &ctx->window};
     for (DeviceBuffer* b : bufs) b->release();
     for (DeviceBuffer& b : ctx->twiddle) b.release();
@@ -749,7 +765,7 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     if (!base) return fail(ctx, AUG_ERR_HIP, "the static scratch array is not available on this device");
     if (ctx->ring.bytes < ring_bytes((size_t)n_utt + 1)) return fail(ctx, AUG_ERR_HIP, "staging ring missing");
 
-    float2* const tw = reinterpret_cast<float2*>(base + ScratchLayout::twiddle);
+    float* const lane_consts = reinterpret_cast<float*>(base + ScratchLayout::lane_consts);
     float* const window = reinterpret_cast<float*>(base + ScratchLayout::window);
     float* const dct = reinterpret_cast<float*>(base + ScratchLayout::dct);
     int64_t* const d_off = reinterpret_cast<int64_t*>(base + ScratchLayout::offsets);
@@ -765,11 +781,11 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     pa.d_frame_offsets = d_foff;
     pa.frame_items = d_items;
     AUG_TRY(upload_packing(ctx, pa, offsets, true, 0, frame_offsets));
-    AUG_HIP(aug::launch_twiddle(ctx->stream, cfg->nfft / 2, tw), "twiddle kernel");
+    AUG_HIP(aug::launch_mel_lanes(ctx->stream, lane_consts), "lane constants kernel");
     AUG_HIP(aug::launch_window(ctx->stream, cfg->win, window), "window kernel");
     if (cfg->feature == AUG_FEAT_MFCC)
         AUG_HIP(aug::launch_dct_table(ctx->stream, cfg->n_ceps, cfg->n_mel, dct), "cosine table kernel");
-    AUG_HIP(aug::launch_mel_table(ctx->stream, n_utt, alpha, *cfg, mel_tab), "mel table kernel");
+    AUG_HIP(aug::launch_mel_table(ctx->stream, n_utt, mel_table_args(ctx, cfg, alpha, mel_tab)), "mel table kernel");
     aug::MelArgs ma;
     ma.offsets = d_off;
     ma.frame_offsets = d_foff;
@@ -784,7 +800,7 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     ma.mel_tab = mel_tab;
     ma.dct = cfg->feature == AUG_FEAT_MFCC ? dct : nullptr;
     ma.window = window;
-    ma.twiddle = tw;
+    ma.lane_consts = lane_consts;
     ma.cfg = *cfg;
     ma.feats = feats_out;
     AUG_HIP(aug::launch_mel(ctx->stream, ma), "mel kernel");

@@ -45,6 +45,15 @@ struct HostRing {
     int next = 0;
 };
 
+// Per-utterance (band, weight) table of the warped mel bank followed by how the filters are dealt to the matrix
+// cores: tab float2 [n_utt][mel_table_stride(nfft)].  mel_edges fills in what depends on the configuration only.
+struct MelTableArgs {
+    double edges[AUG_MAX_MEL + 2];   // band edges, Hz
+    float mel_lo, inv_step;          // f_lo in mel, 1 / spacing of the edges in mel
+    aug_frontend_cfg cfg;
+    const float* alpha;
+    float2* tab;
+};
 }  // namespace aug
 
 struct aug_ctx {
@@ -76,13 +85,16 @@ struct aug_ctx {
     aug::DeviceBuffer energy;            // double [n_utt][1+n_noise]: energies of the reverberated signals
     aug::DeviceBuffer gains;             // float [n_utt][n_noise]
     aug::DeviceBuffer first_tap;         // int [n_utt][1+n_noise]
-    aug::DeviceBuffer mel_tab;           // float2 [n_utt][nfft/2+1]: (channel, weight) per bin
+    aug::DeviceBuffer mel_tab;           // float2 [n_utt][mel_table_stride(nfft)]: (band, weight) per bin, then the plan
+    aug::DeviceBuffer mel_lanes;         // float [mel_lane_floats()], filled once
     aug::DeviceBuffer twiddle[16];       // per log2(n): float2 [n + n/2 + 1] FFT twiddles
     aug::DeviceBuffer window;            // float [win]
     aug::DeviceBuffer dct;               // float [n_ceps][n_mel]
     int dct_ceps = 0, dct_mel = 0;       // shape the table was built for
     aug::DeviceBuffer vtlp_tab;          // float2 [n_utt][vtlp_table_entries()]: (source bin, weight) per output bin
     int window_n = 0;
+    aug::MelTableArgs mel_args{};        // band edges of the last front-end configuration seen
+    bool have_mel_args = false;
 
     // stage timing: events recorded in stream order, each tagged with the stage it ends (-1 = a start mark)
     bool profiling = false;
@@ -150,11 +162,13 @@ hipError_t launch_gains(hipStream_t s, int n_utt, int n_src, const double* energ
 hipError_t launch_mix(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t stride, int n_src,
                       const float* reverb, const float* gains, float* mixed_out, int64_t max_len);
 
-// Per-utterance (band, weight) table of the warped mel bank followed by the lane partition of the
-// bins: tab float2 [n_utt][mel_table_stride(nfft)].
+void mel_edges(const aug_frontend_cfg& cfg, MelTableArgs& a);
 int mel_table_stride(int nfft);
-hipError_t launch_mel_table(hipStream_t s, int n_utt, const float* alpha, const aug_frontend_cfg& cfg,
-                            float2* tab);
+hipError_t launch_mel_table(hipStream_t s, int n_utt, const MelTableArgs& a);
+
+// The front end's per-lane constants, float [mel_lane_floats()].
+int mel_lane_floats();
+hipError_t launch_mel_lanes(hipStream_t s, float* lane_consts);
 
 // Hamming window, float [win].
 hipError_t launch_window(hipStream_t s, int win, float* w);
@@ -181,7 +195,7 @@ struct MelArgs {
     const float2* mel_tab;
     const float* dct;              // [n_ceps][n_mel] orthonormal DCT-II rows (AUG_FEAT_MFCC), else null
     const float* window;
-    const float2* twiddle;         // table for the nfft/2-point complex transform
+    const float* lane_consts;
     aug_frontend_cfg cfg;
     float* feats;
 };

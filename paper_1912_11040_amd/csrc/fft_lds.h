@@ -28,23 +28,23 @@ namespace aug {
 __device__ __host__ constexpr int lds_pad(int i) { return i + (i >> 4); }
 __device__ __host__ constexpr int lds_padded_size(int n) { return n + (n >> 4); }
 
-__device__ inline float2 cmul(float2 a, float2 b) {
+__host__ __device__ inline float2 cmul(float2 a, float2 b) {
     return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-__device__ inline float2 cmul_conj(float2 a, float2 b) {   // a * conj(b)
+__host__ __device__ inline float2 cmul_conj(float2 a, float2 b) {   // a * conj(b)
     return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
-__device__ inline float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ inline float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
-__device__ inline float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
+__host__ __device__ inline float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
+__host__ __device__ inline float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+__host__ __device__ inline float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 // multiply by -i (forward) or +i (inverse)
-template <bool INV> __device__ inline float2 rot90(float2 a) {
+template <bool INV> __host__ __device__ inline float2 rot90(float2 a) {
     return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
 }
 
 // 4-point DFT, natural order in and out; INV uses exp(+2 pi i / 4).
 template <bool INV>
-__device__ inline void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
+__host__ __device__ inline void dft4(float2& a0, float2& a1, float2& a2, float2& a3) {
     const float2 s02 = cadd(a0, a2), d02 = csub(a0, a2);
     const float2 s13 = cadd(a1, a3), d13 = rot90<INV>(csub(a1, a3));
     a0 = cadd(s02, s13);
@@ -100,6 +100,135 @@ template <bool INV> struct SmallDft<16, INV> {
             }
     }
 };
+
+// ---- radix-4 and radix-16 steps with their twiddles folded into multiply-adds ----------------------------
+// A twiddle w = c (1 + i t), t = tan of its angle, costs two fused multiply-adds if the factor c is left for
+// the additions that follow, where it is the multiplier of a fused multiply-add and costs nothing: a radix-4
+// step on twiddled inputs takes 22 instructions instead of 12 + 16, a radix-16 step 176 instead of 228.
+// Results round as those of the plain form do: where c is small, t is large and the sum inside is the term
+// that survives the product with c.  (c is kept at 2^-40 or above in magnitude, so that t and the ratio of
+// two such factors stay far from overflow; the twiddle is then off by 2^-40, a 2^-16th of its rounding.)
+struct Tw4 {
+    float t1, t2, t3;      // tangents of w1, w2 = w1^2, w3 = w1^3
+    float c1, c2, r;       // cosines of w1, w2; cosine of w3 over that of w1
+};
+constexpr int kTw4Floats = sizeof(Tw4) / sizeof(float);
+
+// w1 = exp(-i pi x), evaluated in double precision
+__host__ __device__ inline Tw4 make_tw4(double x) {
+    double c[3], t[3];
+    for (int m = 0; m < 3; ++m) {
+        double sn;
+        sincospi(-x * (double)(m + 1), &sn, &c[m]);
+        if (fabs(c[m]) < 0x1p-40) c[m] = c[m] < 0.0 ? -0x1p-40 : 0x1p-40;
+        t[m] = sn / c[m];
+    }
+    return Tw4{(float)t[0], (float)t[1], (float)t[2], (float)c[0], (float)c[1], (float)(c[2] / c[0])};
+}
+
+// a (1 + i t), the twiddle conjugated for the inverse
+template <bool INV> __host__ __device__ inline float2 tilt(float2 a, float t) {
+    return INV ? make_float2(fmaf(t, a.y, a.x), fmaf(-t, a.x, a.y)) : make_float2(fmaf(-t, a.y, a.x), fmaf(t, a.x, a.y));
+}
+__host__ __device__ inline float2 cfma(float k, float2 b, float2 a) { return make_float2(fmaf(k, b.x, a.x), fmaf(k, b.y, a.y)); }
+
+// 4-point DFT of a0, c1 a1, c2 a2, c1 r a3
+template <bool INV>
+__host__ __device__ inline void dft4_scaled(float2& a0, float2& a1, float2& a2, float2& a3, float c1, float c2, float r) {
+    const float2 s02 = cfma(c2, a2, a0), d02 = cfma(-c2, a2, a0);
+    const float2 s13 = cfma(r, a3, a1), d13 = rot90<INV>(cfma(-r, a3, a1));
+    a0 = cfma(c1, s13, s02);
+    a1 = cfma(c1, d13, d02);
+    a2 = cfma(-c1, s13, s02);
+    a3 = cfma(-c1, d13, d02);
+}
+template <bool INV>
+__host__ __device__ inline void dft4_twiddled(float2& a0, float2& a1, float2& a2, float2& a3, const Tw4& w) {
+    a1 = tilt<INV>(a1, w.t1);
+    a2 = tilt<INV>(a2, w.t2);
+    a3 = tilt<INV>(a3, w.t3);
+    dft4_scaled<INV>(a0, a1, a2, a3, w.c1, w.c2, w.r);
+}
+
+// The four inner butterflies of a 16-point DFT, on v[4 r1 + m2] with the constant twiddles W16^{r1 m2} and, in
+// the SHARED form, inputs that still await the factors c1, c2, c1 r of a twiddle common to all four.
+// cos and sin of pi/8 and 3 pi/8 over each other:
+constexpr float kTan8 = 0.41421356237309505f, kCot8 = 2.414213562373095f, kCos8 = 0.92387953251128674f, kSin8 = 0.38268343236508977f;
+constexpr float kHalfRoot = 0.70710678118654752f;
+template <bool INV, bool SHARED>
+__host__ __device__ inline void dft16_inner(float2* v, float c1, float c2, float r) {
+    if (!SHARED) c1 = c2 = r = 1.f;
+    if (SHARED) dft4_scaled<INV>(v[0], v[1], v[2], v[3], c1, c2, r);
+    else dft4<INV>(v[0], v[1], v[2], v[3]);
+    // r1 = 1: angles pi/8, pi/4, 3 pi/8
+    v[5] = tilt<INV>(v[5], -kTan8);
+    v[6] = tilt<INV>(v[6], -1.f);
+    v[7] = tilt<INV>(v[7], -kCot8);
+    dft4_scaled<INV>(v[4], v[5], v[6], v[7], kCos8 * c1, kHalfRoot * c2, kTan8 * r);
+    // r1 = 2: pi/4, pi/2, 3 pi/4
+    v[9] = tilt<INV>(v[9], -1.f);
+    v[10] = rot90<INV>(v[10]);
+    v[11] = tilt<INV>(v[11], 1.f);
+    dft4_scaled<INV>(v[8], v[9], v[10], v[11], kHalfRoot * c1, c2, -r);
+    // r1 = 3: 3 pi/8, 3 pi/4, 9 pi/8
+    v[13] = tilt<INV>(v[13], -kCot8);
+    v[14] = tilt<INV>(v[14], 1.f);
+    v[15] = tilt<INV>(v[15], -kTan8);
+    dft4_scaled<INV>(v[12], v[13], v[14], v[15], kSin8 * c1, -kHalfRoot * c2, -kCot8 * r);
+}
+// v[4 r1 + r2] = y[r1 + 4 r2] -> natural order (register names only)
+__host__ __device__ inline void dft16_transpose(float2* v) {
+#pragma unroll
+    for (int r1 = 0; r1 < 4; ++r1)
+#pragma unroll
+        for (int r2 = r1 + 1; r2 < 4; ++r2) {
+            const float2 t = v[4 * r1 + r2];
+            v[4 * r1 + r2] = v[4 * r2 + r1];
+            v[4 * r2 + r1] = t;
+        }
+}
+
+// 16-point DFT, natural order in and out: 144 instructions
+template <bool INV> __host__ __device__ inline void dft16(float2* v) {
+#pragma unroll
+    for (int m2 = 0; m2 < 4; ++m2) dft4<INV>(v[m2], v[m2 + 4], v[m2 + 8], v[m2 + 12]);      // v[m2 + 4 r1]
+    dft16_inner<INV, false>(v, 1.f, 1.f, 1.f);
+    dft16_transpose(v);
+}
+
+// 16-point DFT of v[m] w^m.  The first four butterflies share the twiddles w^4, w^8, w^12; those of the second
+// four are (w W16^{r1})^{m2}.  All thirty factors given: 176 instructions.
+struct Tw16 { Tw4 outer, inner[4]; };
+constexpr int kTw16Floats = sizeof(Tw16) / sizeof(float);
+__host__ __device__ inline Tw16 make_tw16(double x) {          // w = exp(-i pi x)
+    Tw16 w;
+    w.outer = make_tw4(4.0 * x);
+    for (int r1 = 0; r1 < 4; ++r1) w.inner[r1] = make_tw4(x + 0.125 * (double)r1);
+    return w;
+}
+template <bool INV> __host__ __device__ inline void dft16_twiddled(float2* v, const Tw16& w) {
+#pragma unroll
+    for (int m2 = 0; m2 < 4; ++m2) dft4_twiddled<INV>(v[m2], v[m2 + 4], v[m2 + 8], v[m2 + 12], w.outer);
+#pragma unroll
+    for (int r1 = 0; r1 < 4; ++r1) dft4_twiddled<INV>(v[4 * r1], v[4 * r1 + 1], v[4 * r1 + 2], v[4 * r1 + 3], w.inner[r1]);
+    dft16_transpose(v);
+}
+// The same from twelve factors, for w that differ from thread to thread: the second four butterflies take w^{m2}
+// and the constant W16^{r1 m2} one after the other.  199 instructions.
+struct Tw16Short { Tw4 outer, inner; };
+__host__ __device__ inline Tw16Short make_tw16_short(double x) { return Tw16Short{make_tw4(4.0 * x), make_tw4(x)}; }
+template <bool INV> __host__ __device__ inline void dft16_twiddled(float2* v, const Tw16Short& w) {
+#pragma unroll
+    for (int m2 = 0; m2 < 4; ++m2) dft4_twiddled<INV>(v[m2], v[m2 + 4], v[m2 + 8], v[m2 + 12], w.outer);
+#pragma unroll
+    for (int r1 = 0; r1 < 4; ++r1) {
+        v[4 * r1 + 1] = tilt<INV>(v[4 * r1 + 1], w.inner.t1);
+        v[4 * r1 + 2] = tilt<INV>(v[4 * r1 + 2], w.inner.t2);
+        v[4 * r1 + 3] = tilt<INV>(v[4 * r1 + 3], w.inner.t3);
+    }
+    dft16_inner<INV, true>(v, w.inner.c1, w.inner.c2, w.inner.r);
+    dft16_transpose(v);
+}
 
 // v[m] *= w^m for m = 1..R-1, powers by products of depth <= 4
 template <int R> __device__ inline void twiddle_inputs(float2* v, float2 w1) {

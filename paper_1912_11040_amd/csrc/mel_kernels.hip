@@ -7,11 +7,11 @@
 // Adjacent unit-peak triangles share their edges, so a bin whose warped frequency
 // falls between band edges c and c+1 feeds only filter c (rising side, weight w) and
 // filter c-1 (falling side, weight 1-w).  A small kernel writes (c, w) per bin and
-// utterance; the main kernel runs each K-point real transform as a K/2-point complex
-// FFT in LDS (16 lanes per frame, two radix-16 passes).  The bins are cut into 16 contiguous ranges that
-// end where the band changes, one per lane, so a lane owns every band sum it forms (no atomics); channel m
-// is the rising side of band m plus the falling side of band m + 1.  Other epilogues of the same
-// energies (log-mel, MFCC) and the on-the-fly mixture of reverberated sources are options of the kernel.
+// utterance and how the filters are dealt to the matrix cores (MelPlan); the main kernel runs each K-point
+// real transform as a K/2-point complex FFT (16 lanes per frame, two radix-16 passes with one exchange
+// through LDS), forms the bin powers in registers and projects them with 4x4x1 matrix instructions.  Other
+// epilogues of the same energies (log-mel, MFCC) and the on-the-fly mixture of reverberated sources
+// are options of the kernel.
 
 #include "aug_internal.h"
 #include "fft_lds.h"
@@ -30,80 +30,156 @@ __global__ void window_kernel(int win, float* w) {
     w[i] = (float)(0.54 - 0.46 * c);
 }
 
-// (band, weight) of bin k for one utterance: where Eq. (1) puts the bin on the mel scale
-__device__ inline float2 mel_bin_entry(const aug_frontend_cfg& cfg, float alpha_u, int k) {
-    const double a = 1.0 - (double)alpha_u;
+// ---- per-utterance tables -----------------------------------------------------------------------------------
+
+// The projection is done by v_mfma_f32_4x4x1_16b_f32: sixteen independent products of a 4 x 1 with a 1 x 4
+// matrix, added to sixteen 4 x 4 accumulators.  The rows are the four frames of a wavefront, the columns four
+// consecutive mel channels (a "quad"); the sixteen blocks run through different stretches of bins.  The bins of
+// a quad are contiguous (five bands of them); they are cut into pieces of `steps` bins, a block each, in `rounds`
+// times sixteen pieces over all quads.  rounds and steps are chosen per utterance so that the number of
+// instructions is least: 24 for 40 channels, where a dense product would need 643.
+constexpr int kMaxRounds = 4;
+constexpr int kMaxQuads = AUG_MAX_MEL / 4;
+constexpr int kMaxSteps = 32;                // rounds x steps that the kernel has room for
+constexpr unsigned short kNoPiece = 0xffff;
+struct MelPlan {
+    unsigned char rounds, steps;             // steps: a multiple of 4; rounds = 0 if no plan within kMaxSteps exists
+    unsigned char first_piece[kMaxQuads + 6];     // of quad g; entry n_quads is the number of pieces
+    unsigned short piece[16 * kMaxRounds];   // first bin (a multiple of 4) | quad << 10, kNoPiece where unused
+};
+static_assert(sizeof(MelPlan) % sizeof(float2) == 0, "the plan follows the bins in an array of float2");
+constexpr int kPlanEntries = sizeof(MelPlan) / sizeof(float2);
+
+// Where Eq. (1) puts bin k on the mel scale: its band c and the weight w of filter c; band -1 below f_lo and
+// n_mel + 1 above f_hi.  `edges`: the n_mel + 2 band edges in Hz.
+__device__ inline int mel_band(const MelTableArgs& a, const double* edges, float alpha_u, int k, float& w) {
+    const double one_minus = 1.0 - (double)alpha_u;
     double sn, cs;
-    sincospi(2.0 * (double)k / (double)cfg.nfft, &sn, &cs);
-    const double omega = 2.0 * M_PI * (double)k / (double)cfg.nfft;
-    const double warped = omega + 2.0 * atan(a * sn / (1.0 - a * cs));          // Eq. (1)
-    const double f = warped * (double)cfg.fs / (2.0 * M_PI);
-    const double mel_lo = 2595.0 * log10(1.0 + (double)cfg.f_lo / 700.0);
-    const double mel_hi = 2595.0 * log10(1.0 + (double)cfg.f_hi / 700.0);
-    const double step = (mel_hi - mel_lo) / (double)(cfg.n_mel + 1);
-    const double mel = 2595.0 * log10(1.0 + f / 700.0);
-    float ch = -2.f, wgt = 0.f;
-    if (f >= (double)cfg.f_lo && f <= (double)cfg.f_hi) {
-        int c = (int)floor((mel - mel_lo) / step);
-        c = c < 0 ? 0 : (c > cfg.n_mel ? cfg.n_mel : c);
-        const double e0 = 700.0 * (pow(10.0, (mel_lo + c * step) / 2595.0) - 1.0);
-        const double e1 = 700.0 * (pow(10.0, (mel_lo + (c + 1) * step) / 2595.0) - 1.0);
-        double w = (f - e0) / (e1 - e0);
-        w = w < 0.0 ? 0.0 : (w > 1.0 ? 1.0 : w);
-        ch = (float)c;
-        wgt = (float)w;
-    }
-    return make_float2(ch, wgt);
+    sincospi(2.0 * (double)k / (double)a.cfg.nfft, &sn, &cs);
+    const double omega = 2.0 * M_PI * (double)k / (double)a.cfg.nfft;
+    const double warped = omega + 2.0 * atan(one_minus * sn / (1.0 - one_minus * cs));          // Eq. (1)
+    const double f = warped * (double)a.cfg.fs / (2.0 * M_PI);
+    w = 0.f;
+    if (f < (double)a.cfg.f_lo) return -1;
+    if (!(f <= (double)a.cfg.f_hi)) return a.cfg.n_mel + 1;
+    // the band from the logarithm in single precision, then by the edges themselves (a bin on an edge has weight 0
+    // in the band above it or 1 in the band below, which is the same)
+    int c = (int)((2595.f * 0.30102999566f * __log2f(1.f + (float)f * (1.f / 700.f)) - a.mel_lo) * a.inv_step);
+    c = c < 0 ? 0 : (c > a.cfg.n_mel ? a.cfg.n_mel : c);
+    while (c > 0 && f < edges[c]) --c;
+    while (c < a.cfg.n_mel && f >= edges[c + 1]) ++c;
+    const double x = (f - edges[c]) / (edges[c + 1] - edges[c]);
+    w = (float)(x < 0.0 ? 0.0 : (x > 1.0 ? 1.0 : x));
+    return c;
 }
 
-// Cut the bins of one utterance into 16 contiguous lane ranges that end on changes of the band
-// index c, so that every (c, utterance) sum is formed by one lane alone.  Range i ends at the band
-// change nearest to (i + 1) bins / 16; the ends are non-decreasing because the targets are.
-// One work group per utterance writes the utterance's table, then threads 0..14 each place one boundary.
-// An entry is a chain of double-precision library calls: with few utterances a group has a thread per bin
-// (K = 512) so that the chains run side by side, with many a single wavefront, which fills the chip anyway
-// and measured twice as fast there.
+// One work group per utterance.  An entry is a chain of double-precision library calls: with few utterances a group
+// has a thread per bin (K = 512) so that the chains run side by side, with many a single wavefront, which fills the
+// chip anyway.  The band edges come from the host (a power each: in this kernel they were two thirds of its time).
 constexpr int kMelTableThreads = 320;
-__global__ __launch_bounds__(kMelTableThreads) void mel_table_kernel(int n_utt, const float* __restrict__ alpha, aug_frontend_cfg cfg,
-                                                       int stride, float2* __restrict__ tab) {
-    __shared__ float band[2050];
-    const int bins = cfg.nfft / 2 + 1;
-    const int u = blockIdx.x;
-    float2* t = tab + (size_t)u * stride;
-    int* kstart = reinterpret_cast<int*>(tab + (size_t)u * stride + bins);
-    const float alpha_u = alpha[u];
-    for (int k = threadIdx.x; k < bins; k += (int)blockDim.x) {
-        const float2 e = mel_bin_entry(cfg, alpha_u, k);
-        t[k] = e;
-        band[k] = e.x;
+__global__ __launch_bounds__(kMelTableThreads) void mel_table_kernel(MelTableArgs a, int stride) {
+    __shared__ double edges[AUG_MAX_MEL + 2];
+    __shared__ short band[2050];
+    __shared__ int first_bin[AUG_MAX_MEL + 8];        // first bin of band c or higher
+    __shared__ MelPlan plan;
+    const int bins = a.cfg.nfft / 2 + 1, n_mel = a.cfg.n_mel, tid = threadIdx.x, threads = (int)blockDim.x;
+    float2* t = a.tab + (size_t)blockIdx.x * stride;
+    const float alpha_u = a.alpha[blockIdx.x];
+    for (int i = tid; i < n_mel + 2; i += threads) edges[i] = a.edges[i];
+    for (int i = tid; i < n_mel + 8; i += threads) first_bin[i] = bins;
+    for (int i = tid; i < 16 * kMaxRounds; i += threads) plan.piece[i] = kNoPiece;
+    __syncthreads();
+    for (int k = tid; k < bins; k += threads) {
+        float w;
+        const int c = mel_band(a, edges, alpha_u, k, w);
+        band[k] = (short)c;
+        t[k] = make_float2(c <= n_mel ? (float)c : -2.f, w);
     }
     __syncthreads();
-    const int lane = threadIdx.x;
-    if (lane == 0) { kstart[0] = 0; kstart[16] = bins; }
-    if (lane < 15) {
-        const int ideal = ((lane + 1) * bins + 8) / 16;
-        int end = bins;                               // no change found: everything up to the end
-        for (int d = 0; d < bins; ++d) {
-            const int lo = ideal - d, hi = ideal + d;
-            if (lo >= 1 && lo < bins && band[lo] != band[lo - 1]) { end = lo; break; }
-            if (hi >= 1 && hi < bins && band[hi] != band[hi - 1]) { end = hi; break; }
+    for (int k = tid; k < bins; k += threads)          // bands do not decrease with the bin
+        for (int c = (k ? (int)band[k - 1] : -1) + 1; c <= band[k]; ++c) first_bin[c] = k;
+    __syncthreads();
+    if (tid < 64) {
+        // a quad's stretch in units of four bins, on lane g
+        const int n_quads = (n_mel + 3) / 4, lane = tid;
+        int lo4 = 0, len4 = 0;
+        if (lane < n_quads) {
+            const int lo = first_bin[4 * lane], hi = first_bin[min(4 * lane + 5, n_mel + 1)];
+            lo4 = lo / 4;
+            len4 = hi > lo ? (hi + 3) / 4 - lo4 : 0;
         }
-        kstart[lane + 1] = end;
+        // lane i counts the pieces that steps = 4 (i + 1) would give
+        const float inv = 1.f / (float)(lane + 1);
+        int count = 0;
+        for (int g = 0; g < n_quads; ++g) count += (int)ceilf((float)__shfl(len4, g, 64) * inv - 1e-4f);
+        int best = 1 << 20, rounds = 0, steps4 = 1;
+        for (int r = 1; r <= kMaxRounds; ++r) {
+            const unsigned long long fits = __ballot(count <= 16 * r);
+            if (!fits) continue;
+            const int s4 = __ffsll((unsigned long long)fits);           // the smallest: lane + 1
+            // (a round's own cost: its stores, and more pieces to add up)
+            if (4 * r * s4 + 6 * r < best && 4 * r * s4 <= kMaxSteps) {
+                best = 4 * r * s4 + 6 * r;
+                rounds = r;
+                steps4 = s4;
+            }
+        }
+        const int mine = (len4 + steps4 - 1) / steps4;
+        int incl = mine;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int up = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += up;
+        }
+        if (lane <= n_quads) plan.first_piece[lane] = (unsigned char)(incl - mine);
+        if (rounds)
+            for (int i = 0; i < mine; ++i) plan.piece[incl - mine + i] = (unsigned short)(4 * (lo4 + i * steps4) | lane << 10);
+        if (lane == 0) {
+            plan.rounds = (unsigned char)rounds;
+            plan.steps = (unsigned char)(4 * steps4);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < kPlanEntries; i += threads) t[bins + i] = reinterpret_cast<const float2*>(&plan)[i];
+}
+
+// Constants of the sixteen lanes of a frame, [value][lane]: the second pass's twiddles exp(-2 pi i lane m / 256) and,
+// for k = lane + 16 i, tangent and cosine of the split's twiddle exp(-i pi k / 256).
+constexpr int kMelLanes = 16;                            // lanes per frame
+constexpr int kLanePairs = 8;
+constexpr int kMelTwFloats = 2 * kTw4Floats;
+constexpr int kLaneConsts = kMelTwFloats + 2 * kLanePairs;
+__global__ void mel_lane_kernel(float* out) {
+    const int lane = threadIdx.x % kMelLanes, part = threadIdx.x / kMelLanes;
+    if (part < 2) {                                      // the two factor sets of a Tw16Short
+        const double x = (double)lane / 128.0;
+        const Tw4 w = make_tw4(part == 0 ? 4.0 * x : x);
+        const float f[kTw4Floats] = {w.t1, w.t2, w.t3, w.c1, w.c2, w.r};
+        for (int i = 0; i < kTw4Floats; ++i) out[(part * kTw4Floats + i) * kMelLanes + lane] = f[i];
+    } else if (part < 2 + kLanePairs) {
+        const int i = part - 2;
+        double s, c;
+        sincospi(-(double)(lane + kMelLanes * i) / 256.0, &s, &c);
+        out[(kMelTwFloats + 2 * i) * kMelLanes + lane] = (float)(s / c);
+        out[(kMelTwFloats + 2 * i + 1) * kMelLanes + lane] = (float)c;
     }
 }
 
-constexpr int kMelLanes = 16;                            // lanes per frame
-constexpr int kProg = 32;                                // steps of a lane's band-sum list, at most
-constexpr int kProgStride = kProg + 1;                   // lists start four banks apart
-// A frame's transform buffer in LDS, in complex values: one more than the padded transform, so that the
-// frames of a wavefront start two banks apart.
-template <int NC> constexpr int mel_slot_stride() { return lds_padded_size(NC) + 1; }
+// ---- the front end ------------------------------------------------------------------------------------------
+
+// A frame's buffer in LDS, in floats: the transform's exchange (real parts, then imaginary parts: 16 rows of 17), then,
+// over it, the bin powers P[0..259] (three zeros behind the last bin), then the pieces' sums.  Frames of a
+// wavefront start sixteen banks apart: its 64 lanes then hit 64 banks in every access of the exchange.
+constexpr int kSlotFloats = 272;
+static_assert(kSlotFloats * 4 >= 64 * 4 * 4 && kSlotFloats >= 64 * kMaxRounds + 12 && kSlotFloats % 64 == 16, "frame buffer");
+constexpr int kBinsPadded = 260;
 constexpr int kMelSlots = kMelThreads / kMelLanes;       // frames in flight per work group
 
-// K = 512: 256-point complex FFT per frame, 16 lanes per frame, 16 frames per pass of the group.
-// WIN: the window length when it is known at compile time (the paper's front end uses 400), else 0.
 // two consecutive samples; only their 4-byte alignment is promised (global loads of two dwords need no more)
 struct __attribute__((aligned(4))) SamplePair { float x, y; };
+struct __attribute__((aligned(4))) SampleQuad { float x, y, z, w; };
+constexpr int kStageLoads = 4;                           // 16-byte loads per lane that stage four frames (1024 samples)
+constexpr int kAheadExtra = 3;                           // sources beside the first that are requested a pass ahead
+constexpr int kStagedHop = (64 * 4 * kStageLoads - 400) / 3;      // largest hop of a 400-sample window that they cover
 
 // e^power for e > 0 as exp2(power log2 e) on the hardware's base-2 logarithm and exponential (about one
 // unit in the last place each; the library's pow spends some 150 instructions on its last bit).  The
@@ -114,22 +190,54 @@ __device__ inline float power_law(float e, float power) {
     return __builtin_amdgcn_exp2f(power * l);
 }
 
-template <int NC, int WIN, bool MIX>
-__global__ __launch_bounds__(kMelThreads, 3) void mel_kernel(MelArgs a, const float2* __restrict__ tw, int tab_stride) {
-    static_assert(NC == 256 && NC / 16 == kMelLanes, "two radix-16 passes, sixteen lanes per frame");
+// the value that lane (16 - i) mod 16 of a row of sixteen lanes holds, for lane i: mirrored, then rotated by one
+__device__ inline float row_negate(float x) {
+    const int m = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xf, 0xf, false);         // row_mirror
+    return __int_as_float(__builtin_amdgcn_mov_dpp(m, 0x121, 0xf, 0xf, false));                // row_ror:1
+}
+
+typedef float vec4 __attribute__((ext_vector_type(4)));
+
+// 4-point DFT of windowed inputs x_m w_m, m < 4 (or 3): the window's factors ride on the additions
+template <bool FOUR>
+__device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2& a3, float2 w0, float2 w1, float2 w2, float2 w3) {
+    const float2 m0 = make_float2(a0.x * w0.x, a0.y * w0.y), m1 = make_float2(a1.x * w1.x, a1.y * w1.y);
+    const float2 s02 = make_float2(fmaf(a2.x, w2.x, m0.x), fmaf(a2.y, w2.y, m0.y));
+    const float2 d02 = make_float2(fmaf(-a2.x, w2.x, m0.x), fmaf(-a2.y, w2.y, m0.y));
+    const float2 s13 = FOUR ? make_float2(fmaf(a3.x, w3.x, m1.x), fmaf(a3.y, w3.y, m1.y)) : m1;
+    const float2 d13 = rot90<false>(FOUR ? make_float2(fmaf(-a3.x, w3.x, m1.x), fmaf(-a3.y, w3.y, m1.y)) : m1);
+    a0 = cadd(s02, s13);
+    a1 = cadd(d02, d13);
+    a2 = csub(s02, s13);
+    a3 = csub(d02, d13);
+}
+
+// K = 512: a 256-point complex FFT per frame, 16 lanes per frame, 16 frames per pass of the group.
+// WIN: the window length when it is known at compile time (the paper's front end uses 400), else 0.
+//
+// What bounds it: vector issue (about 650 vector instructions per pass of four frames, 0.97 of one in four cycles on
+// 4096 utterances of 8 s), with the LDS busy half the time.  The first design sent the second pass's outputs through
+// LDS to pair the bins and summed the bands from step lists there: 770 vector and 126 LDS instructions, a third
+// of the LDS's cycles bank conflicts.  Pairing by row permutations, twiddles folded into multiply-adds and the
+// projection on the matrix cores, which read every power once and need no vector arithmetic, took that batch from
+// 1500 to 1080-1140 us; cepstra from a cosine table in LDS instead of global memory, 256 padded utterances from 350
+// to 134 us.  (The first radix-16 pass on the matrix cores as well measured slower, 1350 us: products of 32-bit
+// floats there take the vector units' time.)
+template <int WIN, bool MIX>
+__global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(MelArgs a, int tab_stride) {
+    constexpr int NC = 256;
     extern __shared__ __align__(16) unsigned char smem[];
     const int n_mel = a.cfg.n_mel;
     const int feature = a.cfg.feature;
     const int n_out = feature == AUG_FEAT_MFCC ? a.cfg.n_ceps : n_mel;     // values per output row
-    const int n_seg = n_mel + 3;                         // band sums (A, B)[c + 1] for c = -1..n_mel (+1 pad)
-    float2* fft_buf = reinterpret_cast<float2*>(smem);                       // [slots][mel_slot_stride]
-    float4* s_prog = reinterpret_cast<float4*>(fft_buf + kMelSlots * mel_slot_stride<NC>());   // [16][kProgStride]
-    float2* s_tab = reinterpret_cast<float2*>(s_prog + kMelLanes * kProgStride);   // [NC + 1]: (c, w) per bin
-    float2* s_tw = s_tab + (NC + 1);                                         // [NC + 1]: exp(-i pi k / NC)
-    float2* s_ab = s_tw + (NC + 1);                                          // [slots][n_seg]
-    int* s_kstart = reinterpret_cast<int*>(s_ab + kMelSlots * n_seg);        // [17]
+    float* const slots = reinterpret_cast<float*>(smem);                     // [kMelSlots][kSlotFloats]
+    vec4* const s_weight = reinterpret_cast<vec4*>(slots + kMelSlots * kSlotFloats);       // [kMaxSteps / 4][64]
+    int2* const s_pieces = reinterpret_cast<int2*>(s_weight + kMaxSteps / 4 * 64);          // [n_mel]: a channel's sums
+    float2* const s_pair = reinterpret_cast<float2*>(s_pieces + AUG_MAX_MEL);               // [kLanePairs][kMelLanes]
+    float2* const s_window = s_pair + kLanePairs * kMelLanes;                               // [256]
+    vec4* const s_dct = reinterpret_cast<vec4*>(s_window + NC);                             // [n_mel / 4][n_out up to 16s]
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int slot = tid / kMelLanes, sub = tid % kMelLanes;
     // Group ids are dealt round-robin to the eight XCDs.  XCD x takes the x-th contiguous eighth of the item
     // list, so that every XCD gets the same mix of full and nearly empty groups whatever the period of the
@@ -153,243 +261,367 @@ __global__ __launch_bounds__(kMelThreads, 3) void mel_kernel(MelArgs a, const fl
     const int first = (a.items[item].y / a.frames_per_group) * rows_per_group;
     const float power = a.cfg.power;
     float* feats = a.feats + (size_t)a.frame_offsets[u] * n_out;
-    float2* buf = fft_buf + slot * mel_slot_stride<NC>();
-    float* pw = reinterpret_cast<float*>(buf);           // the frame's bin powers P[0..NC], once they are formed
-    float2* AB = s_ab + slot * n_seg;                    // (A, B)[c + 1]; entry 0 takes what belongs to no band
+    float* const buf = slots + slot * kSlotFloats;       // the frame's buffer
+    float* const wave_buf = slots + (slot & ~3) * kSlotFloats;     // the four frames of this wavefront
 
+    // the utterance's tables: the plan, and from it the weights in the order in which the lanes use them
     const float2* g_tab = a.mel_tab + (size_t)u * tab_stride;
-    for (int k = tid; k <= NC; k += kMelThreads) {
-        s_tab[k] = g_tab[k];
-        s_tw[k] = k <= NC / 2 ? tw[NC + k] : make_float2(-tw[NC + (NC - k)].x, tw[NC + (NC - k)].y);
-    }
-    if (tid < 17) s_kstart[tid] = reinterpret_cast<const int*>(g_tab + (NC + 1))[tid];
-
-    // this lane's window samples never change: z[n] = w[2n] x[2n] + i w[2n+1] x[2n+1], n = sub + 16 m
-    float2 wnd[16];
+    const MelPlan* plan = reinterpret_cast<const MelPlan*>(g_tab + (NC + 1));
+    const int rounds = plan->rounds, steps = plan->steps;
+    for (int e = tid; e < rounds * (steps / 4) * 64; e += kMelThreads) {
+        const int l = e & 63, q = e >> 6, r = q / (steps / 4), s0 = 4 * (q - r * (steps / 4));
+        const int piece = plan->piece[16 * r + (l >> 2)];
+        vec4 w = {0.f, 0.f, 0.f, 0.f};
+        if (piece != kNoPiece) {
+            const int begin = piece & 1023, m = 4 * (piece >> 10) + (l & 3);
+            const int k0 = min(begin, kBinsPadded - steps) + s0;             // (a piece at the end starts earlier, to stay inside)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int i0 = 2 * (sub + kMelLanes * i);
-        wnd[i] = make_float2(i0 < win ? a.window[i0] : 0.f, i0 + 1 < win ? a.window[i0 + 1] : 0.f);
-    }
-    // twiddles of the second pass, exp(-2 pi i sub m / NC), are the same for every frame of this lane
-    float2 twp[16];
-#pragma unroll
-    for (int m = 1; m < 16; ++m) twp[m] = tw[(sub * m) & (NC - 1)];
-    __syncthreads();
-    const int k_lo = s_kstart[sub], k_hi = s_kstart[sub + 1];
-    // Each lane sums the bins of its own bands by a fixed list of steps, one per bin, that is the same for
-    // every frame of the utterance: (keep, w, 1 - w, where the running sums go).  keep is 0 where a new band
-    // begins, else 1.  The running sums are stored after every bin, so a band's entry ends up holding its
-    // whole sum without any test on the way.  Lists are padded to a common length (a multiple of four,
-    // the same for all lanes) by steps that add nothing; with more than kProg bins in one lane's range
-    // (very wide bands) the plain loop further down is used instead.
-    int n_steps = 0;
-#pragma unroll
-    for (int l = 0; l < kMelLanes; ++l) n_steps = max(n_steps, s_kstart[l + 1] - s_kstart[l]);
-    n_steps = (n_steps + 3) & ~3;
-    const bool listed = n_steps <= kProg;
-    if (listed) {
-        for (int e = tid; e < kMelLanes * kProg; e += kMelThreads) {
-            const int l = e / kProg, i = e - l * kProg;
-            const int lo = s_kstart[l], k = lo + i;
-            float4 step = make_float4(1.f, 0.f, 0.f, __int_as_float(0));      // adds nothing, stores to entry 0
-            if (k < s_kstart[l + 1]) {
-                const float2 cw = s_tab[k];
-                const int c = (int)cw.x;
-                const bool same = i > 0 && (int)s_tab[k - 1].x == c;
-                if (c >= 0) step = make_float4(same ? 1.f : 0.f, cw.y, 1.f - cw.y, __int_as_float(8 * (c + 1)));
-                else step.x = same ? 1.f : 0.f;
+            for (int i = 0; i < 4; ++i) {
+                const int k = k0 + i;
+                if (k >= begin && k <= NC) {
+                    const float2 cw = g_tab[k];
+                    const int c = (int)cw.x;
+                    w[i] = c == m ? cw.y : (c == m + 1 ? 1.f - cw.y : 0.f);
+                }
             }
-            s_prog[l * kProgStride + i] = step;
         }
-        __syncthreads();
+        s_weight[q * 64 + l] = w;
     }
-    // Band sums are stored, never added to: an entry that some bin's band owns is rewritten for every frame,
-    // and the others (bands without a bin, the padding) keep the zero they get here.
-    for (int m = sub; m < n_seg; m += kMelLanes) AB[m] = make_float2(0.f, 0.f);
-    const bool even_win = (win & 1) == 0;
+    for (int m = tid; m < n_mel; m += kMelThreads) {
+        const int p0 = plan->first_piece[m / 4], p1 = plan->first_piece[m / 4 + 1];
+        s_pieces[m] = make_int2(4 * p0 + (m & 3), p1 - p0);
+    }
+    const int q_pad = (n_out + kMelLanes - 1) & ~(kMelLanes - 1);
+    if (feature == AUG_FEAT_MFCC) {                       // cosine rows by fours of channels, zero past the last
+        for (int e = tid; e < (n_mel + 3) / 4 * q_pad; e += kMelThreads) {
+            const int m4 = e / q_pad, q = e - m4 * q_pad;
+            vec4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (q < n_out && 4 * m4 + i < n_mel) d[i] = a.dct[q * n_mel + 4 * m4 + i];
+            s_dct[e] = d;
+        }
+    }
+    // where this lane's block starts to read powers, per round
+    int at[kMaxRounds];
+#pragma unroll
+    for (int r = 0; r < kMaxRounds; ++r) {
+        const int piece = r < rounds ? plan->piece[16 * r + (lane >> 2)] : kNoPiece;
+        at[r] = (lane & 3) * kSlotFloats + (piece == kNoPiece ? 0 : min(piece & 1023, kBinsPadded - steps));
+    }
+
+    // Window samples, z[n] = w[2n] x[2n] + i w[2n+1] x[2n+1], halved: the even/odd split below then needs no halves of
+    // its own.  Lane sub takes n = sub + 16 m.
+    constexpr int kRows = WIN ? (WIN + 2 * kMelLanes - 1) / (2 * kMelLanes) : 16;     // rows m with any sample in the window
+    static_assert(kRows == 16 || kRows == 13, "the first butterflies are written for 13 or 16 rows");
+    s_window[tid] = make_float2(2 * tid < win ? 0.5f * a.window[2 * tid] : 0.f, 2 * tid + 1 < win ? 0.5f * a.window[2 * tid + 1] : 0.f);
+    Tw16Short tw;
+    {
+        float f[2 * kTw4Floats];
+#pragma unroll
+        for (int i = 0; i < 2 * kTw4Floats; ++i) f[i] = a.lane_consts[i * kMelLanes + sub];
+        tw.outer = Tw4{f[0], f[1], f[2], f[3], f[4], f[5]};
+        tw.inner = Tw4{f[6], f[7], f[8], f[9], f[10], f[11]};
+    }
+    // The window and the tangents and cosines of the split's twiddles are read from LDS where they are used: in registers
+    // they would cost a wavefront per SIMD, and a wavefront alone issues a vector instruction only every six cycles
+    // where the SIMD could take one every two.
+    if (tid < kLanePairs * kMelLanes) {
+        const int i = tid / kMelLanes, l = tid % kMelLanes;
+        s_pair[tid] = make_float2(a.lane_consts[(kMelTwFloats + 2 * i) * kMelLanes + l], a.lane_consts[(kMelTwFloats + 2 * i + 1) * kMelLanes + l]);
+    }
+    __syncthreads();
+
+    [[maybe_unused]] const bool even_win = (win & 1) == 0;
     const float* extra = MIX ? a.extra + start : nullptr;
     const float* gains = MIX ? a.gains + (size_t)u * a.n_extra : nullptr;
 
-    for (int it = 0; it < rows_per_group / kMelSlots; ++it) {
+    // With a mixture (and the paper's window) the samples of a wavefront's four frames, which overlap, are staged: 16 bytes
+    // per lane and load, each sample of each source once, mixed while still in registers, into the frames' buffers and
+    // from there into the butterflies.  They are requested a pass ahead, when the registers of the transform are free.  What lies past the
+    // utterance's end is not read: frames that do not exist compute something, and it is dropped.
+    constexpr bool STAGED = WIN == 400 && MIX;
+    constexpr int kMore = MIX ? kAheadExtra : 0;
+    const int staged = STAGED ? (3 * hop + 400 + 3) & ~3 : 0;
+    const int wave_first = __builtin_amdgcn_readfirstlane(first + (slot & ~3));
+    // where this lane's i-th four samples lie among those of the frames t_wave .. t_wave + 3 (the last four that exist, if
+    // there are no more)
+    auto limit = [&](int t_wave) { return (int)min((int64_t)staged, len - (int64_t)t_wave * hop) - 4; };
+    auto place = [&](int i, int most) { return min(4 * lane + 256 * i, most); };
+    auto load = [&](SampleQuad (&q)[kStageLoads], const float* src, int t_wave) {
+        const char* base = reinterpret_cast<const char*>(src + (int64_t)t_wave * hop);
+        const int most = limit(t_wave);
+#pragma unroll
+        for (int i = 0; i < kStageLoads; ++i) q[i] = *reinterpret_cast<const SampleQuad*>(base + 4u * (uint32_t)place(i, most));
+    };
+    SampleQuad ahead[kStageLoads], more[kMore ? kMore : 1][kStageLoads];
+    // (every register is assigned on every path, so that none is kept for its old value)
+    auto request = [&](int t_wave) {
+        const bool any = t_wave < n_frames_u;
+        if (any) {
+            load(ahead, x, t_wave);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kStageLoads; ++i) ahead[i] = SampleQuad{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int j = 0; j < kMore; ++j) {
+            if (any && j < a.n_extra) {
+                load(more[j], extra + (size_t)j * a.extra_stride, t_wave);
+            } else {
+#pragma unroll
+                for (int i = 0; i < kStageLoads; ++i) more[j][i] = SampleQuad{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
+    if (STAGED) request(wave_first);
+
+    const int passes = rows_per_group / kMelSlots;
+    for (int it = 0; it < passes; ++it) {
         const int64_t t = (int64_t)first + it * kMelSlots + slot;
-        if ((int64_t)first + it * kMelSlots >= n_frames_u) {      // only padding rows are left in this group
+        const int t_wave = wave_first + it * kMelSlots;
+        if (t_wave >= n_frames_u) {                       // only padding rows are left for this wavefront
             if (t < rows_u)
                 for (int m = sub; m < n_out; m += kMelLanes) feats[t * n_out + m] = 0.f;
             continue;
         }
         const bool live = t < n_frames_u;
         float2 v[16];
-        // Loads are unconditional: a slot past the utterance's last frame recomputes that last frame (its
-        // result is dropped) and inputs past the window are read from the frame's last samples and meet a
-        // zero window weight.  With MIX the analysed signal is formed here, in source order:
-        // x + sum_j gains[j] extra_j.
-        const int x0 = (int)(live ? t : n_frames_u - 1) * hop;
-        if (even_win) {                                   // one 8-byte load per complex input
+        // With MIX the analysed signal is formed here, in source order: x + sum_j gains[j] extra_j.
+        if constexpr (STAGED) {
+            auto add = [&](const SampleQuad (&e)[kStageLoads], float gain) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int i0 = min(2 * (sub + kMelLanes * i), win - 2);
-                const SamplePair s2 = *reinterpret_cast<const SamplePair*>(x + (x0 + i0));
-                v[i] = make_float2(s2.x, s2.y);
+                for (int i = 0; i < kStageLoads; ++i) {
+                    ahead[i].x += gain * e[i].x;
+                    ahead[i].y += gain * e[i].y;
+                    ahead[i].z += gain * e[i].z;
+                    ahead[i].w += gain * e[i].w;
+                }
+            };
+#pragma unroll
+            for (int j = 0; j < kMore; ++j)
+                if (j < a.n_extra) add(more[j], gains[j]);
+            const int most = limit(t_wave);
+            if (MIX)
+                for (int j = kMore; j < a.n_extra; ++j) {
+                    load(more[0], extra + (size_t)j * a.extra_stride, t_wave);
+                    add(more[0], gains[j]);
+                }
+#pragma unroll
+            for (int i = 0; i < kStageLoads; ++i) {
+                float* to = wave_buf + place(i, most);
+                if (most == staged - 4) *reinterpret_cast<vec4*>(to) = vec4{ahead[i].x, ahead[i].y, ahead[i].z, ahead[i].w};
+                else *reinterpret_cast<SampleQuad*>(to) = ahead[i];
             }
-            if (MIX) {
-                for (int j = 0; j < a.n_extra; ++j) {
-                    const float g = gains[j];
-                    const float* xj = extra + (size_t)j * a.extra_stride;
-                    // all sixteen loads of a source are issued before the first of them is used (the
-                    // scheduler may otherwise pair every load with its wait to save registers)
-                    SamplePair s2[16];
+            fft_sync<FftSync::Wave>();
+            const float2* mine = reinterpret_cast<const float2*>(wave_buf + (slot & 3) * hop);      // (the hop is even)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int i0 = min(2 * (sub + kMelLanes * i), win - 2);
-                        s2[i] = *reinterpret_cast<const SamplePair*>(xj + (x0 + i0));
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+            for (int i = 0; i < kRows; ++i) v[i] = mine[min(sub + kMelLanes * i, WIN / 2 - 1)];    // (past the window: times zero)
+            fft_sync<FftSync::Wave>();
+        } else {
+            // Loads are unconditional: a slot past the utterance's last frame recomputes that last frame (its
+            // result is dropped) and inputs past the window are read from the frame's last samples and meet a
+            // zero window weight.
+            const int x0 = (int)(live ? t : n_frames_u - 1) * hop;
+            // (opaque in the general kernel, whose clamped positions would otherwise all be kept in registers)
+            int at_sub = sub;
+            if (!WIN) asm volatile("" : "+v"(at_sub));
+            if (even_win) {                                   // one 8-byte load per complex input
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        v[i].x += g * s2[i].x;
-                        v[i].y += g * s2[i].y;
+                for (int i = 0; i < kRows; ++i) {
+                    const int i0 = min(2 * (at_sub + kMelLanes * i), win - 2);
+                    const SamplePair s2 = *reinterpret_cast<const SamplePair*>(x + (x0 + i0));
+                    v[i] = make_float2(s2.x, s2.y);
+                }
+                if (MIX) {
+                    for (int j = 0; j < a.n_extra; ++j) {
+                        const float g = gains[j];
+                        const float* xj = extra + (size_t)j * a.extra_stride;
+                        // all loads of a source are issued before the first of them is used (the
+                        // scheduler may otherwise pair every load with its wait to save registers)
+                        SamplePair s2[kRows];
+#pragma unroll
+                        for (int i = 0; i < kRows; ++i) {
+                            const int i0 = min(2 * (at_sub + kMelLanes * i), win - 2);
+                            s2[i] = *reinterpret_cast<const SamplePair*>(xj + (x0 + i0));
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int i = 0; i < kRows; ++i) {
+                            v[i].x += g * s2[i].x;
+                            v[i].y += g * s2[i].y;
+                        }
                     }
                 }
-            }
-        } else {
+            } else {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int i0 = 2 * (sub + kMelLanes * i);
-                v[i] = make_float2(x[x0 + min(i0, win - 1)], x[x0 + min(i0 + 1, win - 1)]);
-            }
-            if (MIX) {
-                for (int j = 0; j < a.n_extra; ++j) {
-                    const float g = gains[j];
-                    const float* xj = extra + (size_t)j * a.extra_stride;
+                for (int i = 0; i < kRows; ++i) {
+                    const int i0 = 2 * (at_sub + kMelLanes * i);
+                    v[i] = make_float2(x[x0 + min(i0, win - 1)], x[x0 + min(i0 + 1, win - 1)]);
+                }
+                if (MIX) {
+                    for (int j = 0; j < a.n_extra; ++j) {
+                        const float g = gains[j];
+                        const float* xj = extra + (size_t)j * a.extra_stride;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int i0 = 2 * (sub + kMelLanes * i);
-                        v[i].x += g * xj[x0 + min(i0, win - 1)];
-                        v[i].y += g * xj[x0 + min(i0 + 1, win - 1)];
+                        for (int i = 0; i < kRows; ++i) {
+                            const int i0 = 2 * (at_sub + kMelLanes * i);
+                            v[i].x += g * xj[x0 + min(i0, win - 1)];
+                            v[i].y += g * xj[x0 + min(i0 + 1, win - 1)];
+                        }
                     }
                 }
             }
         }
+        // 256 = 16 x 16: first pass without twiddles (inputs past the window are zero), exchange through LDS,
+        // second pass with this lane's fixed twiddles
+        float2 wnd[kRows];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = make_float2(v[i].x * wnd[i].x, v[i].y * wnd[i].y);
-        // 256 = 16 x 16: first pass without twiddles (inputs past the window are zero and fold away when
-        // WIN is known), exchange through LDS, second pass with this lane's fixed twiddles
-        SmallDft<16, false>::run(v);
-        fft_store<NC, kMelLanes, 16, 1>(v, buf, sub);
-        fft_sync<FftSync::Wave>();
-        fft_load<NC, kMelLanes, 16>(v, buf, sub);
-        fft_sync<FftSync::Wave>();
+        for (int m = 0; m < kRows; ++m) wnd[m] = s_window[sub + kMelLanes * m];
+        if constexpr (kRows == 16) {
 #pragma unroll
-        for (int m = 1; m < 16; ++m) v[m] = cmul(v[m], twp[m]);
-        SmallDft<16, false>::run(v);
-        fft_store_natural<NC, kMelLanes>(v, buf, sub);
-        fft_sync<FftSync::Wave>();                       // a frame's 16 lanes share a wavefront
+            for (int m = 0; m < 4; ++m)
+                dft4_windowed<true>(v[m], v[m + 4], v[m + 8], v[m + 12], wnd[m], wnd[m + 4], wnd[m + 8], wnd[m + 12]);
+        } else {
+            dft4_windowed<true>(v[0], v[4], v[8], v[12], wnd[0], wnd[4], wnd[8], wnd[12]);
+#pragma unroll
+            for (int m = 1; m < 4; ++m)
+                dft4_windowed<false>(v[m], v[m + 4], v[m + 8], v[m + 12], wnd[m], wnd[m + 4], wnd[m + 8], wnd[m + 8]);
+        }
+        dft16_inner<false, false>(v, 1.f, 1.f, 1.f);
+        dft16_transpose(v);
+        {
+            // lane sub's outputs are elements 16 sub + r, its next inputs sub + 16 m; element i lives at i + i / 16
+            float* const to = buf + 17 * sub;
+            const float* const from = buf + sub;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) to[r] = v[r].x;
+            fft_sync<FftSync::Wave>();                   // a frame's 16 lanes share a wavefront
+#pragma unroll
+            for (int m = 0; m < 16; ++m) v[m].x = from[17 * m];
+            fft_sync<FftSync::Wave>();
+#pragma unroll
+            for (int r = 0; r < 16; ++r) to[r] = v[r].y;
+            fft_sync<FftSync::Wave>();
+#pragma unroll
+            for (int m = 0; m < 16; ++m) v[m].y = from[17 * m];
+            fft_sync<FftSync::Wave>();
+        }
+        dft16_twiddled<false>(v, tw);
 
-        // Bin powers, two at a time: with E = (Z[k] + conj Z[N-k])/2, O = -(i/2)(Z[k] - conj Z[N-k]) and
-        // w = exp(-i pi k / N):  X[k] = E + w O and conj(X[N-k]) = E - w O.
-        // The powers go back into the frame's buffer as a plain array P[0..N] of floats, so every lane reads
-        // all its bins before any lane writes.
-        constexpr int kPairs = NC / 2 / kMelLanes + 1;    // the last one (bin N/2) only for lane 0
-        float p_lo[kPairs], p_hi[kPairs];
+        // v[i] = Z[k], k = sub + 16 i.  Bin powers, two at a time: with A = Z[k], B = conj Z[N-k] (halved inputs),
+        // E = A + B, O = -i (A - B) and w = exp(-i pi k / N):  X[k] = E + w O and conj(X[N-k]) = E - w O.  Z[N-k] is
+        // v[15 - i] of lane 16 - sub (lane 0 finds its own in v[16 - i]).
 #pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-            const int k = min(sub + kMelLanes * i, NC / 2);   // 0..N/2 (lanes past it repeat bin N/2, unused)
-            const int kn = (NC - k) & (NC - 1);
-            const float2 Zk = buf[lds_pad(k)];
-            const float2 Zn = buf[lds_pad(kn)];
-            const float2 w = s_tw[k];
-            const float2 E = make_float2(0.5f * (Zk.x + Zn.x), 0.5f * (Zk.y - Zn.y));
-            const float2 O = make_float2(0.5f * (Zk.y + Zn.y), -0.5f * (Zk.x - Zn.x));
-            const float2 wO = cmul(w, O);
+        for (int i = 0; i < kLanePairs; ++i) {
+            const float2 other = sub == 0 ? v[(16 - i) & 15] : v[15 - i];
+            const float2 B = make_float2(row_negate(other.x), -row_negate(other.y));
+            const float2 E = cadd(v[i], B), d = csub(v[i], B);
+            const float2 tc = s_pair[i * kMelLanes + sub];
+            const float2 wO = tilt<false>(make_float2(d.y, -d.x), tc.x);                 // awaits the cosine
             // sums first, then squares: a weak bin next to a strong mirror bin keeps its relative accuracy
-            const float2 Xk = cadd(E, wO), Xn = csub(E, wO);
-            p_lo[i] = Xk.x * Xk.x + Xk.y * Xk.y;
-            p_hi[i] = Xn.x * Xn.x + Xn.y * Xn.y;
+            const float2 Xk = cfma(tc.y, wO, E), Xn = cfma(-tc.y, wO, E);
+            buf[sub + kMelLanes * i] = fmaf(Xk.x, Xk.x, Xk.y * Xk.y);
+            buf[NC - (sub + kMelLanes * i)] = fmaf(Xn.x, Xn.x, Xn.y * Xn.y);             // k = 0: P[N] (from Z[0] too)
         }
-        fft_sync<FftSync::Wave>();
-#pragma unroll
-        for (int i = 0; i < kPairs; ++i) {
-            if (i == kPairs - 1 && sub != 0) break;
-            const int k = sub + kMelLanes * i;
-            pw[k] = p_lo[i];
-            pw[NC - k] = p_hi[i];                         // k = 0: P[N] (it comes from Z[0] too); k = N/2: itself
-        }
+        // bin N/2 is its own partner; the three places behind bin N meet zero weights and must be finite
+        if (sub < 4) buf[sub == 0 ? NC / 2 : NC + sub] = sub == 0 ? 4.f * fmaf(v[8].x, v[8].x, v[8].y * v[8].y) : 0.f;
+        if (STAGED) request(it + 1 < passes ? t_wave + kMelSlots : 0x7fffffff);
         fft_sync<FftSync::Wave>();
 
-        // bins [k_lo, k_hi) -> per-band sums; this lane owns every band it meets
-        if (listed) {
-            const float4* step = s_prog + sub * kProgStride;
-            const float* p = pw + k_lo;
-            char* dst = reinterpret_cast<char*>(AB);
-            float run_a = 0.f, run_b = 0.f;
-            for (int i = 0; i < n_steps; i += 4) {
-                float4 s4[4];
-                float pk[4];
+        // pieces of the projection: row i of a block is frame i of the wavefront, column j channel 4 quad + j
+        if (rounds) {
+            vec4 sums[kMaxRounds];
+            const vec4* wq = s_weight + lane;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {             // all reads of the four steps before their stores
-                    s4[j] = step[i + j];
-                    pk[j] = p[i + j];                     // (past k_hi: some finite value, times zero)
-                }
+            for (int r = 0; r < kMaxRounds; ++r) {
+                if (r >= rounds) break;
+                const vec4* pq = reinterpret_cast<const vec4*>(wave_buf + at[r]);
+                vec4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    run_a = fmaf(s4[j].y, pk[j], run_a * s4[j].x);
-                    run_b = fmaf(s4[j].z, pk[j], run_b * s4[j].x);
-                    *reinterpret_cast<float2*>(dst + __float_as_int(s4[j].w)) = make_float2(run_a, run_b);
+                for (int q = 0; q < kMaxSteps / 4; ++q) {
+                    if (4 * q >= steps) break;
+                    const vec4 p = pq[q], w = wq[64 * q];
+                    acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[0], w[0], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[1], w[1], acc1, 0, 0, 0);
+                    acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[2], w[2], acc0, 0, 0, 0);
+                    acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[3], w[3], acc1, 0, 0, 0);
                 }
+                wq += 64 * (steps / 4);
+                sums[r] = acc0 + acc1;
             }
-        } else {
-            float run_a = 0.f, run_b = 0.f;
-            int cur = -100;
-            for (int k = k_lo; k < k_hi; ++k) {
-                const float pk = pw[k];
-                const float2 cw = s_tab[k];
-                const int c = (int)cw.x;
-                if (c != cur) {
-                    if (cur >= 0) AB[cur + 1] = make_float2(run_a, run_b);
-                    cur = c;
-                    run_a = 0.f;
-                    run_b = 0.f;
-                }
-                run_a += cw.y * pk;
-                run_b += (1.f - cw.y) * pk;
+            fft_sync<FftSync::Wave>();                   // the powers are read before the sums take their place
+#pragma unroll
+            for (int r = 0; r < kMaxRounds; ++r) {
+                if (r >= rounds) break;
+                float* to = wave_buf + 64 * r + lane;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) to[i * kSlotFloats] = sums[r][i];
             }
-            if (cur >= 0) AB[cur + 1] = make_float2(run_a, run_b);
+            fft_sync<FftSync::Wave>();
         }
-        fft_sync<FftSync::Wave>();
-
-        // channel m collects the rising side of band m and the falling side of band m + 1
-        if (feature == AUG_FEAT_POWER_LAW) {
-            if (live) {
-                for (int m = sub; m < n_mel; m += kMelLanes) {
-                    const float e = AB[m + 1].x + AB[m + 2].y;
-                    feats[t * n_mel + m] = e > 0.f ? power_law(e, power) : 0.f;
+        // energy of channel m: the sum of its pieces.  (Without a plan, for warps that do not keep the bins in
+        // order, a plain sum over all bins.)
+        auto energy = [&](int m) {
+            float e = 0.f;
+            if (rounds) {
+                // (the first four at once, the few pieces of a wider quad after them; what lies behind a quad's
+                // last piece is read and dropped)
+                const int2 pc = s_pieces[m];
+                const float* from = buf + pc.x;
+                const float e0 = from[0], e1 = from[4], e2 = from[8], e3 = from[12];
+                e = ((pc.y > 0 ? e0 : 0.f) + (pc.y > 1 ? e1 : 0.f)) + ((pc.y > 2 ? e2 : 0.f) + (pc.y > 3 ? e3 : 0.f));
+                for (int i = 4; i < pc.y; ++i) e += from[4 * i];
+            } else {
+                for (int k = 0; k <= NC; ++k) {
+                    const float2 cw = g_tab[k];
+                    if ((int)cw.x == m) e = fmaf(cw.y, buf[k], e);
+                    else if ((int)cw.x == m + 1) e = fmaf(1.f - cw.y, buf[k], e);
                 }
             }
-        } else {
-            // log-mel; for cepstra the log energies go to the front of the frame's buffer (the bin powers are
-            // no longer needed), then every lane takes the dot products of its coefficients with the whole vector
-            for (int m = sub; m < n_mel; m += kMelLanes) {
-                const float le = logf(fmaxf(AB[m + 1].x + AB[m + 2].y, a.cfg.log_floor));
-                if (feature == AUG_FEAT_LOG) {
-                    if (live) feats[t * n_mel + m] = le;
+            return e;
+        };
+        // For cepstra the log energies go over the sums: channel m at place m, which is at or before its own sums, so
+        // what a later channel still has to read is not overwritten.
+        const bool to_lds = feature == AUG_FEAT_MFCC && rounds;
+        const int m_end = to_lds ? (n_mel + 3) & ~3 : feature == AUG_FEAT_MFCC ? 0 : n_mel;
+#pragma unroll 1
+        for (int m = sub; m < m_end; m += kMelLanes) {
+            const float e = m < n_mel ? energy(m) : 0.f;
+            if (feature == AUG_FEAT_POWER_LAW) {
+                if (live) feats[t * n_mel + m] = e > 0.f ? power_law(e, power) : 0.f;
+            } else {
+                const float le = m < n_mel ? logf(fmaxf(e, a.cfg.log_floor)) : 0.f;
+                if (to_lds) {
+                    fft_sync<FftSync::Wave>();
+                    buf[m] = le;
+                } else if (live) {
+                    feats[t * n_mel + m] = le;
+                }
+            }
+        }
+        if (feature == AUG_FEAT_MFCC) {
+            // every lane takes the dot products of its coefficients with the whole vector, four channels at a time
+            fft_sync<FftSync::Wave>();
+            const vec4* lq = reinterpret_cast<const vec4*>(buf);
+#pragma unroll 1
+            for (int q = sub; q < q_pad; q += kMelLanes) {
+                vec4 acc = {0.f, 0.f, 0.f, 0.f};
+                if (to_lds) {
+                    for (int m4 = 0; m4 < m_end / 4; ++m4) {
+                        const vec4 l = lq[m4], d = s_dct[m4 * q_pad + q];
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[i] = fmaf(l[i], d[i], acc[i]);
+                    }
                 } else {
-                    pw[m] = le;
+                    for (int m = 0; m < n_mel; ++m) acc[0] = fmaf(logf(fmaxf(energy(m), a.cfg.log_floor)), s_dct[(m / 4) * q_pad + q][m & 3], acc[0]);
                 }
-            }
-            if (feature == AUG_FEAT_MFCC) {
-                fft_sync<FftSync::Wave>();
-                for (int q = sub; q < n_out; q += kMelLanes) {
-                    const float* row = a.dct + q * n_mel;
-                    float acc = 0.f;
-                    for (int m = 0; m < n_mel; ++m) acc += row[m] * pw[m];
-                    if (live) feats[t * n_out + q] = acc;
-                }
+                if (live && q < n_out) feats[t * n_out + q] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
         }
         if (!live && t < rows_u)
             for (int m = sub; m < n_out; m += kMelLanes) feats[t * n_out + m] = 0.f;
-        fft_sync<FftSync::Wave>();                       // sums are read before the next frame clears them
+        fft_sync<FftSync::Wave>();                       // everything is read before the next frame's exchange
     }
 }
 
@@ -411,19 +643,34 @@ hipError_t launch_dct_table(hipStream_t s, int n_ceps, int n_mel, float* dct) {
 }
 
 int mel_frames_per_group() { return kFramesPerGroup; }
+int mel_lane_floats() { return kLaneConsts * kMelLanes; }
+
+hipError_t launch_mel_lanes(hipStream_t s, float* lane_consts) {
+    mel_lane_kernel<<<dim3(1), dim3(256), 0, s>>>(lane_consts);
+    return hipGetLastError();
+}
 
 hipError_t launch_window(hipStream_t s, int win, float* w) {
     window_kernel<<<dim3((win + 255) / 256), dim3(256), 0, s>>>(win, w);
     return hipGetLastError();
 }
 
-int mel_table_stride(int nfft) { return nfft / 2 + 1 + 9; }   // (c, w) per bin, then 17 lane starts (+ pad)
+int mel_table_stride(int nfft) { return nfft / 2 + 1 + kPlanEntries; }   // (c, w) per bin, then the plan
 
-hipError_t launch_mel_table(hipStream_t s, int n_utt, const float* alpha, const aug_frontend_cfg& cfg,
-                            float2* tab) {
+void mel_edges(const aug_frontend_cfg& cfg, MelTableArgs& a) {
+    const double mel_lo = 2595.0 * log10(1.0 + (double)cfg.f_lo / 700.0);
+    const double mel_hi = 2595.0 * log10(1.0 + (double)cfg.f_hi / 700.0);
+    const double step = (mel_hi - mel_lo) / (double)(cfg.n_mel + 1);
+    for (int c = 0; c < cfg.n_mel + 2; ++c) a.edges[c] = 700.0 * (pow(10.0, (mel_lo + c * step) / 2595.0) - 1.0);
+    a.mel_lo = (float)mel_lo;
+    a.inv_step = (float)(1.0 / step);
+    a.cfg = cfg;
+}
+
+hipError_t launch_mel_table(hipStream_t s, int n_utt, const MelTableArgs& a) {
     if (n_utt <= 0) return hipSuccess;
     const int threads = n_utt >= 1024 ? 64 : kMelTableThreads;
-    mel_table_kernel<<<dim3((unsigned)n_utt), dim3(threads), 0, s>>>(n_utt, alpha, cfg, mel_table_stride(cfg.nfft), tab);
+    mel_table_kernel<<<dim3((unsigned)n_utt), dim3(threads), 0, s>>>(a, mel_table_stride(a.cfg.nfft));
     return hipGetLastError();
 }
 
@@ -431,17 +678,22 @@ hipError_t launch_mel(hipStream_t s, const MelArgs& a) {
     if (a.n_items <= 0) return hipSuccess;
     if (a.cfg.nfft != 512) return hipErrorInvalidValue;
     constexpr int NC = 256;
-    const size_t lds = sizeof(float2) * (kMelSlots * mel_slot_stride<NC>() + 2 * (NC + 1)) +
-                       sizeof(float4) * kMelLanes * kProgStride +
-                       sizeof(float2) * kMelSlots * (a.cfg.n_mel + 3) + sizeof(int) * 20;
+    static_assert(kMelThreads == NC, "a thread per pair of window samples");
+    size_t lds = sizeof(float) * kMelSlots * kSlotFloats + sizeof(vec4) * (kMaxSteps / 4) * 64 + sizeof(int2) * AUG_MAX_MEL +
+                 sizeof(float2) * (kLanePairs * kMelLanes + NC);
+    if (a.cfg.feature == AUG_FEAT_MFCC)
+        lds += sizeof(vec4) * (size_t)((a.cfg.n_mel + 3) / 4) * ((a.cfg.n_ceps + kMelLanes - 1) & ~(kMelLanes - 1));
     const bool mix = a.n_extra > 0;
-    auto k = a.cfg.win == 400 ? (mix ? &mel_kernel<NC, 400, true> : &mel_kernel<NC, 400, false>)
-                              : (mix ? &mel_kernel<NC, 0, true> : &mel_kernel<NC, 0, false>);
+    auto k = a.cfg.win == 400 && a.cfg.hop <= kStagedHop && a.cfg.hop % 2 == 0 ? (mix ? &mel_kernel<400, true> : &mel_kernel<400, false>)
+                              : (mix ? &mel_kernel<0, true> : &mel_kernel<0, false>);
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
     // (launched by address, not called through the pointer: see the convolution's launcher)
     MelArgs by_value = a;
-    const float2* tw = a.twiddle;
     int tab_stride = mel_table_stride(a.cfg.nfft);
-    void* args[] = {&by_value, &tw, &tab_stride};
+    void* args[] = {&by_value, &tab_stride};
     return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3((unsigned)a.n_items), dim3(kMelThreads), args, lds, s);
 }
 

@@ -1,0 +1,83 @@
+"""The front end at the edges of its kernels' tiles: numbers of mel channels around the quads and rounds of the
+projection, hops on either side of what a wavefront stages, frame counts around the four and sixteen frames in flight,
+and more noise sources than are requested ahead."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from oracle import aug_oracle as O
+from paper_1912_11040_amd import workloads as W
+from tests.parity import FEAT_TOL, dev, feat_err
+
+pytestmark = pytest.mark.gpu
+FE = W.FrontendConfig()
+
+
+@pytest.fixture(scope="module")
+def aug():
+    from paper_1912_11040_amd.binding import Augmenter
+    a = Augmenter(0)
+    yield a
+    a.close()
+
+
+def _check(aug, fe, lens, seed, spare=0):
+    import torch
+    rng = np.random.default_rng(seed)
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    x = rng.standard_normal(int(offsets[-1])).astype(np.float32)
+    alpha = rng.uniform(0.8, 1.2, len(lens)).astype(np.float32)
+    t = np.array([O.frame_count(int(n), fe.win, fe.hop) for n in lens])
+    foff = np.concatenate([[0], np.cumsum(t + spare)]).astype(np.int64)
+    feats = torch.full((int(foff[-1]), fe.feature_dim), float("nan"), dtype=torch.float32, device="cuda")
+    aug.aug_vtlp_mel_batch(offsets, dev(x), dev(alpha), fe, foff, feats)
+    torch.cuda.synchronize()
+    got, ref = feats.cpu().numpy(), O.vtlp_mel_batch(offsets, x, alpha, fe)
+    packed = np.concatenate([[0], np.cumsum(t)])
+    for u in range(len(lens)):
+        mine = got[foff[u]:foff[u + 1]]
+        assert not mine[t[u]:].any()
+        if t[u]:
+            assert feat_err(mine[:t[u]], ref[packed[u]:packed[u + 1]]) <= FEAT_TOL, (fe, u)
+
+
+@pytest.mark.parametrize("n_mel,feature", [(1, "power"), (3, "power"), (4, "mfcc"), (5, "log"), (16, "power"), (17, "mfcc"),
+                                           (45, "power"), (60, "mfcc"), (64, "log"), (96, "power"), (127, "mfcc"), (128, "mfcc")])
+def test_mel_channels(aug, n_mel, feature):
+    fe = dataclasses.replace(FE, n_mel=n_mel, feature=feature, n_ceps=min(n_mel, 40), log_floor=1e-6)
+    _check(aug, fe, [4000, 900, 16000], n_mel)
+
+
+@pytest.mark.parametrize("f_lo,f_hi", [(0.0, 300.0), (7010.0, 7890.0), (3000.0, 3100.0)])
+def test_narrow_bands(aug, f_lo, f_hi):
+    _check(aug, dataclasses.replace(FE, f_lo=f_lo, f_hi=f_hi), [4000, 2000], 5)
+
+
+@pytest.mark.parametrize("win,hop", [(400, 1), (400, 207), (400, 208), (400, 210), (400, 700), (401, 160), (512, 3), (399, 160)])
+def test_hops_and_windows(aug, win, hop):
+    _check(aug, dataclasses.replace(FE, win=win, hop=hop), [win + 3 * hop, win - 1, win + 17 * hop + 1, win + 40], win + hop)
+
+
+def test_frame_counts_with_spare_rows(aug):
+    lens = [400 + 160 * k + e for k in (0, 1, 2, 3, 4, 14, 15, 16, 17, 31, 63) for e in (0, 159)]
+    _check(aug, FE, lens, 11, spare=2)
+
+
+@pytest.mark.parametrize("n_noise,hop", [(1, 160), (3, 160), (4, 160), (6, 160), (2, 161)])
+def test_mixture_on_the_fly(aug, n_noise, hop):
+    import torch
+    fe = dataclasses.replace(FE, hop=hop)
+    w = W.varlen(n_utt=4, rir_len=1000, min_s=0.03, max_s=0.5, seed=n_noise)
+    rng = np.random.default_rng(n_noise)
+    noise = rng.standard_normal((n_noise, w.total)).astype(np.float32)
+    geom = np.stack([W.draw_geometry(rng, 1 + n_noise, [5.0, 4.0, 3.0], 0.6) for _ in range(w.n_utt)])
+    snr = rng.uniform(0, 20, (w.n_utt, n_noise)).astype(np.float32)
+    t = np.array([O.frame_count(int(n), fe.win, fe.hop) for n in w.lengths()])
+    foff = np.concatenate([[0], np.cumsum(t)]).astype(np.int64)
+    feats = torch.full((int(foff[-1]), 40), float("nan"), dtype=torch.float32, device="cuda")
+    aug.aug_pipeline_batch(w.offsets, dev(w.speech), dev(noise), dev(geom), w.rir_len, w.fs, w.c, dev(snr), dev(w.alpha), fe,
+                           foff, feats)
+    torch.cuda.synchronize()
+    ref = O.pipeline_batch(w.offsets, w.speech, noise, geom, w.rir_len, w.fs, w.c, snr, w.alpha, fe)
+    assert feat_err(feats.cpu().numpy(), ref["feats"]) <= FEAT_TOL
