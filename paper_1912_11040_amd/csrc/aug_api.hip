@@ -191,11 +191,12 @@ int ring_reserve(aug_ctx* ctx, size_t bytes) {
     return AUG_OK;
 }
 
-// Write a batch's arrays into the next staging slot and enqueue the packing kernel on them, without waiting for
-// the stream.  conv_block / frames_per_group > 0 ask for that table; upload_offsets is false where the device
-// already holds these offsets.  The slot's arrays: offsets, frame offsets, block prefix, group prefix.
-int upload_packing(aug_ctx* ctx, aug::PackArgs pa, const int64_t* offsets, bool upload_offsets, int conv_block,
-                   const int64_t* frame_offsets) {
+// Write a batch's arrays into the next staging slot and point `pa` at them, without waiting for the stream; the caller
+// launches the packing (alone, or with the front end's set-up) and then calls packing_launched.  conv_block > 0 and
+// frame_offsets ask for that table; upload_offsets is false where the device already holds these offsets.  The slot's
+// arrays: offsets, frame offsets, block prefix, group prefix.
+int stage_packing(aug_ctx* ctx, aug::PackArgs& pa, const int64_t* offsets, bool upload_offsets, int conv_block,
+                  const int64_t* frame_offsets) {
     aug::HostRing& r = ctx->ring;
     const int i = r.next, e = i / aug::HostRing::kPerEvent;
     if (i % aug::HostRing::kPerEvent == 0)
@@ -232,18 +233,46 @@ int upload_packing(aug_ctx* ctx, aug::PackArgs pa, const int64_t* offsets, bool 
         first[pa.n_utt] = at;
         pa.conv_first = reinterpret_cast<const int*>(d + 2 * i64);
     }
-    AUG_HIP(aug::launch_pack(ctx->stream, pa), "packing kernel");
+    return AUG_OK;
+}
+
+// The kernel that reads the current staging slot has been enqueued.
+int packing_launched(aug_ctx* ctx) {
+    aug::HostRing& r = ctx->ring;
+    const int i = r.next, e = i / aug::HostRing::kPerEvent;
     if (i % aug::HostRing::kPerEvent == aug::HostRing::kPerEvent - 1)
         AUG_HIP(hipEventRecord(r.done[e], ctx->stream), "staging event record");
     r.next = (i + 1) % aug::HostRing::kSlots;
     return AUG_OK;
 }
 
+// A batch's packing between the check of its offsets and the launch that builds its tables.  The context's record of
+// what the device holds is written when the packing is staged; if the call ends before the launch (out of memory), the
+// record is dropped and the next call packs anew.
+struct PendingPack {
+    aug_ctx* ctx;
+    aug::PackArgs args{};            // args.n_utt == 0: nothing to do
+    explicit PendingPack(aug_ctx* c) : ctx(c) {}
+    ~PendingPack() {
+        if (args.n_utt > 0) ctx->packing = aug::Packing();
+    }
+    int launched() {                 // as part of another kernel
+        if (args.n_utt == 0) return AUG_OK;
+        args.n_utt = 0;
+        return packing_launched(ctx);
+    }
+    int launch() {                   // on its own
+        if (args.n_utt == 0) return AUG_OK;
+        AUG_HIP(aug::launch_pack(ctx->stream, args), "packing kernel");
+        return launched();
+    }
+};
+
 // Device copies of the offsets and the (utterance, block) / (utterance, frame group) tables.  When the host
 // arrays equal the previous call's nothing is done (a steady-state call is kernel launches only).  Otherwise
-// the arrays go through pinned staging and one kernel rebuilds the tables, in stream order behind the earlier
+// the arrays go to pinned staging and `pending` is left for the caller to launch, in stream order behind the earlier
 // calls' kernels: the call does not wait for the stream.
-int sync_packing(aug_ctx* ctx, int n_utt, const int64_t* offsets, const int64_t* frame_offsets,
+int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* offsets, const int64_t* frame_offsets,
                  int conv_block, int frames_per_group) {
     aug::Packing& pk = ctx->packing;
     const size_t n = (size_t)n_utt + 1;
@@ -279,7 +308,7 @@ int sync_packing(aug_ctx* ctx, int n_utt, const int64_t* offsets, const int64_t*
         AUG_TRY(grow(ctx, ctx->d_frame_items, (size_t)std::max<int64_t>(n_groups, 1) * sizeof(int2), "frame group table"));
     }
     AUG_TRY(ring_reserve(ctx, ring_bytes(n)));
-    aug::PackArgs pa{};
+    aug::PackArgs& pa = pending.args;
     pa.n_utt = n_utt;
     pa.frames_per_group = frames_per_group;
     pa.d_offsets = ctx->d_offsets.as<int64_t>();
@@ -287,7 +316,7 @@ int sync_packing(aug_ctx* ctx, int n_utt, const int64_t* offsets, const int64_t*
     pa.d_conv_first = ctx->d_conv_first.as<int>();
     pa.conv_items = ctx->d_conv_items.as<int2>();
     pa.frame_items = ctx->d_frame_items.as<int2>();
-    AUG_TRY(upload_packing(ctx, pa, offsets, !same_off, need_conv ? conv_block : 0, need_fr ? frame_offsets : nullptr));
+    AUG_TRY(stage_packing(ctx, pa, offsets, !same_off, need_conv ? conv_block : 0, need_fr ? frame_offsets : nullptr));
 
     if (!same_off) {
         pk.offsets.assign(offsets, offsets + n);
@@ -304,18 +333,6 @@ int sync_packing(aug_ctx* ctx, int n_utt, const int64_t* offsets, const int64_t*
         pk.n_frame_groups = n_groups;
     }
     return AUG_OK;
-}
-
-// Output rows per work group of the front end (an upper bound: the kernel shares an utterance's rows evenly
-// among its groups).  A group sets up its utterance's tables once, so larger groups are cheaper per frame
-// as long as the launch still has several times more groups than the chip runs at once (three per compute
-// unit); measured on 4096 utterances of 798 frames: 1.70 ms with 64 rows, 1.55 with 160, 1.51 with 400.
-int frontend_rows_per_group(const aug_ctx* ctx, int n_utt, const int64_t* frame_offsets) {
-    const int base = aug::mel_frames_per_group();
-    const int64_t rows = n_utt > 0 ? frame_offsets[n_utt] : 0;
-    const int64_t wanted = 8LL * 3 * ctx->n_cu;
-    const int64_t fit = rows / wanted / 16 * 16;
-    return (int)std::min<int64_t>(std::max<int64_t>(fit, base), 8 * base);
 }
 
 int ensure_twiddle(aug_ctx* ctx, int n, const float2** out) {
@@ -366,19 +383,15 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
     const int n_part = (rir_len + fft_n - 1) / fft_n;
     AUG_TRY(grow(ctx, ctx->rir_spec, sizeof(float2) * (size_t)n_utt * n_src * n_part * (fft_n + 1), "spectrum workspace"));
     AUG_TRY(grow(ctx, ctx->reverb, sizeof(float) * (size_t)n_src * reverb_stride(total), "reverberation workspace"));
-    AUG_TRY(grow(ctx, ctx->gains, sizeof(float) * (size_t)std::max(1, n_utt * n_noise), "gain workspace"));
     AUG_TRY(grow(ctx, ctx->energy, sizeof(double) * (size_t)n_utt * n_src, "energy workspace"));
-    AUG_TRY(grow(ctx, ctx->first_tap, sizeof(int) * (size_t)n_utt * n_src, "first-tap workspace"));
+    AUG_TRY(grow(ctx, ctx->first_tap, sizeof(int) * (size_t)n_utt * n_src * n_part, "first-tap workspace"));
     return AUG_OK;
 }
 
 int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
     if (n_utt == 0 || ctx->packing.n_frame_groups == 0) return AUG_OK;
     AUG_TRY(grow(ctx, ctx->window, sizeof(float) * (size_t)cfg->win, "window table"));
-    if (!ctx->mel_lanes.ptr) {
-        AUG_TRY(grow(ctx, ctx->mel_lanes, sizeof(float) * (size_t)aug::mel_lane_floats(), "lane constants"));
-        AUG_HIP(aug::launch_mel_lanes(ctx->stream, ctx->mel_lanes.as<float>()), "lane constants kernel");
-    }
+    AUG_TRY(grow(ctx, ctx->mel_lanes, sizeof(float) * (size_t)aug::mel_lane_floats(), "lane constants"));
     if (cfg->feature == AUG_FEAT_MFCC)
         AUG_TRY(grow(ctx, ctx->dct, sizeof(float) * (size_t)cfg->n_ceps * cfg->n_mel, "cosine table"));
     AUG_TRY(grow(ctx, ctx->mel_tab, sizeof(float2) * (size_t)n_utt * aug::mel_table_stride(cfg->nfft), "mel table"));
@@ -408,8 +421,8 @@ int run_rir(aug_ctx* ctx, int n_rir, const float* geom, int rir_len, float fs, f
     return AUG_OK;
 }
 
-// Reverberates every source, measures the energies and derives the gains.  With mixed_out the mixture
-// is written there; without it the caller mixes on the fly from the context's reverberated signals.
+// Reverberates every source and measures the energies.  With mixed_out the mixture
+// is written there; without it the caller mixes on the fly from the context's reverberated signals and energies.
 int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, const float* noise,
                      const float* rir, int rir_len, const float* snr_db, float* mixed_out, float* gains_out) {
     const aug::Packing& pk = ctx->packing;
@@ -433,11 +446,8 @@ int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, 
     double* const energy = ctx->energy.as<double>();
 
     AUG_TRY(mark(ctx, -1));
-    AUG_HIP(aug::launch_fill2_u32(ctx->stream, energy, 0u, (int64_t)n_utt * n_src * 2, ctx->first_tap.ptr, 0x7fffffffu,
-                                  (int64_t)n_utt * n_src), "energy and first-tap reset");
-    AUG_TRY(mark(ctx, AUG_STAGE_OTHER));
     AUG_HIP(aug::launch_rir_spectrum(ctx->stream, n_utt * n_src, rir, rir_len, fft_n, tw, ctx->rir_spec.as<float2>(),
-                                     ctx->first_tap.as<int>(), ctx->n_cu),
+                                     ctx->first_tap.as<int>(), energy, ctx->n_cu),
             "spectrum kernel");
     AUG_TRY(mark(ctx, AUG_STAGE_RIR_SPECTRUM));
     aug::ConvArgs ca;
@@ -457,15 +467,16 @@ int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, 
     ca.first_tap = ctx->first_tap.as<int>();
     AUG_HIP(aug::launch_convolve(ctx->stream, fft_n, tw, ca, ctx->n_cu), "convolution kernel");
     AUG_TRY(mark(ctx, AUG_STAGE_CONVOLVE));
-    AUG_HIP(aug::launch_gains(ctx->stream, n_utt, n_src, energy, snr_db, ctx->gains.as<float>(), gains_out), "gain kernel");
     if (mixed_out)
         AUG_HIP(aug::launch_mix(ctx->stream, n_utt, ctx->d_offsets.as<int64_t>(), stride, n_src, ctx->reverb.as<float>(),
-                                ctx->gains.as<float>(), mixed_out, max_len), "mix kernel");
-    AUG_TRY(mark(ctx, AUG_STAGE_MIX));
+                                energy, snr_db, mixed_out, gains_out, max_len), "mix kernel");
+    else if (gains_out)
+        AUG_HIP(aug::launch_gains(ctx->stream, n_utt, n_src, energy, snr_db, gains_out), "gain kernel");
+    if (mixed_out || gains_out) AUG_TRY(mark(ctx, AUG_STAGE_MIX));
     return AUG_OK;
 }
 
-// The mel table kernel's arguments; the band edges are kept from call to call of one configuration.
+// The mel tables' arguments; the band edges are kept from call to call of one configuration.
 const aug::MelTableArgs& mel_table_args(aug_ctx* ctx, const aug_frontend_cfg* cfg, const float* alpha, float2* tab) {
     aug::MelTableArgs& a = ctx->mel_args;
     if (!ctx->have_mel_args || a.cfg.n_mel != cfg->n_mel || a.cfg.f_lo != cfg->f_lo || a.cfg.f_hi != cfg->f_hi) {
@@ -478,29 +489,38 @@ const aug::MelTableArgs& mel_table_args(aug_ctx* ctx, const aug_frontend_cfg* cf
     return a;
 }
 
-// n_extra > 0: the analysed signal is wave + sum_j gains[u][j] extra[j * extra_stride + .] (mixed on the fly)
-int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const float* alpha, const aug_frontend_cfg* cfg,
-            float* feats_out, int n_extra = 0, const float* extra = nullptr, int64_t extra_stride = 0,
-            const float* gains = nullptr) {
+// The front end's tables (they need no signal, so a call may enqueue this first) and the packing, if it is pending.
+int run_mel_setup(aug_ctx* ctx, PendingPack& pending, int n_utt, const float* alpha, const aug_frontend_cfg* cfg) {
+    if (n_utt == 0 || ctx->packing.n_frame_groups == 0) return pending.launch();
+    AUG_TRY(prepare_mel(ctx, n_utt, cfg));
+    AUG_TRY(mark(ctx, -1));
+    const bool mfcc = cfg->feature == AUG_FEAT_MFCC;
+    aug::MelSetupArgs a;
+    a.n_utt = n_utt;
+    a.table = mel_table_args(ctx, cfg, alpha, ctx->mel_tab.as<float2>());
+    a.pack = pending.args;
+    a.lane_consts = ctx->have_lanes ? nullptr : ctx->mel_lanes.as<float>();
+    a.window = ctx->window_n == cfg->win ? nullptr : ctx->window.as<float>();
+    a.dct = !mfcc || (ctx->dct_ceps == cfg->n_ceps && ctx->dct_mel == cfg->n_mel) ? nullptr : ctx->dct.as<float>();
+    AUG_HIP(aug::launch_mel_setup(ctx->stream, a), "front-end set-up kernel");
+    AUG_TRY(pending.launched());
+    ctx->have_lanes = true;
+    ctx->window_n = cfg->win;
+    if (mfcc) {
+        ctx->dct_ceps = cfg->n_ceps;
+        ctx->dct_mel = cfg->n_mel;
+    }
+    return mark(ctx, AUG_STAGE_OTHER);
+}
+
+// After run_mel_setup.  n_extra > 0: the analysed signal is wave + sum_j gain[u][j] extra[j * extra_stride + .], mixed on
+// the fly with the gains that the energies [n_utt][1 + n_extra] and snr_db give.
+int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const aug_frontend_cfg* cfg, float* feats_out, int n_extra = 0,
+            const float* extra = nullptr, int64_t extra_stride = 0, const double* energy = nullptr,
+            const float* snr_db = nullptr) {
     const aug::Packing& pk = ctx->packing;
     if (n_utt == 0 || pk.n_frame_groups == 0) return AUG_OK;
-    AUG_TRY(prepare_mel(ctx, n_utt, cfg));
-    if (ctx->window_n != cfg->win) {
-        AUG_HIP(aug::launch_window(ctx->stream, cfg->win, ctx->window.as<float>()), "window kernel");
-        ctx->window_n = cfg->win;
-    }
-    const float* dct = nullptr;
-    if (cfg->feature == AUG_FEAT_MFCC) {
-        if (ctx->dct_ceps != cfg->n_ceps || ctx->dct_mel != cfg->n_mel) {
-            AUG_HIP(aug::launch_dct_table(ctx->stream, cfg->n_ceps, cfg->n_mel, ctx->dct.as<float>()), "cosine table kernel");
-            ctx->dct_ceps = cfg->n_ceps;
-            ctx->dct_mel = cfg->n_mel;
-        }
-        dct = ctx->dct.as<float>();
-    }
     AUG_TRY(mark(ctx, -1));
-    AUG_HIP(aug::launch_mel_table(ctx->stream, n_utt, mel_table_args(ctx, cfg, alpha, ctx->mel_tab.as<float2>())),
-            "mel table kernel");
     aug::MelArgs ma;
     ma.offsets = ctx->d_offsets.as<int64_t>();
     ma.frame_offsets = ctx->d_frame_offsets.as<int64_t>();
@@ -510,17 +530,17 @@ int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const float* alpha, cons
     ma.wave = wave;
     ma.extra = extra;
     ma.extra_stride = extra_stride;
-    ma.gains = gains;
+    ma.energy = energy;
+    ma.snr_db = snr_db;
     ma.n_extra = n_extra;
     ma.mel_tab = ctx->mel_tab.as<float2>();
-    ma.dct = dct;
+    ma.dct = cfg->feature == AUG_FEAT_MFCC ? ctx->dct.as<float>() : nullptr;
     ma.window = ctx->window.as<float>();
     ma.lane_consts = ctx->mel_lanes.as<float>();
     ma.cfg = *cfg;
     ma.feats = feats_out;
     AUG_HIP(aug::launch_mel(ctx->stream, ma), "mel kernel");
-    AUG_TRY(mark(ctx, AUG_STAGE_MEL));
-    return AUG_OK;
+    return mark(ctx, AUG_STAGE_MEL);
 }
 
 int check_rir_args(aug_ctx* ctx, int rir_len, float fs, float c) {
@@ -607,7 +627,7 @@ int aug_destroy(aug_ctx* ctx) {
     }
     DeviceBuffer* bufs[] = {&ctx->d_offsets, &ctx->d_frame_offsets, &ctx->d_conv_items, &ctx->d_frame_items,
                             &ctx->d_conv_first,
-                            &ctx->rir_items, &ctx->rir_ctrl, &ctx->mic_rows, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->gains, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab, &ctx->mel_lanes,
+                            &ctx->rir_items, &ctx->rir_ctrl, &ctx->mic_rows, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab, &ctx->mel_lanes,
                             &ctx->window};
     for (DeviceBuffer* b : bufs) b->release();
     for (DeviceBuffer& b : ctx->twiddle) b.release();
@@ -726,7 +746,10 @@ int aug_convolve_mix_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, cons
                     "rir_len must be in 1..%d", AUG_MAX_RIR_LEN);
     if ((!rir && n_utt > 0) || (!mixed_out && offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "rir or mixed_out is null");
-    AUG_TRY(sync_packing(ctx, n_utt, offsets, nullptr, aug::conv_fft_size(rir_len), 0));
+    PendingPack pending(ctx);
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, aug::conv_fft_size(rir_len), 0));
+    AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
+    AUG_TRY(pending.launch());
     return run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out);
 }
 
@@ -738,8 +761,10 @@ int aug_vtlp_mel_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     AUG_TRY(check_frame_offsets(ctx, n_utt, offsets, frame_offsets, cfg));
     if ((!wave && offsets[n_utt] > 0) || (!alpha && n_utt > 0) || (!feats_out && frame_offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave, alpha or feats_out is null");
-    AUG_TRY(sync_packing(ctx, n_utt, offsets, frame_offsets, 0, frontend_rows_per_group(ctx, n_utt, frame_offsets)));
-    return run_mel(ctx, n_utt, wave, alpha, cfg, feats_out);
+    PendingPack pending(ctx);
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, 0, aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt])));
+    AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
+    return run_mel(ctx, n_utt, wave, cfg, feats_out);
 }
 
 int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, const float* wave, const float* alpha,
@@ -753,12 +778,21 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     if (n_utt > AUG_STATIC_MAX_UTT)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "%d utterances: the static scratch array holds tables for at most %d",
                     n_utt, AUG_STATIC_MAX_UTT);
-    const int fpg = aug::mel_frames_per_group();
-    int64_t n_groups = 0;
-    for (int u = 0; u < n_utt; ++u) n_groups += (frame_offsets[u + 1] - frame_offsets[u] + fpg - 1) / fpg;
-    if (n_groups > AUG_STATIC_MAX_ROW_GROUPS)
+    auto count_groups = [&](int fpg) {
+        int64_t n = 0;
+        for (int u = 0; u < n_utt; ++u) n += (frame_offsets[u + 1] - frame_offsets[u] + fpg - 1) / fpg;
+        return n;
+    };
+    constexpr int kStaticRows = 64;                      // the group size that the limit is stated in
+    if (count_groups(kStaticRows) > AUG_STATIC_MAX_ROW_GROUPS)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "%lld groups of %d output rows: the static scratch array holds at most %d",
-                    (long long)n_groups, fpg, AUG_STATIC_MAX_ROW_GROUPS);
+                    (long long)count_groups(kStaticRows), kStaticRows, AUG_STATIC_MAX_ROW_GROUPS);
+    int fpg = aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt]);
+    int64_t n_groups = count_groups(fpg);
+    if (n_groups > AUG_STATIC_MAX_ROW_GROUPS) {          // smaller groups than that, and too many of them
+        fpg = kStaticRows;
+        n_groups = count_groups(fpg);
+    }
     if (cfg->win > 2048) return fail(ctx, AUG_ERR_UNSUPPORTED, "window longer than 2048 samples");
     if (n_utt == 0 || n_groups == 0) return AUG_OK;
     unsigned char* const base = ctx->scratch;            // the device address, not the array's name
@@ -774,18 +808,21 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     float2* const mel_tab = reinterpret_cast<float2*>(base + ScratchLayout::mel_tab);
 
     // Everything the kernels read from the array is rewritten here, in stream order, by this call.
-    aug::PackArgs pa{};
-    pa.n_utt = n_utt;
-    pa.frames_per_group = fpg;
-    pa.d_offsets = d_off;
-    pa.d_frame_offsets = d_foff;
-    pa.frame_items = d_items;
-    AUG_TRY(upload_packing(ctx, pa, offsets, true, 0, frame_offsets));
-    AUG_HIP(aug::launch_mel_lanes(ctx->stream, lane_consts), "lane constants kernel");
-    AUG_HIP(aug::launch_window(ctx->stream, cfg->win, window), "window kernel");
-    if (cfg->feature == AUG_FEAT_MFCC)
-        AUG_HIP(aug::launch_dct_table(ctx->stream, cfg->n_ceps, cfg->n_mel, dct), "cosine table kernel");
-    AUG_HIP(aug::launch_mel_table(ctx->stream, n_utt, mel_table_args(ctx, cfg, alpha, mel_tab)), "mel table kernel");
+    aug::MelSetupArgs sa;
+    sa.n_utt = n_utt;
+    sa.pack = aug::PackArgs{};
+    sa.pack.n_utt = n_utt;
+    sa.pack.frames_per_group = fpg;
+    sa.pack.d_offsets = d_off;
+    sa.pack.d_frame_offsets = d_foff;
+    sa.pack.frame_items = d_items;
+    AUG_TRY(stage_packing(ctx, sa.pack, offsets, true, 0, frame_offsets));
+    sa.table = mel_table_args(ctx, cfg, alpha, mel_tab);
+    sa.lane_consts = lane_consts;
+    sa.window = window;
+    sa.dct = cfg->feature == AUG_FEAT_MFCC ? dct : nullptr;
+    AUG_HIP(aug::launch_mel_setup(ctx->stream, sa), "front-end set-up kernel");
+    AUG_TRY(packing_launched(ctx));
     aug::MelArgs ma;
     ma.offsets = d_off;
     ma.frame_offsets = d_foff;
@@ -795,7 +832,8 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     ma.wave = wave;
     ma.extra = nullptr;
     ma.extra_stride = 0;
-    ma.gains = nullptr;
+    ma.energy = nullptr;
+    ma.snr_db = nullptr;
     ma.n_extra = 0;
     ma.mel_tab = mel_tab;
     ma.dct = cfg->feature == AUG_FEAT_MFCC ? dct : nullptr;
@@ -826,7 +864,9 @@ int aug_vtlp_resynth_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, cons
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave, alpha or wave_out is null");
     if (total > 0 && wave_out < wave + total && wave < wave_out + total)
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave_out overlaps wave");
-    AUG_TRY(sync_packing(ctx, n_utt, offsets, nullptr, 0, 0));
+    PendingPack pending(ctx);
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, 0, 0));
+    AUG_TRY(pending.launch());
     if (n_utt == 0 || total == 0) return AUG_OK;
     int64_t max_len = 0;
     for (int u = 0; u < n_utt; ++u) max_len = std::max(max_len, offsets[u + 1] - offsets[u]);
@@ -860,8 +900,9 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     const int n_src = 1 + n_noise;
     if ((int64_t)n_utt * n_src * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
-    AUG_TRY(sync_packing(ctx, n_utt, offsets, frame_offsets, aug::conv_fft_size(rir_len),
-                         frontend_rows_per_group(ctx, n_utt, frame_offsets)));
+    PendingPack pending(ctx);
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_fft_size(rir_len),
+                         aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt])));
     const int64_t total = offsets[n_utt];
     float* rir = rir_out;
     if (!rir) {
@@ -870,15 +911,15 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     }
     AUG_TRY(prepare_rir(ctx, n_utt * n_src, rir_len));
     AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
-    AUG_TRY(prepare_mel(ctx, n_utt, cfg));
+    AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
     AUG_TRY(run_rir(ctx, n_utt * n_src, geom, rir_len, fs, c, rir, nullptr));
     AUG_TRY(run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out));
-    if (mixed_out || total == 0) return run_mel(ctx, n_utt, mixed_out, alpha, cfg, feats_out);
+    if (mixed_out || total == 0) return run_mel(ctx, n_utt, mixed_out, cfg, feats_out);
     // The mixture itself is not wanted: the front end adds the scaled reverberated noises to the
     // reverberated speech as it loads its frames, which saves one pass over the batch through HBM.
     const float* reverb = ctx->reverb.as<float>();
     const int64_t stride = reverb_stride(total);
-    return run_mel(ctx, n_utt, reverb, alpha, cfg, feats_out, n_noise, reverb + stride, stride, ctx->gains.as<float>());
+    return run_mel(ctx, n_utt, reverb, cfg, feats_out, n_noise, reverb + stride, stride, ctx->energy.as<double>(), snr_db);
 }
 
 }  // extern "C"

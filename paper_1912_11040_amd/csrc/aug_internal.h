@@ -45,6 +45,22 @@ struct HostRing {
     int next = 0;
 };
 
+// Device copies of a batch's offsets and its item tables, from the arrays that the host has left in pinned
+// memory: offsets, frame offsets and the exclusive prefix sums of the items per utterance (blocks of the
+// convolution; groups of frames_per_group output rows), n_utt + 1 entries each.  A null source is skipped.
+struct PackArgs {
+    int n_utt;
+    int frames_per_group;
+    const int64_t* offsets;          // pinned host memory, as the device sees it
+    const int64_t* frame_offsets;
+    const int* conv_first;
+    const int* frame_first;
+    int64_t* d_offsets;              // device
+    int64_t* d_frame_offsets;
+    int* d_conv_first;
+    int2* conv_items;                // (utterance, block)
+    int2* frame_items;               // (utterance, first row)
+};
 // Per-utterance (band, weight) table of the warped mel bank followed by how the filters are dealt to the matrix
 // cores: tab float2 [n_utt][mel_table_stride(nfft)].  mel_edges fills in what depends on the configuration only.
 struct MelTableArgs {
@@ -83,8 +99,7 @@ struct aug_ctx {
     aug::DeviceBuffer rir_spec;          // float2 [n_rir][n_part][P+1]
     aug::DeviceBuffer reverb;            // float [1+n_noise][total rounded up to even]
     aug::DeviceBuffer energy;            // double [n_utt][1+n_noise]: energies of the reverberated signals
-    aug::DeviceBuffer gains;             // float [n_utt][n_noise]
-    aug::DeviceBuffer first_tap;         // int [n_utt][1+n_noise]
+    aug::DeviceBuffer first_tap;         // int [n_utt][1+n_noise][n_part]
     aug::DeviceBuffer mel_tab;           // float2 [n_utt][mel_table_stride(nfft)]: (band, weight) per bin, then the plan
     aug::DeviceBuffer mel_lanes;         // float [mel_lane_floats()], filled once
     aug::DeviceBuffer twiddle[16];       // per log2(n): float2 [n + n/2 + 1] FFT twiddles
@@ -95,6 +110,7 @@ struct aug_ctx {
     int window_n = 0;
     aug::MelTableArgs mel_args{};        // band edges of the last front-end configuration seen
     bool have_mel_args = false;
+    bool have_lanes = false;             // mel_lanes is filled
 
     // stage timing: events recorded in stream order, each tagged with the stage it ends (-1 = a start mark)
     bool profiling = false;
@@ -129,9 +145,9 @@ hipError_t launch_rir_mic_rows(hipStream_t s, int n_rir, int n_mic, const float*
 int conv_fft_size(int rir_len);
 
 // Spectra of the zero-padded partitions of each response: spec float2 [n_rir][n_part][P+1], P = fft_n;
-// the index of every response's first non-zero tap is taken into first_tap[n_rir] (INT_MAX on entry).
+// first_tap[n_rir][n_part] gets the index of every partition's first non-zero tap (INT_MAX: none), energy[n_rir] zeros.
 hipError_t launch_rir_spectrum(hipStream_t s, int n_rir, const float* rir, int rir_len, int fft_n,
-                               const float2* twiddle, float2* spec, int* first_tap, int n_cu);
+                               const float2* twiddle, float2* spec, int* first_tap, double* energy, int n_cu);
 
 // Overlap-save convolution of every (utterance, source) with its response; adds the block's energy
 // to energy[u][j] (double, must be zero on entry).  src_base[j] points at source j's packed signal.
@@ -149,29 +165,41 @@ struct ConvArgs {
     float* reverb;               // [n_src][reverb_stride]
     int64_t reverb_stride;
     double* energy;              // [n_utt][n_src] of the reverberated signals
-    const int* first_tap;        // [n_utt][n_src] first non-zero tap of each response
+    const int* first_tap;        // [n_utt][n_src][n_part] first non-zero tap of each partition
 };
 // n_cu: compute units of the device (the kernel runs as persistent work groups)
 hipError_t launch_convolve(hipStream_t s, int fft_n, const float2* twiddle, const ConvArgs& a, int n_cu);
 
-// gains [n_utt][n_src - 1] from the energies and the target SNRs (also copied to gains_out when given)
-// energy: [n_utt][n_src] energies of the reverberated signals
-hipError_t launch_gains(hipStream_t s, int n_utt, int n_src, const double* energy, const float* snr_db, float* gains,
-                        float* gains_out);
-// mixed = reverb[0] + sum_j gains[j - 1] reverb[j]; source j of the reverberated signals starts at j * stride
-hipError_t launch_mix(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t stride, int n_src,
-                      const float* reverb, const float* gains, float* mixed_out, int64_t max_len);
+// The gain that puts noise j at its target SNR against the speech, from the energies [n_src] of one utterance's
+// reverberated signals; zero energy on either side gives gain 0.  (A source whose direct path arrives after the
+// utterance has ended has exactly zero energy: the convolution writes exact zeros before the response's first
+// non-zero tap.)
+__device__ inline float snr_gain(const double* energy, int j, float snr_db) {
+    const double e0 = energy[0], ej = energy[1 + j];
+    return e0 > 0.0 && ej > 0.0 ? (float)sqrt(e0 / (ej * pow(10.0, (double)snr_db / 10.0))) : 0.f;
+}
+// gains_out [n_utt][n_src - 1]
+hipError_t launch_gains(hipStream_t s, int n_utt, int n_src, const double* energy, const float* snr_db, float* gains_out);
+// mixed = reverb[0] + sum_j gain_j reverb[j]; source j of the reverberated signals starts at j * stride; gains_out may be null
+hipError_t launch_mix(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t stride, int n_src, const float* reverb,
+                      const double* energy, const float* snr_db, float* mixed_out, float* gains_out, int64_t max_len);
 
 void mel_edges(const aug_frontend_cfg& cfg, MelTableArgs& a);
 int mel_table_stride(int nfft);
-hipError_t launch_mel_table(hipStream_t s, int n_utt, const MelTableArgs& a);
+int mel_lane_floats();               // the front end's per-lane constants
 
-// The front end's per-lane constants, float [mel_lane_floats()].
-int mel_lane_floats();
-hipError_t launch_mel_lanes(hipStream_t s, float* lane_consts);
-
-// Hamming window, float [win].
-hipError_t launch_window(hipStream_t s, int win, float* w);
+// Everything a front-end call needs before its main kernel, in one launch: the utterances' tables, the packing if
+// pack.n_utt > 0, and those of the constants whose pointer is given (per-lane constants, Hamming window of
+// table.cfg.win samples, orthonormal DCT-II rows [n_ceps][n_mel]).
+struct MelSetupArgs {
+    int n_utt;
+    MelTableArgs table;
+    PackArgs pack;
+    float* lane_consts;
+    float* window;
+    float* dct;
+};
+hipError_t launch_mel_setup(hipStream_t s, const MelSetupArgs& a);
 
 // tw[t] = exp(-2 pi i t / n), t < n, then tw[n + k] = exp(-i pi k / n), k <= n/2, then
 // exp(-i pi 16 j / n), j < n/32; each computed in fp64 and rounded once.
@@ -187,10 +215,11 @@ struct MelArgs {
     int frames_per_group;
     const float* wave;
     // Mixing on the fly: when n_extra > 0 the analysed signal is
-    // wave[n] + sum_j gains[u][j] * extra[j * extra_stride + n], j < n_extra.
+    // wave[n] + sum_j gain[u][j] * extra[j * extra_stride + n], j < n_extra, with the gains of snr_gain.
     const float* extra;
     int64_t extra_stride;
-    const float* gains;            // [n_utt][n_extra]
+    const double* energy;          // [n_utt][1 + n_extra]
+    const float* snr_db;           // [n_utt][n_extra]
     int n_extra;
     const float2* mel_tab;
     const float* dct;              // [n_ceps][n_mel] orthonormal DCT-II rows (AUG_FEAT_MFCC), else null
@@ -199,9 +228,7 @@ struct MelArgs {
     aug_frontend_cfg cfg;
     float* feats;
 };
-int mel_frames_per_group();
-// dct float [n_ceps][n_mel]: s_q cos(pi q (m + 1/2) / n_mel), computed in fp64
-hipError_t launch_dct_table(hipStream_t s, int n_ceps, int n_mel, float* dct);
+int mel_rows_per_group(int n_cu, int64_t rows);
 hipError_t launch_mel(hipStream_t s, const MelArgs& a);
 
 // Waveform VTLP: per-utterance table of (lower source bin, interpolation weight) for every output bin,
@@ -213,27 +240,9 @@ hipError_t launch_vtlp_table(hipStream_t s, int n_utt, const float* alpha, float
 hipError_t launch_vtlp_resynth(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t max_len,
                                const float* wave, const float2* tab, const float2* twiddle, float* out);
 
-// Device copies of a batch's offsets and its item tables, from the arrays that the host has left in pinned
-// memory: offsets, frame offsets and the exclusive prefix sums of the items per utterance (blocks of the
-// convolution; groups of frames_per_group output rows), n_utt + 1 entries each.  A null source is skipped.
-struct PackArgs {
-    int n_utt;
-    int frames_per_group;
-    const int64_t* offsets;          // pinned host memory, as the device sees it
-    const int64_t* frame_offsets;
-    const int* conv_first;
-    const int* frame_first;
-    int64_t* d_offsets;              // device
-    int64_t* d_frame_offsets;
-    int* d_conv_first;
-    int2* conv_items;                // (utterance, block)
-    int2* frame_items;               // (utterance, first row)
-};
 hipError_t launch_pack(hipStream_t s, const PackArgs& a);
 
 // fill n 32-bit words with a value (used instead of memset so that calls stay graph-capturable)
 hipError_t launch_fill_u32(hipStream_t s, void* p, uint32_t v, int64_t n);
-// the same for two arrays in one launch
-hipError_t launch_fill2_u32(hipStream_t s, void* p, uint32_t v, int64_t n, void* q, uint32_t w, int64_t m);
 
 }  // namespace aug

@@ -12,8 +12,8 @@
 // Work groups are persistent and walk along the reverberated signals block after block (see
 // convolve_kernel); each block's energy is added to E[u][j] (fp64 atomics).  A response of two partitions
 // costs one forward and one inverse transform per block as well: the previous window's spectrum stays in
-// registers.  A small kernel forms the gains g_j = sqrt(E_0 / (E_j 10^(snr_j/10))) (zero where an energy is
-// zero); the mixture y_0 + sum_j g_j y_j is written by mix_kernel when the caller wants it, and formed by
+// registers.  The gains g_j = sqrt(E_0 / (E_j 10^(snr_j/10))) (zero where an energy is zero) are formed where they are
+// used: the mixture y_0 + sum_j g_j y_j is written by mix_kernel when the caller wants it, and formed by
 // the front end on the fly otherwise.
 
 #include "aug_internal.h"
@@ -90,8 +90,9 @@ __device__ inline int load_taps(float2 (&v)[8], const float* __restrict__ h, int
 template <int N, int T>
 __global__ __launch_bounds__(T) void rir_spectrum_kernel(
     const float* __restrict__ rir, int rir_len, int n_part, int n_work, const float2* __restrict__ tw,
-    float2* __restrict__ spec, int* __restrict__ first_tap) {
+    float2* __restrict__ spec, int* __restrict__ first_tap, double* __restrict__ energy) {
     extern __shared__ float2 buf[];
+    __shared__ int wave_first[(T + 63) / 64];
     constexpr int M = N / 16;
     float2* const row_tw = buf + lds_padded_size(N);
     RowTwiddles<M>::template fill<16>(row_tw, tw, threadIdx.x, T);
@@ -106,14 +107,22 @@ __global__ __launch_bounds__(T) void rir_spectrum_kernel(
         asm volatile("" : "+v"(tid));
         const int r = work / n_part, p = work % n_part;
         // the response is zero before its first non-zero tap, and so is everything convolved with it
+        // (a partition's first tap is its group's alone to write, so the array needs no reset, and the response's
+        // energy, which the convolution adds to later, gets its zero here)
         for (int off = 32; off > 0; off >>= 1) first = min(first, __shfl_down(first, off, 64));
-        if ((tid & 63) == 0 && first != 0x7fffffff) atomicMin(&first_tap[r], first);
+        if ((tid & 63) == 0) wave_first[tid >> 6] = first;
         float2 v[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) v[i] = i < 8 ? taps[i] : make_float2(0.f, 0.f);
         fft_columns_forward<N>(v, tw, tid);
         fft_columns_store<N, T>(v, buf, tid);
         __syncthreads();
+        if (tid == 0) {
+            int f = wave_first[0];
+            for (int i = 1; i < (T + 63) / 64; ++i) f = min(f, wave_first[i]);
+            first_tap[work] = f;
+            if (p == 0) energy[r] = 0.0;
+        }
         const int next = work + (int)gridDim.x;
         if (next < n_work)
             first = load_taps<N>(taps, rir + (size_t)(next / n_part) * rir_len, rir_len, next % n_part, tid);
@@ -323,7 +332,8 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         c.H = a.spec + uj * a.n_part * (size_t)(N + 1);
         c.y = a.reverb + (size_t)jj * a.reverb_stride + start;
         c.energy = a.energy + uj;
-        c.first = a.first_tap[uj];
+        c.first = a.first_tap[uj * a.n_part];
+        if (MULTI) c.first = min(c.first, a.first_tap[uj * a.n_part + 1]);
         c.b = bb;
         return c;
     };
@@ -474,46 +484,77 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
     }
 }
 
-// One thread per (utterance, noise source): the gain that puts the reverberated noise at its target
-// SNR against the reverberated speech; zero energy on either side gives gain 0.  (A source whose direct
-// path arrives after the utterance has ended has exactly zero energy: the convolution writes exact zeros
-// before the response's first non-zero tap.)
+// One thread per (utterance, noise source), for callers that want the gains but not the mixture.
 __global__ void gain_kernel(int n_utt, int n_src, const double* __restrict__ energy, const float* __restrict__ snr_db,
-                            float* __restrict__ gains, float* __restrict__ gains_out) {
+                            float* __restrict__ gains_out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int n_noise = n_src - 1;
     if (i >= n_utt * n_noise) return;
-    const int u = i / n_noise, j = 1 + i % n_noise;
-    const double e0 = energy[(size_t)u * n_src], ej = energy[(size_t)u * n_src + j];
-    const double snr = (double)snr_db[i];
-    const float gain = (e0 > 0.0 && ej > 0.0) ? (float)sqrt(e0 / (ej * pow(10.0, snr / 10.0))) : 0.f;
-    gains[i] = gain;
-    if (gains_out) gains_out[i] = gain;
+    const int u = i / n_noise;
+    gains_out[i] = snr_gain(energy + (size_t)u * n_src, i - u * n_noise, snr_db[i]);
 }
 
-__global__ __launch_bounds__(256) void mix_kernel(
+// mixed = y_0 + sum_j g_j y_j, kMixChunk samples of one utterance per work group, four consecutive ones per thread and
+// round.  The group forms the utterance's gains itself, while its first samples are on their way (a launch for the
+// gains took 5 us); the first group of an utterance also writes them out.  Bound by HBM.
+constexpr int kMixThreads = 256, kMixRounds = 4, kMixChunk = kMixThreads * 4 * kMixRounds;
+struct __attribute__((aligned(4))) SampleQuad { float x, y, z, w; };
+__global__ __launch_bounds__(kMixThreads) void mix_kernel(
     const int64_t* __restrict__ offsets, int64_t stride, int n_src, const float* __restrict__ reverb,
-    const float* __restrict__ gains, float* __restrict__ mixed) {
+    const double* __restrict__ energy, const float* __restrict__ snr_db, float* __restrict__ mixed,
+    float* __restrict__ gains_out) {
+    __shared__ float gains[AUG_MAX_NOISE];
     const int u = blockIdx.y;
     const int64_t start = offsets[u];
     const int64_t len = offsets[u + 1] - start;
-    const int64_t first = (int64_t)blockIdx.x * blockDim.x * 4;
-    if (first >= len) return;
-    const float* g = gains + (size_t)u * (n_src - 1);
+    const int64_t first = (int64_t)blockIdx.x * kMixChunk;
+    if (first >= len && blockIdx.x > 0) return;
+    const float* y0 = reverb + start;
+    float* out = mixed + start;
+    auto load = [&](const float* y, int64_t n) {
+        if (n + 4 <= len) return *reinterpret_cast<const SampleQuad*>(y + n);
+        return SampleQuad{n < len ? y[n] : 0.f, n + 1 < len ? y[n + 1] : 0.f, n + 2 < len ? y[n + 2] : 0.f, 0.f};
+    };
+    SampleQuad acc[kMixRounds];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int64_t n = first + (int64_t)i * blockDim.x + threadIdx.x;
-        if (n < len) {
-            float acc = reverb[start + n];
-            for (int j = 1; j < n_src; ++j) acc += g[j - 1] * reverb[(size_t)j * stride + start + n];
-            mixed[start + n] = acc;
+    for (int i = 0; i < kMixRounds; ++i) acc[i] = load(y0, first + 4 * ((int64_t)i * kMixThreads + threadIdx.x));
+    if ((int)threadIdx.x < n_src - 1) {
+        const int j = threadIdx.x;
+        const float g = snr_gain(energy + (size_t)u * n_src, j, snr_db[(size_t)u * (n_src - 1) + j]);
+        gains[j] = g;
+        if (gains_out && blockIdx.x == 0) gains_out[(size_t)u * (n_src - 1) + j] = g;
+    }
+    __syncthreads();
+    for (int j = 1; j < n_src; ++j) {
+        const float g = gains[j - 1];
+        const float* y = y0 + (size_t)j * stride;
+        SampleQuad e[kMixRounds];
+#pragma unroll
+        for (int i = 0; i < kMixRounds; ++i) e[i] = load(y, first + 4 * ((int64_t)i * kMixThreads + threadIdx.x));
+#pragma unroll
+        for (int i = 0; i < kMixRounds; ++i) {
+            acc[i].x += g * e[i].x;
+            acc[i].y += g * e[i].y;
+            acc[i].z += g * e[i].z;
+            acc[i].w += g * e[i].w;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kMixRounds; ++i) {
+        const int64_t n = first + 4 * ((int64_t)i * kMixThreads + threadIdx.x);
+        if (n + 4 <= len) {
+            *reinterpret_cast<SampleQuad*>(out + n) = acc[i];
+        } else {
+            if (n < len) out[n] = acc[i].x;
+            if (n + 1 < len) out[n + 1] = acc[i].y;
+            if (n + 2 < len) out[n + 2] = acc[i].z;
         }
     }
 }
 
 template <int N>
 hipError_t spectrum_n(hipStream_t s, int n_rir, const float* rir, int rir_len, const float2* tw,
-                      float2* spec, int* first_tap, int n_cu) {
+                      float2* spec, int* first_tap, double* energy, int n_cu) {
     constexpr int T = conv_threads(N);
     int n_part = (rir_len + N - 1) / N;
     int n_work = n_rir * n_part;
@@ -530,7 +571,7 @@ hipError_t spectrum_n(hipStream_t s, int n_rir, const float* rir, int rir_len, c
     if (groups > n_work) groups = n_work;
     // (launched by address, not called through the pointer: the call form is what undefined-behaviour
     // sanitizers of the host code instrument, and with them it was seen to launch nothing)
-    void* args[] = {&rir, &rir_len, &n_part, &n_work, &tw, &spec, &first_tap};
+    void* args[] = {&rir, &rir_len, &n_part, &n_work, &tw, &spec, &first_tap, &energy};
     return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3((unsigned)groups), dim3(T), args, lds, s);
 }
 
@@ -589,9 +630,9 @@ hipError_t launch_twiddle(hipStream_t s, int n, float2* tw) {
     }
 
 hipError_t launch_rir_spectrum(hipStream_t s, int n_rir, const float* rir, int rir_len, int fft_n,
-                               const float2* twiddle, float2* spec, int* first_tap, int n_cu) {
+                               const float2* twiddle, float2* spec, int* first_tap, double* energy, int n_cu) {
     if (n_rir <= 0) return hipSuccess;
-#define CALL(NN) spectrum_n<NN>(s, n_rir, rir, rir_len, twiddle, spec, first_tap, n_cu)
+#define CALL(NN) spectrum_n<NN>(s, n_rir, rir, rir_len, twiddle, spec, first_tap, energy, n_cu)
     AUG_FFT_DISPATCH(fft_n, CALL)
 #undef CALL
 }
@@ -603,22 +644,20 @@ hipError_t launch_convolve(hipStream_t s, int fft_n, const float2* twiddle, cons
 #undef CALL
 }
 
-hipError_t launch_gains(hipStream_t s, int n_utt, int n_src, const double* energy, const float* snr_db, float* gains,
-                        float* gains_out) {
+hipError_t launch_gains(hipStream_t s, int n_utt, int n_src, const double* energy, const float* snr_db, float* gains_out) {
     const int n = n_utt * (n_src - 1);
     if (n <= 0) return hipSuccess;
-    gain_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(n_utt, n_src, energy, snr_db, gains,
-                                                                         gains_out);
+    gain_kernel<<<dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s>>>(n_utt, n_src, energy, snr_db, gains_out);
     return hipGetLastError();
 }
 
-hipError_t launch_mix(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t stride, int n_src,
-                      const float* reverb, const float* gains, float* mixed_out, int64_t max_len) {
+hipError_t launch_mix(hipStream_t s, int n_utt, const int64_t* d_offsets, int64_t stride, int n_src, const float* reverb,
+                      const double* energy, const float* snr_db, float* mixed_out, float* gains_out, int64_t max_len) {
     if (n_utt <= 0) return hipSuccess;
-    int64_t chunks = (max_len + 1023) / 1024;
+    int64_t chunks = (max_len + kMixChunk - 1) / kMixChunk;
     if (chunks < 1) chunks = 1;
-    mix_kernel<<<dim3((unsigned)chunks, (unsigned)n_utt), dim3(256), 0, s>>>(
-        d_offsets, stride, n_src, reverb, gains, mixed_out);
+    mix_kernel<<<dim3((unsigned)chunks, (unsigned)n_utt), dim3(kMixThreads), 0, s>>>(
+        d_offsets, stride, n_src, reverb, energy, snr_db, mixed_out, gains_out);
     return hipGetLastError();
 }
 

@@ -13,21 +13,20 @@
 // epilogues of the same energies (log-mel, MFCC) and the on-the-fly mixture of reverberated sources
 // are options of the kernel.
 
-#include "aug_internal.h"
 #include "fft_lds.h"
+#include "pack_device.h"
 
 namespace aug {
 namespace {
 
 constexpr int kMelThreads = 256;
-constexpr int kFramesPerGroup = 64;        // smallest target of output rows per work group (the host picks up to 8 times as many)
+constexpr int kFramesPerGroup = 64;        // output rows per work group of an ordinary batch (see mel_rows_per_group)
 
-__global__ void window_kernel(int win, float* w) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= win) return;
+// sample i of the symmetric Hamming window
+__device__ inline float hamming(int i, int win) {
     double s, c;
     sincospi(2.0 * (double)i / (double)(win - 1), &s, &c);
-    w[i] = (float)(0.54 - 0.46 * c);
+    return (float)(0.54 - 0.46 * c);
 }
 
 // ---- per-utterance tables -----------------------------------------------------------------------------------
@@ -73,18 +72,18 @@ __device__ inline int mel_band(const MelTableArgs& a, const double* edges, float
     return c;
 }
 
-// One work group per utterance.  An entry is a chain of double-precision library calls: with few utterances a group
-// has a thread per bin (K = 512) so that the chains run side by side, with many a single wavefront, which fills the
-// chip anyway.  The band edges come from the host (a power each: in this kernel they were two thirds of its time).
+// The tables of utterance u, by one work group.  An entry is a chain of double-precision library calls: with few
+// utterances a group has a thread per bin (K = 512) so that the chains run side by side, with many a single wavefront,
+// which fills the chip anyway.  The band edges come from the host (a power each: here they were two thirds of the time).
 constexpr int kMelTableThreads = 320;
-__global__ __launch_bounds__(kMelTableThreads) void mel_table_kernel(MelTableArgs a, int stride) {
+__device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
     __shared__ double edges[AUG_MAX_MEL + 2];
     __shared__ short band[2050];
     __shared__ int first_bin[AUG_MAX_MEL + 8];        // first bin of band c or higher
     __shared__ MelPlan plan;
     const int bins = a.cfg.nfft / 2 + 1, n_mel = a.cfg.n_mel, tid = threadIdx.x, threads = (int)blockDim.x;
-    float2* t = a.tab + (size_t)blockIdx.x * stride;
-    const float alpha_u = a.alpha[blockIdx.x];
+    float2* t = a.tab + (size_t)u * stride;
+    const float alpha_u = a.alpha[u];
     for (int i = tid; i < n_mel + 2; i += threads) edges[i] = a.edges[i];
     for (int i = tid; i < n_mel + 8; i += threads) first_bin[i] = bins;
     for (int i = tid; i < 16 * kMaxRounds; i += threads) plan.piece[i] = kNoPiece;
@@ -148,20 +147,59 @@ constexpr int kMelLanes = 16;                            // lanes per frame
 constexpr int kLanePairs = 8;
 constexpr int kMelTwFloats = 2 * kTw4Floats;
 constexpr int kLaneConsts = kMelTwFloats + 2 * kLanePairs;
-__global__ void mel_lane_kernel(float* out) {
-    const int lane = threadIdx.x % kMelLanes, part = threadIdx.x / kMelLanes;
-    if (part < 2) {                                      // the two factor sets of a Tw16Short
+__device__ inline void mel_lane_value(int i, float* out) {
+    const int lane = i % kMelLanes, f = i / kMelLanes;
+    if (f < kMelTwFloats) {                              // the two factor sets of a Tw16Short
         const double x = (double)lane / 128.0;
-        const Tw4 w = make_tw4(part == 0 ? 4.0 * x : x);
-        const float f[kTw4Floats] = {w.t1, w.t2, w.t3, w.c1, w.c2, w.r};
-        for (int i = 0; i < kTw4Floats; ++i) out[(part * kTw4Floats + i) * kMelLanes + lane] = f[i];
-    } else if (part < 2 + kLanePairs) {
-        const int i = part - 2;
+        const Tw4 w = make_tw4(f < kTw4Floats ? 4.0 * x : x);
+        const float v[kTw4Floats] = {w.t1, w.t2, w.t3, w.c1, w.c2, w.r};
+        float pick = v[0];
+        for (int k = 1; k < kTw4Floats; ++k) pick = f % kTw4Floats == k ? v[k] : pick;
+        out[i] = pick;
+    } else {
+        const int pair = (f - kMelTwFloats) / 2;
         double s, c;
-        sincospi(-(double)(lane + kMelLanes * i) / 256.0, &s, &c);
-        out[(kMelTwFloats + 2 * i) * kMelLanes + lane] = (float)(s / c);
-        out[(kMelTwFloats + 2 * i + 1) * kMelLanes + lane] = (float)c;
+        sincospi(-(double)(lane + kMelLanes * pair) / 256.0, &s, &c);
+        out[i] = (f - kMelTwFloats) % 2 ? (float)c : (float)(s / c);
     }
+}
+
+// element i of the orthonormal DCT-II rows
+__device__ inline float dct_value(int i, int n_mel) {
+    const int q = i / n_mel, m = i % n_mel;
+    const double s = q == 0 ? sqrt(1.0 / (double)n_mel) : sqrt(2.0 / (double)n_mel);
+    return (float)(s * cos(M_PI * (double)q * ((double)m + 0.5) / (double)n_mel));
+}
+
+// Everything a front-end call needs before its main kernel, in one launch: the utterances' tables (a group each), the
+// batch's packing if its offsets are new, the constants that are not there yet.  Each of these was a launch of its own:
+// five of them and two copies took 40 us before a static call's main kernel.
+__global__ __launch_bounds__(kMelTableThreads) void mel_setup_kernel(MelSetupArgs a, int stride, int pack_groups) {
+    int group = blockIdx.x;
+    if (group < a.n_utt) {
+        mel_table(a.table, stride, group);
+        return;
+    }
+    group -= a.n_utt;
+    const int threads = (int)blockDim.x;
+    if (group < pack_groups) {
+        pack_utterances(a.pack, group * threads + (int)threadIdx.x);
+        return;
+    }
+    int i = (group - pack_groups) * threads + (int)threadIdx.x;
+    const int n_lanes = a.lane_consts ? kLaneConsts * kMelLanes : 0, n_window = a.window ? a.table.cfg.win : 0;
+    const int n_dct = a.dct ? a.table.cfg.n_ceps * a.table.cfg.n_mel : 0;
+    if (i < n_lanes) {
+        mel_lane_value(i, a.lane_consts);
+        return;
+    }
+    i -= n_lanes;
+    if (i < n_window) {
+        a.window[i] = hamming(i, a.table.cfg.win);
+        return;
+    }
+    i -= n_window;
+    if (i < n_dct) a.dct[i] = dct_value(i, a.table.cfg.n_mel);
 }
 
 // ---- the front end ------------------------------------------------------------------------------------------
@@ -235,7 +273,8 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     int2* const s_pieces = reinterpret_cast<int2*>(s_weight + kMaxSteps / 4 * 64);          // [n_mel]: a channel's sums
     float2* const s_pair = reinterpret_cast<float2*>(s_pieces + AUG_MAX_MEL);               // [kLanePairs][kMelLanes]
     float2* const s_window = s_pair + kLanePairs * kMelLanes;                               // [256]
-    vec4* const s_dct = reinterpret_cast<vec4*>(s_window + NC);                             // [n_mel / 4][n_out up to 16s]
+    float* const s_gains = reinterpret_cast<float*>(s_window + NC);                         // [AUG_MAX_NOISE]
+    vec4* const s_dct = reinterpret_cast<vec4*>(s_gains + AUG_MAX_NOISE);                             // [n_mel / 4][n_out up to 16s]
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int slot = tid / kMelLanes, sub = tid % kMelLanes;
@@ -264,6 +303,10 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     float* const buf = slots + slot * kSlotFloats;       // the frame's buffer
     float* const wave_buf = slots + (slot & ~3) * kSlotFloats;     // the four frames of this wavefront
 
+    if (MIX && tid >= kMelThreads - 64 && tid - (kMelThreads - 64) < a.n_extra) {
+        const int j = tid - (kMelThreads - 64);
+        s_gains[j] = snr_gain(a.energy + (size_t)u * (a.n_extra + 1), j, a.snr_db[(size_t)u * a.n_extra + j]);
+    }
     // the utterance's tables: the plan, and from it the weights in the order in which the lanes use them
     const float2* g_tab = a.mel_tab + (size_t)u * tab_stride;
     const MelPlan* plan = reinterpret_cast<const MelPlan*>(g_tab + (NC + 1));
@@ -334,7 +377,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
 
     [[maybe_unused]] const bool even_win = (win & 1) == 0;
     const float* extra = MIX ? a.extra + start : nullptr;
-    const float* gains = MIX ? a.gains + (size_t)u * a.n_extra : nullptr;
+    const float* gains = s_gains;
 
     // With a mixture (and the paper's window) the samples of a wavefront's four frames, which overlap, are staged: 16 bytes
     // per lane and load, each sample of each source once, mixed while still in registers, into the frames' buffers and
@@ -625,35 +668,26 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     }
 }
 
-__global__ void dct_table_kernel(int n_ceps, int n_mel, float* dct) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_ceps * n_mel) return;
-    const int q = i / n_mel, m = i % n_mel;
-    const double s = q == 0 ? sqrt(1.0 / (double)n_mel) : sqrt(2.0 / (double)n_mel);
-    dct[i] = (float)(s * cos(M_PI * (double)q * ((double)m + 0.5) / (double)n_mel));
-}
-
 }  // namespace
 
-hipError_t launch_dct_table(hipStream_t s, int n_ceps, int n_mel, float* dct) {
-    const int n = n_ceps * n_mel;
-    if (n <= 0) return hipSuccess;
-    dct_table_kernel<<<dim3((n + 255) / 256), dim3(256), 0, s>>>(n_ceps, n_mel, dct);
-    return hipGetLastError();
+// Output rows per work group of the front end (an upper bound: the kernel shares an utterance's rows evenly among its
+// groups), in multiples of the frames a group has in flight.  A group sets up its utterance's tables once, so a large
+// batch takes large groups, as long as the launch still has several times more of them than the chip runs at once (4096
+// utterances of 798 frames: 1.70 ms with 64 rows, 1.55 with 160, 1.51 with 400, of the kernel of that day).  A batch that
+// does not fill the chip with groups of 64 rows takes the smallest ones that all run at once: one pass instead of four
+// is what bounds a single utterance.
+int mel_rows_per_group(int n_cu, int64_t rows) {
+    const int64_t at_once = 3LL * n_cu;
+    int64_t fit;
+    if (rows <= kFramesPerGroup * at_once) {
+        fit = (rows + at_once - 1) / at_once;
+        fit = (fit + kMelSlots - 1) / kMelSlots * kMelSlots;
+        return fit < kMelSlots ? kMelSlots : (int)fit;
+    }
+    fit = rows / (8 * at_once) / kMelSlots * kMelSlots;
+    return (int)(fit < kFramesPerGroup ? kFramesPerGroup : fit > 8 * kFramesPerGroup ? 8 * kFramesPerGroup : fit);
 }
-
-int mel_frames_per_group() { return kFramesPerGroup; }
 int mel_lane_floats() { return kLaneConsts * kMelLanes; }
-
-hipError_t launch_mel_lanes(hipStream_t s, float* lane_consts) {
-    mel_lane_kernel<<<dim3(1), dim3(256), 0, s>>>(lane_consts);
-    return hipGetLastError();
-}
-
-hipError_t launch_window(hipStream_t s, int win, float* w) {
-    window_kernel<<<dim3((win + 255) / 256), dim3(256), 0, s>>>(win, w);
-    return hipGetLastError();
-}
 
 int mel_table_stride(int nfft) { return nfft / 2 + 1 + kPlanEntries; }   // (c, w) per bin, then the plan
 
@@ -667,10 +701,14 @@ void mel_edges(const aug_frontend_cfg& cfg, MelTableArgs& a) {
     a.cfg = cfg;
 }
 
-hipError_t launch_mel_table(hipStream_t s, int n_utt, const MelTableArgs& a) {
-    if (n_utt <= 0) return hipSuccess;
-    const int threads = n_utt >= 1024 ? 64 : kMelTableThreads;
-    mel_table_kernel<<<dim3((unsigned)n_utt), dim3(threads), 0, s>>>(a, mel_table_stride(a.cfg.nfft));
+hipError_t launch_mel_setup(hipStream_t s, const MelSetupArgs& a) {
+    const int threads = a.n_utt >= 1024 ? 64 : kMelTableThreads;
+    const int64_t pack = a.pack.n_utt > 0 ? (pack_threads(a.pack) + threads - 1) / threads : 0;
+    const int64_t consts = (a.lane_consts ? kLaneConsts * kMelLanes : 0) + (a.window ? a.table.cfg.win : 0) +
+                           (a.dct ? a.table.cfg.n_ceps * a.table.cfg.n_mel : 0);
+    const int64_t groups = a.n_utt + pack + (consts + threads - 1) / threads;
+    if (groups <= 0) return hipSuccess;
+    mel_setup_kernel<<<dim3((unsigned)groups), dim3(threads), 0, s>>>(a, mel_table_stride(a.table.cfg.nfft), (int)pack);
     return hipGetLastError();
 }
 
@@ -680,7 +718,7 @@ hipError_t launch_mel(hipStream_t s, const MelArgs& a) {
     constexpr int NC = 256;
     static_assert(kMelThreads == NC, "a thread per pair of window samples");
     size_t lds = sizeof(float) * kMelSlots * kSlotFloats + sizeof(vec4) * (kMaxSteps / 4) * 64 + sizeof(int2) * AUG_MAX_MEL +
-                 sizeof(float2) * (kLanePairs * kMelLanes + NC);
+                 sizeof(float2) * (kLanePairs * kMelLanes + NC) + sizeof(float) * AUG_MAX_NOISE;
     if (a.cfg.feature == AUG_FEAT_MFCC)
         lds += sizeof(vec4) * (size_t)((a.cfg.n_mel + 3) / 4) * ((a.cfg.n_ceps + kMelLanes - 1) & ~(kMelLanes - 1));
     const bool mix = a.n_extra > 0;

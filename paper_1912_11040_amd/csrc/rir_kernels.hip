@@ -890,13 +890,6 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v, int64_t n) {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = v;
 }
 
-__global__ void fill2_u32_kernel(uint32_t* p, uint32_t v, int64_t n, uint32_t* q, uint32_t w, int64_t m) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + m; i += stride) {
-        if (i < n) p[i] = v; else q[i - n] = w;
-    }
-}
-
 }  // namespace
 
 hipError_t launch_fill_u32(hipStream_t s, void* p, uint32_t v, int64_t n) {
@@ -904,15 +897,6 @@ hipError_t launch_fill_u32(hipStream_t s, void* p, uint32_t v, int64_t n) {
     int64_t blocks = (n + 255) / 256;
     if (blocks > 8192) blocks = 8192;
     fill_u32_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(static_cast<uint32_t*>(p), v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill2_u32(hipStream_t s, void* p, uint32_t v, int64_t n, void* q, uint32_t w, int64_t m) {
-    if (n + m <= 0) return hipSuccess;
-    int64_t blocks = (n + m + 255) / 256;
-    if (blocks > 8192) blocks = 8192;
-    fill2_u32_kernel<<<dim3((unsigned)blocks), dim3(256), 0, s>>>(static_cast<uint32_t*>(p), v, n,
-                                                                  static_cast<uint32_t*>(q), w, m);
     return hipGetLastError();
 }
 
