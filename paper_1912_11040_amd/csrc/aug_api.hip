@@ -335,13 +335,27 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
     return AUG_OK;
 }
 
-int ensure_twiddle(aug_ctx* ctx, int n, const float2** out) {
+int log2_of(int n) {
     int lg = 0;
     while ((1 << lg) < n) ++lg;
-    DeviceBuffer& b = ctx->twiddle[lg];
+    return lg;
+}
+
+int ensure_twiddle(aug_ctx* ctx, int n, const float2** out) {
+    DeviceBuffer& b = ctx->twiddle[log2_of(n)];
     if (!b.ptr) {
         AUG_TRY(grow(ctx, b, sizeof(float2) * (size_t)aug::twiddle_entries(n), "twiddle table"));
         AUG_HIP(aug::launch_twiddle(ctx->stream, n, b.as<float2>()), "twiddle kernel");
+    }
+    *out = b.as<float2>();
+    return AUG_OK;
+}
+
+int ensure_conv_table(aug_ctx* ctx, int n, const float2** out) {
+    DeviceBuffer& b = ctx->conv_tab[log2_of(n)];
+    if (!b.ptr) {
+        AUG_TRY(grow(ctx, b, sizeof(float2) * (size_t)aug::conv_table_entries(n), "convolution tables"));
+        AUG_HIP(aug::launch_conv_table(ctx->stream, n, b.as<float2>()), "convolution tables kernel");
     }
     *out = b.as<float2>();
     return AUG_OK;
@@ -381,7 +395,7 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
     const int n_src = 1 + n_noise;
     const int fft_n = aug::conv_fft_size(rir_len);
     const int n_part = (rir_len + fft_n - 1) / fft_n;
-    AUG_TRY(grow(ctx, ctx->rir_spec, sizeof(float2) * (size_t)n_utt * n_src * n_part * (fft_n + 1), "spectrum workspace"));
+    AUG_TRY(grow(ctx, ctx->rir_spec, sizeof(float2) * (size_t)n_utt * n_src * n_part * aug::conv_spectrum_entries(fft_n), "spectrum workspace"));
     AUG_TRY(grow(ctx, ctx->reverb, sizeof(float) * (size_t)n_src * reverb_stride(total), "reverberation workspace"));
     AUG_TRY(grow(ctx, ctx->energy, sizeof(double) * (size_t)n_utt * n_src, "energy workspace"));
     AUG_TRY(grow(ctx, ctx->first_tap, sizeof(int) * (size_t)n_utt * n_src * n_part, "first-tap workspace"));
@@ -431,7 +445,7 @@ int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, 
     const int fft_n = aug::conv_fft_size(rir_len);
     const int n_part = (rir_len + fft_n - 1) / fft_n;
     const float2* tw = nullptr;
-    AUG_TRY(ensure_twiddle(ctx, fft_n, &tw));
+    AUG_TRY(ensure_conv_table(ctx, fft_n, &tw));
     if (n_utt == 0) return AUG_OK;
     if (total == 0) {       // no signal anywhere: every energy is zero, so every gain is
         if (gains_out && n_noise > 0)
@@ -631,6 +645,7 @@ int aug_destroy(aug_ctx* ctx) {
                             &ctx->window};
     for (DeviceBuffer* b : bufs) b->release();
     for (DeviceBuffer& b : ctx->twiddle) b.release();
+    for (DeviceBuffer& b : ctx->conv_tab) b.release();
     for (auto& m : ctx->marks) (void)hipEventDestroy(m.first);
     for (hipEvent_t e : ctx->ring.done)
         if (e) (void)hipEventDestroy(e);

@@ -96,13 +96,14 @@ struct aug_ctx {
 
     // intermediate results
     aug::DeviceBuffer rir;               // float [n_rir][rir_len]            (pipeline only)
-    aug::DeviceBuffer rir_spec;          // float2 [n_rir][n_part][P+1]
+    aug::DeviceBuffer rir_spec;          // float2 [n_rir][n_part][conv_spectrum_entries]
     aug::DeviceBuffer reverb;            // float [1+n_noise][total rounded up to even]
     aug::DeviceBuffer energy;            // double [n_utt][1+n_noise]: energies of the reverberated signals
     aug::DeviceBuffer first_tap;         // int [n_utt][1+n_noise][n_part]
     aug::DeviceBuffer mel_tab;           // float2 [n_utt][mel_table_stride(nfft)]: (band, weight) per bin, then the plan
     aug::DeviceBuffer mel_lanes;         // float [mel_lane_floats()], filled once
-    aug::DeviceBuffer twiddle[16];       // per log2(n): float2 [n + n/2 + 1] FFT twiddles
+    aug::DeviceBuffer twiddle[16];       // per log2(n): float2 [twiddle_entries(n)] FFT twiddles
+    aug::DeviceBuffer conv_tab[16];      // per log2(n): float2 [conv_table_entries(n)] tables of the convolution
     aug::DeviceBuffer window;            // float [win]
     aug::DeviceBuffer dct;               // float [n_ceps][n_mel]
     int dct_ceps = 0, dct_mel = 0;       // shape the table was built for
@@ -144,7 +145,13 @@ hipError_t launch_rir_mic_rows(hipStream_t s, int n_rir, int n_mic, const float*
 // Largest complex FFT size the convolution kernels are built for, and the size chosen for a response length.
 int conv_fft_size(int rir_len);
 
-// Spectra of the zero-padded partitions of each response: spec float2 [n_rir][n_part][P+1], P = fft_n;
+// The tables that the transforms of that size read (float2 [conv_table_entries(fft_n)]), and the size of a partition's
+// spectrum, in float2.
+int conv_table_entries(int fft_n);
+hipError_t launch_conv_table(hipStream_t s, int fft_n, float2* tab);
+size_t conv_spectrum_entries(int fft_n);
+
+// Spectra of the zero-padded partitions of each response: spec float2 [n_rir][n_part][conv_spectrum_entries(fft_n)];
 // first_tap[n_rir][n_part] gets the index of every partition's first non-zero tap (INT_MAX: none), energy[n_rir] zeros.
 hipError_t launch_rir_spectrum(hipStream_t s, int n_rir, const float* rir, int rir_len, int fft_n,
                                const float2* twiddle, float2* spec, int* first_tap, double* energy, int n_cu);
@@ -160,7 +167,7 @@ struct ConvArgs {
     const float* speech;
     const float* noise;          // [n_src-1][total]
     int64_t total;
-    const float2* spec;          // [n_utt][n_src][n_part][P+1]
+    const float2* spec;          // [n_utt][n_src][n_part][conv_spectrum_entries]
     int n_part;
     float* reverb;               // [n_src][reverb_stride]
     int64_t reverb_stride;

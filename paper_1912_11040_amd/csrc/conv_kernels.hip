@@ -17,7 +17,7 @@
 // the front end on the fly otherwise.
 
 #include "aug_internal.h"
-#include "fft_lds.h"
+#include "fft_inplace.h"
 
 namespace aug {
 namespace {
@@ -264,19 +264,82 @@ __device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, i
     return e;
 }
 
-// Work groups are persistent and take their blocks from the list of all blocks ordered by (utterance,
-// source, block), either a contiguous share or every 32nd block of an eighth of the list (see the kernel).  While a block's
+// Work groups are persistent and take their blocks from the list of all blocks ordered by (utterance, source, block).
+// With one partition, the groups that share an L2 (the hardware deals group ids round-robin to the eight XCDs) take one
+// contiguous eighth of the list together and go through it side by side, group s of the 32 on blocks s, s + 32, ...: at
+// any time they are on a few neighbouring signals, so a response spectrum and the halves that neighbouring windows have
+// in common are fetched from HBM once and found in L2 by the other groups, not re-read by one group a whole block later.
+// With two partitions (CONTIGUOUS) a group needs consecutive blocks of a signal, so it takes one contiguous range.
+template <bool CONTIGUOUS>
+struct ConvWalk {
+    const ConvArgs& a;
+    int at, end, step;       // list position, end of the share, stride
+    int u, nb, j, b;         // utterance, blocks of each of its sources, source, block
+
+    __device__ inline explicit ConvWalk(const ConvArgs& args) : a(args), u(0), nb(0), j(0), b(0) {
+        const int total = (int)(a.n_items * a.n_src);      // (the launcher refuses lists of 2^31 blocks or more)
+        if (CONTIGUOUS) {
+            at = (int)((int64_t)total * blockIdx.x / gridDim.x);
+            end = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
+            step = 1;
+        } else {
+            const int teams = gridDim.x % 8 == 0 ? 8 : 1;
+            const int team = blockIdx.x % teams, slot = blockIdx.x / teams;
+            at = (int)((int64_t)total * team / teams) + slot;
+            end = (int)((int64_t)total * (team + 1) / teams);
+            step = (int)gridDim.x / teams;
+        }
+        if (at < end) locate();
+    }
+    // utterance u is the one that holds item at / n_src of the per-source block table
+    __device__ inline void locate() {
+        u = a.items[(unsigned int)at / (unsigned int)a.n_src].x;
+        nb = a.first[u + 1] - a.first[u];
+        const unsigned int r = (unsigned int)(at - a.first[u] * a.n_src);
+        j = (int)(r / (unsigned int)nb);
+        b = (int)r - j * nb;
+    }
+    __device__ inline bool more() const { return at + step < end; }
+    __device__ inline void next() {
+        at += step;
+        if (!CONTIGUOUS) {
+            locate();
+        } else if (++b == nb) {
+            b = 0;
+            if (++j == a.n_src) {
+                j = 0;
+                do {
+                    ++u;
+                    nb = a.first[u + 1] - a.first[u];
+                } while (nb == 0);
+            }
+        }
+    }
+    // spec_stride: float2 entries per partition
+    __device__ inline ConvBlock describe(size_t spec_stride) const {
+        ConvBlock c;
+        const int64_t start = a.offsets[u];
+        const size_t uj = (size_t)u * a.n_src + j;
+        c.len = (int)(a.offsets[u + 1] - start);           // utterances are shorter than 2^30 samples (checked on the host)
+        c.x = (j == 0 ? a.speech : a.noise + (size_t)(j - 1) * a.total) + start;
+        c.H = a.spec + uj * a.n_part * spec_stride;
+        c.y = a.reverb + (size_t)j * a.reverb_stride + start;
+        c.energy = a.energy + uj;
+        c.first = a.first_tap[uj * a.n_part];
+        if (CONTIGUOUS) c.first = min(c.first, a.first_tap[uj * a.n_part + 1]);
+        c.b = b;
+        return c;
+    }
+};
+
+// Responses of up to 2048 taps: transforms in natural order.  While a block's
 // inverse transform runs, the inputs of the next block are already on their way from HBM, and the response
 // spectrum is requested before the forward row transforms that precede its use: the loads' latency is
 // hidden behind arithmetic instead of being paid at either end of a short-lived group.
-// MULTI: the response has two partitions.  Block b is then the inverse transform of
-// H_0 W_b + H_1 W_{b-1}; W_{b-1} is the window spectrum of the block this group finished just before, and
-// each thread keeps its sixteen bins of it in registers, so a block still costs one forward and one inverse
-// transform (plus one forward transform at the start of a group's share).
-template <int N, int T, bool MULTI>
+template <int N, int T>
 __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* __restrict__ tw) {
     extern __shared__ float2 buf[];
-    __shared__ double red[T / 64];
+    __shared__ double red[(T + 63) / 64];
     constexpr int M = N / 16;
     static_assert(T == M, "one thread per column of the split transform");
     // behind the transform buffer: the row transforms' twiddles with their powers, and the two factors of
@@ -287,83 +350,25 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
     RowTwiddles<M>::template fill<16>(row_tw, tw, threadIdx.x, T);
     for (int i = threadIdx.x; i < 16 + M / 2; i += T) split_lo[i] = i < 16 ? tw[N + i] : tw[N + N / 2 + 1 + (i - 16)];
     // (the first barrier of the loop below comes before any of these is read)
-    // With two partitions the kept spectrum takes the registers that the single-partition kernel spends on
-    // loads issued ahead of time; the inputs and the response spectrum are then loaded where they are used.
-    constexpr bool AHEAD = !MULTI;
     const int tid0 = threadIdx.x;
-    const int total = (int)(a.n_items * a.n_src);          // (the launcher refuses lists of 2^31 blocks or more)
-    // Shares.  With two partitions a group needs consecutive blocks of a signal, so it takes one contiguous
-    // range of the list.  Otherwise the groups that share an L2 (the hardware deals group ids round-robin to
-    // the eight XCDs) take one contiguous eighth of the list together and go through it side by side, group
-    // s of the 32 on blocks s, s + 32, ...: at any time they are on a few neighbouring signals, so a
-    // response spectrum and the halves that neighbouring windows have in common are fetched from HBM once
-    // and found in L2 by the other groups, not re-read by one group a whole block later.
-    constexpr bool STRIDED = !MULTI;
-    int w_begin, w_end, w_step;
-    if (STRIDED) {
-        const int teams = gridDim.x % 8 == 0 ? 8 : 1;
-        const int team = blockIdx.x % teams, slot = blockIdx.x / teams;
-        w_begin = (int)((int64_t)total * team / teams) + slot;
-        w_end = (int)((int64_t)total * (team + 1) / teams);
-        w_step = (int)gridDim.x / teams;
-    } else {
-        w_begin = (int)((int64_t)total * blockIdx.x / gridDim.x);
-        w_end = (int)((int64_t)total * (blockIdx.x + 1) / gridDim.x);
-        w_step = 1;
-    }
-    if (w_begin >= w_end) return;
-
-    // block w of the list: utterance u (the one that holds item w / n_src), source j, block b
-    int u, nb, j, b;
-    auto locate = [&](int at) {
-        u = a.items[(unsigned int)at / (unsigned int)a.n_src].x;
-        nb = a.first[u + 1] - a.first[u];
-        const unsigned int r = (unsigned int)(at - a.first[u] * a.n_src);
-        j = (int)(r / (unsigned int)nb);
-        b = (int)r - j * nb;
-    };
-    locate(w_begin);
-    auto describe = [&](int uu, int jj, int bb) {
-        ConvBlock c;
-        const int64_t start = a.offsets[uu];
-        const size_t uj = (size_t)uu * a.n_src + jj;
-        c.len = (int)(a.offsets[uu + 1] - start);          // utterances are shorter than 2^30 samples (checked on the host)
-        c.x = (jj == 0 ? a.speech : a.noise + (size_t)(jj - 1) * a.total) + start;
-        c.H = a.spec + uj * a.n_part * (size_t)(N + 1);
-        c.y = a.reverb + (size_t)jj * a.reverb_stride + start;
-        c.energy = a.energy + uj;
-        c.first = a.first_tap[uj * a.n_part];
-        if (MULTI) c.first = min(c.first, a.first_tap[uj * a.n_part + 1]);
-        c.b = bb;
-        return c;
-    };
-    ConvBlock cur = describe(u, j, b);
-
+    ConvWalk<false> walk(a);
+    if (walk.at >= walk.end) return;
+    ConvBlock cur = walk.describe(N + 1);
     float2 v[16];
-    float2 prev_a[MULTI ? 8 : 1], prev_b[MULTI ? 8 : 1], prev_mid = make_float2(0.f, 0.f);
-    bool have_prev = false;         // prev_* hold the window spectrum of block cur.b - 1 of this signal
-    if (MULTI) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) prev_a[i] = prev_b[i] = make_float2(0.f, 0.f);
-        have_prev = cur.b == 0;     // the window before the first block is all zeros, and so is its spectrum
-    }
-    if (AHEAD) load_window<N>(v, cur.x, cur.len, cur.b, tid0);
+    load_window<N>(v, cur.x, cur.len, cur.b, tid0);
 
-    for (int w = w_begin;;) {
+    for (;;) {
         // The thread index is made opaque in every round so that twiddle powers and addresses are not
         // hoisted out of the loop, where they would sit on top of the transforms' registers.
         int tid = tid0;
         asm volatile("" : "+v"(tid));
-        const bool warm_up = MULTI && !have_prev;          // this pass only produces the spectrum of window b - 1
-        if (!AHEAD) load_window<N>(v, cur.x, cur.len, warm_up ? cur.b - 1 : cur.b, tid);
-
         fft_columns_forward<N>(v, tw, tid);
         fft_columns_store<N, T>(v, buf, tid);
         __syncthreads();
 
         // the response spectrum of this thread's bins, requested now, used after the row transforms
         float2 hk[8], hn[8];
-        if (AHEAD) {
+        {
             const int k2 = tid % (M / 2), half = tid / (M / 2);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
@@ -377,42 +382,14 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         // (opaque again: bin positions are recomputed here rather than kept in registers across the transform)
         asm volatile("" : "+v"(tid));
         const int k2 = tid % (M / 2), half = tid / (M / 2);
-
-        if (warm_up) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const PairIndex<N> ix(half * 8 + i, k2);
-                prev_a[i] = buf[lds_pad(ix.pos)];
-                prev_b[i] = cconj(buf[lds_pad(ix.pos_partner)]);
-            }
-            prev_mid = buf[lds_pad(M / 2)];
-            have_prev = true;
-            __syncthreads();                               // all bins are read before the next column store
-            continue;
-        }
-
-        const float2* H1 = cur.H + (N + 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const PairIndex<N> ix(half * 8 + i, k2);
             const float2 A = buf[lds_pad(ix.pos)];
             const float2 B = cconj(buf[lds_pad(ix.pos_partner)]);
             const float2 wk = cmul(split_lo[half * 8 + i], split_hi[k2]);
-            if (!AHEAD) {
-                hk[i] = load_bin(cur.H, 8u * (uint32_t)ix.pos);
-                hn[i] = load_bin(cur.H, 8u * (uint32_t)ix.h_partner);
-            }
             float2 Zk, ZNk;
             multiply_pair(A, B, wk, hk[i], hn[i], Zk, ZNk);
-            if (MULTI) {
-                float2 Zk1, ZNk1;
-                multiply_pair(prev_a[i], prev_b[i], wk, load_bin(H1, 8u * (uint32_t)ix.pos),
-                              load_bin(H1, 8u * (uint32_t)ix.h_partner), Zk1, ZNk1);
-                Zk = cadd(Zk, Zk1);
-                ZNk = cadd(ZNk, ZNk1);
-                prev_a[i] = A;
-                prev_b[i] = B;
-            }
             buf[lds_pad(ix.pos)] = Zk;                     // both positions belong to this thread alone
             if (ix.k != 0) buf[lds_pad(ix.pos_partner)] = ZNk;
         }
@@ -422,36 +399,19 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
             const float2 wk = tw[N + N / 2];
             float2 Zk, ZNk;
             multiply_pair(A, cconj(A), wk, cur.H[ix.pos], cur.H[ix.h_partner], Zk, ZNk);
-            if (MULTI) {
-                float2 Zk1, ZNk1;
-                multiply_pair(prev_mid, cconj(prev_mid), wk, H1[ix.pos], H1[ix.h_partner], Zk1, ZNk1);
-                Zk = cadd(Zk, Zk1);
-                prev_mid = A;
-            }
             buf[lds_pad(ix.pos)] = Zk;
         }
         __syncthreads();
 
         // the next block of the share: its inputs are requested now and arrive during the inverse transform
-        const bool more = w + w_step < w_end;
+        const bool more = walk.more();
         ConvBlock nxt = cur;
         asm volatile("" : "+v"(tid));
         if (more) {
-            if (STRIDED) {
-                locate(w + w_step);
-            } else if (++b == nb) {
-                b = 0;
-                if (++j == a.n_src) {
-                    j = 0;
-                    do {
-                        ++u;
-                        nb = a.first[u + 1] - a.first[u];
-                    } while (nb == 0);
-                }
-            }
-            nxt = describe(u, j, b);
-            if (AHEAD) load_window<N>(v, nxt.x, nxt.len, nxt.b, tid);
-        } else if (AHEAD) {
+            walk.next();
+            nxt = walk.describe(N + 1);
+            load_window<N>(v, nxt.x, nxt.len, nxt.b, tid);
+        } else {
             // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
 #pragma unroll
             for (int i = 0; i < 16; ++i) v[i] = make_float2(0.f, 0.f);
@@ -470,9 +430,268 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         __syncthreads();                                   // also: every thread has read its columns from LDS
         if (tid == 0) {
             double tot = 0.0;
-            for (int i = 0; i < T / 64; ++i) tot += red[i];
+            for (int i = 0; i < (T + 63) / 64; ++i) tot += red[i];
             atomicAdd(cur.energy, tot);
         }
+        if (!more) break;
+        cur = nxt;
+    }
+}
+
+// ---- responses of more than 2048 taps: in-place transforms (fft_inplace.h) ------------------------------------
+
+template <int N>
+__global__ void inplace_table_kernel(float* tab) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < InPlace<N>::kFloats) tab[i] = inplace_table_value<N>(i);
+}
+
+// the tables that the transforms read from LDS
+template <int N>
+__device__ inline void copy_tables(float* lds, const float* __restrict__ tab, int tid) {
+    for (int i = tid; i < InPlace<N>::kLdsFloats / 4; i += InPlace<N>::T)
+        reinterpret_cast<float4*>(lds)[i] = reinterpret_cast<const float4*>(tab)[i];
+}
+
+template <int N>
+__device__ inline void load_step_d(float4 (&q)[InPlace<N>::Units][InPlace<N>::kDQuads], const float* __restrict__ tab, int tid) {
+    using P = InPlace<N>;
+    const float4* d = reinterpret_cast<const float4*>(tab + P::kD0) + tid;
+#pragma unroll
+    for (int i = 0; i < P::Units; ++i)
+#pragma unroll
+        for (int k = 0; k < P::kDQuads; ++k) q[i][k] = d[(i * P::kDQuads + k) * P::T];
+}
+
+// tangent of pair s (see inplace_table_value)
+template <int N>
+__device__ inline float pair_tangent(const float4 (&q)[InPlace<N>::kDQuads], int s) {
+    if constexpr (InPlace<N>::RD == 4) return s == 0 ? q[1].z : s == 1 ? q[1].w : s == 2 ? q[2].x : q[2].y;
+    else return s == 0 ? q[0].z : q[0].w;
+}
+
+// Spectra of the response partitions as the products need them: (S, D) per pair of bins (see product_pair), scaled by
+// 1/(2N) (1/N for the unnormalised inverse, 1/2 from the product).  Persistent groups, each taking every gridDim.x-th
+// partition; the next one's taps are requested before the current one's transform.  Bound by the traffic (N 8 bytes
+// written per N taps read).
+template <int N>
+__global__ __launch_bounds__(InPlace<N>::T) void rir_spectrum_inplace_kernel(
+    const float* __restrict__ rir, int rir_len, int n_part, int n_work, const float* __restrict__ tab,
+    float4* __restrict__ spec, int* __restrict__ first_tap, double* __restrict__ energy) {
+    using P = InPlace<N>;
+    constexpr int T = P::T, RD = P::RD;
+    extern __shared__ __align__(16) float2 buf[];
+    __shared__ int wave_first[T / 64];
+    float* const lds_tab = reinterpret_cast<float*>(buf + P::kPadded);
+    const int tid0 = threadIdx.x;
+    copy_tables<N>(lds_tab, tab, tid0);
+    int work = blockIdx.x;
+    if (work >= n_work) return;
+    float2 taps[8];
+    int first = load_taps<N>(taps, rir + (size_t)(work / n_part) * rir_len, rir_len, work % n_part, tid0);
+    for (;;) {
+        int tid = tid0;
+        asm volatile("" : "+v"(tid));
+        const int r = work / n_part, p = work % n_part;
+        // the response is zero before its first non-zero tap, and so is everything convolved with it
+        for (int off = 32; off > 0; off >>= 1) first = min(first, __shfl_down(first, off, 64));
+        if ((tid & 63) == 0) wave_first[tid >> 6] = first;
+        float2 v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = i < 8 ? taps[i] : make_float2(0.f, 0.f);
+        const int next = work + (int)gridDim.x;
+        if (next < n_work)
+            first = load_taps<N>(taps, rir + (size_t)(next / n_part) * rir_len, rir_len, next % n_part, tid);
+        inplace_forward_ab<N>(v, buf, lds_tab, tid);
+        inplace_forward_c<N>(v, buf, lds_tab, tid);
+        __syncthreads();
+        if (tid == 0) {
+            int f = wave_first[0];
+            for (int i = 1; i < T / 64; ++i) f = min(f, wave_first[i]);
+            first_tap[work] = f;
+            if (p == 0) energy[r] = 0.0;
+        }
+        asm volatile("" : "+v"(tid));
+        float4 q[P::Units][P::kDQuads];
+        load_step_d<N>(q, tab, tid);
+        float4* out = spec + (size_t)work * inplace_spectrum_entries<N>();
+        const float scale = 0.5f / (float)N;
+#pragma unroll
+        for (int i = 0; i < P::Units; ++i) {
+            int pos_a, pos_b;
+            P::unit(tid, i, pos_a, pos_b);
+            float2 a[RD], b[RD], mid = make_float2(0.f, 0.f);
+            if (i == 0) inplace_step_d<N, true>(a, b, mid, buf, pos_a, pos_b, q[i], tid == 0);
+            else inplace_step_d<N, false>(a, b, mid, buf, pos_a, pos_b, q[i], false);
+#pragma unroll
+            for (int s = 0; s < RD; ++s) {
+                // E = A + B is H[k] + conj H[N-k]; -i w (A - B) is their difference, w = c (1 + i tau)
+                const float2 A = a[s], B = cconj(b[RD - 1 - s]), d = csub(A, B);
+                const float tau = pair_tangent<N>(q[i], s);
+                const float2 D = tilt<false>(make_float2(d.y, -d.x), tau);
+                const float cc = scale / fmaf(tau, tau, 1.f);                   // c^2
+                out[(i * RD + s) * T + tid] = make_float4(scale * (A.x + B.x), scale * (A.y + B.y), cc * D.x, cc * D.y);
+            }
+            if (i == 0 && tid == 0) out[N / 2] = make_float4(2.f * scale * mid.x, 2.f * scale * mid.y, 0.f, 0.f);
+        }
+        if (next >= n_work) break;
+        work = next;
+        __syncthreads();                             // every value is read before the next step A
+    }
+}
+
+// What bounds it: one group of sixteen wavefronts fills a compute unit (the block is 128 KB of LDS), its barriers keep the
+// wavefronts in step, and so the time in the LDS and the time in the vector units add up.  Against transforms in natural
+// order, with the product from LDS between them, this one makes 12 passes over the block in LDS instead of 16, has four
+// barriers per block instead of five, and about 1450 vector instructions per thread and block instead of 2200: twiddles
+// folded into the butterflies' additions, the product in twenty multiply-adds per pair from the registers that the last
+// forward and the first inverse step share.
+// While a block's inverse transform runs, the inputs of the next block are already on their way from HBM; the response
+// spectrum is requested before the step that precedes its use.
+// MULTI: the response has two partitions.  Block b is then the inverse transform of H_0 W_b + H_1 W_{b-1}; W_{b-1} is the
+// window spectrum of the block this group finished just before, and each thread keeps its sixteen bins of it in
+// registers, so a block still costs one forward and one inverse transform (plus one forward transform at the start of a
+// group's share).  The kept spectrum takes the registers that the single-partition kernel spends on inputs requested
+// ahead of time; they are then loaded where they are used.
+template <int N, bool MULTI>
+__global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArgs a, const float* __restrict__ tab) {
+    using P = InPlace<N>;
+    constexpr int T = P::T, RD = P::RD;
+    constexpr bool AHEAD = !MULTI;
+    constexpr size_t kEntries = inplace_spectrum_entries<N>();
+    extern __shared__ __align__(16) float2 buf[];
+    __shared__ float red[2][T / 64];                       // energies per wavefront of this block and the one before
+    float* const lds_tab = reinterpret_cast<float*>(buf + P::kPadded);
+    const int tid0 = threadIdx.x;
+    copy_tables<N>(lds_tab, tab, tid0);                    // (a barrier of the loop below comes before these are read)
+    ConvWalk<MULTI> walk(a);
+    if (walk.at >= walk.end) return;
+    ConvBlock cur = walk.describe(2 * kEntries);
+
+    float2 v[16];
+    float2 prev_a[MULTI ? 8 : 1], prev_b[MULTI ? 8 : 1], prev_mid = make_float2(0.f, 0.f);
+    bool have_prev = false;         // prev_* hold the window spectrum of block cur.b - 1 of this signal
+    if (MULTI) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) prev_a[i] = prev_b[i] = make_float2(0.f, 0.f);
+        have_prev = cur.b == 0;     // the window before the first block is all zeros, and so is its spectrum
+    }
+    if (AHEAD) load_window<N>(v, cur.x, cur.len, cur.b, tid0);
+    double* done_energy = nullptr;  // where the energies in red[parity ^ 1] belong
+    int parity = 0;
+    // the energy of the block before this one: a wavefront's 1024 squares in fp32, the rest in fp64
+    auto flush_energy = [&](int tid) {
+        if (tid == 0 && done_energy) {
+            double tot = 0.0;
+            for (int i = 0; i < T / 64; ++i) tot += (double)red[parity ^ 1][i];
+            atomicAdd(done_energy, tot);
+        }
+    };
+
+    for (;;) {
+        // The thread index is made opaque in every round so that addresses are not hoisted out of the loop, where they
+        // would sit on top of the transforms' registers.
+        int tid = tid0;
+        asm volatile("" : "+v"(tid));
+        const bool warm_up = MULTI && !have_prev;          // this pass only produces the spectrum of window b - 1
+        if (!AHEAD) load_window<N>(v, cur.x, cur.len, warm_up ? cur.b - 1 : cur.b, tid);
+
+        inplace_forward_ab<N>(v, buf, lds_tab, tid);
+        flush_energy(tid);
+        done_energy = nullptr;
+        float4 q[P::Units][P::kDQuads];
+        load_step_d<N>(q, tab, tid);
+        inplace_forward_c<N>(v, buf, lds_tab, tid);
+        asm volatile("" : "+v"(tid));
+        const float4* H = reinterpret_cast<const float4*>(cur.H);
+        float4 sd[AHEAD ? 8 : 1];
+        if (AHEAD) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sd[i] = H[i * T + tid];
+        }
+        __syncthreads();
+
+#pragma unroll
+        for (int i = 0; i < P::Units; ++i) {
+            int pos_a, pos_b;
+            P::unit(tid, i, pos_a, pos_b);
+            float2 x[RD], y[RD], mid = make_float2(0.f, 0.f);
+            // (thread 0's unit 0 is told apart in the first wavefront only)
+            const bool thread0 = i == 0 && tid == 0;
+            if (i == 0) inplace_step_d<N, true>(x, y, mid, buf, pos_a, pos_b, q[i], thread0);
+            else inplace_step_d<N, false>(x, y, mid, buf, pos_a, pos_b, q[i], false);
+            if (warm_up) {
+#pragma unroll
+                for (int s = 0; s < RD; ++s) {
+                    prev_a[MULTI ? i * RD + s : 0] = x[s];
+                    prev_b[MULTI ? i * RD + s : 0] = cconj(y[RD - 1 - s]);
+                }
+                if (i == 0) prev_mid = mid;
+                continue;
+            }
+#pragma unroll
+            for (int s = 0; s < RD; ++s) {
+                const float2 A = x[s], B = cconj(y[RD - 1 - s]);
+                const float tau = pair_tangent<N>(q[i], s);
+                float2 zk, zn;
+                product_pair<false>(A, B, AHEAD ? sd[AHEAD ? i * RD + s : 0] : H[(i * RD + s) * T + tid], tau, zk, zn);
+                if (MULTI) {
+                    float2& pa = prev_a[MULTI ? i * RD + s : 0];
+                    float2& pb = prev_b[MULTI ? i * RD + s : 0];
+                    product_pair<true>(pa, pb, H[kEntries + (i * RD + s) * T + tid], tau, zk, zn);
+                    pa = A;
+                    pb = B;
+                }
+                x[s] = zk;
+                y[RD - 1 - s] = cconj(zn);
+            }
+            if (thread0) {                                 // the bin in the middle
+                const float4 h = H[N / 2];
+                float2 z = cmul(mid, make_float2(h.x, h.y));
+                if (MULTI) {
+                    const float4 h1 = H[kEntries + N / 2];
+                    z = cadd(z, cmul(prev_mid, make_float2(h1.x, h1.y)));
+                    prev_mid = mid;
+                }
+                mid = z;
+            }
+            if (i == 0) inplace_step_d_inverse<N, true>(x, y, mid, buf, pos_a, pos_b, thread0);
+            else inplace_step_d_inverse<N, false>(x, y, mid, buf, pos_a, pos_b, false);
+        }
+        if (warm_up) {
+            have_prev = true;
+            __syncthreads();                               // all values are read before the next step A
+            continue;
+        }
+        asm volatile("" : "+v"(tid));
+        float4 wa[3];                                      // the last step's factors, requested before the next inputs
+#pragma unroll
+        for (int i = 0; i < 3; ++i) wa[i] = reinterpret_cast<const float4*>(tab + P::kA0)[i * T + tid];
+        __syncthreads();
+
+        // the next block of the share: its inputs are requested now and arrive during the inverse transform
+        const bool more = walk.more();
+        ConvBlock nxt = cur;
+        if (more) {
+            walk.next();
+            nxt = walk.describe(2 * kEntries);
+            if (AHEAD) load_window<N>(v, nxt.x, nxt.len, nxt.b, tid);
+        } else if (AHEAD) {
+            // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = make_float2(0.f, 0.f);
+        }
+
+        float2 o[16];
+        const Tw16Short w{{wa[0].x, wa[0].y, wa[0].z, wa[0].w, wa[1].x, wa[1].y}, {wa[1].z, wa[1].w, wa[2].x, wa[2].y, wa[2].z, wa[2].w}};
+        inplace_inverse<N>(o, buf, lds_tab, tid, w);
+        const float e = store_block<N>(o, cur, tid);
+
+        float es = e;
+        for (int off = 32; off > 0; off >>= 1) es += __shfl_down(es, off, 64);
+        if ((tid & 63) == 0) red[parity][tid >> 6] = es;
+        done_energy = cur.energy;
+        parity ^= 1;
         if (!more) break;
         if (MULTI && nxt.b == 0) {                         // a new signal starts: nothing precedes its first window
 #pragma unroll
@@ -480,8 +699,9 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
             prev_mid = make_float2(0.f, 0.f);
         }
         cur = nxt;
-        w += w_step;
     }
+    __syncthreads();
+    flush_energy(tid0);
 }
 
 // One thread per (utterance, noise source), for callers that want the gains but not the mixture.
@@ -552,55 +772,66 @@ __global__ __launch_bounds__(kMixThreads) void mix_kernel(
     }
 }
 
+constexpr bool in_place(int n) { return n >= 4096; }
+
+// As many persistent groups of T threads as the chip holds at once: per compute unit, what the 160 KB of LDS and
+// sixteen wavefronts (128 registers each) allow.
+int64_t groups_at_once(int n_cu, size_t lds, int threads) {
+    const int by_lds = (int)((160 * 1024) / (lds + 256));
+    const int by_waves = 16 / ((threads + 63) / 64);
+    const int per_cu = by_lds < 1 ? 1 : (by_lds < by_waves ? by_lds : by_waves);
+    return (int64_t)n_cu * per_cu;
+}
+
+// (launched by address, not called through the pointer: the call form is what undefined-behaviour
+// sanitizers of the host code instrument, and with them it was seen to launch nothing)
+hipError_t launch_groups(hipStream_t s, const void* kernel, int n_cu, int64_t work, int threads, size_t lds, void** args) {
+    hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    int64_t groups = groups_at_once(n_cu, lds, threads);
+    if (groups > work) groups = work;
+    return hipLaunchKernel(kernel, dim3((unsigned)groups), dim3(threads), args, lds, s);
+}
+
+template <int N>
+size_t inplace_lds() { return sizeof(float2) * InPlace<N>::kPadded + sizeof(float) * InPlace<N>::kLdsFloats; }
+
 template <int N>
 hipError_t spectrum_n(hipStream_t s, int n_rir, const float* rir, int rir_len, const float2* tw,
                       float2* spec, int* first_tap, double* energy, int n_cu) {
-    constexpr int T = conv_threads(N);
     int n_part = (rir_len + N - 1) / N;
     int n_work = n_rir * n_part;
-    const size_t lds = sizeof(float2) * (lds_padded_size(N) + RowTwiddles<N / 16>::kEntries);
-    auto k = &rir_spectrum_kernel<N, T>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    // as many persistent groups as the chip holds at once (see convolve_n)
-    const int by_lds = (int)((160 * 1024) / (lds + 256));
-    const int by_waves = 16 / ((T + 63) / 64);
-    const int per_cu = by_lds < 1 ? 1 : (by_lds < by_waves ? by_lds : by_waves);
-    int groups = n_cu * per_cu;
-    if (groups > n_work) groups = n_work;
-    // (launched by address, not called through the pointer: the call form is what undefined-behaviour
-    // sanitizers of the host code instrument, and with them it was seen to launch nothing)
     void* args[] = {&rir, &rir_len, &n_part, &n_work, &tw, &spec, &first_tap, &energy};
-    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3((unsigned)groups), dim3(T), args, lds, s);
+    if constexpr (in_place(N)) {
+        return launch_groups(s, reinterpret_cast<const void*>(&rir_spectrum_inplace_kernel<N>), n_cu, n_work, InPlace<N>::T,
+                             inplace_lds<N>(), args);
+    } else {
+        constexpr int T = conv_threads(N);
+        return launch_groups(s, reinterpret_cast<const void*>(&rir_spectrum_kernel<N, T>), n_cu, n_work, T,
+                             sizeof(float2) * (lds_padded_size(N) + RowTwiddles<N / 16>::kEntries), args);
+    }
 }
 
 template <int N>
 hipError_t convolve_n(hipStream_t s, const float2* tw, const ConvArgs& a, int n_cu) {
-    constexpr int T = conv_threads(N);
-    const size_t lds = sizeof(float2) * (lds_padded_size(N) + RowTwiddles<N / 16>::kEntries + 16 + N / 32);
-    // responses longer than one partition exist only at the largest transform size (conv_fft_size)
-    void (*k)(ConvArgs, const float2*) = &convolve_kernel<N, T, false>;
-    if (a.n_part > 1) {
-        if constexpr (N == 16384) k = &convolve_kernel<N, T, true>;
-        else return hipErrorInvalidValue;
-        if (a.n_part != 2) return hipErrorInvalidValue;
-    }
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    // as many persistent groups as the chip holds at once: per compute unit, what the 160 KB of LDS and
-    // sixteen wavefronts (128 registers each) allow
-    const int by_lds = (int)((160 * 1024) / (lds + 256));
-    const int by_waves = 16 / ((T + 63) / 64);
-    const int per_cu = by_lds < 1 ? 1 : (by_lds < by_waves ? by_lds : by_waves);
-    int64_t groups = (int64_t)n_cu * per_cu;
     const int64_t total = a.n_items * a.n_src;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (groups > total) groups = total;
     ConvArgs by_value = a;
     void* args[] = {&by_value, &tw};
-    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3((unsigned)groups), dim3(T), args, lds, s);
+    if constexpr (in_place(N)) {
+        // responses longer than one partition exist only at the largest transform size (conv_fft_size)
+        const void* k = reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false>);
+        if (a.n_part > 1) {
+            if (N != 16384 || a.n_part != 2) return hipErrorInvalidValue;
+            k = reinterpret_cast<const void*>(&convolve_inplace_kernel<16384, true>);
+        }
+        return launch_groups(s, k, n_cu, total, InPlace<N>::T, inplace_lds<N>(), args);
+    } else {
+        if (a.n_part > 1) return hipErrorInvalidValue;
+        constexpr int T = conv_threads(N);
+        return launch_groups(s, reinterpret_cast<const void*>(&convolve_kernel<N, T>), n_cu, total, T,
+                             sizeof(float2) * (lds_padded_size(N) + RowTwiddles<N / 16>::kEntries + 16 + N / 32), args);
+    }
 }
 
 }  // namespace
@@ -609,6 +840,28 @@ int conv_fft_size(int rir_len) {
     int n = 1024;                       // at least one full wave of sixteen-point butterflies
     while (n < rir_len && n < 16384) n <<= 1;
     return n;
+}
+
+int conv_table_entries(int n) {
+    switch (n) {
+        case 4096: return InPlace<4096>::kFloats / 2;
+        case 8192: return InPlace<8192>::kFloats / 2;
+        case 16384: return InPlace<16384>::kFloats / 2;
+        default: return twiddle_count(n);
+    }
+}
+size_t conv_spectrum_entries(int n) { return in_place(n) ? (size_t)n + 2 : (size_t)n + 1; }
+
+hipError_t launch_conv_table(hipStream_t s, int n, float2* tab) {
+    float* f = reinterpret_cast<float*>(tab);
+    const dim3 grid((unsigned)((2 * conv_table_entries(n) + 255) / 256)), block(256);
+    switch (n) {
+        case 4096: inplace_table_kernel<4096><<<grid, block, 0, s>>>(f); break;
+        case 8192: inplace_table_kernel<8192><<<grid, block, 0, s>>>(f); break;
+        case 16384: inplace_table_kernel<16384><<<grid, block, 0, s>>>(f); break;
+        default: return launch_twiddle(s, n, tab);
+    }
+    return hipGetLastError();
 }
 
 int twiddle_entries(int n) { return twiddle_count(n); }
