@@ -98,15 +98,16 @@ __device__ inline void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ inline int wave_inclusive_scan(int v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int t = __shfl_up(v, off, 64);
-        if (lane >= off) v += t;
-    }
+// inclusive sum over the lanes of a wavefront: shifts within rows of sixteen lanes, then the rows' last lanes passed on
+__device__ inline int wave_inclusive_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);      // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true);      // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true);      // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true);      // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);     // row_bcast:15 into rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);     // row_bcast:31 into rows 2 and 3
     return v;
 }
-
 
 constexpr int kClasses = 32;            // cost classes for the order in which items are handed out
 // ctrl: [0] number of items, [1] next item to hand out, [2 .. 2+kClasses) items per class,
@@ -252,7 +253,7 @@ __global__ __launch_bounds__(kPlanThreads) void rir_plan_all_kernel(
 
     int bounds[kMaxBounds];
     const int count = r < n_rir ? cut_shells(work, rir_len, target, items_per_rir, bounds) : 0;
-    const int incl = wave_inclusive_scan(count, lane);
+    const int incl = wave_inclusive_scan(count);
     if (lane == 63) part[wave] = incl;
     __syncthreads();
     int before = 0, n_items = 0;
@@ -342,15 +343,14 @@ __global__ void rir_sort_items_kernel(const Item* __restrict__ unsorted, Item* _
 }
 
 // per-column record shared through LDS between the lane that built it and the lanes that walk its pieces
-// (16 bytes: reflection counts stay below 2^16 for every room the interface accepts, and a batch of 64
-// columns has at most 64 * 2 kAxisCap / kPiece pieces)
 struct __align__(8) Column {
     double a;                    // dx*dx + dy*dy
-    unsigned short kxy;          // reflections along x and y
-    unsigned short pfx;          // the column's first piece within the wave's batch
-    unsigned short start, len;   // range of the sorted z table that can fall inside the shell
+    float bxy;                   // beta^(reflections along x and y)
+    unsigned int place;          // first piece within the wave's batch | start << 12 | length << 22 of the range of the sorted
+                                 // z table that can fall inside the shell
 };
 static_assert(sizeof(Column) == 16, "column records are packed");
+static_assert(2 * kAxisCap < 1024 && 64 * ((2 * kAxisCap + kPiece - 1) / kPiece) < 4096, "the fields of Column::place");
 
 // One image along an axis, as stored in the sorted tables: key = squared distance to the microphone
 // along that axis (reference operation order); aux = beta^reflections (z axis) or the reflection count
@@ -539,98 +539,92 @@ __device__ __attribute__((noinline)) void walk_column_direct(const WalkCtx w, co
 
 // All images (1 - 2q) s + 2 n L - m, q in {0,1}, |n| <= nm, of one axis, written to `out` in order of
 // squared distance.  For each q the signed distance grows with n, so the images with negative
-// distance (walked towards smaller n) and those with non-negative distance are two sorted lists;
-// an image's place in the merged order is its place in its own list plus, by binary search, the
-// number of images of the other three lists that sort before it (ties go to the lower list).
-// All threads of the group must call; aux(q, n) supplies the entry's second field.
+// distance (walked towards smaller n) and those with non-negative distance are two sorted lists.  All four lists step
+// by 2 L and begin within 2 L of the microphone, so the merged order is known: element p of a list follows every
+// list's elements 0 .. p-1 and, of the elements p, those of the lists that begin nearer (ties: the lower list).
+// (Searching the other lists for every entry's place, eight steps each, took a sixth of all the kernel's instructions.)
+// aux(q, n) supplies the entry's second field.
 template <class Aux>
-__device__ inline void build_sorted_images(const Axis& ax, int nm, int* s_split, AxisImage* out, int tid, Aux aux) {
+__device__ inline void build_sorted_images(const Axis& ax, int nm, AxisImage* out, int tid, Aux aux) {
     const int per_q = 2 * nm + 1, n_all = 2 * per_q;
-    if (tid < 2) s_split[tid] = per_q;
-    __syncthreads();
-    for (int i = tid; i < n_all; i += kThreads) {
-        const int q = i >= per_q, n = i - q * per_q - nm;
-        if (axis_delta(ax, q, n) >= 0.0 && (n == -nm || axis_delta(ax, q, n - 1) < 0.0)) s_split[q] = n + nm;
+    // list 2 q + side: its first distance and its length.  The first image at a non-negative distance is n = 0 or 1
+    // while source and microphone lie between the walls.
+    double begin[4];
+    int length[4];
+    int split[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int n = axis_delta(ax, q, 0) >= 0.0 ? 0 : 1;
+        split[q] = n + nm;                        // index of that image; nm >= 1
+        begin[2 * q] = -axis_delta(ax, q, n - 1);
+        begin[2 * q + 1] = axis_delta(ax, q, n);
+        length[2 * q] = n + nm;
+        length[2 * q + 1] = nm - n + 1;
     }
-    __syncthreads();
-    auto key_at = [&](int l, int pos) {           // list l = 2 q + side, position pos in walking order
-        const int sp = s_split[l >> 1];
-        const double d = axis_delta(ax, l >> 1, ((l & 1) ? sp + pos : sp - 1 - pos) - nm);
-        return __dmul_rn(d, d);
-    };
     for (int i = tid; i < n_all; i += kThreads) {
-        const int q = i >= per_q, t = i - q * per_q, sp = s_split[q];
+        const int q = i >= per_q, t = i - q * per_q, sp = q ? split[1] : split[0];
         const int side = t >= sp, own = 2 * q + side;
         const double d = axis_delta(ax, q, t - nm);
-        const double key = __dmul_rn(d, d);
-        int rank = side ? t - sp : sp - 1 - t;
+        const int p = side ? t - sp : sp - 1 - t;
+        const double mine = own == 0 ? begin[0] : own == 1 ? begin[1] : own == 2 ? begin[2] : begin[3];
+        int rank = p;
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
             if (l == own) continue;
-            int lo = 0, hi = (l & 1) ? per_q - s_split[l >> 1] : s_split[l >> 1];
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                const double km = key_at(l, mid);
-                if (km < key || (km == key && l < own)) lo = mid + 1; else hi = mid;
-            }
-            rank += lo;
+            const bool nearer = begin[l] < mine || (begin[l] == mine && l < own);
+            rank += min(p + (nearer ? 1 : 0), length[l]);
         }
         AxisImage e;
-        e.key = key;
+        e.key = __dmul_rn(d, d);
         e.aux = aux(q, t - nm);
         out[rank] = e;
     }
-    __syncthreads();
 }
 
 // Position in an axis's sorted table without searching it.  The table holds the images c_q + 2 n L,
 // q in {0,1}, |n| <= nm, ordered by squared distance, so the number of entries within distance s of the
 // microphone is the number of terms of the two arithmetic progressions that lie in [-s, s].
+// Single precision is enough: a bound is widened (or narrowed) by `slack`, a fifth of a tap plus two millionths of the
+// distance, which covers the rounding of these counts for every axis of up to 4e5 taps (longer ones take the plain
+// path).  An entry that close to a bound is then visited although it may lie outside; it lands, less than half a tap
+// away, in one of the two slots that are never read.
+constexpr double kMaxAxisTaps = 4e5;
 struct AxisCount {
-    double k0, k1;       // -c_q / (2 L), c_q = (1 - 2q) src - mic
-    double inv2l;        // 1 / (2 L)
-    double nm;
+    float k0, k1;        // -c_q / (2 L), c_q = (1 - 2q) src - mic
+    float inv2l;         // 1 / (2 L)
+    float nm;
+    float slack;         // metres
 };
 
-__device__ inline AxisCount axis_count(const Axis& a, int nm) {
+__device__ inline AxisCount axis_count(const Axis& a, int nm, double k_fs_c) {
     const double inv2l = 1.0 / (2.0 * a.room);
-    return AxisCount{uni(-(a.src - a.mic) * inv2l), uni(-(-a.src - a.mic) * inv2l), uni(inv2l), uni((double)nm)};
+    return AxisCount{uni((float)(-(a.src - a.mic) * inv2l)), uni((float)(-(-a.src - a.mic) * inv2l)), uni((float)inv2l),
+                     uni((float)nm), uni((float)(0.2 / k_fs_c))};
 }
 
 // terms n of c_q + 2 n L, |n| <= nm, within [-s, s]: (-s - c_q) / 2L <= n <= (s - c_q) / 2L
-__device__ inline int count_within(const AxisCount& a, double s) {
-    int total = 0;
+__device__ inline int count_within(const AxisCount& a, float s) {
+    float total = 0.f;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-        const double k = q ? a.k1 : a.k0;
-        const double hi = fmin(floor(fma(s, a.inv2l, k)), a.nm);
-        const double lo = fmax(ceil(fma(-s, a.inv2l, k)), -a.nm);
-        total += max((int)hi - (int)lo + 1, 0);
+        const float k = q ? a.k1 : a.k0;
+        const float hi = fminf(floorf(fmaf(s, a.inv2l, k)), a.nm);
+        const float minus_lo = fminf(floorf(fmaf(s, a.inv2l, -k)), a.nm);
+        total += fmaxf(hi + minus_lo + 1.f, 0.f);
     }
-    return total;
+    return (int)total;
 }
 
-// sqrt(b) to a few 1e-15 relative for b > 0 (the hardware's estimate of 1/sqrt and one Newton step), 0 for b <= 0
-__device__ inline double quick_sqrt(double b) {
-    if (!(b > 1e-30)) return 0.0;
-    const double y = __builtin_amdgcn_rsq(b);
-    const double s0 = __dmul_rn(b, y);
-    return fma(__dmul_rn(fma(-s0, s0, b), y), 0.5, s0);
-}
-
-// The table's keys and these counts round differently, so a bound is widened (or narrowed) by far more
-// than either rounding error before counting.  An entry that close to a bound is then visited although
-// it may lie outside; every visited image is tested against the item's taps anyway.
 // number of entries with key <= bound, or a few more
 __device__ inline int count_not_above(const AxisCount& a, int n, double bound) {
     if (!(bound >= 0.0)) return 0;
-    const double s = quick_sqrt(bound);
-    return min(count_within(a, s * (1.0 + 1e-9) + 1e-9), n);
+    const float s = __builtin_amdgcn_sqrtf((float)bound);
+    return min(count_within(a, fmaf(s, 1.000002f, a.slack)), n);
 }
 // number of entries with key < bound, or a few fewer
 __device__ inline int count_below(const AxisCount& a, double bound) {
-    const double s = quick_sqrt(bound) * (1.0 - 1e-9) - 1e-9;
-    return s > 0.0 ? count_within(a, s) : 0;
+    const float s = fmaf(__builtin_amdgcn_sqrtf(fmaxf((float)bound, 0.f)), 0.999998f, -a.slack);
+    return s > 0.f ? count_within(a, s) : 0;
 }
 
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
@@ -645,7 +639,6 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     AxisImage* const ztab = ztab_store + kWalkGroup;       // z images sorted by dz*dz (spare entries in front and behind)
     __shared__ AxisImage ytab[2 * kAxisCap];       // y images sorted by dy*dy
     __shared__ int row_pfx[2 * kAxisCap];          // per x image: inclusive prefix of live column counts
-    __shared__ int s_split[2];
     __shared__ Column cols[kWaves][64];
     __shared__ __align__(8) unsigned int piece_starts[kWaves][kStartWords];
     __shared__ int s_item;
@@ -668,20 +661,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             for (int i = tid; i <= n_taps + 1; i += kThreads) hist32[i] = 0u;
         } else {
             for (int i = tid; i <= n_taps + 1; i += kThreads) hist[i] = 0ull;
-            // beta^k by squaring (k < 1024: ten steps, a few units in the last place of the double, far inside
-            // the float it is kept as; the library pow is some ten times the instructions)
-            for (int i = tid; i < kPow; i += kThreads) {
-                double b = (double)g[9], acc = 1.0;
-#pragma unroll
-                for (int bit = 0; bit < 10; ++bit) {
-                    if ((i >> bit) & 1) acc *= b;
-                    b *= b;
-                }
-                bpow[i] = (float)acc;
-            }
         }
-        __syncthreads();
-
         if (room_ok(g)) {
             const Axis ax{uni((double)g[0]), uni((double)g[3]), uni((double)g[6])};
             const Axis ay{uni((double)g[1]), uni((double)g[4]), uni((double)g[7])};
@@ -702,7 +682,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             nmx = min(nmx, k_cut_item / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
             nmy = min(nmy, k_cut_item / 2 + 1);
             const int nix = 2 * (2 * nmx + 1), niy = 2 * (2 * nmy + 1), niz = 2 * (2 * nmz + 1);
-            const AxisCount cy = axis_count(ay, nmy), cz = axis_count(az, nmz);
+            const AxisCount cy = axis_count(ay, nmy, k_fs_c), cz = axis_count(az, nmz, k_fs_c);
             Column* wc = cols[wave];
             WalkCtx wctx;
             wctx.k_fs_c = k_fs_c;
@@ -725,15 +705,32 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             };
 
             // fast path: the y and z images fit the LDS tables and so do the x rows
-            const bool fast = nix <= 2 * kAxisCap && niy <= 2 * kAxisCap && niz <= 2 * kAxisCap;
+            const bool fast = nix <= 2 * kAxisCap && niy <= 2 * kAxisCap && niz <= 2 * kAxisCap &&
+                              fmax(ay.room, az.room) * k_fs_c < kMaxAxisTaps;
             int n_cand;
+            if (!COUNT) {
+                // beta^k by squaring (k < 1024: ten steps, a few units in the last place of the double, far inside
+                // the float it is kept as; the library pow is some ten times the instructions), for the counts that
+                // can be asked for: those of the z images, and of a column at most the cut or all there are
+                const int k_most = max(2 * nmz + 1, min(k_cut_item, 2 * (nmx + nmy) + 2));
+                for (int i = tid; i <= min(k_most, kPow - 1); i += kThreads) {
+                    double b = beta, acc = 1.0;
+#pragma unroll
+                    for (int bit = 0; bit < 10; ++bit) {
+                        if ((i >> bit) & 1) acc *= b;
+                        b *= b;
+                    }
+                    bpow[i] = (float)acc;
+                }
+            }
+            __syncthreads();
             if (fast) {
-                build_sorted_images(az, nmz, s_split, ztab, tid, [&](int q, int n) {
+                build_sorted_images(az, nmz, ztab, tid, [&](int q, int n) {
                     if (COUNT) return 0.0;
                     const int k = iabs(n - q) + iabs(n);
                     return (double)(k < kPow ? bpow[k] : beta_pow_slow(beta, k));
                 });
-                build_sorted_images(ay, nmy, s_split, ytab, tid, [&](int q, int n) { return (double)(iabs(n - q) + iabs(n)); });
+                build_sorted_images(ay, nmy, ytab, tid, [&](int q, int n) { return (double)(iabs(n - q) + iabs(n)); });
                 // live columns of x image ix: the y images with dy^2 <= r_out^2 - dx^2 that the reflection
                 // cut can still reach -- a prefix of the sorted y table
                 for (int ix = tid; ix < nix; ix += kThreads) {
@@ -749,7 +746,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     int carry = 0;
                     for (int base = 0; base < nix; base += 64) {
                         const int i = base + lane;
-                        const int v = wave_inclusive_scan(i < nix ? row_pfx[i] : 0, lane) + carry;
+                        const int v = wave_inclusive_scan(i < nix ? row_pfx[i] : 0) + carry;
                         if (i < nix) row_pfx[i] = v;
                         carry = __shfl(v, 63, 64);
                     }
@@ -768,7 +765,8 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 if (fast)
                     while (row_pfx[row_lo] <= batch * 64) ++row_lo;       // (the same in every lane; batch * 64 < n_cand)
                 Column col;
-                col.a = 0.0; col.kxy = 0; col.start = 0; col.len = 0;
+                col.a = 0.0;
+                int kxy = 0, z_first = 0, z_len = 0;
                 int pieces = 0;
                 if (cand < n_cand) {
                     if (fast) {
@@ -780,7 +778,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                         const AxisImage ye = ytab[cand - (ix ? row_pfx[ix - 1] : 0)];
                         const double dx = axis_delta(ax, qx, nx);
                         col.a = __dadd_rn(__dmul_rn(dx, dx), ye.key);
-                        col.kxy = (unsigned short)(iabs(nx - qx) + iabs(nx) + (int)ye.aux);
+                        kxy = iabs(nx - qx) + iabs(nx) + (int)ye.aux;
                     } else {
                         const int ix = cand / niy, iy = cand - ix * niy;
                         const int qx = ix & 1, nx = (ix >> 1) - nmx;
@@ -788,11 +786,11 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                         const double dx = axis_delta(ax, qx, nx);
                         const double dy = axis_delta(ay, qy, ny);
                         col.a = __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy));
-                        col.kxy = (unsigned short)(iabs(nx - qx) + iabs(nx) + iabs(ny - qy) + iabs(ny));
+                        kxy = iabs(nx - qx) + iabs(nx) + iabs(ny - qy) + iabs(ny);
                     }
                     // reflections left for the z axis before this column's images vanish
                     // (beyond the first shell the shell's own inner radius bounds the distance well enough)
-                    const int kz_max = (n0 > 0 ? k_cut_item : reflection_cut(log2_beta, sqrtf((float)col.a))) - (int)col.kxy;
+                    const int kz_max = (n0 > 0 ? k_cut_item : reflection_cut(log2_beta, sqrtf((float)col.a))) - kxy;
                     if (col.a < r_out2 && kz_max >= 0) {
                         if (fast) {
                             // images with r_in^2 - a <= dz^2 <= r_out^2 - a within reach of the reflection cut:
@@ -804,19 +802,20 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                             const int first = lo2 > 0.0 ? count_below(cz, lo2) : 0;     // entries with dz2 < lo2
                             const int last = count_not_above(cz, niz, hi2);
                             if (last > first) {
-                                col.start = (unsigned short)first;
-                                col.len = (unsigned short)(last - first);
-                                pieces = (last - first + kPiece - 1) / kPiece;
+                                z_first = first;
+                                z_len = last - first;
+                                pieces = (z_len + kPiece - 1) / kPiece;
                             }
                         } else {
                             pieces = 1;                        // one lane walks every z image of the column
                         }
                     }
                 }
-                const int pfx = wave_inclusive_scan(pieces, lane);
+                const int pfx = wave_inclusive_scan(pieces);
                 const int my_first = pfx - pieces;             // this column's first piece
-                col.pfx = (unsigned short)my_first;
-                const int n_pieces = __shfl(pfx, 63, 64);
+                col.place = (unsigned int)(my_first | z_first << 12 | z_len << 22);
+                if (!COUNT) col.bxy = kxy < kPow ? bpow[kxy] : (pieces ? beta_pow_slow(beta, kxy) : 0.f);
+                const int n_pieces = __builtin_amdgcn_readlane(pfx, 63);
                 // columns with pieces, packed in order
                 const unsigned long long live = __ballot(pieces > 0);
                 if (pieces > 0)
@@ -843,13 +842,12 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                         const int p = p0 + lane;
                         if (p < chunk_end) {
                             const Column c = wc[before + upto - 1];
-                            const int local = p - (int)c.pfx;
+                            const int done = (p - (int)(c.place & 4095u)) * kPiece;       // images of the column's earlier pieces
                             double cxy = 0.0;      // beta^kxy / (4 pi) * 2^56
-                            if (!COUNT)
-                                cxy = (double)(c.kxy < kPow ? bpow[c.kxy] : beta_pow_slow(beta, c.kxy)) * (0.07957747154594767 * 0x1p56);
+                            if (!COUNT) cxy = (double)c.bxy * (0.07957747154594767 * 0x1p56);
                             if (fast) {
-                                const int first = (int)c.start + local * kPiece;
-                                const int len = min(kPiece, (int)c.len - local * kPiece);
+                                const int first = (int)(c.place >> 12 & 1023u) + done;
+                                const int len = min(kPiece, (int)(c.place >> 22) - done);
                                 if (far_item) walk_piece_table<COUNT, true>(wctx, c.a, cxy, ztab + first, len, hist, hist32);
                                 else walk_piece_table<COUNT, false>(wctx, c.a, cxy, ztab + first, len, hist, hist32);
                                 if (VISITS) walked += (unsigned long long)len;
