@@ -29,6 +29,8 @@
 //     A wave takes 64 live columns at a time; their z ranges are cut into pieces of at most kPiece
 //     images, a wave scan numbers the pieces, and lanes take pieces 64 at a time (a piece finds its column by
 //     counting bits in a map of the columns' first pieces) and walk them, two images side by side.
+//     Bound by issue and by LDS about equally (256 x 16000 taps: vector units 0.80, LDS 0.78 of the time, half of that
+//     conflicts of reads at scattered table entries and of sums at scattered taps).
 //     Rooms so flat or narrow that an axis has more images than the tables hold take a plain path
 //     (all columns of the bounding box, every z image of a live column).
 //   * amplitudes accumulate as 64-bit fixed point (2^-56, each increment rounded to the nearest unit)
@@ -46,8 +48,10 @@ constexpr int kMaxTaps = 5632;            // taps owned by one item (LDS: 8 byte
 constexpr int kMinTaps = 64;
 constexpr int kPow = 1024;                // beta^k table entries held in LDS
 constexpr int kAxisCap = 320;             // y or z images per q held in the sorted LDS tables 
-constexpr int kPiece = 12;                // images per piece
-constexpr int kWalkGroup = 2;             // images a lane works on side by side (three or four measured no better)
+// Images per piece, even (two are worked on side by side).  A column's pieces start kPiece sixteen-byte entries apart, so
+// the number also decides which LDS banks neighbouring lanes read: 2000 responses of 8000 taps take 312 us at 10 and
+// 14, 320 at 12, 318 at 18, 395 at 16 (all lanes of a column on the same banks).
+constexpr int kPiece = 14;
 constexpr int kStartWords = 32;           // pieces are dealt in chunks of 32 * kStartWords (one bit each in LDS)
 // Work per item, in image visits (see item_cost): the batch's estimated work divided by the number of
 // persistent groups and by kItemsPerGroup, within limits.  Thick shells visit fewer (x, y) columns per image
@@ -343,14 +347,15 @@ __global__ void rir_sort_items_kernel(const Item* __restrict__ unsorted, Item* _
 }
 
 // per-column record shared through LDS between the lane that built it and the lanes that walk its pieces
-struct __align__(8) Column {
+struct __align__(16) Column {
     double a;                    // dx*dx + dy*dy
     float bxy;                   // beta^(reflections along x and y)
-    unsigned int place;          // first piece within the wave's batch | start << 12 | length << 22 of the range of the sorted
-                                 // z table that can fall inside the shell
+    int place;                   // of the range of the sorted z table that can fall inside the shell: its end, and above
+                                 // bit 10 its start less kPiece times the column's first piece, so that piece p
+                                 // starts at that number plus kPiece p
 };
 static_assert(sizeof(Column) == 16, "column records are packed");
-static_assert(2 * kAxisCap < 1024 && 64 * ((2 * kAxisCap + kPiece - 1) / kPiece) < 4096, "the fields of Column::place");
+static_assert(2 * kAxisCap < 1024 && kPiece % 2 == 0, "the fields of Column::place, and pairs of images");
 
 // One image along an axis, as stored in the sorted tables: key = squared distance to the microphone
 // along that axis (reference operation order); aux = beta^reflections (z axis) or the reflection count
@@ -362,15 +367,17 @@ struct __align__(16) AxisImage {
 
 struct WalkCtx {
     double k_fs_c;
-    double shift;        // 0.5 + guard - (n0 - 1): added to d fs/c, it gives slot = tap - n0 + 1 by truncation
-    double guard2;       // estimates whose fraction (after the shift) is below this are redone exactly
     double beta;
-    int n0m1;            // n0 - 1
-    unsigned int n_slots;   // taps of the item + 2: slot 0 takes what belongs below the item, the last slot what
-                            // belongs above it; neither is read
+    double quick_k;         // fs/c, less the middle of the hardware estimate's error
+    double quick_shift;     // 0.5 + margin - (n0 - 1) + kQuickMagic
+    int quick_margin2;      // quick estimates whose 16-bit fraction is below this are settled by tap_slot
+    double shift;           // 0.5 + guard - (n0 - 1)
+    double guard2;
+    int n0, n1;             // the item's taps.  Slots are tap - n0 + 1: slot 0 takes what belongs below the item, slot
+                            // n1 - n0 + 1 what belongs above it; neither is read
 };
 
-// the reference recipe, kept out of line so that the estimate's loop stays short
+// the reference recipe, out of line so that the table walk stays short
 __device__ __attribute__((noinline)) int exact_tap(double d2, double k_fs_c) {
     const double d = __dsqrt_rn(d2);
     return (int)__dadd_rn(__dmul_rn(d, k_fs_c), 0.5);     // positive: truncation is floor
@@ -389,27 +396,33 @@ __device__ inline int reflection_cut(float log2_beta, float d_min) {
     return k > 1.0e6f ? (1 << 20) : (int)k + 2;
 }
 
-// Slot (tap - n0 + 1) of an image at squared distance d2, and y ~ 1/sqrt(d2) (the hardware's
-// double-precision estimate, good to 2^-24: enough for the amplitude) for its amplitude.
-// One Newton step on the root leaves d fs/c good to ~1e-10 taps; shifted up by the guard, its fraction
-// falls below 2 guard exactly when the true value may lie within the guard of a rounding boundary, and only
-// then is the reference recipe evaluated.
-// (in two parts, so that a caller with several images in hand can run their estimates side by side
-// before any of the rare exact evaluations)
-__device__ inline double tap_estimate(const WalkCtx& w, double d2, double& y) {
-    y = __builtin_amdgcn_rsq(d2);
+// Slot (tap - n0 + 1) of an image at squared distance d2, given y, the hardware's estimate of 1/sqrt(d2).
+// One Newton step on the root leaves d fs/c good to ~1e-10 taps; shifted up by the guard, its fraction falls below
+// 2 guard exactly when the true value may lie within the guard of a rounding boundary, and only then is the
+// reference recipe evaluated.
+__device__ inline int tap_slot(const WalkCtx& w, double d2, double y) {
     const double s0 = __dmul_rn(d2, y);                    // sqrt(d2) to 2^-24
     const double res = fma(-s0, s0, d2);                   // exact residual
     const double s1 = fma(__dmul_rn(res, y), 0.5, s0);     // one Newton step: ~4e-15 relative
-    return fma(s1, w.k_fs_c, w.shift);
-}
-__device__ inline int tap_settle(const WalkCtx& w, double d2, double t) {
+    const double t = fma(s1, w.k_fs_c, w.shift);
     int slot = (int)t;
-    if (__builtin_amdgcn_fract(t) < w.guard2) slot = exact_tap(d2, w.k_fs_c) - w.n0m1;
+    if (__builtin_amdgcn_fract(t) < w.guard2) slot = exact_tap(d2, w.k_fs_c) - (w.n0 - 1);
     return slot;
 }
-__device__ inline int tap_slot(const WalkCtx& w, double d2, double& y) {
-    return tap_settle(w, d2, tap_estimate(w, d2, y));
+
+// The table walk first asks for less.  d2 rsq(d2) without the Newton step is the distance to within the hardware
+// estimate's own error, which over all 2^31 leading mantissas of [1, 4) (three fillings of the remaining bits) lies
+// between -3.24 and +7.10 units of 2^-27; with the middle of that range taken out of fs/c the error is below
+// 5.2 * 2^-27: 3e-4 taps at tap 8000.  Adding 1.5 * 2^36 leaves slot and fraction as two sixteen-bit halves of the
+// sum's low word: the address is a shift and a mask, the test one 16-bit comparison, and the Newton step,
+// conversion, fraction and double-precision comparison are not needed (40 instead of 60 issue cycles, without rsq,
+// per image).  y ~ 1/sqrt(d2) is enough for the amplitude.
+constexpr double kAmplitude = 0.07957747154594767 * 0x1p56;      // 1 / (4 pi) in the sums' fixed point
+constexpr double kQuickMagic = 0x1.8p36;
+constexpr double kQuickMiddle = 1.93 * 0x1p-27, kQuickError = 5.2 * 0x1p-27;
+__device__ inline unsigned int quick_estimate(const WalkCtx& w, double d2, double& y) {
+    y = __builtin_amdgcn_rsq(d2);
+    return (unsigned int)__double2loint(fma(__dmul_rn(d2, y), w.quick_k, w.quick_shift));
 }
 
 // amp2 = amplitude * 2^56, rounded to an integer, goes to the tap's 64-bit integer sum.  Below 2^51 (every
@@ -417,14 +430,12 @@ __device__ inline int tap_slot(const WalkCtx& w, double d2, double& y) {
 // mantissa, whose low 51 bits are then the increment; larger ones are rounded and split in two exact steps
 // (amp2 < 2^64: images at least a third of a millimetre away).  Which of the two an image takes depends on
 // its own amplitude only, so a response does not depend on how the batch was cut into items.
-// FAR: every image of the item lies beyond 2.6 m, the test is not needed.
-// CHECKED: the caller may pass slots outside the item (they are dropped); the table walk never does.
-template <bool COUNT, bool FAR, bool CHECKED>
-__device__ inline void deposit(const WalkCtx& w, int slot, double a, double y, unsigned long long* hist,
-                               unsigned int* hist32) {
-    if (CHECKED && (unsigned int)slot >= w.n_slots) return;
+// FAR: the image lies beyond kNearMetres, the test is not needed.  slot8 is the slot times eight.
+constexpr double kNearMetres = 2.6;
+template <bool COUNT, bool FAR>
+__device__ inline void deposit(unsigned int slot8, double a, double y, unsigned long long* hist) {
     if (COUNT) {
-        atomicAdd(&hist32[slot], 1u);
+        atomicAdd((unsigned int*)((char*)hist + slot8 / 2), 1u);
         return;
     }
     unsigned int hi, lo;
@@ -437,81 +448,72 @@ __device__ inline void deposit(const WalkCtx& w, int slot, double a, double y, u
         hi = (unsigned int)__dmul_rn(amp2, 0x1p-32);
         lo = (unsigned int)fma(-(double)hi, 0x1p32, amp2);
     }
-    atomicAdd(&hist[slot], ((unsigned long long)hi << 32) | lo);
+    atomicAdd((unsigned long long*)((char*)hist + slot8), ((unsigned long long)hi << 32) | lo);
 }
 
-// Every entry of a piece lies inside the item's shell up to the slack of the closed-form table positions
-// (a relative 1e-9: a few 1e-5 taps), so its slot is one of 0 .. taps + 1 and needs no test.
-template <bool COUNT, bool FAR>
-__device__ inline void walk_piece_table(const WalkCtx& w, double a, double cxy, const AxisImage* z, int len,
-                                        unsigned long long* hist, unsigned int* hist32) {
-    // walked from the far end so that one register is both the address and the loop condition
-    // (the sums are integers: the order does not matter)
-    // (the LDS address itself is the loop variable, opaque to the compiler so that it is not split into
-    // a counter plus an offset)
+// The images z[first .. first + len) of a column, 1 <= len <= kPiece, all beyond kNearMetres unless images are counted.
+// Every one lies inside the item's shell up to the slack of the closed-form table positions (a fifth of a tap), so
+// its slot is one of 0 .. taps + 1 and needs no test.
+// Two images at a time, so that each lane has two independent chains of arithmetic in flight (three or four measured
+// no better); the pair of the next round is requested before the current one is worked on.  Walked from the far end
+// so that the LDS address is also the loop's condition (the sums are integers: the order does not matter), and opaque
+// to the compiler so that it is not split into a counter plus an offset.  An odd piece's top pair is its last image
+// twice, the second time with amplitude zero (where images are counted, in slot 0, which is never read).  The last
+// round requests the pair below the piece: the table has spare entries in front.
+template <bool COUNT>
+__device__ inline void walk_piece_table(const WalkCtx& w, double a, double bxy, const AxisImage* z, int first, int len,
+                                        unsigned long long* hist) {
     typedef const AxisImage __attribute__((address_space(3))) * LdsImages;
-    // kGroup images at a time, so that each lane has as many independent chains of arithmetic in flight; the
-    // group of the next round is requested before the current one is worked on.  A piece whose length is
-    // not a multiple of kGroup takes the entries above it as partners whose distance is made not-a-number:
-    // every comparison on them fails and they land in slot 0, which is never read.  The last round requests
-    // the kGroup entries below the piece, and a ragged piece reads up to kGroup - 1 entries above it: the
-    // table has spare entries in front and behind.
-    constexpr int kGroup = kWalkGroup;
     constexpr unsigned int kE = (unsigned int)sizeof(AxisImage);
-    const unsigned int first = (unsigned int)(uintptr_t)(LdsImages)z;
-    const int groups = (len + kGroup - 1) / kGroup;
-    unsigned int cur = first + (unsigned int)((groups - 1) * kGroup) * kE;      // lowest entry of the top group
-    auto entry_at = [](unsigned int lds_address) {
-        const LdsImages p = (LdsImages)(uintptr_t)lds_address;
-        AxisImage e;
-        e.key = p->key;
-        e.aux = p->aux;
-        return e;
-    };
-    struct Group { AxisImage e[kGroup]; };
-    auto load = [&](unsigned int at) {
-        Group g;
-#pragma unroll
-        for (int i = 0; i < kGroup; ++i) g.e[i] = entry_at(at + (unsigned int)i * kE);
+    struct Pair { AxisImage e[2]; };
+    auto load = [](unsigned int at, unsigned int partner) {
+        const LdsImages p = (LdsImages)(uintptr_t)at, q = (LdsImages)(uintptr_t)partner;
+        Pair g;
+        g.e[0].key = p->key;
+        g.e[0].aux = p->aux;
+        g.e[1].key = q->key;
+        g.e[1].aux = q->aux;
         return g;
     };
-    auto step = [&](const Group& g) {
-        double d2[kGroup], y[kGroup], t[kGroup];
-        int slot[kGroup];
+    auto step = [&](const Pair& g) {
+        double d2[2], y[2];
+        unsigned int slot8[2];
         bool redo = false;
 #pragma unroll
-        for (int i = 0; i < kGroup; ++i) {
+        for (int i = 0; i < 2; ++i) {
             d2[i] = __dadd_rn(a, g.e[i].key);
-            t[i] = tap_estimate(w, d2[i], y[i]);
-            slot[i] = (int)t[i];
-            redo |= __builtin_amdgcn_fract(t[i]) < w.guard2;
+            const unsigned int t = quick_estimate(w, d2[i], y[i]);
+            slot8[i] = t >> 13 & 0x7fff8u;
+            redo |= (unsigned short)t < (unsigned short)w.quick_margin2;
         }
-        if (redo) {       // (one test for all, so that the estimates are complete before the branch)
+        if (redo) {       // (one test for both, so that the estimates are complete before the branch)
 #pragma unroll
-            for (int i = 0; i < kGroup; ++i) slot[i] = tap_settle(w, d2[i], t[i]);
+            for (int i = 0; i < 2; ++i) slot8[i] = 8u * (unsigned int)tap_slot(w, d2[i], y[i]);
         }
 #pragma unroll
-        for (int i = 0; i < kGroup; ++i)
-            deposit<COUNT, FAR, false>(w, slot[i], COUNT ? 0.0 : __dmul_rn(g.e[i].aux, cxy), y[i], hist, hist32);
+        for (int i = 0; i < 2; ++i) deposit<COUNT, true>(slot8[i], COUNT ? 0.0 : __dmul_rn(g.e[i].aux, bxy), y[i], hist);
     };
-    Group g0 = load(cur), g1;
-    {
-        const int top = len - 1 - (groups - 1) * kGroup;       // index of the piece's last entry within the top group
-        const double nan = __longlong_as_double(0x7ff8000000000000ll);
-#pragma unroll
-        for (int i = 1; i < kGroup; ++i) if (i > top) g0.e[i].key = nan;
+    const unsigned int bottom = (unsigned int)(uintptr_t)(LdsImages)z + (unsigned int)first * kE;
+    const bool odd = len & 1;
+    unsigned int cur = bottom + ((unsigned int)(len - 1) & ~1u) * kE;      // the top pair
+    Pair g0 = load(cur, cur + (odd ? 0u : kE)), g1;
+    if (COUNT) {
+        if (odd) g0.e[1].key = __longlong_as_double(0x7ff8000000000000ll);      // not a number: slot 0
+    } else {
+        // (the upper half alone: what is left of the number is below 2^-1022 and adds nothing)
+        g0.e[1].aux = __hiloint2double(odd ? 0 : __double2hiint(g0.e[1].aux), __double2loint(g0.e[1].aux));
     }
     for (;;) {
-        const bool last0 = cur == first;
-        cur -= (unsigned int)kGroup * kE;
+        const bool last0 = cur == bottom;
+        cur -= 2 * kE;
         asm("" : "+v"(cur));
-        g1 = load(cur);
+        g1 = load(cur, cur + kE);
         step(g0);
         if (last0) break;
-        const bool last1 = cur == first;
-        cur -= (unsigned int)kGroup * kE;
+        const bool last1 = cur == bottom;
+        cur -= 2 * kE;
         asm("" : "+v"(cur));
-        g0 = load(cur);
+        g0 = load(cur, cur + kE);
         step(g1);
         if (last1) break;
     }
@@ -524,17 +526,29 @@ __device__ __attribute__((noinline)) float beta_pow_slow(double beta, int k) { r
 // (out of line for the same reason: only rooms too flat or narrow for the tables come here)
 template <bool COUNT>
 __device__ __attribute__((noinline)) void walk_column_direct(const WalkCtx w, const Axis az, double a, double cxy, int nmz,
-                                                             unsigned long long* hist, unsigned int* hist32) {
+                                                             unsigned long long* hist) {
     for (int q = 0; q < 2; ++q)
         for (int n = -nmz; n <= nmz; ++n) {
             const double dz = axis_delta(az, q, n);
             const double d2 = __dadd_rn(a, __dmul_rn(dz, dz));
-            double y;
+            const double y = __builtin_amdgcn_rsq(d2);
             const int slot = tap_slot(w, d2, y);
+            if ((unsigned int)slot > (unsigned int)(w.n1 - w.n0 + 1)) continue;          // outside the item
             double bz = 0.0;
             if (!COUNT) bz = (double)beta_pow_slow(w.beta, iabs(n - q) + iabs(n));
-            deposit<COUNT, false, true>(w, slot, __dmul_rn(bz, cxy), y, hist, hist32);
+            deposit<COUNT, false>(8u * (unsigned int)slot, __dmul_rn(bz, cxy), y, hist);
         }
+}
+
+// The images z[first .. last) of a column, with the test for amplitudes too large for the fast rounding.
+__device__ __attribute__((noinline)) void walk_near(const WalkCtx w, double a, double bxy, const AxisImage* z, int first,
+                                                    int last, unsigned long long* hist) {
+    for (int i = first; i < last; ++i) {
+        const double d2 = __dadd_rn(a, z[i].key), y = __builtin_amdgcn_rsq(d2);
+        const int slot = tap_slot(w, d2, y);
+        if ((unsigned int)slot <= (unsigned int)(w.n1 - w.n0 + 1))
+            deposit<false, false>(8u * (unsigned int)slot, __dmul_rn(z[i].aux, bxy), y, hist);
+    }
 }
 
 // All images (1 - 2q) s + 2 n L - m, q in {0,1}, |n| <= nm, of one axis, written to `out` in order of
@@ -635,13 +649,13 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     int32_t* __restrict__ cnt_out, unsigned long long* __restrict__ visits = nullptr) {
     __shared__ unsigned long long hist[(COUNT ? kMaxTaps / 2 : kMaxTaps) + 2];     // first and last slot are never read
     __shared__ float bpow[COUNT ? 1 : kPow];
-    __shared__ AxisImage ztab_store[2 * kAxisCap + 2 * kWalkGroup - 1];
-    AxisImage* const ztab = ztab_store + kWalkGroup;       // z images sorted by dz*dz (spare entries in front and behind)
+    __shared__ AxisImage ztab_store[2 * kAxisCap + 2];
+    AxisImage* const ztab = ztab_store + 2;        // z images sorted by dz*dz (spare entries in front)
     __shared__ AxisImage ytab[2 * kAxisCap];       // y images sorted by dy*dy
     __shared__ int row_pfx[2 * kAxisCap];          // per x image: inclusive prefix of live column counts
     __shared__ Column cols[kWaves][64];
     __shared__ __align__(8) unsigned int piece_starts[kWaves][kStartWords];
-    __shared__ int s_item;
+    __shared__ int s_item, s_batch;
     unsigned int* hist32 = reinterpret_cast<unsigned int*>(hist);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -649,7 +663,10 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     unsigned long long walked = 0;
 
     for (;;) {
-        if (tid == 0) s_item = atomicAdd(&ctrl[1], 1);
+        if (tid == 0) {
+            s_item = atomicAdd(&ctrl[1], 1);
+            s_batch = kWaves;
+        }
         __syncthreads();
         const int it = uni(s_item);
         if (it >= n_items) break;
@@ -686,13 +703,22 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             Column* wc = cols[wave];
             WalkCtx wctx;
             wctx.k_fs_c = k_fs_c;
+            // (in whole units of the estimate's 2^-16 tap, so that adding it to the magic number is exact; one unit
+            // for the sum's rounding)
+            const double margin = ceil(kQuickError * 65536.0 * (double)(n1 + 2)) + 1.0;
+            wctx.quick_k = uni(k_fs_c * (1.0 - kQuickMiddle));
+            wctx.quick_shift = kQuickMagic + (0.5 + margin * 0x1p-16 - (double)(n0 - 1));
+            wctx.quick_margin2 = uni((int)(2.0 * margin) + 1);
             const double guard = 1e-12 * (double)(n1 + 1) + 1e-13;
-            wctx.shift = (0.5 + guard) - (double)(n0 - 1);      // (a vector register: the index step's other factor is scalar)
+            wctx.shift = (0.5 + guard) - (double)(n0 - 1);
             wctx.guard2 = uni(2.0 * guard);
-            wctx.n0m1 = n0 - 1;
-            wctx.n_slots = (unsigned int)n_taps + 2u;
-            // beyond 2.6 m every amplitude is below 2^-5 (see deposit)
-            const bool far_item = r_in >= 2.6;
+            wctx.n0 = n0;
+            wctx.n1 = n1;
+            // beyond 2.6 m every amplitude is below 2^-5 (see deposit); the few images of the innermost items that may be
+            // nearer are walked apart.  (The table positions that separate the two are off by less than 0.25 taps.)
+            const double r_near = kNearMetres + 0.25 / k_fs_c, r_near2 = uni(r_near * r_near);
+            const bool near_item = !COUNT && r_in < r_near;
+            const double r_walk2 = near_item ? r_near2 : r_in2;
             wctx.beta = beta;
             const float y0_max = uni(fmaxf(fabsf((float)(ay.src - ay.mic)), fabsf((float)(ay.src + ay.mic))));
             const float z0_max = uni(fmaxf(fabsf((float)(az.src - az.mic)), fabsf((float)(az.src + az.mic))));
@@ -728,7 +754,8 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 build_sorted_images(az, nmz, ztab, tid, [&](int q, int n) {
                     if (COUNT) return 0.0;
                     const int k = iabs(n - q) + iabs(n);
-                    return (double)(k < kPow ? bpow[k] : beta_pow_slow(beta, k));
+                    // beta^k / (4 pi) * 2^56
+                    return (double)(k < kPow ? bpow[k] : beta_pow_slow(beta, k)) * kAmplitude;
                 });
                 build_sorted_images(ay, nmy, ytab, tid, [&](int q, int n) { return (double)(iabs(n - q) + iabs(n)); });
                 // live columns of x image ix: the y images with dy^2 <= r_out^2 - dx^2 that the reflection
@@ -756,10 +783,30 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             } else {
                 n_cand = nix * niy;
             }
+            if (fast && near_item) {
+                // the columns within r_near: y images up to that, of the x images with |n| <= n_near
+                const int n_near = min((int)(r_near / (2.0 * ax.room)) + 1, nmx), n_rows = 2 * (2 * n_near + 1);
+                const int n_y = count_not_above(cy, niy, r_near2);
+                for (int i = tid; i < n_rows * n_y; i += kThreads) {
+                    const int ix = i / n_y, qx = ix & 1, nx = (ix >> 1) - n_near;
+                    const AxisImage ye = ytab[i - ix * n_y];
+                    const double dx = axis_delta(ax, qx, nx);
+                    const double a = __dadd_rn(__dmul_rn(dx, dx), ye.key);
+                    const int first = count_below(cz, r_in2 - a);
+                    const int last = min(count_below(cz, r_near2 - a), count_not_above(cz, niz, r_out2 - a));
+                    const int kxy = iabs(nx - qx) + iabs(nx) + (int)ye.aux;
+                    if (last > first)
+                        walk_near(wctx, a, (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(beta, kxy)), ztab, first, last, hist);
+                    if (VISITS) walked += (unsigned long long)max(last - first, 0);
+                }
+            }
             const int n_batch = (n_cand + 63) / 64;
 
+            // Batches are taken from a counter (they differ in work by their columns' ranges; dealt in turn, a wave in
+            // eight waited an eighth of the time for the others); the next one is asked for while this one is worked on.
             int row_lo = 0;          // row of the batch's first candidate: it only moves up from batch to batch
-            for (int batch = wave; batch < n_batch; batch += kWaves) {
+            for (int batch = wave, next = 0; batch < n_batch; batch = uni(next)) {
+                if (lane == 0) next = atomicAdd(&s_batch, 1);
                 // ---- each lane describes one candidate column ----
                 const int cand = batch * 64 + lane;
                 if (fast)
@@ -798,7 +845,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                             // keeps add exactly zero)
                             double hi2 = r_out2 - col.a;
                             if (kz_max < (1 << 18)) hi2 = fmin(hi2, reach2(z0_max, lzf, kz_max));
-                            const double lo2 = r_in2 - col.a;
+                            const double lo2 = r_walk2 - col.a;
                             const int first = lo2 > 0.0 ? count_below(cz, lo2) : 0;     // entries with dz2 < lo2
                             const int last = count_not_above(cz, niz, hi2);
                             if (last > first) {
@@ -813,7 +860,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 }
                 const int pfx = wave_inclusive_scan(pieces);
                 const int my_first = pfx - pieces;             // this column's first piece
-                col.place = (unsigned int)(my_first | z_first << 12 | z_len << 22);
+                col.place = (z_first - kPiece * my_first) * 1024 + (z_first + z_len);
                 if (!COUNT) col.bxy = kxy < kPow ? bpow[kxy] : (pieces ? beta_pow_slow(beta, kxy) : 0.f);
                 const int n_pieces = __builtin_amdgcn_readlane(pfx, 63);
                 // columns with pieces, packed in order
@@ -822,37 +869,31 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     wc[__builtin_amdgcn_mbcnt_hi((unsigned int)(live >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)live, 0u))] = col;
 
                 // ---- pieces are dealt to lanes ----
-                // Piece p belongs to the last column that starts at or before it.  Every column sets the bit of
-                // its first piece in a bit map; a piece's column is then a count of bits, not a search.
+                // Piece p belongs to the last column that starts at or before it.  Every column but a chunk's first sets
+                // bit f - 1 of a bit map, f its first piece; a piece's column is then a count of the bits below it.
                 unsigned int* starts = piece_starts[wave];
                 constexpr int kChunk = 32 * kStartWords;
                 for (int chunk = 0; chunk < n_pieces; chunk += kChunk) {
                     if (lane < kStartWords) starts[lane] = 0u;
                     wave_sync_lds();
-                    if (pieces > 0 && my_first >= chunk && my_first < chunk + kChunk)
-                        atomicOr(&starts[(my_first - chunk) >> 5], 1u << (my_first & 31));
-                    int before = __popcll(__ballot(pieces > 0 && my_first < chunk));     // columns begun in earlier chunks
+                    const int bit = my_first - chunk - 1;
+                    if (pieces > 0 && bit >= 0 && bit < kChunk) atomicOr(&starts[bit >> 5], 1u << (bit & 31));
+                    int before = __popcll(__ballot(pieces > 0 && bit < 0)) - 1;       // the column of the chunk's first piece
                     wave_sync_lds();
                     const int chunk_end = min(n_pieces, chunk + kChunk);
                     for (int p0 = chunk; p0 < chunk_end; p0 += 64) {
                         const uint2 m = *reinterpret_cast<const uint2*>(&starts[(p0 - chunk) >> 5]);   // pieces p0 .. p0 + 63
-                        // starts in [p0, p0 + lane]: bit 0, and the bits below this lane of the map moved down by one
-                        const unsigned int s_lo = (m.x >> 1) | (m.y << 31), s_hi = m.y >> 1;
-                        const int upto = (int)(m.x & 1u) + (int)__builtin_amdgcn_mbcnt_hi(s_hi, __builtin_amdgcn_mbcnt_lo(s_lo, 0u));
+                        const int mine = (int)__builtin_amdgcn_mbcnt_hi(m.y, __builtin_amdgcn_mbcnt_lo(m.x, (unsigned int)before));
                         const int p = p0 + lane;
                         if (p < chunk_end) {
-                            const Column c = wc[before + upto - 1];
-                            const int done = (p - (int)(c.place & 4095u)) * kPiece;       // images of the column's earlier pieces
-                            double cxy = 0.0;      // beta^kxy / (4 pi) * 2^56
-                            if (!COUNT) cxy = (double)c.bxy * (0.07957747154594767 * 0x1p56);
+                            const Column c = wc[mine];
                             if (fast) {
-                                const int first = (int)(c.place >> 12 & 1023u) + done;
-                                const int len = min(kPiece, (int)(c.place >> 22) - done);
-                                if (far_item) walk_piece_table<COUNT, true>(wctx, c.a, cxy, ztab + first, len, hist, hist32);
-                                else walk_piece_table<COUNT, false>(wctx, c.a, cxy, ztab + first, len, hist, hist32);
+                                const int first = (c.place >> 10) + __mul24(kPiece, p);
+                                const int len = min(kPiece, (c.place & 1023) - first);
+                                walk_piece_table<COUNT>(wctx, c.a, (double)c.bxy, ztab, first, len, hist);
                                 if (VISITS) walked += (unsigned long long)len;
                             } else {
-                                walk_column_direct<COUNT>(wctx, az, c.a, cxy, nmz, hist, hist32);
+                                walk_column_direct<COUNT>(wctx, az, c.a, (double)c.bxy * kAmplitude, nmz, hist);
                                 if (VISITS) walked += (unsigned long long)niz;
                             }
                         }

@@ -1,0 +1,47 @@
+"""Images on either side of 2.6 m (walked apart from the rest) and pieces of every length, against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import aug_oracle as O
+from tests.parity import RIR_TOL, dev, rir_err
+
+pytestmark = pytest.mark.gpu
+C = 343.0
+
+
+@pytest.fixture(scope="module")
+def aug():
+    import torch
+    from paper_1912_11040_amd.binding import Augmenter
+    assert torch.cuda.is_available()
+    a = Augmenter(0)
+    yield a
+    a.close()
+
+
+def _rooms(fs):
+    """Distances in steps across the boundary, microphone on or near the source, small and large rooms."""
+    rows = []
+    for d in (0.001, 0.2, 2.3, 2.54, 2.56, 2.6, 2.6 + 0.24 * C / fs, 2.6 + 0.26 * C / fs, 2.7):
+        for beta in (0.0, 0.8, 1.0):
+            rows.append([6.0, 5.0, 3.0, 1.5, 2.0, 1.25, 1.5 + d, 2.0, 1.25, beta])
+        rows.append([1.0, 2.9, 0.4, 0.5, 0.05, 0.21, 0.5, 0.05 + min(d, 2.8), 0.2, 0.9])
+    return np.array(rows, np.float32)
+
+
+@pytest.mark.parametrize("fs", [1000.0, 16000.0, 48000.0])
+@pytest.mark.parametrize("length", [1, 62, 121, 122, 128, 700])
+def test_near_images(aug, fs, length):
+    import torch
+    g = _rooms(fs)
+    print(f"case: fs={fs} length={length}", flush=True)
+    h = torch.full((len(g), length), float("nan"), dtype=torch.float32, device="cuda")
+    cnt = torch.full((len(g), length), -7, dtype=torch.int32, device="cuda")
+    if fs < 2000 and length > 200:
+        length = 200                                    # (more would be millions of images in the small room)
+        h, cnt = h[:, :length].contiguous(), cnt[:, :length].contiguous()
+    aug.aug_rir_batch(dev(g), length, fs, C, h, cnt)
+    torch.cuda.synchronize()
+    h_ref, cnt_ref = O.rir_batch(g, length, fs, C)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
+    assert rir_err(h.cpu().numpy(), h_ref) <= RIR_TOL
