@@ -414,20 +414,20 @@ int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
 
 // ---- stage drivers: arguments already validated, packing already synchronised ----
 
-int run_rir(aug_ctx* ctx, int n_rir, const float* geom, int rir_len, float fs, float c, float* rir_out,
+int run_rir(aug_ctx* ctx, int n_rir, const aug::Rooms& rooms, int rir_len, float fs, float c, float* rir_out,
             int32_t* tap_count_out) {
     const double k = (double)fs / (double)c;
     AUG_TRY(prepare_rir(ctx, n_rir, rir_len));
     const int n_groups = 2 * ctx->n_cu;
     AUG_TRY(mark(ctx, -1));
-    AUG_HIP(aug::launch_rir_plan(ctx->stream, n_groups, n_rir, geom, rir_len, k, ctx->rir_items.ptr,
+    AUG_HIP(aug::launch_rir_plan(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
                                  ctx->rir_ctrl.as<int>()), "rir plan kernel");
     AUG_TRY(mark(ctx, AUG_STAGE_OTHER));
-    AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, geom, rir_len, k, ctx->rir_items.ptr,
+    AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
                             ctx->rir_ctrl.as<int>(), rir_out, nullptr, false), "rir kernel");
     AUG_TRY(mark(ctx, AUG_STAGE_RIR));
     if (tap_count_out) {
-        AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, geom, rir_len, k, ctx->rir_items.ptr,
+        AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
                                 ctx->rir_ctrl.as<int>(), nullptr, tap_count_out, true),
                 "rir count kernel");
         AUG_TRY(mark(ctx, AUG_STAGE_OTHER));
@@ -641,7 +641,7 @@ int aug_destroy(aug_ctx* ctx) {
     }
     DeviceBuffer* bufs[] = {&ctx->d_offsets, &ctx->d_frame_offsets, &ctx->d_conv_items, &ctx->d_frame_items,
                             &ctx->d_conv_first,
-                            &ctx->rir_items, &ctx->rir_ctrl, &ctx->mic_rows, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab, &ctx->mel_lanes,
+                            &ctx->rir_items, &ctx->rir_ctrl, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab, &ctx->mel_lanes,
                             &ctx->window};
     for (DeviceBuffer* b : bufs) b->release();
     for (DeviceBuffer& b : ctx->twiddle) b.release();
@@ -699,7 +699,7 @@ int aug_rir_batch(aug_ctx* ctx, int n_rir, const float* geom, int rir_len, float
     if (!geom || !rir_out) return fail(ctx, AUG_ERR_INVALID_ARG, "geom or rir_out is null");
     if ((int64_t)n_rir * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
-    return run_rir(ctx, n_rir, geom, rir_len, fs, c, rir_out, tap_count_out);
+    return run_rir(ctx, n_rir, {geom, nullptr, 1}, rir_len, fs, c, rir_out, tap_count_out);
 }
 
 int aug_rir_visited_images(aug_ctx* ctx, int n_rir, const float* geom, int rir_len, float fs, float c,
@@ -717,10 +717,11 @@ int aug_rir_visited_images(aug_ctx* ctx, int n_rir, const float* geom, int rir_l
     AUG_TRY(grow(ctx, ctx->visits, sizeof(unsigned long long), "visit counter"));
     const double k = (double)fs / (double)c;
     const int n_groups = 2 * ctx->n_cu;
+    const aug::Rooms rooms{geom, nullptr, 1};
     AUG_HIP(aug::launch_fill_u32(ctx->stream, ctx->visits.ptr, 0u, 2), "visit counter clear");
-    AUG_HIP(aug::launch_rir_plan(ctx->stream, n_groups, n_rir, geom, rir_len, k, ctx->rir_items.ptr,
+    AUG_HIP(aug::launch_rir_plan(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
                                  ctx->rir_ctrl.as<int>()), "rir plan kernel");
-    AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, geom, rir_len, k, ctx->rir_items.ptr, ctx->rir_ctrl.as<int>(),
+    AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr, ctx->rir_ctrl.as<int>(),
                             rir_out, nullptr, false, ctx->visits.as<unsigned long long>()),
             "rir kernel");
     unsigned long long v = 0;
@@ -741,13 +742,7 @@ int aug_rir_mics_batch(aug_ctx* ctx, int n_rir, int n_mic, const float* geom, co
     const int64_t n_rows = (int64_t)n_rir * n_mic;
     if (n_rows * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
-    // rewriting the rows is ordered after an earlier call's kernels by the stream; growing the buffer frees
-    // the old one, which waits for them
-    AUG_TRY(grow(ctx, ctx->mic_rows, sizeof(float) * 10 * (size_t)n_rows, "microphone rows"));
-    AUG_TRY(mark(ctx, -1));
-    AUG_HIP(aug::launch_rir_mic_rows(ctx->stream, n_rir, n_mic, geom, mics, ctx->mic_rows.as<float>()), "microphone rows kernel");
-    AUG_TRY(mark(ctx, AUG_STAGE_OTHER));
-    return run_rir(ctx, (int)n_rows, ctx->mic_rows.as<float>(), rir_len, fs, c, rir_out, tap_count_out);
+    return run_rir(ctx, (int)n_rows, {geom, mics, n_mic}, rir_len, fs, c, rir_out, tap_count_out);
 }
 
 int aug_convolve_mix_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const float* speech, int n_noise,
@@ -927,7 +922,7 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     AUG_TRY(prepare_rir(ctx, n_utt * n_src, rir_len));
     AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
     AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
-    AUG_TRY(run_rir(ctx, n_utt * n_src, geom, rir_len, fs, c, rir, nullptr));
+    AUG_TRY(run_rir(ctx, n_utt * n_src, {geom, nullptr, 1}, rir_len, fs, c, rir, nullptr));
     AUG_TRY(run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out));
     if (mixed_out || total == 0) return run_mel(ctx, n_utt, mixed_out, cfg, feats_out);
     // The mixture itself is not wanted: the front end adds the scaled reverberated noises to the

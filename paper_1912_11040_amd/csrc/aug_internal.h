@@ -92,7 +92,6 @@ struct aug_ctx {
     aug::DeviceBuffer rir_items;         // Item [n_rir * items_per_response]
     aug::DeviceBuffer rir_ctrl;          // int [rir_ctrl_ints()]: item count, next item, class counters
     aug::DeviceBuffer visits;            // one 64-bit counter (aug_rir_visited_images)
-    aug::DeviceBuffer mic_rows;          // float [n_rir * n_mic][10]: one geometry row per microphone
 
     // intermediate results
     aug::DeviceBuffer rir;               // float [n_rir][rir_len]            (pipeline only)
@@ -130,17 +129,22 @@ namespace aug {
 // rir_out float [n_rir][rir_len] or, if rir_out is null, tap counts cnt_out int32 [n_rir][rir_len].
 // With `visits` (device, one 64-bit counter, zero on entry) the amplitude pass runs in a measuring
 // instantiation that adds the number of images it walked.
+// Response r is that of geometry row r, or, with mics (float [n_rir][3]), of row r / n_mic with its microphone replaced
+// by mics[r].
+struct Rooms {
+    const float* geom;           // device, float [n_rir / n_mic][10]
+    const float* mics;           // device, may be null
+    int n_mic;                   // used with mics
+};
 int rir_items_per_response(int rir_len);
 size_t rir_item_bytes();
 int rir_ctrl_ints();
-hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const float* geom, int rir_len, double fs_over_c,
+hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const Rooms& rooms, int rir_len, double fs_over_c,
                            void* items, int* ctrl);
-hipError_t launch_rir(hipStream_t s, int n_groups, int n_rir, const float* geom, int rir_len, double fs_over_c,
+hipError_t launch_rir(hipStream_t s, int n_groups, int n_rir, const Rooms& rooms, int rir_len, double fs_over_c,
                       const void* items, int* ctrl, float* rir_out, int32_t* cnt_out,
                       bool restart, unsigned long long* visits = nullptr);
 
-// rows float [n_rir * n_mic][10]: geometry row r / n_mic with microphone mics[r] (float [n_rir][n_mic][3]).
-hipError_t launch_rir_mic_rows(hipStream_t s, int n_rir, int n_mic, const float* geom, const float* mics, float* rows);
 
 // Largest complex FFT size the convolution kernels are built for, and the size chosen for a response length.
 int conv_fft_size(int rir_len);

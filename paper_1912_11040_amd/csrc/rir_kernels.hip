@@ -94,6 +94,19 @@ __device__ inline bool room_ok(const float* g) {
            (g[9] >= 0.f) && (g[9] <= 1.f);
 }
 
+// The geometry of one response: its room's row, with the microphone replaced where a room has several.
+struct Room { float g[10]; };
+__device__ inline Room load_room(const Rooms& rooms, int rir) {
+    const float* row = rooms.geom + (size_t)(rooms.mics ? rir / rooms.n_mic : rir) * 10;
+    Room r;
+#pragma unroll
+    for (int i = 0; i < 10; ++i) r.g[i] = row[i];
+    if (rooms.mics)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) r.g[6 + i] = rooms.mics[(size_t)rir * 3 + i];
+    return r;
+}
+
 struct Item { int rir, n0, n1, cls; };
 
 __device__ inline void wave_sync_lds() {
@@ -120,51 +133,54 @@ constexpr int kClasses = 32;            // cost classes for the order in which i
 constexpr int kCtrlWork = 2 + 2 * kClasses;
 constexpr int kCtrlInts = kCtrlWork + 1;
 
-// Fraction of the images at distance d that the reflection cut keeps: an image in direction u has
-// about d (|ux|/Lx + |uy|/Ly + |uz|/Lz) reflections, so this is the share of directions whose
-// reflections per metre stay under cut / d, counted on a fixed 8 x 8 equal-area lattice of an octant.
-__device__ inline float kept_fraction(const float* g, float log2_beta, float d) {
-    if (!(log2_beta < 0.f) || !(d > 1e-3f)) return 1.f;
-    const float per_metre = (__log2f(12.566371f * d) - 57.f) / (log2_beta * d);
-    const float ix = 1.f / g[0], iy = 1.f / g[1], iz = 1.f / g[2];
-    int kept = 0;
-    for (int i = 0; i < 8; ++i) {
-        const float uz = (i + 0.5f) * 0.125f, rho = sqrtf(1.f - uz * uz);
-        for (int j = 0; j < 8; ++j) {
-            float sn, cs;
-            __sincosf((j + 0.5f) * 0.19634954f, &sn, &cs);
-            kept += (rho * cs * ix + rho * sn * iy + uz * iz) <= per_metre;
+// Estimate of the work in a response's taps [n0, n1), in units of one image visit: the images it keeps plus about twelve
+// visits' worth of set-up for every live (x image, y image) column inside its outer radius.
+// What the reflection cut keeps: an image in direction u at distance d has about d (|ux|/Lx + |uy|/Ly + |uz|/Lz)
+// reflections, so it is the share of directions whose reflections per metre stay under cut / d.  Over an octant that
+// sum runs from the smallest of the 1/L to the length of the vector (1/Lx, 1/Ly, 1/Lz); the share below a fraction x of
+// that range is x^2.5 to within 0.02 on average over rooms of 3 x 3 x 2.4 to 10 x 8 x 4 m.  (Counting a lattice of
+// directions for every item, with library divisions and powers, took most of the plan's time.)
+struct WorkModel {
+    float images, columns;       // per cubic tap, per square tap
+    float metres, inv_log2_beta; // per tap; 0: no cut
+    float least, inv_range;      // of the reflections per metre
+    __device__ float operator()(float n0, float n1) const {
+        float kept = 1.f, kept_columns = 1.f;
+        const float d = 0.5f * (n0 + n1) * metres;
+        if (inv_log2_beta < 0.f && d > 1e-3f) {
+            const float per_metre = (__builtin_amdgcn_logf(12.566371f * d) - 57.f) * inv_log2_beta * __builtin_amdgcn_rcpf(d);
+            const float x = fminf(fmaxf((per_metre - least) * inv_range, 0.19f), 1.f);     // (0.19^2.5 = 1/64)
+            const float root = __builtin_amdgcn_sqrtf(x);
+            kept = x * x * root;
+            kept_columns = x * root;
         }
+        return images * (n1 * n1 * n1 - n0 * n0 * n0) * kept + columns * n1 * n1 * kept_columns;
     }
-    return fmaxf((float)kept * (1.f / 64.f), 1.f / 128.f);
-}
+};
 
-// Work of one item in units of one image visit: the images it keeps plus about twelve visits' worth
-// of set-up for every live (x image, y image) column inside its outer radius.
-__device__ inline float item_cost(const float* g, float log2_beta, float est_images, float rir_len, float n0, float n1,
-                                  float metres_per_tap) {
-    const float share = (n1 * n1 * n1 - n0 * n0 * n0) / (rir_len * rir_len * rir_len);
-    const float f = kept_fraction(g, log2_beta, 0.5f * (n0 + n1) * metres_per_tap);
-    const float r_out = n1 * metres_per_tap;
-    const float columns = 3.14159265f * r_out * r_out / (g[0] * g[1]);
-    return est_images * share * f + 12.f * columns * __powf(f, 0.6667f);
+__device__ inline WorkModel work_model(const float* g, double k_fs_c) {
+    WorkModel m;
+    m.metres = __builtin_amdgcn_rcpf((float)k_fs_c);
+    const float ix = __builtin_amdgcn_rcpf(g[0]), iy = __builtin_amdgcn_rcpf(g[1]), iz = __builtin_amdgcn_rcpf(g[2]);
+    m.images = 4.18879f * (m.metres * m.metres) * m.metres * ix * iy * iz;
+    m.columns = 12.f * 3.14159265f * (m.metres * m.metres) * ix * iy;
+    m.inv_log2_beta = (g[9] > 0.f && g[9] < 1.f) ? __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(g[9])) : 0.f;
+    m.least = fminf(fminf(ix, iy), iz);
+    m.inv_range = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ix * ix + iy * iy + iz * iz) - m.least);
+    return m;
 }
 
 // estimated work of a whole response (0 for a room that is not usable)
 __device__ inline float response_work(const float* g, int rir_len, double k_fs_c) {
-    if (!room_ok(g)) return 0.f;
-    const double radius = (double)rir_len / k_fs_c;
-    const float log2_beta = (g[9] > 0.f && g[9] < 1.f) ? __log2f(g[9]) : 0.f;
-    const float est = 4.18879f * (float)(radius * radius * radius) / (g[0] * g[1] * g[2]);
-    return item_cost(g, log2_beta, est, (float)rir_len, 0.f, (float)rir_len, (float)(1.0 / k_fs_c));
+    return room_ok(g) ? work_model(g, k_fs_c)(0.f, (float)rir_len) : 0.f;
 }
 
 // one thread per response: the batch's estimated work (an integer sum, so it does not depend on the order)
-__global__ void rir_work_kernel(int n_rir, const float* __restrict__ geom, int rir_len, double k_fs_c,
+__global__ void rir_work_kernel(int n_rir, Rooms rooms, int rir_len, double k_fs_c,
                                 int* __restrict__ ctrl) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     int units = 0;
-    if (r < n_rir) units = (int)fminf(response_work(geom + (size_t)r * 10, rir_len, k_fs_c) / kWorkUnit, 500000.f) + 1;
+    if (r < n_rir) units = (int)fminf(response_work(load_room(rooms, r).g, rir_len, k_fs_c) / kWorkUnit, 500000.f) + 1;
     for (int off = 32; off > 0; off >>= 1) units += __shfl_down(units, off, 64);      // one atomic per wavefront
     if ((threadIdx.x & 63) == 0 && units) atomicAdd(&ctrl[kCtrlWork], units);
 }
@@ -174,145 +190,156 @@ __device__ inline float item_target(int units, int n_groups) {
     return fminf(fmaxf(kWorkUnit * (float)units / ((float)n_groups * kItemsPerGroup), kMinTargetWork), kMaxTargetWork);
 }
 
-constexpr int kMaxBounds = kMaxShells + AUG_MAX_RIR_LEN / kMaxTaps + 4;
-
-// Cut the taps of a response of estimated work `work` into shells of about equal image count (equal volume), at most kMaxTaps wide:
-// bounds[i] is the lower bound of shell i, outermost shell first; returns their number.
+// Cut the taps of a response of estimated work `work` into shells of about equal image count (equal volume), at most
+// kMaxTaps wide: calls take(lower, upper) for every shell, outermost first; returns their number.
 // Shells are cut from the outside in: every shell sets up all (x, y) columns inside its outer radius, so
 // where the tap limit, not the work, decides the width it is the inner shells, with few columns, that
 // should be the many and the narrow ones, and the left-over sliver belongs at the centre.
-__device__ inline int cut_shells(float work, int rir_len, float target, int items_per_rir, int (&bounds)[kMaxBounds]) {
+// (Single precision: the cuts need not be exact, and the library's cube root in double precision took a microsecond
+// per shell.  Callers that first count and then write run it twice rather than keep a table of bounds.)
+template <class Take>
+__device__ inline int cut_shells(float work, int rir_len, float target, int items_per_rir, Take take) {
     const float shells = fminf(fmaxf(ceilf(work / target), 1.f), (float)kMaxShells);
-    const double L3 = (double)rir_len * rir_len * rir_len;
-    const double step = L3 / (double)shells;
+    const float step = (float)rir_len * (float)rir_len * (float)rir_len / shells;
     int count = 0, hi = rir_len;
     while (hi > 0 && count < items_per_rir - 1) {
-        const double h3 = (double)hi * hi * hi;
-        int lo = h3 > step ? (int)cbrt(h3 - step) : 0;
+        const float inner = (float)hi * (float)hi * (float)hi - step;
+        int lo = inner > 0.f ? (int)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf(inner) * (1.f / 3.f)) : 0;
         lo = min(lo, hi - kMinTaps);
         lo = max(max(lo, hi - kMaxTaps), 0);
         if (lo < kMinTaps && hi <= kMaxTaps) lo = 0;              // no sliver at the centre
-        bounds[count++] = lo;
+        take(lo, hi);
+        ++count;
         hi = lo;
     }
     while (hi > 0 && count < items_per_rir) {                       // out of table space: cannot happen with the
         const int lo = max(hi - kMaxTaps, 0);                       // sizes chosen by the host
-        bounds[count++] = lo;
+        take(lo, hi);
+        ++count;
         hi = lo;
     }
     return count;
 }
 
 // cost class of an item (0 = heaviest)
-__device__ inline int item_class(const float* g, int rir_len, double k_fs_c, int n0, int n1) {
-    if (!room_ok(g)) return kClasses - 1;
-    const double radius = (double)rir_len / k_fs_c;
-    const float est = 4.18879f * (float)(radius * radius * radius) / (g[0] * g[1] * g[2]);
-    const float log2_beta = (g[9] > 0.f && g[9] < 1.f) ? __log2f(g[9]) : 0.f;
-    const float cost = item_cost(g, log2_beta, est, (float)rir_len, (float)n0, (float)n1, (float)(1.0 / k_fs_c));
-    return min(max((int)(2.5f * __log2f(3.2e7f / fmaxf(cost, 1.f))), 0), kClasses - 1);
+__device__ inline int item_class(const WorkModel& model, bool ok, int n0, int n1) {
+    if (!ok) return kClasses - 1;
+    const float cost = model((float)n0, (float)n1);
+    return min(max((int)(2.5f * (24.93f - __builtin_amdgcn_logf(fmaxf(cost, 1.f)))), 0), kClasses - 1);     // 2^24.93 = 3.2e7
 }
 
-// One thread per response: cut its taps into shells and append them to the unsorted item table.
-__global__ void rir_plan_kernel(int n_rir, const float* __restrict__ geom, int rir_len, double k_fs_c,
-                                Item* __restrict__ unsorted, int items_per_rir, int* __restrict__ ctrl, int n_groups) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n_rir) return;
-    const float* g = geom + (size_t)r * 10;
-    int bounds[kMaxBounds];
-    const int count = cut_shells(response_work(g, rir_len, k_fs_c), rir_len, item_target(ctrl[kCtrlWork], n_groups),
-                                 items_per_rir, bounds);
-    const int base = atomicAdd(&ctrl[0], count);
-    int top = rir_len;
-    for (int i = 0; i < count; ++i) {
-        unsorted[base + i] = Item{r, bounds[i], top, kClasses - 1};
-        top = bounds[i];
-    }
-}
-
-// The whole plan in one work group, for batches of at most kPlanThreads responses (four launches and a clear
-// cost more than the work there): a thread per response for the batch's work and the shells (their places in
-// the table by a scan, not by atomics), then all threads over the items for their classes and the counting
-// sort.  Leaves ctrl[0] = number of items, ctrl[1] = 0.
-constexpr int kPlanThreads = 1024;
-__global__ __launch_bounds__(kPlanThreads) void rir_plan_all_kernel(
-    int n_rir, const float* __restrict__ geom, int rir_len, double k_fs_c, Item* __restrict__ sorted,
-    Item* __restrict__ unsorted, int items_per_rir, int* __restrict__ ctrl, int n_groups) {
-    __shared__ int part[kPlanThreads / 64];
-    __shared__ int census[kClasses], first_slot[kClasses], cursor[kClasses];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (tid < kClasses) census[tid] = cursor[tid] = 0;
-    const int r = tid;                                 // this thread's response, if any
-    const float* g = geom + (size_t)min(r, n_rir - 1) * 10;
-
-    const float work = r < n_rir ? response_work(g, rir_len, k_fs_c) : 0.f;
-    int units = r < n_rir ? (int)fminf(work / kWorkUnit, 500000.f) + 1 : 0;
-    for (int off = 32; off > 0; off >>= 1) units += __shfl_down(units, off, 64);
-    if (lane == 0) part[wave] = units;
-    __syncthreads();
-    int total_units = 0;
-    for (int w = 0; w < kPlanThreads / 64; ++w) total_units += part[w];
-    const float target = item_target(total_units, n_groups);
-    __syncthreads();
-
-    int bounds[kMaxBounds];
-    const int count = r < n_rir ? cut_shells(work, rir_len, target, items_per_rir, bounds) : 0;
-    const int incl = wave_inclusive_scan(count);
-    if (lane == 63) part[wave] = incl;
-    __syncthreads();
-    int before = 0, n_items = 0;
-    for (int w = 0; w < kPlanThreads / 64; ++w) {
-        if (w < wave) before += part[w];
-        n_items += part[w];
-    }
-    {
-        const int base = before + incl - count;
-        int top = rir_len;
-        for (int i = 0; i < count; ++i) {
-            unsorted[base + i] = Item{r, bounds[i], top, kClasses - 1};
-            top = bounds[i];
-        }
-    }
-    __syncthreads();                                   // the group's writes to `unsorted` are visible to it
-    for (int i = tid; i < n_items; i += kPlanThreads) {
-        const Item it = unsorted[i];
-        const int cls = item_class(geom + (size_t)it.rir * 10, rir_len, k_fs_c, it.n0, it.n1);
-        unsorted[i].cls = cls;                         // (read back by this same thread below)
-        atomicAdd(&census[cls], 1);
-    }
-    __syncthreads();
-    if (tid == 0) {
-        int at = 0;
-        for (int c = 0; c < kClasses; ++c) {
-            first_slot[c] = at;
-            at += census[c];
-        }
-        ctrl[0] = n_items;
-        ctrl[1] = 0;
-    }
-    __syncthreads();
-    for (int i = tid; i < n_items; i += kPlanThreads) {
-        const Item it = unsorted[i];
-        sorted[first_slot[it.cls] + atomicAdd(&cursor[it.cls], 1)] = it;
-    }
-}
-
-// one thread per item: its cost class (0 = heaviest), and the class census
-__global__ void rir_classify_kernel(const float* __restrict__ geom, int rir_len, double k_fs_c,
-                                    Item* __restrict__ unsorted, int* __restrict__ ctrl) {
-    // (the census is taken per work group in LDS first: one global atomic per class and group, not per item)
+// One thread per response: cut its taps into shells and append them to the unsorted item table, with their cost classes
+// and the class census (taken in LDS first: one global atomic per class and group, not per item).
+__global__ void rir_plan_kernel(int n_rir, Rooms rooms, int rir_len, double k_fs_c, Item* __restrict__ unsorted,
+                                int items_per_rir, int* __restrict__ ctrl, int n_groups) {
     __shared__ int census[kClasses];
     if (threadIdx.x < kClasses) census[threadIdx.x] = 0;
     __syncthreads();
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < ctrl[0]) {
-        const Item it = unsorted[i];
-        const int cls = item_class(geom + (size_t)it.rir * 10, rir_len, k_fs_c, it.n0, it.n1);
-        unsorted[i].cls = cls;
-        atomicAdd(&census[cls], 1);
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r < n_rir) {
+        const Room room = load_room(rooms, r);
+        const float work = response_work(room.g, rir_len, k_fs_c), target = item_target(ctrl[kCtrlWork], n_groups);
+        const int count = cut_shells(work, rir_len, target, items_per_rir, [](int, int) {});
+        const WorkModel model = work_model(room.g, k_fs_c);
+        const bool ok = room_ok(room.g);
+        int at = atomicAdd(&ctrl[0], count);
+        cut_shells(work, rir_len, target, items_per_rir, [&](int lo, int hi) {
+            const int cls = item_class(model, ok, lo, hi);
+            unsorted[at++] = Item{r, lo, hi, cls};
+            atomicAdd(&census[cls], 1);
+        });
     }
     __syncthreads();
     if (threadIdx.x < kClasses && census[threadIdx.x]) atomicAdd(&ctrl[2 + threadIdx.x], census[threadIdx.x]);
+}
+
+// The whole plan in one work group, for batches of at most kPlanRows * kPlanThreads responses (beyond, the four launches
+// of the kernels around this one).  A thread per
+// response, up to kPlanRows in turn, for the batch's work, the shells (their places in the table by a scan, not by
+// atomics) and their classes, then all threads over the items for the counting sort.  Between the two the items lie in
+// LDS, or in `unsorted` if there are more than it holds.  Leaves ctrl[0] = number of items, ctrl[1] = 0.
+// Latency bound: the 16 waves of one CU.
+constexpr int kPlanThreads = 1024, kPlanRows = 4;
+constexpr int kPlanItems = 8192;
+static_assert(AUG_MAX_RIR_LEN < 1 << 16 && kPlanRows * kPlanThreads <= 1 << 12 && kClasses <= 1 << 5, "the packing of items in LDS");
+__global__ __launch_bounds__(kPlanThreads) void rir_plan_all_kernel(
+    int n_rir, Rooms rooms, int rir_len, double k_fs_c, Item* __restrict__ sorted,
+    Item* __restrict__ unsorted, int items_per_rir, int* __restrict__ ctrl, int n_groups) {
+    __shared__ unsigned long long held[kPlanItems];
+    __shared__ int part[2][kPlanThreads / 64];
+    __shared__ int census[kClasses], cursor[kClasses];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid < kClasses) census[tid] = 0;
+
+    float work[kPlanRows];
+    int units = 0;
+#pragma unroll
+    for (int k = 0; k < kPlanRows; ++k) {
+        const int r = tid + k * kPlanThreads;
+        work[k] = 0.f;
+        if (r < n_rir) {
+            work[k] = response_work(load_room(rooms, r).g, rir_len, k_fs_c);
+            units += (int)fminf(work[k] * (1.f / kWorkUnit), 500000.f) + 1;
+        }
+    }
+    units = wave_inclusive_scan(units);
+    if (lane == 63) part[0][wave] = units;
+    __syncthreads();
+    int total_units = 0;
+    for (int w = 0; w < kPlanThreads / 64; ++w) total_units += part[0][w];
+    const float target = item_target(total_units, n_groups);
+
+    int count = 0;
+#pragma unroll
+    for (int k = 0; k < kPlanRows; ++k)
+        if (tid + k * kPlanThreads < n_rir) count += cut_shells(work[k], rir_len, target, items_per_rir, [](int, int) {});
+    const int incl = wave_inclusive_scan(count);
+    if (lane == 63) part[1][wave] = incl;
+    __syncthreads();
+    int at = incl - count, n_items = 0;
+    for (int w = 0; w < kPlanThreads / 64; ++w) {
+        if (w < wave) at += part[1][w];
+        n_items += part[1][w];
+    }
+    const bool in_lds = n_items <= kPlanItems;
+    auto pack = [](const Item& it) {
+        return (unsigned long long)(unsigned int)(it.n0 | it.n1 << 16) | (unsigned long long)(unsigned int)(it.rir | it.cls << 12) << 32;
+    };
+    auto get = [&](int i) {
+        if (!in_lds) return unsorted[i];
+        const unsigned int lo = (unsigned int)held[i], hi = (unsigned int)(held[i] >> 32);
+        return Item{(int)(hi & 4095u), (int)(lo & 65535u), (int)(lo >> 16), (int)(hi >> 12)};
+    };
+#pragma unroll
+    for (int k = 0; k < kPlanRows; ++k) {
+        const int r = tid + k * kPlanThreads;
+        if (r >= n_rir) continue;
+        const Room room = load_room(rooms, r);
+        const WorkModel model = work_model(room.g, k_fs_c);
+        const bool ok = room_ok(room.g);
+        cut_shells(work[k], rir_len, target, items_per_rir, [&](int lo, int hi) {
+            const Item it{r, lo, hi, item_class(model, ok, lo, hi)};
+            if (in_lds) held[at] = pack(it);
+            else unsorted[at] = it;
+            ++at;
+            atomicAdd(&census[it.cls], 1);
+        });
+    }
+    __syncthreads();                                   // (the group's writes to `unsorted` are visible to it)
+    if (wave == 0) {
+        const int mine = lane < kClasses ? census[lane] : 0;
+        const int incl_classes = wave_inclusive_scan(mine);
+        if (lane < kClasses) cursor[lane] = incl_classes - mine;
+        if (lane == 0) {
+            ctrl[0] = n_items;
+            ctrl[1] = 0;
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < n_items; i += kPlanThreads) {
+        const Item it = get(i);
+        sorted[atomicAdd(&cursor[it.cls], 1)] = it;
+    }
 }
 
 // Items move to their class's stretch of the sorted table, heaviest class first: persistent groups then take
@@ -644,7 +671,7 @@ __device__ inline int count_below(const AxisCount& a, double bound) {
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
 template <bool COUNT, bool VISITS = false>
 __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
-    const float* __restrict__ geom, int rir_len, double k_fs_c, const Item* __restrict__ items,
+    Rooms rooms, int rir_len, double k_fs_c, const Item* __restrict__ items,
     int* __restrict__ ctrl, float* __restrict__ rir_out,
     int32_t* __restrict__ cnt_out, unsigned long long* __restrict__ visits = nullptr) {
     __shared__ unsigned long long hist[(COUNT ? kMaxTaps / 2 : kMaxTaps) + 2];     // first and last slot are never read
@@ -672,7 +699,8 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
         if (it >= n_items) break;
         const Item item = items[it];
         const int n0 = item.n0, n1 = item.n1, n_taps = n1 - n0;
-        const float* g = geom + (size_t)item.rir * 10;
+        const Room room = load_room(rooms, uni(item.rir));
+        const float* g = room.g;
 
         if (COUNT) {
             for (int i = tid; i <= n_taps + 1; i += kThreads) hist32[i] = 0u;
@@ -939,58 +967,39 @@ hipError_t launch_fill_u32(hipStream_t s, void* p, uint32_t v, int64_t n) {
     return hipGetLastError();
 }
 
-// One geometry row per (response, microphone): the row of the response with its microphone columns replaced.
-__global__ void rir_mic_rows_kernel(int n_rows, int n_mic, const float* __restrict__ geom, const float* __restrict__ mics,
-                                    float* __restrict__ rows) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;       // one thread per output value
-    if (i >= n_rows * 10) return;
-    const int row = i / 10, col = i - row * 10;
-    rows[i] = (col >= 6 && col < 9) ? mics[(size_t)row * 3 + (col - 6)] : geom[(size_t)(row / n_mic) * 10 + col];
-}
-
-hipError_t launch_rir_mic_rows(hipStream_t s, int n_rir, int n_mic, const float* geom, const float* mics, float* rows) {
-    const int n_rows = n_rir * n_mic;
-    if (n_rows <= 0) return hipSuccess;
-    rir_mic_rows_kernel<<<dim3((unsigned)((n_rows * 10 + 255) / 256)), dim3(256), 0, s>>>(n_rows, n_mic, geom, mics, rows);
-    return hipGetLastError();
-}
-
 int rir_items_per_response(int rir_len) { return kMaxShells + rir_len / kMaxTaps + 2; }
 size_t rir_item_bytes() { return sizeof(Item); }
 
 int rir_ctrl_ints() { return kCtrlInts; }
 
-hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const float* geom, int rir_len, double fs_over_c,
+hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const Rooms& rooms, int rir_len, double fs_over_c,
                            void* items, int* ctrl) {
     if (n_rir <= 0) return hipSuccess;
     // `items` holds the sorted table followed by the unsorted one
     const int per_rir = rir_items_per_response(rir_len);
     Item* sorted = static_cast<Item*>(items);
     Item* unsorted = sorted + (size_t)n_rir * per_rir;
-    if (n_rir <= kPlanThreads) {                             // one launch instead of five
-        rir_plan_all_kernel<<<dim3(1), dim3(kPlanThreads), 0, s>>>(n_rir, geom, rir_len, fs_over_c, sorted, unsorted,
+    if (n_rir <= kPlanRows * kPlanThreads) {                 // one launch instead of four
+        rir_plan_all_kernel<<<dim3(1), dim3(kPlanThreads), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, sorted, unsorted,
                                                                     per_rir, ctrl, n_groups);
         return hipGetLastError();
     }
     hipError_t e = launch_fill_u32(s, ctrl, 0u, kCtrlInts);
     if (e != hipSuccess) return e;
-    rir_work_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, geom, rir_len, fs_over_c, ctrl);
+    rir_work_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, ctrl);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    rir_plan_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, geom, rir_len, fs_over_c, unsorted, per_rir, ctrl,
+    rir_plan_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, unsorted, per_rir, ctrl,
                                                                     n_groups);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t max_items = (size_t)n_rir * per_rir;
     const int item_groups = (int)((max_items + 255) / 256);
-    rir_classify_kernel<<<dim3((unsigned)item_groups), dim3(256), 0, s>>>(geom, rir_len, fs_over_c, unsorted, ctrl);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
     rir_sort_items_kernel<<<dim3((unsigned)item_groups), dim3(256), 0, s>>>(unsorted, sorted, ctrl);
     return hipGetLastError();
 }
 
-hipError_t launch_rir(hipStream_t s, int n_groups, int n_rir, const float* geom, int rir_len, double fs_over_c,
+hipError_t launch_rir(hipStream_t s, int n_groups, int n_rir, const Rooms& rooms, int rir_len, double fs_over_c,
                       const void* items, int* ctrl, float* rir_out, int32_t* cnt_out,
                       bool restart, unsigned long long* visits) {
     if (n_rir <= 0) return hipSuccess;
@@ -1002,13 +1011,13 @@ hipError_t launch_rir(hipStream_t s, int n_groups, int n_rir, const float* geom,
     const Item* it = static_cast<const Item*>(items);
     if (rir_out && visits)
         rir_image_kernel<false, true><<<dim3((unsigned)n_groups), dim3(kThreads), 0, s>>>(
-            geom, rir_len, fs_over_c, it, ctrl, rir_out, nullptr, visits);
+            rooms, rir_len, fs_over_c, it, ctrl, rir_out, nullptr, visits);
     else if (rir_out)
         rir_image_kernel<false><<<dim3((unsigned)n_groups), dim3(kThreads), 0, s>>>(
-            geom, rir_len, fs_over_c, it, ctrl, rir_out, nullptr);
+            rooms, rir_len, fs_over_c, it, ctrl, rir_out, nullptr);
     else
         rir_image_kernel<true><<<dim3((unsigned)n_groups), dim3(kThreads), 0, s>>>(
-            geom, rir_len, fs_over_c, it, ctrl, nullptr, cnt_out);
+            rooms, rir_len, fs_over_c, it, ctrl, nullptr, cnt_out);
     return hipGetLastError();
 }
 
