@@ -20,6 +20,13 @@
 // the chip, sending every sample through HBM atomics more than doubled the kernel's time.
 // Per utterance a table holds, for every output bin, the lower source bin and the interpolation weight;
 // both come from fp64 arithmetic so that the choice of the bin pair matches a double-precision evaluation.
+//
+// What bounds it: latency.  The windows and transform buffers leave room for two wavefronts per SIMD, whose
+// vector units are busy half the time and the LDS two fifths of it (1450 vector and 218 LDS instructions per frame on 256
+// utterances of 1-16 s).  Twiddles folded into multiply-adds, zero inputs skipped, mirrored bins at constant distances from
+// two places and frames inside the utterance without range tests took that batch from 530 to 506 us, an utterance's
+// frames shared evenly among its wavefronts instead of in runs of 16 and a rest to 495.  Longer runs would save
+// atomics and lose in balance (at most 24 frames: 506 us; 32: 479, but a single utterance then has half the wavefronts).
 
 #include "aug_internal.h"
 #include "fft_lds.h"
@@ -31,7 +38,8 @@ constexpr int kWin = 800, kHop = 400, kFft = 2048;
 constexpr int kN = kFft / 2;                       // complex transform length
 constexpr int kBins = kN + 1;                      // real-spectrum bins 0..1024
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
-constexpr int kRun = 16;                           // consecutive frames overlap-added by one wavefront
+constexpr int kRun = 16;                           // consecutive frames overlap-added by one wavefront, at most
+constexpr int kMinRun = 8;                         // and at least: with runs of six or more no sample gets more than two shares
 constexpr int kFramesPerGroup = kRun * kWaves;
 constexpr int kSlot = lds_padded_size(kN) + 2;     // a wavefront's transform buffer plus the slot of bin 1024
 constexpr int kReach = kFft / 2;                   // a frame adds to [centre - kReach, centre + kReach)
@@ -56,18 +64,87 @@ __global__ void vtlp_table_kernel(int n_utt, const float* __restrict__ alpha, fl
 
 __device__ inline int frame_count(int len) { return len > 0 ? (len - 1) / kHop + 2 : 0; }
 
-// value of output bin q of the warped spectrum; X is in natural order in buf, bin 1024 in the extra slot
+// Value of output bin q of the warped spectrum; X is in natural order in buf, bin 1024 in the extra slot.  The table in
+// LDS holds the places of the two source bins in bytes, sixteen bits each, and the weight.
 __device__ inline float2 warped_bin(const float2* buf, const float2* s_tab, int q) {
-    const float2 jf = s_tab[q];
-    const int j = (int)jf.x;
-    const float2 lo = buf[lds_pad(j)], hi = buf[lds_pad(j + 1)];
-    return make_float2(lo.x + jf.y * (hi.x - lo.x), lo.y + jf.y * (hi.y - lo.y));
+    const float2 e = s_tab[q];
+    const unsigned int at = (unsigned int)__float_as_int(e.x);
+    const float2 lo = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(buf) + (at & 0xffffu));
+    const float2 hi = *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(buf) + (at >> 16));
+    return make_float2(lo.x + e.y * (hi.x - lo.x), lo.y + e.y * (hi.y - lo.y));
+}
+static_assert(sizeof(float2) * kSlot < 1 << 16, "places in the buffer have sixteen bits");
+
+// A lane's twiddles, the same for every frame: of the 1024 = 16 x 16 x 4 point transform's second pass w = W256^(lane mod
+// 16), of its third w = W1024^(lane + 64 i) for butterfly i.  From the table of W1024.
+struct LaneTwiddles {
+    Tw16Short second;
+    Tw4 third[4];
+};
+__device__ inline Tw4 tw4_of(const float2* __restrict__ tw, int k) {       // w = tw[k]
+    float c[3], t[3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        const float2 w = tw[(m + 1) * k];
+        c[m] = fabsf(w.x) < 0x1p-40f ? copysignf(0x1p-40f, w.x) : w.x;
+        t[m] = w.y / c[m];
+    }
+    return Tw4{t[0], t[1], t[2], c[0], c[1], c[2] / c[0]};
+}
+__device__ inline LaneTwiddles lane_twiddles(const float2* __restrict__ tw, int lane) {
+    LaneTwiddles w;
+    w.second.outer = tw4_of(tw, 16 * (lane & 15));
+    w.second.inner = tw4_of(tw, 4 * (lane & 15));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w.third[i] = tw4_of(tw, lane + 64 * i);
+    return w;
+}
+
+// A wavefront's 1024-point transform after its first butterflies; on return v[i] is output fft_out_index(lane, i).
+template <bool INV>
+__device__ inline void later_passes(float2 (&v)[16], float2* buf, const LaneTwiddles& w, int lane) {
+    fft_store<kN, 64, 16, 1>(v, buf, lane);
+    fft_sync<FftSync::Wave>();
+    fft_load<kN, 64, 16>(v, buf, lane);
+    fft_sync<FftSync::Wave>();
+    dft16_twiddled<INV>(v, w.second);
+    fft_store<kN, 64, 16, 16>(v, buf, lane);
+    fft_sync<FftSync::Wave>();
+    fft_load<kN, 64, 4>(v, buf, lane);
+    fft_sync<FftSync::Wave>();
+#pragma unroll
+    for (int i = 0; i < 4; ++i) dft4_twiddled<INV>(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3], w.third[i]);
+}
+
+// Forward 16-point DFT of values of which those in places 4 .. 11 are zero.
+__device__ inline void dft16_outer_inputs(float2 (&v)[16]) {
+#pragma unroll
+    for (int m2 = 0; m2 < 4; ++m2) {
+        const float2 a = v[m2], b = v[m2 + 12], ib = make_float2(-b.y, b.x);
+        v[m2] = cadd(a, b);
+        v[m2 + 4] = cadd(a, ib);
+        v[m2 + 8] = csub(a, b);
+        v[m2 + 12] = csub(a, ib);
+    }
+    dft16_inner<false, false>(v, 1.f, 1.f, 1.f);
+    dft16_transpose(v);
 }
 
 // Write positions [p0, p0 + 2 count) of the wavefront's window to the output and clear them.  Positions in
 // [excl_lo, excl_hi) receive nothing from other runs and are stored; the rest is added atomically.
 // p0, excl_lo and excl_hi are even, so a pair never straddles a boundary.
 __device__ inline void flush_window(float* acc, float* y, int len, int p0, int count, int excl_lo, int excl_hi, int lane) {
+    const int p1 = p0 + 2 * count;
+    if (p0 >= max(excl_lo, 0) && p1 <= min(excl_hi, len)) {      // the usual case, alike for the whole wavefront
+        for (int i = lane; i < count; i += 64) {
+            const int p = p0 + 2 * i;
+            float2* slot = reinterpret_cast<float2*>(acc + (p & (kFft - 1)));
+            const float2 s = *slot;
+            *slot = make_float2(0.f, 0.f);
+            *reinterpret_cast<SamplePair*>(y + p) = SamplePair{s.x, s.y};
+        }
+        return;
+    }
     for (int i = lane; i < count; i += 64) {
         const int p = p0 + 2 * i;
         float2* slot = reinterpret_cast<float2*>(acc + (p & (kFft - 1)));
@@ -88,20 +165,26 @@ __device__ inline void flush_window(float* acc, float* y, int len, int p0, int c
 }
 
 // grid: (frame groups of the longest utterance, utterances); `out` must be zero on entry
-__global__ __launch_bounds__(kThreads) void vtlp_resynth_kernel(
+__global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
     const int64_t* __restrict__ offsets, const float* __restrict__ wave, const float2* __restrict__ tab,
     const float2* __restrict__ tw, float* __restrict__ out) {
     extern __shared__ float2 smem[];
-    const int tid = threadIdx.x, wv = tid / 64, lane = tid % 64;
+    const int tid = threadIdx.x, wv = __builtin_amdgcn_readfirstlane(tid / 64), lane = tid % 64;
     const int u = blockIdx.y;
     const int64_t start = offsets[u];
     const int len = (int)(offsets[u + 1] - start);      // utterances are shorter than 2^30 samples (checked on the host)
     const int n_frames = frame_count(len);
-    if (blockIdx.x * kFramesPerGroup >= n_frames) return;    // the whole group leaves together
+    const int n_groups = (n_frames + kFramesPerGroup - 1) / kFramesPerGroup;
+    if ((int)blockIdx.x >= n_groups) return;                 // the whole group leaves together
+    const int run = max((n_frames + n_groups * kWaves - 1) / (n_groups * kWaves), kMinRun);
     float2* buf = smem + wv * kSlot;
     float2* s_tab = smem + kWaves * kSlot;
     float* acc = reinterpret_cast<float*>(s_tab + kBins + 1) + wv * kFft;     // [waves][2048], 8-byte aligned
-    for (int k = tid; k < kBins; k += kThreads) s_tab[k] = tab[(size_t)u * kBins + k];
+    for (int k = tid; k < kBins; k += kThreads) {
+        const float2 jf = tab[(size_t)u * kBins + k];
+        const int j = (int)jf.x;
+        s_tab[k] = make_float2(__int_as_float((int)sizeof(float2) * (lds_pad(j) | lds_pad(j + 1) << 16)), jf.y);
+    }
     for (int k = lane; k < kFft / 2; k += 64) reinterpret_cast<float2*>(acc)[k] = make_float2(0.f, 0.f);
 
     // Lane l holds packed inputs m = l + 64 i, i.e. frame offsets tau = 2m, 2m + 1 for m < 200 and
@@ -120,8 +203,7 @@ __global__ __launch_bounds__(kThreads) void vtlp_resynth_kernel(
                       : make_float2(0.f, 0.f);
     }
     // twiddles of this lane's butterflies and of its bin pairs are the same for every frame
-    FftLaneTwiddles<kN, 64> lane_tw;
-    lane_tw.load(tw, lane);
+    const LaneTwiddles lane_tw = lane_twiddles(tw, lane);
     float2 pair_tw[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) pair_tw[i] = tw[kN + lane + 64 * i];     // exp(-i pi k / N), k = lane + 64 i
@@ -129,9 +211,9 @@ __global__ __launch_bounds__(kThreads) void vtlp_resynth_kernel(
     __syncthreads();
 
     // this wavefront's run of frames, and the positions that only its frames reach
-    const int t_first = blockIdx.x * kFramesPerGroup + wv * kRun;
+    const int t_first = ((int)blockIdx.x * kWaves + wv) * run;
     if (t_first >= n_frames) return;                     // no barriers below
-    const int t_last = min(t_first + kRun, n_frames) - 1;
+    const int t_last = min(t_first + run, n_frames) - 1;
     const int excl_lo = t_first == 0 ? -(1 << 30) : t_first * kHop + (kReach - kHop);
     const int excl_hi = t_last == n_frames - 1 ? (1 << 30) : t_last * kHop - (kReach - kHop);
 
@@ -140,6 +222,15 @@ __global__ __launch_bounds__(kThreads) void vtlp_resynth_kernel(
     // the lane's eight sample pairs of frame t (unweighted); a zero window weight marks inputs the lane does
     // not have, and unsigned compares fold the test for positions before the utterance in
     auto load_frame = [&](float2 (&xs)[8], int t) {
+        if (t > 0 && (t + 1) * kHop <= len) {          // the whole frame lies in the utterance
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const bool used = wnd[s].x != 0.f || wnd[s].y != 0.f;
+                const SamplePair p = *reinterpret_cast<const SamplePair*>(x + t * kHop + (used ? tau0[s] : 0));
+                xs[s] = make_float2(used ? p.x : 0.f, used ? p.y : 0.f);
+            }
+            return;
+        }
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int g = t * kHop + tau0[s];
@@ -152,69 +243,75 @@ __global__ __launch_bounds__(kThreads) void vtlp_resynth_kernel(
     load_frame(next_x, t_first);
     for (int t = t_first; t <= t_last; ++t) {
         const int centre = t * kHop;
-        lane_tw.keep_in_loop();
+        // (opaque: addresses are formed anew for every frame rather than kept in registers from one to the next)
+        int l = lane;
+        asm volatile("" : "+v"(l));
         float2 v[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) v[i] = make_float2(0.f, 0.f);
 #pragma unroll
         for (int s = 0; s < 8; ++s) v[s < 4 ? s : s + 8] = make_float2(next_x[s].x * wnd[s].x, next_x[s].y * wnd[s].y);
         if (t < t_last) load_frame(next_x, t + 1);       // arrives while this frame is transformed
-        fft_passes_cached<kN, 64, false, FftSync::Wave>(v, buf, lane_tw, lane);
-        fft_store_natural<kN, 64>(v, buf, lane);
+        dft16_outer_inputs(v);
+        later_passes<false>(v, buf, lane_tw, l);
+        fft_store_natural<kN, 64>(v, buf, l);
         fft_sync<FftSync::Wave>();
 
-        // Packed transform Z -> real spectrum X, in place: with A = Z[k], B = conj Z[N-k], E = (A + B)/2,
-        // O = -(i/2)(A - B), w = exp(-i pi k / N):  X[k] = E + w O,  X[N-k] = conj(E - w O).
-        // A lane owns the pair (k, N-k); k = 0 yields X[0] and X[N], the latter kept in the extra slot.
-        auto unpack = [&](int k, float2 w) {
-            const int kn = (kN - k) & (kN - 1);
-            const float2 A = buf[lds_pad(k)], B = cconj(buf[lds_pad(kn)]);
-            const float2 E = make_float2(0.5f * (A.x + B.x), 0.5f * (A.y + B.y));
-            const float2 O = make_float2(0.5f * (A.y - B.y), -0.5f * (A.x - B.x));
+        // Packed transform Z -> twice the real spectrum X, in place: with A = Z[k], B = conj Z[N-k], E = A + B,
+        // O = -i (A - B), w = exp(-i pi k / N):  X[k] = E + w O,  X[N-k] = conj(E - w O).  (The halves of both splits are
+        // left to the scale of the output.)
+        // A lane owns the pairs (k, N-k), k = l + 64 i: one place below and one above plus constants.  k = 0 yields X[0]
+        // and X[N], the latter kept in the extra slot.
+        float2* const below = buf + lds_pad(l);
+        float2* const above = buf + lds_pad(64 - l);
+        auto unpack = [&](float2* at_k, float2* at_n, const float2* from_n, float2 w) {
+            const float2 A = *at_k, B = cconj(*from_n);
+            const float2 E = cadd(A, B), O = make_float2(A.y - B.y, B.x - A.x);
             const float2 wO = cmul(w, O);
-            buf[lds_pad(k)] = cadd(E, wO);
-            buf[lds_pad(k ? kn : kN)] = cconj(csub(E, wO));
+            *at_k = cadd(E, wO);
+            *at_n = cconj(csub(E, wO));
         };
 #pragma unroll
-        for (int i = 0; i < 8; ++i) unpack(lane + 64 * i, pair_tw[i]);
-        if (lane == 0) unpack(kN / 2, quarter_tw);
+        for (int i = 0; i < 8; ++i) {
+            float2* const at_n = above + lds_pad(kN - 64 - 64 * i);
+            unpack(below + lds_pad(64 * i), at_n, i == 0 && l == 0 ? buf : at_n, pair_tw[i]);
+        }
+        if (l == 0) unpack(buf + lds_pad(kN / 2), buf + lds_pad(kN / 2), buf + lds_pad(kN / 2), quarter_tw);
         fft_sync<FftSync::Wave>();
 
         // Warped spectrum Y (two interpolated bins per pair), packed for the inverse transform:
-        // Ye = (Y[k] + conj Y[N-k])/2, Yo = conj(w) (Y[k] - conj Y[N-k])/2, Z'[k] = Ye + i Yo,
+        // Ye = Y[k] + conj Y[N-k], Yo = conj(w) (Y[k] - conj Y[N-k]), Z'[k] = Ye + i Yo,
         // Z'[N-k] = conj(Ye) + i conj(Yo).  All reads of X finish before the buffer is overwritten.
         float2 zk[9], zn[9];
         auto pack = [&](int k, int slot, float2 w) {
             const float2 Yk = warped_bin(buf, s_tab, k), Yn = cconj(warped_bin(buf, s_tab, kN - k));
-            const float2 Ye = make_float2(0.5f * (Yk.x + Yn.x), 0.5f * (Yk.y + Yn.y));
-            const float2 dY = make_float2(0.5f * (Yk.x - Yn.x), 0.5f * (Yk.y - Yn.y));
-            const float2 Yo = cmul_conj(dY, w);
+            const float2 Ye = cadd(Yk, Yn), Yo = cmul_conj(csub(Yk, Yn), w);
             zk[slot] = make_float2(Ye.x - Yo.y, Ye.y + Yo.x);
             zn[slot] = make_float2(Ye.x + Yo.y, Yo.x - Ye.y);
         };
 #pragma unroll
-        for (int i = 0; i < 8; ++i) pack(lane + 64 * i, i, pair_tw[i]);
-        if (lane == 0) pack(kN / 2, 8, quarter_tw);
+        for (int i = 0; i < 8; ++i) {
+            pack(l + 64 * i, i, pair_tw[i]);
+        }
+        if (l == 0) pack(kN / 2, 8, quarter_tw);
         fft_sync<FftSync::Wave>();
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            const int k = lane + 64 * i;
-            buf[lds_pad(k)] = zk[i];
-            if (k) buf[lds_pad(kN - k)] = zn[i];
+            below[lds_pad(64 * i)] = zk[i];
+            if (i || l) above[lds_pad(kN - 64 - 64 * i)] = zn[i];
         }
-        if (lane == 0) buf[lds_pad(kN / 2)] = zk[8];
+        if (l == 0) buf[lds_pad(kN / 2)] = zk[8];
         fft_sync<FftSync::Wave>();
 
-        fft_load_natural<kN, 64>(v, buf, lane);
+        fft_load_natural<kN, 64>(v, buf, l);
         fft_sync<FftSync::Wave>();
-        fft_passes_cached<kN, 64, true, FftSync::Wave>(v, buf, lane_tw, lane);
-        // v[i] is packed output m = fft_out_index(lane, i) times N: samples at offsets 2m, 2m + 1 (m < N/2)
+        dft16<true>(v);
+        later_passes<true>(v, buf, lane_tw, l);
+        // v[i] is packed output m = fft_out_index(l, i) times 4 N: samples at offsets 2m, 2m + 1 (m < N/2)
         // or 2m - 2048, 2m - 2047 from the frame centre; position p lives at window slot p mod 2048, and the
         // centre is even, so a pair is one aligned float2 of the window
-        const float scale = 1.0f / (float)kN;
+        constexpr float scale = 0.25f / (float)kN;
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int m = fft_out_index<kN, 64>(lane, i);
+            const int m = fft_out_index<kN, 64>(l, i);
             float2* slot = reinterpret_cast<float2*>(acc + ((centre + 2 * m) & (kFft - 1)));
             float2 a = *slot;
             a.x += v[i].x * scale;
@@ -223,7 +320,7 @@ __global__ __launch_bounds__(kThreads) void vtlp_resynth_kernel(
         }
         fft_sync<FftSync::Wave>();
         // the next frame starts kHop later: the first kHop positions of the window are complete for this run
-        flush_window(acc, y, len, centre - kReach, kHop / 2, excl_lo, excl_hi, lane);
+        flush_window(acc, y, len, centre - kReach, kHop / 2, excl_lo, excl_hi, l);
         fft_sync<FftSync::Wave>();                       // also: the next frame reuses the transform buffer
     }
     flush_window(acc, y, len, t_last * kHop - kReach + kHop, (kFft - kHop) / 2, excl_lo, excl_hi, lane);

@@ -49,6 +49,19 @@ def test_ragged_lengths_and_warp_factors(aug):
     assert np.max(np.abs(got[a:b] - wave[a:b])) <= 1e-5 * np.sqrt(np.mean(wave[a:b] ** 2.0)) * 10
 
 
+@pytest.mark.parametrize("n_frames", [2, 3, 8, 9, 32, 33, 64, 65, 66, 128, 129])
+def test_frames_shared_among_wavefronts(aug, n_frames):
+    # lengths whose frames fill runs, wavefronts and groups exactly, by one more and by one less than whole hops
+    lens = [400 * (n_frames - 2) + 1, 400 * (n_frames - 1) - 1, 400 * (n_frames - 1)]
+    rng = np.random.default_rng(n_frames)
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    wave = rng.standard_normal(int(offsets[-1])).astype(np.float32)
+    alpha = np.array([0.8, 1.07, 1.2], np.float32)
+    print(f"case: {n_frames} frames", flush=True)
+    got, _ = _check(aug, offsets, wave, alpha)
+    assert np.array_equal(got, _run(aug, offsets, wave, alpha))      # at most two shares per sample: any order
+
+
 def test_tiny_speech(aug):
     w = W.tiny()
     print("case: tiny workload speech", flush=True)
