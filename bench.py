@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "b10178e637ae96d5",
-    "varlen": {"rir": 144776913, "rir_spectrum": 201797926, "convolve": 1254849701, "mel": 617857198},
-    "throughput": {"rir": 782242713, "rir_spectrum": 1213474671, "convolve": 13819990189, "mel": 2201970965},
+    "digest": "9d19643bdf964b5a",
+    "varlen": {"rir": 84528872, "rir_spectrum": 202469539, "convolve": 1255802136, "mel": 612443424},
+    "throughput": {"rir": 446958198, "rir_spectrum": 1217856063, "convolve": 13996055237, "mel": 2176042273},
 }
 
 
