@@ -25,8 +25,8 @@
 // vector units are busy half the time and the LDS two fifths of it (1450 vector and 218 LDS instructions per frame on 256
 // utterances of 1-16 s).  Twiddles folded into multiply-adds, zero inputs skipped, mirrored bins at constant distances from
 // two places and frames inside the utterance without range tests took that batch from 530 to 506 us, an utterance's
-// frames shared evenly among its wavefronts instead of in runs of 16 and a rest to 495.  Longer runs would save
-// atomics and lose in balance (at most 24 frames: 506 us; 32: 479, but a single utterance then has half the wavefronts).
+// frames shared evenly among its wavefronts instead of in runs of 16 and a rest to 495, zeros only where runs meet to 484.  Longer runs would save
+// atomics and lose in balance (at most 24 frames: 506 us against 495; 32: 479, but a single utterance then has half the wavefronts).
 
 #include "aug_internal.h"
 #include "fft_lds.h"
@@ -63,6 +63,31 @@ __global__ void vtlp_table_kernel(int n_utt, const float* __restrict__ alpha, fl
 }
 
 __device__ inline int frame_count(int len) { return len > 0 ? (len - 1) / kHop + 2 : 0; }
+
+// How an utterance's frames are shared: groups of kWaves runs, `run` frames each (the last ones fewer or none).
+struct Share { int n_groups, run; };
+__device__ inline Share share_frames(int n_frames) {
+    const int n_groups = (n_frames + kFramesPerGroup - 1) / kFramesPerGroup;
+    return Share{n_groups, max((n_frames + n_groups * kWaves - 1) / max(n_groups * kWaves, 1), kMinRun)};
+}
+
+// Zeros where runs meet: the samples that two of them add to.  All others are stored by the kernel below.  (Clearing the
+// whole output cost a write of it; this is a quarter.)  Same grid as below.
+__global__ __launch_bounds__(kThreads) void vtlp_clear_kernel(const int64_t* __restrict__ offsets, float* __restrict__ out) {
+    const int u = blockIdx.y;
+    const int64_t start = offsets[u];
+    const int len = (int)(offsets[u + 1] - start);
+    const int n_frames = frame_count(len);
+    const Share share = share_frames(n_frames);
+    if ((int)blockIdx.x >= share.n_groups) return;
+    float* const y = out + start;
+    for (int w = 0; w < kWaves; ++w) {
+        const int t = ((int)blockIdx.x * kWaves + w) * share.run;       // first frame of a run
+        if (t == 0 || t >= n_frames) continue;
+        const int lo = max(t * kHop - kReach, 0), hi = min(t * kHop + (kReach - kHop), len);
+        for (int p = lo + (int)threadIdx.x; p < hi; p += kThreads) y[p] = 0.f;
+    }
+}
 
 // Value of output bin q of the warped spectrum; X is in natural order in buf, bin 1024 in the extra slot.  The table in
 // LDS holds the places of the two source bins in bytes, sixteen bits each, and the weight.
@@ -164,7 +189,7 @@ __device__ inline void flush_window(float* acc, float* y, int len, int p0, int c
     }
 }
 
-// grid: (frame groups of the longest utterance, utterances); `out` must be zero on entry
+// grid: (frame groups of the longest utterance, utterances); `out` as vtlp_clear_kernel leaves it
 __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
     const int64_t* __restrict__ offsets, const float* __restrict__ wave, const float2* __restrict__ tab,
     const float2* __restrict__ tw, float* __restrict__ out) {
@@ -174,9 +199,8 @@ __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
     const int64_t start = offsets[u];
     const int len = (int)(offsets[u + 1] - start);      // utterances are shorter than 2^30 samples (checked on the host)
     const int n_frames = frame_count(len);
-    const int n_groups = (n_frames + kFramesPerGroup - 1) / kFramesPerGroup;
-    if ((int)blockIdx.x >= n_groups) return;                 // the whole group leaves together
-    const int run = max((n_frames + n_groups * kWaves - 1) / (n_groups * kWaves), kMinRun);
+    const Share share = share_frames(n_frames);
+    if ((int)blockIdx.x >= share.n_groups) return;           // the whole group leaves together
     float2* buf = smem + wv * kSlot;
     float2* s_tab = smem + kWaves * kSlot;
     float* acc = reinterpret_cast<float*>(s_tab + kBins + 1) + wv * kFft;     // [waves][2048], 8-byte aligned
@@ -211,9 +235,9 @@ __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
     __syncthreads();
 
     // this wavefront's run of frames, and the positions that only its frames reach
-    const int t_first = ((int)blockIdx.x * kWaves + wv) * run;
+    const int t_first = ((int)blockIdx.x * kWaves + wv) * share.run;
     if (t_first >= n_frames) return;                     // no barriers below
-    const int t_last = min(t_first + run, n_frames) - 1;
+    const int t_last = min(t_first + share.run, n_frames) - 1;
     const int excl_lo = t_first == 0 ? -(1 << 30) : t_first * kHop + (kReach - kHop);
     const int excl_hi = t_last == n_frames - 1 ? (1 << 30) : t_last * kHop - (kReach - kHop);
 
@@ -345,6 +369,7 @@ hipError_t launch_vtlp_resynth(hipStream_t s, int n_utt, const int64_t* d_offset
     const int64_t frames = (max_len - 1) / kHop + 2;
     const int64_t groups = (frames + kFramesPerGroup - 1) / kFramesPerGroup;
     const size_t lds = sizeof(float2) * (size_t)(kWaves * kSlot + kBins + 1) + sizeof(float) * kWaves * kFft;
+    vtlp_clear_kernel<<<dim3((unsigned)groups, (unsigned)n_utt), dim3(kThreads), 0, s>>>(d_offsets, out);
     vtlp_resynth_kernel<<<dim3((unsigned)groups, (unsigned)n_utt), dim3(kThreads), lds, s>>>(
         d_offsets, wave, tab, twiddle, out);
     return hipGetLastError();
