@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "9d19643bdf964b5a",
-    "varlen": {"rir": 84528872, "rir_spectrum": 202469539, "convolve": 1255802136, "mel": 612443424},
-    "throughput": {"rir": 446958198, "rir_spectrum": 1217856063, "convolve": 13996055237, "mel": 2176042273},
+    "digest": "26ed125015052ce0",
+    "varlen": {"rir": 84493024, "rir_spectrum": 202457166, "convolve": 1256028415, "mel": 612607108},
+    "throughput": {"rir": 447056275, "rir_spectrum": 1217756672, "convolve": 13991084909, "mel": 2175878532},
 }
 
 
