@@ -107,10 +107,11 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
             lo4 = lo / 4;
             len4 = hi > lo ? (hi + 3) / 4 - lo4 : 0;
         }
-        // lane i counts the pieces that steps = 4 (i + 1) would give
+        // lane i counts the pieces that steps = 4 (i + 1) would give.  A quad without bins owns a piece too, with zero
+        // weights: quad g's first sum is then at or behind place 4 g, which the cepstra rely on (see mel_kernel).
         const float inv = 1.f / (float)(lane + 1);
         int count = 0;
-        for (int g = 0; g < n_quads; ++g) count += (int)ceilf((float)__shfl(len4, g, 64) * inv - 1e-4f);
+        for (int g = 0; g < n_quads; ++g) count += max((int)ceilf((float)__shfl(len4, g, 64) * inv - 1e-4f), 1);
         int best = 1 << 20, rounds = 0, steps4 = 1;
         for (int r = 1; r <= kMaxRounds; ++r) {
             const unsigned long long fits = __ballot(count <= 16 * r);
@@ -123,7 +124,7 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
                 steps4 = s4;
             }
         }
-        const int mine = (len4 + steps4 - 1) / steps4;
+        const int mine = lane < n_quads ? max((len4 + steps4 - 1) / steps4, 1) : 0;
         int incl = mine;
         for (int off = 1; off < 64; off <<= 1) {
             const int up = __shfl_up(incl, off, 64);
@@ -624,8 +625,9 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
             }
             return e;
         };
-        // For cepstra the log energies go over the sums: channel m at place m, which is at or before its own sums, so
-        // what a later channel still has to read is not overwritten.
+        // For cepstra the log energies go over the sums: channel m at place m, which is at or before its own sums (every
+        // quad owns a piece, so those of quad g begin at 4 g or later), so what a later channel still has to read is not
+        // overwritten.
         const bool to_lds = feature == AUG_FEAT_MFCC && rounds;
         const int m_end = to_lds ? (n_mel + 3) & ~3 : feature == AUG_FEAT_MFCC ? 0 : n_mel;
 #pragma unroll 1

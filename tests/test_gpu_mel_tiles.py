@@ -54,6 +54,17 @@ def test_narrow_bands(aug, f_lo, f_hi):
     _check(aug, dataclasses.replace(FE, f_lo=f_lo, f_hi=f_hi), [4000, 2000], 5)
 
 
+# Bands narrower than the bins are apart: whole quads of channels hold no bin, and what a cepstrum's later channels
+# read lies closer to the front of the frame's buffer.
+@pytest.mark.parametrize("feature", ["power", "log", "mfcc"])
+@pytest.mark.parametrize("fs,n_mel,f_lo,f_hi", [(16000.0, 40, 0.0, 300.0), (16000.0, 40, 3000.0, 3100.0), (16000.0, 64, 0.0, 300.0),
+                                                (16000.0, 128, 0.0, 1600.0), (48000.0, 80, 20.0, 8000.0), (48000.0, 128, 20.0, 8000.0),
+                                                (16000.0, 128, 0.0, 60.0)])
+def test_channels_without_bins(aug, fs, n_mel, f_lo, f_hi, feature):
+    fe = dataclasses.replace(FE, fs=fs, n_mel=n_mel, f_lo=f_lo, f_hi=f_hi, feature=feature, n_ceps=n_mel, log_floor=1e-2)
+    _check(aug, fe, [4000, 2000, 900, 5000, 600], 5)
+
+
 @pytest.mark.parametrize("win,hop", [(400, 1), (400, 207), (400, 208), (400, 210), (400, 700), (401, 160), (512, 3), (399, 160)])
 def test_hops_and_windows(aug, win, hop):
     _check(aug, dataclasses.replace(FE, win=win, hop=hop), [win + 3 * hop, win - 1, win + 17 * hop + 1, win + 40], win + hop)
