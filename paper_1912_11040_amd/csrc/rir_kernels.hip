@@ -823,9 +823,10 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     const int first = count_below(cz, r_in2 - a);
                     const int last = min(count_below(cz, r_near2 - a), count_not_above(cz, niz, r_out2 - a));
                     const int kxy = iabs(nx - qx) + iabs(nx) + (int)ye.aux;
-                    if (last > first)
-                        walk_near(wctx, a, (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(beta, kxy)), ztab, first, last, hist);
-                    if (VISITS) walked += (unsigned long long)max(last - first, 0);
+                    // (past the cut the amplitudes are zero, and bpow has not been formed)
+                    if (last <= first || kxy > k_cut_item) continue;
+                    walk_near(wctx, a, (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(beta, kxy)), ztab, first, last, hist);
+                    if (VISITS) walked += (unsigned long long)(last - first);
                 }
             }
             const int n_batch = (n_cand + 63) / 64;

@@ -45,3 +45,25 @@ def test_near_images(aug, fs, length):
     h_ref, cnt_ref = O.rir_batch(g, length, fs, C)
     np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
     assert rir_err(h.cpu().numpy(), h_ref) <= RIR_TOL
+
+
+@pytest.mark.parametrize("beta", [0.3, 0.32, 0.1])
+def test_near_columns_past_the_reflection_cut(aug, beta):
+    """Rooms so narrow that columns within 2.6 m have more reflections than the cut leaves.  Their amplitudes round to
+    nothing, and must not come from the powers of other rooms, which the work groups' tables held in the call before."""
+    import torch
+    rng = np.random.default_rng(3)
+    n, length, fs = 320, 130, 16000.0            # (two shells a response: one begins at a distance above 0, within 2.6 m)
+    g = []
+    for b in (1.0, beta):
+        side = rng.uniform(0.1, 0.11, (n, 3))
+        g.append(np.concatenate([side, side * rng.uniform(0.2, 0.8, (n, 3)), side * rng.uniform(0.2, 0.8, (n, 3)),
+                                 np.full((n, 1), b)], 1).astype(np.float32))
+    h = torch.full((2, n, length), float("nan"), dtype=torch.float32, device="cuda")
+    for i in range(2):
+        aug.aug_rir_batch(dev(g[i]), length, fs, C, h[i])
+    torch.cuda.synchronize()
+    got = h[1].cpu().numpy()
+    for r in range(0, n, 5):
+        h_ref, _ = O.rir_batch(g[1][r:r + 1], length, fs, C)
+        assert rir_err(got[r:r + 1], h_ref) <= RIR_TOL, r
