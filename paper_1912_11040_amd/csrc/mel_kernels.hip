@@ -36,13 +36,16 @@ __device__ inline float hamming(int i, int win) {
 // consecutive mel channels (a "quad"); the sixteen blocks run through different stretches of bins.  The bins of
 // a quad are contiguous (five bands of them); they are cut into pieces of `steps` bins, a block each, in `rounds`
 // times sixteen pieces over all quads.  rounds and steps are chosen per utterance so that the number of
-// instructions is least: 24 for 40 channels, where a dense product would need 643.
+// instructions is least: 24 for 40 channels, where a dense product would need 643.  There is no plan where the bins are
+// not in the order of their bands (warp factors outside (0, 2), for which Eq. (1) is not increasing), or where more than
+// a hundred channels meet a strong warp (the nearest to 1 that were found: 0.64 and 1.39); the kernel then sums over all
+// bins.
 constexpr int kMaxRounds = 4;
 constexpr int kMaxQuads = AUG_MAX_MEL / 4;
 constexpr int kMaxSteps = 32;                // rounds x steps that the kernel has room for
 constexpr unsigned short kNoPiece = 0xffff;
 struct MelPlan {
-    unsigned char rounds, steps;             // steps: a multiple of 4; rounds = 0 if no plan within kMaxSteps exists
+    unsigned char rounds, steps;             // steps: a multiple of 4; rounds = 0: no plan
     unsigned char first_piece[kMaxQuads + 6];     // of quad g; entry n_quads is the number of pieces
     unsigned short piece[16 * kMaxRounds];   // first bin (a multiple of 4) | quad << 10, kNoPiece where unused
 };
@@ -81,12 +84,14 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
     __shared__ short band[2050];
     __shared__ int first_bin[AUG_MAX_MEL + 8];        // first bin of band c or higher
     __shared__ MelPlan plan;
+    __shared__ bool unordered;
     const int bins = a.cfg.nfft / 2 + 1, n_mel = a.cfg.n_mel, tid = threadIdx.x, threads = (int)blockDim.x;
     float2* t = a.tab + (size_t)u * stride;
     const float alpha_u = a.alpha[u];
     for (int i = tid; i < n_mel + 2; i += threads) edges[i] = a.edges[i];
     for (int i = tid; i < n_mel + 8; i += threads) first_bin[i] = bins;
     for (int i = tid; i < 16 * kMaxRounds; i += threads) plan.piece[i] = kNoPiece;
+    if (tid == 0) unordered = false;
     __syncthreads();
     for (int k = tid; k < bins; k += threads) {
         float w;
@@ -95,8 +100,11 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
         t[k] = make_float2(c <= n_mel ? (float)c : -2.f, w);
     }
     __syncthreads();
-    for (int k = tid; k < bins; k += threads)          // bands do not decrease with the bin
-        for (int c = (k ? (int)band[k - 1] : -1) + 1; c <= band[k]; ++c) first_bin[c] = k;
+    for (int k = tid; k < bins; k += threads) {
+        const int below = k ? (int)band[k - 1] : -1;
+        if (band[k] < below) unordered = true;
+        for (int c = below + 1; c <= band[k]; ++c) first_bin[c] = k;
+    }
     __syncthreads();
     if (tid < 64) {
         // a quad's stretch in units of four bins, on lane g
@@ -113,7 +121,7 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
         int count = 0;
         for (int g = 0; g < n_quads; ++g) count += max((int)ceilf((float)__shfl(len4, g, 64) * inv - 1e-4f), 1);
         int best = 1 << 20, rounds = 0, steps4 = 1;
-        for (int r = 1; r <= kMaxRounds; ++r) {
+        for (int r = 1; r <= kMaxRounds && !unordered; ++r) {
             const unsigned long long fits = __ballot(count <= 16 * r);
             if (!fits) continue;
             const int s4 = __ffsll((unsigned long long)fits);           // the smallest: lane + 1
@@ -604,8 +612,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
             }
             fft_sync<FftSync::Wave>();
         }
-        // energy of channel m: the sum of its pieces.  (Without a plan, for warps that do not keep the bins in
-        // order, a plain sum over all bins.)
+        // energy of channel m: the sum of its pieces, without a plan a plain sum over all bins
         auto energy = [&](int m) {
             float e = 0.f;
             if (rounds) {

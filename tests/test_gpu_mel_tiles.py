@@ -22,12 +22,12 @@ def aug():
     a.close()
 
 
-def _check(aug, fe, lens, seed, spare=0):
+def _check(aug, fe, lens, seed, spare=0, warp=None):
     import torch
     rng = np.random.default_rng(seed)
     offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     x = rng.standard_normal(int(offsets[-1])).astype(np.float32)
-    alpha = rng.uniform(0.8, 1.2, len(lens)).astype(np.float32)
+    alpha = rng.uniform(0.8, 1.2, len(lens)).astype(np.float32) if warp is None else np.full(len(lens), warp, np.float32)
     t = np.array([O.frame_count(int(n), fe.win, fe.hop) for n in lens])
     foff = np.concatenate([[0], np.cumsum(t + spare)]).astype(np.int64)
     feats = torch.full((int(foff[-1]), fe.feature_dim), float("nan"), dtype=torch.float32, device="cuda")
@@ -63,6 +63,16 @@ def test_narrow_bands(aug, f_lo, f_hi):
 def test_channels_without_bins(aug, fs, n_mel, f_lo, f_hi, feature):
     fe = dataclasses.replace(FE, fs=fs, n_mel=n_mel, f_lo=f_lo, f_hi=f_hi, feature=feature, n_ceps=n_mel, log_floor=1e-2)
     _check(aug, fe, [4000, 2000, 900, 5000, 600], 5)
+
+
+# Warps without a plan for the projection: Eq. (1) does not increase outside (0, 2), so that bands fall as well as rise
+# with the bin; and one inside (0, 2) for which the plan has no room.
+@pytest.mark.parametrize("feature", ["power", "log", "mfcc"])
+@pytest.mark.parametrize("warp,n_mel", [(2.5, 40), (2.5, 128), (-0.3, 40), (-3.0, 17), (7.0, 23), (0.1204675, 125)])
+def test_warps_without_a_plan(aug, warp, n_mel, feature):
+    fs = 48000.0 if n_mel == 125 else 16000.0
+    fe = dataclasses.replace(FE, fs=fs, n_mel=n_mel, f_hi=fs / 2, feature=feature, n_ceps=min(n_mel, 20), log_floor=1e-2)
+    _check(aug, fe, [4000, 900, 400], n_mel, warp=warp)
 
 
 @pytest.mark.parametrize("win,hop", [(400, 1), (400, 207), (400, 208), (400, 210), (400, 700), (401, 160), (512, 3), (399, 160)])
