@@ -65,13 +65,20 @@ def test_channels_without_bins(aug, fs, n_mel, f_lo, f_hi, feature):
     _check(aug, fe, [4000, 2000, 900, 5000, 600], 5)
 
 
-# Warps without a plan for the projection: Eq. (1) does not increase outside (0, 2), so that bands fall as well as rise
-# with the bin; and one inside (0, 2) for which the plan has no room.
+# Warps without a plan for the projection.  Strong ones inside (0, 2) of many channels, for which it has no room:
 @pytest.mark.parametrize("feature", ["power", "log", "mfcc"])
-@pytest.mark.parametrize("warp,n_mel", [(2.5, 40), (2.5, 128), (-0.3, 40), (-3.0, 17), (7.0, 23), (0.1204675, 125)])
-def test_warps_without_a_plan(aug, warp, n_mel, feature):
-    fs = 48000.0 if n_mel == 125 else 16000.0
-    fe = dataclasses.replace(FE, fs=fs, n_mel=n_mel, f_hi=fs / 2, feature=feature, n_ceps=min(n_mel, 20), log_floor=1e-2)
+@pytest.mark.parametrize("warp,fs,n_mel,f_lo", [(0.1204675, 48000.0, 125, 0.0), (0.1585413, 8000.0, 117, 0.0), (0.0894, 8000.0, 121, 20.0)])
+def test_warps_without_room_for_a_plan(aug, warp, fs, n_mel, f_lo, feature):
+    fe = dataclasses.replace(FE, fs=fs, n_mel=n_mel, f_lo=f_lo, f_hi=fs / 2, feature=feature, n_ceps=20, log_floor=1e-2)
+    _check(aug, fe, [4000, 900, 400], n_mel, warp=warp)
+
+
+# ... and those outside, for which Eq. (1) does not increase: it then puts every bin at or beyond the ends of the band.  (The
+# floor is one: what rounding leaves of the bins at the very ends is far below it.)
+@pytest.mark.parametrize("feature", ["log", "mfcc"])
+@pytest.mark.parametrize("warp,n_mel", [(2.5, 40), (2.5, 128), (-0.3, 40), (-3.0, 17), (7.0, 23)])
+def test_warps_that_do_not_keep_the_order(aug, warp, n_mel, feature):
+    fe = dataclasses.replace(FE, n_mel=n_mel, feature=feature, n_ceps=min(n_mel, 20), log_floor=1.0)
     _check(aug, fe, [4000, 900, 400], n_mel, warp=warp)
 
 
