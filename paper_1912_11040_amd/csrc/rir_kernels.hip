@@ -31,8 +31,8 @@
 //     counting bits in a map of the columns' first pieces) and walk them, two images side by side.
 //     Bound by issue and by LDS about equally (256 x 16000 taps: vector units 0.80, LDS 0.78 of the time, half of that
 //     conflicts of reads at scattered table entries and of sums at scattered taps).
-//     Rooms so flat or narrow that an axis has more images than the tables hold take a plain path
-//     (all columns of the bounding box, every z image of a live column).
+//     Rooms so flat or narrow that an axis has more images than the tables hold, and positions far outside
+//     the room, take a plain path (all columns of the bounding box, every z image of a live column).
 //   * amplitudes accumulate as 64-bit fixed point (2^-56, each increment rounded to the nearest unit)
 //     with integer LDS atomics: gfx950 executes float LDS atomics about thirty times slower than integer
 //     ones, and integer sums do not depend on the order of arrival nor on how a batch is cut into items.
@@ -578,11 +578,19 @@ __device__ __attribute__((noinline)) void walk_near(const WalkCtx w, double a, d
     }
 }
 
+// Source and microphone lie between the walls, or not so far outside that an axis' images stop beginning within 2 L of
+// the microphone (false where a position is not a number).  Rows beyond that are not refused: they take the plain path,
+// which tests every tap.
+__device__ inline bool axis_in_order(const Axis& a) {
+    return fabs(a.src - a.mic) <= 2.0 * a.room && fabs(a.src + a.mic) <= 2.0 * a.room;
+}
+
 // All images (1 - 2q) s + 2 n L - m, q in {0,1}, |n| <= nm, of one axis, written to `out` in order of
 // squared distance.  For each q the signed distance grows with n, so the images with negative
 // distance (walked towards smaller n) and those with non-negative distance are two sorted lists.  All four lists step
 // by 2 L and begin within 2 L of the microphone, so the merged order is known: element p of a list follows every
 // list's elements 0 .. p-1 and, of the elements p, those of the lists that begin nearer (ties: the lower list).
+// That takes an axis_in_order.
 // (Searching the other lists for every entry's place, eight steps each, took a sixth of all the kernel's instructions.)
 // aux(q, n) supplies the entry's second field.
 template <class Aux>
@@ -758,8 +766,9 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 return (double)(r * r * 1.0001f + 1e-3f);
             };
 
-            // fast path: the y and z images fit the LDS tables and so do the x rows
-            const bool fast = nix <= 2 * kAxisCap && niy <= 2 * kAxisCap && niz <= 2 * kAxisCap &&
+            // fast path: the y and z images fit the LDS tables and so do the x rows, and the closed forms hold
+            const bool fast = axis_in_order(ax) && axis_in_order(ay) && axis_in_order(az) &&
+                              nix <= 2 * kAxisCap && niy <= 2 * kAxisCap && niz <= 2 * kAxisCap &&
                               fmax(ay.room, az.room) * k_fs_c < kMaxAxisTaps;
             int n_cand;
             if (!COUNT) {

@@ -53,6 +53,36 @@ def test_ragged_lengths(aug, L):
     _check(aug, w.geom, L)
 
 
+def test_positions_outside_the_room(aug):
+    """Not checked, and bounded all the same: the images whose index the room's size allows, and in the rooms beside them
+    what they get alone.  (The order of an axis' images that the tables are built in needs |s - m|, |s + m| <= 2 L.)"""
+    room = np.array([5.0, 4.0, 3.0])
+    inside = np.concatenate([room, 0.4 * room, 0.7 * room, [0.8]])
+    rows = []
+    for axis in range(3):
+        for s, m in ((1.0, 1.0), (1.001, 1.0), (1.3, 1.2), (-0.1, 0.5), (-1.2, -1.3), (2.5, 0.4), (0.3, -2.2), (-1.9, 0.9), (1e4, 0.5), (0.5, -1e15)):
+            row = inside.copy()
+            row[3 + axis], row[6 + axis] = s * room[axis], m * room[axis]
+            rows += [row, inside]
+    rows.append(np.concatenate([room, 1.4 * room, 1.3 * room, [1.0]]))
+    for axis in range(3):
+        row = inside.copy()
+        row[3 + axis] = np.nan
+        rows.append(row)
+    rows = np.array(rows, np.float32)
+    known = len(rows) - 3
+    for L in (62, 3000):
+        print(f"case: positions outside the room, L={L}", flush=True)
+        h, cnt = _run(aug, rows, L)
+        h_ref, cnt_ref = O.rir_batch(rows[:known], L, FS, C)
+        np.testing.assert_array_equal(cnt[:known], cnt_ref)
+        for r in range(known):
+            assert rir_err(h[r], h_ref[r]) <= RIR_TOL, rows[r]
+        assert not h[known:].any() and not cnt[known:].any()
+        alone, _ = _run(aug, inside, L)
+        np.testing.assert_array_equal(h[1:known - 1:2], np.broadcast_to(alone, (len(h[1:known - 1:2]), L)))
+
+
 def test_random_rooms_8000_taps(aug):
     w = W.batch(n_utt=6, seconds=0.1)
     print("case: batch geom 12 rirs, L=8000", flush=True)
