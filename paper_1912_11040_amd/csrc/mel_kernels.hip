@@ -260,7 +260,8 @@ __device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2&
 }
 
 // K = 512: a 256-point complex FFT per frame, 16 lanes per frame, 16 frames per pass of the group.
-// WIN: the window length when it is known at compile time (the paper's front end uses 400), else 0.
+// WIN: the window length when it is known at compile time (the paper's front end uses 400), else 0.  MIX: the signal is
+// mixed on the fly.  STAGED: by way of LDS (see the launcher).
 //
 // What bounds it: vector issue (about 650 vector instructions per pass of four frames, 0.97 of one in four cycles on
 // 4096 utterances of 8 s), with the LDS busy half the time.  The first design sent the second pass's outputs through
@@ -270,7 +271,7 @@ __device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2&
 // 1500 to 1080-1140 us; cepstra from a cosine table in LDS instead of global memory, 256 padded utterances from 350
 // to 134 us.  (The first radix-16 pass on the matrix cores as well measured slower, 1350 us: products of 32-bit
 // floats there take the vector units' time.)
-template <int WIN, bool MIX>
+template <int WIN, bool MIX, bool STAGED>
 __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(MelArgs a, int tab_stride) {
     constexpr int NC = 256;
     extern __shared__ __align__(16) unsigned char smem[];
@@ -388,11 +389,11 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     const float* extra = MIX ? a.extra + start : nullptr;
     const float* gains = s_gains;
 
-    // With a mixture (and the paper's window) the samples of a wavefront's four frames, which overlap, are staged: 16 bytes
+    // With STAGED the samples of a wavefront's four frames, which overlap, are staged: 16 bytes
     // per lane and load, each sample of each source once, mixed while still in registers, into the frames' buffers and
     // from there into the butterflies.  They are requested a pass ahead, when the registers of the transform are free.  What lies past the
     // utterance's end is not read: frames that do not exist compute something, and it is dropped.
-    constexpr bool STAGED = WIN == 400 && MIX;
+    static_assert(!STAGED || (WIN == 400 && MIX), "staging is written for a mixture and 400 samples");
     constexpr int kMore = MIX ? kAheadExtra : 0;
     const int staged = STAGED ? (3 * hop + 400 + 3) & ~3 : 0;
     const int wave_first = __builtin_amdgcn_readfirstlane(first + (slot & ~3));
@@ -731,8 +732,13 @@ hipError_t launch_mel(hipStream_t s, const MelArgs& a) {
     if (a.cfg.feature == AUG_FEAT_MFCC)
         lds += sizeof(vec4) * (size_t)((a.cfg.n_mel + 3) / 4) * ((a.cfg.n_ceps + kMelLanes - 1) & ~(kMelLanes - 1));
     const bool mix = a.n_extra > 0;
-    auto k = a.cfg.win == 400 && a.cfg.hop <= kStagedHop && a.cfg.hop % 2 == 0 ? (mix ? &mel_kernel<400, true> : &mel_kernel<400, false>)
-                              : (mix ? &mel_kernel<0, true> : &mel_kernel<0, false>);
+    // A window of 400 samples has kernels of its own for every hop; its mixtures are staged where the loads cover four frames
+    // and the samples of a frame start on a pair.  (With hops of 161 and 240 the general kernel, 16 rows of inputs instead of
+    // 13 and a wavefront per SIMD fewer, took 379 and 281 us where these take 299 and 221 for 1024 utterances of 8 s,
+    // and 133 and 107 us where these take 103 and 85 for a mixture of 256 x 4 s with three noises.)
+    const bool staged = a.cfg.hop <= kStagedHop && a.cfg.hop % 2 == 0;
+    auto k = a.cfg.win == 400 ? (!mix ? &mel_kernel<400, false, false> : staged ? &mel_kernel<400, true, true> : &mel_kernel<400, true, false>)
+                              : (mix ? &mel_kernel<0, true, false> : &mel_kernel<0, false, false>);
     if (lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

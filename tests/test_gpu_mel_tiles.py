@@ -92,7 +92,7 @@ def test_frame_counts_with_spare_rows(aug):
     _check(aug, FE, lens, 11, spare=2)
 
 
-@pytest.mark.parametrize("n_noise,hop", [(1, 160), (3, 160), (4, 160), (6, 160), (2, 161)])
+@pytest.mark.parametrize("n_noise,hop", [(1, 160), (3, 160), (4, 160), (6, 160), (2, 161), (6, 161), (1, 208), (1, 210), (4, 400)])
 def test_mixture_on_the_fly(aug, n_noise, hop):
     import torch
     fe = dataclasses.replace(FE, hop=hop)
