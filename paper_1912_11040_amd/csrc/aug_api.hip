@@ -247,8 +247,9 @@ int packing_launched(aug_ctx* ctx) {
 }
 
 // A batch's packing between the check of its offsets and the launch that builds its tables.  The context's record of
-// what the device holds is written when the packing is staged; if the call ends before the launch (out of memory), the
-// record is dropped and the next call packs anew.
+// what the device holds is written when the packing is staged; if the call ends before the launch (out of memory, also
+// while it grows the tables themselves, whose old contents are then gone), the record is dropped and the next call packs
+// anew.
 struct PendingPack {
     aug_ctx* ctx;
     aug::PackArgs args{};            // args.n_utt == 0: nothing to do
@@ -298,6 +299,8 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
     if (n_conv > 0x7fffffffLL || n_groups > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many blocks or frame groups in one call");
 
+    aug::PackArgs& pa = pending.args;
+    pa.n_utt = n_utt;                // from here on the record is dropped unless the launch follows
     AUG_TRY(grow(ctx, ctx->d_offsets, n * sizeof(int64_t), "offsets buffer"));
     if (need_conv) {
         AUG_TRY(grow(ctx, ctx->d_conv_first, n * sizeof(int), "block prefix table"));
@@ -308,8 +311,6 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
         AUG_TRY(grow(ctx, ctx->d_frame_items, (size_t)std::max<int64_t>(n_groups, 1) * sizeof(int2), "frame group table"));
     }
     AUG_TRY(ring_reserve(ctx, ring_bytes(n)));
-    aug::PackArgs& pa = pending.args;
-    pa.n_utt = n_utt;
     pa.frames_per_group = frames_per_group;
     pa.d_offsets = ctx->d_offsets.as<int64_t>();
     pa.d_frame_offsets = ctx->d_frame_offsets.as<int64_t>();
@@ -404,10 +405,16 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
 
 int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
     if (n_utt == 0 || ctx->packing.n_frame_groups == 0) return AUG_OK;
-    AUG_TRY(grow(ctx, ctx->window, sizeof(float) * (size_t)cfg->win, "window table"));
+    // (a table that grows loses its contents, also where a later one then runs out of memory)
+    const size_t window_bytes = sizeof(float) * (size_t)cfg->win;
+    if (window_bytes > ctx->window.bytes) ctx->window_n = 0;
+    AUG_TRY(grow(ctx, ctx->window, window_bytes, "window table"));
     AUG_TRY(grow(ctx, ctx->mel_lanes, sizeof(float) * (size_t)aug::mel_lane_floats(), "lane constants"));
-    if (cfg->feature == AUG_FEAT_MFCC)
-        AUG_TRY(grow(ctx, ctx->dct, sizeof(float) * (size_t)cfg->n_ceps * cfg->n_mel, "cosine table"));
+    if (cfg->feature == AUG_FEAT_MFCC) {
+        const size_t dct_bytes = sizeof(float) * (size_t)cfg->n_ceps * cfg->n_mel;
+        if (dct_bytes > ctx->dct.bytes) ctx->dct_ceps = ctx->dct_mel = 0;
+        AUG_TRY(grow(ctx, ctx->dct, dct_bytes, "cosine table"));
+    }
     AUG_TRY(grow(ctx, ctx->mel_tab, sizeof(float2) * (size_t)n_utt * aug::mel_table_stride(cfg->nfft), "mel table"));
     return AUG_OK;
 }
