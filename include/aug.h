@@ -17,9 +17,9 @@
  *     the call returns.
  *   - Work is enqueued on the context's HIP stream and the call returns
  *     without waiting for it, also when the batch's offsets differ from the
- *     previous call's (they reach the device through pinned staging and
- *     asynchronous copies, and the work-item tables are rebuilt there by small
- *     kernels); the caller synchronises that stream before reading outputs.
+ *     previous call's (the device reads them from pinned staging, in the kernel
+ *     that rebuilds the work-item tables); the caller synchronises that stream
+ *     before reading outputs.
  *     HOST arrays are free for reuse as soon as the call returns.  Calls on one
  *     context must not overlap in time from several host threads.
  *   - The context owns a private device workspace (impulse-response spectra,
@@ -241,12 +241,12 @@ int aug_vtlp_mel_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
  * allocation at an awkward moment.  Arguments, output and errors are those of
  * aug_vtlp_mel_batch, and so are the kernels; what differs is where the
  * tables of the call live (device copies of the offsets, the frame-group
- * table, the per-utterance warped mel tables, twiddles, window, cosine
+ * table, the per-utterance warped mel tables, lane constants, window, cosine
  * table): in a fixed array of AUG_STATIC_SCRATCH_BYTES that is part of the
  * library's device image, one copy per GPU, held from the moment the library
  * is loaded on that GPU until the process ends.  The call makes no hipMalloc,
- * hipFree or other allocating call (the pinned staging it copies the offsets
- * through is set up by aug_create).
+ * hipFree or other allocating call (the pinned staging that the offsets are
+ * read from is set up by aug_create).
  *
  * Limits: n_utt <= AUG_STATIC_MAX_UTT, and the output rows, counted in groups
  * of 64 per utterance (sum over u of ceil(rows_u / 64)), at most
@@ -289,8 +289,8 @@ typedef struct aug_vtlp_cfg {
  * j + f = nfft/(2 pi) (w' - 2 atan(a sin w' / (1 + a cos w'))), w' = 2 pi k'/nfft,
  * a = 1 - alpha, k' = 0..nfft/2: the frequency that Eq. (1) maps onto w'.
  * All nfft samples of the inverse DFT of Y are added at the frame's position.
- * Sums of overlapping frames use floating-point atomics, so the last bits of
- * wave_out can differ between runs.
+ * No sample of wave_out is a sum of more than two shares that are added by
+ * floating-point atomics, onto zero, so repeated calls give the same bits.
  * Errors: AUG_ERR_UNSUPPORTED for any cfg other than 800 / 400 / 2048.
  */
 int aug_vtlp_resynth_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const float* wave,

@@ -67,7 +67,7 @@ template <int N> __device__ inline float2 pair_twiddle(const float2* __restrict_
     return cmul(tw[N + k1], tw[N + N / 2 + 1 + k2]);           // exp(-i pi (k1 + 16 k2) / N)
 }
 
-// Spectra of the response partitions, stored in the split order (k at fft_split_pos(k), k = N last)
+// Spectra of the response partitions, stored in the split order (k at (k mod 16) N/16 + k div 16, k = N last)
 // and scaled by 1/(4N): 1/N for the unnormalised inverse, 1/4 for the halves that multiply_pair leaves out.
 // Work groups are persistent: each takes every gridDim.x-th partition and requests the taps of its next one
 // before the row transforms of the current one, whose twiddles come from a table in LDS (no global load of

@@ -169,7 +169,7 @@ __device__ inline void inplace_forward_ab(float2 (&v)[16], float2* buf, const fl
 #pragma unroll
         for (int m = 0; m < 16; ++m) at[P::pad(l) + P::pad(P::M2 * m)] = v[m];
     }
-    fft_sync<FftSync::Wave>();
+    fft_sync();
 }
 
 // Step C: the values are left in LDS for step D, which needs a barrier before it.
@@ -217,7 +217,7 @@ __device__ inline void inplace_inverse(float2 (&v)[16], float2* buf, const float
 #pragma unroll
             for (int m = 0; m < P::RC; ++m) buf[P::pad(c.at(g)) + P::pad(P::RD * m)] = v[P::RC * g + m];
     }
-    fft_sync<FftSync::Wave>();
+    fft_sync();
     {
         const int row = tid / P::RowLanes, l = tid % P::RowLanes;
         const Tw16Short w = read_short(tab + P::kBi0 + P::kShort * l);

@@ -1,21 +1,23 @@
 // Complex FFT of a power-of-two length N held in LDS and worked on by T = N/16 threads,
-// shared by the overlap-save convolution (N = 256..16384) and the STFT (N = nfft/2).
+// and the butterflies that the library's transforms share: the convolution for responses of up to 2048 taps
+// (N = 1024, 2048) and the waveform VTLP (N = 1024) run the passes below, the front end and the convolution for longer
+// responses (fft_inplace.h) have passes of their own.
 //
 // Stockham autosort passes: a pass of radix R over sub-transforms of length NS reads, for
 // butterfly j < N/R, x[j + m N/R] (m < R), multiplies by exp(-+2 pi i (j mod NS) m / (NS R)),
 // takes an R-point DFT and writes y[(j div NS) NS R + (j mod NS) + r NS].  Input and output
 // are in natural order.  The transform runs in place: every thread keeps its 16 values of a
-// pass in registers, so all reads of a pass complete (barrier) before its writes begin.
+// pass in registers, so all reads of a pass complete before its writes begin.
 // Radix 16 while four or more bits remain, then radix 4 and/or 2.
 //
-// Twiddles: one table value w = exp(-2 pi i t / N) per butterfly; its powers are formed by
+// Twiddles come from a table in LDS (RowTwiddles), from per-lane factors folded into the butterflies' additions
+// (dft16_twiddled), or, in the convolution's column step, from one table value per butterfly whose powers are formed by
 // at most four successive complex products.  The inverse uses conjugates and is unscaled.
 //
-// Synchronisation between the reads and writes of a pass is a work-group barrier, or, when all
-// threads of one transform sit in one wavefront, only a wave-level fence (LDS operations of a wave
-// complete in order).  Large transforms are split as N = 16 x M: one radix-16 step across the
-// group, then 16 independent M-point row transforms of at most 64 lanes each, which need no
-// barriers and so overlap each other's LDS and ALU phases (see fft_columns_*).
+// All threads of one transform sit in one wavefront, so a wave-level fence separates the reads and writes of a
+// pass (LDS operations of a wave complete in order).  The convolution's transforms are split as N = 16 x M: one
+// radix-16 step across the group, with barriers, then 16 independent M-point row transforms of at most 64 lanes
+// each, which need none and so overlap each other's LDS and ALU phases (see fft_columns_*).
 //
 // LDS addressing is padded by one complex per 16 (element i lives at lds_pad(i)) so that both
 // the unit-stride reads and the stride-NS writes of every pass spread over all banks.
@@ -196,27 +198,10 @@ template <bool INV> __host__ __device__ inline void dft16(float2* v) {
     dft16_transpose(v);
 }
 
-// 16-point DFT of v[m] w^m.  The first four butterflies share the twiddles w^4, w^8, w^12; those of the second
-// four are (w W16^{r1})^{m2}.  All thirty factors given: 176 instructions.
-struct Tw16 { Tw4 outer, inner[4]; };
-constexpr int kTw16Floats = sizeof(Tw16) / sizeof(float);
-__host__ __device__ inline Tw16 make_tw16(double x) {          // w = exp(-i pi x)
-    Tw16 w;
-    w.outer = make_tw4(4.0 * x);
-    for (int r1 = 0; r1 < 4; ++r1) w.inner[r1] = make_tw4(x + 0.125 * (double)r1);
-    return w;
-}
-template <bool INV> __host__ __device__ inline void dft16_twiddled(float2* v, const Tw16& w) {
-#pragma unroll
-    for (int m2 = 0; m2 < 4; ++m2) dft4_twiddled<INV>(v[m2], v[m2 + 4], v[m2 + 8], v[m2 + 12], w.outer);
-#pragma unroll
-    for (int r1 = 0; r1 < 4; ++r1) dft4_twiddled<INV>(v[4 * r1], v[4 * r1 + 1], v[4 * r1 + 2], v[4 * r1 + 3], w.inner[r1]);
-    dft16_transpose(v);
-}
-// The same from twelve factors, for w that differ from thread to thread: the second four butterflies take w^{m2}
-// and the constant W16^{r1 m2} one after the other.  199 instructions.
+// 16-point DFT of v[m] w^m from twelve factors, for w that differ from thread to thread: the first four butterflies share
+// the twiddles w^4, w^8, w^12; the second four take w^{m2} and the constant W16^{r1 m2} one after the other.  199
+// instructions.
 struct Tw16Short { Tw4 outer, inner; };
-__host__ __device__ inline Tw16Short make_tw16_short(double x) { return Tw16Short{make_tw4(4.0 * x), make_tw4(x)}; }
 template <bool INV> __host__ __device__ inline void dft16_twiddled(float2* v, const Tw16Short& w) {
 #pragma unroll
     for (int m2 = 0; m2 < 4; ++m2) dft4_twiddled<INV>(v[m2], v[m2 + 4], v[m2 + 8], v[m2 + 12], w.outer);
@@ -230,41 +215,31 @@ template <bool INV> __host__ __device__ inline void dft16_twiddled(float2* v, co
     dft16_transpose(v);
 }
 
-// v[m] *= w^m for m = 1..R-1, powers by products of depth <= 4
-template <int R> __device__ inline void twiddle_inputs(float2* v, float2 w1) {
-    if constexpr (R == 2) {
-        v[1] = cmul(v[1], w1);
-    } else if constexpr (R == 4) {
-        const float2 w2 = cmul(w1, w1), w3 = cmul(w2, w1);
-        v[1] = cmul(v[1], w1);
-        v[2] = cmul(v[2], w2);
-        v[3] = cmul(v[3], w3);
-    } else {
-        static_assert(R == 16, "radix");
-        // powers are formed and used in an order that keeps few of them alive: w1..w8, then w8 w_m
-        const float2 w2 = cmul(w1, w1);
-        const float2 w3 = cmul(w2, w1);
-        const float2 w4 = cmul(w2, w2);
-        v[1] = cmul(v[1], w1);
-        v[2] = cmul(v[2], w2);
-        v[3] = cmul(v[3], w3);
-        v[4] = cmul(v[4], w4);
-        const float2 w5 = cmul(w4, w1);
-        const float2 w6 = cmul(w4, w2);
-        const float2 w7 = cmul(w4, w3);
-        const float2 w8 = cmul(w4, w4);
-        v[5] = cmul(v[5], w5);
-        v[6] = cmul(v[6], w6);
-        v[7] = cmul(v[7], w7);
-        v[8] = cmul(v[8], w8);
-        v[9] = cmul(v[9], cmul(w8, w1));
-        v[10] = cmul(v[10], cmul(w8, w2));
-        v[11] = cmul(v[11], cmul(w8, w3));
-        v[12] = cmul(v[12], cmul(w8, w4));
-        v[13] = cmul(v[13], cmul(w8, w5));
-        v[14] = cmul(v[14], cmul(w8, w6));
-        v[15] = cmul(v[15], cmul(w8, w7));
-    }
+// v[m] *= w^m for m = 1..15, powers by products of depth <= 4
+__device__ inline void twiddle_inputs(float2* v, float2 w1) {
+    // powers are formed and used in an order that keeps few of them alive: w1..w8, then w8 w_m
+    const float2 w2 = cmul(w1, w1);
+    const float2 w3 = cmul(w2, w1);
+    const float2 w4 = cmul(w2, w2);
+    v[1] = cmul(v[1], w1);
+    v[2] = cmul(v[2], w2);
+    v[3] = cmul(v[3], w3);
+    v[4] = cmul(v[4], w4);
+    const float2 w5 = cmul(w4, w1);
+    const float2 w6 = cmul(w4, w2);
+    const float2 w7 = cmul(w4, w3);
+    const float2 w8 = cmul(w4, w4);
+    v[5] = cmul(v[5], w5);
+    v[6] = cmul(v[6], w6);
+    v[7] = cmul(v[7], w7);
+    v[8] = cmul(v[8], w8);
+    v[9] = cmul(v[9], cmul(w8, w1));
+    v[10] = cmul(v[10], cmul(w8, w2));
+    v[11] = cmul(v[11], cmul(w8, w3));
+    v[12] = cmul(v[12], cmul(w8, w4));
+    v[13] = cmul(v[13], cmul(w8, w5));
+    v[14] = cmul(v[14], cmul(w8, w6));
+    v[15] = cmul(v[15], cmul(w8, w7));
 }
 
 constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n >> 1); }
@@ -327,31 +302,11 @@ __device__ inline void fft_store(const float2 (&v)[16], float2* buf, int tid) {
     }
 }
 
-enum class FftSync { Group, Wave };
-
-template <FftSync S> __device__ inline void fft_sync() {
-    if constexpr (S == FftSync::Group) {
-        __syncthreads();
-    } else {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    }
-}
-
-// TWS: the table holds exp(-2 pi i t / (N TWS)), i.e. it was built for a TWS times longer transform.
-template <int N, int T, int R, int NS, bool INV, int TWS>
-__device__ inline void fft_compute(float2 (&v)[16], const float2* __restrict__ tw, int tid) {
-#pragma unroll
-    for (int bi = 0; bi < 16 / R; ++bi) {
-        if constexpr (NS > 1) {
-            const int k = (tid + bi * T) % NS;
-            float2 w1 = tw[k * (N / (NS * R)) * TWS];
-            if (INV) w1.y = -w1.y;
-            twiddle_inputs<R>(&v[bi * R], w1);
-        }
-        SmallDft<R, INV>::run(&v[bi * R]);
-    }
+// what the wavefront wrote to LDS before is there for the reads after
+__device__ inline void fft_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Natural index of value v[bi R + r] after the last pass, and before the first pass of input v[bi R + m].
@@ -364,23 +319,6 @@ template <int N, int T>
 __device__ inline int fft_in_index(int tid, int i) {
     constexpr int R = FftPlan<N>::radix(0);
     return tid + (i / R) * T + (i % R) * (N / R);
-}
-
-// Run passes P.. of the transform.  On entry v holds the inputs of pass P (fft_in_index order for
-// P = 0); on return it holds the outputs of the last pass (fft_out_index order), not yet stored.
-// All T threads of the group must call; buf contents are overwritten.
-template <int N, int T, bool INV, FftSync S = FftSync::Group, int TWS = 1, int P = 0>
-__device__ inline void fft_passes(float2 (&v)[16], float2* buf, const float2* __restrict__ tw, int tid) {
-    using Plan = FftPlan<N>;
-    constexpr int R = Plan::radix(P), NS = Plan::ns(P);
-    fft_compute<N, T, R, NS, INV, TWS>(v, tw, tid);
-    if constexpr (P + 1 < Plan::kPasses) {
-        fft_store<N, T, R, NS>(v, buf, tid);
-        fft_sync<S>();
-        fft_load<N, T, Plan::radix(P + 1)>(v, buf, tid);
-        fft_sync<S>();
-        fft_passes<N, T, INV, S, TWS, P + 1>(v, buf, tw, tid);
-    }
 }
 
 // Store the last pass's outputs in natural order.
@@ -417,13 +355,11 @@ __device__ inline void fft_load_natural(float2 (&v)[16], const float2* buf, int 
 // to row k1, column n2.  Row k1 lives at buf[lds_pad(k1 M + .)] and is transformed by M/16 lanes of
 // one wavefront.  After the forward transform frequency k = k1 + 16 k2 sits at row k1, column k2.
 
-template <int N> __device__ __host__ constexpr int fft_split_pos(int k) { return (k & 15) * (N / 16) + (k >> 4); }
-
 // forward column step on registers: v[n1] -> v[k1] (twiddled), to be stored at row k1, column n2
 template <int N>
 __device__ inline void fft_columns_forward(float2 (&v)[16], const float2* __restrict__ tw, int n2) {
     SmallDft<16, false>::run(v);
-    twiddle_inputs<16>(v, tw[n2]);
+    twiddle_inputs(v, tw[n2]);
 }
 
 // inverse column step: v[k1] (row k1, column n2) -> v[n1] = N x[n2 + M n1]
@@ -431,7 +367,7 @@ template <int N>
 __device__ inline void fft_columns_inverse(float2 (&v)[16], const float2* __restrict__ tw, int n2) {
     float2 w1 = tw[n2];
     w1.y = -w1.y;
-    twiddle_inputs<16>(v, w1);
+    twiddle_inputs(v, w1);
     SmallDft<16, true>::run(v);
 }
 
@@ -478,8 +414,10 @@ struct RowTwiddles {
     }
 };
 
-// fft_passes with every twiddle factor read from a RowTwiddles table in LDS
-template <int M, int T, bool INV, FftSync S, int P = 0>
+// All passes, with every twiddle factor read from a RowTwiddles table in LDS.  On entry v holds the inputs of the first
+// (fft_in_index order); on return it holds the outputs of the last (fft_out_index order), not yet stored.  All T threads of
+// the transform must call; buf contents are overwritten.
+template <int M, int T, bool INV, int P = 0>
 __device__ inline void fft_passes_table(float2 (&v)[16], float2* buf, const float2* tab, int tid) {
     using Plan = FftPlan<M>;
     constexpr int R = Plan::radix(P), NS = Plan::ns(P);
@@ -495,29 +433,16 @@ __device__ inline void fft_passes_table(float2 (&v)[16], float2* buf, const floa
     }
     if constexpr (P + 1 < Plan::kPasses) {
         fft_store<M, T, R, NS>(v, buf, tid);
-        fft_sync<S>();
+        fft_sync();
         fft_load<M, T, Plan::radix(P + 1)>(v, buf, tid);
-        fft_sync<S>();
-        fft_passes_table<M, T, INV, S, P + 1>(v, buf, tab, tid);
+        fft_sync();
+        fft_passes_table<M, T, INV, P + 1>(v, buf, tab, tid);
     }
 }
 
-// The 16 row transforms, in place in natural order within each row; wave-level synchronisation only.
-// Thread tid works on row tid / (M/16) as lane tid % (M/16).  Rows must be complete (barrier) before.
-template <int N, bool INV>
-__device__ inline void fft_rows(float2* buf, const float2* __restrict__ tw, int tid) {
-    constexpr int M = N / 16, LANES = M / 16;
-    static_assert(LANES >= 1 && LANES <= 64, "a row is transformed inside one wavefront");
-    float2* row = buf + lds_pad((tid / LANES) * M);
-    const int lane = tid % LANES;
-    float2 v[16];
-    fft_load_natural<M, LANES>(v, row, lane);
-    fft_sync<FftSync::Wave>();
-    fft_passes<M, LANES, INV, FftSync::Wave, 16>(v, row, tw, lane);
-    fft_store_natural<M, LANES>(v, row, lane);
-}
-
-// the same with the twiddles of a RowTwiddles<N / 16> table
+// The 16 row transforms, in place in natural order within each row, with the twiddles of a RowTwiddles<N / 16> table;
+// wave-level synchronisation only.  Thread tid works on row tid / (M/16) as lane tid % (M/16).  Rows must be complete
+// (barrier) before.
 template <int N, bool INV>
 __device__ inline void fft_rows_table(float2* buf, const float2* tab, int tid) {
     constexpr int M = N / 16, LANES = M / 16;
@@ -526,8 +451,8 @@ __device__ inline void fft_rows_table(float2* buf, const float2* tab, int tid) {
     const int lane = tid % LANES;
     float2 v[16];
     fft_load_natural<M, LANES>(v, row, lane);
-    fft_sync<FftSync::Wave>();
-    fft_passes_table<M, LANES, INV, FftSync::Wave>(v, row, tab, lane);
+    fft_sync();
+    fft_passes_table<M, LANES, INV>(v, row, tab, lane);
     fft_store_natural<M, LANES>(v, row, lane);
 }
 

@@ -466,11 +466,11 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
                 if (most == staged - 4) *reinterpret_cast<vec4*>(to) = vec4{ahead[i].x, ahead[i].y, ahead[i].z, ahead[i].w};
                 else *reinterpret_cast<SampleQuad*>(to) = ahead[i];
             }
-            fft_sync<FftSync::Wave>();
+            fft_sync();
             const float2* mine = reinterpret_cast<const float2*>(wave_buf + (slot & 3) * hop);      // (the hop is even)
 #pragma unroll
             for (int i = 0; i < kRows; ++i) v[i] = mine[min(sub + kMelLanes * i, WIN / 2 - 1)];    // (past the window: times zero)
-            fft_sync<FftSync::Wave>();
+            fft_sync();
         } else {
             // Loads are unconditional: a slot past the utterance's last frame recomputes that last frame (its
             // result is dropped) and inputs past the window are read from the frame's last samples and meet a
@@ -549,16 +549,16 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
             const float* const from = buf + sub;
 #pragma unroll
             for (int r = 0; r < 16; ++r) to[r] = v[r].x;
-            fft_sync<FftSync::Wave>();                   // a frame's 16 lanes share a wavefront
+            fft_sync();                   // a frame's 16 lanes share a wavefront
 #pragma unroll
             for (int m = 0; m < 16; ++m) v[m].x = from[17 * m];
-            fft_sync<FftSync::Wave>();
+            fft_sync();
 #pragma unroll
             for (int r = 0; r < 16; ++r) to[r] = v[r].y;
-            fft_sync<FftSync::Wave>();
+            fft_sync();
 #pragma unroll
             for (int m = 0; m < 16; ++m) v[m].y = from[17 * m];
-            fft_sync<FftSync::Wave>();
+            fft_sync();
         }
         dft16_twiddled<false>(v, tw);
 
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         // bin N/2 is its own partner; the three places behind bin N meet zero weights and must be finite
         if (sub < 4) buf[sub == 0 ? NC / 2 : NC + sub] = sub == 0 ? 4.f * fmaf(v[8].x, v[8].x, v[8].y * v[8].y) : 0.f;
         if (STAGED) request(it + 1 < passes ? t_wave + kMelSlots : 0x7fffffff);
-        fft_sync<FftSync::Wave>();
+        fft_sync();
 
         // pieces of the projection: row i of a block is frame i of the wavefront, column j channel 4 quad + j
         if (rounds) {
@@ -603,7 +603,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
                 wq += 64 * (steps / 4);
                 sums[r] = acc0 + acc1;
             }
-            fft_sync<FftSync::Wave>();                   // the powers are read before the sums take their place
+            fft_sync();                   // the powers are read before the sums take their place
 #pragma unroll
             for (int r = 0; r < kMaxRounds; ++r) {
                 if (r >= rounds) break;
@@ -611,7 +611,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
 #pragma unroll
                 for (int i = 0; i < 4; ++i) to[i * kSlotFloats] = sums[r][i];
             }
-            fft_sync<FftSync::Wave>();
+            fft_sync();
         }
         // energy of channel m: the sum of its pieces, without a plan a plain sum over all bins
         auto energy = [&](int m) {
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
             } else {
                 const float le = m < n_mel ? logf(fmaxf(e, a.cfg.log_floor)) : 0.f;
                 if (to_lds) {
-                    fft_sync<FftSync::Wave>();
+                    fft_sync();
                     buf[m] = le;
                 } else if (live) {
                     feats[t * n_mel + m] = le;
@@ -655,7 +655,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         }
         if (feature == AUG_FEAT_MFCC) {
             // every lane takes the dot products of its coefficients with the whole vector, four channels at a time
-            fft_sync<FftSync::Wave>();
+            fft_sync();
             const vec4* lq = reinterpret_cast<const vec4*>(buf);
 #pragma unroll 1
             for (int q = sub; q < q_pad; q += kMelLanes) {
@@ -674,7 +674,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         }
         if (!live && t < rows_u)
             for (int m = sub; m < n_out; m += kMelLanes) feats[t * n_out + m] = 0.f;
-        fft_sync<FftSync::Wave>();                       // everything is read before the next frame's exchange
+        fft_sync();                       // everything is read before the next frame's exchange
     }
 }
 

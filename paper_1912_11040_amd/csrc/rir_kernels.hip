@@ -9,9 +9,9 @@
 // The tap index is integer work decided by floating point, so it follows one fixed
 // fp64 recipe with no contraction:
 //     d2 = (dx*dx + dy*dy) + dz*dz;  idx = floor(sqrt(d2) * (fs/c) + 0.5)
-// A cheap estimate of sqrt (the hardware's double-precision rsq + one Newton step) decides
-// the index whenever the result is farther from a rounding boundary than the estimate's
-// error bound; the rare remaining images take the exact correctly-rounded sqrt.
+// An estimate of sqrt from the hardware's double-precision rsq decides the index whenever the result is
+// farther from a rounding boundary than the estimate's error bound; the images nearer to one take a Newton
+// step more, and those that this leaves open, rarely, the exact correctly-rounded sqrt.
 //
 // Layout of the work
 //   * plan kernels: one thread per response cuts its taps into shells [n0, n1) of about
@@ -29,7 +29,7 @@
 //     A wave takes 64 live columns at a time; their z ranges are cut into pieces of at most kPiece
 //     images, a wave scan numbers the pieces, and lanes take pieces 64 at a time (a piece finds its column by
 //     counting bits in a map of the columns' first pieces) and walk them, two images side by side.
-//     Bound by issue and by LDS about equally (256 x 16000 taps: vector units 0.80, LDS 0.78 of the time, half of that
+//     Bound by issue and by LDS about equally (256 x 16000 taps: vector units 0.80, LDS 0.75 of the time, half of that
 //     conflicts of reads at scattered table entries and of sums at scattered taps).
 //     Rooms so flat or narrow that an axis has more images than the tables hold, and positions far outside
 //     the room, take a plain path (all columns of the bounding box, every z image of a live column).

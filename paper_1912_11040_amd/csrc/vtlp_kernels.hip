@@ -129,14 +129,14 @@ __device__ inline LaneTwiddles lane_twiddles(const float2* __restrict__ tw, int 
 template <bool INV>
 __device__ inline void later_passes(float2 (&v)[16], float2* buf, const LaneTwiddles& w, int lane) {
     fft_store<kN, 64, 16, 1>(v, buf, lane);
-    fft_sync<FftSync::Wave>();
+    fft_sync();
     fft_load<kN, 64, 16>(v, buf, lane);
-    fft_sync<FftSync::Wave>();
+    fft_sync();
     dft16_twiddled<INV>(v, w.second);
     fft_store<kN, 64, 16, 16>(v, buf, lane);
-    fft_sync<FftSync::Wave>();
+    fft_sync();
     fft_load<kN, 64, 4>(v, buf, lane);
-    fft_sync<FftSync::Wave>();
+    fft_sync();
 #pragma unroll
     for (int i = 0; i < 4; ++i) dft4_twiddled<INV>(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3], w.third[i]);
 }
@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
         dft16_outer_inputs(v);
         later_passes<false>(v, buf, lane_tw, l);
         fft_store_natural<kN, 64>(v, buf, l);
-        fft_sync<FftSync::Wave>();
+        fft_sync();
 
         // Packed transform Z -> twice the real spectrum X, in place: with A = Z[k], B = conj Z[N-k], E = A + B,
         // O = -i (A - B), w = exp(-i pi k / N):  X[k] = E + w O,  X[N-k] = conj(E - w O).  (The halves of both splits are
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
             unpack(below + lds_pad(64 * i), at_n, i == 0 && l == 0 ? buf : at_n, pair_tw[i]);
         }
         if (l == 0) unpack(buf + lds_pad(kN / 2), buf + lds_pad(kN / 2), buf + lds_pad(kN / 2), quarter_tw);
-        fft_sync<FftSync::Wave>();
+        fft_sync();
 
         // Warped spectrum Y (two interpolated bins per pair), packed for the inverse transform:
         // Ye = Y[k] + conj Y[N-k], Yo = conj(w) (Y[k] - conj Y[N-k]), Z'[k] = Ye + i Yo,
@@ -316,17 +316,17 @@ __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
             pack(l + 64 * i, i, pair_tw[i]);
         }
         if (l == 0) pack(kN / 2, 8, quarter_tw);
-        fft_sync<FftSync::Wave>();
+        fft_sync();
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             below[lds_pad(64 * i)] = zk[i];
             if (i || l) above[lds_pad(kN - 64 - 64 * i)] = zn[i];
         }
         if (l == 0) buf[lds_pad(kN / 2)] = zk[8];
-        fft_sync<FftSync::Wave>();
+        fft_sync();
 
         fft_load_natural<kN, 64>(v, buf, l);
-        fft_sync<FftSync::Wave>();
+        fft_sync();
         dft16<true>(v);
         later_passes<true>(v, buf, lane_tw, l);
         // v[i] is packed output m = fft_out_index(l, i) times 4 N: samples at offsets 2m, 2m + 1 (m < N/2)
@@ -342,10 +342,10 @@ __global__ __launch_bounds__(kThreads, 2) void vtlp_resynth_kernel(
             a.y += v[i].y * scale;
             *slot = a;
         }
-        fft_sync<FftSync::Wave>();
+        fft_sync();
         // the next frame starts kHop later: the first kHop positions of the window are complete for this run
         flush_window(acc, y, len, centre - kReach, kHop / 2, excl_lo, excl_hi, l);
-        fft_sync<FftSync::Wave>();                       // also: the next frame reuses the transform buffer
+        fft_sync();                       // also: the next frame reuses the transform buffer
     }
     flush_window(acc, y, len, t_last * kHop - kReach + kHop, (kFft - kHop) / 2, excl_lo, excl_hi, lane);
 }
