@@ -169,7 +169,7 @@ int aug_rir_mics_batch(aug_ctx* ctx, int n_rir, int n_mic, const float* geom, co
  *               zeros (the transforms alone would leave rounding noise
  *               there), so a source whose direct path arrives after the
  *               utterance has ended has energy 0 and gain 0.
- *   gains_out   DEVICE float [n_utt][n_noise] or NULL: the g_j.
+ *   gains_out   DEVICE float [n_utt][n_noise] or NULL: the g_j.  May be snr_db.
  */
 int aug_convolve_mix_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets,
                            const float* speech, int n_noise, const float* noise,
@@ -303,7 +303,7 @@ int aug_vtlp_resynth_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, cons
  * Responses and the mixture stay in the context's workspace unless asked for:
  *   rir_out    DEVICE float [n_utt][1+n_noise][rir_len] or NULL
  *   mixed_out  DEVICE float [total] or NULL
- *   gains_out  DEVICE float [n_utt][n_noise] or NULL
+ *   gains_out  DEVICE float [n_utt][n_noise] or NULL; may be snr_db
  */
 int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const float* speech,
                        int n_noise, const float* noise, const float* geom, int rir_len,

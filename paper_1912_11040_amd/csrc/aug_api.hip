@@ -442,8 +442,11 @@ int run_rir(aug_ctx* ctx, int n_rir, const aug::Rooms& rooms, int rir_len, float
     return AUG_OK;
 }
 
-// Reverberates every source and measures the energies.  With mixed_out the mixture
-// is written there; without it the caller mixes on the fly from the context's reverberated signals and energies.
+bool share_memory(const float* a, const float* b, int64_t n) { return a < b + n && b < a + n; }
+
+// Reverberates every source and measures the energies.  With mixed_out the mixture and the gains are written; without it
+// the caller mixes on the fly from the context's reverberated signals and energies, and asks for the gains itself once it
+// has read the SNRs, which gains_out may overwrite.
 int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, const float* noise,
                      const float* rir, int rir_len, const float* snr_db, float* mixed_out, float* gains_out) {
     const aug::Packing& pk = ctx->packing;
@@ -488,13 +491,13 @@ int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, 
     ca.first_tap = ctx->first_tap.as<int>();
     AUG_HIP(aug::launch_convolve(ctx->stream, fft_n, tw, ca, ctx->n_cu), "convolution kernel");
     AUG_TRY(mark(ctx, AUG_STAGE_CONVOLVE));
-    if (mixed_out)
-        AUG_HIP(aug::launch_mix(ctx->stream, n_utt, ctx->d_offsets.as<int64_t>(), stride, n_src, ctx->reverb.as<float>(),
-                                energy, snr_db, mixed_out, gains_out, max_len), "mix kernel");
-    else if (gains_out)
-        AUG_HIP(aug::launch_gains(ctx->stream, n_utt, n_src, energy, snr_db, gains_out), "gain kernel");
-    if (mixed_out || gains_out) AUG_TRY(mark(ctx, AUG_STAGE_MIX));
-    return AUG_OK;
+    if (!mixed_out) return AUG_OK;
+    // (the first group of an utterance writes its gains while others still read the SNRs)
+    const bool gains_apart = gains_out && share_memory(gains_out, snr_db, (int64_t)n_utt * n_noise);
+    AUG_HIP(aug::launch_mix(ctx->stream, n_utt, ctx->d_offsets.as<int64_t>(), stride, n_src, ctx->reverb.as<float>(),
+                            energy, snr_db, mixed_out, gains_apart ? nullptr : gains_out, max_len), "mix kernel");
+    if (gains_apart) AUG_HIP(aug::launch_gains(ctx->stream, n_utt, n_src, energy, snr_db, gains_out), "gain kernel");
+    return mark(ctx, AUG_STAGE_MIX);
 }
 
 // The mel tables' arguments; the band edges are kept from call to call of one configuration.
@@ -935,7 +938,12 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     // reverberated speech as it loads its frames, which saves one pass over the batch through HBM.
     const float* reverb = ctx->reverb.as<float>();
     const int64_t stride = reverb_stride(total);
-    return run_mel(ctx, n_utt, reverb, cfg, feats_out, n_noise, reverb + stride, stride, ctx->energy.as<double>(), snr_db);
+    const double* energy = ctx->energy.as<double>();
+    AUG_TRY(run_mel(ctx, n_utt, reverb, cfg, feats_out, n_noise, reverb + stride, stride, energy, snr_db));
+    if (!gains_out) return AUG_OK;
+    AUG_TRY(mark(ctx, -1));
+    AUG_HIP(aug::launch_gains(ctx->stream, n_utt, n_src, energy, snr_db, gains_out), "gain kernel");
+    return mark(ctx, AUG_STAGE_MIX);
 }
 
 }  // extern "C"

@@ -74,6 +74,25 @@ def test_tiny_config_end_to_end(aug):
     assert feat_err(again["feats"], got["feats"].astype(np.float64)) <= 1e-5
 
 
+@pytest.mark.parametrize("want_mixed", [True, False])
+def test_gains_over_their_snrs(aug, want_mixed):
+    """gains_out may be the array that holds the SNRs: every use of the SNRs comes before it."""
+    import torch
+    w = W.batch(n_utt=64, seconds=4.0)
+    print(f"case: gains in place of SNRs, mixture written: {want_mixed}", flush=True)
+    apart = _run(aug, w, want_rir=False, want_mixed=want_mixed)
+    d = DeviceWorkload(w)
+    feats, snr = d.empty_feats(), d.snr_db.clone()
+    mixed = torch.full((w.total,), float("nan"), dtype=torch.float32, device="cuda") if want_mixed else None
+    aug.aug_pipeline_batch(w.offsets, d.speech, d.noise, d.geom, w.rir_len, w.fs, w.c, snr, d.alpha, w.frontend,
+                           d.frame_offsets, feats, None, mixed, snr)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(snr.cpu().numpy().reshape(w.n_utt, w.n_noise), apart["gains"], rtol=GAIN_TOL)
+    assert feat_err(feats.cpu().numpy(), apart["feats"].astype(np.float64)) <= FEAT_TOL
+    if want_mixed:
+        assert wave_err(mixed.cpu().numpy(), apart["mixed"].astype(np.float64), w.offsets) <= WAVE_TOL
+
+
 def test_batch_config_subset(aug):
     w = W.batch(n_utt=4, seconds=4.0)
     print("case: batch config, 4 utterances, L=8000, direct oracle", flush=True)
