@@ -366,7 +366,7 @@ def test_batch_with_no_frames_and_batch_with_no_samples(aug):
 def test_batches_with_new_lengths_every_call(aug):
     # The example queue hands over a batch with new lengths at every step (Sec. 2.2): batches that differ in
     # utterance count, lengths and response length alternate on one context with no synchronisation between
-    # the calls (nine calls, so the four staging slots for the offsets are reused twice); every call's
+    # the calls (40 calls, so the sixteen staging slots for the offsets are reused twice); every call's
     # features and gains against the oracle.
     import torch
     ws = [W.varlen(n_utt=3, rir_len=1200, min_s=0.05, max_s=0.9, seed=21),
@@ -375,7 +375,7 @@ def test_batches_with_new_lengths_every_call(aug):
     refs = [_oracle(w) for w in ws]
     devs = [DeviceWorkload(w) for w in ws]
     outs = []
-    for k in range(9):
+    for k in range(40):
         w, d = ws[k % 3], devs[k % 3]
         feats = d.empty_feats()
         gains = torch.full((w.n_utt, w.n_noise), float("nan"), dtype=torch.float32, device="cuda")
