@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "26ed125015052ce0",
-    "varlen": {"rir": 84493024, "rir_spectrum": 202457166, "convolve": 1256028415, "mel": 612607108},
-    "throughput": {"rir": 447056275, "rir_spectrum": 1217756672, "convolve": 13991084909, "mel": 2175878532},
+    "digest": "b6f2fb3f932447b7",
+    "varlen": {"rir": 84529771, "rir_spectrum": 202477975, "convolve": 1256927984, "mel": 612817306},
+    "throughput": {"rir": 447095288, "rir_spectrum": 1218139929, "convolve": 13978578920, "mel": 2176123960},
 }
 
 

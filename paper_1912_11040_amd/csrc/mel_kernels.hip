@@ -36,7 +36,7 @@ __device__ inline float hamming(int i, int win) {
 // consecutive mel channels (a "quad"); the sixteen blocks run through different stretches of bins.  The bins of
 // a quad are contiguous (five bands of them); they are cut into pieces of `steps` bins, a block each, in `rounds`
 // times sixteen pieces over all quads.  rounds and steps are chosen per utterance so that the number of
-// instructions is least: 24 for 40 channels, where a dense product would need 643.  There is no plan where the bins are
+// instructions is least: 24 for 40 channels, where a dense product would need 161.  There is no plan where the bins are
 // not in the order of their bands (warp factors outside (0, 2), for which Eq. (1) does not increase and puts the bins at or
 // beyond the ends of the band), or where more than a hundred channels meet a strong warp (the nearest to 1 that were
 // found: 0.64 and 1.39); the kernel then sums over all bins.

@@ -22,7 +22,7 @@
 // both come from fp64 arithmetic so that the choice of the bin pair matches a double-precision evaluation.
 //
 // What bounds it: latency.  The windows and transform buffers leave room for two wavefronts per SIMD, whose
-// vector units are busy half the time and the LDS two fifths of it (1450 vector and 218 LDS instructions per frame on 256
+// vector units are busy half the time and the LDS two fifths of it (1440 vector and 217 LDS instructions per frame on 256
 // utterances of 1-16 s).  Twiddles folded into multiply-adds, zero inputs skipped, mirrored bins at constant distances from
 // two places and frames inside the utterance without range tests took that batch from 530 to 506 us, an utterance's
 // frames shared evenly among its wavefronts instead of in runs of 16 and a rest to 495, zeros only where runs meet to 484.  Longer runs would save
