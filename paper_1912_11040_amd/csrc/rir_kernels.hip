@@ -14,28 +14,35 @@
 // step more, and those that this leaves open, rarely, the exact correctly-rounded sqrt.
 //
 // Layout of the work
-//   * plan kernels: one thread per response cuts its taps into shells [n0, n1) of about
-//     equal image count (equal volume of the spherical shell) and at most kMaxTaps taps; the shell size
-//     follows the batch's estimated work per persistent group.  Every shell gets an estimate of its work
+//   * plan kernels: a response's taps are cut into shells [n0, n1) of about equal estimated work, at most kMaxTaps taps
+//     wide; the shell size follows the batch's work per persistent group.  Every shell gets an estimate of its work
 //     and a counting sort orders the items heaviest first.
 //   * image kernel: persistent work groups fetch items from a counter.  An item owns its
 //     taps, so sums live in LDS and are stored once, without global atomics.
-//     The z images of the response (both q, both signs) are merged into one LDS table sorted by
-//     dz*dz, so the images of an (x image, y image) column that can fall inside the shell are one
-//     contiguous range of that table between r_in^2 - a and r_out^2 - a, whose ends are counted from the
-//     two arithmetic progressions that the axis's images form rather than searched for.
-//     The y images are sorted the same way, so the live columns of an x image are a prefix of the
-//     y table; a prefix sum over the x images numbers the live columns and dead ones are never seen.
-//     A wave takes 64 live columns at a time; their z ranges are cut into pieces of at most kPiece
-//     images, a wave scan numbers the pieces, and lanes take pieces 64 at a time (a piece finds its column by
-//     counting bits in a map of the columns' first pieces) and walk them, two images side by side.
-//     Bound by issue and by LDS about equally (256 x 16000 taps: vector units 0.80, LDS 0.75 of the time, half of that
-//     conflicts of reads at scattered table entries and of sums at scattered taps).
+//     The y images of the response (both q, both signs) lie in an LDS table in order of distance, so the columns (x image,
+//     y image) of an x image that can still reach the shell are the first of that table; a prefix sum over the x images
+//     numbers the columns and dead ones are never seen.
+//     Along z the images are four arithmetic progressions of one step, 2 L.  A column's images inside the shell are
+//     therefore those of a range of steps p, with up to three more at either end, and a lane walks a column from the
+//     first p to the last, four images a step, without reading any table of images: distances are formed from the step,
+//     amplitudes from one power per step.  Columns are sorted by length, some thousand at a time, so that the 64 lanes of a
+//     wavefront walk columns of one length.
 //     Rooms so flat or narrow that an axis has more images than the tables hold, and positions far outside
 //     the room, take a plain path (all columns of the bounding box, every z image of a live column).
 //   * amplitudes accumulate as 64-bit fixed point (2^-56, each increment rounded to the nearest unit)
-//     with integer LDS atomics: gfx950 executes float LDS atomics about thirty times slower than integer
+//     with integer LDS atomics: gfx950 executes float LDS atomics far slower than integer
 //     ones, and integer sums do not depend on the order of arrival nor on how a batch is cut into items.
+//
+// What bounds it: vector issue (a double-precision operation takes four cycles, its rsq sixteen: 55 per image with four
+// wavefronts per SIMD) and LDS (64 adds of 64 bits to scattered places take the CU 13 to 16 cycles, six if no two meet in a
+// bank).  Measured on 2000 responses of 8000 taps, plan included: a walk of pieces of 14 images read from a sorted table of z images, which
+// were dealt to lanes as a wavefront's 64 columns gave them, 289 us (a quarter of the lanes idle in the mean, up to half
+// in small batches); this walk, 261; the item's constants formed by one wavefront while the others walk, 239; rows found by
+// comparing 64 at once and the near images walked last, 224; the ends of a column walked like its middle, with a
+// slot per lane for what lies outside, 215.  Groups of 1024 threads with 64 registers
+// took 294.  What the long responses want costs this batch 9 of those us: six candidate columns per thread and chunk instead of
+// four, rows with a gap where the cut leaves their middle empty, and shells of equal work (the plan is 16 us instead of 10).  For
+// it 32 responses of 32768 taps went from 210 to 126 us, 192 of 16000 from 252 to 186.
 
 #include "aug_internal.h"
 
@@ -44,15 +51,15 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kMaxTaps = 5632;            // taps owned by one item (LDS: 8 bytes each)
+constexpr int kMaxTaps = 5568;            // taps owned by one item (LDS: 8 bytes each)
 constexpr int kMinTaps = 64;
-constexpr int kPow = 1024;                // beta^k table entries held in LDS
-constexpr int kAxisCap = 320;             // y or z images per q held in the sorted LDS tables 
-// Images per piece, even (two are worked on side by side).  A column's pieces start kPiece sixteen-byte entries apart, so
-// the number also decides which LDS banks neighbouring lanes read: 2000 responses of 8000 taps take 312 us at 10 and
-// 14, 320 at 12, 318 at 18, 395 at 16 (all lanes of a column on the same banks).
-constexpr int kPiece = 14;
-constexpr int kStartWords = 32;           // pieces are dealt in chunks of 32 * kStartWords (one bit each in LDS)
+constexpr int kPow = 704;                 // beta^k table entries held in LDS: more than a column of the fast walk can ask for
+constexpr int kAxisCap = 320;             // x or y images per q held in the LDS tables
+constexpr int kYCap = 2 * kAxisCap + 8;
+constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) held in the LDS table
+constexpr int kPerThread = 6;             // candidate columns per thread and chunk
+constexpr int kChunk = kThreads * kPerThread;
+constexpr int kColumns = 3 * kThreads;    // live columns that the LDS has room for: a chunk's are walked in as many goes
 // Work per item, in image visits (see item_cost): the batch's estimated work divided by the number of
 // persistent groups and by kItemsPerGroup, within limits.  Thick shells visit fewer (x, y) columns per image
 // (every shell sets up all columns inside its outer radius), thin ones even out the groups' finishing
@@ -78,7 +85,11 @@ __device__ inline double axis_delta(const Axis& a, int q, int n) {
     return __dsub_rn(coord, a.mic);
 }
 
-__device__ inline int iabs(int v) { return v < 0 ? -v : v; }
+// reflections of image (q, n) along its axis: |n - q| + |n|
+__device__ inline int reflections(int q, int n) {
+    const int v = 2 * n - q;
+    return v < 0 ? -v : v;
+}
 
 // A value that every lane of the wavefront has computed alike, moved to scalar registers: what an item's
 // geometry determines is the same in all lanes and would otherwise occupy vector registers for the whole item.
@@ -115,6 +126,15 @@ __device__ inline void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Barrier of the work group, with the wait for this wavefront's LDS operations spelled out: where a barrier begins a loop's
+// body, the compiler (ROCm 7.2) has been seen to leave out the wait that the barrier's fence asks for.
+__device__ inline void group_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0xc07f);                    // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
 // inclusive sum over the lanes of a wavefront: shifts within rows of sixteen lanes, then the rows' last lanes passed on
 __device__ inline int wave_inclusive_scan(int v) {
     v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true);      // row_shr:1
@@ -133,46 +153,68 @@ constexpr int kClasses = 32;            // cost classes for the order in which i
 constexpr int kCtrlWork = 2 + 2 * kClasses;
 constexpr int kCtrlInts = kCtrlWork + 1;
 
-// Estimate of the work in a response's taps [n0, n1), in units of one image visit: the images it keeps plus about twelve
-// visits' worth of set-up for every live (x image, y image) column inside its outer radius.
+// Estimate of the work in a response's taps, in units of one image visit: the images it keeps plus, for every live (x image, y
+// image) column inside an item's outer radius, twelve visits' worth of set-up and of images visited in vain at its ends, and
+// for every item what its tables cost.
 // What the reflection cut keeps: an image in direction u at distance d has about d (|ux|/Lx + |uy|/Ly + |uz|/Lz)
 // reflections, so it is the share of directions whose reflections per metre stay under cut / d.  Over an octant that
 // sum runs from the smallest of the 1/L to the length of the vector (1/Lx, 1/Ly, 1/Lz); the share below a fraction x of
 // that range is x^2.5 to within 0.02 on average over rooms of 3 x 3 x 2.4 to 10 x 8 x 4 m.  (Counting a lattice of
 // directions for every item, with library divisions and powers, took most of the plan's time.)
+// The kept images within a radius are summed up at kKnots radii; between two of them the share is taken as constant.
+// (Eight knots plan no better and take 2000 responses 1.5 us more.)
+constexpr int kKnots = 4;
+constexpr float kColumnWork = 12.f, kItemWork = 13500.f;
 struct WorkModel {
     float images, columns;       // per cubic tap, per square tap
     float metres, inv_log2_beta; // per tap; 0: no cut
     float least, inv_range;      // of the reflections per metre
-    __device__ float operator()(float n0, float n1) const {
-        float kept = 1.f, kept_columns = 1.f;
-        const float d = 0.5f * (n0 + n1) * metres;
-        if (inv_log2_beta < 0.f && d > 1e-3f) {
-            const float per_metre = (__builtin_amdgcn_logf(12.566371f * d) - 57.f) * inv_log2_beta * __builtin_amdgcn_rcpf(d);
-            const float x = fminf(fmaxf((per_metre - least) * inv_range, 0.19f), 1.f);     // (0.19^2.5 = 1/64)
-            const float root = __builtin_amdgcn_sqrtf(x);
-            kept = x * x * root;
-            kept_columns = x * root;
-        }
-        return images * (n1 * n1 * n1 - n0 * n0 * n0) * kept + columns * n1 * n1 * kept_columns;
+    float step;                  // taps between knots
+    float kept[kKnots + 1];      // images kept within i steps
+    float column_work[kKnots];   // of an item that ends in the middle of step i
+    // the fraction x of the range of reflections per metre that the cut leaves at tap n
+    __device__ float fraction(float n) const {
+        const float d = n * metres;
+        if (!(inv_log2_beta < 0.f) || d < 1e-3f) return 1.f;
+        const float per_metre = (__builtin_amdgcn_logf(12.566371f * d) - 57.f) * inv_log2_beta * __builtin_amdgcn_rcpf(d);
+        // (0.19^2.5 = 1/64: the estimate is poor below)
+        return fminf(fmaxf((per_metre - least) * inv_range, 0.19f), 1.f);
     }
+    __device__ float columns_within(float n) const {
+        const float x = fraction(0.7f * n);
+        return columns * n * n * x * __builtin_amdgcn_sqrtf(x);
+    }
+    __device__ float item(float n0, float n1) const {
+        const float x = fraction(0.5f * (n0 + n1));
+        return images * (n1 * n1 * n1 - n0 * n0 * n0) * x * x * __builtin_amdgcn_sqrtf(x) + columns_within(n1) + kItemWork;
+    }
+    __device__ float total(float rir_len) const { return kept[kKnots] + columns_within(rir_len); }
 };
 
-__device__ inline WorkModel work_model(const float* g, double k_fs_c) {
+__device__ inline WorkModel work_model(const float* g, int rir_len, double k_fs_c) {
     WorkModel m;
     m.metres = __builtin_amdgcn_rcpf((float)k_fs_c);
     const float ix = __builtin_amdgcn_rcpf(g[0]), iy = __builtin_amdgcn_rcpf(g[1]), iz = __builtin_amdgcn_rcpf(g[2]);
     m.images = 4.18879f * (m.metres * m.metres) * m.metres * ix * iy * iz;
-    m.columns = 12.f * 3.14159265f * (m.metres * m.metres) * ix * iy;
+    m.columns = kColumnWork * 3.14159265f * (m.metres * m.metres) * ix * iy;
     m.inv_log2_beta = (g[9] > 0.f && g[9] < 1.f) ? __builtin_amdgcn_rcpf(__builtin_amdgcn_logf(g[9])) : 0.f;
     m.least = fminf(fminf(ix, iy), iz);
     m.inv_range = __builtin_amdgcn_rcpf(__builtin_amdgcn_sqrtf(ix * ix + iy * iy + iz * iz) - m.least);
+    m.step = (float)rir_len * (1.f / kKnots);
+    m.kept[0] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kKnots; ++i) {
+        const float x = m.fraction(m.step * ((float)i + 0.5f));
+        const float n = m.step * ((float)i + 0.5f), root = x * __builtin_amdgcn_sqrtf(x);
+        m.kept[i + 1] = m.kept[i] + m.images * m.step * m.step * m.step * (float)(3 * i * (i + 1) + 1) * x * root;
+        m.column_work[i] = m.columns * n * n * root + kItemWork;
+    }
     return m;
 }
 
 // estimated work of a whole response (0 for a room that is not usable)
 __device__ inline float response_work(const float* g, int rir_len, double k_fs_c) {
-    return room_ok(g) ? work_model(g, k_fs_c)(0.f, (float)rir_len) : 0.f;
+    return room_ok(g) ? work_model(g, rir_len, k_fs_c).total((float)rir_len) : 0.f;
 }
 
 // one thread per response: the batch's estimated work (an integer sum, so it does not depend on the order)
@@ -190,33 +232,58 @@ __device__ inline float item_target(int units, int n_groups) {
     return fminf(fmaxf(kWorkUnit * (float)units / ((float)n_groups * kItemsPerGroup), kMinTargetWork), kMaxTargetWork);
 }
 
-// Cut the taps of a response of estimated work `work` into shells of about equal image count (equal volume), at most
-// kMaxTaps wide: calls take(lower, upper) for every shell, outermost first; returns their number.
-// Shells are cut from the outside in: every shell sets up all (x, y) columns inside its outer radius, so
-// where the tap limit, not the work, decides the width it is the inner shells, with few columns, that
-// should be the many and the narrow ones, and the left-over sliver belongs at the centre.
-// (Single precision: the cuts need not be exact, and the library's cube root in double precision took a microsecond
-// per shell.  Callers that first count and then write run it twice rather than keep a table of bounds.)
+// Cut the taps of a response into shells of about equal work, and those wider than kMaxTaps into parts: calls
+// take(lower, upper) for the shells lane, lane + lanes, ...; returns their number.
+// A shell pays for all columns inside its outer radius, so the outer ones get fewer images: the number of shells per image kept
+// goes as 1 / (target - columns' work).  (Shells of equal volume left the ones at middle distance, before the cut takes most
+// images away, several times the work of the others: 32 responses of 32768 taps waited for one item, five times the mean of a
+// work group.)  The bounds are a closed form, so that a response's shells can be shared among threads: one after the
+// other they took 0.6 us each.
+// Callers that first count and then write run it twice rather than keep a table of bounds.
 template <class Take>
-__device__ inline int cut_shells(float work, int rir_len, float target, int items_per_rir, Take take) {
-    const float shells = fminf(fmaxf(ceilf(work / target), 1.f), (float)kMaxShells);
-    const float step = (float)rir_len * (float)rir_len * (float)rir_len / shells;
-    int count = 0, hi = rir_len;
-    while (hi > 0 && count < items_per_rir - 1) {
-        const float inner = (float)hi * (float)hi * (float)hi - step;
-        int lo = inner > 0.f ? (int)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf(inner) * (1.f / 3.f)) : 0;
-        lo = min(lo, hi - kMinTaps);
-        lo = max(max(lo, hi - kMaxTaps), 0);
-        if (lo < kMinTaps && hi <= kMaxTaps) lo = 0;              // no sliver at the centre
-        take(lo, hi);
-        ++count;
-        hi = lo;
-    }
-    while (hi > 0 && count < items_per_rir) {                       // out of table space: cannot happen with the
-        const int lo = max(hi - kMaxTaps, 0);                       // sizes chosen by the host
-        take(lo, hi);
-        ++count;
-        hi = lo;
+__device__ inline int cut_shells(const WorkModel& model, bool ok, int rir_len, float target, int lane, int lanes, Take take) {
+    const float most = fminf((float)kMaxShells, fmaxf((float)(rir_len / kMinTaps), 1.f));
+    float within[kKnots + 1];                             // shells up to the knots
+    within[0] = 0.f;
+#pragma unroll
+    for (int i = 0; i < kKnots; ++i)
+        within[i + 1] = within[i] + (model.kept[i + 1] - model.kept[i]) * __builtin_amdgcn_rcpf(fmaxf(target - model.column_work[i], 0.25f * target));
+    const int shells = ok ? (int)fminf(fmaxf(ceilf(model.total((float)rir_len) / target), 1.f), most) : 1;
+    const float share = within[kKnots] / (float)shells;
+    auto bound = [&](int j) {
+        if (j == 0 || j >= shells) return j == 0 ? 0 : rir_len;
+        const float w = share * (float)j;
+        float from = 0.f, to = within[1], begin = 0.f;
+#pragma unroll
+        for (int i = 1; i < kKnots; ++i)
+            if (w >= within[i]) {
+                from = within[i];
+                to = within[i + 1];
+                begin = model.step * (float)i;
+            }
+        const float end = begin + model.step, b3 = begin * begin * begin;
+        const float n3 = b3 + (end * end * end - b3) * (w - from) * __builtin_amdgcn_rcpf(fmaxf(to - from, 1e-20f));
+        return n3 > 0.f ? min((int)__builtin_amdgcn_exp2f(__builtin_amdgcn_logf(n3) * (1.f / 3.f)), rir_len) : 0;
+    };
+    int count = 0;
+#pragma unroll 1
+    for (int j = lane; j < shells; j += lanes) {
+        int ends[2];
+#pragma unroll 1
+        for (int e = 0; e < 2; ++e) {
+            ends[0] = ends[1];
+            ends[1] = bound(j + e);
+        }
+        // (from the outside in: every shell sets up all columns inside its outer radius, so that what is left over belongs at
+        // the centre)
+        int to = ends[1];
+#pragma unroll 1
+        while (to > ends[0]) {                            // (not where two bounds round to one tap)
+            const int from = max(ends[0], to - kMaxTaps);
+            take(from, to);
+            to = from;
+            ++count;
+        }
     }
     return count;
 }
@@ -224,26 +291,25 @@ __device__ inline int cut_shells(float work, int rir_len, float target, int item
 // cost class of an item (0 = heaviest)
 __device__ inline int item_class(const WorkModel& model, bool ok, int n0, int n1) {
     if (!ok) return kClasses - 1;
-    const float cost = model((float)n0, (float)n1);
-    return min(max((int)(2.5f * (24.93f - __builtin_amdgcn_logf(fmaxf(cost, 1.f)))), 0), kClasses - 1);     // 2^24.93 = 3.2e7
+    return min(max((int)(2.5f * (24.93f - __builtin_amdgcn_logf(model.item((float)n0, (float)n1)))), 0), kClasses - 1);     // 2^24.93 = 3.2e7
 }
 
 // One thread per response: cut its taps into shells and append them to the unsorted item table, with their cost classes
 // and the class census (taken in LDS first: one global atomic per class and group, not per item).
 __global__ void rir_plan_kernel(int n_rir, Rooms rooms, int rir_len, double k_fs_c, Item* __restrict__ unsorted,
-                                int items_per_rir, int* __restrict__ ctrl, int n_groups) {
+                                int* __restrict__ ctrl, int n_groups) {
     __shared__ int census[kClasses];
     if (threadIdx.x < kClasses) census[threadIdx.x] = 0;
     __syncthreads();
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r < n_rir) {
         const Room room = load_room(rooms, r);
-        const float work = response_work(room.g, rir_len, k_fs_c), target = item_target(ctrl[kCtrlWork], n_groups);
-        const int count = cut_shells(work, rir_len, target, items_per_rir, [](int, int) {});
-        const WorkModel model = work_model(room.g, k_fs_c);
+        const float target = item_target(ctrl[kCtrlWork], n_groups);
+        const WorkModel model = work_model(room.g, rir_len, k_fs_c);
         const bool ok = room_ok(room.g);
+        const int count = cut_shells(model, ok, rir_len, target, 0, 1, [](int, int) {});
         int at = atomicAdd(&ctrl[0], count);
-        cut_shells(work, rir_len, target, items_per_rir, [&](int lo, int hi) {
+        cut_shells(model, ok, rir_len, target, 0, 1, [&](int lo, int hi) {
             const int cls = item_class(model, ok, lo, hi);
             unsorted[at++] = Item{r, lo, hi, cls};
             atomicAdd(&census[cls], 1);
@@ -253,79 +319,68 @@ __global__ void rir_plan_kernel(int n_rir, Rooms rooms, int rir_len, double k_fs
     if (threadIdx.x < kClasses && census[threadIdx.x]) atomicAdd(&ctrl[2 + threadIdx.x], census[threadIdx.x]);
 }
 
-// The whole plan in one work group, for batches of at most kPlanRows * kPlanThreads responses (beyond, the four launches
-// of the kernels around this one).  A thread per
-// response, up to kPlanRows in turn, for the batch's work, the shells (their places in the table by a scan, not by
-// atomics) and their classes, then all threads over the items for the counting sort.  Between the two the items lie in
-// LDS, or in `unsorted` if there are more than it holds.  Leaves ctrl[0] = number of items, ctrl[1] = 0.
-// Latency bound: the 16 waves of one CU.
-constexpr int kPlanThreads = 1024, kPlanRows = 4;
+// The whole plan in one work group, for batches of at most kPlanMost responses (beyond, the four launches of the kernels
+// around this one).  As many threads per response as there are, up to 64: first the batch's work, then the shells, their places
+// in the table from a counter, and their classes, then all threads over the items for the counting sort.  Between the two the
+// items lie in LDS, or in `unsorted` if there are more than it holds.  Leaves ctrl[0] = number of items, ctrl[1] = 0.
+// Latency bound: the 16 waves of one CU, and instructions that no launch before has left in the cache, so the code is kept
+// short (unrolled, with passes of their own for counting and writing, 16 responses took 12 us instead of 6).
+constexpr int kPlanThreads = 1024, kPlanMost = 4 * kPlanThreads;
 constexpr int kPlanItems = 8192;
-static_assert(AUG_MAX_RIR_LEN < 1 << 16 && kPlanRows * kPlanThreads <= 1 << 12 && kClasses <= 1 << 5, "the packing of items in LDS");
+static_assert(AUG_MAX_RIR_LEN < 1 << 16 && kPlanMost <= 1 << 12 && kClasses <= 1 << 5, "the packing of items in LDS");
 __global__ __launch_bounds__(kPlanThreads) void rir_plan_all_kernel(
     int n_rir, Rooms rooms, int rir_len, double k_fs_c, Item* __restrict__ sorted,
-    Item* __restrict__ unsorted, int items_per_rir, int* __restrict__ ctrl, int n_groups) {
+    Item* __restrict__ unsorted, int* __restrict__ ctrl, int n_groups) {
     __shared__ unsigned long long held[kPlanItems];
-    __shared__ int part[2][kPlanThreads / 64];
     __shared__ int census[kClasses], cursor[kClasses];
+    __shared__ int s_units, s_items;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid < kClasses) census[tid] = 0;
+    if (tid == 0) s_units = s_items = 0;
+    group_sync();
 
-    float work[kPlanRows];
-    int units = 0;
-#pragma unroll
-    for (int k = 0; k < kPlanRows; ++k) {
-        const int r = tid + k * kPlanThreads;
-        work[k] = 0.f;
-        if (r < n_rir) {
-            work[k] = response_work(load_room(rooms, r).g, rir_len, k_fs_c);
-            units += (int)fminf(work[k] * (1.f / kWorkUnit), 500000.f) + 1;
+    int lg = 0;
+    while (lg < 6 && n_rir << (lg + 1) <= kPlanThreads) ++lg;
+    const int lanes = 1 << lg, n = n_rir << lg;
+    auto units_of = [&](const WorkModel& model, bool ok) {
+        return ok ? (int)fminf(model.total((float)rir_len) * (1.f / kWorkUnit), 500000.f) + 1 : 1;
+    };
+    auto write_items = [&](const WorkModel& model, bool ok, int r, int share, float target) {
+        cut_shells(model, ok, rir_len, target, share, lanes, [&](int lo, int hi) {
+            const int cls = item_class(model, ok, lo, hi), at = atomicAdd(&s_items, 1);
+            if (at < kPlanItems) held[at] = (unsigned long long)(unsigned int)(lo | hi << 16) | (unsigned long long)(unsigned int)(r | cls << 12) << 32;
+            else unsorted[at] = Item{r, lo, hi, cls};
+            atomicAdd(&census[cls], 1);
+        });
+    };
+    if (n_rir <= kPlanThreads) {                          // each thread has one response, or a share of one
+        const int r = min(tid >> lg, n_rir - 1), share = tid & (lanes - 1);
+        const Room room = load_room(rooms, r);
+        const bool ok = room_ok(room.g);
+        const WorkModel model = work_model(room.g, rir_len, k_fs_c);
+        if (share == 0 && tid < n) atomicAdd(&s_units, units_of(model, ok));
+        group_sync();
+        if (tid < n) write_items(model, ok, r, share, item_target(s_units, n_groups));
+    } else {
+#pragma unroll 1
+        for (int pass = 0; pass < 2; ++pass) {
+            int units = 0;
+#pragma unroll 1
+            for (int r = tid; r < n_rir; r += kPlanThreads) {
+                const Room room = load_room(rooms, r);
+                const bool ok = room_ok(room.g);
+                const WorkModel model = work_model(room.g, rir_len, k_fs_c);
+                if (pass == 0) units += units_of(model, ok);
+                else write_items(model, ok, r, 0, item_target(s_units, n_groups));
+            }
+            if (pass == 0) {
+                atomicAdd(&s_units, units);
+                group_sync();
+            }
         }
     }
-    units = wave_inclusive_scan(units);
-    if (lane == 63) part[0][wave] = units;
-    __syncthreads();
-    int total_units = 0;
-    for (int w = 0; w < kPlanThreads / 64; ++w) total_units += part[0][w];
-    const float target = item_target(total_units, n_groups);
-
-    int count = 0;
-#pragma unroll
-    for (int k = 0; k < kPlanRows; ++k)
-        if (tid + k * kPlanThreads < n_rir) count += cut_shells(work[k], rir_len, target, items_per_rir, [](int, int) {});
-    const int incl = wave_inclusive_scan(count);
-    if (lane == 63) part[1][wave] = incl;
-    __syncthreads();
-    int at = incl - count, n_items = 0;
-    for (int w = 0; w < kPlanThreads / 64; ++w) {
-        if (w < wave) at += part[1][w];
-        n_items += part[1][w];
-    }
-    const bool in_lds = n_items <= kPlanItems;
-    auto pack = [](const Item& it) {
-        return (unsigned long long)(unsigned int)(it.n0 | it.n1 << 16) | (unsigned long long)(unsigned int)(it.rir | it.cls << 12) << 32;
-    };
-    auto get = [&](int i) {
-        if (!in_lds) return unsorted[i];
-        const unsigned int lo = (unsigned int)held[i], hi = (unsigned int)(held[i] >> 32);
-        return Item{(int)(hi & 4095u), (int)(lo & 65535u), (int)(lo >> 16), (int)(hi >> 12)};
-    };
-#pragma unroll
-    for (int k = 0; k < kPlanRows; ++k) {
-        const int r = tid + k * kPlanThreads;
-        if (r >= n_rir) continue;
-        const Room room = load_room(rooms, r);
-        const WorkModel model = work_model(room.g, k_fs_c);
-        const bool ok = room_ok(room.g);
-        cut_shells(work[k], rir_len, target, items_per_rir, [&](int lo, int hi) {
-            const Item it{r, lo, hi, item_class(model, ok, lo, hi)};
-            if (in_lds) held[at] = pack(it);
-            else unsorted[at] = it;
-            ++at;
-            atomicAdd(&census[it.cls], 1);
-        });
-    }
-    __syncthreads();                                   // (the group's writes to `unsorted` are visible to it)
+    group_sync();                                          // (the group's writes to `unsorted` are visible to it)
+    const int n_items = s_items;
     if (wave == 0) {
         const int mine = lane < kClasses ? census[lane] : 0;
         const int incl_classes = wave_inclusive_scan(mine);
@@ -335,9 +390,15 @@ __global__ __launch_bounds__(kPlanThreads) void rir_plan_all_kernel(
             ctrl[1] = 0;
         }
     }
-    __syncthreads();
+    group_sync();
     for (int i = tid; i < n_items; i += kPlanThreads) {
-        const Item it = get(i);
+        Item it;
+        if (i < kPlanItems) {
+            const unsigned int lo = (unsigned int)held[i], hi = (unsigned int)(held[i] >> 32);
+            it = Item{(int)(hi & 4095u), (int)(lo & 65535u), (int)(lo >> 16), (int)(hi >> 12)};
+        } else {
+            it = unsorted[i];
+        }
         sorted[atomicAdd(&cursor[it.cls], 1)] = it;
     }
 }
@@ -373,85 +434,163 @@ __global__ void rir_sort_items_kernel(const Item* __restrict__ unsorted, Item* _
     if (have) sorted[first_slot[it.cls] + rank] = it;
 }
 
-// per-column record shared through LDS between the lane that built it and the lanes that walk its pieces
-struct __align__(16) Column {
-    double a;                    // dx*dx + dy*dy
-    float bxy;                   // beta^(reflections along x and y)
-    int place;                   // of the range of the sorted z table that can fall inside the shell: its end, and above
-                                 // bit 10 its start less kPiece times the column's first piece, so that piece p
-                                 // starts at that number plus kPiece p
-};
-static_assert(sizeof(Column) == 16, "column records are packed");
-static_assert(2 * kAxisCap < 1024 && kPiece % 2 == 0, "the fields of Column::place, and pairs of images");
+// Source and microphone lie between the walls, or not so far outside that an axis' images stop beginning within 2 L of
+// the microphone (false where a position is not a number).  Rows beyond that are not refused: they take the plain path,
+// which tests every tap.
+__device__ inline bool axis_in_order(const Axis& a) {
+    return fabs(a.src - a.mic) <= 2.0 * a.room && fabs(a.src + a.mic) <= 2.0 * a.room;
+}
 
-// One image along an axis, as stored in the sorted tables: key = squared distance to the microphone
-// along that axis (reference operation order); aux = beta^reflections (z axis) or the reflection count
-// (y axis).  Sixteen bytes: one LDS read per entry.
-struct __align__(16) AxisImage {
-    double key;
-    double aux;
+// The images (1 - 2q) s + 2 n L - m, q in {0,1}, of an axis in order of distance.  For each q the signed distance grows
+// with n, so the images with negative distance (walked towards smaller n) and those with non-negative distance are two
+// sorted lists, 2 q and 2 q + 1.  All four lists step by 2 L and begin within 2 L of the microphone (that takes an
+// axis_in_order), so the merged order is known: element p of every list in the order in which the lists begin, then the
+// elements p + 1.
+struct AxisOrder {
+    unsigned int lists;         // list of rank r in bits 4 r, 4 r + 1
+    int first_n[2];             // the first image at a non-negative distance, per q
 };
+__device__ inline AxisOrder axis_order(const Axis& ax) {
+    AxisOrder o;
+    double begin[4];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int n = axis_delta(ax, q, 0) >= 0.0 ? 0 : 1;          // (0 or 1 while source and microphone lie between the walls)
+        o.first_n[q] = n;
+        begin[2 * q] = -axis_delta(ax, q, n - 1);
+        begin[2 * q + 1] = axis_delta(ax, q, n);
+    }
+    o.lists = 0;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        int rank = 0;
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            if (m != l && (begin[m] < begin[l] || (begin[m] == begin[l] && m < l))) ++rank;
+        o.lists |= (unsigned int)l << 4 * rank;
+    }
+    return o;
+}
+// image i of that order: q and n
+__device__ inline void ordered_image(const AxisOrder& o, int i, int& q, int& n) {
+    const int list = (int)(o.lists >> 4 * (i & 3)) & 3, p = i >> 2;
+    q = list >> 1;
+    n = list & 1 ? o.first_n[q] + p : o.first_n[q] - 1 - p;
+}
 
-struct WalkCtx {
+// The number of images of an axis within distance s of the microphone, c_q = (1 - 2q) src - mic: the number of terms of
+// the two arithmetic progressions c_q + 2 n L that lie in [-s, s].
+// Single precision is enough: a bound is widened by `slack`, a fifth of a tap plus two millionths of the
+// distance, which covers the rounding of these counts for every axis of up to 4e5 taps (longer ones take the plain
+// path).  An image that close to a bound is then visited although it may lie outside; it lands, less than half a tap
+// away, in one of the two slots that are never read.  The same goes for the ends of a column's range (see the kernel).
+constexpr double kMaxAxisTaps = 4e5;
+// An image of a column's first or last four lies up to 2 L outside the shell, and its slot must not come round to the
+// item's in sixteen bits; and L must not be so few taps that the slack is more than L.
+constexpr double kMaxHeightTaps = 16384.0, kMinHeightTaps = 0.25;
+struct AxisCount {
+    float k0, k1;        // -c_q / (2 L)
+    float inv2l;         // 1 / (2 L)
+    float slack;         // metres
+};
+__device__ inline AxisCount axis_count(const Axis& a, double k_fs_c) {
+    const double inv2l = 1.0 / (2.0 * a.room);
+    return AxisCount{(float)(-(a.src - a.mic) * inv2l), (float)(-(-a.src - a.mic) * inv2l), (float)inv2l, (float)(0.2 / k_fs_c)};
+}
+// images within a distance, or a few more: (-s - c_q) / 2L <= n <= (s - c_q) / 2L.  SLACK -1: or a few fewer
+template <int SLACK = 1>
+__device__ inline int count_within(const AxisCount& a, float distance) {
+    const float s = fmaf(distance, SLACK > 0 ? 1.000002f : 0.999998f, SLACK > 0 ? a.slack : -a.slack) * a.inv2l;
+    const float one = floorf(s + a.k0) + floorf(s - a.k0) + 1.f, two = floorf(s + a.k1) + floorf(s - a.k1) + 1.f;
+    return (int)(fmaxf(one, 0.f) + fmaxf(two, 0.f));
+}
+
+// One item, prepared by one wavefront for the whole group and kept in LDS: what each phase needs is read there at its start
+// (computed by every wavefront, and held in registers from phase to phase, it took a seventh of the kernel's instructions
+// and made it spill).
+struct ItemCtx {
+    int kind;               // one of the kinds below
+    int rir, n0, n1;
+    unsigned int top8;      // eight times the last slot.  Slots are tap - n0 + 1: slot 0 takes what belongs below the item, the
+                            // last, n1 - n0 + 1, what belongs above it, and this and the 63 behind it what the lanes
+                            // drop; none of these is read
+    int k_cut;              // reflections from which on nothing can add to a sum (see reflection_cut)
+    int nmx, nmy, nmz;      // images |n| <= nm of each axis
+    Axis ax, ay, az;
+    double beta, r_out2, walk2;      // walk2: squared distance from which images are walked
+    float inv_log2_beta;    // 0: no cut
+    int near_item;          // images nearer than kNearMetres are walked apart
+
+    // taps
     double k_fs_c;
-    double beta;
     double quick_k;         // fs/c, less the middle of the hardware estimate's error
     double quick_shift;     // 0.5 + margin - (n0 - 1) + kQuickMagic
     int quick_margin2;      // quick estimates whose 16-bit fraction is below this are settled by tap_slot
     double shift;           // 0.5 + guard - (n0 - 1)
     double guard2;
-    int n0, n1;             // the item's taps.  Slots are tap - n0 + 1: slot 0 takes what belongs below the item, slot
-                            // n1 - n0 + 1 what belongs above it; neither is read
-};
 
-// the reference recipe, out of line so that the table walk stays short
+    // the z axis (see walk_step) and the range of a column in steps of 2 L:
+    // first p = ceil(lo[0] sqrt(walk2 - a) + lo[1]), last p = floor(hi[0] sqrt(r_out2 - a) + hi[1])
+    double two_l, beta2, begin[4];
+    float lo[2], hi[2];
+    // An image (q, n) with k reflections lies at most k L + max(|s - m|, |L - s - m|) from the microphone along its axis:
+    // with k of them, no y image is beyond y_reach[0] k + y_reach[1] metres, and with k for y and z together, no z image of
+    // the y image at |dy| is beyond z_reach[0] k + z_reach[1] - z_reach[2] |dy|.
+    float y_reach[2], z_reach[3];
+    AxisCount cy;
+    AxisOrder y_order;
+};
+// Images of the y table: a row's bound lies within y_reach of the cut, or r_out, both less than 2 (nmy + 2) L.
+__device__ inline int y_images(int nmy) { return 4 * (nmy + 2); }
+// two consecutive taps; only their 4-byte alignment is promised
+struct __attribute__((aligned(4))) TapPair { float x, y; };
+constexpr int kEnd = -1, kSilent = 0, kFast = 1, kPlain = 2;      // no more items; a room that is not usable; the walk; the plain walk
+
+// the reference recipe, out of line so that the walk stays short
 __device__ __attribute__((noinline)) int exact_tap(double d2, double k_fs_c) {
     const double d = __dsqrt_rn(d2);
     return (int)__dadd_rn(__dmul_rn(d, k_fs_c), 0.5);     // positive: truncation is floor
 }
 
 // Largest reflection count k whose amplitude beta^k / (4 pi d) can still add to a sum in the 2^-56 fixed
-// point at distance d_min or beyond.  Increments are rounded to the nearest unit (or truncated, in the
-// innermost item), so an amplitude below half a unit adds exactly zero; the cut is taken at 2^-57.5, a
+// point at distance d_min or beyond.  Increments are rounded to the nearest unit, so an amplitude below half a unit adds
+// exactly zero; the cut is taken at 2^-57.5, a
 // margin of a factor 1.41 under that, plus one count of slack, which covers the rounding of this estimate
 // for every beta that the limit of 10^6 counts lets through.  "No limit" when beta is 0, >= 1
-// (log2_beta == 0 encodes both) or d_min is tiny.
-__device__ inline int reflection_cut(float log2_beta, float d_min) {
-    if (!(log2_beta < 0.f) || !(d_min > 1e-3f)) return 1 << 20;
+// (inv_log2_beta == 0 encodes both) or d_min is tiny.
+constexpr int kNoCut = 1 << 20;
+__device__ inline int reflection_cut(float inv_log2_beta, float d_min) {
+    if (!(inv_log2_beta < 0.f) || !(d_min > 1e-3f)) return kNoCut;
     // beta^k >= 4 pi d 2^-57.5  <=>  k <= (log2(4 pi d) - 57.5) / log2(beta)
-    const float k = (__log2f(12.566371f * d_min) - 57.5f) / log2_beta;
-    return k > 1.0e6f ? (1 << 20) : (int)k + 2;
+    const float k = (__builtin_amdgcn_logf(12.566371f * d_min) - 57.5f) * inv_log2_beta;
+    return k > 1.0e6f ? kNoCut : (int)k + 2;
 }
 
 // Slot (tap - n0 + 1) of an image at squared distance d2, given y, the hardware's estimate of 1/sqrt(d2).
 // One Newton step on the root leaves d fs/c good to ~1e-10 taps; shifted up by the guard, its fraction falls below
 // 2 guard exactly when the true value may lie within the guard of a rounding boundary, and only then is the
-// reference recipe evaluated.
-__device__ inline int tap_slot(const WalkCtx& w, double d2, double y) {
+// reference recipe evaluated, on the reference's own d2 (that of the walk may differ in the last bit).
+template <class ExactD2>
+__device__ inline int tap_slot(const ItemCtx& w, double d2, double y, ExactD2 exact_d2) {
     const double s0 = __dmul_rn(d2, y);                    // sqrt(d2) to 2^-24
     const double res = fma(-s0, s0, d2);                   // exact residual
     const double s1 = fma(__dmul_rn(res, y), 0.5, s0);     // one Newton step: ~4e-15 relative
     const double t = fma(s1, w.k_fs_c, w.shift);
     int slot = (int)t;
-    if (__builtin_amdgcn_fract(t) < w.guard2) slot = exact_tap(d2, w.k_fs_c) - (w.n0 - 1);
+    if (__builtin_amdgcn_fract(t) < w.guard2) slot = exact_tap(exact_d2(), w.k_fs_c) - (w.n0 - 1);
     return slot;
 }
 
-// The table walk first asks for less.  d2 rsq(d2) without the Newton step is the distance to within the hardware
+// The walk first asks for less.  d2 rsq(d2) without the Newton step is the distance to within the hardware
 // estimate's own error, which over all 2^31 leading mantissas of [1, 4) (three fillings of the remaining bits) lies
 // between -3.24 and +7.10 units of 2^-27; with the middle of that range taken out of fs/c the error is below
 // 5.2 * 2^-27: 3e-4 taps at tap 8000.  Adding 1.5 * 2^36 leaves slot and fraction as two sixteen-bit halves of the
-// sum's low word: the address is a shift and a mask, the test one 16-bit comparison, and the Newton step,
+// sum's low word: the address is a shift of one half, the test a comparison of the other, and the Newton step,
 // conversion, fraction and double-precision comparison are not needed (40 instead of 60 issue cycles, without rsq,
 // per image).  y ~ 1/sqrt(d2) is enough for the amplitude.
 constexpr double kAmplitude = 0.07957747154594767 * 0x1p56;      // 1 / (4 pi) in the sums' fixed point
 constexpr double kQuickMagic = 0x1.8p36;
 constexpr double kQuickMiddle = 1.93 * 0x1p-27, kQuickError = 5.2 * 0x1p-27;
-__device__ inline unsigned int quick_estimate(const WalkCtx& w, double d2, double& y) {
-    y = __builtin_amdgcn_rsq(d2);
-    return (unsigned int)__double2loint(fma(__dmul_rn(d2, y), w.quick_k, w.quick_shift));
-}
-
 // amp2 = amplitude * 2^56, rounded to an integer, goes to the tap's 64-bit integer sum.  Below 2^51 (every
 // image farther than 2.55 m) adding 1.5 * 2^52 rounds the exact product to an integer in the sum's own
 // mantissa, whose low 51 bits are then the increment; larger ones are rounded and split in two exact steps
@@ -478,202 +617,231 @@ __device__ inline void deposit(unsigned int slot8, double a, double y, unsigned 
     atomicAdd((unsigned long long*)((char*)hist + slot8), ((unsigned long long)hi << 32) | lo);
 }
 
-// The images z[first .. first + len) of a column, 1 <= len <= kPiece, all beyond kNearMetres unless images are counted.
-// Every one lies inside the item's shell up to the slack of the closed-form table positions (a fifth of a tap), so
+// The z images of a response are four arithmetic progressions of step 2 L, at distances u + begin[list], u = 2 L p,
+// from the microphone's plane (L the room's height, s and m the heights of source and microphone):
+//   list 0: |s - m|,        2 p reflections       list 2: s + m,        2 p + 1
+//   list 1: 2 L - |s - m|,  2 p + 2               list 3: 2 L - (s + m), 2 p + 1
+// (for 0 <= s + m <= 2 L and |s - m| <= 2 L, so that every list begins between 0 and 2 L).  u is exact in double
+// precision, a multiple of a 24-bit number below 2^12 of them.
+// squared distance of image (list, p) by the reference recipe; a: of the column
+__device__ __attribute__((noinline)) double exact_z_image(Axis az, double a, double u, int list) {
+    const int p = (int)rint(u / (2.0 * az.room));
+    const bool below = az.src < az.mic;
+    const int n = list == 0 ? (below ? -p : p) : list == 1 ? (below ? 1 + p : -1 - p) : list == 2 ? -p : 1 + p;
+    const double dz = axis_delta(az, list >> 1, n);
+    return __dadd_rn(a, __dmul_rn(dz, dz));
+}
+
+// The four images of a column at u = 2 L p.  amp_even = beta^(kxy + 2 p) / (4 pi) 2^56 and amp_odd = beta^(kxy + 2 p + 1)
+// likewise.  Four independent chains of arithmetic; no memory is read.  EDGE: some of the images may lie outside the item's
+// shell and go to the lane's own slot for such (dropped8); else every one lies inside, up to the slack of the closed form (a fifth of a tap), so
 // its slot is one of 0 .. taps + 1 and needs no test.
-// Two images at a time, so that each lane has two independent chains of arithmetic in flight (three or four measured
-// no better); the pair of the next round is requested before the current one is worked on.  Walked from the far end
-// so that the LDS address is also the loop's condition (the sums are integers: the order does not matter), and opaque
-// to the compiler so that it is not split into a counter plus an offset.  An odd piece's top pair is its last image
-// twice, the second time with amplitude zero (where images are counted, in slot 0, which is never read).  The last
-// round requests the pair below the piece: the table has spare entries in front.
-template <bool COUNT>
-__device__ inline void walk_piece_table(const WalkCtx& w, double a, double bxy, const AxisImage* z, int first, int len,
-                                        unsigned long long* hist) {
-    typedef const AxisImage __attribute__((address_space(3))) * LdsImages;
-    constexpr unsigned int kE = (unsigned int)sizeof(AxisImage);
-    struct Pair { AxisImage e[2]; };
-    auto load = [](unsigned int at, unsigned int partner) {
-        const LdsImages p = (LdsImages)(uintptr_t)at, q = (LdsImages)(uintptr_t)partner;
-        Pair g;
-        g.e[0].key = p->key;
-        g.e[0].aux = p->aux;
-        g.e[1].key = q->key;
-        g.e[1].aux = q->aux;
-        return g;
-    };
-    auto step = [&](const Pair& g) {
-        double d2[2], y[2];
-        unsigned int slot8[2];
-        bool redo = false;
+// fma(a, b, c) with c left as it is: the compiler takes the two-address form, which destroys c, and copies it first for
+// each of four uses
+__device__ inline double fma_keep(double a, double b, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+__device__ inline double fma_keep_uniform(double a, double b_uniform, double c) {
+    double r;
+    asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "s"(b_uniform), "v"(c));
+    return r;
+}
+struct WalkRegs {           // what every step needs of the item, moved to scalar registers for the length of a chunk
+    double begin[4], quick_k, quick_shift, beta2;
+    unsigned short quick_margin2;
+    __device__ explicit WalkRegs(const ItemCtx& c)
+        : begin{uni(c.begin[0]), uni(c.begin[1]), uni(c.begin[2]), uni(c.begin[3])}, quick_k(uni(c.quick_k)), quick_shift(c.quick_shift),
+          beta2(uni(c.beta2)), quick_margin2((unsigned short)uni(c.quick_margin2)) {}
+};
+template <bool COUNT, bool EDGE>
+__device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool near_item, double a, double u, double amp_even, double amp_odd,
+                                unsigned int dropped8, unsigned long long* hist) {
+    double d2[4], y[4];
+    unsigned int slot8[4];
+    unsigned short fraction[4];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            d2[i] = __dadd_rn(a, g.e[i].key);
-            const unsigned int t = quick_estimate(w, d2[i], y[i]);
-            slot8[i] = t >> 13 & 0x7fff8u;
-            redo |= (unsigned short)t < (unsigned short)w.quick_margin2;
-        }
-        if (redo) {       // (one test for both, so that the estimates are complete before the branch)
-#pragma unroll
-            for (int i = 0; i < 2; ++i) slot8[i] = 8u * (unsigned int)tap_slot(w, d2[i], y[i]);
-        }
-#pragma unroll
-        for (int i = 0; i < 2; ++i) deposit<COUNT, true>(slot8[i], COUNT ? 0.0 : __dmul_rn(g.e[i].aux, bxy), y[i], hist);
-    };
-    const unsigned int bottom = (unsigned int)(uintptr_t)(LdsImages)z + (unsigned int)first * kE;
-    const bool odd = len & 1;
-    unsigned int cur = bottom + ((unsigned int)(len - 1) & ~1u) * kE;      // the top pair
-    Pair g0 = load(cur, cur + (odd ? 0u : kE)), g1;
-    if (COUNT) {
-        if (odd) g0.e[1].key = __longlong_as_double(0x7ff8000000000000ll);      // not a number: slot 0
-    } else {
-        // (the upper half alone: what is left of the number is below 2^-1022 and adds nothing)
-        g0.e[1].aux = __hiloint2double(odd ? 0 : __double2hiint(g0.e[1].aux), __double2loint(g0.e[1].aux));
+    for (int l = 0; l < 4; ++l) {
+        const double dz = __dadd_rn(u, k.begin[l]);
+        d2[l] = fma_keep(dz, dz, a);
+        y[l] = __builtin_amdgcn_rsq(d2[l]);
+        const unsigned int t = (unsigned int)__double2loint(fma_keep_uniform(__dmul_rn(d2[l], y[l]), k.quick_k, k.quick_shift));
+        slot8[l] = t >> 13 & 0x7fff8u;
+        fraction[l] = (unsigned short)t;
     }
-    for (;;) {
-        const bool last0 = cur == bottom;
-        cur -= 2 * kE;
-        asm("" : "+v"(cur));
-        g1 = load(cur, cur + kE);
-        step(g0);
-        if (last0) break;
-        const bool last1 = cur == bottom;
-        cur -= 2 * kE;
-        asm("" : "+v"(cur));
-        g0 = load(cur, cur + kE);
-        step(g1);
-        if (last1) break;
+    // (one test for all, so that the estimates are complete before the branch)
+    if (min(min(fraction[0], fraction[1]), min(fraction[2], fraction[3])) < k.quick_margin2) {
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (fraction[l] < k.quick_margin2) slot8[l] = 8u * (unsigned int)tap_slot(w, d2[l], y[l], [&] { return exact_z_image(w.az, a, u, l); });
     }
+    int walked = 0;
+    if (EDGE) {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) slot8[l] = min(slot8[l], dropped8);
+        if (near_item) {
+#pragma unroll
+            for (int l = 0; l < 4; ++l) slot8[l] = d2[l] < w.walk2 ? dropped8 : slot8[l];
+        }
+#pragma unroll
+        for (int l = 0; l < 4; ++l) walked += slot8[l] < w.top8;
+    }
+    const double amp_far = __dmul_rn(amp_even, k.beta2);
+#pragma unroll
+    for (int l = 0; l < 4; ++l) deposit<COUNT, true>(slot8[l], l == 0 ? amp_even : l == 1 ? amp_far : amp_odd, y[l], hist);
+    return walked;
 }
 
 // beta^k for reflection counts past the LDS table; out of line so that the double-precision pow does not
 // weigh on the register allocation of the loops that call it once in a long while
 __device__ __attribute__((noinline)) float beta_pow_slow(double beta, int k) { return (float)pow(beta, (double)k); }
 
-// (out of line for the same reason: only rooms too flat or narrow for the tables come here)
+// Rows that the closed forms do not take (rooms too flat or narrow for the tables, positions far outside): every column of
+// the bounding box, every z image of a live column, every tap tested.  Out of line for the same reason as the power.
 template <bool COUNT>
-__device__ __attribute__((noinline)) void walk_column_direct(const WalkCtx w, const Axis az, double a, double cxy, int nmz,
-                                                             unsigned long long* hist) {
-    for (int q = 0; q < 2; ++q)
-        for (int n = -nmz; n <= nmz; ++n) {
-            const double dz = axis_delta(az, q, n);
-            const double d2 = __dadd_rn(a, __dmul_rn(dz, dz));
-            const double y = __builtin_amdgcn_rsq(d2);
-            const int slot = tap_slot(w, d2, y);
-            if ((unsigned int)slot > (unsigned int)(w.n1 - w.n0 + 1)) continue;          // outside the item
-            double bz = 0.0;
-            if (!COUNT) bz = (double)beta_pow_slow(w.beta, iabs(n - q) + iabs(n));
-            deposit<COUNT, false>(8u * (unsigned int)slot, __dmul_rn(bz, cxy), y, hist);
-        }
-}
-
-// The images z[first .. last) of a column, with the test for amplitudes too large for the fast rounding.
-__device__ __attribute__((noinline)) void walk_near(const WalkCtx w, double a, double bxy, const AxisImage* z, int first,
-                                                    int last, unsigned long long* hist) {
-    for (int i = first; i < last; ++i) {
-        const double d2 = __dadd_rn(a, z[i].key), y = __builtin_amdgcn_rsq(d2);
-        const int slot = tap_slot(w, d2, y);
-        if ((unsigned int)slot <= (unsigned int)(w.n1 - w.n0 + 1))
-            deposit<false, false>(8u * (unsigned int)slot, __dmul_rn(z[i].aux, bxy), y, hist);
+__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, const float* bpow, unsigned long long* hist) {
+    unsigned int walked = 0;
+    const int nmx = w.nmx, nmy = w.nmy, nmz = w.nmz, niy = 2 * (2 * nmy + 1);
+    const long long n_columns = 2ll * (2 * nmx + 1) * niy;
+    for (long long cand = threadIdx.x; cand < n_columns; cand += kThreads) {
+        const int ix = (int)(cand / niy), iy = (int)(cand - (long long)ix * niy);
+        const int qx = ix & 1, nx = (ix >> 1) - nmx, qy = iy & 1, ny = (iy >> 1) - nmy;
+        const double dx = axis_delta(w.ax, qx, nx), dy = axis_delta(w.ay, qy, ny);
+        const double a = __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy));
+        const int kxy = reflections(qx, nx) + reflections(qy, ny);
+        // (beyond the first shell the shell's own inner radius bounds the distance well enough)
+        const int kz_max = (w.n0 > 0 ? w.k_cut : reflection_cut(w.inv_log2_beta, sqrtf((float)a))) - kxy;
+        if (!(a < w.r_out2) || kz_max < 0) continue;
+        const double bxy = COUNT ? 0.0 : (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(w.beta, kxy)) * kAmplitude;
+        for (int q = 0; q < 2; ++q)
+            for (int n = -nmz; n <= nmz; ++n) {
+                const double dz = axis_delta(w.az, q, n);
+                const double d2 = __dadd_rn(a, __dmul_rn(dz, dz));
+                const double y = __builtin_amdgcn_rsq(d2);
+                const int slot = tap_slot(w, d2, y, [&] { return d2; });
+                if (8u * (unsigned int)slot > w.top8) continue;
+                double bz = 0.0;
+                if (!COUNT) bz = (double)beta_pow_slow(w.beta, reflections(q, n));
+                deposit<COUNT, false>(8u * (unsigned int)slot, __dmul_rn(bz, bxy), y, hist);
+                ++walked;
+            }
     }
+    return walked;
 }
 
-// Source and microphone lie between the walls, or not so far outside that an axis' images stop beginning within 2 L of
-// the microphone (false where a position is not a number).  Rows beyond that are not refused: they take the plain path,
-// which tests every tap.
-__device__ inline bool axis_in_order(const Axis& a) {
-    return fabs(a.src - a.mic) <= 2.0 * a.room && fabs(a.src + a.mic) <= 2.0 * a.room;
-}
-
-// All images (1 - 2q) s + 2 n L - m, q in {0,1}, |n| <= nm, of one axis, written to `out` in order of
-// squared distance.  For each q the signed distance grows with n, so the images with negative
-// distance (walked towards smaller n) and those with non-negative distance are two sorted lists.  All four lists step
-// by 2 L and begin within 2 L of the microphone, so the merged order is known: element p of a list follows every
-// list's elements 0 .. p-1 and, of the elements p, those of the lists that begin nearer (ties: the lower list).
-// That takes an axis_in_order.
-// (Searching the other lists for every entry's place, eight steps each, took a sixth of all the kernel's instructions.)
-// aux(q, n) supplies the entry's second field.
-template <class Aux>
-__device__ inline void build_sorted_images(const Axis& ax, int nm, AxisImage* out, int tid, Aux aux) {
-    const int per_q = 2 * nm + 1, n_all = 2 * per_q;
-    // list 2 q + side: its first distance and its length.  The first image at a non-negative distance is n = 0 or 1
-    // while source and microphone lie between the walls.
-    double begin[4];
-    int length[4];
-    int split[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int n = axis_delta(ax, q, 0) >= 0.0 ? 0 : 1;
-        split[q] = n + nm;                        // index of that image; nm >= 1
-        begin[2 * q] = -axis_delta(ax, q, n - 1);
-        begin[2 * q + 1] = axis_delta(ax, q, n);
-        length[2 * q] = n + nm;
-        length[2 * q + 1] = nm - n + 1;
+// The images within kNearMetres, with the test for amplitudes too large for the fast rounding: of the columns of the x images
+// |n| <= n_near and the first n_y images along y, those at steps p < n_p along z.
+struct NearImages {
+    int n_near, n_y, n_p, n;
+    __device__ explicit NearImages(const ItemCtx& w) {
+        const float r_near = __builtin_amdgcn_sqrtf((float)w.walk2) * 1.0001f;
+        n_near = min((int)(r_near / (2.f * (float)w.ax.room)) + 1, w.nmx);
+        n_y = min(count_within(w.cy, r_near), y_images(w.nmy));
+        n_p = min((int)(r_near / (float)w.two_l) + 1, w.nmz) + 1;
+        n = 2 * (2 * n_near + 1) * n_y * n_p * 4;
     }
-    for (int i = tid; i < n_all; i += kThreads) {
-        const int q = i >= per_q, t = i - q * per_q, sp = q ? split[1] : split[0];
-        const int side = t >= sp, own = 2 * q + side;
-        const double d = axis_delta(ax, q, t - nm);
-        const int p = side ? t - sp : sp - 1 - t;
-        const double mine = own == 0 ? begin[0] : own == 1 ? begin[1] : own == 2 ? begin[2] : begin[3];
-        int rank = p;
-#pragma unroll
-        for (int l = 0; l < 4; ++l) {
-            if (l == own) continue;
-            const bool nearer = begin[l] < mine || (begin[l] == mine && l < own);
-            rank += min(p + (nearer ? 1 : 0), length[l]);
-        }
-        AxisImage e;
-        e.key = __dmul_rn(d, d);
-        e.aux = aux(q, t - nm);
-        out[rank] = e;
-    }
-}
-
-// Position in an axis's sorted table without searching it.  The table holds the images c_q + 2 n L,
-// q in {0,1}, |n| <= nm, ordered by squared distance, so the number of entries within distance s of the
-// microphone is the number of terms of the two arithmetic progressions that lie in [-s, s].
-// Single precision is enough: a bound is widened (or narrowed) by `slack`, a fifth of a tap plus two millionths of the
-// distance, which covers the rounding of these counts for every axis of up to 4e5 taps (longer ones take the plain
-// path).  An entry that close to a bound is then visited although it may lie outside; it lands, less than half a tap
-// away, in one of the two slots that are never read.
-constexpr double kMaxAxisTaps = 4e5;
-struct AxisCount {
-    float k0, k1;        // -c_q / (2 L), c_q = (1 - 2q) src - mic
-    float inv2l;         // 1 / (2 L)
-    float nm;
-    float slack;         // metres
 };
-
-__device__ inline AxisCount axis_count(const Axis& a, int nm, double k_fs_c) {
-    const double inv2l = 1.0 / (2.0 * a.room);
-    return AxisCount{uni((float)(-(a.src - a.mic) * inv2l)), uni((float)(-(-a.src - a.mic) * inv2l)), uni((float)inv2l),
-                     uni((float)nm), uni((float)(0.2 / k_fs_c))};
+__device__ __attribute__((noinline)) unsigned int walk_near(const ItemCtx& w, int n_near, int n_y, int n_p, int i, const double* ykey, const unsigned short* ycount,
+                                                            const float* bpow, const double* zpow, unsigned long long* hist) {
+    const int l = i & 3, column = (i >> 2) / n_p, p = (i >> 2) - column * n_p, ix = column / n_y, iy = column - ix * n_y;
+    const int qx = ix & 1, nx = (ix >> 1) - n_near;
+    const double dx = axis_delta(w.ax, qx, nx);
+    const double a = __dadd_rn(__dmul_rn(dx, dx), ykey[iy]);
+    const int kxy = reflections(qx, nx) + ycount[iy];
+    const double u = w.two_l * (double)p, dz = __dadd_rn(u, w.begin[l]), d2 = fma(dz, dz, a);
+    // (past the cut the amplitudes are zero, and bpow has not been formed)
+    if (!(d2 < w.walk2) || kxy > w.k_cut) return 0;
+    const double y = __builtin_amdgcn_rsq(d2);
+    const int slot = tap_slot(w, d2, y, [&] { return exact_z_image(w.az, a, u, l); });
+    if (8u * (unsigned int)slot > w.top8) return 0;
+    const double bxy = (double)bpow[kxy], even = __dmul_rn(zpow[p], bxy);
+    deposit<false, false>(8u * (unsigned int)slot, l == 0 ? even : l == 1 ? __dmul_rn(even, w.beta2) : __dmul_rn(zpow[p], __dmul_rn(bxy, w.beta)), y, hist);
+    return 1;
 }
 
-// terms n of c_q + 2 n L, |n| <= nm, within [-s, s]: (-s - c_q) / 2L <= n <= (s - c_q) / 2L
-__device__ inline int count_within(const AxisCount& a, float s) {
-    float total = 0.f;
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const float k = q ? a.k1 : a.k0;
-        const float hi = fminf(floorf(fmaf(s, a.inv2l, k)), a.nm);
-        const float minus_lo = fminf(floorf(fmaf(s, a.inv2l, -k)), a.nm);
-        total += fmaxf(hi + minus_lo + 1.f, 0.f);
+// Prepares item `it`: all lanes of one wavefront compute the same, lane 0 writes.
+template <bool COUNT>
+__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
+    ItemCtx c{};
+    c.kind = kEnd;
+    if (it < n_items) {
+        const Item item = items[it];
+        const Room room = load_room(rooms, uni(item.rir));
+        const float* g = room.g;
+        const int n0 = item.n0, n1 = item.n1;
+        c.kind = kSilent;
+        c.rir = item.rir;
+        c.n0 = n0;
+        c.n1 = n1;
+        c.top8 = 8u * (unsigned int)(n1 - n0 + 1);
+        if (room_ok(g)) {
+            const Axis ax{(double)g[0], (double)g[3], (double)g[6]}, ay{(double)g[1], (double)g[4], (double)g[7]},
+                az{(double)g[2], (double)g[5], (double)g[8]};
+            c.ax = ax;
+            c.ay = ay;
+            c.az = az;
+            c.beta = (double)g[9];
+            // every image of this item lies in r_in <= d < r_out (half a tap of slack on either side)
+            const double r_out = (double)n1 / k_fs_c, r_in = n0 > 0 ? (double)(n0 - 1) / k_fs_c : 0.0;
+            c.r_out2 = r_out * r_out;
+            // An image reflected k times adds beta^k / (4 pi d) * 2^56, rounded to an integer, to its
+            // tap; once beta^k < 2 pi d 2^-56 that is exactly zero, so such images are never visited.
+            // (amplitude sums only; tap counts visit every image)
+            c.inv_log2_beta = (!COUNT && g[9] > 0.f && g[9] < 1.f) ? 1.f / __log2f(g[9]) : 0.f;
+            c.k_cut = reflection_cut(c.inv_log2_beta, (float)r_in);
+            c.nmx = min((int)ceil(r_out / (2.0 * ax.room)) + 1, c.k_cut / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
+            c.nmy = min((int)ceil(r_out / (2.0 * ay.room)) + 1, c.k_cut / 2 + 1);
+            c.nmz = (int)ceil(r_out / (2.0 * az.room)) + 1;
+            c.k_fs_c = k_fs_c;
+            // (in whole units of the estimate's 2^-16 tap, so that adding it to the magic number is exact; one unit
+            // for the sum's rounding)
+            const double margin = ceil(kQuickError * 65536.0 * (double)(n1 + 2)) + 1.0;
+            c.quick_k = k_fs_c * (1.0 - kQuickMiddle);
+            c.quick_shift = kQuickMagic + (0.5 + margin * 0x1p-16 - (double)(n0 - 1));
+            c.quick_margin2 = (int)(2.0 * margin) + 1;
+            const double guard = 1e-12 * (double)(n1 + 1) + 1e-13;
+            c.shift = (0.5 + guard) - (double)(n0 - 1);
+            c.guard2 = 2.0 * guard;
+            c.two_l = 2.0 * az.room;
+            const double apart = fabs(az.src - az.mic), both = az.src + az.mic;
+            c.begin[0] = apart;
+            c.begin[1] = c.two_l - apart;
+            c.begin[2] = both;
+            c.begin[3] = c.two_l - both;
+            c.beta2 = c.beta * c.beta;
+            // beyond 2.6 m every amplitude is below 2^-5 (see deposit); the few images of the innermost items that may be
+            // nearer are walked apart
+            const double r_near = kNearMetres + 0.25 / k_fs_c;
+            c.near_item = !COUNT && r_in < r_near;
+            c.walk2 = c.near_item ? r_near * r_near : r_in * r_in;
+            // the fast walk: the x and y images fit the LDS tables and so do the powers along z, and the closed forms hold
+            const double height_taps = az.room * k_fs_c;
+            const bool fast = axis_in_order(ax) && axis_in_order(ay) && axis_in_order(az) && both >= 0.0 &&
+                              2 * (2 * c.nmx + 1) <= 2 * kAxisCap && y_images(c.nmy) <= kYCap && c.nmz <= kMaxP &&
+                              ay.room * k_fs_c < kMaxAxisTaps && height_taps <= kMaxHeightTaps && height_taps >= kMinHeightTaps;
+            c.kind = fast ? kFast : kPlain;
+            c.cy = axis_count(ay, k_fs_c);
+            c.y_order = axis_order(ay);
+            const float slack = c.cy.slack, inv2l = (float)(1.0 / c.two_l), z_per_y = (float)(az.room / ay.room);
+            auto farthest = [](const Axis& ax1) {
+                return 1.0001f * fmaxf(fabsf((float)(ax1.src - ax1.mic)), fabsf((float)(ax1.room - ax1.src - ax1.mic))) + 1e-3f;
+            };
+            c.y_reach[0] = 1.0001f * (float)ay.room;
+            c.y_reach[1] = farthest(ay);
+            c.z_reach[0] = 1.0001f * (float)az.room;
+            c.z_reach[1] = farthest(az) + c.y_reach[1] * z_per_y;
+            c.z_reach[2] = 0.9999f * z_per_y;
+            // the nearest and the farthest beginning of a list, in units of 2 L
+            const float least = (float)(fmin(fmin(apart, c.begin[1]), fmin(both, c.begin[3])) / c.two_l);
+            const float most = (float)(fmax(fmax(apart, c.begin[1]), fmax(both, c.begin[3])) / c.two_l);
+            c.lo[0] = 0.999998f * inv2l;
+            c.lo[1] = -slack * inv2l - most;
+            c.hi[0] = 1.000002f * inv2l;
+            c.hi[1] = slack * inv2l - least;
+        }
     }
-    return (int)total;
-}
-
-// number of entries with key <= bound, or a few more
-__device__ inline int count_not_above(const AxisCount& a, int n, double bound) {
-    if (!(bound >= 0.0)) return 0;
-    const float s = __builtin_amdgcn_sqrtf((float)bound);
-    return min(count_within(a, fmaf(s, 1.000002f, a.slack)), n);
-}
-// number of entries with key < bound, or a few fewer
-__device__ inline int count_below(const AxisCount& a, double bound) {
-    const float s = fmaf(__builtin_amdgcn_sqrtf(fmaxf((float)bound, 0.f)), 0.999998f, -a.slack);
-    return s > 0.f ? count_within(a, s) : 0;
+    if (lane == 0) ctx = c;
 }
 
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
@@ -682,279 +850,306 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     Rooms rooms, int rir_len, double k_fs_c, const Item* __restrict__ items,
     int* __restrict__ ctrl, float* __restrict__ rir_out,
     int32_t* __restrict__ cnt_out, unsigned long long* __restrict__ visits = nullptr) {
-    __shared__ unsigned long long hist[(COUNT ? kMaxTaps / 2 : kMaxTaps) + 2];     // first and last slot are never read
-    __shared__ float bpow[COUNT ? 1 : kPow];
-    __shared__ AxisImage ztab_store[2 * kAxisCap + 2];
-    AxisImage* const ztab = ztab_store + 2;        // z images sorted by dz*dz (spare entries in front)
-    __shared__ AxisImage ytab[2 * kAxisCap];       // y images sorted by dy*dy
-    __shared__ int row_pfx[2 * kAxisCap];          // per x image: inclusive prefix of live column counts
-    __shared__ Column cols[kWaves][64];
-    __shared__ __align__(8) unsigned int piece_starts[kWaves][kStartWords];
-    __shared__ int s_item, s_batch;
+    constexpr int kSlots = kMaxTaps + 2 + 64;      // (see ItemCtx::top8)
+    __shared__ __align__(16) unsigned long long hist[COUNT ? kSlots / 2 : kSlots];
+    __shared__ float bpow[COUNT ? 1 : kPow];       // beta^k
+    __shared__ double zpow[kMaxP + 2];             // beta^(2 p) / (4 pi) 2^56
+    __shared__ double ykey[kYCap];                 // y images in order of distance: dy*dy
+    __shared__ unsigned short ycount[kYCap];       // and reflections
+    __shared__ unsigned short row_count[2 * kAxisCap];     // live columns per x image, summed up within every 64 of them
+    __shared__ int row_part[2 * kAxisCap / 64];    // the totals of those
+    __shared__ unsigned int row_gap[2 * kAxisCap];         // y images before the dead ones, and how many these are << 16
+    __shared__ int row_begin[2 * kAxisCap + 5];    // the first column of every x image (and what is read past the last)
+    __shared__ double col_a[kColumns];             // live columns of a chunk, longest first: dx*dx + dy*dy
+    __shared__ unsigned int col_range[kColumns];     // first p, last p less that << 8, reflections << 16
+    __shared__ int census[2][64];                  // columns per length
+    __shared__ int s_round;
+    __shared__ ItemCtx s_ctx[2];
     unsigned int* hist32 = reinterpret_cast<unsigned int*>(hist);
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int n_items = ctrl[0];
+    int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uni(tid >> 6), n_items = ctrl[0];
     unsigned long long walked = 0;
+    auto prepare_next = [&](ItemCtx& ctx) {        // by one wavefront
+        int it = 0;
+        if (lane == 0) it = atomicAdd(&ctrl[1], 1);
+        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane);
+    };
 
-    for (;;) {
-        if (tid == 0) {
-            s_item = atomicAdd(&ctrl[1], 1);
-            s_batch = kWaves;
-        }
-        __syncthreads();
-        const int it = uni(s_item);
-        if (it >= n_items) break;
-        const Item item = items[it];
-        const int n0 = item.n0, n1 = item.n1, n_taps = n1 - n0;
-        const Room room = load_room(rooms, uni(item.rir));
-        const float* g = room.g;
+    // sums start at zero and are left at zero where an item is written out
+    if (COUNT) {
+        for (int i = tid; i < kSlots; i += kThreads) hist32[i] = 0u;
+    } else {
+        for (int i = tid; i < kSlots; i += kThreads) hist[i] = 0ull;
+    }
+    if (wave == kWaves - 1) prepare_next(s_ctx[0]);
 
-        if (COUNT) {
-            for (int i = tid; i <= n_taps + 1; i += kThreads) hist32[i] = 0u;
-        } else {
-            for (int i = tid; i <= n_taps + 1; i += kThreads) hist[i] = 0ull;
-        }
-        if (room_ok(g)) {
-            const Axis ax{uni((double)g[0]), uni((double)g[3]), uni((double)g[6])};
-            const Axis ay{uni((double)g[1]), uni((double)g[4]), uni((double)g[7])};
-            const Axis az{uni((double)g[2]), uni((double)g[5]), uni((double)g[8])};
-            const double beta = uni((double)g[9]);
-            // every image of this item lies in r_in <= d < r_out (half a tap of slack on either side)
-            const double r_out = uni((double)n1 / k_fs_c);
-            const double r_in = n0 > 0 ? uni((double)(n0 - 1) / k_fs_c) : 0.0;
-            const double r_out2 = uni(r_out * r_out), r_in2 = uni(r_in * r_in);
-            // An image reflected k times adds beta^k / (4 pi d) * 2^56, rounded to an integer, to its
-            // tap; once beta^k < 2 pi d 2^-56 that is exactly zero, so such images are never visited.
-            // log2_beta < 0 enables the cut (amplitude sums only; tap counts visit every image).
-            const float log2_beta = (!COUNT && g[9] > 0.f && g[9] < 1.f) ? uni(__log2f(g[9])) : 0.f;
-            const int k_cut_item = uni(reflection_cut(log2_beta, (float)r_in));
-            int nmx = uni((int)ceil(r_out / (2.0 * ax.room)) + 1);
-            int nmy = uni((int)ceil(r_out / (2.0 * ay.room)) + 1);
-            const int nmz = uni((int)ceil(r_out / (2.0 * az.room)) + 1);
-            nmx = min(nmx, k_cut_item / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
-            nmy = min(nmy, k_cut_item / 2 + 1);
-            const int nix = 2 * (2 * nmx + 1), niy = 2 * (2 * nmy + 1), niz = 2 * (2 * nmz + 1);
-            const AxisCount cy = axis_count(ay, nmy, k_fs_c), cz = axis_count(az, nmz, k_fs_c);
-            Column* wc = cols[wave];
-            WalkCtx wctx;
-            wctx.k_fs_c = k_fs_c;
-            // (in whole units of the estimate's 2^-16 tap, so that adding it to the magic number is exact; one unit
-            // for the sum's rounding)
-            const double margin = ceil(kQuickError * 65536.0 * (double)(n1 + 2)) + 1.0;
-            wctx.quick_k = uni(k_fs_c * (1.0 - kQuickMiddle));
-            wctx.quick_shift = kQuickMagic + (0.5 + margin * 0x1p-16 - (double)(n0 - 1));
-            wctx.quick_margin2 = uni((int)(2.0 * margin) + 1);
-            const double guard = 1e-12 * (double)(n1 + 1) + 1e-13;
-            wctx.shift = (0.5 + guard) - (double)(n0 - 1);
-            wctx.guard2 = uni(2.0 * guard);
-            wctx.n0 = n0;
-            wctx.n1 = n1;
-            // beyond 2.6 m every amplitude is below 2^-5 (see deposit); the few images of the innermost items that may be
-            // nearer are walked apart.  (The table positions that separate the two are off by less than 0.25 taps.)
-            const double r_near = kNearMetres + 0.25 / k_fs_c, r_near2 = uni(r_near * r_near);
-            const bool near_item = !COUNT && r_in < r_near;
-            const double r_walk2 = near_item ? r_near2 : r_in2;
-            wctx.beta = beta;
-            const float y0_max = uni(fmaxf(fabsf((float)(ay.src - ay.mic)), fabsf((float)(ay.src + ay.mic))));
-            const float z0_max = uni(fmaxf(fabsf((float)(az.src - az.mic)), fabsf((float)(az.src + az.mic))));
-            const float lyf = uni((float)ay.room), lzf = uni((float)az.room);
-            // every image with at most k reflections along an axis lies within max|c_q| + (k + 1) L of the
-            // microphone on that axis; squared, with a little slack, this bounds the table range to visit
-            auto reach2 = [](float c_max, float room, int k) {
-                const float r = c_max + (float)(k + 1) * room;
-                return (double)(r * r * 1.0001f + 1e-3f);
-            };
-
-            // fast path: the y and z images fit the LDS tables and so do the x rows, and the closed forms hold
-            const bool fast = axis_in_order(ax) && axis_in_order(ay) && axis_in_order(az) &&
-                              nix <= 2 * kAxisCap && niy <= 2 * kAxisCap && niz <= 2 * kAxisCap &&
-                              fmax(ay.room, az.room) * k_fs_c < kMaxAxisTaps;
-            int n_cand;
-            if (!COUNT) {
-                // beta^k by squaring (k < 1024: ten steps, a few units in the last place of the double, far inside
-                // the float it is kept as; the library pow is some ten times the instructions), for the counts that
-                // can be asked for: those of the z images, and of a column at most the cut or all there are
-                const int k_most = max(2 * nmz + 1, min(k_cut_item, 2 * (nmx + nmy) + 2));
-                for (int i = tid; i <= min(k_most, kPow - 1); i += kThreads) {
-                    double b = beta, acc = 1.0;
-#pragma unroll
-                    for (int bit = 0; bit < 10; ++bit) {
-                        if ((i >> bit) & 1) acc *= b;
-                        b *= b;
-                    }
-                    bpow[i] = (float)acc;
+    for (int now = 0, items_done = 0;; now ^= 1, ++items_done) {
+        group_sync();                              // s_ctx[now] is there, and the sums of the item before are complete
+        // (opaque: addresses are formed anew for every item, kept from one to the next they do not fit the registers)
+        asm volatile("" : "+v"(tid));
+        lane = tid & 63;
+        const ItemCtx& c = s_ctx[now];
+        if (items_done > 0) {
+            const ItemCtx& before = s_ctx[now ^ 1];
+            const int n_taps = uni(before.n1 - before.n0);
+            const size_t to = (size_t)uni(before.rir) * rir_len + uni(before.n0) - 1;
+            if (COUNT) {
+                for (int i = tid; i < n_taps + 65; i += kThreads) {
+                    const unsigned int v = hist32[i];
+                    hist32[i] = 0u;
+                    if (i > 0 && i <= n_taps) cnt_out[to + i] = (int32_t)v;
                 }
-            }
-            __syncthreads();
-            if (fast) {
-                build_sorted_images(az, nmz, ztab, tid, [&](int q, int n) {
-                    if (COUNT) return 0.0;
-                    const int k = iabs(n - q) + iabs(n);
-                    // beta^k / (4 pi) * 2^56
-                    return (double)(k < kPow ? bpow[k] : beta_pow_slow(beta, k)) * kAmplitude;
-                });
-                build_sorted_images(ay, nmy, ytab, tid, [&](int q, int n) { return (double)(iabs(n - q) + iabs(n)); });
-                // live columns of x image ix: the y images with dy^2 <= r_out^2 - dx^2 that the reflection
-                // cut can still reach -- a prefix of the sorted y table
-                for (int ix = tid; ix < nix; ix += kThreads) {
-                    const int qx = ix & 1, nx = (ix >> 1) - nmx;
-                    const double dx = axis_delta(ax, qx, nx);
-                    double bound = r_out2 - __dmul_rn(dx, dx);
-                    const int ky_max = k_cut_item - (iabs(nx - qx) + iabs(nx));
-                    if (ky_max < (1 << 18)) bound = fmin(bound, reach2(y0_max, lyf, ky_max));
-                    row_pfx[ix] = (bound >= 0.0 && ky_max >= 0) ? count_not_above(cy, niy, bound) : 0;
-                }
-                __syncthreads();
-                if (wave == 0) {                              // inclusive scan over the rows, 64 at a time
-                    int carry = 0;
-                    for (int base = 0; base < nix; base += 64) {
-                        const int i = base + lane;
-                        const int v = wave_inclusive_scan(i < nix ? row_pfx[i] : 0) + carry;
-                        if (i < nix) row_pfx[i] = v;
-                        carry = __shfl(v, 63, 64);
-                    }
-                }
-                __syncthreads();
-                n_cand = row_pfx[nix - 1];
             } else {
-                n_cand = nix * niy;
-            }
-            if (fast && near_item) {
-                // the columns within r_near: y images up to that, of the x images with |n| <= n_near
-                const int n_near = min((int)(r_near / (2.0 * ax.room)) + 1, nmx), n_rows = 2 * (2 * n_near + 1);
-                const int n_y = count_not_above(cy, niy, r_near2);
-                for (int i = tid; i < n_rows * n_y; i += kThreads) {
-                    const int ix = i / n_y, qx = ix & 1, nx = (ix >> 1) - n_near;
-                    const AxisImage ye = ytab[i - ix * n_y];
-                    const double dx = axis_delta(ax, qx, nx);
-                    const double a = __dadd_rn(__dmul_rn(dx, dx), ye.key);
-                    const int first = count_below(cz, r_in2 - a);
-                    const int last = min(count_below(cz, r_near2 - a), count_not_above(cz, niz, r_out2 - a));
-                    const int kxy = iabs(nx - qx) + iabs(nx) + (int)ye.aux;
-                    // (past the cut the amplitudes are zero, and bpow has not been formed)
-                    if (last <= first || kxy > k_cut_item) continue;
-                    walk_near(wctx, a, (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(beta, kxy)), ztab, first, last, hist);
-                    if (VISITS) walked += (unsigned long long)(last - first);
-                }
-            }
-            const int n_batch = (n_cand + 63) / 64;
-
-            // Batches are taken from a counter (they differ in work by their columns' ranges; dealt in turn, a wave in
-            // eight waited an eighth of the time for the others); the next one is asked for while this one is worked on.
-            int row_lo = 0;          // row of the batch's first candidate: it only moves up from batch to batch
-            for (int batch = wave, next = 0; batch < n_batch; batch = uni(next)) {
-                if (lane == 0) next = atomicAdd(&s_batch, 1);
-                // ---- each lane describes one candidate column ----
-                const int cand = batch * 64 + lane;
-                if (fast)
-                    while (row_pfx[row_lo] <= batch * 64) ++row_lo;       // (the same in every lane; batch * 64 < n_cand)
-                Column col;
-                col.a = 0.0;
-                int kxy = 0, z_first = 0, z_len = 0;
-                int pieces = 0;
-                if (cand < n_cand) {
-                    if (fast) {
-                        // smallest row with row_pfx > cand: a short walk from the row of the batch's first
-                        // column, since 64 consecutive columns span few rows
-                        int lo = row_lo;
-                        while (row_pfx[lo] <= cand) ++lo;
-                        const int ix = lo, qx = ix & 1, nx = (ix >> 1) - nmx;
-                        const AxisImage ye = ytab[cand - (ix ? row_pfx[ix - 1] : 0)];
-                        const double dx = axis_delta(ax, qx, nx);
-                        col.a = __dadd_rn(__dmul_rn(dx, dx), ye.key);
-                        kxy = iabs(nx - qx) + iabs(nx) + (int)ye.aux;
+                // two slots per thread and round
+                float* const out = rir_out + to;
+                ulonglong2* const pairs = reinterpret_cast<ulonglong2*>(hist);
+                auto value = [](unsigned long long v) {
+                    return (float)(fma((double)(unsigned int)(v >> 32), 0x1p32, (double)(unsigned int)v) * 0x1p-56);
+                };
+#pragma unroll 3
+                for (int i = tid; 2 * i < n_taps + 65; i += kThreads) {
+                    const ulonglong2 v = pairs[i];
+                    pairs[i] = make_ulonglong2(0ull, 0ull);
+                    const TapPair t{value(v.x), value(v.y)};
+                    if (i > 0 && 2 * i + 1 <= n_taps) {
+                        *reinterpret_cast<TapPair*>(out + 2 * i) = t;
                     } else {
-                        const int ix = cand / niy, iy = cand - ix * niy;
-                        const int qx = ix & 1, nx = (ix >> 1) - nmx;
-                        const int qy = iy & 1, ny = (iy >> 1) - nmy;
-                        const double dx = axis_delta(ax, qx, nx);
-                        const double dy = axis_delta(ay, qy, ny);
-                        col.a = __dadd_rn(__dmul_rn(dx, dx), __dmul_rn(dy, dy));
-                        kxy = iabs(nx - qx) + iabs(nx) + iabs(ny - qy) + iabs(ny);
+                        if (i > 0 && 2 * i <= n_taps) out[2 * i] = t.x;
+                        if (2 * i + 1 <= n_taps) out[2 * i + 1] = t.y;
                     }
-                    // reflections left for the z axis before this column's images vanish
-                    // (beyond the first shell the shell's own inner radius bounds the distance well enough)
-                    const int kz_max = (n0 > 0 ? k_cut_item : reflection_cut(log2_beta, sqrtf((float)col.a))) - kxy;
-                    if (col.a < r_out2 && kz_max >= 0) {
-                        if (fast) {
-                            // images with r_in^2 - a <= dz^2 <= r_out^2 - a within reach of the reflection cut:
-                            // one contiguous range of the sorted z table (the few images past the cut that it
-                            // keeps add exactly zero)
-                            double hi2 = r_out2 - col.a;
-                            if (kz_max < (1 << 18)) hi2 = fmin(hi2, reach2(z0_max, lzf, kz_max));
-                            const double lo2 = r_walk2 - col.a;
-                            const int first = lo2 > 0.0 ? count_below(cz, lo2) : 0;     // entries with dz2 < lo2
-                            const int last = count_not_above(cz, niz, hi2);
-                            if (last > first) {
-                                z_first = first;
-                                z_len = last - first;
-                                pieces = (z_len + kPiece - 1) / kPiece;
-                            }
-                        } else {
-                            pieces = 1;                        // one lane walks every z image of the column
-                        }
-                    }
-                }
-                const int pfx = wave_inclusive_scan(pieces);
-                const int my_first = pfx - pieces;             // this column's first piece
-                col.place = (z_first - kPiece * my_first) * 1024 + (z_first + z_len);
-                if (!COUNT) col.bxy = kxy < kPow ? bpow[kxy] : (pieces ? beta_pow_slow(beta, kxy) : 0.f);
-                const int n_pieces = __builtin_amdgcn_readlane(pfx, 63);
-                // columns with pieces, packed in order
-                const unsigned long long live = __ballot(pieces > 0);
-                if (pieces > 0)
-                    wc[__builtin_amdgcn_mbcnt_hi((unsigned int)(live >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)live, 0u))] = col;
-
-                // ---- pieces are dealt to lanes ----
-                // Piece p belongs to the last column that starts at or before it.  Every column but a chunk's first sets
-                // bit f - 1 of a bit map, f its first piece; a piece's column is then a count of the bits below it.
-                unsigned int* starts = piece_starts[wave];
-                constexpr int kChunk = 32 * kStartWords;
-                for (int chunk = 0; chunk < n_pieces; chunk += kChunk) {
-                    if (lane < kStartWords) starts[lane] = 0u;
-                    wave_sync_lds();
-                    const int bit = my_first - chunk - 1;
-                    if (pieces > 0 && bit >= 0 && bit < kChunk) atomicOr(&starts[bit >> 5], 1u << (bit & 31));
-                    int before = __popcll(__ballot(pieces > 0 && bit < 0)) - 1;       // the column of the chunk's first piece
-                    wave_sync_lds();
-                    const int chunk_end = min(n_pieces, chunk + kChunk);
-                    for (int p0 = chunk; p0 < chunk_end; p0 += 64) {
-                        const uint2 m = *reinterpret_cast<const uint2*>(&starts[(p0 - chunk) >> 5]);   // pieces p0 .. p0 + 63
-                        const int mine = (int)__builtin_amdgcn_mbcnt_hi(m.y, __builtin_amdgcn_mbcnt_lo(m.x, (unsigned int)before));
-                        const int p = p0 + lane;
-                        if (p < chunk_end) {
-                            const Column c = wc[mine];
-                            if (fast) {
-                                const int first = (c.place >> 10) + __mul24(kPiece, p);
-                                const int len = min(kPiece, (c.place & 1023) - first);
-                                walk_piece_table<COUNT>(wctx, c.a, (double)c.bxy, ztab, first, len, hist);
-                                if (VISITS) walked += (unsigned long long)len;
-                            } else {
-                                walk_column_direct<COUNT>(wctx, az, c.a, (double)c.bxy * kAmplitude, nmz, hist);
-                                if (VISITS) walked += (unsigned long long)niz;
-                            }
-                        }
-                        before += __popc(m.x) + __popc(m.y);
-                    }
-                    wave_sync_lds();
                 }
             }
         }
-        __syncthreads();
+        const int kind = uni(c.kind);
+        if (kind == kEnd) break;
 
-        if (COUNT) {
-            int32_t* out = cnt_out + (size_t)item.rir * rir_len + n0;
-            for (int i = tid; i < n_taps; i += kThreads) out[i] = (int32_t)hist32[i + 1];
-        } else {
-            float* out = rir_out + (size_t)item.rir * rir_len + n0;
-            for (int i = tid; i < n_taps; i += kThreads) {
-                const unsigned long long v = hist[i + 1];
-                const double d = (double)(unsigned int)(v >> 32) * 4294967296.0 + (double)(unsigned int)v;
-                out[i] = (float)(d * 1.3877787807814457e-17);       // 2^-56
+        const int nmx = uni(c.nmx), nmy = uni(c.nmy), nmz = uni(c.nmz), k_cut = uni(c.k_cut);
+        const int nix = 2 * (2 * nmx + 1), n_yimages = y_images(nmy), segments = (nix + 63) / 64;
+        if (!COUNT && kind != kSilent) {
+            // beta^k by squaring (k < 1024: ten steps, a few units in the last place of the double, far inside
+            // the float it is kept as; the library pow is some ten times the instructions), for the counts that
+            // a column can have: at most the cut or all there are
+            const int k_most = min(min(k_cut, 2 * (nmx + nmy) + 8), kPow - 1), n_z = min(nmz, kMaxP) + 1;
+            for (int i = tid; i <= k_most + 1 + n_z; i += kThreads) {
+                const bool z = i > k_most;
+                const int k = z ? 2 * (i - k_most - 1) : i;
+                double b = c.beta, v = 1.0;
+#pragma unroll
+                for (int bit = 0; bit < 10; ++bit) {
+                    if ((k >> bit) & 1) v *= b;
+                    b *= b;
+                }
+                if (z) zpow[i - k_most - 1] = v * kAmplitude;
+                else bpow[i] = (float)v;
             }
         }
-        __syncthreads();
+        if (kind == kFast) {
+            for (int i = tid; i < n_yimages; i += kThreads) {
+                int q, n;
+                ordered_image(c.y_order, i, q, n);
+                const double dy = axis_delta(c.ay, q, n);
+                ykey[i] = __dmul_rn(dy, dy);
+                ycount[i] = (unsigned short)reflections(q, n);
+            }
+            // Columns of x image ix that may be live: the y images with dy^2 <= r_out^2 - dx^2 that the reflection
+            // cut can still reach -- the first of the y table --, but for those in a gap: what reflections they leave does
+            // not take their z images as far as the shell's inner radius, A - B |dy| < sqrt(R^2 - dy^2), an interval of |dy|.
+            // (Five of six columns of 32 responses of 32768 taps, half of those of 3072.)  The wavefronts from the other
+            // end: those have no y image.
+            for (int seg = kWaves - 1 - wave; seg < segments; seg += kWaves) {
+                const int ix = 64 * seg + lane, qx = ix & 1, nx = (ix >> 1) - nmx;
+                const double dx = axis_delta(c.ax, qx, nx), dx2 = __dmul_rn(dx, dx);
+                const float outer = (float)(c.r_out2 - dx2), inner = (float)(c.walk2 - dx2) * 0.9999f;
+                const int k_left = k_cut - reflections(qx, nx);
+                const float reach = fmaf((float)k_left, c.y_reach[0], c.y_reach[1]);
+                int count = 0;
+                unsigned int gap = 0;
+                if (outer >= 0.f && k_left >= 0 && ix < nix) {
+                    count = min(count_within(c.cy, fminf(__builtin_amdgcn_sqrtf(outer), reach)), n_yimages);
+                    const float A = fmaf((float)k_left, c.z_reach[0], c.z_reach[1]), B = c.z_reach[2], s = fmaf(B, B, 1.f);
+                    const float D = fmaf(inner, s, -A * A);
+                    if (D > 0.f) {
+                        const float root = __builtin_amdgcn_sqrtf(D), scale = __builtin_amdgcn_rcpf(s);
+                        const float from = (A * B - root) * scale, to = (A * B + root) * scale;
+                        const int first = from > 0.f ? min(count_within(c.cy, from), count) : 0;
+                        const int last = min(count_within<-1>(c.cy, to * 0.99999f), count);
+                        if (last > first) {
+                            gap = (unsigned int)(first | (last - first) << 16);
+                            count -= last - first;
+                        }
+                    }
+                }
+                const int part = wave_inclusive_scan(count);
+                if (ix < nix) {
+                    row_count[ix] = (unsigned short)part;
+                    row_gap[ix] = gap;
+                }
+                if (lane == 63) row_part[seg] = part;
+            }
+            if (tid < 128) census[tid >> 6][lane] = 0;
+        }
+        group_sync();
+
+        bool prepared = false;
+        if (kind == kFast) {
+            // the rows' prefix sums: every wavefront forms all of them (and writes what the others write), so that none
+            // waits for another
+            const int my_part = lane < segments ? row_part[lane] : 0, up_to_part = wave_inclusive_scan(my_part);
+            const int n_cand = __builtin_amdgcn_readlane(up_to_part, 63);
+            for (int seg = 0; seg < segments; ++seg) {
+                const int i = 64 * seg + lane;
+                if (i < nix) row_begin[i + 1] = (int)row_count[i] + (seg ? __builtin_amdgcn_readlane(up_to_part, seg - 1) : 0);
+            }
+            if (lane < 4) row_begin[lane ? nix + lane : 0] = lane ? 0x7fffffff : 0;
+            wave_sync_lds();
+            const bool near_item = uni(c.near_item) != 0;
+
+            // Columns are worked through a chunk at a time.  Each thread describes kPerThread candidates (the wavefronts'
+            // stretches of 64 side by side, so that a wavefront's rows only move up); the live ones are sorted by length,
+            // in LDS, and taken 64 at a time, longest first, from a counter.
+            for (int base = 0, parity = 0; base < n_cand; base += kChunk, parity ^= 1) {
+                double a[kPerThread];
+                unsigned int range[kPerThread];
+                int place[kPerThread];                    // length << 16 | number among those of that length, -1: not live
+#pragma unroll
+                for (int j = 0; j < kPerThread; ++j) {
+                    const int cand0 = base + 64 * (kWaves * j + wave), cand = cand0 + lane;
+                    a[j] = 0.0;
+                    range[j] = 0u;
+                    place[j] = -1;
+                    if (cand0 >= n_cand) continue;
+                    // the row of the stretch's first column, and from there the lane's own: 64 consecutive columns span
+                    // few rows, so the next four are compared at once
+                    int row = 0;
+                    for (int seg = 0; seg < segments; ++seg) {
+                        const int i = 64 * seg + lane;
+                        row += __popcll(__ballot(i < nix && row_begin[i + 1] <= cand0));
+                    }
+                    int ix = row, begin = row_begin[row];
+#pragma unroll
+                    for (int k = 1; k <= 4; ++k) {
+                        const int at = row_begin[row + k];
+                        if (at <= cand) {
+                            ix = row + k;
+                            begin = at;
+                        }
+                    }
+                    if (cand < n_cand) {
+                        while (row_begin[ix + 1] <= cand) begin = row_begin[++ix];        // (seldom)
+                        const unsigned int gap = row_gap[ix];
+                        const int qx = ix & 1, nx = (ix >> 1) - nmx, nth = cand - begin;
+                        const int iy = nth + (nth >= (int)(gap & 0xffffu) ? (int)(gap >> 16) : 0);
+                        const double dx = axis_delta(c.ax, qx, nx);
+                        a[j] = __dadd_rn(__dmul_rn(dx, dx), ykey[iy]);
+                        const int kxy = reflections(qx, nx) + ycount[iy];
+                        // reflections left for the z axis before this column's images vanish
+                        // (beyond the first shell the shell's own inner radius bounds the distance well enough)
+                        const int cut = c.n0 > 0 ? k_cut : reflection_cut(c.inv_log2_beta, __builtin_amdgcn_sqrtf((float)a[j]));
+                        const float outer = (float)(c.r_out2 - a[j]), inner = (float)(c.walk2 - a[j]);
+                        // The images with r_in^2 <= a + dz^2 <= r_out^2 and reflections left: from the first p at which some
+                        // list has begun to the last at which not all have ended.
+                        const float to = fmaf(__builtin_amdgcn_sqrtf(fmaxf(outer, 0.f)), c.hi[0], c.hi[1]);
+                        const float from = fmaf(__builtin_amdgcn_sqrtf(fmaxf(inner, 0.f)), c.lo[0], c.lo[1]);
+                        const int p1 = min(min((int)floorf(to), (cut - kxy) >> 1), nmz), p0 = max((int)ceilf(from), 0);
+                        if (outer > 0.f && cut >= kxy && p1 >= p0) {
+                            range[j] = (unsigned int)(p0 | (p1 - p0) << 8 | kxy << 16);
+                            const int length = min(p1 - p0, 63);
+                            place[j] = atomicAdd(&census[parity][63 - length], 1) | (63 - length) << 16;
+                        }
+                    }
+                }
+                group_sync();                             // also: every column of the chunk before has been walked
+                const int of_length = census[parity][lane], up_to = wave_inclusive_scan(of_length);
+                const int n_live = __builtin_amdgcn_readlane(up_to, 63), first = up_to - of_length;
+                if (wave == 0) census[parity ^ 1][lane] = 0;
+#pragma unroll
+                for (int j = 0; j < kPerThread; ++j) {
+                    if (base + kThreads * j >= n_cand) continue;
+                    const int at = __shfl(first, (place[j] >> 16) & 63, 64) + (place[j] & 0xffff);
+                    place[j] = place[j] >= 0 ? at : -1;
+                }
+                const WalkRegs regs(c);
+                const double two_l = uni(c.two_l), beta = uni(c.beta);
+                const unsigned int dropped8 = uni((int)c.top8) + 8u * (unsigned int)lane;      // (slots apart: adds to one place queue up)
+                int walked_to = 0;
+                do {
+                    // in the last go of the last chunk a wavefront prepares the next item before it joins in
+                    const bool last = base + kChunk >= n_cand && walked_to + kColumns >= n_live, apart = last && wave == kWaves - 1;
+                    if (walked_to) group_sync();              // the columns of the go before have been walked
+                    if (tid == 0) s_round = last ? kWaves - 1 : kWaves;
+#pragma unroll
+                    for (int j = 0; j < kPerThread; ++j) {
+                        if (base + kThreads * j >= n_cand) continue;
+                        const int at = place[j] - walked_to;
+                        if (place[j] >= 0 && at >= 0 && at < kColumns) {
+                            col_a[at] = a[j];
+                            col_range[at] = range[j];
+                        }
+                    }
+                    group_sync();
+                    const int n_here = min(n_live - walked_to, kColumns), column_rounds = (n_here + 63) / 64;
+                    int round = wave;
+                    auto next_round = [&] {
+                        int next = 0;
+                        if (lane == 0) next = atomicAdd(&s_round, 1);
+                        return uni(next);
+                    };
+                    if (apart) {
+                        prepare_next(s_ctx[now ^ 1]);
+                        round = next_round();
+                    }
+                    prepared |= last;
+                    for (; round < column_rounds; round = next_round()) {
+                        const int mine = 64 * round + lane;
+                        if (mine < n_here) {
+                            const double col = col_a[mine];
+                            const unsigned int r = col_range[mine];
+                            const int p0 = (int)(r & 255u), n = (int)(r >> 8 & 255u);
+                            const double even = COUNT ? 0.0 : (double)bpow[r >> 16], odd = __dmul_rn(even, beta);
+                            const double* zp = zpow + p0;
+                            const double u0 = two_l * (double)p0;
+                            // the first and the last four images, and, next to images that are walked apart, the second, may
+                            // lie outside the shell
+                            const int edges = near_item ? 3 : 2;
+#pragma unroll 1
+                            for (int e = 0; e < edges; ++e) {
+                                const int at = e == 0 ? 0 : e == 1 ? n : 1;
+                                if (e && n < e) break;
+                                const double z = COUNT ? 0.0 : zp[at];
+                                const int in = walk_step<COUNT, true>(c, regs, near_item, col, fma(two_l, (double)at, u0), z * even, z * odd, dropped8, hist);
+                                if (VISITS) walked += in;
+                            }
+                            int left = n + 1 - edges;
+                            if (left > 0) {
+                                if (VISITS) walked += 4 * left;
+                                zp += edges - 1;
+                                double u = fma(two_l, (double)(edges - 1), u0);
+                                do {
+                                    const double z = COUNT ? 0.0 : *zp++;
+                                    walk_step<COUNT, false>(c, regs, false, col, u, z * even, z * odd, 0u, hist);
+                                    u += two_l;
+                                } while (--left > 0);
+                            }
+                        }
+                    }
+                    if (last && near_item) {
+                        const NearImages near(c);
+                        for (; 64 * (round - column_rounds) < near.n; round = next_round()) {
+                            const int i = 64 * (round - column_rounds) + lane;
+                            if (i < near.n) {
+                                const unsigned int in = walk_near(c, near.n_near, near.n_y, near.n_p, i, ykey, ycount, bpow, zpow, hist);
+                                if (VISITS) walked += in;
+                            }
+                        }
+                    }
+                    walked_to += kColumns;
+                } while (walked_to < n_live);
+            }
+        } else if (kind == kPlain) {
+            walked += walk_plain<COUNT>(c, bpow, hist);
+        }
+        if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1]);
     }
     if (VISITS) {
         for (int off = 32; off > 0; off >>= 1) walked += __shfl_down(walked, off, 64);
@@ -989,9 +1184,9 @@ hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const Rooms& 
     const int per_rir = rir_items_per_response(rir_len);
     Item* sorted = static_cast<Item*>(items);
     Item* unsorted = sorted + (size_t)n_rir * per_rir;
-    if (n_rir <= kPlanRows * kPlanThreads) {                 // one launch instead of four
+    if (n_rir <= kPlanMost) {                                // one launch instead of four
         rir_plan_all_kernel<<<dim3(1), dim3(kPlanThreads), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, sorted, unsorted,
-                                                                    per_rir, ctrl, n_groups);
+                                                                    ctrl, n_groups);
         return hipGetLastError();
     }
     hipError_t e = launch_fill_u32(s, ctrl, 0u, kCtrlInts);
@@ -999,7 +1194,7 @@ hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const Rooms& 
     rir_work_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, ctrl);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    rir_plan_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, unsorted, per_rir, ctrl,
+    rir_plan_kernel<<<dim3((n_rir + 127) / 128), dim3(128), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, unsorted, ctrl,
                                                                     n_groups);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

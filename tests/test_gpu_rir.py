@@ -179,3 +179,28 @@ def test_symmetric_geometry_with_tied_distances(aug):
                   [4.0, 4.0, 3.0, 2.0, 2.0, 1.5, 2.0, 2.0, 1.0, 0.5]], np.float32)
     print("case: symmetric rooms, L=3000", flush=True)
     _check(aug, g, 3000)
+
+
+@pytest.mark.parametrize("fs,length", [(500.0, 1), (500.0, 200), (16000.0, 1), (16000.0, 700), (16000.0, 1700), (16000.0, 7000)])
+def test_edges_of_the_walk_along_z(aug, fs, length):
+    """Either side of what the walk in steps of 2 L takes: heights around a quarter of a tap and 16384 taps, walls so close that an
+    axis has more images than the tables hold, and positions on floor and ceiling (lists of images that fall together, the
+    mirror image at distance zero)."""
+    import torch
+    z = []
+    for h in (0.1, 0.1714, 0.1716, 0.3, 2.9, 351.0, 351.5, 1e4):
+        for s, m in ((0.37, 0.62), (0.0, 0.0), (1.0, 1.0), (0.0, 1.0), (0.5, 0.5)):
+            z.append((h, s, m))
+    floor = 7.0 * max(1.0, length * 16000.0 / fs / 2000.0)
+    rows = [[5 * floor, 4 * floor, h, 1.1, 1.3, s * h, 3.2, 2.1, m * h, 0.85] for h, s, m in z if h >= 2.9 or length <= 1700]
+    rows += [[w, 3 * floor, 2.4 * floor, 0.4 * w, 1.3, 1.0, 0.7 * w, 2.1, 1.4, 0.9] for w in (0.1, 0.12, 0.15, 0.3)]
+    rows += [[3 * floor, w, 2.4 * floor, 1.3, 0.4 * w, 1.0, 2.1, 0.7 * w, 1.4, 0.9] for w in (0.1, 0.12, 0.15, 0.3)]
+    geom = np.asarray(rows, np.float32)
+    print(f"case: edges of the z walk, fs={fs} L={length}", flush=True)
+    h = torch.full((len(rows), length), float("nan"), device="cuda")
+    cnt = torch.full((len(rows), length), -7, dtype=torch.int32, device="cuda")
+    aug.aug_rir_batch(dev(geom), length, fs, C, h, cnt)
+    torch.cuda.synchronize()
+    h_ref, cnt_ref = O.rir_batch(geom, length, fs, C)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
+    assert rir_err(h.cpu().numpy(), h_ref) <= RIR_TOL
