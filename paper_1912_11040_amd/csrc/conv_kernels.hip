@@ -3,7 +3,8 @@
 // y_j[n] = sum_{k < L} h_j[k] x_j[n-k] is evaluated by uniformly partitioned
 // overlap-save: the response is cut into partitions of P taps, each transformed once
 // (2P-point real FFT); an output block of P samples is the inverse transform of
-// sum_p X_{b-p} H_p, X_w the transform of input samples [(w-1)P, (w+1)P).
+// sum_p X_{b-p} H_p, X_w the transform of input samples [(w-1)P, (w+1)P).  Where one partition holds the response,
+// a window gives more than its last P samples, and the blocks are as long as that (see conv_plan).
 // A 2P-point real transform is run as a P-point complex FFT of the even/odd packed
 // sequence, entirely in LDS, split as 16 x P/16: the radix-16 column step reads its inputs
 // straight from HBM (and, inverse, writes the block straight back); the 16 row transforms
@@ -190,78 +191,102 @@ struct ConvBlock {
     double* energy;          // E[u][j]
     int len;                 // samples of the utterance
     int first;               // first non-zero tap of the response
-    int b;                   // block index: outputs [b N, (b+1) N)
+    int b;                   // block index: rows [b rows, (b+1) rows) of the utterance are its outputs (see window_row)
 };
 
-// The window of block wb, samples [(wb-1) N, (wb+1) N) of the utterance, as the inputs of the column step:
-// v[n1] = (x[2n], x[2n+1]), n = tid + M n1.  Block wb - 1 is a whole block of the utterance or (wb = 0) lies
-// before its start; block wb is whole except at the utterance's end.  Whole blocks are read with two-sample
-// loads and nothing to test, the same for every thread of the group.
-template <int N>
-__device__ inline void load_window(float2 (&v)[16], const float* x, int len, int wb, int tid) {
+// Rows: the 2 N samples of a window in sixteenths, row n1 in v[n1] (two samples per thread).  A block's outputs are the
+// last `rows` rows of its window, those that no tap reaches from beyond its start, and block b + 1 begins that many rows
+// later; so window and outputs of block b are the rows window_row(b, rows) + n1 of the utterance.
+__device__ inline int window_row(int b, int rows) { return (b + 1) * rows - 16; }
+
+// The window from row `row`, as the inputs of the column step: v[n1] = (x[2n], x[2n+1]), n = tid + M n1; zeros before the
+// utterance and past its end.  Only a window that reaches past the end tests its samples: what a branch loads without looking
+// at it stays on its way behind the transform that follows.  ROWS as in convolve_inplace_kernel: of a window whose block has eight
+// rows, the first eight are a whole block of the utterance or lie before it.
+template <int N, int ROWS>
+__device__ inline void load_window(float2 (&v)[16], const float* x, int len, int row, int tid) {
     constexpr int M = N / 16;
+    const int from = row * (2 * M);                        // (signals are shorter than 2^30 samples)
+    const float* at = x + from;
     const uint32_t lane_off = 8u * (uint32_t)tid;
-    if (wb >= 1) {
-        const float* blk = x + (size_t)(wb - 1) * N;
-#pragma unroll
-        for (int n1 = 0; n1 < 8; ++n1) {
-            const SamplePair s2 = load_pair(blk + 2 * M * n1, lane_off);
+    auto whole_row = [&](int n1) {                         // (the same for all threads)
+        if (n1 < 8 && row + (ROWS == 8 ? 0 : n1) < 0) {    // (the last eight rows are never before the utterance)
+            v[n1] = make_float2(0.f, 0.f);
+        } else {
+            const SamplePair s2 = load_pair(at + 2 * M * n1, lane_off);
             v[n1] = make_float2(s2.x, s2.y);
         }
-    } else {
+    };
+    if (from + 32 * M <= len) {
 #pragma unroll
-        for (int n1 = 0; n1 < 8; ++n1) v[n1] = make_float2(0.f, 0.f);
-    }
-    const float* blk = x + (size_t)wb * N;
-    if ((wb + 1) * (int64_t)N <= len) {
+        for (int n1 = 0; n1 < 16; ++n1) whole_row(n1);
+    } else if (ROWS == 8 || len < 2) {
+        // addresses are clamped to the utterance's samples, values outside it are zero
+        constexpr int kTested = ROWS == 8 ? 8 : 0;
 #pragma unroll
-        for (int n1 = 8; n1 < 16; ++n1) {
-            const SamplePair s2 = load_pair(blk + 2 * M * (n1 - 8), lane_off);
-            v[n1] = make_float2(s2.x, s2.y);
+        for (int n1 = 0; n1 < kTested; ++n1) whole_row(n1);
+#pragma unroll
+        for (int n1 = kTested; n1 < 16; ++n1) {
+            const int g = from + 2 * M * n1 + 2 * tid, low = n1 < 8 ? max(g, 0) : g;
+            const float x0 = load_sample(x, 4u * (uint32_t)min(low, len - 1));
+            const float x1 = load_sample(x, 4u * (uint32_t)min(low + 1, len - 1));
+            v[n1] = make_float2(g < len && (n1 >= 8 || g >= 0) ? x0 : 0.f, g + 1 < len && (n1 >= 8 || g >= 0) ? x1 : 0.f);
         }
     } else {
-        // the utterance ends inside this block: addresses are clamped to its last sample, values past it are zero
-        const int left = len - wb * N;                     // 1 .. N - 1 samples of this block exist
+        // any row may be the one that the end cuts: pairs clamped to the utterance's last, whose second sample is then the one
+        // wanted (sixteen loads, not 32: 96 signals with 12001 taps 155 us, not 159)
 #pragma unroll
-        for (int n1 = 8; n1 < 16; ++n1) {
-            const int g = 2 * tid + 2 * M * (n1 - 8);
-            const float x0 = load_sample(blk, 4u * (uint32_t)min(g, left - 1));
-            const float x1 = load_sample(blk, 4u * (uint32_t)min(g + 1, left - 1));
-            v[n1] = make_float2(g < left ? x0 : 0.f, g + 1 < left ? x1 : 0.f);
+        for (int n1 = 0; n1 < 16; ++n1) {
+            const SamplePair s2 = load_pair(x, 4u * (uint32_t)min(max(from + 2 * M * n1 + 2 * tid, 0), len - 2));
+            v[n1] = make_float2(s2.x, s2.y);
+        }
+#pragma unroll
+        for (int n1 = 0; n1 < 16; ++n1) {
+            const int r = from + 2 * M * n1, g = r + 2 * tid;
+            if (r >= 0 && r + 2 * M <= len) continue;      // (the same for all threads)
+            asm volatile("");                              // a branch, not selects in every row: those took 1 us a window
+            const float first = g == len - 1 ? v[n1].y : v[n1].x;
+            v[n1] = make_float2(g >= 0 && g < len ? first : 0.f, g >= 0 && g + 1 < len ? v[n1].y : 0.f);
         }
     }
 }
 
-// The outputs of a block, v[8 + i] = (y[n], y[n+1]) with n = b N + 2 tid + 2 M i, go to HBM; returns the
+// The outputs of a block, v[n1] = (y[n], y[n+1]) in its last rows (see window_row), go to HBM; returns the
 // lane's share of the block's energy.  Samples before the response's first non-zero tap are exact zeros
 // (the transforms leave rounding noise there, which the power law of the front end would magnify).
-template <int N>
-__device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, int tid) {
+// ROWS: the number of rows where it is fixed, 0: `rows`, at least 8.
+template <int N, int ROWS>
+__device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, int rows, int tid) {
     constexpr int M = N / 16;
-    float* yb = c.y + (size_t)c.b * N;
-    const int first = c.first - c.b * N;                   // first live sample of this block (may be <= 0)
-    const int left = c.len - c.b * N;                      // samples of this block inside the utterance
-    float e = 0.f;
-    if (left >= N && first <= 0) {                         // whole and live: eight two-sample stores
+    if (ROWS) rows = ROWS;
+    const int row = window_row(c.b, rows);
+    float* yb = c.y + (int64_t)row * (2 * M);              // (row 0 of the window, which may lie before the utterance)
+    const int first = min(c.first, c.len) - row * (2 * M); // first live sample (a silent response has none: its first tap is 2^31 - 1)
+    const int left = c.len - row * (2 * M);                // samples up to the utterance's end
+    constexpr int kFrom = ROWS ? 16 - ROWS : 0;
+    float e[2] = {0.f, 0.f};                               // (of sixteen squares each, however many rows there are)
+    if (left >= 32 * M && first <= (16 - rows) * (2 * M)) {     // whole and live: two-sample stores
         char* dst = reinterpret_cast<char*>(yb) + 8u * (uint32_t)tid;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
+        for (int n1 = kFrom; n1 < 16; ++n1) {
+            if (n1 < 8 && n1 < 16 - rows) continue;
             SamplePair s2;
-            s2.x = v[8 + i].x;
-            s2.y = v[8 + i].y;
-            *reinterpret_cast<SamplePair*>(dst + 8 * M * i) = s2;
-            e += s2.x * s2.x + s2.y * s2.y;
+            s2.x = v[n1].x;
+            s2.y = v[n1].y;
+            *reinterpret_cast<SamplePair*>(dst + 8 * M * n1) = s2;
+            e[n1 / 8] += s2.x * s2.x + s2.y * s2.y;
         }
     } else {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int g = 2 * tid + 2 * M * i;
-            const float s0 = g >= first ? v[8 + i].x : 0.f, s1 = g + 1 >= first ? v[8 + i].y : 0.f;
-            if (g < left) { yb[g] = s0; e += s0 * s0; }
-            if (g + 1 < left) { yb[g + 1] = s1; e += s1 * s1; }
+        for (int n1 = kFrom; n1 < 16; ++n1) {
+            if (n1 < 8 && n1 < 16 - rows) continue;
+            const int g = 2 * tid + 2 * M * n1;
+            const float s0 = g >= first ? v[n1].x : 0.f, s1 = g + 1 >= first ? v[n1].y : 0.f;
+            if (g < left) { yb[g] = s0; e[n1 / 8] += s0 * s0; }
+            if (g + 1 < left) { yb[g + 1] = s1; e[n1 / 8] += s1 * s1; }
         }
     }
-    return e;
+    return e[0] + e[1];
 }
 
 // Work groups are persistent and take their blocks from the list of all blocks ordered by (utterance, source, block).
@@ -332,11 +357,11 @@ struct ConvWalk {
     }
 };
 
-// Responses of up to 2048 taps: transforms in natural order.  While a block's
+// Responses of up to 2048 taps: transforms in natural order (ROWS as in convolve_inplace_kernel).  While a block's
 // inverse transform runs, the inputs of the next block are already on their way from HBM, and the response
 // spectrum is requested before the forward row transforms that precede its use: the loads' latency is
 // hidden behind arithmetic instead of being paid at either end of a short-lived group.
-template <int N, int T>
+template <int N, int T, int ROWS>
 __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* __restrict__ tw) {
     extern __shared__ float2 buf[];
     __shared__ double red[(T + 63) / 64];
@@ -355,7 +380,8 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
     if (walk.at >= walk.end) return;
     ConvBlock cur = walk.describe(N + 1);
     float2 v[16];
-    load_window<N>(v, cur.x, cur.len, cur.b, tid0);
+    const int rows = ROWS ? ROWS : a.rows;
+    load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, rows), tid0);
 
     for (;;) {
         // The thread index is made opaque in every round so that twiddle powers and addresses are not
@@ -410,7 +436,7 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         if (more) {
             walk.next();
             nxt = walk.describe(N + 1);
-            load_window<N>(v, nxt.x, nxt.len, nxt.b, tid);
+            load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, rows), tid);
         } else {
             // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
 #pragma unroll
@@ -422,7 +448,7 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         float2 o[16];
         fft_columns_load<N, T>(o, buf, tid);
         fft_columns_inverse<N>(o, tw, tid);
-        const float e = store_block<N>(o, cur, tid);
+        const float e = store_block<N, ROWS>(o, cur, rows, tid);
 
         float es = e;                                      // a wave's 1024 squares in fp32, the rest in fp64
         for (int off = 32; off > 0; off >>= 1) es += __shfl_down(es, off, 64);
@@ -553,7 +579,8 @@ __global__ __launch_bounds__(InPlace<N>::T) void rir_spectrum_inplace_kernel(
 // registers, so a block still costs one forward and one inverse transform (plus one forward transform at the start of a
 // group's share).  The kept spectrum takes the registers that the single-partition kernel spends on inputs requested
 // ahead of time; they are then loaded where they are used.
-template <int N, bool MULTI>
+// ROWS: a block's rows where they are fixed (8: half of the last step's outputs are then never formed), 0: any.
+template <int N, bool MULTI, int ROWS>
 __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArgs a, const float* __restrict__ tab) {
     using P = InPlace<N>;
     constexpr int T = P::T, RD = P::RD;
@@ -576,7 +603,8 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         for (int i = 0; i < 8; ++i) prev_a[i] = prev_b[i] = make_float2(0.f, 0.f);
         have_prev = cur.b == 0;     // the window before the first block is all zeros, and so is its spectrum
     }
-    if (AHEAD) load_window<N>(v, cur.x, cur.len, cur.b, tid0);
+    const int rows = ROWS ? ROWS : a.rows;
+    if (AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, rows), tid0);
     double* done_energy = nullptr;  // where the energies in red[parity ^ 1] belong
     int parity = 0;
     // the energy of the block before this one: a wavefront's 1024 squares in fp32, the rest in fp64
@@ -594,7 +622,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         int tid = tid0;
         asm volatile("" : "+v"(tid));
         const bool warm_up = MULTI && !have_prev;          // this pass only produces the spectrum of window b - 1
-        if (!AHEAD) load_window<N>(v, cur.x, cur.len, warm_up ? cur.b - 1 : cur.b, tid);
+        if (!AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(warm_up ? cur.b - 1 : cur.b, rows), tid);
 
         inplace_forward_ab<N>(v, buf, lds_tab, tid);
         flush_energy(tid);
@@ -675,7 +703,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         if (more) {
             walk.next();
             nxt = walk.describe(2 * kEntries);
-            if (AHEAD) load_window<N>(v, nxt.x, nxt.len, nxt.b, tid);
+            if (AHEAD) load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, rows), tid);
         } else if (AHEAD) {
             // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
 #pragma unroll
@@ -685,7 +713,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         float2 o[16];
         const Tw16Short w{{wa[0].x, wa[0].y, wa[0].z, wa[0].w, wa[1].x, wa[1].y}, {wa[1].z, wa[1].w, wa[2].x, wa[2].y, wa[2].z, wa[2].w}};
         inplace_inverse<N>(o, buf, lds_tab, tid, w);
-        const float e = store_block<N>(o, cur, tid);
+        const float e = store_block<N, ROWS>(o, cur, rows, tid);
 
         float es = e;
         for (int off = 32; off > 0; off >>= 1) es += __shfl_down(es, off, 64);
@@ -820,16 +848,19 @@ hipError_t convolve_n(hipStream_t s, const float2* tw, const ConvArgs& a, int n_
     void* args[] = {&by_value, &tw};
     if constexpr (in_place(N)) {
         // responses longer than one partition exist only at the largest transform size (conv_fft_size)
-        const void* k = reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false>);
+        const void* k = a.rows == 8 ? reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false, 8>)
+                                    : reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false, 0>);
         if (a.n_part > 1) {
             if (N != 16384 || a.n_part != 2) return hipErrorInvalidValue;
-            k = reinterpret_cast<const void*>(&convolve_inplace_kernel<16384, true>);
+            k = reinterpret_cast<const void*>(&convolve_inplace_kernel<16384, true, 8>);
         }
         return launch_groups(s, k, n_cu, total, InPlace<N>::T, inplace_lds<N>(), args);
     } else {
         if (a.n_part > 1) return hipErrorInvalidValue;
         constexpr int T = conv_threads(N);
-        return launch_groups(s, reinterpret_cast<const void*>(&convolve_kernel<N, T>), n_cu, total, T,
+        const void* k = a.rows == 8 ? reinterpret_cast<const void*>(&convolve_kernel<N, T, 8>)
+                                    : reinterpret_cast<const void*>(&convolve_kernel<N, T, 0>);
+        return launch_groups(s, k, n_cu, total, T,
                              sizeof(float2) * (lds_padded_size(N) + RowTwiddles<N / 16>::kEntries + 16 + N / 32), args);
     }
 }

@@ -268,3 +268,35 @@ def test_utterances_that_end_as_a_source_arrives(aug):
                 assert ratio < 1e-9
         print(f"  seed {seed}: worst error / RMS among speech-like slivers {worst_ordinary:.2e}", flush=True)
         assert worst_ordinary <= 2e-4
+
+
+@pytest.mark.parametrize("L", [1, 2, 129, 130, 1025, 1793, 2049, 2561, 2562, 3585, 4097, 5121, 8193, 12001, 14337, 14338, 16384, 16385])
+def test_blocks_of_every_number_of_rows(aug, L):
+    """Response lengths where a block gains or loses a row of its window, signals that end around a row's and a block's end; the
+    responses' last tap is the largest, so that a row kept too many shows.  The last utterance's noise response is all zeros."""
+    n = 1024
+    while n < min(L, 16384):
+        n *= 2
+    row = n // 8
+    block = row * (8 if L > n else 16 - (L - 1 + row - 1) // row)
+    lens = [1, row - 1, row + 1, block - 1, block, block + 1, 2 * n - 1, 2 * n + 1, 2 * block + row, 3 * block - 1, 2 * block + 3]
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    rng = np.random.default_rng(L)
+    speech, noise = (rng.standard_normal(s).astype(np.float32) for s in (offsets[-1], (1, offsets[-1])))
+    rir = 0.3 * _decaying_rirs(rng, len(lens), 2, L)
+    rir[..., -1] = 3.0
+    rir[-1, 1] = 0.0
+    print(f"case: rows of a block, L={L}, block={block}", flush=True)
+    mixed, _ = _check(aug, offsets, speech, noise, rir.astype(np.float32), rng.uniform(0, 20, (len(lens), 1)).astype(np.float32), method="fft")
+
+
+@pytest.mark.parametrize("L,n_utt", [(3000, 256), (4096, 128), (4200, 256), (8000, 64)])
+def test_short_responses_that_take_the_largest_transform(aug, L, n_utt):
+    """Batches that fill the chip with the largest transform's blocks, where a smaller one would hold the response."""
+    rng = np.random.default_rng(L + n_utt)
+    lens = rng.integers(60000, 68001, n_utt)
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    speech = rng.standard_normal(offsets[-1]).astype(np.float32)
+    rir = _decaying_rirs(rng, n_utt, 1, L)
+    print(f"case: largest transform, L={L}, {n_utt} signals", flush=True)
+    _check(aug, offsets, speech, None, rir, None, method="fft")
