@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "b6f2fb3f932447b7",
-    "varlen": {"rir": 84529771, "rir_spectrum": 202477975, "convolve": 1256927984, "mel": 612817306},
-    "throughput": {"rir": 447095288, "rir_spectrum": 1218139929, "convolve": 13978578920, "mel": 2176123960},
+    "digest": "4d1ab659757896b2",
+    "varlen": {"rir": 73367900, "rir_spectrum": 202562709, "convolve": 1256413643, "mel": 612950226},
+    "throughput": {"rir": 424393514, "rir_spectrum": 1218383824, "convolve": 13979475224, "mel": 2175481205},
 }
 
 
