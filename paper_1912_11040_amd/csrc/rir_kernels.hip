@@ -696,13 +696,25 @@ __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool near_i
 // beta^k for reflection counts past the LDS table; out of line so that the double-precision pow does not
 // weigh on the register allocation of the loops that call it once in a long while
 __device__ __attribute__((noinline)) float beta_pow_slow(double beta, int k) { return (float)pow(beta, (double)k); }
+// beta^(2 p) / (4 pi) 2^56, of the same operations as the table of them in LDS
+__device__ __attribute__((noinline)) double z_power(double beta, int p) {
+    double v = 1.0;
+    for (int k = 2 * p; k; k >>= 1) {
+        if (k & 1) v *= beta;
+        beta *= beta;
+    }
+    return v * kAmplitude;
+}
 
-// Rows that the closed forms do not take (rooms too flat or narrow for the tables, positions far outside): every column of
+// Items that the closed forms do not take (rooms too flat or narrow for the tables, positions far outside): every column of
 // the bounding box, every z image of a live column, every tap tested.  Out of line for the same reason as the power.
+// Distance and amplitude of an image are formed as walk_step forms them, step for step: whether an item fits the tables
+// depends on where the batch's plan has cut the response, and the response must not.
 template <bool COUNT>
-__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, const float* bpow, unsigned long long* hist) {
+__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, const float* bpow, const double* zpow, unsigned long long* hist) {
     unsigned int walked = 0;
     const int nmx = w.nmx, nmy = w.nmy, nmz = w.nmz, niy = 2 * (2 * nmy + 1);
+    const bool below = w.az.src < w.az.mic, in_steps = axis_in_order(w.az);
     const long long n_columns = 2ll * (2 * nmx + 1) * niy;
     for (long long cand = threadIdx.x; cand < n_columns; cand += kThreads) {
         const int ix = (int)(cand / niy), iy = (int)(cand - (long long)ix * niy);
@@ -713,17 +725,26 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, c
         // (beyond the first shell the shell's own inner radius bounds the distance well enough)
         const int kz_max = (w.n0 > 0 ? w.k_cut : reflection_cut(w.inv_log2_beta, sqrtf((float)a))) - kxy;
         if (!(a < w.r_out2) || kz_max < 0) continue;
-        const double bxy = COUNT ? 0.0 : (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(w.beta, kxy)) * kAmplitude;
+        const double bxy = COUNT ? 0.0 : (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(w.beta, kxy));
         for (int q = 0; q < 2; ++q)
             for (int n = -nmz; n <= nmz; ++n) {
-                const double dz = axis_delta(w.az, q, n);
-                const double d2 = __dadd_rn(a, __dmul_rn(dz, dz));
+                // image (q, n) as element p of its list (see walk_step)
+                const bool up = q ? n > 0 : n && (n > 0) == below;
+                const int list = 2 * q + (int)up, p = up ? abs(n) - 1 : abs(n);
+                const double dz = axis_delta(w.az, q, n), recipe = __dadd_rn(a, __dmul_rn(dz, dz));
+                // (the recipe rounds positions far outside to less than the tap's guard allows: there it is what counts)
+                const double step = __dadd_rn(__dmul_rn(w.two_l, (double)p), w.begin[list]);
+                const double d2 = in_steps ? fma(step, step, a) : recipe;
                 const double y = __builtin_amdgcn_rsq(d2);
-                const int slot = tap_slot(w, d2, y, [&] { return d2; });
+                const int slot = tap_slot(w, d2, y, [&] { return recipe; });
                 if (8u * (unsigned int)slot > w.top8) continue;
-                double bz = 0.0;
-                if (!COUNT) bz = (double)beta_pow_slow(w.beta, reflections(q, n));
-                deposit<COUNT, false>(8u * (unsigned int)slot, __dmul_rn(bz, bxy), y, hist);
+                double amp = 0.0;
+                if (!COUNT) {
+                    const double z = p <= kMaxP ? zpow[p] : z_power(w.beta, p);
+                    amp = __dmul_rn(z, q ? __dmul_rn(bxy, w.beta) : bxy);
+                    if (list == 1) amp = __dmul_rn(amp, w.beta2);
+                }
+                deposit<COUNT, false>(8u * (unsigned int)slot, amp, y, hist);
                 ++walked;
             }
     }
@@ -1147,7 +1168,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 } while (walked_to < n_live);
             }
         } else if (kind == kPlain) {
-            walked += walk_plain<COUNT>(c, bpow, hist);
+            walked += walk_plain<COUNT>(c, bpow, zpow, hist);
         }
         if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1]);
     }

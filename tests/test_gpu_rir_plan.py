@@ -48,3 +48,32 @@ def test_batch_sizes(aug, n, length, side):
     h_ref, cnt_ref = O.rir_batch(g[rows], length, FS, C)
     np.testing.assert_array_equal(cnt.cpu().numpy()[rows], cnt_ref)
     assert rir_err(h.cpu().numpy()[rows], h_ref) <= RIR_TOL
+
+
+@pytest.mark.parametrize("dims", [(3.0, 2.0, 0.1), (0.1, 2.5, 3.0), (2.5, 0.1, 3.0), (0.15, 1.5, 0.12)])
+@pytest.mark.parametrize("length", [1600, 2300])
+def test_rooms_that_fit_the_tables_in_part(aug, dims, length):
+    """Rooms so flat or narrow that the outer shells have more images along an axis than the tables hold and the inner ones have
+    not.  Alone in a call a response is cut into many shells, in the batch into one or two: the same bits."""
+    import torch
+    n, rng = 400, np.random.default_rng(length)
+    room = np.tile(np.array(dims), (n, 1)) * rng.uniform(1.0, 1.05, (n, 3))
+    g = np.concatenate([room, room * rng.uniform(0.05, 0.95, (n, 3)), room * rng.uniform(0.05, 0.95, (n, 3)),
+                        rng.choice([0.1, 0.5, 0.9, 1.0], (n, 1))], 1).astype(np.float32)
+    g[0] = [*dims, *(0.25 * np.array(dims)), *(0.75 * np.array(dims)), 1.0]
+    print(f"case: {dims}, {length} taps", flush=True)
+    d = dev(g)
+    h = torch.full((n, length), float("nan"), dtype=torch.float32, device="cuda")
+    cnt = torch.full((n, length), -7, dtype=torch.int32, device="cuda")
+    aug.aug_rir_batch(d, length, FS, C, h, cnt)
+    rows = [0, 1, 2, 3, 4, 200, n - 1]
+    alone = torch.full((len(rows), length), float("nan"), dtype=torch.float32, device="cuda")
+    cnt_alone = torch.full((len(rows), length), -7, dtype=torch.int32, device="cuda")
+    for i, r in enumerate(rows):
+        aug.aug_rir_batch(d[r:r + 1].contiguous(), length, FS, C, alone[i:i + 1], cnt_alone[i:i + 1])
+    torch.cuda.synchronize()
+    assert torch.equal(h[rows], alone) and torch.equal(cnt[rows], cnt_alone)
+    head = 400                                            # (a response's first taps do not depend on its length)
+    h_ref, cnt_ref = O.rir_batch(g[rows], head, FS, C)
+    np.testing.assert_array_equal(cnt.cpu().numpy()[rows, :head], cnt_ref)
+    assert rir_err(h.cpu().numpy()[rows, :head], h_ref) <= RIR_TOL
