@@ -1029,7 +1029,9 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             // Columns are worked through a chunk at a time.  Each thread describes kPerThread candidates (the wavefronts'
             // stretches of 64 side by side, so that a wavefront's rows only move up); the live ones are sorted by length,
             // in LDS, and taken 64 at a time, longest first, from a counter.
-            for (int base = 0, parity = 0; base < n_cand; base += kChunk, parity ^= 1) {
+            // (The images near the microphone are walked in the last go of the last chunk.  An item that has such images takes one
+            // chunk also where the gaps leave it no column: they remove the columns whose images all lie that near.)
+            for (int base = 0, parity = 0; base < n_cand || (base == 0 && near_item); base += kChunk, parity ^= 1) {
                 double a[kPerThread];
                 unsigned int range[kPerThread];
                 int place[kPerThread];                    // length << 16 | number among those of that length, -1: not live
