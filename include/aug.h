@@ -169,6 +169,12 @@ int aug_rir_mics_batch(aug_ctx* ctx, int n_rir, int n_mic, const float* geom, co
  *               zeros (the transforms alone would leave rounding noise
  *               there), so a source whose direct path arrives after the
  *               utterance has ended has energy 0 and gain 0.
+ *               Elsewhere an exact zero (a pause of digital silence) may
+ *               hold rounding noise, some 1e-7 of the loudest y_j nearby, up
+ *               to 2 P samples away from any x_j[n] != 0 and not farther (behind
+ *               it 3 P where rir_len > 16384): P is the power of two from 1024
+ *               to 16384 that is the smallest >= rir_len, or 16384.  y_j does
+ *               not depend on the other utterances of the call.
  *   gains_out   DEVICE float [n_utt][n_noise] or NULL: the g_j.  May be snr_db.
  */
 int aug_convolve_mix_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets,

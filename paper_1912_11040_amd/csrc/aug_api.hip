@@ -394,7 +394,7 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
     const int64_t total = ctx->packing.offsets[n_utt];
     if (n_utt == 0 || total == 0) return AUG_OK;
     const int n_src = 1 + n_noise;
-    const aug::ConvPlan plan = aug::conv_plan(rir_len, n_utt, total, ctx->n_cu);
+    const aug::ConvPlan plan = aug::conv_plan(rir_len);
     const int fft_n = plan.fft_n;
     const int n_part = (rir_len + fft_n - 1) / fft_n;
     AUG_TRY(grow(ctx, ctx->rir_spec, sizeof(float2) * (size_t)n_utt * n_src * n_part * aug::conv_spectrum_entries(fft_n), "spectrum workspace"));
@@ -453,7 +453,7 @@ int run_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, const float* speech, 
     const aug::Packing& pk = ctx->packing;
     const int64_t total = pk.offsets[n_utt];
     const int n_src = 1 + n_noise;
-    const aug::ConvPlan plan = aug::conv_plan(rir_len, n_utt, total, ctx->n_cu);
+    const aug::ConvPlan plan = aug::conv_plan(rir_len);
     const int fft_n = plan.fft_n;
     const int n_part = (rir_len + fft_n - 1) / fft_n;
     const float2* tw = nullptr;
@@ -770,7 +770,7 @@ int aug_convolve_mix_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, cons
     if ((!rir && n_utt > 0) || (!mixed_out && offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "rir or mixed_out is null");
     PendingPack pending(ctx);
-    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, aug::conv_plan(rir_len, n_utt, offsets[n_utt], ctx->n_cu).block(), 0));
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, aug::conv_plan(rir_len).block(), 0));
     AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
     AUG_TRY(pending.launch());
     return run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out);
@@ -923,7 +923,7 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((int64_t)n_utt * n_src * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
     PendingPack pending(ctx);
-    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_plan(rir_len, n_utt, offsets[n_utt], ctx->n_cu).block(),
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_plan(rir_len).block(),
                          aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt])));
     const int64_t total = offsets[n_utt];
     float* rir = rir_out;

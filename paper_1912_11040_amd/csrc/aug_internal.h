@@ -4,8 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
-#include <cmath>
 #include <string>
 #include <utility>
 #include <vector>
@@ -154,39 +152,17 @@ int conv_fft_size(int rir_len);
 // Size of the convolution's transforms (N complex points) and outputs per block, in rows of N / 8 samples: of the sixteen
 // rows of a window those that no tap reaches from beyond its start, 8 .. 16.  (12001 taps at N = 16384 leave ten: three sources
 // of 96 signals took 139 us with eight rows at every length, 120 now.)
+// Both follow from the response's length alone, so that a signal's reverberation does not depend on the batch it is in, and
+// the window is the smallest that there is: a transform spreads its rounding error over its whole window, at the level of the
+// window's loudest part.  (The largest transform at every length that fills the chip took 256 signals of 64000 samples with 4096
+// taps from 189 us to 158, and put 1.8e-7 of the loud part where 3.7e-8 had been in a pause 8000 samples behind it.)
 struct ConvPlan {
     int fft_n, rows;
     int block() const { return rows * (fft_n / 8); }
 };
-inline ConvPlan conv_plan_at(int rir_len, int fft_n) {
-    const int row = fft_n / 8;
+inline ConvPlan conv_plan(int rir_len) {
+    const int fft_n = conv_fft_size(rir_len), row = fft_n / 8;
     return {fft_n, rir_len > fft_n ? 8 : 16 - (rir_len - 1 + row - 1) / row};      // more than one partition: whole blocks of N
-}
-
-// The smallest transform that holds the response or, for signals that fill the chip all the same, the largest: with a response
-// much shorter than its window a block has up to 28672 outputs for 17 us of a compute unit.  Measured, microseconds per round of as many groups as the chip holds at once: 4096 points 15,
-// 8192 points 11, 16384 points 17; more bytes of spectra at 4 TB/s, and 3 us.  Whole calls for 64 signals of 64000 samples with
-// 8000 taps and two sources: 67 us at 8192 points, 55 at 16384; 256 of them, 4096 taps: 192 at 4096, 158.  Over 189 batches
-// (1100 to 8000 taps, 32 to 512 signals of 12000 to 200000 samples, one to three sources) no choice lost and the largest was
-// up to a quarter faster where it is chosen.  Up to 2048 points it gains too little to choose it: 1500 taps 0.97 to 2.1 times.
-// Its rounding error is no larger: relative to the signal 2.15e-7 rms against 2.26e-7 at 8000 taps.
-// The choice depends on the response length and the offsets only, as does the table of blocks that goes with it, and not on the
-// number of sources; so it has to pay at two, and not to lose at one, three or four (more make it smoother still).  The rounds of
-// the small transforms count as shares and the large one's whole: where the chip is not full, the small ones' groups run
-// faster.
-inline ConvPlan conv_plan(int rir_len, int n_utt, int64_t total, int n_cu) {
-    const ConvPlan small = conv_plan_at(rir_len, conv_fft_size(rir_len));
-    if (small.fft_n < 4096 || small.fft_n == 16384) return small;
-    const ConvPlan large = conv_plan_at(rir_len, 16384);
-    const int per_cu = small.fft_n == 4096 ? 3 : 1;
-    const double round_us = small.fft_n == 4096 ? 15.0 : 11.0, spectrum_us = 2e-6 * (16384 - small.fft_n);
-    auto rounds = [&](const ConvPlan& p, int sources, int groups) { return sources * ((double)total / p.block() + 0.5 * n_utt) / groups; };
-    for (int sources = 1; sources <= 4; ++sources) {
-        const double small_us = round_us * std::max(rounds(small, sources, n_cu * per_cu), 0.5);
-        const double large_us = 17.0 * std::ceil(rounds(large, sources, n_cu)) + 3.0 + spectrum_us * n_utt * sources;
-        if (large_us > (sources == 2 ? 0.95 : 1.0) * small_us) return small;
-    }
-    return large;
 }
 
 // The tables that the transforms of that size read (float2 [conv_table_entries(fft_n)]), and the size of a partition's

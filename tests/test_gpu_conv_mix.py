@@ -291,12 +291,50 @@ def test_blocks_of_every_number_of_rows(aug, L):
 
 
 @pytest.mark.parametrize("L,n_utt", [(3000, 256), (4096, 128), (4200, 256), (8000, 64)])
-def test_short_responses_that_take_the_largest_transform(aug, L, n_utt):
-    """Batches that fill the chip with the largest transform's blocks, where a smaller one would hold the response."""
+def test_short_responses_in_batches_that_fill_the_chip(aug, L, n_utt):
+    """Batches of several rounds of groups, with responses much shorter than the signals."""
     rng = np.random.default_rng(L + n_utt)
     lens = rng.integers(60000, 68001, n_utt)
     offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     speech = rng.standard_normal(offsets[-1]).astype(np.float32)
     rir = _decaying_rirs(rng, n_utt, 1, L)
-    print(f"case: largest transform, L={L}, {n_utt} signals", flush=True)
+    print(f"case: full chip, L={L}, {n_utt} signals", flush=True)
     _check(aug, offsets, speech, None, rir, None, method="fft")
+
+
+@pytest.mark.parametrize("L,n_utt", [(100, 8), (1100, 8), (2049, 256), (4096, 256), (8000, 64), (8193, 8), (12001, 8), (16385, 8)])
+def test_pauses_and_neighbours(aug, L, n_utt):
+    """Bursts between digital silences.  What the transforms leave in the silences reaches no farther than aug.h says and is as
+    small there as rounding makes it, and a signal comes out of a batch with the bits that it has alone."""
+    p = 1024
+    while p < min(L, 16384):
+        p *= 2
+    reach = 2 * p if L <= p else 3 * p
+    rng = np.random.default_rng(L)
+    lens = np.maximum(64000, 7 * p) + rng.integers(0, 2000, n_utt)
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    onset, burst = rng.integers(2 * p, 3 * p, n_utt), rng.integers(p // 8, p // 2, n_utt)
+    speech = np.zeros(offsets[-1], np.float32)
+    for u in range(n_utt):
+        a = offsets[u] + onset[u]
+        speech[a:a + burst[u]] = rng.standard_normal(burst[u])
+    rir = _decaying_rirs(rng, n_utt, 1, L)
+    print(f"case: pauses, L={L}, {n_utt} signals", flush=True)
+    mixed, _ = _run(aug, offsets, speech, None, rir, None)
+    worst = 0.0
+    for u in range(n_utt):
+        y, end = mixed[offsets[u]:offsets[u + 1]].astype(np.float64), onset[u] + burst[u]
+        assert not y[:max(onset[u] - reach + 1, 0)].any() and not y[end - 1 + reach:].any(), u
+        # a transform of 2p points in single precision: an error of log2(2p) roundings at most of a spectrum's norm, twice
+        # (forward and inverse) and that of the response's, spread evenly over the window (three windows at most hold a burst)
+        level = np.sqrt(burst[u]) * np.linalg.norm(rir[u, 0].astype(np.float64)) / np.sqrt(2 * p)
+        bound = 3 * 2.0 ** -24 * np.log2(2 * p) * level
+        for pause in (y[max(onset[u] - reach + 1, 0):onset[u]], y[end - 1 + L:end - 1 + reach]):
+            if pause.size:
+                worst = max(worst, np.sqrt(np.mean(pause ** 2)) / bound)
+    print(f"  rounding in the pauses, of its bound: {worst:.2f}", flush=True)
+    assert worst <= 1.0
+    for u in (0, 1, n_utt // 2, n_utt - 1):
+        a, b = offsets[u], offsets[u + 1]
+        alone, _ = _run(aug, np.array([0, b - a], np.int64), speech[a:b], None, rir[u:u + 1], None)
+        np.testing.assert_array_equal(alone, mixed[a:b])
