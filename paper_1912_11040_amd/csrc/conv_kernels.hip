@@ -264,7 +264,7 @@ __device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, i
     const int first = min(c.first, c.len) - row * (2 * M); // first live sample (a silent response has none: its first tap is 2^31 - 1)
     const int left = c.len - row * (2 * M);                // samples up to the utterance's end
     constexpr int kFrom = ROWS ? 16 - ROWS : 0;
-    float e[2] = {0.f, 0.f};                               // (of sixteen squares each, however many rows there are)
+    float e[2] = {0.f, 0.f};                               // (chains of sixteen squares, however many rows there are)
     if (left >= 32 * M && first <= (16 - rows) * (2 * M)) {     // whole and live: two-sample stores
         char* dst = reinterpret_cast<char*>(yb) + 8u * (uint32_t)tid;
 #pragma unroll
@@ -287,6 +287,15 @@ __device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, i
         }
     }
     return e[0] + e[1];
+}
+
+// A wavefront's energy in lane 0: 1024 squares in fp32, however many rows a block has, the rest in fp64.  (Sixteen squares per
+// lane with eight rows, up to 32 with more: then the two halves of the wavefront are joined in fp64.)
+template <int ROWS>
+__device__ inline double wave_energy(float e) {
+    for (int off = ROWS == 8 ? 32 : 16; off > 0; off >>= 1) e += __shfl_down(e, off, 64);
+    if (ROWS == 8) return (double)e;
+    return (double)e + (double)__uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(e), 32));
 }
 
 // Work groups are persistent and take their blocks from the list of all blocks ordered by (utterance, source, block).
@@ -448,11 +457,8 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         float2 o[16];
         fft_columns_load<N, T>(o, buf, tid);
         fft_columns_inverse<N>(o, tw, tid);
-        const float e = store_block<N, ROWS>(o, cur, rows, tid);
-
-        float es = e;                                      // a wave's 1024 squares in fp32, the rest in fp64
-        for (int off = 32; off > 0; off >>= 1) es += __shfl_down(es, off, 64);
-        if ((tid & 63) == 0) red[tid >> 6] = (double)es;
+        const double es = wave_energy<ROWS>(store_block<N, ROWS>(o, cur, rows, tid));
+        if ((tid & 63) == 0) red[tid >> 6] = es;
         __syncthreads();                                   // also: every thread has read its columns from LDS
         if (tid == 0) {
             double tot = 0.0;
@@ -587,7 +593,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
     constexpr bool AHEAD = !MULTI;
     constexpr size_t kEntries = inplace_spectrum_entries<N>();
     extern __shared__ __align__(16) float2 buf[];
-    __shared__ float red[2][T / 64];                       // energies per wavefront of this block and the one before
+    __shared__ double red[2][T / 64];                      // energies per wavefront of this block and the one before
     float* const lds_tab = reinterpret_cast<float*>(buf + P::kPadded);
     const int tid0 = threadIdx.x;
     copy_tables<N>(lds_tab, tab, tid0);                    // (a barrier of the loop below comes before these are read)
@@ -607,11 +613,11 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
     if (AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, rows), tid0);
     double* done_energy = nullptr;  // where the energies in red[parity ^ 1] belong
     int parity = 0;
-    // the energy of the block before this one: a wavefront's 1024 squares in fp32, the rest in fp64
+    // the energy of the block before this one
     auto flush_energy = [&](int tid) {
         if (tid == 0 && done_energy) {
             double tot = 0.0;
-            for (int i = 0; i < T / 64; ++i) tot += (double)red[parity ^ 1][i];
+            for (int i = 0; i < T / 64; ++i) tot += red[parity ^ 1][i];
             atomicAdd(done_energy, tot);
         }
     };
@@ -713,10 +719,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         float2 o[16];
         const Tw16Short w{{wa[0].x, wa[0].y, wa[0].z, wa[0].w, wa[1].x, wa[1].y}, {wa[1].z, wa[1].w, wa[2].x, wa[2].y, wa[2].z, wa[2].w}};
         inplace_inverse<N>(o, buf, lds_tab, tid, w);
-        const float e = store_block<N, ROWS>(o, cur, rows, tid);
-
-        float es = e;
-        for (int off = 32; off > 0; off >>= 1) es += __shfl_down(es, off, 64);
+        const double es = wave_energy<ROWS>(store_block<N, ROWS>(o, cur, rows, tid));
         if ((tid & 63) == 0) red[parity][tid >> 6] = es;
         done_energy = cur.energy;
         parity ^= 1;
