@@ -204,3 +204,31 @@ def test_edges_of_the_walk_along_z(aug, fs, length):
     h_ref, cnt_ref = O.rir_batch(geom, length, fs, C)
     np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
     assert rir_err(h.cpu().numpy(), h_ref) <= RIR_TOL
+
+
+@pytest.mark.parametrize("fs,length", [(16000.0, 700), (16000.0, 7000), (16000.0, 32768), (48000.0, 20000)])
+def test_tall_rooms(aug, fs, length):
+    """Heights on either side of 16384 taps, up to 4e5 taps and beyond: images outside a shell lie so far from it that sixteen bits
+    of their slots come round.  Against the oracle, and in a batch (where a response is cut into other shells) the same bits."""
+    import torch
+    rng = np.random.default_rng(length)
+    rows = []
+    for taps in (16000, 16383, 16385, 24000, 32600, 32768, 33000, 49000, 65500, 65536, 66000, 131072, 390000, 410000):
+        h = taps * C / fs
+        for s, m in ((0.4, 0.41), (0.0, 0.0), (1.0, 0.999), (0.5, 0.5), (0.01, 0.02), (0.3, 0.7)):
+            w, d = rng.uniform(8.0, 30.0, 2)
+            rows.append([w, d, h, 0.3 * w, 0.6 * d, s * h, 0.7 * w, 0.2 * d, m * h, rng.choice([0.3, 0.8, 1.0])])
+    geom = np.asarray(rows, np.float32)
+    n = len(rows)
+    print(f"case: tall rooms, fs={fs} L={length}", flush=True)
+    h = torch.full((12 * n, length), float("nan"), device="cuda")
+    cnt = torch.full((n, length), -7, dtype=torch.int32, device="cuda")
+    aug.aug_rir_batch(dev(np.tile(geom, (12, 1))), length, fs, C, h)
+    alone = torch.full((n, length), float("nan"), device="cuda")
+    aug.aug_rir_batch(dev(geom), length, fs, C, alone, cnt)
+    torch.cuda.synchronize()
+    for k in range(12):
+        assert torch.equal(h[k * n:(k + 1) * n], alone)
+    h_ref, cnt_ref = O.rir_batch(geom, length, fs, C)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
+    assert rir_err(alone.cpu().numpy(), h_ref) <= RIR_TOL
