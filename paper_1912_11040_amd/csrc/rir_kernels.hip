@@ -522,6 +522,7 @@ struct ItemCtx {
     float inv_log2_beta;    // 0: no cut
     int near_item;          // images nearer than kNearMetres are walked apart
     int tested;             // the ends of columns drop what lies outside by its distance
+    int edges;              // steps of a column that may hold images outside the shell: its first, last, second, last but one, ...
 
     // taps
     double k_fs_c;
@@ -623,8 +624,9 @@ __device__ inline void deposit(unsigned int slot8, double a, double y, unsigned 
 // from the microphone's plane (L the room's height, s and m the heights of source and microphone):
 //   list 0: |s - m|,        2 p reflections       list 2: s + m,        2 p + 1
 //   list 1: 2 L - |s - m|,  2 p + 2               list 3: 2 L - (s + m), 2 p + 1
-// (for 0 <= s + m <= 2 L and |s - m| <= 2 L, so that every list begins between 0 and 2 L).  u is exact in double
-// precision, a multiple of a 24-bit number below 2^12 of them.
+// (for |s + m| <= 2 L and |s - m| <= 2 L, so that every list begins between 0 and 2 L; below the floor, s + m < 0, list 2
+// begins with an image at |s + m| on the other side, and list 3 beyond 2 L).  u is exact in double precision, a multiple of a
+// 24-bit number below 2^12 of them.
 // squared distance of image (list, p) by the reference recipe; a: of the column
 __device__ __attribute__((noinline)) double exact_z_image(Axis az, double a, double u, int list) {
     const int p = (int)rint(u / (2.0 * az.room));
@@ -840,10 +842,12 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
             c.walk2 = c.near_item ? r_near * r_near : r_in * r_in;
             // the fast walk: the x and y images fit the LDS tables and so do the powers along z, and the closed forms hold
             const double height_taps = az.room * k_fs_c;
-            const bool fast = axis_in_order(ax) && axis_in_order(ay) && axis_in_order(az) && both >= 0.0 &&
-                              2 * (2 * c.nmx + 1) <= 2 * kAxisCap && y_images(c.nmy) <= kYCap && c.nmz <= kMaxP &&
+            const bool fast = axis_in_order(ax) && axis_in_order(ay) && axis_in_order(az) && 2 * (2 * c.nmx + 1) <= 2 * kAxisCap && y_images(c.nmy) <= kYCap && c.nmz <= kMaxP &&
                               fmax(ay.room, az.room) * k_fs_c < kMaxAxisTaps && height_taps >= kMinHeightTaps;
-            c.tested = c.near_item || height_taps > kWrapTaps;
+            c.tested = c.near_item || height_taps > kWrapTaps || both < 0.0;
+            // (the lists begin within 2 L of each other, or, with positions below the floor, 6 L; next to images that are walked
+            // apart the bound counts to the last bit, and its slack is worth another step)
+            c.edges = (both < 0.0 ? 6 : 2) + (c.near_item ? 1 : 0);
             c.kind = fast ? kFast : kPlain;
             c.cy = axis_count(ay, k_fs_c);
             c.y_order = axis_order(ay);
@@ -1028,6 +1032,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             if (lane < 4) row_begin[lane ? nix + lane : 0] = lane ? 0x7fffffff : 0;
             wave_sync_lds();
             const bool near_item = uni(c.near_item) != 0, tested = uni(c.tested) != 0;
+            const int edges = uni(c.edges);
 
             // Columns are worked through a chunk at a time.  Each thread describes kPerThread candidates (the wavefronts'
             // stretches of 64 side by side, so that a wavefront's rows only move up); the live ones are sorted by length,
@@ -1135,13 +1140,10 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                             const double even = COUNT ? 0.0 : (double)bpow[r >> 16], odd = __dmul_rn(even, beta);
                             const double* zp = zpow + p0;
                             const double u0 = two_l * (double)p0;
-                            // the first and the last four images, and, next to images that are walked apart, the second, may
-                            // lie outside the shell
-                            const int edges = near_item ? 3 : 2;
 #pragma unroll 1
                             for (int e = 0; e < edges; ++e) {
-                                const int at = e == 0 ? 0 : e == 1 ? n : 1;
-                                if (e && n < e) break;
+                                const int at = e & 1 ? n - (e >> 1) : e >> 1;
+                                if (n < e) break;
                                 const double z = COUNT ? 0.0 : zp[at];
                                 const int in = walk_step<COUNT, true>(c, regs, tested, col, fma(two_l, (double)at, u0), z * even, z * odd, dropped8, hist);
                                 if (VISITS) walked += in;
@@ -1149,8 +1151,9 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                             int left = n + 1 - edges;
                             if (left > 0) {
                                 if (VISITS) walked += 4 * left;
-                                zp += edges - 1;
-                                double u = fma(two_l, (double)(edges - 1), u0);
+                                const int inner = (edges + 1) >> 1;
+                                zp += inner;
+                                double u = fma(two_l, (double)inner, u0);
                                 do {
                                     const double z = COUNT ? 0.0 : *zp++;
                                     walk_step<COUNT, false>(c, regs, false, col, u, z * even, z * odd, 0u, hist);

@@ -232,3 +232,31 @@ def test_tall_rooms(aug, fs, length):
     h_ref, cnt_ref = O.rir_batch(geom, length, fs, C)
     np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
     assert rir_err(alone.cpu().numpy(), h_ref) <= RIR_TOL
+
+
+@pytest.mark.parametrize("fs,length", [(16000.0, 62), (16000.0, 1500), (16000.0, 6000), (96000.0, 700)])
+def test_positions_below_the_floor(aug, fs, length):
+    """Positions up to a room's height below it, where the images of one list along z change sides, with short responses (images
+    walked apart) and long ones.  Against the oracle, and in a batch the same bits."""
+    import torch
+    rng = np.random.default_rng(length)
+    rows = []
+    for h in (0.4, 1.0, 2.5):
+        for s, m in ((-0.1, -0.2), (-0.5, 0.2), (0.3, -0.9), (-0.999, -0.99), (-1.0, -1.0), (-1.0, 0.9), (-0.4, 0.4), (-0.001, 0.0), (-0.6, -0.6)):
+            for near in (0.05, 0.8):
+                w, d = rng.uniform(4.0, 9.0, 2)
+                rows.append([w, d, h, 0.4 * w, 0.5 * d, s * h, 0.4 * w + near, 0.5 * d + near, m * h, rng.choice([0.1, 0.6, 0.9, 1.0])])
+    geom = np.asarray(rows, np.float32)
+    n = len(rows)
+    print(f"case: below the floor, fs={fs} L={length}", flush=True)
+    h = torch.full((10 * n, length), float("nan"), device="cuda")
+    cnt = torch.full((n, length), -7, dtype=torch.int32, device="cuda")
+    aug.aug_rir_batch(dev(np.tile(geom, (10, 1))), length, fs, C, h)
+    alone = torch.full((n, length), float("nan"), device="cuda")
+    aug.aug_rir_batch(dev(geom), length, fs, C, alone, cnt)
+    torch.cuda.synchronize()
+    for k in range(10):
+        assert torch.equal(h[k * n:(k + 1) * n], alone)
+    h_ref, cnt_ref = O.rir_batch(geom, length, fs, C)
+    np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
+    assert rir_err(alone.cpu().numpy(), h_ref) <= RIR_TOL
