@@ -754,7 +754,7 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, c
                 const double d2 = in_steps ? fma(step, step, a) : recipe;
                 const double y = __builtin_amdgcn_rsq(d2);
                 const int slot = tap_slot(w, d2, y, [&] { return recipe; });
-                if (8u * (unsigned int)slot > w.top8) continue;
+                if ((unsigned int)slot > w.top8 / 8u) continue;       // (eight times a slot beyond 2^29 would come round)
                 double amp = 0.0;
                 if (!COUNT) {
                     const double z = p <= kMaxP ? zpow[p] : z_power(w.beta, p);

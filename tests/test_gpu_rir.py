@@ -260,3 +260,15 @@ def test_positions_below_the_floor(aug, fs, length):
     h_ref, cnt_ref = O.rir_batch(geom, length, fs, C)
     np.testing.assert_array_equal(cnt.cpu().numpy(), cnt_ref)
     assert rir_err(alone.cpu().numpy(), h_ref) <= RIR_TOL
+
+
+def test_images_whose_slots_come_round_in_32_bits(aug):
+    """Rooms so high that the image behind the ceiling lies 2^29 taps and a few away: it belongs to no tap."""
+    k = np.float64(np.float32(FS)) / np.float64(np.float32(C))
+    rows, heights = [], (2.0 ** 29 + np.linspace(50.0, 2900.0, 40)) / (2.0 * k)
+    for h in heights.astype(np.float32):
+        rows.append([6.0, 5.0, h, 2.0, 3.0, 0.0, 4.0, 1.5, 0.0, 1.0])
+    geom = np.asarray(rows, np.float32)
+    assert np.any(np.floor(2.0 * geom[:, 2].astype(np.float64) * k + 0.5) % 2 ** 29 < 3000)
+    print("case: images 2^29 taps away, L=3000", flush=True)
+    _check(aug, geom, 3000)
