@@ -801,7 +801,7 @@ __device__ __attribute__((noinline)) unsigned int walk_near(const ItemCtx& w, in
 
 // Prepares item `it`: all lanes of one wavefront compute the same, lane 0 writes.
 template <bool COUNT>
-__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
+__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, int rir_len, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
     ItemCtx c{};
     c.kind = kEnd;
     if (it < n_items) {
@@ -829,9 +829,13 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
             // (amplitude sums only; tap counts visit every image)
             c.inv_log2_beta = (!COUNT && g[9] > 0.f && g[9] < 1.f) ? 1.f / __log2f(g[9]) : 0.f;
             c.k_cut = reflection_cut(c.inv_log2_beta, (float)r_in);
-            c.nmx = min((int)ceil(r_out / (2.0 * ax.room)) + 1, c.k_cut / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
-            c.nmy = min((int)ceil(r_out / (2.0 * ay.room)) + 1, c.k_cut / 2 + 1);
-            c.nmz = (int)ceil(r_out / (2.0 * az.room)) + 1;
+            // (of positions far outside, where no such bound holds, those of the whole response's radius, in whatever item they land)
+            auto most_n = [&](const Axis& ax1) {
+                return (int)ceil((axis_in_order(ax1) ? r_out : (double)rir_len / k_fs_c) / (2.0 * ax1.room)) + 1;
+            };
+            c.nmx = min(most_n(ax), c.k_cut / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
+            c.nmy = min(most_n(ay), c.k_cut / 2 + 1);
+            c.nmz = most_n(az);
             c.k_fs_c = k_fs_c;
             // (in whole units of the estimate's 2^-16 tap, so that adding it to the magic number is exact; one unit
             // for the sum's rounding)
@@ -915,7 +919,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     auto prepare_next = [&](ItemCtx& ctx) {        // by one wavefront
         int it = 0;
         if (lane == 0) it = atomicAdd(&ctrl[1], 1);
-        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane);
+        prepare_item<COUNT>(ctx, rooms, rir_len, k_fs_c, items, uni(it), n_items, lane);
     };
 
     // sums start at zero and are left at zero where an item is written out

@@ -272,3 +272,22 @@ def test_images_whose_slots_come_round_in_32_bits(aug):
     assert np.any(np.floor(2.0 * geom[:, 2].astype(np.float64) * k + 0.5) % 2 ** 29 < 3000)
     print("case: images 2^29 taps away, L=3000", flush=True)
     _check(aug, geom, 3000)
+
+
+def test_positions_many_rooms_outside(aug):
+    """Source and microphone many sides apart along one axis: the images near the microphone have numbers that only the whole
+    response's radius allows.  Against the oracle, and in a batch (where a response is cut into other shells) the same bits."""
+    rng = np.random.default_rng(3)
+    length = 8000
+    rows = []
+    for axis in range(3):
+        for share in (0.3, 0.6, -0.8, 0.95):
+            room = rng.uniform(1.8, 3.0, 3)
+            src, mic = 0.4 * room, 0.7 * room
+            (src if rng.random() < 0.5 else mic)[axis] += share * length * C / FS
+            rows.append(np.concatenate([room, src, mic, [rng.choice([0.6, 0.9, 1.0])]]))
+    geom = np.asarray(rows, np.float32)
+    print("case: positions many rooms outside, L=8000", flush=True)
+    h, _ = _check(aug, geom, length)
+    many, _ = _run(aug, np.tile(geom, (15, 1)), length, counts=False)
+    np.testing.assert_array_equal(many, np.tile(h, (15, 1)))
