@@ -722,6 +722,9 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, c
     const bool below = w.az.src < w.az.mic, in_steps = axis_in_order(w.az);
     const long long n_columns = 2ll * (2 * nmx + 1) * niy;
     const double r_in = w.n0 > 0 ? (double)(w.n0 - 1) / w.k_fs_c : 0.0, inv_2l = 1.0 / w.two_l;
+    // what the recipe's operations may move an image of the z axis by: positions so far outside that it is more than a room's
+    // height put several images in one place, or none
+    const double rounding = 0x1p-50 * (fabs(w.az.src) + fabs(w.az.mic) + w.two_l * (double)(nmz + 1));
     for (long long cand = threadIdx.x; cand < n_columns; cand += kThreads) {
         const int ix = (int)(cand / niy), iy = (int)(cand - (long long)ix * niy);
         const int qx = ix & 1, nx = (ix >> 1) - nmx, qy = iy & 1, ny = (iy >> 1) - nmy;
@@ -732,7 +735,7 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, c
         const int kz_max = (w.n0 > 0 ? w.k_cut : reflection_cut(w.inv_log2_beta, sqrtf((float)a))) - kxy;
         if (!(a < w.r_out2) || kz_max < 0) continue;
         const double bxy = COUNT ? 0.0 : (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(w.beta, kxy));
-        const double far = sqrt(w.r_out2 - a), near = sqrt(fmax(r_in * r_in - a, 0.0));
+        const double far = sqrt(w.r_out2 - a) + rounding, near = fmax(sqrt(fmax(r_in * r_in - a, 0.0)) - rounding, 0.0);
         const int nz = min(nmz, kz_max / 2 + 1);                     // |n - q| + |n| >= 2 |n| - 1
         for (int q = 0; q < 2; ++q) {
             // the images from -far to far but for those between -near and near, and one more at every end for rounding

@@ -291,3 +291,15 @@ def test_positions_many_rooms_outside(aug):
     h, _ = _check(aug, geom, length)
     many, _ = _run(aug, np.tile(geom, (15, 1)), length, counts=False)
     np.testing.assert_array_equal(many, np.tile(h, (15, 1)))
+
+
+def test_heights_so_far_outside_that_rounding_moves_images(aug):
+    """Source and microphone 1e16 to 7e16 m above or below the room: the recipe rounds its images' heights to more than the distance between
+    two of them."""
+    rng = np.random.default_rng(9)
+    rows = []
+    for i in range(48):
+        s = np.float32(rng.uniform(1e16, 7e16) * rng.choice([-1.0, 1.0]))
+        rows.append([4.0, 3.0, rng.uniform(0.4, 3.5), 1.0, 1.1, s, 2.5, 1.7, s * rng.choice([-1.0, 1.0]), 0.9])
+    print("case: heights far outside the room, L=3000", flush=True)
+    _check(aug, np.asarray(rows, np.float32), 3000)
