@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "4d1ab659757896b2",
-    "varlen": {"rir": 73367900, "rir_spectrum": 202562709, "convolve": 1256413643, "mel": 612950226},
-    "throughput": {"rir": 424393514, "rir_spectrum": 1218383824, "convolve": 13979475224, "mel": 2175481205},
+    "digest": "ecf3cc55a6230d74",
+    "varlen": {"rir": 78219242, "rir_spectrum": 202575909, "convolve": 1254578504, "mel": 612832888},
+    "throughput": {"rir": 430358318, "rir_spectrum": 1218104202, "convolve": 13984461762, "mel": 2175850729},
 }
 
 

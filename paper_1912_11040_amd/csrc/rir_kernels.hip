@@ -27,8 +27,9 @@
 //     first p to the last, four images a step, without reading any table of images: distances are formed from the step,
 //     amplitudes from one power per step.  Columns are sorted by length, some thousand at a time, so that the 64 lanes of a
 //     wavefront walk columns of one length.
-//     Rooms so flat or narrow that an axis has more images than the tables hold, and positions far outside
-//     the room, take a plain path (all columns of the bounding box, every z image of a live column).
+//     Rooms so flat or narrow that an axis has more images than the tables hold, rooms of more than 4e5 taps along y or z,
+//     and positions far outside the room take a plain path (all columns of the bounding box, of a live column the z
+//     images about the shell, every tap tested).
 //   * amplitudes accumulate as 64-bit fixed point (2^-56, each increment rounded to the nearest unit)
 //     with integer LDS atomics: gfx950 executes float LDS atomics far slower than integer
 //     ones, and integer sums do not depend on the order of arrival nor on how a batch is cut into items.
@@ -60,17 +61,17 @@ constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step
 constexpr int kPerThread = 6;             // candidate columns per thread and chunk
 constexpr int kChunk = kThreads * kPerThread;
 constexpr int kColumns = 3 * kThreads;    // live columns that the LDS has room for: a chunk's are walked in as many goes
-// Work per item, in image visits (see item_cost): the batch's estimated work divided by the number of
+// Work per item, in image visits (see WorkModel): the batch's estimated work divided by the number of
 // persistent groups and by kItemsPerGroup, within limits.  Thick shells visit fewer (x, y) columns per image
 // (every shell sets up all columns inside its outer radius), thin ones even out the groups' finishing
-// times; every response yields at least one item, so the groups still get several items each.  Measured:
-// 16000-tap batch 0.89 -> 0.80 ms, 32768-tap batch 12.8 -> 7.6 ms against a fixed 600000.
+// times; every response yields at least one item, so the groups still get several items each.  Whole calls against
+// 600000 at every batch: 3072 responses of 32768 taps (1024 utterances of 10 s) 7.8 -> 6.7 ms, 128 of 8000 (64 of 4 s) 180 -> 134 us.
 constexpr float kItemsPerGroup = 1.25f;
-// (the lower limit matters for small batches only, where items must be small for all groups to get one:
-// 64 utterances with 8000-tap responses take 0.122 ms at 300000, 0.080 ms at 50000)
+// (the lower limit matters for small batches only, where items must be small for all groups to get one: 64 utterances of 4 s
+// with two responses of 8000 taps each take 156 us at 300000, 130 at 50000, eight of 1 s with 4096 taps 58 and 54)
 constexpr float kMinTargetWork = 50000.f, kMaxTargetWork = 8000000.f;
 constexpr float kWorkUnit = 4096.f;       // the batch total is summed in integers of this many visits
-constexpr int kMaxShells = 96;            // volume-balanced shells per response, at most
+constexpr int kMaxShells = 96;            // shells per response, before those wider than kMaxTaps are split
 
 #pragma clang fp contract(off)
 
@@ -126,8 +127,11 @@ __device__ inline void wave_sync_lds() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Barrier of the work group, with the wait for this wavefront's LDS operations spelled out: where a barrier begins a loop's
-// body, the compiler (ROCm 7.2) has been seen to leave out the wait that the barrier's fence asks for.
+// Barrier of the work group, with the wait for this wavefront's LDS operations spelled out.  With __syncthreads the compiler
+// (ROCm 7.2) emits two of the image kernel's barriers without one, that behind the candidates and that of a further go, where it
+// takes every operation on the paths to them for waited for.  Reading those paths finds nothing in flight either; spelled out,
+// the wait costs nothing and does not rest on that.  (The other kernels keep __syncthreads: the wait stands before all of
+// their barriers but the last of the spectrum kernels' loops, where every value read has been used.)
 __device__ inline void group_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0xc07f);                    // lgkmcnt(0)
@@ -636,10 +640,6 @@ __device__ __attribute__((noinline)) double exact_z_image(Axis az, double a, dou
     return __dadd_rn(a, __dmul_rn(dz, dz));
 }
 
-// The four images of a column at u = 2 L p.  amp_even = beta^(kxy + 2 p) / (4 pi) 2^56 and amp_odd = beta^(kxy + 2 p + 1)
-// likewise.  Four independent chains of arithmetic; no memory is read.  EDGE: some of the images may lie outside the item's
-// shell and go to the lane's own slot for such (dropped8); else every one lies inside, up to the slack of the closed form (a fifth of a tap), so
-// its slot is one of 0 .. taps + 1 and needs no test.
 // fma(a, b, c) with c left as it is: the compiler takes the two-address form, which destroys c, and copies it first for
 // each of four uses
 __device__ inline double fma_keep(double a, double b, double c) {
@@ -659,6 +659,10 @@ struct WalkRegs {           // what every step needs of the item, moved to scala
         : begin{uni(c.begin[0]), uni(c.begin[1]), uni(c.begin[2]), uni(c.begin[3])}, quick_k(uni(c.quick_k)), quick_shift(c.quick_shift),
           beta2(uni(c.beta2)), quick_margin2((unsigned short)uni(c.quick_margin2)) {}
 };
+// The four images of a column at u = 2 L p.  amp_even = beta^(kxy + 2 p) / (4 pi) 2^56 and amp_odd = beta^(kxy + 2 p + 1)
+// likewise.  Four independent chains of arithmetic; no memory is read.  EDGE: some of the images may lie outside the item's
+// shell and go to the lane's own slot for such (dropped8), with `tested` by their distance (see ItemCtx::tested); else every one
+// lies inside, up to the slack of the closed form (a fifth of a tap), so its slot is one of 0 .. taps + 1 and needs no test.
 template <bool COUNT, bool EDGE>
 __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested, double a, double u, double amp_even, double amp_odd,
                                 unsigned int dropped8, unsigned long long* hist) {
