@@ -154,8 +154,8 @@ int conv_fft_size(int rir_len);
 // of 96 signals took 139 us with eight rows at every length, 120 now.)
 // The kernel for any number of rows takes a sixth longer for a block of 16384 points than the one for eight, which a ninth row does
 // not repay (14000 taps: 300 signals of 15000 to 30000 samples 79 us with eight rows, 81 with nine; 96 of up to 100000, three sources,
-// 123 and 125).  Shorter transforms repay it (3300 taps, the same batches: 60 and 58 us, 125 and 117).  A call of one or
-// a few signals that a single block holds has nothing to gain and takes 1 to 2 us longer.
+// 123 and 125).  Shorter transforms repay it (3300 taps, the same batches: 60 and 58 us, 125 and 117).
+// Every number of rows has a kernel of its own (see convolve_of_rows).
 // Both follow from the response's length alone, so that a signal's reverberation does not depend on the batch it is in, and
 // the window is the smallest that there is: a transform spreads its rounding error over its whole window, at the level of the
 // window's loudest part.  (The largest transform at every length that fills the chip took 256 signals of 64000 samples with 4096

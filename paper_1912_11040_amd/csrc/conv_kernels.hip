@@ -200,53 +200,53 @@ struct ConvBlock {
 __device__ inline int window_row(int b, int rows) { return (b + 1) * rows - 16; }
 
 // The window from row `row`, as the inputs of the column step: v[n1] = (x[2n], x[2n+1]), n = tid + M n1; zeros before the
-// utterance and past its end.  Only a window that reaches past the end tests its samples: what a branch loads without looking
-// at it stays on its way behind the transform that follows.  ROWS as in convolve_inplace_kernel: of a window whose block has eight
-// rows, the first eight are a whole block of the utterance or lie before it.
+// utterance and past its end.  The rows before the block's own are all there or, in the first window, all before the utterance,
+// and its own never are before it.  Only a window that reaches past the end tests its samples: what a branch loads without looking
+// at it stays on its way behind the transform that follows.
 template <int N, int ROWS>
 __device__ inline void load_window(float2 (&v)[16], const float* x, int len, int row, int tid) {
-    constexpr int M = N / 16;
+    constexpr int M = N / 16, kOwn = 16 - ROWS;
     const int from = row * (2 * M);                        // (signals are shorter than 2^30 samples)
     const float* at = x + from;
     const uint32_t lane_off = 8u * (uint32_t)tid;
-    auto whole_row = [&](int n1) {                         // (the same for all threads)
-        if (n1 < 8 && row + (ROWS == 8 ? 0 : n1) < 0) {    // (the last eight rows are never before the utterance)
-            v[n1] = make_float2(0.f, 0.f);
-        } else {
-            const SamplePair s2 = load_pair(at + 2 * M * n1, lane_off);
-            v[n1] = make_float2(s2.x, s2.y);
-        }
+    auto whole_row = [&](int n1) {
+        const SamplePair s2 = load_pair(at + 2 * M * n1, lane_off);
+        v[n1] = make_float2(s2.x, s2.y);
     };
+    if (row >= 0) {
+#pragma unroll
+        for (int n1 = 0; n1 < kOwn; ++n1) whole_row(n1);
+    } else {
+#pragma unroll
+        for (int n1 = 0; n1 < kOwn; ++n1) v[n1] = make_float2(0.f, 0.f);
+    }
     if (from + 32 * M <= len) {
 #pragma unroll
-        for (int n1 = 0; n1 < 16; ++n1) whole_row(n1);
+        for (int n1 = kOwn; n1 < 16; ++n1) whole_row(n1);
     } else if (ROWS == 8 || len < 2) {
-        // addresses are clamped to the utterance's samples, values outside it are zero
-        constexpr int kTested = ROWS == 8 ? 8 : 0;
+        // addresses are clamped to the utterance's last sample, values past it are zero
 #pragma unroll
-        for (int n1 = 0; n1 < kTested; ++n1) whole_row(n1);
-#pragma unroll
-        for (int n1 = kTested; n1 < 16; ++n1) {
-            const int g = from + 2 * M * n1 + 2 * tid, low = n1 < 8 ? max(g, 0) : g;
-            const float x0 = load_sample(x, 4u * (uint32_t)min(low, len - 1));
-            const float x1 = load_sample(x, 4u * (uint32_t)min(low + 1, len - 1));
-            v[n1] = make_float2(g < len && (n1 >= 8 || g >= 0) ? x0 : 0.f, g + 1 < len && (n1 >= 8 || g >= 0) ? x1 : 0.f);
+        for (int n1 = kOwn; n1 < 16; ++n1) {
+            const int g = from + 2 * M * n1 + 2 * tid;
+            const float x0 = load_sample(x, 4u * (uint32_t)min(g, len - 1));
+            const float x1 = load_sample(x, 4u * (uint32_t)min(g + 1, len - 1));
+            v[n1] = make_float2(g < len ? x0 : 0.f, g + 1 < len ? x1 : 0.f);
         }
     } else {
-        // any row may be the one that the end cuts: pairs clamped to the utterance's last, whose second sample is then the one
-        // wanted (sixteen loads, not 32: 96 signals with 12001 taps 155 us, not 159)
+        // pairs clamped to the utterance's last, whose second sample is then the one wanted (half as many loads: 96
+        // signals with 12001 taps 155 us, not 159)
 #pragma unroll
-        for (int n1 = 0; n1 < 16; ++n1) {
-            const SamplePair s2 = load_pair(x, 4u * (uint32_t)min(max(from + 2 * M * n1 + 2 * tid, 0), len - 2));
+        for (int n1 = kOwn; n1 < 16; ++n1) {
+            const SamplePair s2 = load_pair(x, 4u * (uint32_t)min(from + 2 * M * n1 + 2 * tid, len - 2));
             v[n1] = make_float2(s2.x, s2.y);
         }
 #pragma unroll
-        for (int n1 = 0; n1 < 16; ++n1) {
+        for (int n1 = kOwn; n1 < 16; ++n1) {
             const int r = from + 2 * M * n1, g = r + 2 * tid;
-            if (r >= 0 && r + 2 * M <= len) continue;      // (the same for all threads)
+            if (r + 2 * M <= len) continue;                // (the same for all threads)
             asm volatile("");                              // a branch, not selects in every row: those took 1 us a window
             const float first = g == len - 1 ? v[n1].y : v[n1].x;
-            v[n1] = make_float2(g >= 0 && g < len ? first : 0.f, g >= 0 && g + 1 < len ? v[n1].y : 0.f);
+            v[n1] = make_float2(g < len ? first : 0.f, g + 1 < len ? v[n1].y : 0.f);
         }
     }
 }
@@ -254,22 +254,18 @@ __device__ inline void load_window(float2 (&v)[16], const float* x, int len, int
 // The outputs of a block, v[n1] = (y[n], y[n+1]) in its last rows (see window_row), go to HBM; returns the
 // lane's share of the block's energy.  Samples before the response's first non-zero tap are exact zeros
 // (the transforms leave rounding noise there, which the power law of the front end would magnify).
-// ROWS: the number of rows where it is fixed, 0: `rows`, at least 8.
 template <int N, int ROWS>
-__device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, int rows, int tid) {
-    constexpr int M = N / 16;
-    if (ROWS) rows = ROWS;
-    const int row = window_row(c.b, rows);
+__device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, int tid) {
+    constexpr int M = N / 16, kOwn = 16 - ROWS;
+    const int row = window_row(c.b, ROWS);
     float* yb = c.y + (int64_t)row * (2 * M);              // (row 0 of the window, which may lie before the utterance)
     const int first = min(c.first, c.len) - row * (2 * M); // first live sample (a silent response has none: its first tap is 2^31 - 1)
     const int left = c.len - row * (2 * M);                // samples up to the utterance's end
-    constexpr int kFrom = ROWS ? 16 - ROWS : 0;
     float e[2] = {0.f, 0.f};                               // (chains of sixteen squares, however many rows there are)
-    if (left >= 32 * M && first <= (16 - rows) * (2 * M)) {     // whole and live: two-sample stores
+    if (left >= 32 * M && first <= kOwn * (2 * M)) {     // whole and live: two-sample stores
         char* dst = reinterpret_cast<char*>(yb) + 8u * (uint32_t)tid;
 #pragma unroll
-        for (int n1 = kFrom; n1 < 16; ++n1) {
-            if (n1 < 8 && n1 < 16 - rows) continue;
+        for (int n1 = kOwn; n1 < 16; ++n1) {
             SamplePair s2;
             s2.x = v[n1].x;
             s2.y = v[n1].y;
@@ -278,8 +274,7 @@ __device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, i
         }
     } else {
 #pragma unroll
-        for (int n1 = kFrom; n1 < 16; ++n1) {
-            if (n1 < 8 && n1 < 16 - rows) continue;
+        for (int n1 = kOwn; n1 < 16; ++n1) {
             const int g = 2 * tid + 2 * M * n1;
             const float s0 = g >= first ? v[n1].x : 0.f, s1 = g + 1 >= first ? v[n1].y : 0.f;
             if (g < left) { yb[g] = s0; e[n1 / 8] += s0 * s0; }
@@ -389,8 +384,7 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
     if (walk.at >= walk.end) return;
     ConvBlock cur = walk.describe(N + 1);
     float2 v[16];
-    const int rows = ROWS ? ROWS : a.rows;
-    load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, rows), tid0);
+    load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, ROWS), tid0);
 
     for (;;) {
         // The thread index is made opaque in every round so that twiddle powers and addresses are not
@@ -445,7 +439,7 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         if (more) {
             walk.next();
             nxt = walk.describe(N + 1);
-            load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, rows), tid);
+            load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, ROWS), tid);
         } else {
             // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
 #pragma unroll
@@ -457,7 +451,7 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         float2 o[16];
         fft_columns_load<N, T>(o, buf, tid);
         fft_columns_inverse<N>(o, tw, tid);
-        const double es = wave_energy<ROWS>(store_block<N, ROWS>(o, cur, rows, tid));
+        const double es = wave_energy<ROWS>(store_block<N, ROWS>(o, cur, tid));
         if ((tid & 63) == 0) red[tid >> 6] = es;
         __syncthreads();                                   // also: every thread has read its columns from LDS
         if (tid == 0) {
@@ -585,7 +579,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void rir_spectrum_inplace_kernel(
 // registers, so a block still costs one forward and one inverse transform (plus one forward transform at the start of a
 // group's share).  The kept spectrum takes the registers that the single-partition kernel spends on inputs requested
 // ahead of time; they are then loaded where they are used.
-// ROWS: a block's rows where they are fixed (8: half of the last step's outputs are then never formed), 0: any.
+// ROWS: a block's rows (the last step's other outputs are never formed).
 template <int N, bool MULTI, int ROWS>
 __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArgs a, const float* __restrict__ tab) {
     using P = InPlace<N>;
@@ -609,8 +603,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         for (int i = 0; i < 8; ++i) prev_a[i] = prev_b[i] = make_float2(0.f, 0.f);
         have_prev = cur.b == 0;     // the window before the first block is all zeros, and so is its spectrum
     }
-    const int rows = ROWS ? ROWS : a.rows;
-    if (AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, rows), tid0);
+    if (AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(cur.b, ROWS), tid0);
     double* done_energy = nullptr;  // where the energies in red[parity ^ 1] belong
     int parity = 0;
     // the energy of the block before this one
@@ -628,7 +621,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         int tid = tid0;
         asm volatile("" : "+v"(tid));
         const bool warm_up = MULTI && !have_prev;          // this pass only produces the spectrum of window b - 1
-        if (!AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(warm_up ? cur.b - 1 : cur.b, rows), tid);
+        if (!AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(warm_up ? cur.b - 1 : cur.b, ROWS), tid);
 
         inplace_forward_ab<N>(v, buf, lds_tab, tid);
         flush_energy(tid);
@@ -709,7 +702,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         if (more) {
             walk.next();
             nxt = walk.describe(2 * kEntries);
-            if (AHEAD) load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, rows), tid);
+            if (AHEAD) load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, ROWS), tid);
         } else if (AHEAD) {
             // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
 #pragma unroll
@@ -719,7 +712,7 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         float2 o[16];
         const Tw16Short w{{wa[0].x, wa[0].y, wa[0].z, wa[0].w, wa[1].x, wa[1].y}, {wa[1].z, wa[1].w, wa[2].x, wa[2].y, wa[2].z, wa[2].w}};
         inplace_inverse<N>(o, buf, lds_tab, tid, w);
-        const double es = wave_energy<ROWS>(store_block<N, ROWS>(o, cur, rows, tid));
+        const double es = wave_energy<ROWS>(store_block<N, ROWS>(o, cur, tid));
         if ((tid & 63) == 0) red[parity][tid >> 6] = es;
         done_energy = cur.energy;
         parity ^= 1;
@@ -843,27 +836,38 @@ hipError_t spectrum_n(hipStream_t s, int n_rir, const float* rir, int rir_len, c
     }
 }
 
+// The kernel for blocks of that many rows.  (One for any number tested every row and formed all sixteen: calls of a few signals
+// took up to 2 us longer with it, one signal of 8000 samples 18.9 -> 20.5 us with 1100 taps and 27.9 -> 29.2 with 12001, 32
+// of 16000 with 3300 taps 23.3 -> 24.1.)  A response longer than half a transform leaves at most twelve, shorter ones exist at
+// the smallest transform only, and nine are not taken at the largest (see conv_plan).
+template <int N, int ROWS = 8>
+const void* convolve_of_rows(int rows) {
+    if (rows == ROWS) {
+        if constexpr (in_place(N)) return reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false, ROWS>);
+        else return reinterpret_cast<const void*>(&convolve_kernel<N, conv_threads(N), ROWS>);
+    }
+    if constexpr (ROWS < (N == 1024 ? 16 : 12)) return convolve_of_rows<N, N == 16384 && ROWS == 8 ? 10 : ROWS + 1>(rows);
+    else return nullptr;
+}
+
 template <int N>
 hipError_t convolve_n(hipStream_t s, const float2* tw, const ConvArgs& a, int n_cu) {
     const int64_t total = a.n_items * a.n_src;
     if (total > 0x7fffffffLL) return hipErrorInvalidValue;
     ConvArgs by_value = a;
     void* args[] = {&by_value, &tw};
+    const void* k = convolve_of_rows<N>(a.rows);
     if constexpr (in_place(N)) {
         // responses longer than one partition exist only at the largest transform size (conv_fft_size)
-        const void* k = a.rows == 8 ? reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false, 8>)
-                                    : reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false, 0>);
         if (a.n_part > 1) {
-            if (N != 16384 || a.n_part != 2) return hipErrorInvalidValue;
+            if (N != 16384 || a.n_part != 2 || a.rows != 8) return hipErrorInvalidValue;
             k = reinterpret_cast<const void*>(&convolve_inplace_kernel<16384, true, 8>);
         }
+        if (!k) return hipErrorInvalidValue;
         return launch_groups(s, k, n_cu, total, InPlace<N>::T, inplace_lds<N>(), args);
     } else {
-        if (a.n_part > 1) return hipErrorInvalidValue;
-        constexpr int T = conv_threads(N);
-        const void* k = a.rows == 8 ? reinterpret_cast<const void*>(&convolve_kernel<N, T, 8>)
-                                    : reinterpret_cast<const void*>(&convolve_kernel<N, T, 0>);
-        return launch_groups(s, k, n_cu, total, T,
+        if (a.n_part > 1 || !k) return hipErrorInvalidValue;
+        return launch_groups(s, k, n_cu, total, conv_threads(N),
                              sizeof(float2) * (lds_padded_size(N) + RowTwiddles<N / 16>::kEntries + 16 + N / 32), args);
     }
 }
