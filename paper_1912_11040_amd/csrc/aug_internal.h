@@ -151,12 +151,10 @@ int conv_fft_size(int rir_len);
 
 // Size of the convolution's transforms (N complex points) and outputs per block, in rows of N / 8 samples: of the sixteen
 // rows of a window those that no tap reaches from beyond its start, 8 .. 16.  (12001 taps at N = 16384 leave ten: three sources
-// of 96 signals took 139 us with eight rows at every length, 120 now.)
-// The kernel for any number of rows takes a sixth longer for a block of 16384 points than the one for eight, which a ninth row does
-// not repay (14000 taps: 300 signals of 15000 to 30000 samples 79 us with eight rows, 81 with nine; 96 of up to 100000, three sources,
-// 123 and 125).  Shorter transforms repay it (3300 taps, the same batches: 60 and 58 us, 125 and 117).
+// of 96 signals took 139 us with eight rows at every length, 120 now; 14000 leave nine: three sources of 96 signals of up to 100000
+// samples 118 us with eight, 108 so, 256 of 64000 alone 197 and 188, 1000 of 9000 no difference.)
 // Every number of rows has a kernel of its own (see convolve_of_rows).
-// Both follow from the response's length alone, so that a signal's reverberation does not depend on the batch it is in, and
+// Size and rows follow from the response's length alone, so that a signal's reverberation does not depend on the batch it is in, and
 // the window is the smallest that there is: a transform spreads its rounding error over its whole window, at the level of the
 // window's loudest part.  (The largest transform at every length that fills the chip took 256 signals of 64000 samples with 4096
 // taps from 189 us to 158, and put 1.8e-7 of the loud part where 3.7e-8 had been in a pause 8000 samples behind it.)
@@ -166,9 +164,7 @@ struct ConvPlan {
 };
 inline ConvPlan conv_plan(int rir_len) {
     const int fft_n = conv_fft_size(rir_len), row = fft_n / 8;
-    int rows = rir_len > fft_n ? 8 : 16 - (rir_len - 1 + row - 1) / row;           // more than one partition: whole blocks of N
-    if (fft_n == 16384 && rows < 10) rows = 8;
-    return {fft_n, rows};
+    return {fft_n, rir_len > fft_n ? 8 : 16 - (rir_len - 1 + row - 1) / row};      // more than one partition: whole blocks of N
 }
 
 // The tables that the transforms of that size read (float2 [conv_table_entries(fft_n)]), and the size of a partition's

@@ -838,15 +838,15 @@ hipError_t spectrum_n(hipStream_t s, int n_rir, const float* rir, int rir_len, c
 
 // The kernel for blocks of that many rows.  (One for any number tested every row and formed all sixteen: calls of a few signals
 // took up to 2 us longer with it, one signal of 8000 samples 18.9 -> 20.5 us with 1100 taps and 27.9 -> 29.2 with 12001, 32
-// of 16000 with 3300 taps 23.3 -> 24.1.)  A response longer than half a transform leaves at most twelve, shorter ones exist at
-// the smallest transform only, and nine are not taken at the largest (see conv_plan).
+// of 16000 with 3300 taps 23.3 -> 24.1.)  A response longer than half a transform leaves
+// at most twelve rows; shorter ones exist at the smallest transform only.
 template <int N, int ROWS = 8>
 const void* convolve_of_rows(int rows) {
     if (rows == ROWS) {
         if constexpr (in_place(N)) return reinterpret_cast<const void*>(&convolve_inplace_kernel<N, false, ROWS>);
         else return reinterpret_cast<const void*>(&convolve_kernel<N, conv_threads(N), ROWS>);
     }
-    if constexpr (ROWS < (N == 1024 ? 16 : 12)) return convolve_of_rows<N, N == 16384 && ROWS == 8 ? 10 : ROWS + 1>(rows);
+    if constexpr (ROWS < (N == 1024 ? 16 : 12)) return convolve_of_rows<N, ROWS + 1>(rows);
     else return nullptr;
 }
 

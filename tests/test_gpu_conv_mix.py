@@ -270,7 +270,10 @@ def test_utterances_that_end_as_a_source_arrives(aug):
         assert worst_ordinary <= 2e-4
 
 
-@pytest.mark.parametrize("L", [1, 2, 129, 130, 1025, 1793, 2049, 2561, 2562, 3585, 4097, 5121, 8193, 12001, 12289, 12290, 14337, 16384, 16385])
+@pytest.mark.parametrize("L", [
+    1, 2, 129, 130, 258, 386, 514, 642, 770, 898, 1025, 1026, 1282, 1538, 1793, 1794, 2049, 2050, 2561, 2562,
+    3074, 3585, 3586, 4097, 4098, 5121, 5122, 6146, 7170, 8193, 8194, 10242, 12001, 12289, 12290, 14337, 14338,
+    16384, 16385])
 def test_blocks_of_every_number_of_rows(aug, L):
     """Response lengths where a block gains or loses a row of its window, signals that end around a row's and a block's end; the
     responses' last tap is the largest, so that a row kept too many shows.  The last utterance's noise response is all zeros."""
@@ -279,7 +282,7 @@ def test_blocks_of_every_number_of_rows(aug, L):
         n *= 2
     row = n // 8
     rows = 8 if L > n else 16 - (L - 1 + row - 1) // row
-    block = row * (8 if n == 16384 and rows < 10 else rows)
+    block = row * rows
     lens = [1, row - 1, row + 1, block - 1, block, block + 1, 2 * n - 1, 2 * n + 1, 2 * block + row, 3 * block - 1, 2 * block + 3]
     offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     rng = np.random.default_rng(L)
