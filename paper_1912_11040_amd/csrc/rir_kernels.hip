@@ -705,14 +705,14 @@ __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested
 // beta^k for reflection counts past the LDS table; out of line so that the double-precision pow does not
 // weigh on the register allocation of the loops that call it once in a long while
 __device__ __attribute__((noinline)) float beta_pow_slow(double beta, int k) { return (float)pow(beta, (double)k); }
-// beta^(2 p) / (4 pi) 2^56, of the same operations as the table of them in LDS
-__device__ __attribute__((noinline)) double z_power(double beta, int p) {
+// beta^k of the same operations as the tables in LDS
+__device__ __attribute__((noinline)) double table_power(double beta, int k) {
     double v = 1.0;
-    for (int k = 2 * p; k; k >>= 1) {
+    for (; k; k >>= 1) {
         if (k & 1) v *= beta;
         beta *= beta;
     }
-    return v * kAmplitude;
+    return v;
 }
 
 // Items that the closed forms do not take (rooms too flat or narrow for the tables, positions far outside): every column of
@@ -721,9 +721,18 @@ __device__ __attribute__((noinline)) double z_power(double beta, int p) {
 // Distance and amplitude of an image are formed as walk_step forms them, step for step: whether an item fits the tables
 // depends on where the batch's plan has cut the response, and the response must not.
 template <bool COUNT>
-__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, const float* bpow, const double* zpow, unsigned long long* hist) {
+__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, int rir_len, const float* bpow, const double* zpow, unsigned long long* hist) {
     unsigned int walked = 0;
-    const int nmx = w.nmx, nmy = w.nmy, nmz = w.nmz, niy = 2 * (2 * nmy + 1);
+    // Of positions far outside, no shell's radius bounds the numbers of its images: those of the whole response's radius, in
+    // whatever item they land.  (Formed here, where they are asked for: in prepare_item they took 2048 responses of 1000 taps of ordinary
+    // rooms 51 us instead of 49.5.)
+    auto most_n = [&](const Axis& ax, int within, int most) {
+        return axis_in_order(ax) ? within : min((int)ceil((double)rir_len / w.k_fs_c / (2.0 * ax.room)) + 1, most);
+    };
+    const int nmx = most_n(w.ax, w.nmx, w.k_cut / 2 + 1), nmy = most_n(w.ay, w.nmy, w.k_cut / 2 + 1), nmz = most_n(w.az, w.nmz, kNoCut);
+    const int niy = 2 * (2 * nmy + 1);
+    // what the tables in LDS hold
+    const int n_bpow = min(min(w.k_cut, 2 * (w.nmx + w.nmy) + 8), kPow - 1), n_zpow = min(w.nmz, kMaxP);
     const bool below = w.az.src < w.az.mic, in_steps = axis_in_order(w.az);
     const long long n_columns = 2ll * (2 * nmx + 1) * niy;
     const double r_in = w.n0 > 0 ? (double)(w.n0 - 1) / w.k_fs_c : 0.0, inv_2l = 1.0 / w.two_l;
@@ -739,7 +748,7 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, c
         // (beyond the first shell the shell's own inner radius bounds the distance well enough)
         const int kz_max = (w.n0 > 0 ? w.k_cut : reflection_cut(w.inv_log2_beta, sqrtf((float)a))) - kxy;
         if (!(a < w.r_out2) || kz_max < 0) continue;
-        const double bxy = COUNT ? 0.0 : (double)(kxy < kPow ? bpow[kxy] : beta_pow_slow(w.beta, kxy));
+        const double bxy = COUNT ? 0.0 : (double)(kxy <= n_bpow ? bpow[kxy] : kxy < kPow ? (float)table_power(w.beta, kxy) : beta_pow_slow(w.beta, kxy));
         const double far = sqrt(w.r_out2 - a) + rounding, near = fmax(sqrt(fmax(r_in * r_in - a, 0.0)) - rounding, 0.0);
         const int nz = min(nmz, kz_max / 2 + 1);                     // |n - q| + |n| >= 2 |n| - 1
         for (int q = 0; q < 2; ++q) {
@@ -765,7 +774,7 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, c
                 if ((unsigned int)slot > w.top8 / 8u) continue;       // (eight times a slot beyond 2^29 would come round)
                 double amp = 0.0;
                 if (!COUNT) {
-                    const double z = p <= kMaxP ? zpow[p] : z_power(w.beta, p);
+                    const double z = p <= n_zpow ? zpow[p] : table_power(w.beta, 2 * p) * kAmplitude;
                     amp = __dmul_rn(z, q ? __dmul_rn(bxy, w.beta) : bxy);
                     if (list == 1) amp = __dmul_rn(amp, w.beta2);
                 }
@@ -809,7 +818,7 @@ __device__ __attribute__((noinline)) unsigned int walk_near(const ItemCtx& w, in
 
 // Prepares item `it`: all lanes of one wavefront compute the same, lane 0 writes.
 template <bool COUNT>
-__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, int rir_len, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
+__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
     ItemCtx c{};
     c.kind = kEnd;
     if (it < n_items) {
@@ -837,13 +846,9 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, int rir_le
             // (amplitude sums only; tap counts visit every image)
             c.inv_log2_beta = (!COUNT && g[9] > 0.f && g[9] < 1.f) ? 1.f / __log2f(g[9]) : 0.f;
             c.k_cut = reflection_cut(c.inv_log2_beta, (float)r_in);
-            // (of positions far outside, where no such bound holds, those of the whole response's radius, in whatever item they land)
-            auto most_n = [&](const Axis& ax1) {
-                return (int)ceil((axis_in_order(ax1) ? r_out : (double)rir_len / k_fs_c) / (2.0 * ax1.room)) + 1;
-            };
-            c.nmx = min(most_n(ax), c.k_cut / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
-            c.nmy = min(most_n(ay), c.k_cut / 2 + 1);
-            c.nmz = most_n(az);
+            c.nmx = min((int)ceil(r_out / (2.0 * ax.room)) + 1, c.k_cut / 2 + 1);          // |n - q| + |n| >= 2 |n| - 1
+            c.nmy = min((int)ceil(r_out / (2.0 * ay.room)) + 1, c.k_cut / 2 + 1);
+            c.nmz = (int)ceil(r_out / (2.0 * az.room)) + 1;
             c.k_fs_c = k_fs_c;
             // (in whole units of the estimate's 2^-16 tap, so that adding it to the magic number is exact; one unit
             // for the sum's rounding)
@@ -927,7 +932,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     auto prepare_next = [&](ItemCtx& ctx) {        // by one wavefront
         int it = 0;
         if (lane == 0) it = atomicAdd(&ctrl[1], 1);
-        prepare_item<COUNT>(ctx, rooms, rir_len, k_fs_c, items, uni(it), n_items, lane);
+        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane);
     };
 
     // sums start at zero and are left at zero where an item is written out
@@ -1202,7 +1207,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 } while (walked_to < n_live);
             }
         } else if (kind == kPlain) {
-            walked += walk_plain<COUNT>(c, bpow, zpow, hist);
+            walked += walk_plain<COUNT>(c, rir_len, bpow, zpow, hist);
         }
         if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1]);
     }
