@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "ecf3cc55a6230d74",
-    "varlen": {"rir": 78219242, "rir_spectrum": 202575909, "convolve": 1254578504, "mel": 612832888},
-    "throughput": {"rir": 430358318, "rir_spectrum": 1218104202, "convolve": 13984461762, "mel": 2175850729},
+    "digest": "41158b088053b3dc",
+    "varlen": {"rir": 72864204, "rir_spectrum": 202471170, "convolve": 1256960287, "mel": 612835959},
+    "throughput": {"rir": 415483888, "rir_spectrum": 1218177979, "convolve": 13989975525, "mel": 2175541239},
 }
 
 
