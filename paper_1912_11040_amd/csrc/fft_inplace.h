@@ -1,5 +1,6 @@
 // Complex FFT of N = 4096, 8192 or 16384 points in LDS by T = N / 16 threads, in place, for the overlap-save
-// convolution: the forward transform leaves its output in digit-reversed order, the inverse takes it from there, and
+// convolution, and of 1024 points by one wavefront for the waveform VTLP (which has its own steps A and B, with no barrier,
+// and no step C): the forward transform leaves its output in digit-reversed order, the inverse takes it from there, and
 // the product between them happens in the registers that the forward transform's last step and the inverse's first
 // step share.
 //
@@ -30,7 +31,7 @@ namespace aug {
 
 template <int N>
 struct InPlace {
-    static_assert(N == 4096 || N == 8192 || N == 16384, "transform size");
+    static_assert(N == 1024 || N == 4096 || N == 8192 || N == 16384, "transform size");
     static constexpr int T = N / 16, M = N / 16, M2 = N / 256;
     static constexpr int RD = N == 8192 ? 2 : 4, RC = M2 / RD;
     static constexpr int Y = 16 * RC;                   // butterflies of step D in a row

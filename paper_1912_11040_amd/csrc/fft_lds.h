@@ -1,7 +1,7 @@
 // Complex FFT of a power-of-two length N held in LDS and worked on by T = N/16 threads,
 // and the butterflies that the library's transforms share: the convolution for responses of up to 2048 taps
-// (N = 1024, 2048) and the waveform VTLP (N = 1024) run the passes below, the front end and the convolution for longer
-// responses (fft_inplace.h) have passes of their own.
+// (N = 1024, 2048) runs the passes below, the front end, the convolution for longer
+// responses and the waveform VTLP (fft_inplace.h) have passes of their own.
 //
 // Stockham autosort passes: a pass of radix R over sub-transforms of length NS reads, for
 // butterfly j < N/R, x[j + m N/R] (m < R), multiplies by exp(-+2 pi i (j mod NS) m / (NS R)),

@@ -62,6 +62,18 @@ def test_frames_shared_among_wavefronts(aug, n_frames):
     assert np.array_equal(got, _run(aug, offsets, wave, alpha))      # at most two shares per sample: any order
 
 
+@pytest.mark.parametrize("alpha", [0.05, 0.5, 1.0, 1.5, 1.95])
+def test_window_moves_and_strong_warps(aug, alpha):
+    # runs of 8 to 16 frames, in which the lanes' columns go round more than once, that begin at every place of their cycle of
+    # eight, with ends everywhere in a hop; warps that gather from a few bins and from all
+    lens = [400 * f + e for f, e in zip(range(9, 42), [0, 1, 2, 127, 128, 199, 200, 201, 399] * 4)]
+    rng = np.random.default_rng(int(100 * alpha))
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    wave = rng.standard_normal(int(offsets[-1])).astype(np.float32)
+    print(f"case: alpha {alpha}", flush=True)
+    _check(aug, offsets, wave, np.full(len(lens), alpha, np.float32))
+
+
 def test_tiny_speech(aug):
     w = W.tiny()
     print("case: tiny workload speech", flush=True)
