@@ -191,12 +191,40 @@ int ring_reserve(aug_ctx* ctx, size_t bytes) {
     return AUG_OK;
 }
 
+// The framing of a front-end call and the number of work groups that the chip runs at once of its kernel.
+struct Framing {
+    int win, hop, slots;
+};
+
+// The batch's frames shared out evenly, in consecutive stretches, among as many groups as run at once (fewer if there are not
+// that many units), so that a group meets few utterances and all end together.  In groups of so many rows of one utterance,
+// as many as made eight rounds, the last round was half empty and every group set up an utterance's tables for four passes of
+// sixteen frames: 256 padded utterances of 1-16 s 131 us, 99 so.  Shares of more than kUnitsPerGroup units are cut further: with
+// 200 each, 4096 utterances of 8 s waited for the slowest groups (1151 us; in twice as many 1132, four times 1097, eight times
+// 1100), while with 13 each every set-up counts (110, 115, 124, 138 us).
+constexpr int kUnitsPerGroup = 40;
+aug::FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* frame_offsets, const Framing& f) {
+    aug::FrameShares s;
+    for (;; ++s.shift) {                                     // (units of more frames where 31 bits would not number them)
+        int64_t units = 0;
+        for (int u = 0; u < n_utt; ++u)
+            units += aug::frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], f.win, f.hop, s.shift);
+        if (units >= 1 << 30) continue;
+        s.n_groups = (int)std::min<int64_t>(units, f.slots * std::max<int64_t>(units / ((int64_t)f.slots * kUnitsPerGroup), 1));
+        if (s.n_groups > 0) {
+            s.per_group = (int)(units / s.n_groups);
+            s.longer = (int)(units % s.n_groups);
+        }
+        return s;
+    }
+}
+
 // Write a batch's arrays into the next staging slot and point `pa` at them, without waiting for the stream; the caller
 // launches the packing (alone, or with the front end's set-up) and then calls packing_launched.  conv_block > 0 and
-// frame_offsets ask for that table; upload_offsets is false where the device already holds these offsets.  The slot's
-// arrays: offsets, frame offsets, block prefix, group prefix.
+// frame_offsets (with pa.shares) ask for that table; upload_offsets is false where the device already holds these offsets.  The
+// slot's arrays: offsets, frame offsets, block prefix, prefix of the front end's units.
 int stage_packing(aug_ctx* ctx, aug::PackArgs& pa, const int64_t* offsets, bool upload_offsets, int conv_block,
-                  const int64_t* frame_offsets) {
+                  const int64_t* frame_offsets, const Framing* framing) {
     aug::HostRing& r = ctx->ring;
     const int i = r.next, e = i / aug::HostRing::kPerEvent;
     if (i % aug::HostRing::kPerEvent == 0)
@@ -218,7 +246,7 @@ int stage_packing(aug_ctx* ctx, aug::PackArgs& pa, const int64_t* offsets, bool 
         int at = 0;
         for (int u = 0; u < pa.n_utt; ++u) {
             first[u] = at;
-            at += (int)((frame_offsets[u + 1] - frame_offsets[u] + pa.frames_per_group - 1) / pa.frames_per_group);
+            at += (int)aug::frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], framing->win, framing->hop, pa.shares.shift);
         }
         first[pa.n_utt] = at;
         pa.frame_first = reinterpret_cast<const int*>(d + 2 * i64 + n * sizeof(int));
@@ -274,14 +302,14 @@ struct PendingPack {
 // the arrays go to pinned staging and `pending` is left for the caller to launch, in stream order behind the earlier
 // calls' kernels: the call does not wait for the stream.
 int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* offsets, const int64_t* frame_offsets,
-                 int conv_block, int frames_per_group) {
+                 int conv_block, const Framing* framing) {
     aug::Packing& pk = ctx->packing;
     const size_t n = (size_t)n_utt + 1;
     const bool same_off = pk.offsets.size() == n && !memcmp(pk.offsets.data(), offsets, n * sizeof(int64_t));
     const bool need_conv = conv_block > 0 && !(same_off && pk.conv_block == conv_block);
     const bool need_fr = frame_offsets && !(same_off && pk.frame_offsets.size() == n &&
                           !memcmp(pk.frame_offsets.data(), frame_offsets, n * sizeof(int64_t)) &&
-                          pk.frames_per_group == frames_per_group);
+                          pk.win == framing->win && pk.hop == framing->hop && pk.frame_slots == framing->slots);
     if (same_off && !need_conv && !need_fr) return AUG_OK;
 
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
@@ -290,14 +318,12 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
         return fail(ctx, AUG_ERR_UNSUPPORTED, "the offsets differ from the previous call's: the tables cannot be "
                     "rebuilt while the stream is being captured (run the same call once before capturing it)");
 
-    int64_t n_conv = 0, n_groups = 0;
+    int64_t n_conv = 0;
     if (need_conv)
         for (int u = 0; u < n_utt; ++u) n_conv += (offsets[u + 1] - offsets[u] + conv_block - 1) / conv_block;
-    if (need_fr)
-        for (int u = 0; u < n_utt; ++u)
-            n_groups += (frame_offsets[u + 1] - frame_offsets[u] + frames_per_group - 1) / frames_per_group;
-    if (n_conv > 0x7fffffffLL || n_groups > 0x7fffffffLL)
-        return fail(ctx, AUG_ERR_UNSUPPORTED, "too many blocks or frame groups in one call");
+    if (n_conv > 0x7fffffffLL) return fail(ctx, AUG_ERR_UNSUPPORTED, "too many blocks in one call");
+    if (need_fr && frame_offsets[n_utt] >= (int64_t)1 << 40) return fail(ctx, AUG_ERR_UNSUPPORTED, "too many output rows in one call");
+    const aug::FrameShares shares = need_fr ? share_frames(n_utt, offsets, frame_offsets, *framing) : aug::FrameShares();
 
     aug::PackArgs& pa = pending.args;
     pa.n_utt = n_utt;                // from here on the record is dropped unless the launch follows
@@ -308,16 +334,16 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
     }
     if (need_fr) {
         AUG_TRY(grow(ctx, ctx->d_frame_offsets, n * sizeof(int64_t), "frame offsets buffer"));
-        AUG_TRY(grow(ctx, ctx->d_frame_items, (size_t)std::max<int64_t>(n_groups, 1) * sizeof(int2), "frame group table"));
+        AUG_TRY(grow(ctx, ctx->d_frame_items, (size_t)std::max(shares.n_groups, 1) * sizeof(int2), "frame group table"));
     }
     AUG_TRY(ring_reserve(ctx, ring_bytes(n)));
-    pa.frames_per_group = frames_per_group;
+    pa.shares = shares;
     pa.d_offsets = ctx->d_offsets.as<int64_t>();
     pa.d_frame_offsets = ctx->d_frame_offsets.as<int64_t>();
     pa.d_conv_first = ctx->d_conv_first.as<int>();
     pa.conv_items = ctx->d_conv_items.as<int2>();
     pa.frame_items = ctx->d_frame_items.as<int2>();
-    AUG_TRY(stage_packing(ctx, pa, offsets, !same_off, need_conv ? conv_block : 0, need_fr ? frame_offsets : nullptr));
+    AUG_TRY(stage_packing(ctx, pa, offsets, !same_off, need_conv ? conv_block : 0, need_fr ? frame_offsets : nullptr, framing));
 
     if (!same_off) {
         pk.offsets.assign(offsets, offsets + n);
@@ -330,8 +356,10 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
     }
     if (need_fr) {
         pk.frame_offsets.assign(frame_offsets, frame_offsets + n);
-        pk.frames_per_group = frames_per_group;
-        pk.n_frame_groups = n_groups;
+        pk.win = framing->win;
+        pk.hop = framing->hop;
+        pk.frame_slots = framing->slots;
+        pk.shares = shares;
     }
     return AUG_OK;
 }
@@ -405,7 +433,7 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
 }
 
 int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
-    if (n_utt == 0 || ctx->packing.n_frame_groups == 0) return AUG_OK;
+    if (n_utt == 0 || ctx->packing.shares.n_groups == 0) return AUG_OK;
     // (a table that grows loses its contents, also where a later one then runs out of memory)
     const size_t window_bytes = sizeof(float) * (size_t)cfg->win;
     if (window_bytes > ctx->window.bytes) ctx->window_n = 0;
@@ -518,7 +546,7 @@ const aug::MelTableArgs& mel_table_args(aug_ctx* ctx, const aug_frontend_cfg* cf
 
 // The front end's tables (they need no signal, so a call may enqueue this first) and the packing, if it is pending.
 int run_mel_setup(aug_ctx* ctx, PendingPack& pending, int n_utt, const float* alpha, const aug_frontend_cfg* cfg) {
-    if (n_utt == 0 || ctx->packing.n_frame_groups == 0) return pending.launch();
+    if (n_utt == 0 || ctx->packing.shares.n_groups == 0) return pending.launch();
     AUG_TRY(prepare_mel(ctx, n_utt, cfg));
     AUG_TRY(mark(ctx, -1));
     const bool mfcc = cfg->feature == AUG_FEAT_MFCC;
@@ -546,14 +574,14 @@ int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const aug_frontend_cfg* 
             const float* extra = nullptr, int64_t extra_stride = 0, const double* energy = nullptr,
             const float* snr_db = nullptr) {
     const aug::Packing& pk = ctx->packing;
-    if (n_utt == 0 || pk.n_frame_groups == 0) return AUG_OK;
+    if (n_utt == 0 || pk.shares.n_groups == 0) return AUG_OK;
     AUG_TRY(mark(ctx, -1));
     aug::MelArgs ma;
     ma.offsets = ctx->d_offsets.as<int64_t>();
     ma.frame_offsets = ctx->d_frame_offsets.as<int64_t>();
     ma.items = ctx->d_frame_items.as<int2>();
-    ma.n_items = pk.n_frame_groups;
-    ma.frames_per_group = pk.frames_per_group;
+    ma.n_items = pk.shares.n_groups;
+    ma.shares = pk.shares;
     ma.wave = wave;
     ma.extra = extra;
     ma.extra_stride = extra_stride;
@@ -770,7 +798,7 @@ int aug_convolve_mix_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, cons
     if ((!rir && n_utt > 0) || (!mixed_out && offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "rir or mixed_out is null");
     PendingPack pending(ctx);
-    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, aug::conv_plan(rir_len).block(), 0));
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, aug::conv_plan(rir_len).block(), nullptr));
     AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
     AUG_TRY(pending.launch());
     return run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out);
@@ -785,7 +813,8 @@ int aug_vtlp_mel_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((!wave && offsets[n_utt] > 0) || (!alpha && n_utt > 0) || (!feats_out && frame_offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave, alpha or feats_out is null");
     PendingPack pending(ctx);
-    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, 0, aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt])));
+    const Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, 0, &framing));
     AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
     return run_mel(ctx, n_utt, wave, cfg, feats_out);
 }
@@ -810,14 +839,10 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     if (count_groups(kStaticRows) > AUG_STATIC_MAX_ROW_GROUPS)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "%lld groups of %d output rows: the static scratch array holds at most %d",
                     (long long)count_groups(kStaticRows), kStaticRows, AUG_STATIC_MAX_ROW_GROUPS);
-    int fpg = aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt]);
-    int64_t n_groups = count_groups(fpg);
-    if (n_groups > AUG_STATIC_MAX_ROW_GROUPS) {          // smaller groups than that, and too many of them
-        fpg = kStaticRows;
-        n_groups = count_groups(fpg);
-    }
     if (cfg->win > 2048) return fail(ctx, AUG_ERR_UNSUPPORTED, "window longer than 2048 samples");
-    if (n_utt == 0 || n_groups == 0) return AUG_OK;
+    const Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
+    const aug::FrameShares shares = share_frames(n_utt, offsets, frame_offsets, framing);
+    if (n_utt == 0 || shares.n_groups == 0) return AUG_OK;
     unsigned char* const base = ctx->scratch;            // the device address, not the array's name
     if (!base) return fail(ctx, AUG_ERR_HIP, "the static scratch array is not available on this device");
     if (ctx->ring.bytes < ring_bytes((size_t)n_utt + 1)) return fail(ctx, AUG_ERR_HIP, "staging ring missing");
@@ -835,11 +860,11 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     sa.n_utt = n_utt;
     sa.pack = aug::PackArgs{};
     sa.pack.n_utt = n_utt;
-    sa.pack.frames_per_group = fpg;
+    sa.pack.shares = shares;
     sa.pack.d_offsets = d_off;
     sa.pack.d_frame_offsets = d_foff;
     sa.pack.frame_items = d_items;
-    AUG_TRY(stage_packing(ctx, sa.pack, offsets, true, 0, frame_offsets));
+    AUG_TRY(stage_packing(ctx, sa.pack, offsets, true, 0, frame_offsets, &framing));
     sa.table = mel_table_args(ctx, cfg, alpha, mel_tab);
     sa.lane_consts = lane_consts;
     sa.window = window;
@@ -850,8 +875,8 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
     ma.offsets = d_off;
     ma.frame_offsets = d_foff;
     ma.items = d_items;
-    ma.n_items = n_groups;
-    ma.frames_per_group = fpg;
+    ma.n_items = shares.n_groups;
+    ma.shares = shares;
     ma.wave = wave;
     ma.extra = nullptr;
     ma.extra_stride = 0;
@@ -888,7 +913,7 @@ int aug_vtlp_resynth_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, cons
     if (total > 0 && wave_out < wave + total && wave < wave_out + total)
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave_out overlaps wave");
     PendingPack pending(ctx);
-    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, 0, 0));
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, nullptr, 0, nullptr));
     AUG_TRY(pending.launch());
     if (n_utt == 0 || total == 0) return AUG_OK;
     int64_t max_len = 0;
@@ -923,8 +948,8 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((int64_t)n_utt * n_src * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
     PendingPack pending(ctx);
-    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_plan(rir_len).block(),
-                         aug::mel_rows_per_group(ctx->n_cu, frame_offsets[n_utt])));
+    const Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, !mixed_out && n_noise > 0)};
+    AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_plan(rir_len).block(), &framing));
     const int64_t total = offsets[n_utt];
     float* rir = rir_out;
     if (!rir) {

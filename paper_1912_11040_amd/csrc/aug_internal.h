@@ -21,15 +21,29 @@ struct DeviceBuffer {
     template <class T> T* as() const { return static_cast<T*>(ptr); }
 };
 
+// How the front end's work is shared among its groups.  An utterance's frames are cut into units of 16 << shift (one unit if it
+// has rows but no frames), numbered in the utterances' order; group g takes those from g per_group + min(g, longer), per_group of
+// them, the first `longer` groups one more.
+struct FrameShares {
+    int n_groups = 0, per_group = 0, longer = 0, shift = 0;
+};
+constexpr int kUnitFrames = 16;              // the frames that a group of the front end has in flight
+inline int64_t frame_units(int64_t len, int64_t rows, int win, int hop, int shift) {
+    if (rows <= 0) return 0;
+    const int64_t frames = len < win ? 0 : 1 + (len - win) / hop;
+    return frames > 0 ? ((frames - 1) >> (4 + shift)) + 1 : 1;
+}
+
 // Host-side description of how the packed utterances are cut into work items;
 // rebuilt only when the offsets of a call differ from the cached ones.
 struct Packing {
     std::vector<int64_t> offsets;        // n_utt + 1
     std::vector<int64_t> frame_offsets;  // n_utt + 1 (empty if not a front-end call)
     int conv_block = 0;                  // output samples per convolution block the tables were built for
-    int frames_per_group = 0;            // frames per front-end work group the tables were built for
+    int win = 0, hop = 0;                // the framing that the front end's work was shared out for
+    int frame_slots = 0;                 // work groups it was shared among at most
     int64_t n_conv_blocks = 0;           // sum over utterances of ceil(len / conv_block)
-    int64_t n_frame_groups = 0;
+    FrameShares shares;
 };
 
 // Pinned host staging for the offset arrays: a call writes its arrays into the next slot and the packing kernel
@@ -47,10 +61,10 @@ struct HostRing {
 
 // Device copies of a batch's offsets and its item tables, from the arrays that the host has left in pinned
 // memory: offsets, frame offsets and the exclusive prefix sums of the items per utterance (blocks of the
-// convolution; groups of frames_per_group output rows), n_utt + 1 entries each.  A null source is skipped.
+// convolution; units of the front end, see FrameShares), n_utt + 1 entries each.  A null source is skipped.
 struct PackArgs {
     int n_utt;
-    int frames_per_group;
+    FrameShares shares;
     const int64_t* offsets;          // pinned host memory, as the device sees it
     const int64_t* frame_offsets;
     const int* conv_first;
@@ -59,7 +73,7 @@ struct PackArgs {
     int64_t* d_frame_offsets;
     int* d_conv_first;
     int2* conv_items;                // (utterance, block)
-    int2* frame_items;               // (utterance, first row)
+    int2* frame_items;               // (utterance, unit of it) at which a group begins
 };
 // Per-utterance (band, weight) table of the warped mel bank followed by how the filters are dealt to the matrix
 // cores: tab float2 [n_utt][mel_table_stride(nfft)].  mel_edges fills in what depends on the configuration only.
@@ -82,7 +96,7 @@ struct aug_ctx {
     aug::DeviceBuffer d_offsets;         // int64 [n_utt+1]
     aug::DeviceBuffer d_frame_offsets;   // int64 [n_utt+1]
     aug::DeviceBuffer d_conv_items;      // int2 [n_conv_blocks]: (utterance, block)
-    aug::DeviceBuffer d_frame_items;     // int2 [n_frame_groups]: (utterance, first frame)
+    aug::DeviceBuffer d_frame_items;     // int2 [shares.n_groups]: (utterance, unit of it) at which a group begins
     aug::DeviceBuffer d_conv_first;      // int [n_utt+1]: blocks of the utterances before u
     aug::HostRing ring;
     unsigned char* scratch = nullptr;    // this device's copy of the library's static scratch array
@@ -206,7 +220,7 @@ hipError_t launch_convolve(hipStream_t s, int fft_n, const float2* twiddle, cons
 // non-zero tap.)
 __device__ inline float snr_gain(const double* energy, int j, float snr_db) {
     const double e0 = energy[0], ej = energy[1 + j];
-    return e0 > 0.0 && ej > 0.0 ? (float)sqrt(e0 / (ej * pow(10.0, (double)snr_db / 10.0))) : 0.f;
+    return e0 > 0.0 && ej > 0.0 ? (float)sqrt(e0 / (ej * exp10(0.1 * (double)snr_db))) : 0.f;
 }
 // gains_out [n_utt][n_src - 1]
 hipError_t launch_gains(hipStream_t s, int n_utt, int n_src, const double* energy, const float* snr_db, float* gains_out);
@@ -236,13 +250,26 @@ hipError_t launch_mel_setup(hipStream_t s, const MelSetupArgs& a);
 int twiddle_entries(int n);
 hipError_t launch_twiddle(hipStream_t s, int n, float2* tw);
 
+// The front end's LDS per group in bytes: frame buffers of 272 floats, weights, pieces, constants, for cepstra the cosine table.
+inline size_t mel_lds_bytes(const aug_frontend_cfg& cfg) {
+    size_t lds = 4 * kUnitFrames * 272 + 16 * 8 * 64 + 16 * AUG_MAX_MEL + 8 * (8 * 16 + 256) + 4 * AUG_MAX_NOISE;
+    if (cfg.feature == AUG_FEAT_MFCC) lds += 16 * (size_t)((cfg.n_mel + 3) / 4) * ((cfg.n_ceps + 15) & ~15);
+    return lds;
+}
+// Groups of the front end that the chip runs at once: four wavefronts per SIMD with a window of 400 samples and no mixture, three
+// otherwise, and what the LDS allows.
+inline int mel_slots(int n_cu, const aug_frontend_cfg& cfg, bool mix) {
+    const int by_waves = cfg.win == 400 && !mix ? 4 : 3, by_lds = (int)((160 * 1024) / (mel_lds_bytes(cfg) + 1280));
+    return n_cu * (by_lds < 1 ? 1 : by_lds < by_waves ? by_lds : by_waves);
+}
+
 // STFT power -> warped mel -> power law.
 struct MelArgs {
     const int64_t* offsets;        // device
     const int64_t* frame_offsets;  // device
-    const int2* items;             // device (utterance, first frame of the group)
-    int64_t n_items;
-    int frames_per_group;
+    const int2* items;             // device (utterance, unit of it) at which a group begins
+    int64_t n_items;               // shares.n_groups
+    FrameShares shares;
     const float* wave;
     // Mixing on the fly: when n_extra > 0 the analysed signal is
     // wave[n] + sum_j gain[u][j] * extra[j * extra_stride + n], j < n_extra, with the gains of snr_gain.
@@ -258,7 +285,6 @@ struct MelArgs {
     aug_frontend_cfg cfg;
     float* feats;
 };
-int mel_rows_per_group(int n_cu, int64_t rows);
 hipError_t launch_mel(hipStream_t s, const MelArgs& a);
 
 // Waveform VTLP: per-utterance table of (lower source bin, interpolation weight) for every output bin,

@@ -20,7 +20,6 @@ namespace aug {
 namespace {
 
 constexpr int kMelThreads = 256;
-constexpr int kFramesPerGroup = 64;        // output rows per work group of an ordinary batch (see mel_rows_per_group)
 
 // sample i of the symmetric Hamming window
 __device__ inline float hamming(int i, int win) {
@@ -233,14 +232,13 @@ constexpr int kStagedHop = (64 * 4 * kStageLoads - 400) / 3;      // largest hop
 // logarithm instruction does not take denormal inputs, so tiny energies are scaled into range first.
 __device__ inline float power_law(float e, float power) {
     const bool tiny = e < 0x1p-100f;
-    const float l = __builtin_amdgcn_logf(tiny ? e * 0x1p+64f : e) - (tiny ? 64.f : 0.f);
-    return __builtin_amdgcn_exp2f(power * l);
+    return __builtin_amdgcn_exp2f(power * (__builtin_amdgcn_logf(e * (tiny ? 0x1p+64f : 1.f)) - (tiny ? 64.f : 0.f)));
 }
 
 // the value that lane (16 - i) mod 16 of a row of sixteen lanes holds, for lane i: mirrored, then rotated by one
 __device__ inline float row_negate(float x) {
-    const int m = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xf, 0xf, false);         // row_mirror
-    return __int_as_float(__builtin_amdgcn_mov_dpp(m, 0x121, 0xf, 0xf, false));                // row_ror:1
+    const int m = __builtin_amdgcn_mov_dpp(__float_as_int(x), 0x140, 0xf, 0xf, true);          // row_mirror
+    return __int_as_float(__builtin_amdgcn_mov_dpp(m, 0x121, 0xf, 0xf, true));                 // row_ror:1
 }
 
 typedef float vec4 __attribute__((ext_vector_type(4)));
@@ -263,111 +261,49 @@ __device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2&
 // WIN: the window length when it is known at compile time (the paper's front end uses 400), else 0.  MIX: the signal is
 // mixed on the fly.  STAGED: by way of LDS (see the launcher).
 //
-// What bounds it: vector issue (about 650 vector instructions per pass of four frames, 0.97 of one in four cycles on
-// 4096 utterances of 8 s), with the LDS busy half the time.  The first design sent the second pass's outputs through
+// A group takes an equal share of the batch's frames (FrameShares), utterance by utterance.
+//
+// What bounds it: vector issue (655 vector instructions per pass of four frames, 0.97 of one in four cycles on
+// 4096 utterances of 8 s, at a clock that falls to 1.8 GHz under them), with the LDS busy half the time.  The first design sent the
+// second pass's outputs through
 // LDS to pair the bins and summed the bands from step lists there: 770 vector and 126 LDS instructions, a third
 // of the LDS's cycles bank conflicts.  Pairing by row permutations, twiddles folded into multiply-adds and the
 // projection on the matrix cores, which read every power once and need no vector arithmetic, took that batch from
 // 1500 to 1080-1140 us; cepstra from a cosine table in LDS instead of global memory, 256 padded utterances from 350
-// to 134 us.  (The first radix-16 pass on the matrix cores as well measured slower, 1350 us: products of 32-bit
-// floats there take the vector units' time.)
+// to 134 us, and equal shares, set up from loads that are all on their way at once, to 99.  With a mixture it waits for memory:
+// 152 us for four sources of 256 utterances of 1-16 s (0.56 GB).
+// (The first radix-16 pass on the matrix cores as well measured slower, 1350 us: products of 32-bit
+// floats there take the vector units' time.  Requesting a frame's samples a pass ahead without a mixture as well does not fit
+// the registers of four wavefronts per SIMD: 4096 utterances 1251 us.)
 template <int WIN, bool MIX, bool STAGED>
 __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(MelArgs a, int tab_stride) {
     constexpr int NC = 256;
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ int s_wide;                               // some channel has more than four pieces
     const int n_mel = a.cfg.n_mel;
     const int feature = a.cfg.feature;
     const int n_out = feature == AUG_FEAT_MFCC ? a.cfg.n_ceps : n_mel;     // values per output row
     float* const slots = reinterpret_cast<float*>(smem);                     // [kMelSlots][kSlotFloats]
     vec4* const s_weight = reinterpret_cast<vec4*>(slots + kMelSlots * kSlotFloats);       // [kMaxSteps / 4][64]
-    int2* const s_pieces = reinterpret_cast<int2*>(s_weight + kMaxSteps / 4 * 64);          // [n_mel]: a channel's sums
+    int4* const s_pieces = reinterpret_cast<int4*>(s_weight + kMaxSteps / 4 * 64);          // [n_mel]: a channel's sums (see energy)
     float2* const s_pair = reinterpret_cast<float2*>(s_pieces + AUG_MAX_MEL);               // [kLanePairs][kMelLanes]
     float2* const s_window = s_pair + kLanePairs * kMelLanes;                               // [256]
     float* const s_gains = reinterpret_cast<float*>(s_window + NC);                         // [AUG_MAX_NOISE]
     vec4* const s_dct = reinterpret_cast<vec4*>(s_gains + AUG_MAX_NOISE);                             // [n_mel / 4][n_out up to 16s]
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int slot = tid / kMelLanes, sub = tid % kMelLanes;
-    // Group ids are dealt round-robin to the eight XCDs.  XCD x takes the x-th contiguous eighth of the item
-    // list, so that every XCD gets the same mix of full and nearly empty groups whatever the period of the
-    // list (equal utterances of four groups each would otherwise leave two XCDs with the short groups only),
-    // and groups that read neighbouring frames of an utterance share an L2.
+    int tid = threadIdx.x, lane = tid & 63, slot = tid / kMelLanes, sub = tid % kMelLanes;
+    // Group ids are dealt round-robin to the eight XCDs.  XCD x takes the x-th contiguous eighth of the shares, so that groups
+    // that read neighbouring frames of an utterance share an L2.
     const unsigned int xcd = blockIdx.x % 8u, nth = blockIdx.x / 8u;
     const unsigned int item = xcd * (gridDim.x / 8u) + min(xcd, gridDim.x % 8u) + nth;
-    const int u = a.items[item].x;
-    const int64_t start = a.offsets[u];
-    const float* x = a.wave + start;
+    int u = a.items[item].x, unit = a.items[item].y;
     const int win = WIN ? WIN : a.cfg.win, hop = a.cfg.hop;
-    // The utterance owns rows_u rows of the output; the first n_frames_u hold its frames and the rest,
-    // if the caller reserved more (padded batches), are set to zero.
-    const int64_t len = a.offsets[u + 1] - start;
-    const int64_t rows_u = a.frame_offsets[u + 1] - a.frame_offsets[u];
-    const int64_t n_frames_u = len >= win ? 1 + (len - win) / hop : 0;
-    // The utterance's rows are shared evenly among its groups, ceil(rows / frames_per_group) of them (as the
-    // item table counts them), in multiples of the frames a group has in flight: no group is left with a few rows.
-    const int groups_u = (int)((rows_u + a.frames_per_group - 1) / a.frames_per_group);
-    const int rows_per_group = (int)(((rows_u + groups_u - 1) / groups_u + kMelSlots - 1) / kMelSlots) * kMelSlots;
-    const int first = (a.items[item].y / a.frames_per_group) * rows_per_group;
     const float power = a.cfg.power;
-    float* feats = a.feats + (size_t)a.frame_offsets[u] * n_out;
-    float* const buf = slots + slot * kSlotFloats;       // the frame's buffer
-    float* const wave_buf = slots + (slot & ~3) * kSlotFloats;     // the four frames of this wavefront
-
-    if (MIX && tid >= kMelThreads - 64 && tid - (kMelThreads - 64) < a.n_extra) {
-        const int j = tid - (kMelThreads - 64);
-        s_gains[j] = snr_gain(a.energy + (size_t)u * (a.n_extra + 1), j, a.snr_db[(size_t)u * a.n_extra + j]);
-    }
-    // the utterance's tables: the plan, and from it the weights in the order in which the lanes use them
-    const float2* g_tab = a.mel_tab + (size_t)u * tab_stride;
-    const MelPlan* plan = reinterpret_cast<const MelPlan*>(g_tab + (NC + 1));
-    const int rounds = plan->rounds, steps = plan->steps;
-    for (int e = tid; e < rounds * (steps / 4) * 64; e += kMelThreads) {
-        const int l = e & 63, q = e >> 6, r = q / (steps / 4), s0 = 4 * (q - r * (steps / 4));
-        const int piece = plan->piece[16 * r + (l >> 2)];
-        vec4 w = {0.f, 0.f, 0.f, 0.f};
-        if (piece != kNoPiece) {
-            const int begin = piece & 1023, m = 4 * (piece >> 10) + (l & 3);
-            const int k0 = min(begin, kBinsPadded - steps) + s0;             // (a piece at the end starts earlier, to stay inside)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int k = k0 + i;
-                if (k >= begin && k <= NC) {
-                    const float2 cw = g_tab[k];
-                    const int c = (int)cw.x;
-                    w[i] = c == m ? cw.y : (c == m + 1 ? 1.f - cw.y : 0.f);
-                }
-            }
-        }
-        s_weight[q * 64 + l] = w;
-    }
-    for (int m = tid; m < n_mel; m += kMelThreads) {
-        const int p0 = plan->first_piece[m / 4], p1 = plan->first_piece[m / 4 + 1];
-        s_pieces[m] = make_int2(4 * p0 + (m & 3), p1 - p0);
-    }
-    const int q_pad = (n_out + kMelLanes - 1) & ~(kMelLanes - 1);
-    if (feature == AUG_FEAT_MFCC) {                       // cosine rows by fours of channels, zero past the last
-        for (int e = tid; e < (n_mel + 3) / 4 * q_pad; e += kMelThreads) {
-            const int m4 = e / q_pad, q = e - m4 * q_pad;
-            vec4 d = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (q < n_out && 4 * m4 + i < n_mel) d[i] = a.dct[q * n_mel + 4 * m4 + i];
-            s_dct[e] = d;
-        }
-    }
-    // where this lane's block starts to read powers, per round
-    int at[kMaxRounds];
-#pragma unroll
-    for (int r = 0; r < kMaxRounds; ++r) {
-        const int piece = r < rounds ? plan->piece[16 * r + (lane >> 2)] : kNoPiece;
-        at[r] = (lane & 3) * kSlotFloats + (piece == kNoPiece ? 0 : min(piece & 1023, kBinsPadded - steps));
-    }
-
     // Window samples, z[n] = w[2n] x[2n] + i w[2n+1] x[2n+1], halved: the even/odd split below then needs no halves of
     // its own.  Lane sub takes n = sub + 16 m.
     constexpr int kRows = WIN ? (WIN + 2 * kMelLanes - 1) / (2 * kMelLanes) : 16;     // rows m with any sample in the window
     static_assert(kRows == 16 || kRows == 13, "the first butterflies are written for 13 or 16 rows");
-    s_window[tid] = make_float2(2 * tid < win ? 0.5f * a.window[2 * tid] : 0.f, 2 * tid + 1 < win ? 0.5f * a.window[2 * tid + 1] : 0.f);
+    const float2 window = make_float2(2 * tid < win ? 0.5f * a.window[2 * tid] : 0.f, 2 * tid + 1 < win ? 0.5f * a.window[2 * tid + 1] : 0.f);
     Tw16Short tw;
     {
         float f[2 * kTw4Floats];
@@ -379,14 +315,16 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     // The window and the tangents and cosines of the split's twiddles are read from LDS where they are used: in registers
     // they would cost a wavefront per SIMD, and a wavefront alone issues a vector instruction only every six cycles
     // where the SIMD could take one every two.
-    if (tid < kLanePairs * kMelLanes) {
-        const int i = tid / kMelLanes, l = tid % kMelLanes;
-        s_pair[tid] = make_float2(a.lane_consts[(kMelTwFloats + 2 * i) * kMelLanes + l], a.lane_consts[(kMelTwFloats + 2 * i + 1) * kMelLanes + l]);
-    }
-    __syncthreads();
-
+    const int pair = 2 * (tid / kMelLanes % kLanePairs) + kMelTwFloats;
+    const float2 pair_consts = make_float2(a.lane_consts[pair * kMelLanes + sub], a.lane_consts[(pair + 1) * kMelLanes + sub]);
+    // The group's share: consecutive units of the utterances' frames (see FrameShares), the first of them unit `unit` of utterance u;
+    // its part of an utterance is a stretch.
+    int left = a.shares.per_group + ((int)item < a.shares.longer ? 1 : 0);
+    const int shift = a.shares.shift + 4;
+    // what changes from utterance to utterance
+    const float *x, *extra = nullptr;
+    int len, n_frames_u;
     [[maybe_unused]] const bool even_win = (win & 1) == 0;
-    const float* extra = MIX ? a.extra + start : nullptr;
     const float* gains = s_gains;
 
     // With STAGED the samples of a wavefront's four frames, which overlap, are staged: 16 bytes
@@ -396,13 +334,12 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     static_assert(!STAGED || (WIN == 400 && MIX), "staging is written for a mixture and 400 samples");
     constexpr int kMore = MIX ? kAheadExtra : 0;
     const int staged = STAGED ? (3 * hop + 400 + 3) & ~3 : 0;
-    const int wave_first = __builtin_amdgcn_readfirstlane(first + (slot & ~3));
     // where this lane's i-th four samples lie among those of the frames t_wave .. t_wave + 3 (the last four that exist, if
     // there are no more)
-    auto limit = [&](int t_wave) { return (int)min((int64_t)staged, len - (int64_t)t_wave * hop) - 4; };
+    auto limit = [&](int t_wave) { return min(staged, len - t_wave * hop) - 4; };
     auto place = [&](int i, int most) { return min(4 * lane + 256 * i, most); };
     auto load = [&](SampleQuad (&q)[kStageLoads], const float* src, int t_wave) {
-        const char* base = reinterpret_cast<const char*>(src + (int64_t)t_wave * hop);
+        const char* base = reinterpret_cast<const char*>(src + t_wave * hop);
         const int most = limit(t_wave);
 #pragma unroll
         for (int i = 0; i < kStageLoads; ++i) q[i] = *reinterpret_cast<const SampleQuad*>(base + 4u * (uint32_t)place(i, most));
@@ -427,17 +364,120 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
             }
         }
     };
-    if (STAGED) request(wave_first);
 
-    const int passes = rows_per_group / kMelSlots;
-    for (int it = 0; it < passes; ++it) {
-        const int64_t t = (int64_t)first + it * kMelSlots + slot;
-        const int t_wave = wave_first + it * kMelSlots;
-        if (t_wave >= n_frames_u) {                       // only padding rows are left for this wavefront
-            if (t < rows_u)
-                for (int m = sub; m < n_out; m += kMelLanes) feats[t * n_out + m] = 0.f;
-            continue;
+    // What the next stretch needs, all loads side by side: the utterance's table and plan, from which the weights are formed in LDS
+    // (where the frames' buffers will be), its energies, a lane of the last wavefront per gain, and the first samples.
+    float2* const s_tab = reinterpret_cast<float2*>(slots);                                 // [NC + 1 + kPlanEntries]
+    static_assert(NC + 1 + kPlanEntries <= 2 * kMelThreads && sizeof(float2) * 2 * kMelThreads <= sizeof(float) * kMelSlots * kSlotFloats, "the table in LDS");
+    float2 tab0, tab1;
+    double energies[2];
+    float snr;
+    int units, units_u, wave_first;
+    int64_t rows_u;
+    float* feats;
+    auto has_gain = [&] { return MIX && tid >= kMelThreads - 64 && tid - (kMelThreads - 64) < a.n_extra; };
+    auto begin_stretch = [&] {
+        // The utterance owns rows of the output; the first n_frames_u hold its frames and the rest, if the caller reserved
+        // more (padded batches), are set to zero.  (Utterances are shorter than 2^30 samples: checked on the host.)
+        const int64_t start = a.offsets[u], first_row = a.frame_offsets[u];
+        rows_u = a.frame_offsets[u + 1] - first_row;
+        len = (int)(a.offsets[u + 1] - start);
+        const float2* g_tab = a.mel_tab + (size_t)u * tab_stride;
+        tab0 = g_tab[tid];
+        tab1 = g_tab[min(tid + kMelThreads, NC + kPlanEntries)];
+        if (has_gain()) {
+            const double* const e = a.energy + (size_t)u * (a.n_extra + 1);
+            energies[0] = e[0];
+            energies[1] = e[1 + tid - (kMelThreads - 64)];
+            snr = a.snr_db[(size_t)u * a.n_extra + tid - (kMelThreads - 64)];
+        } else {
+            energies[0] = energies[1] = 0.0;
+            snr = 0.f;
         }
+        x = a.wave + start;
+        if (MIX) extra = a.extra + start;
+        feats = a.feats + first_row * n_out;
+        n_frames_u = len >= win ? 1 + (len - win) / hop : 0;
+        units_u = n_frames_u > 0 ? ((n_frames_u - 1) >> shift) + 1 : 1;
+        units = min(left, units_u - unit);
+        wave_first = __builtin_amdgcn_readfirstlane((unit << shift) + (slot & ~3));
+        if (STAGED) request(wave_first);
+    };
+    begin_stretch();
+    s_window[tid] = window;
+    if (tid < kLanePairs * kMelLanes) s_pair[tid] = pair_consts;
+    const int q_pad = (n_out + kMelLanes - 1) & ~(kMelLanes - 1);
+    if (feature == AUG_FEAT_MFCC) {                       // cosine rows by fours of channels, zero past the last
+        for (int e = tid; e < (n_mel + 3) / 4 * q_pad; e += kMelThreads) {
+            const int m4 = e / q_pad, q = e - m4 * q_pad;
+            vec4 d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (q < n_out && 4 * m4 + i < n_mel) d[i] = a.dct[q * n_mel + 4 * m4 + i];
+            s_dct[e] = d;
+        }
+    }
+    for (;;) {
+    // (opaque: addresses are formed anew for every stretch, kept from one to the next they do not fit the registers)
+    asm volatile("" : "+v"(tid));
+    lane = tid & 63;
+    slot = tid / kMelLanes;
+    sub = tid % kMelLanes;
+    float* const buf = slots + slot * kSlotFloats;       // the frame's buffer
+    float* const wave_buf = slots + (slot & ~3) * kSlotFloats;     // the four frames of this wavefront
+    const float2* const g_tab = a.mel_tab + (size_t)u * tab_stride;
+    if (tid == 0) s_wide = 0;
+    s_tab[tid] = tab0;
+    if (tid + kMelThreads < NC + 1 + kPlanEntries) s_tab[tid + kMelThreads] = tab1;
+    // this stretch's part of the rows without frames
+    if (const int64_t spare = rows_u - n_frames_u; spare > 0) {
+        const int64_t from = n_frames_u + spare * unit / units_u, to = n_frames_u + spare * (unit + units) / units_u;
+        for (int64_t i = from * n_out + tid; i < to * n_out; i += kMelThreads) feats[i] = 0.f;
+    }
+    __syncthreads();
+    // from the plan, the weights in the order in which the lanes use them
+    const MelPlan* plan = reinterpret_cast<const MelPlan*>(s_tab + (NC + 1));
+    const int rounds = __builtin_amdgcn_readfirstlane(plan->rounds), steps = __builtin_amdgcn_readfirstlane(plan->steps);
+    for (int e = tid; e < rounds * (steps / 4) * 64; e += kMelThreads) {
+        const int l = e & 63, q = e >> 6, s4 = steps / 4, r = (q >= s4) + (q >= 2 * s4) + (q >= 3 * s4), s0 = 4 * (q - r * s4);
+        static_assert(kMaxRounds == 4, "the round of a step");
+        const int piece = plan->piece[16 * r + (l >> 2)];
+        vec4 w = {0.f, 0.f, 0.f, 0.f};
+        if (piece != kNoPiece) {
+            const int begin = piece & 1023, m = 4 * (piece >> 10) + (l & 3);
+            const int k0 = min(begin, kBinsPadded - steps) + s0;             // (a piece at the end starts earlier, to stay inside)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int k = k0 + i;
+                const float2 cw = s_tab[min(k, NC)];
+                const int c = (int)cw.x;
+                const float weight = c == m ? cw.y : (c == m + 1 ? 1.f - cw.y : 0.f);
+                w[i] = k >= begin && k <= NC ? weight : 0.f;
+            }
+        }
+        s_weight[q * 64 + l] = w;
+    }
+    for (int m = tid; m < n_mel; m += kMelThreads) {
+        const int p0 = plan->first_piece[m / 4], p1 = plan->first_piece[m / 4 + 1];
+        const int n = p1 - p0;
+        s_pieces[m] = make_int4(4 * p0 + (m & 3), n > 1 ? -1 : 0, n > 2 ? -1 : 0, n > 3 ? (n > 4 ? n : -1) : 0);
+        if (n > 4) s_wide = 1;
+    }
+    if (has_gain()) s_gains[tid - (kMelThreads - 64)] = snr_gain(energies, 0, snr);
+    // where this lane's block starts to read powers, per round
+    int at[kMaxRounds];
+#pragma unroll
+    for (int r = 0; r < kMaxRounds; ++r) {
+        const int piece = r < rounds ? plan->piece[16 * r + (lane >> 2)] : kNoPiece;
+        at[r] = (lane & 3) * kSlotFloats + (piece == kNoPiece ? 0 : min(piece & 1023, kBinsPadded - steps));
+    }
+    __syncthreads();
+
+    const bool wide = __builtin_amdgcn_readfirstlane(s_wide) != 0;
+    const int passes = units << (shift - 4);
+    for (int it = 0; it < passes; ++it) {
+        const int t_wave = wave_first + it * kMelSlots, t = t_wave + (slot & 3);
+        if (t_wave >= n_frames_u) break;                  // (no barrier before the stretch's end)
         const bool live = t < n_frames_u;
         float2 v[16];
         // With MIX the analysed signal is formed here, in source order: x + sum_j gains[j] extra_j.
@@ -472,10 +512,9 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
             for (int i = 0; i < kRows; ++i) v[i] = mine[min(sub + kMelLanes * i, WIN / 2 - 1)];    // (past the window: times zero)
             fft_sync();
         } else {
-            // Loads are unconditional: a slot past the utterance's last frame recomputes that last frame (its
-            // result is dropped) and inputs past the window are read from the frame's last samples and meet a
-            // zero window weight.
-            const int x0 = (int)(live ? t : n_frames_u - 1) * hop;
+            // Loads are unconditional: a slot past the utterance's last frame recomputes that last frame (its result is
+            // dropped) and inputs past the window are read from the frame's last samples and meet a zero window weight.
+            const int x0 = (live ? t : n_frames_u - 1) * hop;
             // (opaque in the general kernel, whose clamped positions would otherwise all be kept in registers)
             int at_sub = sub;
             if (!WIN) asm volatile("" : "+v"(at_sub));
@@ -584,29 +623,32 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
 
         // pieces of the projection: row i of a block is frame i of the wavefront, column j channel 4 quad + j
         if (rounds) {
+            // (opaque: comparisons with them are made where they are used, not kept in scalar registers all along)
+            int n_rounds = rounds, n_steps = steps;
+            asm volatile("" : "+s"(n_rounds), "+s"(n_steps));
             vec4 sums[kMaxRounds];
             const vec4* wq = s_weight + lane;
 #pragma unroll
             for (int r = 0; r < kMaxRounds; ++r) {
-                if (r >= rounds) break;
+                if (r >= n_rounds) break;
                 const vec4* pq = reinterpret_cast<const vec4*>(wave_buf + at[r]);
                 vec4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int q = 0; q < kMaxSteps / 4; ++q) {
-                    if (4 * q >= steps) break;
+                    if (4 * q >= n_steps) break;
                     const vec4 p = pq[q], w = wq[64 * q];
                     acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[0], w[0], acc0, 0, 0, 0);
                     acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[1], w[1], acc1, 0, 0, 0);
                     acc0 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[2], w[2], acc0, 0, 0, 0);
                     acc1 = __builtin_amdgcn_mfma_f32_4x4x1f32(p[3], w[3], acc1, 0, 0, 0);
                 }
-                wq += 64 * (steps / 4);
+                wq += 64 * (n_steps / 4);
                 sums[r] = acc0 + acc1;
             }
             fft_sync();                   // the powers are read before the sums take their place
 #pragma unroll
             for (int r = 0; r < kMaxRounds; ++r) {
-                if (r >= rounds) break;
+                if (r >= n_rounds) break;
                 float* to = wave_buf + 64 * r + lane;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) to[i * kSlotFloats] = sums[r][i];
@@ -617,13 +659,15 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         auto energy = [&](int m) {
             float e = 0.f;
             if (rounds) {
-                // (the first four at once, the few pieces of a wider quad after them; what lies behind a quad's
-                // last piece is read and dropped)
-                const int2 pc = s_pieces[m];
+                // (the first four at once, the few pieces of a wider quad after them; what lies behind a quad's last piece
+                // is read and masked out)
+                const int4 pc = s_pieces[m];
                 const float* from = buf + pc.x;
+                auto masked = [](float v, int mask) { return __int_as_float(__float_as_int(v) & mask); };
                 const float e0 = from[0], e1 = from[4], e2 = from[8], e3 = from[12];
-                e = ((pc.y > 0 ? e0 : 0.f) + (pc.y > 1 ? e1 : 0.f)) + ((pc.y > 2 ? e2 : 0.f) + (pc.y > 3 ? e3 : 0.f));
-                for (int i = 4; i < pc.y; ++i) e += from[4 * i];
+                e = (e0 + masked(e1, pc.y)) + (masked(e2, pc.z) + masked(e3, wide && pc.w ? -1 : pc.w));
+                if (wide)
+                    for (int i = 4; i < pc.w; ++i) e += from[4 * i];
             } else {
                 for (int k = 0; k <= NC; ++k) {
                     const float2 cw = g_tab[k];
@@ -642,14 +686,14 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         for (int m = sub; m < m_end; m += kMelLanes) {
             const float e = m < n_mel ? energy(m) : 0.f;
             if (feature == AUG_FEAT_POWER_LAW) {
-                if (live) feats[t * n_mel + m] = e > 0.f ? power_law(e, power) : 0.f;
+                if (live) feats[(int64_t)t * n_mel + m] = e > 0.f ? power_law(e, power) : 0.f;
             } else {
                 const float le = m < n_mel ? logf(fmaxf(e, a.cfg.log_floor)) : 0.f;
                 if (to_lds) {
                     fft_sync();
                     buf[m] = le;
                 } else if (live) {
-                    feats[t * n_mel + m] = le;
+                    feats[(int64_t)t * n_mel + m] = le;
                 }
             }
         }
@@ -669,34 +713,23 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
                 } else {
                     for (int m = 0; m < n_mel; ++m) acc[0] = fmaf(logf(fmaxf(energy(m), a.cfg.log_floor)), s_dct[(m / 4) * q_pad + q][m & 3], acc[0]);
                 }
-                if (live && q < n_out) feats[t * n_out + q] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                if (live && q < n_out) feats[(int64_t)t * n_out + q] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
             }
         }
-        if (!live && t < rows_u)
-            for (int m = sub; m < n_out; m += kMelLanes) feats[t * n_out + m] = 0.f;
         fft_sync();                       // everything is read before the next frame's exchange
+    }
+    left -= units;
+    if (left == 0) break;
+    do ++u;
+    while (a.frame_offsets[u + 1] == a.frame_offsets[u]);
+    unit = 0;
+    begin_stretch();
+    __syncthreads();                      // every wavefront is done with the tables and its frames
     }
 }
 
 }  // namespace
 
-// Output rows per work group of the front end (an upper bound: the kernel shares an utterance's rows evenly among its
-// groups), in multiples of the frames a group has in flight.  A group sets up its utterance's tables once, so a large
-// batch takes large groups, as long as the launch still has several times more of them than the chip runs at once (4096
-// utterances of 798 frames: 1.70 ms with 64 rows, 1.55 with 160, 1.51 with 400, of the kernel of that day).  A batch that
-// does not fill the chip with groups of 64 rows takes the smallest ones that all run at once: one pass instead of four
-// is what bounds a single utterance.
-int mel_rows_per_group(int n_cu, int64_t rows) {
-    const int64_t at_once = 3LL * n_cu;
-    int64_t fit;
-    if (rows <= kFramesPerGroup * at_once) {
-        fit = (rows + at_once - 1) / at_once;
-        fit = (fit + kMelSlots - 1) / kMelSlots * kMelSlots;
-        return fit < kMelSlots ? kMelSlots : (int)fit;
-    }
-    fit = rows / (8 * at_once) / kMelSlots * kMelSlots;
-    return (int)(fit < kFramesPerGroup ? kFramesPerGroup : fit > 8 * kFramesPerGroup ? 8 * kFramesPerGroup : fit);
-}
 int mel_lane_floats() { return kLaneConsts * kMelLanes; }
 
 int mel_table_stride(int nfft) { return nfft / 2 + 1 + kPlanEntries; }   // (c, w) per bin, then the plan
@@ -727,10 +760,9 @@ hipError_t launch_mel(hipStream_t s, const MelArgs& a) {
     if (a.cfg.nfft != 512) return hipErrorInvalidValue;
     constexpr int NC = 256;
     static_assert(kMelThreads == NC, "a thread per pair of window samples");
-    size_t lds = sizeof(float) * kMelSlots * kSlotFloats + sizeof(vec4) * (kMaxSteps / 4) * 64 + sizeof(int2) * AUG_MAX_MEL +
-                 sizeof(float2) * (kLanePairs * kMelLanes + NC) + sizeof(float) * AUG_MAX_NOISE;
-    if (a.cfg.feature == AUG_FEAT_MFCC)
-        lds += sizeof(vec4) * (size_t)((a.cfg.n_mel + 3) / 4) * ((a.cfg.n_ceps + kMelLanes - 1) & ~(kMelLanes - 1));
+    static_assert(kMelSlots == kUnitFrames && sizeof(float) * kSlotFloats == 4 * 272 && sizeof(vec4) * (kMaxSteps / 4) == 16 * 8 &&
+                  kLanePairs * kMelLanes == 8 * 16 && sizeof(int4) == 16, "mel_lds_bytes");
+    const size_t lds = mel_lds_bytes(a.cfg);
     const bool mix = a.n_extra > 0;
     // A window of 400 samples has kernels of its own for every hop; its mixtures are staged where the loads cover four frames
     // and the samples of a frame start on a pair.  (With hops of 161 and 240 the general kernel, 16 rows of inputs instead of

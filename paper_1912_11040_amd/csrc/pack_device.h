@@ -34,7 +34,20 @@ __device__ inline void pack_utterances(const PackArgs& a, int at) {
         if (a.conv_first) a.d_conv_first[u] = c0;
     }
     for (int i = l; i < c1 - c0; i += lanes) a.conv_items[c0 + i] = make_int2(u, i);
-    for (int i = l; i < f1 - f0; i += lanes) a.frame_items[f0 + i] = make_int2(u, i * a.frames_per_group);
+    if (f1 > f0) {
+        // the groups whose first unit is one of this utterance's
+        const FrameShares& s = a.shares;
+        const int of_longer = s.longer * (s.per_group + 1);
+        auto group_at = [&](int unit) {                 // the first group that begins at this unit or behind it (units < 2^30)
+            return unit <= of_longer ? (int)((unsigned int)(unit + s.per_group) / (unsigned int)(s.per_group + 1))
+                                     : s.longer + (int)((unsigned int)(unit - of_longer + s.per_group - 1) / (unsigned int)s.per_group);
+        };
+        const int end = group_at(f1);
+        for (int g = group_at(f0) + l; g < end; g += lanes) {
+            const int first = g * s.per_group + (g < s.longer ? g : s.longer);
+            a.frame_items[g] = make_int2(u, first - f0);
+        }
+    }
 }
 
 }  // namespace aug

@@ -3,9 +3,9 @@
 // The example queue of Sec. 2.2 hands over a new padded batch, with new utterance lengths, at every step,
 // so the tables that cut a batch into convolution blocks and frame groups are rebuilt per call:
 //   first[u]  = number of items of utterances 0..u-1 (exclusive prefix sum of per-utterance item counts)
-//   items[i]  = (u, index of item i within utterance u, times `step`)
-// Per-utterance item counts: ceil(len_u / conv_block) convolution blocks, ceil(rows_u / frames_per_group)
-// frame groups (rows_u = output rows the utterance owns).
+//   items[i]  = (u, index of item i within utterance u)
+// Per-utterance item counts: ceil(len_u / conv_block) convolution blocks, and units of the front end (FrameShares), whose table
+// has an entry per work group only: where its equal share of all units begins.
 //
 // The host, which counts the items anyway to size the grids, leaves the offsets and the prefix sums in pinned
 // memory; one kernel reads them from there, writes the device copies and spreads the items.  It is bound by
