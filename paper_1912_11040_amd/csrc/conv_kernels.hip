@@ -17,6 +17,8 @@
 // used: the mixture y_0 + sum_j g_j y_j is written by mix_kernel when the caller wants it, and formed by
 // the front end on the fly otherwise.
 
+#include <type_traits>
+
 #include "aug_internal.h"
 #include "fft_inplace.h"
 
@@ -173,11 +175,30 @@ struct __attribute__((aligned(4))) SamplePair { float x, y; };
 
 // Accesses at a per-lane 32-bit byte offset from a wave-uniform base: the address is then a scalar register
 // pair plus one vector register, with no 64-bit vector arithmetic per access.
+// The place `bytes` behind a wave-uniform base, itself kept in scalar registers: of rows a constant apart the compiler would otherwise
+// add the constants to the vector address, two instructions and a wait state per access.  (With that, and without the copies that
+// the first wavefront's special case and zeros for no next window cost all: 59 200 vector instructions per wavefront instead of 64 000
+// on 256 utterances of 1-16 s with three noises, whose kernel is bound as much by what is on its way to and from memory: without
+// the windows' traffic it would take 4.5 % less, without the stores' 4.2.)
+typedef const __attribute__((address_space(1))) char* GlobalRow;
+__device__ inline GlobalRow row_at(const void* base, uint32_t bytes) {
+    GlobalRow p = (GlobalRow)base + bytes;
+    asm("" : "+s"(p));
+    return p;
+}
+typedef float Pair __attribute__((ext_vector_type(2), aligned(4)));
+typedef float Quad __attribute__((ext_vector_type(4)));
 __device__ inline SamplePair load_pair(const float* base, uint32_t byte_off) {
     return *reinterpret_cast<const SamplePair*>(reinterpret_cast<const char*>(base) + byte_off);
 }
 __device__ inline float load_sample(const float* base, uint32_t byte_off) {
     return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + byte_off);
+}
+// element tid of row i, T elements a row
+template <int T>
+__device__ inline float4 load_quad(const float4* base, int i, int tid) {
+    const Quad v = *(const __attribute__((address_space(1))) Quad*)(row_at(base, 16u * T * (uint32_t)i) + 16u * (uint32_t)tid);
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 __device__ inline float2 load_bin(const float2* base, uint32_t byte_off) {
     return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(base) + byte_off);
@@ -210,7 +231,7 @@ __device__ inline void load_window(float2 (&v)[16], const float* x, int len, int
     const float* at = x + from;
     const uint32_t lane_off = 8u * (uint32_t)tid;
     auto whole_row = [&](int n1) {
-        const SamplePair s2 = load_pair(at + 2 * M * n1, lane_off);
+        const Pair s2 = *(const __attribute__((address_space(1))) Pair*)(row_at(at, 8 * M * n1) + lane_off);
         v[n1] = make_float2(s2.x, s2.y);
     };
     if (row >= 0) {
@@ -263,14 +284,12 @@ __device__ inline float store_block(const float2 (&v)[16], const ConvBlock& c, i
     const int left = c.len - row * (2 * M);                // samples up to the utterance's end
     float e[2] = {0.f, 0.f};                               // (chains of sixteen squares, however many rows there are)
     if (left >= 32 * M && first <= kOwn * (2 * M)) {     // whole and live: two-sample stores
-        char* dst = reinterpret_cast<char*>(yb) + 8u * (uint32_t)tid;
+        const uint32_t lane_off = 8u * (uint32_t)tid;
 #pragma unroll
         for (int n1 = kOwn; n1 < 16; ++n1) {
-            SamplePair s2;
-            s2.x = v[n1].x;
-            s2.y = v[n1].y;
-            *reinterpret_cast<SamplePair*>(dst + 8 * M * n1) = s2;
-            e[n1 / 8] += s2.x * s2.x + s2.y * s2.y;
+            const Pair s2 = {v[n1].x, v[n1].y};
+            *(__attribute__((address_space(1))) Pair*)(row_at(yb, 8 * M * n1) + lane_off) = s2;
+            e[n1 / 8] = fmaf(s2.x, s2.x, fmaf(s2.y, s2.y, e[n1 / 8]));
         }
     } else {
 #pragma unroll
@@ -299,13 +318,25 @@ __device__ inline double wave_energy(float e) {
 // any time they are on a few neighbouring signals, so a response spectrum and the halves that neighbouring windows have
 // in common are fetched from HBM once and found in L2 by the other groups, not re-read by one group a whole block later.
 // With two partitions (CONTIGUOUS) a group needs consecutive blocks of a signal, so it takes one contiguous range.
+// What a block needs of the tables comes by scalar loads (nothing here writes them), asked for a block ahead: by vector loads, where
+// it was needed, three round trips to the L2 and the wait for whatever was on its way before them stood between two barriers
+// of every block.  (With the scalar addresses, whole calls: measured responses 156.1 -> 154.0 us, 64 utterances of 4 s with 8000 taps
+// the kernel alone 45.4 -> 43.3.)
+template <class T>
+__device__ inline T scalar_load(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
+
 template <bool CONTIGUOUS>
 struct ConvWalk {
     const ConvArgs& a;
     int at, end, step;       // list position, end of the share, stride
     int u, nb, j, b;         // utterance, blocks of each of its sources, source, block
+    int64_t start;           // the utterance's first sample
+    int len;                 // and its length: utterances are shorter than 2^30 samples (checked on the host)
+    // of the next block: utterance, its prefix of the block table, its offsets; and the utterance of the block after that
+    int u1, f0, f1, u2;
+    int64_t o0, o1;
 
-    __device__ inline explicit ConvWalk(const ConvArgs& args) : a(args), u(0), nb(0), j(0), b(0) {
+    __device__ inline explicit ConvWalk(const ConvArgs& args) : a(args) {
         const int total = (int)(a.n_items * a.n_src);      // (the launcher refuses lists of 2^31 blocks or more)
         if (CONTIGUOUS) {
             at = (int)((int64_t)total * blockIdx.x / gridDim.x);
@@ -318,44 +349,71 @@ struct ConvWalk {
             end = (int)((int64_t)total * (team + 1) / teams);
             step = (int)gridDim.x / teams;
         }
-        if (at < end) locate();
+        if (at >= end) return;
+        u2 = utterance_at(at);
+        ask(u2);
+        arrive();
+        if (!CONTIGUOUS) u2 = utterance_ahead(step);
     }
-    // utterance u is the one that holds item at / n_src of the per-source block table
-    __device__ inline void locate() {
-        u = a.items[(unsigned int)at / (unsigned int)a.n_src].x;
-        nb = a.first[u + 1] - a.first[u];
-        const unsigned int r = (unsigned int)(at - a.first[u] * a.n_src);
+    // the utterance that holds a block is the one that holds block at / n_src of the per-source table
+    __device__ inline int utterance_at(int block) const {
+        return scalar_load(reinterpret_cast<const int*>(a.items) + 2 * (size_t)((unsigned int)block / (unsigned int)a.n_src));
+    }
+    __device__ inline int utterance_ahead(unsigned int by) const { return utterance_at((int)min((unsigned int)at + by, (unsigned int)end - 1u)); }
+    __device__ inline void ask(int of) {
+        u1 = of;
+        f0 = scalar_load(a.first + of);
+        f1 = scalar_load(a.first + of + 1);
+        o0 = scalar_load(a.offsets + of);
+        o1 = scalar_load(a.offsets + of + 1);
+    }
+    // what was asked for is where `at` is
+    __device__ inline void arrive() {
+        u = u1;
+        nb = f1 - f0;
+        start = o0;
+        len = (int)(o1 - o0);
+        const unsigned int r = (unsigned int)(at - f0 * a.n_src);
         j = (int)(r / (unsigned int)nb);
         b = (int)r - j * nb;
     }
     __device__ inline bool more() const { return at + step < end; }
+    // at the beginning of a block: the next block's tables are asked for
+    __device__ inline void look_ahead() {
+        if (CONTIGUOUS) return;
+        ask(u2);
+        u2 = utterance_ahead(2u * (unsigned int)step);
+    }
+    // to the next block; more() must hold
     __device__ inline void next() {
         at += step;
         if (!CONTIGUOUS) {
-            locate();
+            arrive();
         } else if (++b == nb) {
             b = 0;
             if (++j == a.n_src) {
                 j = 0;
                 do {
-                    ++u;
-                    nb = a.first[u + 1] - a.first[u];
+                    ask(u + 1);
+                    u = u1;
+                    nb = f1 - f0;
                 } while (nb == 0);
+                start = o0;
+                len = (int)(o1 - o0);
             }
         }
     }
     // spec_stride: float2 entries per partition
     __device__ inline ConvBlock describe(size_t spec_stride) const {
         ConvBlock c;
-        const int64_t start = a.offsets[u];
         const size_t uj = (size_t)u * a.n_src + j;
-        c.len = (int)(a.offsets[u + 1] - start);           // utterances are shorter than 2^30 samples (checked on the host)
+        c.len = len;
         c.x = (j == 0 ? a.speech : a.noise + (size_t)(j - 1) * a.total) + start;
         c.H = a.spec + uj * a.n_part * spec_stride;
         c.y = a.reverb + (size_t)j * a.reverb_stride + start;
         c.energy = a.energy + uj;
-        c.first = a.first_tap[uj * a.n_part];
-        if (CONTIGUOUS) c.first = min(c.first, a.first_tap[uj * a.n_part + 1]);
+        c.first = scalar_load(a.first_tap + uj * a.n_part);
+        if (CONTIGUOUS) c.first = min(c.first, scalar_load(a.first_tap + uj * a.n_part + 1));
         c.b = b;
         return c;
     }
@@ -391,9 +449,16 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         // hoisted out of the loop, where they would sit on top of the transforms' registers.
         int tid = tid0;
         asm volatile("" : "+v"(tid));
+        walk.look_ahead();
         fft_columns_forward<N>(v, tw, tid);
         fft_columns_store<N, T>(v, buf, tid);
         __syncthreads();
+        const bool more = walk.more();
+        ConvBlock nxt = cur;
+        if (more) {
+            walk.next();
+            nxt = walk.describe(N + 1);
+        }
 
         // the response spectrum of this thread's bins, requested now, used after the row transforms
         float2 hk[8], hn[8];
@@ -433,17 +498,14 @@ __global__ __launch_bounds__(T) void convolve_kernel(ConvArgs a, const float2* _
         __syncthreads();
 
         // the next block of the share: its inputs are requested now and arrive during the inverse transform
-        const bool more = walk.more();
-        ConvBlock nxt = cur;
         asm volatile("" : "+v"(tid));
         if (more) {
-            walk.next();
-            nxt = walk.describe(N + 1);
             load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, ROWS), tid);
         } else {
-            // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
+            // (assigned on this path too, so that the old inputs do not stay alive in registers up to here; to nothing, since zeros
+            // would be written ahead of the branch, in every round)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = make_float2(0.f, 0.f);
+            for (int i = 0; i < 16; ++i) asm volatile("" : "=v"(v[i].x), "=v"(v[i].y));
         }
 
         fft_rows_table<N, true>(buf, row_tw, tid);
@@ -482,11 +544,11 @@ __device__ inline void copy_tables(float* lds, const float* __restrict__ tab, in
 template <int N>
 __device__ inline void load_step_d(float4 (&q)[InPlace<N>::Units][InPlace<N>::kDQuads], const float* __restrict__ tab, int tid) {
     using P = InPlace<N>;
-    const float4* d = reinterpret_cast<const float4*>(tab + P::kD0) + tid;
+    const float4* const d = reinterpret_cast<const float4*>(tab + P::kD0);
 #pragma unroll
     for (int i = 0; i < P::Units; ++i)
 #pragma unroll
-        for (int k = 0; k < P::kDQuads; ++k) q[i][k] = d[(i * P::kDQuads + k) * P::T];
+        for (int k = 0; k < P::kDQuads; ++k) q[i][k] = load_quad<P::T>(d, i * P::kDQuads + k, tid);
 }
 
 // tangent of pair s (see inplace_table_value)
@@ -623,9 +685,19 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         const bool warm_up = MULTI && !have_prev;          // this pass only produces the spectrum of window b - 1
         if (!AHEAD) load_window<N, ROWS>(v, cur.x, cur.len, window_row(warm_up ? cur.b - 1 : cur.b, ROWS), tid);
 
+        walk.look_ahead();
         inplace_forward_ab<N>(v, buf, lds_tab, tid);
         flush_energy(tid);
         done_energy = nullptr;
+        const bool more = !warm_up && walk.more();
+        ConvBlock nxt = cur;
+        if (more) {
+            walk.next();
+            nxt = walk.describe(2 * kEntries);
+        }
+        const float4 middle = reinterpret_cast<const float4*>(cur.H)[N / 2];     // (used by thread 0 alone, which it must not keep waiting)
+        float4 middle1 = middle;
+        if (MULTI) middle1 = reinterpret_cast<const float4*>(cur.H)[kEntries + N / 2];
         float4 q[P::Units][P::kDQuads];
         load_step_d<N>(q, tab, tid);
         inplace_forward_c<N>(v, buf, lds_tab, tid);
@@ -634,38 +706,38 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         float4 sd[AHEAD ? 8 : 1];
         if (AHEAD) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sd[i] = H[i * T + tid];
+            for (int i = 0; i < 8; ++i) sd[i] = load_quad<T>(H, i, tid);
         }
         __syncthreads();
 
-#pragma unroll
-        for (int i = 0; i < P::Units; ++i) {
+        // (thread 0's unit 0 is not like the others: the first wavefront has code of its own for it, which the others neither run
+        // nor make room for)
+        auto unit = [&](auto first, int i) {
+            constexpr bool FIRST = decltype(first)::value;
             int pos_a, pos_b;
             P::unit(tid, i, pos_a, pos_b);
             float2 x[RD], y[RD], mid = make_float2(0.f, 0.f);
-            // (thread 0's unit 0 is told apart in the first wavefront only)
-            const bool thread0 = i == 0 && tid == 0;
-            if (i == 0) inplace_step_d<N, true>(x, y, mid, buf, pos_a, pos_b, q[i], thread0);
-            else inplace_step_d<N, false>(x, y, mid, buf, pos_a, pos_b, q[i], false);
+            const bool thread0 = FIRST && tid == 0;
+            inplace_step_d<N, FIRST>(x, y, mid, buf, pos_a, pos_b, q[i], thread0);
             if (warm_up) {
 #pragma unroll
                 for (int s = 0; s < RD; ++s) {
                     prev_a[MULTI ? i * RD + s : 0] = x[s];
                     prev_b[MULTI ? i * RD + s : 0] = cconj(y[RD - 1 - s]);
                 }
-                if (i == 0) prev_mid = mid;
-                continue;
+                if (FIRST) prev_mid = mid;
+                return;
             }
 #pragma unroll
             for (int s = 0; s < RD; ++s) {
                 const float2 A = x[s], B = cconj(y[RD - 1 - s]);
                 const float tau = pair_tangent<N>(q[i], s);
                 float2 zk, zn;
-                product_pair<false>(A, B, AHEAD ? sd[AHEAD ? i * RD + s : 0] : H[(i * RD + s) * T + tid], tau, zk, zn);
+                product_pair<false>(A, B, AHEAD ? sd[AHEAD ? i * RD + s : 0] : load_quad<T>(H, i * RD + s, tid), tau, zk, zn);
                 if (MULTI) {
                     float2& pa = prev_a[MULTI ? i * RD + s : 0];
                     float2& pb = prev_b[MULTI ? i * RD + s : 0];
-                    product_pair<true>(pa, pb, H[kEntries + (i * RD + s) * T + tid], tau, zk, zn);
+                    product_pair<true>(pa, pb, load_quad<T>(H + kEntries, i * RD + s, tid), tau, zk, zn);
                     pa = A;
                     pb = B;
                 }
@@ -673,18 +745,19 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
                 y[RD - 1 - s] = cconj(zn);
             }
             if (thread0) {                                 // the bin in the middle
-                const float4 h = H[N / 2];
-                float2 z = cmul(mid, make_float2(h.x, h.y));
+                float2 z = cmul(mid, make_float2(middle.x, middle.y));
                 if (MULTI) {
-                    const float4 h1 = H[kEntries + N / 2];
-                    z = cadd(z, cmul(prev_mid, make_float2(h1.x, h1.y)));
+                    z = cadd(z, cmul(prev_mid, make_float2(middle1.x, middle1.y)));
                     prev_mid = mid;
                 }
                 mid = z;
             }
-            if (i == 0) inplace_step_d_inverse<N, true>(x, y, mid, buf, pos_a, pos_b, thread0);
-            else inplace_step_d_inverse<N, false>(x, y, mid, buf, pos_a, pos_b, false);
-        }
+            inplace_step_d_inverse<N, FIRST>(x, y, mid, buf, pos_a, pos_b, thread0);
+        };
+        if (__builtin_amdgcn_readfirstlane(tid) == 0) unit(std::true_type{}, 0);
+        else unit(std::false_type{}, 0);
+#pragma unroll
+        for (int i = 1; i < P::Units; ++i) unit(std::false_type{}, i);
         if (warm_up) {
             have_prev = true;
             __syncthreads();                               // all values are read before the next step A
@@ -693,20 +766,17 @@ __global__ __launch_bounds__(InPlace<N>::T) void convolve_inplace_kernel(ConvArg
         asm volatile("" : "+v"(tid));
         float4 wa[3];                                      // the last step's factors, requested before the next inputs
 #pragma unroll
-        for (int i = 0; i < 3; ++i) wa[i] = reinterpret_cast<const float4*>(tab + P::kA0)[i * T + tid];
+        for (int i = 0; i < 3; ++i) wa[i] = load_quad<T>(reinterpret_cast<const float4*>(tab + P::kA0), i, tid);
         __syncthreads();
 
         // the next block of the share: its inputs are requested now and arrive during the inverse transform
-        const bool more = walk.more();
-        ConvBlock nxt = cur;
-        if (more) {
-            walk.next();
-            nxt = walk.describe(2 * kEntries);
-            if (AHEAD) load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, ROWS), tid);
+        if (AHEAD && more) {
+            load_window<N, ROWS>(v, nxt.x, nxt.len, window_row(nxt.b, ROWS), tid);
         } else if (AHEAD) {
-            // (assigned on this path too, so that the old inputs do not stay alive in registers up to here)
+            // (assigned on this path too, so that the old inputs do not stay alive in registers up to here; to nothing, since zeros
+            // would be written ahead of the branch, in every round)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = make_float2(0.f, 0.f);
+            for (int i = 0; i < 16; ++i) asm volatile("" : "=v"(v[i].x), "=v"(v[i].y));
         }
 
         float2 o[16];
