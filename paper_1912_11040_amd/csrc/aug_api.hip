@@ -450,15 +450,18 @@ int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
 
 // ---- stage drivers: arguments already validated, packing already synchronised ----
 
+// planned: the plan has been made (by run_mel_setup).
 int run_rir(aug_ctx* ctx, int n_rir, const aug::Rooms& rooms, int rir_len, float fs, float c, float* rir_out,
-            int32_t* tap_count_out) {
+            int32_t* tap_count_out, bool planned = false) {
     const double k = (double)fs / (double)c;
     AUG_TRY(prepare_rir(ctx, n_rir, rir_len));
     const int n_groups = 2 * ctx->n_cu;
     AUG_TRY(mark(ctx, -1));
-    AUG_HIP(aug::launch_rir_plan(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
-                                 ctx->rir_ctrl.as<int>()), "rir plan kernel");
-    AUG_TRY(mark(ctx, AUG_STAGE_OTHER));
+    if (!planned) {
+        AUG_HIP(aug::launch_rir_plan(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
+                                     ctx->rir_ctrl.as<int>()), "rir plan kernel");
+        AUG_TRY(mark(ctx, AUG_STAGE_OTHER));
+    }
     AUG_HIP(aug::launch_rir(ctx->stream, n_groups, n_rir, rooms, rir_len, k, ctx->rir_items.ptr,
                             ctx->rir_ctrl.as<int>(), rir_out, nullptr, false), "rir kernel");
     AUG_TRY(mark(ctx, AUG_STAGE_RIR));
@@ -545,7 +548,10 @@ const aug::MelTableArgs& mel_table_args(aug_ctx* ctx, const aug_frontend_cfg* cf
 }
 
 // The front end's tables (they need no signal, so a call may enqueue this first) and the packing, if it is pending.
-int run_mel_setup(aug_ctx* ctx, PendingPack& pending, int n_utt, const float* alpha, const aug_frontend_cfg* cfg) {
+// With `plan` the image sum's plan too, if it fits the launch (plan->n_rir is 0 on return if not).
+int run_mel_setup(aug_ctx* ctx, PendingPack& pending, int n_utt, const float* alpha, const aug_frontend_cfg* cfg,
+                  aug::PlanArgs* plan = nullptr) {
+    if (plan && (ctx->packing.shares.n_groups == 0 || !aug::rir_plan_fits(plan->n_rir))) plan->n_rir = 0;
     if (n_utt == 0 || ctx->packing.shares.n_groups == 0) return pending.launch();
     AUG_TRY(prepare_mel(ctx, n_utt, cfg));
     AUG_TRY(mark(ctx, -1));
@@ -554,6 +560,7 @@ int run_mel_setup(aug_ctx* ctx, PendingPack& pending, int n_utt, const float* al
     a.n_utt = n_utt;
     a.table = mel_table_args(ctx, cfg, alpha, ctx->mel_tab.as<float2>());
     a.pack = pending.args;
+    if (plan) a.plan = *plan;
     a.lane_consts = ctx->have_lanes ? nullptr : ctx->mel_lanes.as<float>();
     a.window = ctx->window_n == cfg->win ? nullptr : ctx->window.as<float>();
     a.dct = !mfcc || (ctx->dct_ceps == cfg->n_ceps && ctx->dct_mel == cfg->n_mel) ? nullptr : ctx->dct.as<float>();
@@ -958,8 +965,17 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     }
     AUG_TRY(prepare_rir(ctx, n_utt * n_src, rir_len));
     AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
-    AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
-    AUG_TRY(run_rir(ctx, n_utt * n_src, {geom, nullptr, 1}, rir_len, fs, c, rir, nullptr));
+    aug::PlanArgs plan;
+    plan.n_rir = n_utt * n_src;
+    plan.rooms = {geom, nullptr, 1};
+    plan.rir_len = rir_len;
+    plan.fs_over_c = (double)fs / (double)c;
+    plan.items = ctx->rir_items.ptr;
+    plan.unsorted = ctx->rir_items.as<unsigned char>() + aug::rir_item_bytes() * (size_t)plan.n_rir * aug::rir_items_per_response(rir_len);
+    plan.ctrl = ctx->rir_ctrl.as<int>();
+    plan.n_groups = 2 * ctx->n_cu;
+    AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg, &plan));
+    AUG_TRY(run_rir(ctx, n_utt * n_src, plan.rooms, rir_len, fs, c, rir, nullptr, plan.n_rir > 0));
     AUG_TRY(run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out));
     if (mixed_out || total == 0) return run_mel(ctx, n_utt, mixed_out, cfg, feats_out);
     // The mixture itself is not wanted: the front end adds the scaled reverberated noises to the

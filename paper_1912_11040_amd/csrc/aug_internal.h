@@ -232,13 +232,27 @@ void mel_edges(const aug_frontend_cfg& cfg, MelTableArgs& a);
 int mel_table_stride(int nfft);
 int mel_lane_floats();               // the front end's per-lane constants
 
+// The image sum's plan as a share of another launch (rir_plan_fits): what launch_rir_plan does for these arguments.
+struct PlanArgs {
+    int n_rir = 0;               // 0: no plan
+    Rooms rooms;
+    int rir_len;
+    double fs_over_c;
+    void *items, *unsorted;      // the two tables in `items` of launch_rir_plan
+    int* ctrl;
+    int n_groups;
+};
+constexpr int kPlanThreads = 1024, kPlanMost = 4 * kPlanThreads;
+inline bool rir_plan_fits(int n_rir) { return n_rir <= kPlanMost; }      // one work group plans so many responses
+
 // Everything a front-end call needs before its main kernel, in one launch: the utterances' tables, the packing if
-// pack.n_utt > 0, and those of the constants whose pointer is given (per-lane constants, Hamming window of
+// pack.n_utt > 0, the image sum's plan if plan.n_rir > 0, and those of the constants whose pointer is given (per-lane constants, Hamming window of
 // table.cfg.win samples, orthonormal DCT-II rows [n_ceps][n_mel]).
 struct MelSetupArgs {
     int n_utt;
     MelTableArgs table;
     PackArgs pack;
+    PlanArgs plan;
     float* lane_consts;
     float* window;
     float* dct;

@@ -15,6 +15,7 @@
 
 #include "fft_lds.h"
 #include "pack_device.h"
+#include "rir_plan.h"
 
 namespace aug {
 namespace {
@@ -74,19 +75,27 @@ __device__ inline int mel_band(const MelTableArgs& a, const double* edges, float
     return c;
 }
 
-// The tables of utterance u, by one work group.  An entry is a chain of double-precision library calls: with few
+// The tables of utterance u, by `threads` threads, five wavefronts or one; all threads of the work group call (u < 0: nothing to
+// do).  An entry is a chain of double-precision library calls: with few
 // utterances a group has a thread per bin (K = 512) so that the chains run side by side, with many a single wavefront,
 // which fills the chip anyway.  The band edges come from the host (a power each: here they were two thirds of the time).
 constexpr int kMelTableThreads = 320;
-__device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
-    __shared__ double edges[AUG_MAX_MEL + 2];
-    __shared__ short band[2050];
-    __shared__ int first_bin[AUG_MAX_MEL + 8];        // first bin of band c or higher
-    __shared__ MelPlan plan;
-    __shared__ bool unordered;
-    const int bins = a.cfg.nfft / 2 + 1, n_mel = a.cfg.n_mel, tid = threadIdx.x, threads = (int)blockDim.x;
-    float2* t = a.tab + (size_t)u * stride;
-    const float alpha_u = a.alpha[u];
+struct MelTableShared {
+    double edges[AUG_MAX_MEL + 2];
+    short band[2050];
+    int first_bin[AUG_MAX_MEL + 8];                   // first bin of band c or higher
+    MelPlan plan;
+    bool unordered;
+};
+__device__ inline void mel_table(MelTableShared& sh, const MelTableArgs& a, int stride, int u, int tid, int threads) {
+    double* const edges = sh.edges;
+    short* const band = sh.band;
+    int* const first_bin = sh.first_bin;
+    MelPlan& plan = sh.plan;
+    bool& unordered = sh.unordered;
+    const int bins = u < 0 ? 0 : a.cfg.nfft / 2 + 1, n_mel = a.cfg.n_mel;
+    float2* t = a.tab + (size_t)max(u, 0) * stride;
+    const float alpha_u = a.alpha[max(u, 0)];
     for (int i = tid; i < n_mel + 2; i += threads) edges[i] = a.edges[i];
     for (int i = tid; i < n_mel + 8; i += threads) first_bin[i] = bins;
     for (int i = tid; i < 16 * kMaxRounds; i += threads) plan.piece[i] = kNoPiece;
@@ -105,7 +114,7 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
         for (int c = below + 1; c <= band[k]; ++c) first_bin[c] = k;
     }
     __syncthreads();
-    if (tid < 64) {
+    if (tid < 64 && u >= 0) {
         // a quad's stretch in units of four bins, on lane g
         const int n_quads = (n_mel + 3) / 4, lane = tid;
         int lo4 = 0, len4 = 0;
@@ -146,7 +155,7 @@ __device__ inline void mel_table(const MelTableArgs& a, int stride, int u) {
         }
     }
     __syncthreads();
-    for (int i = tid; i < kPlanEntries; i += threads) t[bins + i] = reinterpret_cast<const float2*>(&plan)[i];
+    for (int i = tid; i < kPlanEntries && u >= 0; i += threads) t[bins + i] = reinterpret_cast<const float2*>(&plan)[i];
 }
 
 // Constants of the sixteen lanes of a frame, [value][lane]: the second pass's twiddles exp(-2 pi i lane m / 256) and,
@@ -182,13 +191,8 @@ __device__ inline float dct_value(int i, int n_mel) {
 // Everything a front-end call needs before its main kernel, in one launch: the utterances' tables (a group each), the
 // batch's packing if its offsets are new, the constants that are not there yet.  Each of these was a launch of its own:
 // five of them and two copies took 40 us before a static call's main kernel.
-__global__ __launch_bounds__(kMelTableThreads) void mel_setup_kernel(MelSetupArgs a, int stride, int pack_groups) {
-    int group = blockIdx.x;
-    if (group < a.n_utt) {
-        mel_table(a.table, stride, group);
-        return;
-    }
-    group -= a.n_utt;
+// The rest of the set-up, by groups behind those of the tables.
+__device__ inline void mel_setup_rest(const MelSetupArgs& a, int pack_groups, int group) {
     const int threads = (int)blockDim.x;
     if (group < pack_groups) {
         pack_utterances(a.pack, group * threads + (int)threadIdx.x);
@@ -208,6 +212,31 @@ __global__ __launch_bounds__(kMelTableThreads) void mel_setup_kernel(MelSetupArg
     }
     i -= n_window;
     if (i < n_dct) a.dct[i] = dct_value(i, a.table.cfg.n_mel);
+}
+
+__global__ __launch_bounds__(kMelTableThreads) void mel_setup_kernel(MelSetupArgs a, int stride, int pack_groups) {
+    __shared__ MelTableShared shared;
+    const int group = (int)blockIdx.x;
+    if (group < a.n_utt) mel_table(shared, a.table, stride, group, (int)threadIdx.x, (int)blockDim.x);
+    else mel_setup_rest(a, pack_groups, group - a.n_utt);
+}
+
+// The same with the image sum's plan as its first group, which has nothing to do with the others but is a launch of 6 us for
+// a few responses and 14 for 1024 otherwise: eight utterances of 1 s with one noise 51.7 -> 46.9 us, 64 of 4 s 132.7 -> 127.2.  The
+// plan's groups are large, so one makes the tables of three utterances.
+constexpr int kTablesPerGroup = kPlanThreads / kMelTableThreads;
+__global__ __launch_bounds__(kPlanThreads) void mel_setup_plan_kernel(MelSetupArgs a, int stride, int pack_groups) {
+    __shared__ union { PlanShared plan; MelTableShared table[kTablesPerGroup + 1]; } shared;      // (the last for the threads left over)
+    const int table_groups = (a.n_utt + kTablesPerGroup - 1) / kTablesPerGroup, group = (int)blockIdx.x - 1, tid = (int)threadIdx.x;
+    if (group < 0) {
+        const PlanArgs& p = a.plan;
+        plan_all(shared.plan, p.n_rir, p.rooms, p.rir_len, p.fs_over_c, static_cast<Item*>(p.items), static_cast<Item*>(p.unsorted), p.ctrl, p.n_groups);
+    } else if (group < table_groups) {
+        const int part = tid / kMelTableThreads, u = group * kTablesPerGroup + part;
+        mel_table(shared.table[part], a.table, stride, part < kTablesPerGroup && u < a.n_utt ? u : -1, tid - part * kMelTableThreads, kMelTableThreads);
+    } else {
+        mel_setup_rest(a, pack_groups, group - table_groups);
+    }
 }
 
 // ---- the front end ------------------------------------------------------------------------------------------
@@ -745,11 +774,16 @@ void mel_edges(const aug_frontend_cfg& cfg, MelTableArgs& a) {
 }
 
 hipError_t launch_mel_setup(hipStream_t s, const MelSetupArgs& a) {
-    const int threads = a.n_utt >= 1024 ? 64 : kMelTableThreads;
+    const bool plan = a.plan.n_rir > 0;
+    const int threads = plan ? kPlanThreads : a.n_utt >= 1024 ? 64 : kMelTableThreads;
     const int64_t pack = a.pack.n_utt > 0 ? (pack_threads(a.pack) + threads - 1) / threads : 0;
     const int64_t consts = (a.lane_consts ? kLaneConsts * kMelLanes : 0) + (a.window ? a.table.cfg.win : 0) +
                            (a.dct ? a.table.cfg.n_ceps * a.table.cfg.n_mel : 0);
-    const int64_t groups = a.n_utt + pack + (consts + threads - 1) / threads;
+    const int64_t groups = (plan ? (a.n_utt + kTablesPerGroup - 1) / kTablesPerGroup : a.n_utt) + pack + (consts + threads - 1) / threads;
+    if (plan) {
+        mel_setup_plan_kernel<<<dim3((unsigned)groups + 1), dim3(threads), 0, s>>>(a, mel_table_stride(a.table.cfg.nfft), (int)pack);
+        return hipGetLastError();
+    }
     if (groups <= 0) return hipSuccess;
     mel_setup_kernel<<<dim3((unsigned)groups), dim3(threads), 0, s>>>(a, mel_table_stride(a.table.cfg.nfft), (int)pack);
     return hipGetLastError();
