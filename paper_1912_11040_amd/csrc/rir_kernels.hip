@@ -53,13 +53,16 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kPow = 704;                 // beta^k table entries held in LDS: more than a column of the fast walk can ask for
+constexpr int kPow = 256;                 // beta^k table entries held in LDS (see power)
+constexpr int kPowMost = 1024;            // more reflections than an image of the fast walk can have
 constexpr int kAxisCap = 320;             // x or y images per q held in the LDS tables
 constexpr int kYCap = 2 * kAxisCap + 8;
 constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) held in the LDS table
-constexpr int kPerThread = 6;             // candidate columns per thread and chunk
-constexpr int kChunk = kThreads * kPerThread;
-constexpr int kColumns = 3 * kThreads;    // live columns that the LDS has room for: a chunk's are walked in as many goes
+constexpr int kPerThread = 4;             // candidate columns per thread and chunk
+// Sums and columns share LDS: live columns that there is room for behind the sums of the widest item (a chunk's are walked in as
+// many goes as that takes; items of fewer taps have room for more)
+constexpr int kColumns = 3 * kThreads;
+constexpr int kPool = kMaxTaps + 66 + kColumns * 3 / 2;        // words of eight bytes
 #pragma clang fp contract(off)
 
 struct Axis {
@@ -260,10 +263,12 @@ struct ItemCtx {
     int quick_margin2;      // quick estimates whose 16-bit fraction is below this are settled by tap_slot
     double shift;           // 0.5 + guard - (n0 - 1)
     double guard2;
+    double settle_shift;    // the same in units of 2^-32 tap (see walk_step)
+    unsigned int settle_guard2;
 
     // the z axis (see walk_step) and the range of a column in steps of 2 L:
     // first p = ceil(lo[0] sqrt(walk2 - a) + lo[1]), last p = floor(hi[0] sqrt(r_out2 - a) + hi[1])
-    double two_l, beta2, begin[4];
+    double two_l, begin[4];
     float lo[2], hi[2];
     // An image (q, n) with k reflections lies at most k L + max(|s - m|, |L - s - m|) from the microphone along its axis:
     // with k of them, no y image is beyond y_reach[0] k + y_reach[1] metres, and with k for y and z together, no z image of
@@ -321,7 +326,8 @@ __device__ inline int tap_slot(const ItemCtx& w, double d2, double y, ExactD2 ex
 // conversion, fraction and double-precision comparison are not needed (40 instead of 60 issue cycles, without rsq,
 // per image).  y ~ 1/sqrt(d2) is enough for the amplitude.
 constexpr double kAmplitude = 0.07957747154594767 * 0x1p56;      // 1 / (4 pi) in the sums' fixed point
-constexpr double kQuickMagic = 0x1.8p36;
+constexpr double kQuickMagic = 0x1.8p36, kSettleMagic = 0x1.8p20;
+constexpr int kSettleHigh = 0x41380000;                          // high word of kSettleMagic
 constexpr double kQuickMiddle = 1.93 * 0x1p-27, kQuickError = 5.2 * 0x1p-27;
 // amp2 = amplitude * 2^56, rounded to an integer, goes to the tap's 64-bit integer sum.  Below 2^51 (every
 // image farther than 2.55 m) adding 1.5 * 2^52 rounds the exact product to an integer in the sum's own
@@ -378,18 +384,20 @@ __device__ inline double fma_keep_uniform(double a, double b_uniform, double c) 
     return r;
 }
 struct WalkRegs {           // what every step needs of the item, moved to scalar registers for the length of a chunk
-    double begin[4], quick_k, quick_shift, beta2;
+    double begin[4], quick_k, quick_shift, beta, k_fs_c, settle_shift;
+    unsigned int settle_guard2;
     unsigned short quick_margin2;
     __device__ explicit WalkRegs(const ItemCtx& c)
         : begin{uni(c.begin[0]), uni(c.begin[1]), uni(c.begin[2]), uni(c.begin[3])}, quick_k(uni(c.quick_k)), quick_shift(c.quick_shift),
-          beta2(uni(c.beta2)), quick_margin2((unsigned short)uni(c.quick_margin2)) {}
+          beta(uni(c.beta)), k_fs_c(uni(c.k_fs_c)), settle_shift(uni(c.settle_shift)), settle_guard2((unsigned int)uni((int)c.settle_guard2)),
+          quick_margin2((unsigned short)uni(c.quick_margin2)) {}
 };
-// The four images of a column at u = 2 L p.  amp_even = beta^(kxy + 2 p) / (4 pi) 2^56 and amp_odd = beta^(kxy + 2 p + 1)
-// likewise.  Four independent chains of arithmetic; no memory is read.  EDGE: some of the images may lie outside the item's
+// The four images of a column at u = 2 L p.  amp = beta^(kxy + 2 p) / (4 pi) 2^56; leaves that of the next step.
+// Four independent chains of arithmetic; no memory is read.  EDGE: some of the images may lie outside the item's
 // shell and go to the lane's own slot for such (dropped8), with `tested` by their distance (see ItemCtx::tested); else every one
 // lies inside, up to the slack of the closed form (a fifth of a tap), so its slot is one of 0 .. taps + 1 and needs no test.
 template <bool COUNT, bool EDGE>
-__device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested, double a, double u, double amp_even, double amp_odd,
+__device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested, double a, double u, double& amp,
                                 unsigned int dropped8, unsigned long long* hist) {
     double d2[4], y[4];
     unsigned int slot8[4];
@@ -407,7 +415,13 @@ __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested
     if (min(min(fraction[0], fraction[1]), min(fraction[2], fraction[3])) < k.quick_margin2) {
 #pragma unroll
         for (int l = 0; l < 4; ++l)
-            if (fraction[l] < k.quick_margin2) slot8[l] = 8u * (unsigned int)tap_slot(w, d2[l], y[l], [&] { return exact_z_image(w.az, a, u, l); });
+            if (fraction[l] < k.quick_margin2) {
+                const double s0 = __dmul_rn(d2[l], y[l]), s1 = fma(__dmul_rn(fma(-s0, s0, d2[l]), y[l]), 0.5, s0);
+                const double t = fma(s1, k.k_fs_c, k.settle_shift);
+                int slot = __double2hiint(t) - kSettleHigh;
+                if ((unsigned int)__double2loint(t) < k.settle_guard2) slot = exact_tap(exact_z_image(w.az, a, u, l), k.k_fs_c) - (w.n0 - 1);
+                slot8[l] = 8u * (unsigned int)slot;
+            }
     }
     int walked = 0;
     if (EDGE) {
@@ -420,23 +434,23 @@ __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested
 #pragma unroll
         for (int l = 0; l < 4; ++l) walked += slot8[l] < w.top8;
     }
-    const double amp_far = __dmul_rn(amp_even, k.beta2);
+    const double amp_odd = __dmul_rn(amp, k.beta), amp_far = __dmul_rn(amp_odd, k.beta);
 #pragma unroll
-    for (int l = 0; l < 4; ++l) deposit<COUNT, true>(slot8[l], l == 0 ? amp_even : l == 1 ? amp_far : amp_odd, y[l], hist);
+    for (int l = 0; l < 4; ++l) deposit<COUNT, true>(slot8[l], l == 0 ? amp : l == 1 ? amp_far : amp_odd, y[l], hist);
+    amp = amp_far;
     return walked;
 }
 
-// beta^k for reflection counts past the LDS table; out of line so that the double-precision pow does not
-// weigh on the register allocation of the loops that call it once in a long while
-__device__ __attribute__((noinline)) float beta_pow_slow(double beta, int k) { return (float)pow(beta, (double)k); }
-// beta^k of the same operations as the tables in LDS
-__device__ __attribute__((noinline)) double table_power(double beta, int k) {
-    double v = 1.0;
-    for (; k; k >>= 1) {
-        if (k & 1) v *= beta;
-        beta *= beta;
-    }
+// beta^k / (4 pi) in the sums' fixed point: what a walk that multiplies by beta from one reflection to the next comes to, wherever
+// it began, so that an image's amplitude does not depend on where its response was cut.  `table` holds the first kPow.
+// (No walk has kPowMost.)
+__device__ inline double power(const double* table, double beta, int k) {
+    double v = table[min(k, kPow - 1)];
+    for (int i = kPow - 1; i < k; ++i) v *= beta;
     return v;
+}
+__device__ __attribute__((noinline)) double power_any(const double* table, double beta, int k) {
+    return k < kPowMost ? power(table, beta, k) : pow(beta, (double)k) * kAmplitude;
 }
 
 // Items that the closed forms do not take (rooms too flat or narrow for the tables, positions far outside): every column of
@@ -445,7 +459,7 @@ __device__ __attribute__((noinline)) double table_power(double beta, int k) {
 // Distance and amplitude of an image are formed as walk_step forms them, step for step: whether an item fits the tables
 // depends on where the batch's plan has cut the response, and the response must not.
 template <bool COUNT>
-__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, int rir_len, const float* bpow, const double* zpow, unsigned long long* hist) {
+__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, int rir_len, const double* powers, unsigned long long* hist) {
     unsigned int walked = 0;
     // Of positions far outside, no shell's radius bounds the numbers of its images: those of the whole response's radius, in
     // whatever item they land.  (Formed here, where they are asked for: in prepare_item they took 2048 responses of 1000 taps of ordinary
@@ -455,8 +469,6 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, i
     };
     const int nmx = most_n(w.ax, w.nmx, w.k_cut / 2 + 1), nmy = most_n(w.ay, w.nmy, w.k_cut / 2 + 1), nmz = most_n(w.az, w.nmz, kNoCut);
     const int niy = 2 * (2 * nmy + 1);
-    // what the tables in LDS hold
-    const int n_bpow = min(min(w.k_cut, 2 * (w.nmx + w.nmy) + 8), kPow - 1), n_zpow = min(w.nmz, kMaxP);
     const bool below = w.az.src < w.az.mic, in_steps = axis_in_order(w.az);
     const long long n_columns = 2ll * (2 * nmx + 1) * niy;
     const double r_in = w.n0 > 0 ? (double)(w.n0 - 1) / w.k_fs_c : 0.0, inv_2l = 1.0 / w.two_l;
@@ -472,7 +484,6 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, i
         // (beyond the first shell the shell's own inner radius bounds the distance well enough)
         const int kz_max = (w.n0 > 0 ? w.k_cut : reflection_cut(w.inv_log2_beta, sqrtf((float)a))) - kxy;
         if (!(a < w.r_out2) || kz_max < 0) continue;
-        const double bxy = COUNT ? 0.0 : (double)(kxy <= n_bpow ? bpow[kxy] : kxy < kPow ? (float)table_power(w.beta, kxy) : beta_pow_slow(w.beta, kxy));
         const double far = sqrt(w.r_out2 - a) + rounding, near = fmax(sqrt(fmax(r_in * r_in - a, 0.0)) - rounding, 0.0);
         const int nz = min(nmz, kz_max / 2 + 1);                     // |n - q| + |n| >= 2 |n| - 1
         for (int q = 0; q < 2; ++q) {
@@ -496,12 +507,7 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, i
                 const double y = __builtin_amdgcn_rsq(d2);
                 const int slot = tap_slot(w, d2, y, [&] { return recipe; });
                 if ((unsigned int)slot > w.top8 / 8u) continue;       // (eight times a slot beyond 2^29 would come round)
-                double amp = 0.0;
-                if (!COUNT) {
-                    const double z = p <= n_zpow ? zpow[p] : table_power(w.beta, 2 * p) * kAmplitude;
-                    amp = __dmul_rn(z, q ? __dmul_rn(bxy, w.beta) : bxy);
-                    if (list == 1) amp = __dmul_rn(amp, w.beta2);
-                }
+                const double amp = COUNT ? 0.0 : power_any(powers, w.beta, kxy + 2 * p + (q ? 1 : list ? 2 : 0));
                 deposit<COUNT, false>(8u * (unsigned int)slot, amp, y, hist);
                 ++walked;
             }
@@ -523,20 +529,19 @@ struct NearImages {
     }
 };
 __device__ __attribute__((noinline)) unsigned int walk_near(const ItemCtx& w, int n_near, int n_y, int n_p, int i, const double* ykey, const unsigned short* ycount,
-                                                            const float* bpow, const double* zpow, unsigned long long* hist) {
+                                                            const double* powers, unsigned long long* hist) {
     const int l = i & 3, column = (i >> 2) / n_p, p = (i >> 2) - column * n_p, ix = column / n_y, iy = column - ix * n_y;
     const int qx = ix & 1, nx = (ix >> 1) - n_near;
     const double dx = axis_delta(w.ax, qx, nx);
     const double a = __dadd_rn(__dmul_rn(dx, dx), ykey[iy]);
     const int kxy = reflections(qx, nx) + ycount[iy];
     const double u = w.two_l * (double)p, dz = __dadd_rn(u, w.begin[l]), d2 = fma(dz, dz, a);
-    // (past the cut the amplitudes are zero, and bpow has not been formed)
+    // (past the cut the amplitudes are zero, and their powers have not been formed)
     if (!(d2 < w.walk2) || kxy > w.k_cut) return 0;
     const double y = __builtin_amdgcn_rsq(d2);
     const int slot = tap_slot(w, d2, y, [&] { return exact_z_image(w.az, a, u, l); });
     if (8u * (unsigned int)slot > w.top8) return 0;
-    const double bxy = (double)bpow[kxy], even = __dmul_rn(zpow[p], bxy);
-    deposit<false, false>(8u * (unsigned int)slot, l == 0 ? even : l == 1 ? __dmul_rn(even, w.beta2) : __dmul_rn(zpow[p], __dmul_rn(bxy, w.beta)), y, hist);
+    deposit<false, false>(8u * (unsigned int)slot, power(powers, w.beta, kxy + 2 * p + (l == 0 ? 0 : l == 1 ? 2 : 1)), y, hist);
     return 1;
 }
 
@@ -583,13 +588,15 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
             const double guard = 1e-12 * (double)(n1 + 1) + 1e-13;
             c.shift = (0.5 + guard) - (double)(n0 - 1);
             c.guard2 = 2.0 * guard;
+            const double settle = ceil(guard * 0x1p32) + 1.0;
+            c.settle_shift = kSettleMagic + (0.5 + settle * 0x1p-32 - (double)(n0 - 1));
+            c.settle_guard2 = (unsigned int)(2.0 * settle) + 1u;
             c.two_l = 2.0 * az.room;
             const double apart = fabs(az.src - az.mic), both = az.src + az.mic;
             c.begin[0] = apart;
             c.begin[1] = c.two_l - apart;
             c.begin[2] = both;
             c.begin[3] = c.two_l - both;
-            c.beta2 = c.beta * c.beta;
             // beyond 2.6 m every amplitude is below 2^-5 (see deposit); the few images of the innermost items that may be
             // nearer are walked apart
             const double r_near = kNearMetres + 0.25 / k_fs_c;
@@ -627,24 +634,38 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
     if (lane == 0) ctx = c;
 }
 
+// The powers of an item's reflection coefficient, by one wavefront, for the counts that an image can have: at most the cut (which
+// steps near the microphone are not held to) or all there are.  One multiplication after the other (see power): formed while
+// the others walk the item before, but for a group's first.
+template <bool COUNT>
+__device__ inline void form_powers(const ItemCtx& c, double* powers, int lane) {
+    if (COUNT || lane || c.kind == kSilent || c.kind == kEnd) return;
+    const double beta = c.beta, near_steps = c.near_item ? kNearMetres * 1.1 / c.two_l + 3.0 : 0.0;
+    const int k_most = c.kind == kPlain ? kPow - 1 : min(min(c.k_cut + 2 * (int)near_steps, 2 * (c.nmx + c.nmy + c.nmz) + 8), kPow - 1);
+    double v = kAmplitude;
+    for (int k = 0; k <= k_most; k += 8) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            powers[k + i] = v;
+            v *= beta;
+        }
+    }
+}
+
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
 template <bool COUNT, bool VISITS = false>
 __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     Rooms rooms, int rir_len, double k_fs_c, const Item* __restrict__ items,
     int* __restrict__ ctrl, float* __restrict__ rir_out,
     int32_t* __restrict__ cnt_out, unsigned long long* __restrict__ visits = nullptr) {
-    constexpr int kSlots = kMaxTaps + 2 + 64;      // (see ItemCtx::top8)
-    __shared__ __align__(16) unsigned long long hist[COUNT ? kSlots / 2 : kSlots];
-    __shared__ float bpow[COUNT ? 1 : kPow];       // beta^k
-    __shared__ double zpow[kMaxP + 2];             // beta^(2 p) / (4 pi) 2^56
+    __shared__ __align__(16) unsigned long long hist[kPool];       // tap sums, and behind them the live columns of a chunk
+    __shared__ __align__(16) double s_powers[2][COUNT ? 1 : kPow];  // beta^k / (4 pi) 2^56
     __shared__ double ykey[kYCap];                 // y images in order of distance: dy*dy
     __shared__ unsigned short ycount[kYCap];       // and reflections
     __shared__ unsigned short row_count[2 * kAxisCap];     // live columns per x image, summed up within every 64 of them
     __shared__ int row_part[2 * kAxisCap / 64];    // the totals of those
     __shared__ unsigned int row_gap[2 * kAxisCap];         // y images before the dead ones, and how many these are << 16
     __shared__ int row_begin[2 * kAxisCap + 5];    // the first column of every x image (and what is read past the last)
-    __shared__ double col_a[kColumns];             // live columns of a chunk, longest first: dx*dx + dy*dy
-    __shared__ unsigned int col_range[kColumns];     // first p, last p less that << 8, reflections << 16
     __shared__ int census[2][64];                  // columns per length
     __shared__ int s_round;
     __shared__ ItemCtx s_ctx[2];
@@ -653,19 +674,22 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     int tid = threadIdx.x, lane = tid & 63;
     const int wave = uni(tid >> 6), n_items = ctrl[0];
     unsigned long long walked = 0;
-    auto prepare_next = [&](ItemCtx& ctx) {        // by one wavefront
+    // by one wavefront.  A group begins with the item of its own number: 512 groups that ask one counter wait for each other.
+    auto prepare_next = [&](ItemCtx& ctx, double* powers) {
         int it = 0;
-        if (lane == 0) it = atomicAdd(&ctrl[1], 1);
+        if (lane == 0) it = (int)gridDim.x + atomicAdd(&ctrl[1], 1);
         prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane);
+        wave_sync_lds();
+        form_powers<COUNT>(ctx, powers, lane);
     };
 
-    // sums start at zero and are left at zero where an item is written out
+    // sums start at zero and are left at zero where an item is written out (and where the next one's lie over its columns)
     if (COUNT) {
-        for (int i = tid; i < kSlots; i += kThreads) hist32[i] = 0u;
+        for (int i = tid; i < kMaxTaps + 65; i += kThreads) hist32[i] = 0u;
     } else {
-        for (int i = tid; i < kSlots; i += kThreads) hist[i] = 0ull;
+        for (int i = tid; i < kMaxTaps + 65; i += kThreads) hist[i] = 0ull;
     }
-    if (wave == kWaves - 1) prepare_next(s_ctx[0]);
+    if (wave == kWaves - 1) prepare_item<COUNT>(s_ctx[0], rooms, k_fs_c, items, (int)blockIdx.x, n_items, lane);
 
     for (int now = 0, items_done = 0;; now ^= 1, ++items_done) {
         group_sync();                              // s_ctx[now] is there, and the sums of the item before are complete
@@ -675,10 +699,10 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
         const ItemCtx& c = s_ctx[now];
         if (items_done > 0) {
             const ItemCtx& before = s_ctx[now ^ 1];
-            const int n_taps = uni(before.n1 - before.n0);
+            const int n_taps = uni(before.n1 - before.n0), n_clear = max(n_taps, uni(c.n1 - c.n0)) + 65;
             const size_t to = (size_t)uni(before.rir) * rir_len + uni(before.n0) - 1;
             if (COUNT) {
-                for (int i = tid; i < n_taps + 65; i += kThreads) {
+                for (int i = tid; i < n_clear; i += kThreads) {
                     const unsigned int v = hist32[i];
                     hist32[i] = 0u;
                     if (i > 0 && i <= n_taps) cnt_out[to + i] = (int32_t)v;
@@ -691,7 +715,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     return (float)(fma((double)(unsigned int)(v >> 32), 0x1p32, (double)(unsigned int)v) * 0x1p-56);
                 };
 #pragma unroll 3
-                for (int i = tid; 2 * i < n_taps + 65; i += kThreads) {
+                for (int i = tid; 2 * i < n_clear; i += kThreads) {
                     const ulonglong2 v = pairs[i];
                     pairs[i] = make_ulonglong2(0ull, 0ull);
                     const TapPair t{value(v.x), value(v.y)};
@@ -709,26 +733,10 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
 
         const int nmx = uni(c.nmx), nmy = uni(c.nmy), nmz = uni(c.nmz), k_cut = uni(c.k_cut);
         const int nix = 2 * (2 * nmx + 1), n_yimages = y_images(nmy), segments = (nix + 63) / 64;
-        if (!COUNT && kind != kSilent) {
-            // beta^k by squaring (k < 1024: ten steps, a few units in the last place of the double, far inside
-            // the float it is kept as; the library pow is some ten times the instructions), for the counts that
-            // a column can have: at most the cut or all there are
-            const int k_most = min(min(k_cut, 2 * (nmx + nmy) + 8), kPow - 1), n_z = min(nmz, kMaxP) + 1;
-            for (int i = tid; i <= k_most + 1 + n_z; i += kThreads) {
-                const bool z = i > k_most;
-                const int k = z ? 2 * (i - k_most - 1) : i;
-                double b = c.beta, v = 1.0;
-#pragma unroll
-                for (int bit = 0; bit < 10; ++bit) {
-                    if ((k >> bit) & 1) v *= b;
-                    b *= b;
-                }
-                if (z) zpow[i - k_most - 1] = v * kAmplitude;
-                else bpow[i] = (float)v;
-            }
-        }
+        const double* const powers = s_powers[COUNT ? 0 : now];
+        if (items_done == 0 && wave == 0) form_powers<COUNT>(c, s_powers[COUNT ? 0 : now], lane);
         if (kind == kFast) {
-            for (int i = tid; i < n_yimages; i += kThreads) {
+            for (int i = tid ^ 64; i < n_yimages; i += kThreads) {
                 int q, n;
                 ordered_image(c.y_order, i, q, n);
                 const double dy = axis_delta(c.ay, q, n);
@@ -794,7 +802,11 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             // in LDS, and taken 64 at a time, longest first, from a counter.
             // (The images near the microphone are walked in the last go of the last chunk.  An item that has such images takes one
             // chunk also where the gaps leave it no column: they remove the columns whose images all lie that near.)
-            for (int base = 0, parity = 0; base < n_cand || (base == 0 && near_item); base += kChunk, parity ^= 1) {
+            // (as many as there is certainly room for behind the sums)
+            const int behind = uni(c.n1 - c.n0) + 66 & ~1, room = (kPool - behind) * 2 / 3 & ~1, chunk = min(room / kThreads, kPerThread) * kThreads;
+            double* const col_a = reinterpret_cast<double*>(hist + behind);       // the columns, longest first: dx*dx + dy*dy
+            unsigned int* const col_range = reinterpret_cast<unsigned int*>(col_a + room);      // first p, last p less that << 8, reflections << 16
+            for (int base = 0, parity = 0; base < n_cand || (base == 0 && near_item); base += chunk, parity ^= 1) {
                 double a[kPerThread];
                 unsigned int range[kPerThread];
                 int place[kPerThread];                    // length << 16 | number among those of that length, -1: not live
@@ -804,7 +816,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     a[j] = 0.0;
                     range[j] = 0u;
                     place[j] = -1;
-                    if (cand0 >= n_cand) continue;
+                    if (cand0 >= n_cand || kThreads * j >= chunk) continue;
                     // the row of the stretch's first column, and from there the lane's own: 64 consecutive columns span
                     // few rows, so the next four are compared at once
                     int row = 0;
@@ -856,84 +868,73 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     place[j] = place[j] >= 0 ? at : -1;
                 }
                 const WalkRegs regs(c);
-                const double two_l = uni(c.two_l), beta = uni(c.beta);
+                const double two_l = uni(c.two_l);
                 const unsigned int dropped8 = uni((int)c.top8) + 8u * (unsigned int)lane;      // (slots apart: adds to one place queue up)
-                int walked_to = 0;
-                do {
-                    // in the last go of the last chunk a wavefront prepares the next item before it joins in
-                    const bool last = base + kChunk >= n_cand && walked_to + kColumns >= n_live, apart = last && wave == kWaves - 1;
-                    if (walked_to) group_sync();              // the columns of the go before have been walked
-                    if (tid == 0) s_round = last ? kWaves - 1 : kWaves;
 #pragma unroll
-                    for (int j = 0; j < kPerThread; ++j) {
-                        if (base + kThreads * j >= n_cand) continue;
-                        const int at = place[j] - walked_to;
-                        if (place[j] >= 0 && at >= 0 && at < kColumns) {
-                            col_a[at] = a[j];
-                            col_range[at] = range[j];
-                        }
+                for (int j = 0; j < kPerThread; ++j)
+                    if (place[j] >= 0) {
+                        col_a[place[j]] = a[j];
+                        col_range[place[j]] = range[j];
                     }
-                    group_sync();
-                    const int n_here = min(n_live - walked_to, kColumns), column_rounds = (n_here + 63) / 64;
-                    int round = wave;
-                    auto next_round = [&] {
-                        int next = 0;
-                        if (lane == 0) next = atomicAdd(&s_round, 1);
-                        return uni(next);
-                    };
-                    if (apart) {
-                        prepare_next(s_ctx[now ^ 1]);
-                        round = next_round();
-                    }
-                    prepared |= last;
-                    for (; round < column_rounds; round = next_round()) {
-                        const int mine = 64 * round + lane;
-                        if (mine < n_here) {
-                            const double col = col_a[mine];
-                            const unsigned int r = col_range[mine];
-                            const int p0 = (int)(r & 255u), n = (int)(r >> 8 & 255u);
-                            const double even = COUNT ? 0.0 : (double)bpow[r >> 16], odd = __dmul_rn(even, beta);
-                            const double* zp = zpow + p0;
-                            const double u0 = two_l * (double)p0;
+                // behind the last chunk's candidates a wavefront prepares the next item before it joins in
+                const bool last = base + chunk >= n_cand, apart = last && wave == kWaves - 1;
+                if (tid == 0) s_round = last ? kWaves - 1 : kWaves;
+                group_sync();
+                const int column_rounds = (n_live + 63) / 64;
+                int round = wave;
+                auto next_round = [&] {
+                    int next = 0;
+                    if (lane == 0) next = atomicAdd(&s_round, 1);
+                    return uni(next);
+                };
+                if (apart) {
+                    prepare_next(s_ctx[now ^ 1], s_powers[COUNT ? 0 : now ^ 1]);
+                    round = next_round();
+                }
+                prepared |= last;
+                for (; round < column_rounds; round = next_round()) {
+                    const int mine = 64 * round + lane;
+                    if (mine < n_live) {
+                        const double col = col_a[mine];
+                        const unsigned int r = col_range[mine];
+                        const int p0 = (int)(r & 255u), n = (int)(r >> 8 & 255u);
+                        const int k0 = (int)(r >> 16) + 2 * p0;
+                        const double u0 = two_l * (double)p0;
 #pragma unroll 1
-                            for (int e = 0; e < edges; ++e) {
-                                const int at = e & 1 ? n - (e >> 1) : e >> 1;
-                                if (n < e) break;
-                                const double z = COUNT ? 0.0 : zp[at];
-                                const int in = walk_step<COUNT, true>(c, regs, tested, col, fma(two_l, (double)at, u0), z * even, z * odd, dropped8, hist);
-                                if (VISITS) walked += in;
-                            }
-                            int left = n + 1 - edges;
-                            if (left > 0) {
-                                if (VISITS) walked += 4 * left;
-                                const int inner = (edges + 1) >> 1;
-                                zp += inner;
-                                double u = fma(two_l, (double)inner, u0);
-                                do {
-                                    const double z = COUNT ? 0.0 : *zp++;
-                                    walk_step<COUNT, false>(c, regs, false, col, u, z * even, z * odd, 0u, hist);
-                                    u += two_l;
-                                } while (--left > 0);
-                            }
+                        for (int e = 0; e < edges; ++e) {
+                            const int at = e & 1 ? n - (e >> 1) : e >> 1;
+                            if (n < e) break;
+                            double amp = COUNT ? 0.0 : power(powers, regs.beta, k0 + 2 * at);
+                            const int in = walk_step<COUNT, true>(c, regs, tested, col, fma(two_l, (double)at, u0), amp, dropped8, hist);
+                            if (VISITS) walked += in;
+                        }
+                        int left = n + 1 - edges;
+                        if (left > 0) {
+                            if (VISITS) walked += 4 * left;
+                            const int inner = (edges + 1) >> 1;
+                            double amp = COUNT ? 0.0 : power(powers, regs.beta, k0 + 2 * inner), u = fma(two_l, (double)inner, u0);
+                            do {
+                                walk_step<COUNT, false>(c, regs, false, col, u, amp, 0u, hist);
+                                u += two_l;
+                            } while (--left > 0);
                         }
                     }
-                    if (last && near_item) {
-                        const NearImages near(c);
-                        for (; 64 * (round - column_rounds) < near.n; round = next_round()) {
-                            const int i = 64 * (round - column_rounds) + lane;
-                            if (i < near.n) {
-                                const unsigned int in = walk_near(c, near.n_near, near.n_y, near.n_p, i, ykey, ycount, bpow, zpow, hist);
-                                if (VISITS) walked += in;
-                            }
+                }
+                if (last && near_item) {
+                    const NearImages near(c);
+                    for (; 64 * (round - column_rounds) < near.n; round = next_round()) {
+                        const int i = 64 * (round - column_rounds) + lane;
+                        if (i < near.n) {
+                            const unsigned int in = walk_near(c, near.n_near, near.n_y, near.n_p, i, ykey, ycount, powers, hist);
+                            if (VISITS) walked += in;
                         }
                     }
-                    walked_to += kColumns;
-                } while (walked_to < n_live);
+                }
             }
         } else if (kind == kPlain) {
-            walked += walk_plain<COUNT>(c, rir_len, bpow, zpow, hist);
+            walked += walk_plain<COUNT>(c, rir_len, powers, hist);
         }
-        if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1]);
+        if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1], s_powers[COUNT ? 0 : now ^ 1]);
     }
     if (VISITS) {
         for (int off = 32; off > 0; off >>= 1) walked += __shfl_down(walked, off, 64);
