@@ -114,7 +114,7 @@ __global__ void rir_plan_kernel(int n_rir, Rooms rooms, int rir_len, double k_fs
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r < n_rir) {
         const Room room = load_room(rooms, r);
-        const float target = item_target(ctrl[kCtrlWork], n_groups);
+        const float target = item_target(ctrl[kCtrlWork], n_groups, n_rir);
         const WorkModel model = work_model(room.g, rir_len, k_fs_c);
         const bool ok = room_ok(room.g);
         const int count = cut_shells(model, ok, rir_len, target, 0, 1, [](int, int) {});

@@ -17,8 +17,10 @@ constexpr int kMinTaps = 64;
 // 600000 at every batch: 3072 responses of 32768 taps (1024 utterances of 10 s) 7.8 -> 6.7 ms, 128 of 8000 (64 of 4 s) 180 -> 134 us.
 constexpr float kItemsPerGroup = 1.25f;
 // (the lower limit matters for small batches only, where items must be small for all groups to get one: 64 utterances of 4 s
-// with two responses of 8000 taps each take 156 us at 300000, 130 at 50000, eight of 1 s with 4096 taps 58 and 54)
-constexpr float kMinTargetWork = 50000.f, kMaxTargetWork = 8000000.f;
+// with two responses of 8000 taps each take 156 us at 300000, 130 at 50000, and the image sum alone 43.5 us anywhere from 10000 to
+// 50000.  With fewer than a quarter as many responses as groups it falls with their number: most groups would have nothing, and the time is that
+// of the heaviest item.  Image sum of 16 responses of 4096 taps: 19.4 us at 64000, 15.2 at 50000, 13.4 at 20000, 12.9 at 10000.)
+constexpr float kMinTargetWork = 50000.f, kLeastTargetWork = 10000.f, kMaxTargetWork = 8000000.f;
 constexpr float kWorkUnit = 4096.f;       // the batch total is summed in integers of this many visits
 constexpr int kMaxShells = 96;            // shells per response, before those wider than kMaxTaps are split
 
@@ -140,8 +142,9 @@ __device__ inline float response_work(const float* g, int rir_len, double k_fs_c
 }
 
 // Work per item that a batch of `units` work units (kWorkUnit visits each) aims at.
-__device__ inline float item_target(int units, int n_groups) {
-    return fminf(fmaxf(kWorkUnit * (float)units / ((float)n_groups * kItemsPerGroup), kMinTargetWork), kMaxTargetWork);
+__device__ inline float item_target(int units, int n_groups, int n_rir) {
+    const float least = fminf(fmaxf(kMinTargetWork * 4.f * (float)n_rir / (float)n_groups, kLeastTargetWork), kMinTargetWork);
+    return fminf(fmaxf(kWorkUnit * (float)units / ((float)n_groups * kItemsPerGroup), least), kMaxTargetWork);
 }
 
 // Cut the taps of a response into shells of about equal work, and those wider than kMaxTaps into parts: calls
@@ -250,7 +253,7 @@ __device__ inline void plan_all(PlanShared& sh, int n_rir, const Rooms& rooms, i
         const WorkModel model = work_model(room.g, rir_len, k_fs_c);
         if (share == 0 && tid < n) atomicAdd(&s_units, units_of(model, ok));
         group_sync();
-        if (tid < n) write_items(model, ok, r, share, item_target(s_units, n_groups));
+        if (tid < n) write_items(model, ok, r, share, item_target(s_units, n_groups, n_rir));
     } else {
 #pragma unroll 1
         for (int pass = 0; pass < 2; ++pass) {
@@ -261,7 +264,7 @@ __device__ inline void plan_all(PlanShared& sh, int n_rir, const Rooms& rooms, i
                 const bool ok = room_ok(room.g);
                 const WorkModel model = work_model(room.g, rir_len, k_fs_c);
                 if (pass == 0) units += units_of(model, ok);
-                else write_items(model, ok, r, 0, item_target(s_units, n_groups));
+                else write_items(model, ok, r, 0, item_target(s_units, n_groups, n_rir));
             }
             if (pass == 0) {
                 atomicAdd(&s_units, units);
