@@ -76,6 +76,11 @@ __device__ inline double axis_delta(const Axis& a, int q, int n) {
     return __dsub_rn(coord, a.mic);
 }
 
+// the same from 2 n
+__device__ inline double axis_delta_2n(const Axis& a, int q, int n2) {
+    return __dsub_rn(__dadd_rn(q ? -a.src : a.src, __dmul_rn((double)n2, a.room)), a.mic);
+}
+
 // reflections of image (q, n) along its axis: |n - q| + |n|
 __device__ inline int reflections(int q, int n) {
     const int v = 2 * n - q;
@@ -797,12 +802,12 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
             const bool near_item = uni(c.near_item) != 0, tested = uni(c.tested) != 0;
             const int edges = uni(c.edges);
 
-            // Columns are worked through a chunk at a time.  Each thread describes kPerThread candidates (the wavefronts'
-            // stretches of 64 side by side, so that a wavefront's rows only move up); the live ones are sorted by length,
-            // in LDS, and taken 64 at a time, longest first, from a counter.
-            // (The images near the microphone are walked in the last go of the last chunk.  An item that has such images takes one
+            // Columns are worked through a chunk at a time: as many candidates as there is certainly room for behind the sums.
+            // Each thread describes kPerThread of them (the wavefronts' stretches of 64 side by side, so that a wavefront's rows
+            // only move up), two at a time so that one's loads and roots are under way with the other's; the live ones
+            // are sorted by length, in LDS, and taken 64 at a time, longest first, from a counter.
+            // (The images near the microphone are walked after the last chunk's columns.  An item that has such images takes one
             // chunk also where the gaps leave it no column: they remove the columns whose images all lie that near.)
-            // (as many as there is certainly room for behind the sums)
             const int behind = uni(c.n1 - c.n0) + 66 & ~1, room = (kPool - behind) * 2 / 3 & ~1, chunk = min(room / kThreads, kPerThread) * kThreads;
             double* const col_a = reinterpret_cast<double*>(hist + behind);       // the columns, longest first: dx*dx + dy*dy
             unsigned int* const col_range = reinterpret_cast<unsigned int*>(col_a + room);      // first p, last p less that << 8, reflections << 16
@@ -810,52 +815,77 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 double a[kPerThread];
                 unsigned int range[kPerThread];
                 int place[kPerThread];                    // length << 16 | number among those of that length, -1: not live
+                // the rows of the stretches' first columns
+                int first_row[kPerThread];
 #pragma unroll
                 for (int j = 0; j < kPerThread; ++j) {
-                    const int cand0 = base + 64 * (kWaves * j + wave), cand = cand0 + lane;
-                    a[j] = 0.0;
-                    range[j] = 0u;
+                    first_row[j] = 0;
                     place[j] = -1;
-                    if (cand0 >= n_cand || kThreads * j >= chunk) continue;
-                    // the row of the stretch's first column, and from there the lane's own: 64 consecutive columns span
-                    // few rows, so the next four are compared at once
-                    int row = 0;
+                }
+                if (base < n_cand)
                     for (int seg = 0; seg < segments; ++seg) {
-                        const int i = 64 * seg + lane;
-                        row += __popcll(__ballot(i < nix && row_begin[i + 1] <= cand0));
-                    }
-                    int ix = row, begin = row_begin[row];
+                        const int i = 64 * seg + lane, end = i < nix ? row_begin[i + 1] : 0x7fffffff;
 #pragma unroll
-                    for (int k = 1; k <= 4; ++k) {
-                        const int at = row_begin[row + k];
-                        if (at <= cand) {
-                            ix = row + k;
-                            begin = at;
-                        }
+                        for (int j = 0; j < kPerThread; ++j)
+                            first_row[j] += __popcll(__ballot(end <= min(base + 64 * (kWaves * j + wave), n_cand - 1)));
                     }
-                    if (cand < n_cand) {
-                        while (row_begin[ix + 1] <= cand) begin = row_begin[++ix];        // (seldom)
-                        const unsigned int gap = row_gap[ix];
-                        const int qx = ix & 1, nx = (ix >> 1) - nmx, nth = cand - begin;
+                const Axis ax{uni(c.ax.room), uni(c.ax.src), uni(c.ax.mic)};
+                const double r_out2 = uni(c.r_out2), walk2 = uni(c.walk2);
+                const float lo0 = uni(c.lo[0]), lo1 = uni(c.lo[1]), hi0 = uni(c.hi[0]), hi1 = uni(c.hi[1]), inv_log2_beta = uni(c.inv_log2_beta);
+                const bool inner_item = uni(c.n0) == 0;
+#pragma unroll
+                for (int pair = 0; pair < kPerThread; pair += 2) {
+                    if (base + 64 * (kWaves * pair + wave) >= n_cand || kThreads * pair >= chunk) continue;
+                    int cand[2], ix[2], begin[2];
+                    bool farther = false;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        // the lane's own row, from there: 64 consecutive columns span few rows, so the next four are compared at once
+                        const int row = first_row[pair + e];
+                        cand[e] = min(base + 64 * (kWaves * (pair + e) + wave) + lane, n_cand - 1);
+                        ix[e] = row;
+                        begin[e] = row_begin[row];
+#pragma unroll
+                        for (int k = 1; k <= 4; ++k) {
+                            const int at = row_begin[row + k];
+                            if (at <= cand[e]) {
+                                ix[e] = row + k;
+                                begin[e] = at;
+                            }
+                        }
+                        farther |= ix[e] == row + 4;
+                    }
+                    if (farther) {                        // (seldom)
+#pragma unroll
+                        for (int e = 0; e < 2; ++e)
+                            while (row_begin[ix[e] + 1] <= cand[e]) begin[e] = row_begin[++ix[e]];
+                    }
+                    int length[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int j = pair + e;
+                        const unsigned int gap = row_gap[ix[e]];
+                        const int qx = ix[e] & 1, n2 = (ix[e] & ~1) - 2 * nmx, nth = cand[e] - begin[e];
                         const int iy = nth + (nth >= (int)(gap & 0xffffu) ? (int)(gap >> 16) : 0);
-                        const double dx = axis_delta(c.ax, qx, nx);
+                        const double dx = axis_delta_2n(ax, qx, n2);
                         a[j] = __dadd_rn(__dmul_rn(dx, dx), ykey[iy]);
-                        const int kxy = reflections(qx, nx) + ycount[iy];
+                        const int kxy = abs(n2 - qx) + ycount[iy];
                         // reflections left for the z axis before this column's images vanish
                         // (beyond the first shell the shell's own inner radius bounds the distance well enough)
-                        const int cut = c.n0 > 0 ? k_cut : reflection_cut(c.inv_log2_beta, __builtin_amdgcn_sqrtf((float)a[j]));
-                        const float outer = (float)(c.r_out2 - a[j]), inner = (float)(c.walk2 - a[j]);
+                        const int cut = inner_item ? reflection_cut(inv_log2_beta, __builtin_amdgcn_sqrtf((float)a[j])) : k_cut;
+                        const float outer = (float)(r_out2 - a[j]), inner = (float)(walk2 - a[j]);
                         // The images with r_in^2 <= a + dz^2 <= r_out^2 and reflections left: from the first p at which some
                         // list has begun to the last at which not all have ended.
-                        const float to = fmaf(__builtin_amdgcn_sqrtf(fmaxf(outer, 0.f)), c.hi[0], c.hi[1]);
-                        const float from = fmaf(__builtin_amdgcn_sqrtf(fmaxf(inner, 0.f)), c.lo[0], c.lo[1]);
+                        const float to = fmaf(__builtin_amdgcn_sqrtf(fmaxf(outer, 0.f)), hi0, hi1);
+                        const float from = fmaf(__builtin_amdgcn_sqrtf(fmaxf(inner, 0.f)), lo0, lo1);
                         const int p1 = min(min((int)floorf(to), (cut - kxy) >> 1), nmz), p0 = max((int)ceilf(from), 0);
-                        if (outer > 0.f && cut >= kxy && p1 >= p0) {
-                            range[j] = (unsigned int)(p0 | (p1 - p0) << 8 | kxy << 16);
-                            const int length = min(p1 - p0, 63);
-                            place[j] = atomicAdd(&census[parity][63 - length], 1) | (63 - length) << 16;
-                        }
+                        range[j] = (unsigned int)(p0 | (p1 - p0) << 8 | kxy << 16);
+                        const bool mine = base + 64 * (kWaves * j + wave) + lane < n_cand && kThreads * j < chunk;
+                        length[e] = mine && outer > 0.f && cut >= kxy && p1 >= p0 ? min(p1 - p0, 63) : -1;
                     }
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        if (length[e] >= 0) place[pair + e] = atomicAdd(&census[parity][63 - length[e]], 1) | (63 - length[e]) << 16;
                 }
                 group_sync();                             // also: every column of the chunk before has been walked
                 const int of_length = census[parity][lane], up_to = wave_inclusive_scan(of_length);
