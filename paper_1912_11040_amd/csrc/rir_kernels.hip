@@ -836,36 +836,32 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
 #pragma unroll
                 for (int pair = 0; pair < kPerThread; pair += 2) {
                     if (base + 64 * (kWaves * pair + wave) >= n_cand || kThreads * pair >= chunk) continue;
-                    int cand[2], ix[2], begin[2];
+                    // the lanes' own rows, from there: 64 consecutive columns span few rows, so the next four are compared at once
+                    int cand[2], ix[2], ahead[2][4];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) ahead[e][k] = row_begin[first_row[pair + e] + 1 + k];
                     bool farther = false;
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
-                        // the lane's own row, from there: 64 consecutive columns span few rows, so the next four are compared at once
-                        const int row = first_row[pair + e];
                         cand[e] = min(base + 64 * (kWaves * (pair + e) + wave) + lane, n_cand - 1);
-                        ix[e] = row;
-                        begin[e] = row_begin[row];
+                        ix[e] = first_row[pair + e];
 #pragma unroll
-                        for (int k = 1; k <= 4; ++k) {
-                            const int at = row_begin[row + k];
-                            if (at <= cand[e]) {
-                                ix[e] = row + k;
-                                begin[e] = at;
-                            }
-                        }
-                        farther |= ix[e] == row + 4;
+                        for (int k = 0; k < 4; ++k) ix[e] += ahead[e][k] <= cand[e];
+                        farther |= ahead[e][3] <= cand[e];
                     }
                     if (farther) {                        // (seldom)
 #pragma unroll
                         for (int e = 0; e < 2; ++e)
-                            while (row_begin[ix[e] + 1] <= cand[e]) begin[e] = row_begin[++ix[e]];
+                            while (row_begin[ix[e] + 1] <= cand[e]) ++ix[e];
                     }
                     int length[2];
 #pragma unroll
                     for (int e = 0; e < 2; ++e) {
                         const int j = pair + e;
                         const unsigned int gap = row_gap[ix[e]];
-                        const int qx = ix[e] & 1, n2 = (ix[e] & ~1) - 2 * nmx, nth = cand[e] - begin[e];
+                        const int qx = ix[e] & 1, n2 = (ix[e] & ~1) - 2 * nmx, nth = cand[e] - row_begin[ix[e]];
                         const int iy = nth + (nth >= (int)(gap & 0xffffu) ? (int)(gap >> 16) : 0);
                         const double dx = axis_delta_2n(ax, qx, n2);
                         a[j] = __dadd_rn(__dmul_rn(dx, dx), ykey[iy]);
