@@ -25,7 +25,7 @@
 //     Along z the images are four arithmetic progressions of one step, 2 L.  A column's images inside the shell are
 //     therefore those of a range of steps p, with up to three more at either end, and a lane walks a column from the
 //     first p to the last, four images a step, without reading any table of images: distances are formed from the step,
-//     amplitudes from one power per step.  Columns are sorted by length, some thousand at a time, so that the 64 lanes of a
+//     amplitudes by two multiplications a step.  Columns are sorted by length, some thousand at a time, so that the 64 lanes of a
 //     wavefront walk columns of one length.
 //     Rooms so flat or narrow that an axis has more images than the tables hold, rooms of more than 4e5 taps along y or z,
 //     and positions far outside the room take a plain path (all columns of the bounding box, of a live column the z
@@ -41,7 +41,8 @@
 // in small batches); this walk, 261; the item's constants formed by one wavefront while the others walk, 239; rows found by
 // comparing 64 at once and the near images walked last, 224; the ends of a column walked like its middle, with a
 // slot per lane for what lies outside, 215.  Groups of 1024 threads with 64 registers
-// took 294.  What the long responses want costs this batch 9 of those us: six candidate columns per thread and chunk instead of
+// took 294.  Without its walk (the sums left empty) the kernel alone takes 92 of 222 us there, 113 of 383 for 1024 responses of 16000 taps
+// and 28 of 44 for 128 of 8000: candidates, tables, sorting, stores and barriers, so these count as much as the walk does.  What the long responses want costs this batch 9 of those us: six candidate columns per thread and chunk instead of
 // four, rows with a gap where the cut leaves their middle empty, and shells of equal work (the plan is 16 us instead of 10).
 // Other whole calls before this walk and now: 1 response of 1000 taps 17.3 -> 15.6 us, 3000 of 1000 72 -> 67, 16 of 4096 30.5 ->
 // 24.4, 128 of 8000 65 -> 49, 192 of 16000 186 -> 160, 32 of 32768 230 -> 185.
@@ -55,12 +56,15 @@ constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
 constexpr int kPow = 256;                 // beta^k table entries held in LDS (see power)
 constexpr int kPowMost = 1024;            // more reflections than an image of the fast walk can have
+constexpr int kPowTable = kPow + (kPowMost - kPow) / 64;
 constexpr int kAxisCap = 320;             // x or y images per q held in the LDS tables
 constexpr int kYCap = 2 * kAxisCap + 8;
 constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) held in the LDS table
 constexpr int kPerThread = 4;             // candidate columns per thread and chunk
-// Sums and columns share LDS: live columns that there is room for behind the sums of the widest item (a chunk's are walked in as
-// many goes as that takes; items of fewer taps have room for more)
+// Sums and columns share LDS: columns that there is room for behind the sums of the widest item; items of fewer taps have room for
+// more, and a chunk is as many candidates as are sure to have it.  (Columns with LDS of their own and a chunk walked in as many
+// goes as that took kept what was found out about the chunk in registers meanwhile, and the compiler spilled.  Six candidates per
+// thread it spills too: 2000 responses of 8000 taps 282 us.)
 constexpr int kColumns = 3 * kThreads;
 constexpr int kPool = kMaxTaps + 66 + kColumns * 3 / 2;        // words of eight bytes
 #pragma clang fp contract(off)
@@ -447,11 +451,12 @@ __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested
 }
 
 // beta^k / (4 pi) in the sums' fixed point: what a walk that multiplies by beta from one reflection to the next comes to, wherever
-// it began, so that an image's amplitude does not depend on where its response was cut.  `table` holds the first kPow.
-// (No walk has kPowMost.)
+// it began, so that an image's amplitude does not depend on where its response was cut.  `table` holds the first kPow and from
+// there every 64th.
 __device__ inline double power(const double* table, double beta, int k) {
-    double v = table[min(k, kPow - 1)];
-    for (int i = kPow - 1; i < k; ++i) v *= beta;
+    double v = table[k < kPow ? k : kPow + ((k - kPow) >> 6)];
+    if (k >= kPow)
+        for (int i = k & 63; i > 0; --i) v *= beta;
     return v;
 }
 __device__ __attribute__((noinline)) double power_any(const double* table, double beta, int k) {
@@ -646,14 +651,20 @@ template <bool COUNT>
 __device__ inline void form_powers(const ItemCtx& c, double* powers, int lane) {
     if (COUNT || lane || c.kind == kSilent || c.kind == kEnd) return;
     const double beta = c.beta, near_steps = c.near_item ? kNearMetres * 1.1 / c.two_l + 3.0 : 0.0;
-    const int k_most = c.kind == kPlain ? kPow - 1 : min(min(c.k_cut + 2 * (int)near_steps, 2 * (c.nmx + c.nmy + c.nmz) + 8), kPow - 1);
+    const int k_all = c.kind == kPlain ? kPowMost : 2 * (c.nmx + c.nmy + c.nmz) + 8;
+    const int k_most = min(min(c.k_cut + 2 * (int)near_steps + 8, k_all), kPowMost - 1);
     double v = kAmplitude;
-    for (int k = 0; k <= k_most; k += 8) {
+    for (int k = 0; k <= min(k_most, kPow - 1); k += 8) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             powers[k + i] = v;
             v *= beta;
         }
+    }
+    for (int k = kPow; k <= k_most; k += 64) {
+        powers[kPow + ((k - kPow) >> 6)] = v;
+#pragma unroll 8
+        for (int i = 0; i < 64; ++i) v *= beta;
     }
 }
 
@@ -664,7 +675,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     int* __restrict__ ctrl, float* __restrict__ rir_out,
     int32_t* __restrict__ cnt_out, unsigned long long* __restrict__ visits = nullptr) {
     __shared__ __align__(16) unsigned long long hist[kPool];       // tap sums, and behind them the live columns of a chunk
-    __shared__ __align__(16) double s_powers[2][COUNT ? 1 : kPow];  // beta^k / (4 pi) 2^56
+    __shared__ __align__(16) double s_powers[2][COUNT ? 1 : kPowTable];  // beta^k / (4 pi) 2^56
     __shared__ double ykey[kYCap];                 // y images in order of distance: dy*dy
     __shared__ unsigned short ycount[kYCap];       // and reflections
     __shared__ unsigned short row_count[2 * kAxisCap];     // live columns per x image, summed up within every 64 of them
@@ -924,25 +935,25 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                         const double col = col_a[mine];
                         const unsigned int r = col_range[mine];
                         const int p0 = (int)(r & 255u), n = (int)(r >> 8 & 255u);
-                        const int k0 = (int)(r >> 16) + 2 * p0;
-                        const double u0 = two_l * (double)p0;
+                        double amp = COUNT ? 0.0 : power(powers, regs.beta, (int)(r >> 16) + 2 * p0), u = two_l * (double)p0;
+                        // its first steps, those between and its last, in this order so that the amplitude goes on from step to step
+                        int at = 0;
 #pragma unroll 1
-                        for (int e = 0; e < edges; ++e) {
-                            const int at = e & 1 ? n - (e >> 1) : e >> 1;
-                            if (n < e) break;
-                            double amp = COUNT ? 0.0 : power(powers, regs.beta, k0 + 2 * at);
-                            const int in = walk_step<COUNT, true>(c, regs, tested, col, fma(two_l, (double)at, u0), amp, dropped8, hist);
-                            if (VISITS) walked += in;
-                        }
-                        int left = n + 1 - edges;
-                        if (left > 0) {
-                            if (VISITS) walked += 4 * left;
-                            const int inner = (edges + 1) >> 1;
-                            double amp = COUNT ? 0.0 : power(powers, regs.beta, k0 + 2 * inner), u = fma(two_l, (double)inner, u0);
-                            do {
-                                walk_step<COUNT, false>(c, regs, false, col, u, amp, 0u, hist);
-                                u += two_l;
-                            } while (--left > 0);
+                        for (int stop = min((edges + 1) >> 1, n + 1);; stop = n + 1) {
+                            for (; at < stop; ++at, u += two_l) {
+                                const int in = walk_step<COUNT, true>(c, regs, tested, col, u, amp, dropped8, hist);
+                                if (VISITS) walked += in;
+                            }
+                            if (at > n) break;
+                            int left = n + 1 - (edges >> 1) - at;
+                            if (left > 0) {
+                                if (VISITS) walked += 4 * left;
+                                at += left;
+                                do {
+                                    walk_step<COUNT, false>(c, regs, false, col, u, amp, 0u, hist);
+                                    u += two_l;
+                                } while (--left > 0);
+                            }
                         }
                     }
                 }
