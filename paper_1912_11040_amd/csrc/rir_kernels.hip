@@ -49,6 +49,8 @@
 
 #include "rir_plan.h"
 
+#include <type_traits>
+
 namespace aug {
 namespace {
 
@@ -60,7 +62,7 @@ constexpr int kPowTable = kPow + (kPowMost - kPow) / 64;
 constexpr int kAxisCap = 320;             // x or y images per q held in the LDS tables
 constexpr int kYCap = 2 * kAxisCap + 8;
 constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) held in the LDS table
-constexpr int kPerThread = 4;             // candidate columns per thread and chunk
+constexpr int kPerThread = 4;             // candidate columns per thread and chunk (described two and two)
 // Sums and columns share LDS: columns that there is room for behind the sums of the widest item; items of fewer taps have room for
 // more, and a chunk is as many candidates as are sure to have it.  (Columns with LDS of their own and a chunk walked in as many
 // goes as that took kept what was found out about the chunk in registers meanwhile, and the compiler spilled.  Six candidates per
@@ -555,9 +557,34 @@ __device__ __attribute__((noinline)) unsigned int walk_near(const ItemCtx& w, in
     return 1;
 }
 
-// Prepares item `it`: all lanes of one wavefront compute the same, lane 0 writes.
+// The powers of an item's reflection coefficient, by one wavefront, for the counts that an image can have: at most the cut (which
+// steps near the microphone are not held to) or all there are.  One multiplication after the other (see power): formed while
+// the others walk the item before, but for a group's first.
 template <bool COUNT>
-__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
+__device__ inline void form_powers(const ItemCtx& c, double* powers, int lane) {
+    if (COUNT || lane || c.kind == kSilent || c.kind == kEnd) return;
+    const double beta = c.beta;
+    const int near_steps = c.near_item ? (int)((float)kNearMetres * 1.1f * c.lo[0]) + 4 : 0;       // (lo[0] ~ 1 / 2 L)
+    const int k_all = c.kind == kPlain ? kPowMost : 2 * (c.nmx + c.nmy + c.nmz) + 8;
+    const int k_most = min(min(c.k_cut + 2 * near_steps + 8, k_all), kPowMost - 1);
+    double v = kAmplitude;
+    for (int k = 0; k <= min(k_most, kPow - 1); k += 8) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            powers[k + i] = v;
+            v *= beta;
+        }
+    }
+    for (int k = kPow; k <= k_most; k += 64) {
+        powers[kPow + ((k - kPow) >> 6)] = v;
+#pragma unroll 8
+        for (int i = 0; i < 64; ++i) v *= beta;
+    }
+}
+
+// Prepares item `it`, and its powers if there is a place for them: all lanes of one wavefront compute the same, lane 0 writes.
+template <bool COUNT>
+__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane, double* powers) {
     ItemCtx c{};
     c.kind = kEnd;
     if (it < n_items) {
@@ -642,30 +669,7 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
         }
     }
     if (lane == 0) ctx = c;
-}
-
-// The powers of an item's reflection coefficient, by one wavefront, for the counts that an image can have: at most the cut (which
-// steps near the microphone are not held to) or all there are.  One multiplication after the other (see power): formed while
-// the others walk the item before, but for a group's first.
-template <bool COUNT>
-__device__ inline void form_powers(const ItemCtx& c, double* powers, int lane) {
-    if (COUNT || lane || c.kind == kSilent || c.kind == kEnd) return;
-    const double beta = c.beta, near_steps = c.near_item ? kNearMetres * 1.1 / c.two_l + 3.0 : 0.0;
-    const int k_all = c.kind == kPlain ? kPowMost : 2 * (c.nmx + c.nmy + c.nmz) + 8;
-    const int k_most = min(min(c.k_cut + 2 * (int)near_steps + 8, k_all), kPowMost - 1);
-    double v = kAmplitude;
-    for (int k = 0; k <= min(k_most, kPow - 1); k += 8) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            powers[k + i] = v;
-            v *= beta;
-        }
-    }
-    for (int k = kPow; k <= k_most; k += 64) {
-        powers[kPow + ((k - kPow) >> 6)] = v;
-#pragma unroll 8
-        for (int i = 0; i < 64; ++i) v *= beta;
-    }
+    if (powers) form_powers<COUNT>(c, powers, lane);
 }
 
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
@@ -694,9 +698,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     auto prepare_next = [&](ItemCtx& ctx, double* powers) {
         int it = 0;
         if (lane == 0) it = (int)gridDim.x + atomicAdd(&ctrl[1], 1);
-        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane);
-        wave_sync_lds();
-        form_powers<COUNT>(ctx, powers, lane);
+        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane, powers);
     };
 
     // sums start at zero and are left at zero where an item is written out (and where the next one's lie over its columns)
@@ -705,7 +707,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     } else {
         for (int i = tid; i < kMaxTaps + 65; i += kThreads) hist[i] = 0ull;
     }
-    if (wave == kWaves - 1) prepare_item<COUNT>(s_ctx[0], rooms, k_fs_c, items, (int)blockIdx.x, n_items, lane);
+    if (wave == kWaves - 1) prepare_item<COUNT>(s_ctx[0], rooms, k_fs_c, items, (int)blockIdx.x, n_items, lane, nullptr);
 
     for (int now = 0, items_done = 0;; now ^= 1, ++items_done) {
         group_sync();                              // s_ctx[now] is there, and the sums of the item before are complete
@@ -844,18 +846,18 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 const double r_out2 = uni(c.r_out2), walk2 = uni(c.walk2);
                 const float lo0 = uni(c.lo[0]), lo1 = uni(c.lo[1]), hi0 = uni(c.hi[0]), hi1 = uni(c.hi[1]), inv_log2_beta = uni(c.inv_log2_beta);
                 const bool inner_item = uni(c.n0) == 0;
-#pragma unroll
-                for (int pair = 0; pair < kPerThread; pair += 2) {
-                    if (base + 64 * (kWaves * pair + wave) >= n_cand || kThreads * pair >= chunk) continue;
+                // candidates `pair` .. `pair` + N - 1
+                auto describe = [&](auto pair_constant, auto n_constant) {
+                    constexpr int pair = decltype(pair_constant)::value, N = decltype(n_constant)::value;
                     // the lanes' own rows, from there: 64 consecutive columns span few rows, so the next four are compared at once
-                    int cand[2], ix[2], ahead[2][4];
+                    int cand[N], ix[N], ahead[N][4];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e)
+                    for (int e = 0; e < N; ++e)
 #pragma unroll
                         for (int k = 0; k < 4; ++k) ahead[e][k] = row_begin[first_row[pair + e] + 1 + k];
                     bool farther = false;
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
+                    for (int e = 0; e < N; ++e) {
                         cand[e] = min(base + 64 * (kWaves * (pair + e) + wave) + lane, n_cand - 1);
                         ix[e] = first_row[pair + e];
 #pragma unroll
@@ -864,12 +866,12 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     }
                     if (farther) {                        // (seldom)
 #pragma unroll
-                        for (int e = 0; e < 2; ++e)
+                        for (int e = 0; e < N; ++e)
                             while (row_begin[ix[e] + 1] <= cand[e]) ++ix[e];
                     }
-                    int length[2];
+                    int length[N];
 #pragma unroll
-                    for (int e = 0; e < 2; ++e) {
+                    for (int e = 0; e < N; ++e) {
                         const int j = pair + e;
                         const unsigned int gap = row_gap[ix[e]];
                         const int qx = ix[e] & 1, n2 = (ix[e] & ~1) - 2 * nmx, nth = cand[e] - row_begin[ix[e]];
@@ -891,9 +893,17 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                         length[e] = mine && outer > 0.f && cut >= kxy && p1 >= p0 ? min(p1 - p0, 63) : -1;
                     }
 #pragma unroll
-                    for (int e = 0; e < 2; ++e)
+                    for (int e = 0; e < N; ++e)
                         if (length[e] >= 0) place[pair + e] = atomicAdd(&census[parity][63 - length[e]], 1) | (63 - length[e]) << 16;
-                }
+                };
+                const std::integral_constant<int, 1> one;
+                const std::integral_constant<int, 2> two;
+                const auto any = [&](int j) { return base + 64 * (kWaves * j + wave) < n_cand && kThreads * j < chunk; };
+                // (a wavefront with one stretch is not kept by a second that is empty: 3000 responses of 1000 taps, whose items have some 70
+                // candidates, took 68 us instead of 64)
+                if (any(1)) describe(std::integral_constant<int, 0>(), two);
+                else if (any(0)) describe(std::integral_constant<int, 0>(), one);
+                if (any(2)) describe(two, two);
                 group_sync();                             // also: every column of the chunk before has been walked
                 const int of_length = census[parity][lane], up_to = wave_inclusive_scan(of_length);
                 const int n_live = __builtin_amdgcn_readlane(up_to, 63), first = up_to - of_length;
