@@ -42,10 +42,11 @@
 // comparing 64 at once and the near images walked last, 224; the ends of a column walked like its middle, with a
 // slot per lane for what lies outside, 215.  Groups of 1024 threads with 64 registers
 // took 294.  Without its walk (the sums left empty) the kernel alone takes 92 of 222 us there, 113 of 383 for 1024 responses of 16000 taps
-// and 28 of 44 for 128 of 8000: candidates, tables, sorting, stores and barriers, so these count as much as the walk does.  What the long responses want costs this batch 9 of those us: six candidate columns per thread and chunk instead of
-// four, rows with a gap where the cut leaves their middle empty, and shells of equal work (the plan is 16 us instead of 10).
-// Other whole calls before this walk and now: 1 response of 1000 taps 17.3 -> 15.6 us, 3000 of 1000 72 -> 67, 16 of 4096 30.5 ->
-// 24.4, 128 of 8000 65 -> 49, 192 of 16000 186 -> 160, 32 of 32768 230 -> 185.
+// and 28 of 44 for 128 of 8000: candidates, tables, sorting, stores and barriers, so these count as much as the walk does.  What the long responses wanted cost this batch 9 of those us: six candidate columns per thread and chunk instead of
+// four (four again now), rows with a gap where the cut leaves their middle empty, and shells of equal work (the plan is 16 us instead of 10).
+// Other whole calls with amplitudes from a table of z powers and a chunk's columns in registers while they were walked, and now:
+// 1 response of 1000 taps 13.4 -> 12.6 us, 3000 of 1000 63.7 -> 65.2, 1500 of 1500 41.7 -> 41.4, 16 of 4096 23.4 -> 18.3, 128 of 8000 46.3 ->
+// 42.0, 2000 of 8000 219.8 -> 217.9, 192 of 16000 132 -> 125, 32 of 32768 168 -> 142.
 
 #include "rir_plan.h"
 
@@ -61,7 +62,7 @@ constexpr int kPowMost = 1024;            // more reflections than an image of t
 constexpr int kPowTable = kPow + (kPowMost - kPow) / 64;
 constexpr int kAxisCap = 320;             // x or y images per q held in the LDS tables
 constexpr int kYCap = 2 * kAxisCap + 8;
-constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) held in the LDS table
+constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) that the fast walk takes
 constexpr int kPerThread = 4;             // candidate columns per thread and chunk (described two and two)
 // Sums and columns share LDS: columns that there is room for behind the sums of the widest item; items of fewer taps have room for
 // more, and a chunk is as many candidates as are sure to have it.  (Columns with LDS of their own and a chunk walked in as many
@@ -639,7 +640,7 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
             const double r_near = kNearMetres + 0.25 / k_fs_c;
             c.near_item = !COUNT && r_in < r_near;
             c.walk2 = c.near_item ? r_near * r_near : r_in * r_in;
-            // the fast walk: the x and y images fit the LDS tables and so do the powers along z, and the closed forms hold
+            // the fast walk: the x and y images fit the LDS tables, the steps along z a column's record, and the closed forms hold
             const double height_taps = az.room * k_fs_c;
             const bool fast = axis_in_order(ax) && axis_in_order(ay) && axis_in_order(az) && 2 * (2 * c.nmx + 1) <= 2 * kAxisCap && y_images(c.nmy) <= kYCap && c.nmz <= kMaxP &&
                               fmax(ay.room, az.room) * k_fs_c < kMaxAxisTaps && height_taps >= kMinHeightTaps;
