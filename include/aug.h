@@ -30,10 +30,12 @@
  *     call on the context consists of kernel launches only and may be captured
  *     from the context's stream into a graph.  Capture it only after one
  *     identical, uncaptured call.  The graph holds addresses of the workspace:
- *     destroy it before any call with larger sizes or other offsets (which may
- *     move or rewrite the workspace) and before aug_destroy.  A call that would
- *     have to allocate, copy offsets or rebuild tables while its stream is
- *     being captured returns AUG_ERR_UNSUPPORTED instead.
+ *     destroy it before any call with larger sizes, other offsets or another
+ *     response, window or cepstrum length (which may move or rewrite the
+ *     workspace), before front-end calls with more than 15 other combinations
+ *     of hop, feature, channels and mixture on the fly, and before aug_destroy.
+ *     A call that would have to allocate, copy offsets or rebuild tables while
+ *     its stream is being captured returns AUG_ERR_UNSUPPORTED instead.
  *   - Every function returns AUG_OK (0) or a negative aug_status; nothing is
  *     thrown across the boundary.  aug_last_error gives the message of the
  *     last failure on that context.  Arguments are checked on the host, and the

@@ -191,11 +191,6 @@ int ring_reserve(aug_ctx* ctx, size_t bytes) {
     return AUG_OK;
 }
 
-// The framing of a front-end call and the number of work groups that the chip runs at once of its kernel.
-struct Framing {
-    int win, hop, slots;
-};
-
 // The batch's frames shared out evenly, in consecutive stretches, among as many groups as run at once (fewer if there are not
 // that many units), so that a group meets few utterances and all end together.  In groups of so many rows of one utterance,
 // as many as made eight rounds, the last round was half empty and every group set up an utterance's tables for four passes of
@@ -203,7 +198,7 @@ struct Framing {
 // 200 each, 4096 utterances of 8 s waited for the slowest groups (1151 us; in twice as many 1132, four times 1097, eight times
 // 1100), while with 13 each every set-up counts (110, 115, 124, 138 us).
 constexpr int kUnitsPerGroup = 40;
-aug::FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* frame_offsets, const Framing& f) {
+aug::FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* frame_offsets, const aug::Framing& f) {
     aug::FrameShares s;
     for (;; ++s.shift) {                                     // (units of more frames where 31 bits would not number them)
         int64_t units = 0;
@@ -224,7 +219,7 @@ aug::FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* 
 // frame_offsets (with pa.shares) ask for that table; upload_offsets is false where the device already holds these offsets.  The
 // slot's arrays: offsets, frame offsets, block prefix, prefix of the front end's units.
 int stage_packing(aug_ctx* ctx, aug::PackArgs& pa, const int64_t* offsets, bool upload_offsets, int conv_block,
-                  const int64_t* frame_offsets, const Framing* framing) {
+                  const int64_t* frame_offsets, const aug::Framing* framing) {
     aug::HostRing& r = ctx->ring;
     const int i = r.next, e = i / aug::HostRing::kPerEvent;
     if (i % aug::HostRing::kPerEvent == 0)
@@ -302,21 +297,25 @@ struct PendingPack {
 // the arrays go to pinned staging and `pending` is left for the caller to launch, in stream order behind the earlier
 // calls' kernels: the call does not wait for the stream.
 int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* offsets, const int64_t* frame_offsets,
-                 int conv_block, const Framing* framing) {
+                 int conv_block, const aug::Framing* framing) {
     aug::Packing& pk = ctx->packing;
     const size_t n = (size_t)n_utt + 1;
     const bool same_off = pk.offsets.size() == n && !memcmp(pk.offsets.data(), offsets, n * sizeof(int64_t));
     const bool need_conv = conv_block > 0 && !(same_off && pk.conv_block == conv_block);
-    const bool need_fr = frame_offsets && !(same_off && pk.frame_offsets.size() == n &&
-                          !memcmp(pk.frame_offsets.data(), frame_offsets, n * sizeof(int64_t)) &&
-                          pk.win == framing->win && pk.hop == framing->hop && pk.frame_slots == framing->slots);
+    const bool same_frames = frame_offsets && same_off && pk.frame_offsets.size() == n &&
+                             !memcmp(pk.frame_offsets.data(), frame_offsets, n * sizeof(int64_t));
+    int table = aug::Packing::kTables;
+    if (same_frames)
+        for (table = 0; table < aug::Packing::kTables && !(pk.framed[table].framing == *framing);) ++table;
+    const bool need_fr = frame_offsets && table == aug::Packing::kTables;
+    if (frame_offsets && !need_fr) pk.table = table;
     if (same_off && !need_conv && !need_fr) return AUG_OK;
 
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(ctx->stream, &st) != hipSuccess) (void)hipGetLastError();
     if (st != hipStreamCaptureStatusNone)
-        return fail(ctx, AUG_ERR_UNSUPPORTED, "the offsets differ from the previous call's: the tables cannot be "
-                    "rebuilt while the stream is being captured (run the same call once before capturing it)");
+        return fail(ctx, AUG_ERR_UNSUPPORTED, "the tables for these offsets, this response length or this front end are not there: "
+                    "they cannot be built while the stream is being captured (run the same call once before capturing it)");
 
     int64_t n_conv = 0;
     if (need_conv)
@@ -334,7 +333,9 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
     }
     if (need_fr) {
         AUG_TRY(grow(ctx, ctx->d_frame_offsets, n * sizeof(int64_t), "frame offsets buffer"));
-        AUG_TRY(grow(ctx, ctx->d_frame_items, (size_t)std::max(shares.n_groups, 1) * sizeof(int2), "frame group table"));
+        table = same_frames ? pk.next_table : 0;
+        AUG_TRY(grow(ctx, ctx->d_frame_items[table], (size_t)std::max(shares.n_groups, 1) * sizeof(int2), "frame group table"));
+        pa.frame_items = ctx->d_frame_items[table].as<int2>();
     }
     AUG_TRY(ring_reserve(ctx, ring_bytes(n)));
     pa.shares = shares;
@@ -342,7 +343,6 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
     pa.d_frame_offsets = ctx->d_frame_offsets.as<int64_t>();
     pa.d_conv_first = ctx->d_conv_first.as<int>();
     pa.conv_items = ctx->d_conv_items.as<int2>();
-    pa.frame_items = ctx->d_frame_items.as<int2>();
     AUG_TRY(stage_packing(ctx, pa, offsets, !same_off, need_conv ? conv_block : 0, need_fr ? frame_offsets : nullptr, framing));
 
     if (!same_off) {
@@ -355,11 +355,13 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
         pk.n_conv_blocks = n_conv;
     }
     if (need_fr) {
-        pk.frame_offsets.assign(frame_offsets, frame_offsets + n);
-        pk.win = framing->win;
-        pk.hop = framing->hop;
-        pk.frame_slots = framing->slots;
-        pk.shares = shares;
+        if (!same_frames) {
+            pk.frame_offsets.assign(frame_offsets, frame_offsets + n);
+            std::fill(std::begin(pk.framed), std::end(pk.framed), aug::Packing::Framed());
+        }
+        pk.framed[table] = {*framing, shares};
+        pk.table = table;
+        pk.next_table = (table + 1) % aug::Packing::kTables;
     }
     return AUG_OK;
 }
@@ -433,7 +435,7 @@ int prepare_convolve_mix(aug_ctx* ctx, int n_utt, int n_noise, int rir_len) {
 }
 
 int prepare_mel(aug_ctx* ctx, int n_utt, const aug_frontend_cfg* cfg) {
-    if (n_utt == 0 || ctx->packing.shares.n_groups == 0) return AUG_OK;
+    if (n_utt == 0 || ctx->packing.shares().n_groups == 0) return AUG_OK;
     // (a table that grows loses its contents, also where a later one then runs out of memory)
     const size_t window_bytes = sizeof(float) * (size_t)cfg->win;
     if (window_bytes > ctx->window.bytes) ctx->window_n = 0;
@@ -551,8 +553,8 @@ const aug::MelTableArgs& mel_table_args(aug_ctx* ctx, const aug_frontend_cfg* cf
 // With `plan` the image sum's plan too, if it fits the launch (plan->n_rir is 0 on return if not).
 int run_mel_setup(aug_ctx* ctx, PendingPack& pending, int n_utt, const float* alpha, const aug_frontend_cfg* cfg,
                   aug::PlanArgs* plan = nullptr) {
-    if (plan && (ctx->packing.shares.n_groups == 0 || !aug::rir_plan_fits(plan->n_rir))) plan->n_rir = 0;
-    if (n_utt == 0 || ctx->packing.shares.n_groups == 0) return pending.launch();
+    if (plan && (ctx->packing.shares().n_groups == 0 || !aug::rir_plan_fits(plan->n_rir))) plan->n_rir = 0;
+    if (n_utt == 0 || ctx->packing.shares().n_groups == 0) return pending.launch();
     AUG_TRY(prepare_mel(ctx, n_utt, cfg));
     AUG_TRY(mark(ctx, -1));
     const bool mfcc = cfg->feature == AUG_FEAT_MFCC;
@@ -581,14 +583,14 @@ int run_mel(aug_ctx* ctx, int n_utt, const float* wave, const aug_frontend_cfg* 
             const float* extra = nullptr, int64_t extra_stride = 0, const double* energy = nullptr,
             const float* snr_db = nullptr) {
     const aug::Packing& pk = ctx->packing;
-    if (n_utt == 0 || pk.shares.n_groups == 0) return AUG_OK;
+    if (n_utt == 0 || pk.shares().n_groups == 0) return AUG_OK;
     AUG_TRY(mark(ctx, -1));
     aug::MelArgs ma;
     ma.offsets = ctx->d_offsets.as<int64_t>();
     ma.frame_offsets = ctx->d_frame_offsets.as<int64_t>();
-    ma.items = ctx->d_frame_items.as<int2>();
-    ma.n_items = pk.shares.n_groups;
-    ma.shares = pk.shares;
+    ma.items = ctx->d_frame_items[pk.table].as<int2>();
+    ma.n_items = pk.shares().n_groups;
+    ma.shares = pk.shares();
     ma.wave = wave;
     ma.extra = extra;
     ma.extra_stride = extra_stride;
@@ -687,11 +689,11 @@ int aug_destroy(aug_ctx* ctx) {
         (void)hipGetLastError();
         rc = AUG_ERR_HIP;
     }
-    DeviceBuffer* bufs[] = {&ctx->d_offsets, &ctx->d_frame_offsets, &ctx->d_conv_items, &ctx->d_frame_items,
-                            &ctx->d_conv_first,
+    DeviceBuffer* bufs[] = {&ctx->d_offsets, &ctx->d_frame_offsets, &ctx->d_conv_items, &ctx->d_conv_first,
                             &ctx->rir_items, &ctx->rir_ctrl, &ctx->visits, &ctx->rir, &ctx->rir_spec, &ctx->reverb, &ctx->energy, &ctx->first_tap, &ctx->vtlp_tab, &ctx->dct, &ctx->mel_tab, &ctx->mel_lanes,
                             &ctx->window};
     for (DeviceBuffer* b : bufs) b->release();
+    for (DeviceBuffer& b : ctx->d_frame_items) b.release();
     for (DeviceBuffer& b : ctx->twiddle) b.release();
     for (DeviceBuffer& b : ctx->conv_tab) b.release();
     for (auto& m : ctx->marks) (void)hipEventDestroy(m.first);
@@ -820,7 +822,7 @@ int aug_vtlp_mel_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((!wave && offsets[n_utt] > 0) || (!alpha && n_utt > 0) || (!feats_out && frame_offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave, alpha or feats_out is null");
     PendingPack pending(ctx);
-    const Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
+    const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
     AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, 0, &framing));
     AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
     return run_mel(ctx, n_utt, wave, cfg, feats_out);
@@ -847,7 +849,7 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
         return fail(ctx, AUG_ERR_UNSUPPORTED, "%lld groups of %d output rows: the static scratch array holds at most %d",
                     (long long)count_groups(kStaticRows), kStaticRows, AUG_STATIC_MAX_ROW_GROUPS);
     if (cfg->win > 2048) return fail(ctx, AUG_ERR_UNSUPPORTED, "window longer than 2048 samples");
-    const Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
+    const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
     const aug::FrameShares shares = share_frames(n_utt, offsets, frame_offsets, framing);
     if (n_utt == 0 || shares.n_groups == 0) return AUG_OK;
     unsigned char* const base = ctx->scratch;            // the device address, not the array's name
@@ -955,7 +957,7 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((int64_t)n_utt * n_src * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
     PendingPack pending(ctx);
-    const Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, !mixed_out && n_noise > 0)};
+    const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, !mixed_out && n_noise > 0)};
     AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_plan(rir_len).block(), &framing));
     const int64_t total = offsets[n_utt];
     float* rir = rir_out;

@@ -34,16 +34,31 @@ inline int64_t frame_units(int64_t len, int64_t rows, int win, int hop, int shif
     return frames > 0 ? ((frames - 1) >> (4 + shift)) + 1 : 1;
 }
 
+// The framing of a front-end call and the number of work groups that the chip runs at once of its kernel.
+struct Framing {
+    int win = 0, hop = 0, slots = 0;
+    bool operator==(const Framing& o) const { return win == o.win && hop == o.hop && slots == o.slots; }
+};
+
 // Host-side description of how the packed utterances are cut into work items;
 // rebuilt only when the offsets of a call differ from the cached ones.
 struct Packing {
     std::vector<int64_t> offsets;        // n_utt + 1
     std::vector<int64_t> frame_offsets;  // n_utt + 1 (empty if not a front-end call)
     int conv_block = 0;                  // output samples per convolution block the tables were built for
-    int win = 0, hop = 0;                // the framing that the front end's work was shared out for
-    int frame_slots = 0;                 // work groups it was shared among at most
     int64_t n_conv_blocks = 0;           // sum over utterances of ceil(len / conv_block)
-    FrameShares shares;
+    // How the front end's work on these offsets is shared out, one table of beginnings on the device for each framing asked for:
+    // a call that takes other slots (with the mixture on the fly or not, another feature) must not rewrite the table that
+    // a captured call reads.
+    struct Framed {
+        Framing framing;
+        FrameShares shares;
+    };
+    static constexpr int kTables = 16;   // (with more framings of one batch than this the oldest table goes)
+    Framed framed[kTables];              // unused ones have no framing
+    int next_table = 0;                  // the next to be made
+    int table = 0;                       // that of the present call
+    const FrameShares& shares() const { return framed[table].shares; }
 };
 
 // Pinned host staging for the offset arrays: a call writes its arrays into the next slot and the packing kernel
@@ -96,7 +111,7 @@ struct aug_ctx {
     aug::DeviceBuffer d_offsets;         // int64 [n_utt+1]
     aug::DeviceBuffer d_frame_offsets;   // int64 [n_utt+1]
     aug::DeviceBuffer d_conv_items;      // int2 [n_conv_blocks]: (utterance, block)
-    aug::DeviceBuffer d_frame_items;     // int2 [shares.n_groups]: (utterance, unit of it) at which a group begins
+    aug::DeviceBuffer d_frame_items[aug::Packing::kTables];      // int2 [shares.n_groups]: (utterance, unit of it) at which a group begins
     aug::DeviceBuffer d_conv_first;      // int [n_utt+1]: blocks of the utterances before u
     aug::HostRing ring;
     unsigned char* scratch = nullptr;    // this device's copy of the library's static scratch array
