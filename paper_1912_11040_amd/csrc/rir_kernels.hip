@@ -57,9 +57,14 @@ namespace {
 
 constexpr int kThreads = 512;
 constexpr int kWaves = kThreads / 64;
-constexpr int kPow = 256;                 // beta^k table entries held in LDS (see power)
+// beta^k held in LDS (see power): the first kPow and from there every kPowStep-th.  (Two tables of 256 and every 64th, the next
+// item's filled by the wavefront that prepares it: that wavefront is what an item of few images waits for, 3000 responses of 1000 taps
+// 65.3 us instead of 63.9, and columns that begin past 256 multiplied up to 63 times, 64 responses of 8000 taps of rooms of 0.6 to 1 m
+// with beta 0.95 2790 us instead of 2317.)
+constexpr int kPow = 504, kPowStep = 16;
 constexpr int kPowMost = 1024;            // more reflections than an image of the fast walk can have
-constexpr int kPowTable = kPow + (kPowMost - kPow) / 64;
+constexpr int kPowTable = kPow + (kPowMost - kPow + kPowStep - 1) / kPowStep;
+static_assert(kPow % 8 == 0, "form_powers");
 constexpr int kAxisCap = 320;             // x or y images per q held in the LDS tables
 constexpr int kYCap = 2 * kAxisCap + 8;
 constexpr int kMaxP = 160;                // steps of 2 L along z (see walk_step) that the fast walk takes
@@ -455,11 +460,11 @@ __device__ inline int walk_step(const ItemCtx& w, const WalkRegs& k, bool tested
 
 // beta^k / (4 pi) in the sums' fixed point: what a walk that multiplies by beta from one reflection to the next comes to, wherever
 // it began, so that an image's amplitude does not depend on where its response was cut.  `table` holds the first kPow and from
-// there every 64th.
+// there every kPowStep-th.
 __device__ inline double power(const double* table, double beta, int k) {
-    double v = table[k < kPow ? k : kPow + ((k - kPow) >> 6)];
+    double v = table[k < kPow ? k : kPow + (k - kPow) / kPowStep];
     if (k >= kPow)
-        for (int i = k & 63; i > 0; --i) v *= beta;
+        for (int i = (k - kPow) % kPowStep; i > 0; --i) v *= beta;
     return v;
 }
 __device__ __attribute__((noinline)) double power_any(const double* table, double beta, int k) {
@@ -560,7 +565,7 @@ __device__ __attribute__((noinline)) unsigned int walk_near(const ItemCtx& w, in
 
 // The powers of an item's reflection coefficient, by one wavefront, for the counts that an image can have: at most the cut (which
 // steps near the microphone are not held to) or all there are.  One multiplication after the other (see power): formed while
-// the others walk the item before, but for a group's first.
+// others set up the item's y images and rows.
 template <bool COUNT>
 __device__ inline void form_powers(const ItemCtx& c, double* powers, int lane) {
     if (COUNT || lane || c.kind == kSilent || c.kind == kEnd) return;
@@ -576,16 +581,16 @@ __device__ inline void form_powers(const ItemCtx& c, double* powers, int lane) {
             v *= beta;
         }
     }
-    for (int k = kPow; k <= k_most; k += 64) {
-        powers[kPow + ((k - kPow) >> 6)] = v;
-#pragma unroll 8
-        for (int i = 0; i < 64; ++i) v *= beta;
+    for (int k = kPow; k <= k_most; k += kPowStep) {
+        powers[kPow + (k - kPow) / kPowStep] = v;
+#pragma unroll
+        for (int i = 0; i < kPowStep; ++i) v *= beta;
     }
 }
 
-// Prepares item `it`, and its powers if there is a place for them: all lanes of one wavefront compute the same, lane 0 writes.
+// Prepares item `it`: all lanes of one wavefront compute the same, lane 0 writes.
 template <bool COUNT>
-__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane, double* powers) {
+__device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_fs_c, const Item* __restrict__ items, int it, int n_items, int lane) {
     ItemCtx c{};
     c.kind = kEnd;
     if (it < n_items) {
@@ -670,7 +675,6 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
         }
     }
     if (lane == 0) ctx = c;
-    if (powers) form_powers<COUNT>(c, powers, lane);
 }
 
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
@@ -680,7 +684,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     int* __restrict__ ctrl, float* __restrict__ rir_out,
     int32_t* __restrict__ cnt_out, unsigned long long* __restrict__ visits = nullptr) {
     __shared__ __align__(16) unsigned long long hist[kPool];       // tap sums, and behind them the live columns of a chunk
-    __shared__ __align__(16) double s_powers[2][COUNT ? 1 : kPowTable];  // beta^k / (4 pi) 2^56
+    __shared__ __align__(16) double s_powers[COUNT ? 1 : kPowTable];    // beta^k / (4 pi) 2^56
     __shared__ double ykey[kYCap];                 // y images in order of distance: dy*dy
     __shared__ unsigned short ycount[kYCap];       // and reflections
     __shared__ unsigned short row_count[2 * kAxisCap];     // live columns per x image, summed up within every 64 of them
@@ -696,10 +700,10 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     const int wave = uni(tid >> 6), n_items = ctrl[0];
     unsigned long long walked = 0;
     // by one wavefront.  A group begins with the item of its own number: 512 groups that ask one counter wait for each other.
-    auto prepare_next = [&](ItemCtx& ctx, double* powers) {
+    auto prepare_next = [&](ItemCtx& ctx) {
         int it = 0;
         if (lane == 0) it = (int)gridDim.x + atomicAdd(&ctrl[1], 1);
-        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane, powers);
+        prepare_item<COUNT>(ctx, rooms, k_fs_c, items, uni(it), n_items, lane);
     };
 
     // sums start at zero and are left at zero where an item is written out (and where the next one's lie over its columns)
@@ -708,7 +712,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
     } else {
         for (int i = tid; i < kMaxTaps + 65; i += kThreads) hist[i] = 0ull;
     }
-    if (wave == kWaves - 1) prepare_item<COUNT>(s_ctx[0], rooms, k_fs_c, items, (int)blockIdx.x, n_items, lane, nullptr);
+    if (wave == kWaves - 1) prepare_item<COUNT>(s_ctx[0], rooms, k_fs_c, items, (int)blockIdx.x, n_items, lane);
 
     for (int now = 0, items_done = 0;; now ^= 1, ++items_done) {
         group_sync();                              // s_ctx[now] is there, and the sums of the item before are complete
@@ -752,8 +756,8 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
 
         const int nmx = uni(c.nmx), nmy = uni(c.nmy), nmz = uni(c.nmz), k_cut = uni(c.k_cut);
         const int nix = 2 * (2 * nmx + 1), n_yimages = y_images(nmy), segments = (nix + 63) / 64;
-        const double* const powers = s_powers[COUNT ? 0 : now];
-        if (items_done == 0 && wave == 0) form_powers<COUNT>(c, s_powers[COUNT ? 0 : now], lane);
+        const double* const powers = s_powers;
+        if (wave == 0) form_powers<COUNT>(c, s_powers, lane);
         if (kind == kFast) {
             for (int i = tid ^ 64; i < n_yimages; i += kThreads) {
                 int q, n;
@@ -936,7 +940,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                     return uni(next);
                 };
                 if (apart) {
-                    prepare_next(s_ctx[now ^ 1], s_powers[COUNT ? 0 : now ^ 1]);
+                    prepare_next(s_ctx[now ^ 1]);
                     round = next_round();
                 }
                 prepared |= last;
@@ -982,7 +986,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
         } else if (kind == kPlain) {
             walked += walk_plain<COUNT>(c, rir_len, powers, hist);
         }
-        if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1], s_powers[COUNT ? 0 : now ^ 1]);
+        if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1]);
     }
     if (VISITS) {
         for (int off = 32; off > 0; off >>= 1) walked += __shfl_down(walked, off, 64);

@@ -1,4 +1,4 @@
-"""Amplitudes of images with more reflections than the table of powers holds one by one (256), and of the same response cut
+"""Amplitudes of images with many reflections, past what the table of powers holds one by one, and of the same response cut
 differently: every tap to the arithmetic's own error, and bit for bit whatever the batch."""
 import numpy as np
 import pytest
@@ -36,3 +36,23 @@ def test_many_reflections(beta):
         more, _ = _run(np.repeat(row[None], n, axis=0) if n == 24 else np.concatenate([row[None], np.tile(
             np.array([[4.0, 3.0, 2.5, 1.0, 1.0, 1.0, 2.5, 2.0, 1.5, 0.7]], np.float32), (n - 1, 1))]))
         np.testing.assert_array_equal(more[0], h[0])
+
+
+@pytest.mark.parametrize("beta", [0.9, 0.97, 0.999])
+@pytest.mark.parametrize("axis", [0, 1, 2])
+def test_many_reflections_of_a_flat_room(axis, beta):
+    # up to 1115 reflections along one axis, which has more images than the fast walk takes: inner shells are walked one way and
+    # outer ones the other
+    dims, src, mic = [2.5, 3.0], [1.1, 1.3], [1.9, 0.7]
+    for v, thin in ((dims, 0.1), (src, 0.03), (mic, 0.07)):
+        v.insert(axis, thin)
+    row = np.array(dims + src + mic + [beta], np.float32)
+    print(f"case: flat along {axis}, beta {beta}", flush=True)
+    h, cnt = _run(row[None])
+    ref, cnt_ref = O.rir_single(row, L, FS, C)
+    np.testing.assert_array_equal(cnt[0], cnt_ref)
+    bound = np.abs(ref) * (7.1 * 2.0 ** -27 + 2.0 ** -24) + cnt_ref * 2.0 ** -57 + 1e-12 * np.abs(ref)
+    assert np.all(np.abs(h[0] - ref) <= bound)
+    more, _ = _run(np.repeat(row[None], 40, axis=0))
+    np.testing.assert_array_equal(more[0], h[0])
+    np.testing.assert_array_equal(more[39], h[0])
