@@ -324,8 +324,8 @@ __device__ inline int reflection_cut(float inv_log2_beta, float d_min) {
 // One Newton step on the root leaves d fs/c good to ~1e-10 taps; shifted up by the guard, its fraction falls below
 // 2 guard exactly when the true value may lie within the guard of a rounding boundary, and only then is the
 // reference recipe evaluated, on the reference's own d2 (that of the walk may differ in the last bit).
-template <class ExactD2>
-__device__ inline int tap_slot(const ItemCtx& w, double d2, double y, ExactD2 exact_d2) {
+template <class Taps, class ExactD2>
+__device__ inline int tap_slot(const Taps& w, double d2, double y, ExactD2 exact_d2) {
     const double s0 = __dmul_rn(d2, y);                    // sqrt(d2) to 2^-24
     const double res = fma(-s0, s0, d2);                   // exact residual
     const double s1 = fma(__dmul_rn(res, y), 0.5, s0);     // one Newton step: ~4e-15 relative
@@ -467,17 +467,29 @@ __device__ inline double power(const double* table, double beta, int k) {
         for (int i = (k - kPow) % kPowStep; i > 0; --i) v *= beta;
     return v;
 }
-__device__ __attribute__((noinline)) double power_any(const double* table, double beta, int k) {
-    return k < kPowMost ? power(table, beta, k) : pow(beta, (double)k) * kAmplitude;
+// The same for the plain walk, whose images come in no order of their reflections: those past kPow one by one, in the LDS that the
+// fast walk has its y images in.  (Out of line and multiplied up from every 64th for each image, 16 responses of 16000 taps of rooms
+// of 1 to 2 m without a cut took 18.8 ms, 4.8 so.)
+__device__ __attribute__((noinline)) double pow_far(double beta, int k) { return pow(beta, (double)k) * kAmplitude; }
+__device__ inline double power_any(const double* table, const double* past, double beta, int k) {
+    return k < kPowMost ? *(k < kPow ? table + k : past + (k - kPow)) : pow_far(beta, k);
+}
+// by one wavefront, from `table`
+__device__ inline void form_powers_past(const double* table, double* past, double beta, int lane) {
+    static_assert(kPowMost - kPow <= (kYCap < 64 * kPowStep ? kYCap : 64 * kPowStep), "a lane forms kPowStep of them");
+    const int begin = kPowStep * lane, end = min(begin + kPowStep, kPowMost - kPow);
+    if (begin >= end) return;
+    double v = table[kPow + lane];
+    for (int i = begin; i < end; ++i, v *= beta) past[i] = v;
 }
 
 // Items that the closed forms do not take (rooms too flat or narrow for the tables, positions far outside): every column of
 // the bounding box, of a live column the z images about the item's shell, every tap tested.  (All z images of every column: 16
-// responses of 16000 taps of rooms of 1 to 2 m without a cut took 112 ms, 7 so.)  Out of line for the same reason as the power.
+// responses of 16000 taps of rooms of 1 to 2 m without a cut took 112 ms, 4.8 so.)  Out of line for the same reason as the power.
 // Distance and amplitude of an image are formed as walk_step forms them, step for step: whether an item fits the tables
 // depends on where the batch's plan has cut the response, and the response must not.
 template <bool COUNT>
-__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, int rir_len, const double* powers, unsigned long long* hist) {
+__device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, int rir_len, const double* powers, const double* powers_past, unsigned long long* hist) {
     unsigned int walked = 0;
     // Of positions far outside, no shell's radius bounds the numbers of its images: those of the whole response's radius, in
     // whatever item they land.  (Formed here, where they are asked for: in prepare_item they took 2048 responses of 1000 taps of ordinary
@@ -487,7 +499,14 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, i
     };
     const int nmx = most_n(w.ax, w.nmx, w.k_cut / 2 + 1), nmy = most_n(w.ay, w.nmy, w.k_cut / 2 + 1), nmz = most_n(w.az, w.nmz, kNoCut);
     const int niy = 2 * (2 * nmy + 1);
-    const bool below = w.az.src < w.az.mic, in_steps = axis_in_order(w.az);
+    // (what every image needs, in scalar registers: read from LDS again behind every add to the sums, one value after the other, it took
+    // those 16 responses 7.0 ms instead of 4.8)
+    struct { double k_fs_c, shift, guard2; int n0; } const taps{uni(w.k_fs_c), uni(w.shift), uni(w.guard2), uni(w.n0)};
+    const Axis az{uni(w.az.room), uni(w.az.src), uni(w.az.mic)};
+    const double begin[4] = {uni(w.begin[0]), uni(w.begin[1]), uni(w.begin[2]), uni(w.begin[3])};
+    const double two_l = uni(w.two_l), beta = uni(w.beta);
+    const unsigned int last_slot = (unsigned int)uni((int)w.top8) / 8u;
+    const bool below = az.src < az.mic, in_steps = axis_in_order(az);
     const long long n_columns = 2ll * (2 * nmx + 1) * niy;
     const double r_in = w.n0 > 0 ? (double)(w.n0 - 1) / w.k_fs_c : 0.0, inv_2l = 1.0 / w.two_l;
     // what the recipe's operations may move an image of the z axis by: positions so far outside that it is more than a room's
@@ -504,9 +523,10 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, i
         if (!(a < w.r_out2) || kz_max < 0) continue;
         const double far = sqrt(w.r_out2 - a) + rounding, near = fmax(sqrt(fmax(r_in * r_in - a, 0.0)) - rounding, 0.0);
         const int nz = min(nmz, kz_max / 2 + 1);                     // |n - q| + |n| >= 2 |n| - 1
+#pragma unroll
         for (int q = 0; q < 2; ++q) {
             // the images from -far to far but for those between -near and near, and one more at every end for rounding
-            const double at_zero = axis_delta(w.az, q, 0);
+            const double at_zero = axis_delta(az, q, 0);
             auto below_distance = [&](double dz) { return (int)fmin(fmax(floor((dz - at_zero) * inv_2l), -(double)nz - 2.0), (double)nz + 2.0); };
             const int first = max(below_distance(-far), -nz), last = min(below_distance(far) + 1, nz);
             const int hole_first = below_distance(-near) + 2, hole_last = below_distance(near) - 1;
@@ -517,15 +537,15 @@ __device__ __attribute__((noinline)) unsigned int walk_plain(const ItemCtx& w, i
                 }
                 // image (q, n) as element p of its list (see walk_step)
                 const bool up = q ? n > 0 : n && (n > 0) == below;
-                const int list = 2 * q + (int)up, p = up ? abs(n) - 1 : abs(n);
-                const double dz = axis_delta(w.az, q, n), recipe = __dadd_rn(a, __dmul_rn(dz, dz));
+                const int p = up ? abs(n) - 1 : abs(n);
+                const double dz = axis_delta(az, q, n), recipe = __dadd_rn(a, __dmul_rn(dz, dz));
                 // (the recipe rounds positions far outside to less than the tap's guard allows: there it is what counts)
-                const double step = __dadd_rn(__dmul_rn(w.two_l, (double)p), w.begin[list]);
+                const double step = __dadd_rn(__dmul_rn(two_l, (double)p), up ? begin[2 * q + 1] : begin[2 * q]);
                 const double d2 = in_steps ? fma(step, step, a) : recipe;
                 const double y = __builtin_amdgcn_rsq(d2);
-                const int slot = tap_slot(w, d2, y, [&] { return recipe; });
-                if ((unsigned int)slot > w.top8 / 8u) continue;       // (eight times a slot beyond 2^29 would come round)
-                const double amp = COUNT ? 0.0 : power_any(powers, w.beta, kxy + 2 * p + (q ? 1 : list ? 2 : 0));
+                const int slot = tap_slot(taps, d2, y, [&] { return recipe; });
+                if ((unsigned int)slot > last_slot) continue;       // (eight times a slot beyond 2^29 would come round)
+                const double amp = COUNT ? 0.0 : power_any(powers, powers_past, beta, kxy + 2 * p + (q ? 1 : up ? 2 : 0));
                 deposit<COUNT, false>(8u * (unsigned int)slot, amp, y, hist);
                 ++walked;
             }
@@ -802,6 +822,9 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 if (lane == 63) row_part[seg] = part;
             }
             if (tid < 128) census[tid >> 6][lane] = 0;
+        } else if (!COUNT && kind == kPlain && wave == 0) {
+            wave_sync_lds();
+            form_powers_past(powers, ykey, c.beta, lane);
         }
         group_sync();
 
@@ -984,7 +1007,7 @@ __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
                 }
             }
         } else if (kind == kPlain) {
-            walked += walk_plain<COUNT>(c, rir_len, powers, hist);
+            walked += walk_plain<COUNT>(c, rir_len, powers, ykey, hist);
         }
         if (!prepared && wave == kWaves - 1) prepare_next(s_ctx[now ^ 1]);
     }
