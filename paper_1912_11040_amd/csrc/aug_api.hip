@@ -191,29 +191,6 @@ int ring_reserve(aug_ctx* ctx, size_t bytes) {
     return AUG_OK;
 }
 
-// The batch's frames shared out evenly, in consecutive stretches, among as many groups as run at once (fewer if there are not
-// that many units), so that a group meets few utterances and all end together.  In groups of so many rows of one utterance,
-// as many as made eight rounds, the last round was half empty and every group set up an utterance's tables for four passes of
-// sixteen frames: 256 padded utterances of 1-16 s 131 us, 99 so.  Shares of more than kUnitsPerGroup units are cut further: with
-// 200 each, 4096 utterances of 8 s waited for the slowest groups (1151 us; in twice as many 1132, four times 1097, eight times
-// 1100), while with 13 each every set-up counts (110, 115, 124, 138 us).
-constexpr int kUnitsPerGroup = 40;
-aug::FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* frame_offsets, const aug::Framing& f) {
-    aug::FrameShares s;
-    for (;; ++s.shift) {                                     // (units of more frames where 31 bits would not number them)
-        int64_t units = 0;
-        for (int u = 0; u < n_utt; ++u)
-            units += aug::frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], f.win, f.hop, s.shift);
-        if (units >= 1 << 30) continue;
-        s.n_groups = (int)std::min<int64_t>(units, f.slots * std::max<int64_t>(units / ((int64_t)f.slots * kUnitsPerGroup), 1));
-        if (s.n_groups > 0) {
-            s.per_group = (int)(units / s.n_groups);
-            s.longer = (int)(units % s.n_groups);
-        }
-        return s;
-    }
-}
-
 // Write a batch's arrays into the next staging slot and point `pa` at them, without waiting for the stream; the caller
 // launches the packing (alone, or with the front end's set-up) and then calls packing_launched.  conv_block > 0 and
 // frame_offsets (with pa.shares) ask for that table; upload_offsets is false where the device already holds these offsets.  The
@@ -241,7 +218,7 @@ int stage_packing(aug_ctx* ctx, aug::PackArgs& pa, const int64_t* offsets, bool 
         int at = 0;
         for (int u = 0; u < pa.n_utt; ++u) {
             first[u] = at;
-            at += (int)aug::frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], framing->win, framing->hop, pa.shares.shift);
+            at += (int)aug::frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], *framing, pa.shares.shift);
         }
         first[pa.n_utt] = at;
         pa.frame_first = reinterpret_cast<const int*>(d + 2 * i64 + n * sizeof(int));
@@ -322,7 +299,7 @@ int sync_packing(aug_ctx* ctx, PendingPack& pending, int n_utt, const int64_t* o
         for (int u = 0; u < n_utt; ++u) n_conv += (offsets[u + 1] - offsets[u] + conv_block - 1) / conv_block;
     if (n_conv > 0x7fffffffLL) return fail(ctx, AUG_ERR_UNSUPPORTED, "too many blocks in one call");
     if (need_fr && frame_offsets[n_utt] >= (int64_t)1 << 40) return fail(ctx, AUG_ERR_UNSUPPORTED, "too many output rows in one call");
-    const aug::FrameShares shares = need_fr ? share_frames(n_utt, offsets, frame_offsets, *framing) : aug::FrameShares();
+    const aug::FrameShares shares = need_fr ? aug::share_frames(n_utt, offsets, frame_offsets, *framing) : aug::FrameShares();
 
     aug::PackArgs& pa = pending.args;
     pa.n_utt = n_utt;                // from here on the record is dropped unless the launch follows
@@ -850,7 +827,7 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
                     (long long)count_groups(kStaticRows), kStaticRows, AUG_STATIC_MAX_ROW_GROUPS);
     if (cfg->win > 2048) return fail(ctx, AUG_ERR_UNSUPPORTED, "window longer than 2048 samples");
     const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
-    const aug::FrameShares shares = share_frames(n_utt, offsets, frame_offsets, framing);
+    const aug::FrameShares shares = aug::share_frames(n_utt, offsets, frame_offsets, framing);
     if (n_utt == 0 || shares.n_groups == 0) return AUG_OK;
     unsigned char* const base = ctx->scratch;            // the device address, not the array's name
     if (!base) return fail(ctx, AUG_ERR_HIP, "the static scratch array is not available on this device");

@@ -21,24 +21,54 @@ struct DeviceBuffer {
     template <class T> T* as() const { return static_cast<T*>(ptr); }
 };
 
-// How the front end's work is shared among its groups.  An utterance's frames are cut into units of 16 << shift (one unit if it
-// has rows but no frames), numbered in the utterances' order; group g takes those from g per_group + min(g, longer), per_group of
-// them, the first `longer` groups one more.
-struct FrameShares {
-    int n_groups = 0, per_group = 0, longer = 0, shift = 0;
-};
-constexpr int kUnitFrames = 16;              // the frames that a group of the front end has in flight
-inline int64_t frame_units(int64_t len, int64_t rows, int win, int hop, int shift) {
-    if (rows <= 0) return 0;
-    const int64_t frames = len < win ? 0 : 1 + (len - win) / hop;
-    return frames > 0 ? ((frames - 1) >> (4 + shift)) + 1 : 1;
-}
-
 // The framing of a front-end call and the number of work groups that the chip runs at once of its kernel.
 struct Framing {
     int win = 0, hop = 0, slots = 0;
     bool operator==(const Framing& o) const { return win == o.win && hop == o.hop && slots == o.slots; }
 };
+
+// How the front end's work is shared among its groups.  An utterance's frames are cut into units of 16 << shift, its rows without
+// frames into units of 256 << shift (an utterance with rows has one at least), numbered in the utterances' order; group g takes those from
+// g per_group + min(g, longer), per_group of them, the first `longer` groups one more.  The rows without frames, which are set to zero,
+// go with all of their utterance's units evenly.  (Counted by their frames alone, four empty utterances of 20000 rows each were four
+// groups' work, 457 us instead of 50.)
+struct FrameShares {
+    int n_groups = 0, per_group = 0, longer = 0, shift = 0;
+};
+constexpr int kUnitFrames = 16;              // the frames that a group of the front end has in flight
+constexpr int kLgUnitFrames = 4, kLgUnitRows = 8;
+static_assert(1 << kLgUnitFrames == kUnitFrames, "units");
+__host__ __device__ inline int64_t frame_units(int64_t rows, int64_t frames, int shift) {
+    if (rows <= 0) return 0;
+    const int64_t units = ((frames + (((int64_t)kUnitFrames << shift) - 1)) >> (kLgUnitFrames + shift)) + ((rows - frames) >> (kLgUnitRows + shift));
+    return units > 0 ? units : 1;
+}
+inline int64_t frame_units(int64_t len, int64_t rows, const Framing& f, int shift) {
+    return frame_units(rows, len < f.win ? 0 : 1 + (len - f.win) / f.hop, shift);
+}
+
+// The batch's units shared out evenly, in consecutive stretches, among as many groups as run at once (fewer if there are not
+// that many units), so that a group meets few utterances and all end together.  In groups of so many rows of one utterance,
+// as many as made eight rounds, the last round was half empty and every group set up an utterance's tables for four passes of
+// sixteen frames: 256 padded utterances of 1-16 s 131 us, 99 so.  Shares of more than kUnitsPerGroup units are cut further: with
+// 200 each, 4096 utterances of 8 s waited for the slowest groups (1151 us; in twice as many 1132, four times 1097, eight times
+// 1100), while with 13 each every set-up counts (110, 115, 124, 138 us).  `limit`: no more units than that.
+constexpr int kUnitsPerGroup = 40;
+inline FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* frame_offsets, const Framing& f, int64_t limit = 1 << 30) {
+    FrameShares s;
+    for (;; ++s.shift) {                                     // (units of more frames where 31 bits would not number them)
+        int64_t units = 0;
+        for (int u = 0; u < n_utt; ++u) units += frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], f, s.shift);
+        if (units >= limit) continue;
+        const int64_t per_round = (int64_t)f.slots * kUnitsPerGroup, groups = f.slots * (units < per_round ? 1 : units / per_round);
+        s.n_groups = (int)(units < groups ? units : groups);
+        if (s.n_groups > 0) {
+            s.per_group = (int)(units / s.n_groups);
+            s.longer = (int)(units % s.n_groups);
+        }
+        return s;
+    }
+}
 
 // Host-side description of how the packed utterances are cut into work items;
 // rebuilt only when the offsets of a call differ from the cached ones.

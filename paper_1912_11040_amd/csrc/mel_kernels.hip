@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     // The group's share: consecutive units of the utterances' frames (see FrameShares), the first of them unit `unit` of utterance u;
     // its part of an utterance is a stretch.
     int left = a.shares.per_group + ((int)item < a.shares.longer ? 1 : 0);
-    const int shift = a.shares.shift + 4;
+    const int shift = a.shares.shift + kLgUnitFrames;
     // what changes from utterance to utterance
     const float *x, *extra = nullptr;
     int len, n_frames_u;
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     float2 tab0, tab1;
     double energies[2];
     float snr;
-    int units, units_u, wave_first;
+    int units, units_u, frame_units_u, wave_first;
     int64_t rows_u;
     float* feats;
     auto has_gain = [&] { return MIX && tid >= kMelThreads - 64 && tid - (kMelThreads - 64) < a.n_extra; };
@@ -427,9 +427,11 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         if (MIX) extra = a.extra + start;
         feats = a.feats + first_row * n_out;
         n_frames_u = len >= win ? 1 + (len - win) / hop : 0;
-        units_u = n_frames_u > 0 ? ((n_frames_u - 1) >> shift) + 1 : 1;
+        units_u = (int)frame_units(rows_u, n_frames_u, a.shares.shift);
+        frame_units_u = (n_frames_u + ((1 << shift) - 1)) >> shift;
         units = min(left, units_u - unit);
-        wave_first = __builtin_amdgcn_readfirstlane((unit << shift) + (slot & ~3));
+        // (a stretch of rows without frames only: past every frame)
+        wave_first = __builtin_amdgcn_readfirstlane(unit < frame_units_u ? (unit << shift) + (slot & ~3) : 0x7fffffff);
         if (STAGED) request(wave_first);
     };
     begin_stretch();
@@ -460,7 +462,8 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     if (tid + kMelThreads < NC + 1 + kPlanEntries) s_tab[tid + kMelThreads] = tab1;
     // this stretch's part of the rows without frames
     if (const int64_t spare = rows_u - n_frames_u; spare > 0) {
-        const int64_t from = n_frames_u + spare * unit / units_u, to = n_frames_u + spare * (unit + units) / units_u;
+        const int64_t each = spare / units_u, more_rows = spare - each * units_u;
+        const int64_t from = n_frames_u + each * unit + min((int64_t)unit, more_rows), to = from + each * units + max(min(more_rows - unit, (int64_t)units), (int64_t)0);
         for (int64_t i = from * n_out + tid; i < to * n_out; i += kMelThreads) feats[i] = 0.f;
     }
     __syncthreads();
@@ -503,7 +506,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
     __syncthreads();
 
     const bool wide = __builtin_amdgcn_readfirstlane(s_wide) != 0;
-    const int passes = units << (shift - 4);
+    const int passes = max(min(units, frame_units_u - unit), 0) << (shift - kLgUnitFrames);
     for (int it = 0; it < passes; ++it) {
         const int t_wave = wave_first + it * kMelSlots, t = t_wave + (slot & 3);
         if (t_wave >= n_frames_u) break;                  // (no barrier before the stretch's end)
