@@ -944,15 +944,8 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     }
     AUG_TRY(prepare_rir(ctx, n_utt * n_src, rir_len));
     AUG_TRY(prepare_convolve_mix(ctx, n_utt, n_noise, rir_len));
-    aug::PlanArgs plan;
-    plan.n_rir = n_utt * n_src;
-    plan.rooms = {geom, nullptr, 1};
-    plan.rir_len = rir_len;
-    plan.fs_over_c = (double)fs / (double)c;
-    plan.items = ctx->rir_items.ptr;
-    plan.unsorted = ctx->rir_items.as<unsigned char>() + aug::rir_item_bytes() * (size_t)plan.n_rir * aug::rir_items_per_response(rir_len);
-    plan.ctrl = ctx->rir_ctrl.as<int>();
-    plan.n_groups = 2 * ctx->n_cu;
+    aug::PlanArgs plan = aug::rir_plan_args(2 * ctx->n_cu, n_utt * n_src, {geom, nullptr, 1}, rir_len, (double)fs / (double)c,
+                                            ctx->rir_items.ptr, ctx->rir_ctrl.as<int>());
     AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg, &plan));
     AUG_TRY(run_rir(ctx, n_utt * n_src, plan.rooms, rir_len, fs, c, rir, nullptr, plan.n_rir > 0));
     AUG_TRY(run_convolve_mix(ctx, n_utt, n_noise, speech, noise, rir, rir_len, snr_db, mixed_out, gains_out));

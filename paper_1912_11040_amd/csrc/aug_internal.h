@@ -287,6 +287,18 @@ struct PlanArgs {
     int* ctrl;
     int n_groups;
 };
+inline PlanArgs rir_plan_args(int n_groups, int n_rir, const Rooms& rooms, int rir_len, double fs_over_c, void* items, int* ctrl) {
+    PlanArgs p;
+    p.n_rir = n_rir;
+    p.rooms = rooms;
+    p.rir_len = rir_len;
+    p.fs_over_c = fs_over_c;
+    p.items = items;
+    p.unsorted = static_cast<unsigned char*>(items) + rir_item_bytes() * (size_t)n_rir * rir_items_per_response(rir_len);
+    p.ctrl = ctrl;
+    p.n_groups = n_groups;
+    return p;
+}
 constexpr int kPlanThreads = 1024, kPlanMost = 4 * kPlanThreads;
 inline bool rir_plan_fits(int n_rir) { return n_rir <= kPlanMost; }      // one work group plans so many responses
 

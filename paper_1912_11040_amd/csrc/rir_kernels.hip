@@ -1040,10 +1040,8 @@ int rir_ctrl_ints() { return kCtrlInts; }
 hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const Rooms& rooms, int rir_len, double fs_over_c,
                            void* items, int* ctrl) {
     if (n_rir <= 0) return hipSuccess;
-    // `items` holds the sorted table followed by the unsorted one
-    const int per_rir = rir_items_per_response(rir_len);
-    Item* sorted = static_cast<Item*>(items);
-    Item* unsorted = sorted + (size_t)n_rir * per_rir;
+    const PlanArgs p = rir_plan_args(n_groups, n_rir, rooms, rir_len, fs_over_c, items, ctrl);
+    Item *const sorted = static_cast<Item*>(p.items), *const unsorted = static_cast<Item*>(p.unsorted);
     if (n_rir <= kPlanMost) {                                // one launch instead of four
         rir_plan_all_kernel<<<dim3(1), dim3(kPlanThreads), 0, s>>>(n_rir, rooms, rir_len, fs_over_c, sorted, unsorted,
                                                                     ctrl, n_groups);
@@ -1058,7 +1056,7 @@ hipError_t launch_rir_plan(hipStream_t s, int n_groups, int n_rir, const Rooms& 
                                                                     n_groups);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const size_t max_items = (size_t)n_rir * per_rir;
+    const size_t max_items = (size_t)n_rir * rir_items_per_response(rir_len);
     const int item_groups = (int)((max_items + 255) / 256);
     rir_sort_items_kernel<<<dim3((unsigned)item_groups), dim3(256), 0, s>>>(unsorted, sorted, ctrl);
     return hipGetLastError();

@@ -40,3 +40,31 @@ def test_stages_of_one_call(n_utt, n_noise):
     assert not torch.isnan(feats).any() and not torch.isnan(rir).any()
     assert torch.equal(rir, rir2)
     assert torch.equal(feats, feats2)
+
+
+def test_more_items_than_the_plan_keeps_in_lds():
+    # six items a response and more, in large rooms whose responses are quickly summed
+    import torch
+    from paper_1912_11040_amd.binding import Augmenter
+    n_utt, taps, fe = 750, 32768, W.FrontendConfig()
+    rng = np.random.default_rng(8)
+    lens = rng.integers(300, 700, n_utt)
+    offsets = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    foff = np.concatenate([[0], np.cumsum(np.where(lens >= fe.win, 1 + (lens - fe.win) // fe.hop, 0))]).astype(np.int64)
+    total = int(offsets[-1])
+    geom = np.empty((n_utt, 2, 10), np.float32)
+    geom[:, :, 0:3] = rng.uniform([48.0, 40.0, 32.0], [80.0, 72.0, 48.0], (n_utt, 1, 3))
+    geom[:, :, 3:6] = geom[:, :, 0:3] * rng.uniform(0.2, 0.8, (n_utt, 2, 3))
+    geom[:, :, 6:9] = geom[:, :, 0:3] * rng.uniform(0.2, 0.8, (n_utt, 1, 3))
+    geom[:, :, 9] = rng.choice([0.0, 0.3, 0.85, 1.0], (n_utt, 1))
+    g, nan = dev(geom), lambda *shape: torch.full(shape, float("nan"), device="cuda")                 # noqa: E731
+    feats, rir, rir2 = nan(int(foff[-1]), fe.n_mel), nan(n_utt, 2, taps), nan(n_utt, 2, taps)
+    print("case: 1500 responses of 32768 taps", flush=True)
+    with Augmenter(0) as aug:
+        aug.aug_pipeline_batch(offsets, dev(rng.standard_normal(total).astype(np.float32)), dev(rng.standard_normal((1, total)).astype(np.float32)), g, taps,
+                               W.FS, W.SPEED_OF_SOUND, dev(np.full((n_utt, 1), 10.0, np.float32)), dev(np.ones(n_utt, np.float32)), fe, foff, feats, rir)
+        for at in range(0, n_utt, 250):                       # in parts that need no such room
+            aug.aug_rir_batch(g[at:at + 250].reshape(-1, 10).contiguous(), taps, W.FS, W.SPEED_OF_SOUND, rir2[at:at + 250])
+        torch.cuda.synchronize()
+    assert not torch.isnan(feats).any()
+    assert torch.equal(rir, rir2)
