@@ -272,6 +272,14 @@ __device__ inline float row_negate(float x) {
 
 typedef float vec4 __attribute__((ext_vector_type(4)));
 
+// The gain of a source.  Out of line: in the loop over a group's utterances the constants of its exponential were kept in registers all
+// along, or spilled for it (16 of them with a window of 400 samples, 36 with others; so 8 or none, 18): with three noises 256 utterances of
+// 8 s 151 -> 147 us, of 4 s with a hop of 240 78 -> 72, with a window of 320 115 -> 106.
+__device__ __attribute__((noinline)) float source_gain(double e0, double ej, float snr_db) {
+    const double e[2] = {e0, ej};
+    return snr_gain(e, 0, snr_db);
+}
+
 // 4-point DFT of windowed inputs x_m w_m, m < 4 (or 3): the window's factors ride on the additions
 template <bool FOUR>
 __device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2& a3, float2 w0, float2 w1, float2 w2, float2 w3) {
@@ -495,7 +503,7 @@ __global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(M
         s_pieces[m] = make_int4(4 * p0 + (m & 3), n > 1 ? -1 : 0, n > 2 ? -1 : 0, n > 3 ? (n > 4 ? n : -1) : 0);
         if (n > 4) s_wide = 1;
     }
-    if (has_gain()) s_gains[tid - (kMelThreads - 64)] = snr_gain(energies, 0, snr);
+    if (has_gain()) s_gains[tid - (kMelThreads - 64)] = source_gain(energies[0], energies[1], snr);
     // where this lane's block starts to read powers, per round
     int at[kMaxRounds];
 #pragma unroll
@@ -803,8 +811,8 @@ hipError_t launch_mel(hipStream_t s, const MelArgs& a) {
     const bool mix = a.n_extra > 0;
     // A window of 400 samples has kernels of its own for every hop; its mixtures are staged where the loads cover four frames
     // and the samples of a frame start on a pair.  (With hops of 161 and 240 the general kernel, 16 rows of inputs instead of
-    // 13 and a wavefront per SIMD fewer, took 379 and 281 us where these take 299 and 221 for 1024 utterances of 8 s,
-    // and 133 and 107 us where these take 103 and 85 for a mixture of 256 x 4 s with three noises.)
+    // 13 and without a mixture a wavefront per SIMD fewer, took 334 and 236 us where these take 287 and 205 for 1024 utterances of 8 s,
+    // and 105 and 80 us where these take 93 and 72 for a mixture of 256 x 4 s with three noises.)
     const bool staged = a.cfg.hop <= kStagedHop && a.cfg.hop % 2 == 0;
     auto k = a.cfg.win == 400 ? (!mix ? &mel_kernel<400, false, false> : staged ? &mel_kernel<400, true, true> : &mel_kernel<400, true, false>)
                               : (mix ? &mel_kernel<0, true, false> : &mel_kernel<0, false, false>);
