@@ -327,10 +327,12 @@ inline size_t mel_lds_bytes(const aug_frontend_cfg& cfg) {
     if (cfg.feature == AUG_FEAT_MFCC) lds += 16 * (size_t)((cfg.n_mel + 3) / 4) * ((cfg.n_ceps + 15) & ~15);
     return lds;
 }
-// Groups of the front end that the chip runs at once: four wavefronts per SIMD with a window of 400 samples and no mixture, three
-// otherwise, and what the LDS allows.
+// Wavefronts per SIMD that the front end's kernels are built for (their launch bounds): four with a window of 400 samples and no mixture,
+// three otherwise.
+constexpr int mel_waves(bool own_window, bool mix) { return own_window && !mix ? 4 : 3; }
+// Groups of the front end that the chip runs at once, by that and by what the LDS allows.
 inline int mel_slots(int n_cu, const aug_frontend_cfg& cfg, bool mix) {
-    const int by_waves = cfg.win == 400 && !mix ? 4 : 3, by_lds = (int)((160 * 1024) / (mel_lds_bytes(cfg) + 1280));
+    const int by_waves = mel_waves(cfg.win == 400, mix), by_lds = (int)((160 * 1024) / (mel_lds_bytes(cfg) + 1280));
     return n_cu * (by_lds < 1 ? 1 : by_lds < by_waves ? by_lds : by_waves);
 }
 

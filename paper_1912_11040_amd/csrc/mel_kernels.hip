@@ -313,7 +313,7 @@ __device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2&
 // floats there take the vector units' time.  Requesting a frame's samples a pass ahead without a mixture as well does not fit
 // the registers of four wavefronts per SIMD: 4096 utterances 1251 us.)
 template <int WIN, bool MIX, bool STAGED>
-__global__ __launch_bounds__(kMelThreads, WIN && !MIX ? 4 : 3) void mel_kernel(MelArgs a, int tab_stride) {
+__global__ __launch_bounds__(kMelThreads, mel_waves(WIN == 400, MIX)) void mel_kernel(MelArgs a, int tab_stride) {
     constexpr int NC = 256;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int s_wide;                               // some channel has more than four pieces
@@ -805,6 +805,7 @@ hipError_t launch_mel(hipStream_t s, const MelArgs& a) {
     if (a.cfg.nfft != 512) return hipErrorInvalidValue;
     constexpr int NC = 256;
     static_assert(kMelThreads == NC, "a thread per pair of window samples");
+    static_assert(kMelThreads == 4 * 64, "a group is a wavefront on every SIMD (mel_slots)");
     static_assert(kMelSlots == kUnitFrames && sizeof(float) * kSlotFloats == 4 * 272 && sizeof(vec4) * (kMaxSteps / 4) == 16 * 8 &&
                   kLanePairs * kMelLanes == 8 * 16 && sizeof(int4) == 16, "mel_lds_bytes");
     const size_t lds = mel_lds_bytes(a.cfg);

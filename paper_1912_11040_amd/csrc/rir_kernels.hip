@@ -697,6 +697,10 @@ __device__ inline void prepare_item(ItemCtx& ctx, const Rooms& rooms, double k_f
     if (lane == 0) ctx = c;
 }
 
+// What a group of the kernel below keeps in LDS: two must fit a compute unit, or the 2 n_cu persistent groups run in two rounds.
+constexpr size_t kImageLds = 8 * (size_t)kPool + 8 * kPowTable + 10 * kYCap + 10 * 2 * kAxisCap + 4 * (2 * kAxisCap / 64 + 5 + 2 * 64 + 1) + 2 * sizeof(ItemCtx) + 16;      // (the last: alignment)
+static_assert(kImageLds <= 80 * 1024 && 2 * kThreads <= 4 * 4 * 64, "two groups on a compute unit");
+
 // VISITS: a measuring instantiation that also adds the number of images it walked to *visits.
 template <bool COUNT, bool VISITS = false>
 __global__ __launch_bounds__(kThreads, 4) void rir_image_kernel(
