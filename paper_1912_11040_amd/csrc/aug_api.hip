@@ -799,7 +799,7 @@ int aug_vtlp_mel_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((!wave && offsets[n_utt] > 0) || (!alpha && n_utt > 0) || (!feats_out && frame_offsets[n_utt] > 0))
         return fail(ctx, AUG_ERR_INVALID_ARG, "wave, alpha or feats_out is null");
     PendingPack pending(ctx);
-    const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
+    const aug::Framing framing = aug::mel_framing(ctx->n_cu, *cfg, false);
     AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, 0, &framing));
     AUG_TRY(run_mel_setup(ctx, pending, n_utt, alpha, cfg));
     return run_mel(ctx, n_utt, wave, cfg, feats_out);
@@ -826,7 +826,7 @@ int aug_vtlp_mel_batch_static(aug_ctx* ctx, int n_utt, const int64_t* offsets, c
         return fail(ctx, AUG_ERR_UNSUPPORTED, "%lld groups of %d output rows: the static scratch array holds at most %d",
                     (long long)count_groups(kStaticRows), kStaticRows, AUG_STATIC_MAX_ROW_GROUPS);
     if (cfg->win > 2048) return fail(ctx, AUG_ERR_UNSUPPORTED, "window longer than 2048 samples");
-    const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, false)};
+    const aug::Framing framing = aug::mel_framing(ctx->n_cu, *cfg, false);
     const aug::FrameShares shares = aug::share_frames(n_utt, offsets, frame_offsets, framing);
     if (n_utt == 0 || shares.n_groups == 0) return AUG_OK;
     unsigned char* const base = ctx->scratch;            // the device address, not the array's name
@@ -934,7 +934,7 @@ int aug_pipeline_batch(aug_ctx* ctx, int n_utt, const int64_t* offsets, const fl
     if ((int64_t)n_utt * n_src * aug::rir_items_per_response(rir_len) > 0x7fffffffLL)
         return fail(ctx, AUG_ERR_UNSUPPORTED, "too many responses in one call");
     PendingPack pending(ctx);
-    const aug::Framing framing{cfg->win, cfg->hop, aug::mel_slots(ctx->n_cu, *cfg, !mixed_out && n_noise > 0)};
+    const aug::Framing framing = aug::mel_framing(ctx->n_cu, *cfg, !mixed_out && n_noise > 0);
     AUG_TRY(sync_packing(ctx, pending, n_utt, offsets, frame_offsets, aug::conv_plan(rir_len).block(), &framing));
     const int64_t total = offsets[n_utt];
     float* rir = rir_out;

@@ -21,30 +21,32 @@ struct DeviceBuffer {
     template <class T> T* as() const { return static_cast<T*>(ptr); }
 };
 
-// The framing of a front-end call and the number of work groups that the chip runs at once of its kernel.
+// The framing of a front-end call, the values of an output row and the number of work groups that the chip runs at once of its kernel.
 struct Framing {
-    int win = 0, hop = 0, slots = 0;
-    bool operator==(const Framing& o) const { return win == o.win && hop == o.hop && slots == o.slots; }
+    int win = 0, hop = 0, width = 0, slots = 0;
+    bool operator==(const Framing& o) const { return win == o.win && hop == o.hop && width == o.width && slots == o.slots; }
 };
 
 // How the front end's work is shared among its groups.  An utterance's frames are cut into units of 16 << shift, its rows without
-// frames into units of 256 << shift (an utterance with rows has one at least), numbered in the utterances' order; group g takes those from
+// frames into units of 1 << lg_rows + shift, some 8000 to 16000 values (an utterance with rows has one at least), numbered in the utterances' order; group g takes those from
 // g per_group + min(g, longer), per_group of them, the first `longer` groups one more.  The rows without frames, which are set to zero,
 // go with all of their utterance's units evenly.  (Counted by their frames alone, four empty utterances of 20000 rows each were four
 // groups' work, 457 us instead of 50.)
 struct FrameShares {
-    int n_groups = 0, per_group = 0, longer = 0, shift = 0;
+    int n_groups = 0, per_group = 0, longer = 0, shift = 0, lg_rows = 0;
 };
-constexpr int kUnitFrames = 16;              // the frames that a group of the front end has in flight
-constexpr int kLgUnitFrames = 4, kLgUnitRows = 8;
+constexpr int kUnitFrames = 16, kLgUnitFrames = 4;       // the frames that a group of the front end has in flight
 static_assert(1 << kLgUnitFrames == kUnitFrames, "units");
-__host__ __device__ inline int64_t frame_units(int64_t rows, int64_t frames, int shift) {
-    if (rows <= 0) return 0;
-    const int64_t units = ((frames + (((int64_t)kUnitFrames << shift) - 1)) >> (kLgUnitFrames + shift)) + ((rows - frames) >> (kLgUnitRows + shift));
-    return units > 0 ? units : 1;
+inline int unit_lg_rows(int width) {
+    int lg = 13;
+    while (width > 1) width >>= 1, --lg;
+    return lg;
 }
 inline int64_t frame_units(int64_t len, int64_t rows, const Framing& f, int shift) {
-    return frame_units(rows, len < f.win ? 0 : 1 + (len - f.win) / f.hop, shift);
+    if (rows <= 0) return 0;
+    const int64_t frames = len < f.win ? 0 : 1 + (len - f.win) / f.hop;
+    const int64_t units = ((frames + (((int64_t)kUnitFrames << shift) - 1)) >> (kLgUnitFrames + shift)) + ((rows - frames) >> (unit_lg_rows(f.width) + shift));
+    return units > 0 ? units : 1;
 }
 
 // The batch's units shared out evenly, in consecutive stretches, among as many groups as run at once (fewer if there are not
@@ -56,6 +58,7 @@ inline int64_t frame_units(int64_t len, int64_t rows, const Framing& f, int shif
 constexpr int kUnitsPerGroup = 40;
 inline FrameShares share_frames(int n_utt, const int64_t* offsets, const int64_t* frame_offsets, const Framing& f, int64_t limit = 1 << 30) {
     FrameShares s;
+    s.lg_rows = unit_lg_rows(f.width);
     for (;; ++s.shift) {                                     // (units of more frames where 31 bits would not number them)
         int64_t units = 0;
         for (int u = 0; u < n_utt; ++u) units += frame_units(offsets[u + 1] - offsets[u], frame_offsets[u + 1] - frame_offsets[u], f, s.shift);
@@ -334,6 +337,9 @@ constexpr int mel_waves(bool own_window, bool mix) { return own_window && !mix ?
 inline int mel_slots(int n_cu, const aug_frontend_cfg& cfg, bool mix) {
     const int by_waves = mel_waves(cfg.win == 400, mix), by_lds = (int)((160 * 1024) / (mel_lds_bytes(cfg) + 1280));
     return n_cu * (by_lds < 1 ? 1 : by_lds < by_waves ? by_lds : by_waves);
+}
+inline Framing mel_framing(int n_cu, const aug_frontend_cfg& cfg, bool mix) {
+    return {cfg.win, cfg.hop, cfg.feature == AUG_FEAT_MFCC ? cfg.n_ceps : cfg.n_mel, mel_slots(n_cu, cfg, mix)};
 }
 
 // STFT power -> warped mel -> power law.

@@ -177,8 +177,8 @@ struct __attribute__((aligned(4))) SamplePair { float x, y; };
 // pair plus one vector register, with no 64-bit vector arithmetic per access.
 // The place `bytes` behind a wave-uniform base, itself kept in scalar registers: of rows a constant apart the compiler would otherwise
 // add the constants to the vector address, two instructions and a wait state per access.  (With that, and without the copies that
-// the first wavefront's special case and zeros for no next window cost all: 59 200 vector instructions per wavefront instead of 64 000
-// on 256 utterances of 1-16 s with three noises, whose kernel is bound as much by what is on its way to and from memory: without
+// the first wavefront's special case and zeros for no next window cost all: 58 700 vector instructions per wavefront instead of 63 500
+// on 256 utterances of 1-16 s with three noises, whose kernel takes its 1.09 million cycles with either (see convolve_inplace_kernel).  Without
 // the windows' traffic it would take 4.5 % less, without the stores' 4.2.)
 typedef const __attribute__((address_space(1))) char* GlobalRow;
 __device__ inline GlobalRow row_at(const void* base, uint32_t bytes) {
@@ -320,8 +320,8 @@ __device__ inline double wave_energy(float e) {
 // With two partitions (CONTIGUOUS) a group needs consecutive blocks of a signal, so it takes one contiguous range.
 // What a block needs of the tables comes by scalar loads (nothing here writes them), asked for a block ahead: by vector loads, where
 // it was needed, three round trips to the L2 and the wait for whatever was on its way before them stood between two barriers
-// of every block.  (With the scalar addresses, whole calls: measured responses 156.1 -> 154.0 us, 64 utterances of 4 s with 8000 taps
-// the kernel alone 45.4 -> 43.3.)
+// of every block.  (With the scalar addresses, whole calls with one noise: 64 utterances of 4 s with 8000 taps 59.3 -> 57.2 us,
+// 256 of 2 s with 16000 105.9 -> 102.8.)
 template <class T>
 __device__ inline T scalar_load(const T* p) { return *(const __attribute__((address_space(4))) T*)p; }
 
@@ -628,10 +628,13 @@ __global__ __launch_bounds__(InPlace<N>::T) void rir_spectrum_inplace_kernel(
     }
 }
 
-// What bounds it: one group of sixteen wavefronts fills a compute unit (the block is 128 KB of LDS), its barriers keep the
-// wavefronts in step, and so the time in the LDS and the time in the vector units add up.  Against transforms in natural
+// What bounds it: one group of sixteen wavefronts fills a compute unit (the block is 128 KB of LDS) and its barriers keep the
+// wavefronts in step.  On 256 utterances of 1-16 s with three noises the vector units are busy 0.86 of the time and the LDS 0.48, so the
+// two overlap; a wavefront issues for 0.30 of its time, waits to issue for 0.31 and waits for memory, LDS or a barrier for 0.38.  Vector issue
+// alone is not the limit: with 7.6 % fewer instructions (0.86 busy instead of 0.93) it takes the same cycles.  What does limit it is
+// not known.  About 1680 vector instructions per thread and block, all told.  Against transforms in natural
 // order, with the product from LDS between them, this one makes 12 passes over the block in LDS instead of 16, has four
-// barriers per block instead of five, and about 1450 vector instructions per thread and block instead of 2200: twiddles
+// barriers per block instead of five, and two thirds of the vector instructions: twiddles
 // folded into the butterflies' additions, the product in twenty multiply-adds per pair from the registers that the last
 // forward and the first inverse step share.
 // While a block's inverse transform runs, the inputs of the next block are already on their way from HBM; the response

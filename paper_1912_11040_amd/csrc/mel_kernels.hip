@@ -435,8 +435,8 @@ __global__ __launch_bounds__(kMelThreads, mel_waves(WIN == 400, MIX)) void mel_k
         if (MIX) extra = a.extra + start;
         feats = a.feats + first_row * n_out;
         n_frames_u = len >= win ? 1 + (len - win) / hop : 0;
-        units_u = (int)frame_units(rows_u, n_frames_u, a.shares.shift);
         frame_units_u = (n_frames_u + ((1 << shift) - 1)) >> shift;
+        units_u = max(frame_units_u + (int)((rows_u - n_frames_u) >> (a.shares.shift + a.shares.lg_rows)), 1);      // (see frame_units)
         units = min(left, units_u - unit);
         // (a stretch of rows without frames only: past every frame)
         wave_first = __builtin_amdgcn_readfirstlane(unit < frame_units_u ? (unit << shift) + (slot & ~3) : 0x7fffffff);

@@ -41,12 +41,13 @@
 // in small batches); this walk, 261; the item's constants formed by one wavefront while the others walk, 239; rows found by
 // comparing 64 at once and the near images walked last, 224; the ends of a column walked like its middle, with a
 // slot per lane for what lies outside, 215.  Groups of 1024 threads with 64 registers
-// took 294.  Without its walk (the sums left empty) the kernel alone takes 92 of 222 us there, 113 of 383 for 1024 responses of 16000 taps
-// and 28 of 44 for 128 of 8000: candidates, tables, sorting, stores and barriers, so these count as much as the walk does.  What the long responses wanted cost this batch 9 of those us: six candidate columns per thread and chunk instead of
+// took 294.  Without its walk (the sums left empty) the kernel alone takes 85 of 212 us there, 102 of 378 for 1024 responses of 16000
+// taps and 21 of 34 for 128 of 8000: candidates, tables, sorting, stores and barriers, so these count nearly as much as the walk does.
+// What the long responses wanted cost this batch 9 of those us: six candidate columns per thread and chunk instead of
 // four (four again now), rows with a gap where the cut leaves their middle empty, and shells of equal work (the plan is 16 us instead of 10).
 // Other whole calls with amplitudes from a table of z powers and a chunk's columns in registers while they were walked, and now:
-// 1 response of 1000 taps 13.4 -> 12.6 us, 3000 of 1000 63.7 -> 65.2, 1500 of 1500 41.7 -> 41.4, 16 of 4096 23.4 -> 18.3, 128 of 8000 46.3 ->
-// 42.0, 2000 of 8000 219.8 -> 217.9, 192 of 16000 132 -> 125, 32 of 32768 168 -> 142.
+// 1 response of 1000 taps 15.6 -> 12.5 us, 600 of 1000 25.0 -> 25.7, 3000 of 1000 64.2 -> 63.9, 16 of 4096 24.4 -> 17.9, 128 of 8000 43.1 ->
+// 38.7, 2000 of 8000 222 -> 220, 384 of 16000 205 -> 196, 16 of 32768 118 -> 87.
 
 #include "rir_plan.h"
 
@@ -277,7 +278,7 @@ struct ItemCtx {
     double k_fs_c;
     double quick_k;         // fs/c, less the middle of the hardware estimate's error
     double quick_shift;     // 0.5 + margin - (n0 - 1) + kQuickMagic
-    int quick_margin2;      // quick estimates whose 16-bit fraction is below this are settled by tap_slot
+    int quick_margin2;      // quick estimates whose 16-bit fraction is below this are formed again (see walk_step)
     double shift;           // 0.5 + guard - (n0 - 1)
     double guard2;
     double settle_shift;    // the same in units of 2^-32 tap (see walk_step)

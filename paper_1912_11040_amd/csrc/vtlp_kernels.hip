@@ -24,11 +24,12 @@
 // Per utterance a table holds, for every output bin, the lower source bin and the interpolation weight;
 // both come from fp64 arithmetic so that the choice of the bin pair matches a double-precision evaluation.
 //
-// What bounds it: vector issue, about 1220 vector instructions per frame, with three wavefronts per SIMD (the window's 32
+// What bounds it: vector issue, with room for three wavefronts per SIMD (the window's 32
 // registers, factors that do not differ from frame to frame in LDS, 53.7 KB for four wavefronts), and in batches that do not
 // fill the chip many times the last round of groups: 256 utterances of 1-16 s are 1.95 rounds of 768 groups.  On that batch the whole call takes
-// 303 us where transforms in natural order, with the spectrum's split, the product and the window (8 KB) in LDS and so two
-// wavefronts per SIMD, 1440 vector and 217 LDS instructions per frame, took 480; 768 utterances of 640 frames take 2.6 ns a frame.
+// 303 us, the vector units busy 0.87 of the time with 1480 instructions per frame, set-up and the ends of runs included, and 128 of the LDS,
+// where transforms in natural order, with the spectrum's split, the product and the window (8 KB) in LDS and so two
+// wavefronts per SIMD, took 480, busy 0.52 of the time with 1440 and 217: the third wavefront is what it gains by; 768 utterances of 640 frames take 2.6 ns a frame.
 // Runs of at most 10, 12, 14, 20, 24 and 32 frames: 407, 312, 331, 389, 318, 343 us, by how full the last round is; plain
 // stores instead of the atomics would give 14 us, cheaper constants at a group's start nothing.
 

@@ -45,8 +45,9 @@ int main() {
         for (int longest : {0, 300, 5000, 3000000})
             for (int spare : {0, 3, 20000})
                 for (int slots : {1, 2, 768})
-                    for (int64_t limit : {(int64_t)1 << 30, (int64_t)40000, (int64_t)2000}) {
-                        const aug::Framing f{400, 160, slots};
+                    for (int width : {1, 13, 40, 128}) for (int64_t limit : {(int64_t)1 << 30, (int64_t)40000, (int64_t)2000}) {
+                        const aug::Framing f{400, 160, width, slots};
+                        const int64_t unit_rows = 8192 / (width < 2 ? 1 : width < 16 ? 8 : width < 64 ? 32 : 128);
                         std::vector<int64_t> off(1, 0), foff(1, 0);
                         for (int u = 0; u < n_utt; ++u) {
                             const int64_t len = longest ? (int64_t)(rng() % (unsigned)longest) : 0, frames = len < 400 ? 0 : 1 + (len - 400) / 160;
@@ -61,9 +62,9 @@ int main() {
                             const int64_t units = aug::frame_units(len, rows, f, s.shift);
                             first[u + 1] = first[u] + (int)units;
                             if ((units > 0) != (rows > 0)) ++faults;
-                            // a unit holds 16 << shift frames at most and no more than twice 256 << shift of the rows without
-                            if (((units - (rows - frames) / (256 << s.shift)) << (4 + s.shift)) < frames) ++faults;
-                            if (rows - frames > (units + 1) * (256 << s.shift)) ++faults;
+                            // a unit holds 16 << shift frames at most, and rows without frames make one for every unit_rows << shift
+                            if (((units - (rows - frames) / (unit_rows << s.shift)) << (4 + s.shift)) < frames) ++faults;
+                            if (rows - frames > (units + 1) * (unit_rows << s.shift)) ++faults;
                         }
                         const int units = first[n_utt];
                         if (units >= limit || (s.shift > 0) != (aug::share_frames(n_utt, off.data(), foff.data(), f).shift != s.shift)) ++faults;

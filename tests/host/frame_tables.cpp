@@ -90,7 +90,7 @@ static int run(aug_ctx* ctx, int kind) {
 static int faults(const aug::MelArgs& a) {
     int bad = 0, g = 0, next = 0, unit = 0;
     for (size_t u = 0; u + 1 < g_offsets.size(); ++u) {
-        const int64_t n = aug::frame_units(g_offsets[u + 1] - g_offsets[u], g_frames[u + 1] - g_frames[u], aug::Framing{a.cfg.win, a.cfg.hop, 0}, a.shares.shift);
+        const int64_t n = aug::frame_units(g_offsets[u + 1] - g_offsets[u], g_frames[u + 1] - g_frames[u], aug::Framing{a.cfg.win, a.cfg.hop, aug_feature_dim(&a.cfg), 0}, a.shares.shift);
         for (int i = 0; i < n; ++i, ++unit)
             if (unit == next && g < a.shares.n_groups) {
                 if (a.items[g].x != (int)u || a.items[g].y != i) ++bad;
