@@ -42,9 +42,9 @@ PER_CONFIG_STEPS = {"tiny": 300, "features": 100, "batch": 300, "varlen": 200, "
 # runs summarised in profiles/hbm_traffic_<workload>.md, scaled there by a 1 GiB copy.  They describe the
 # kernel sources with this digest only; for any other sources `traffic` is reported as null.
 RECORDED_TRAFFIC = {
-    "digest": "2726a33a307d2e30",
-    "varlen": {"rir": 66969255, "rir_spectrum": 202792583, "convolve": 1258329689, "mel": 654178104},
-    "throughput": {"rir": 408594708, "rir_spectrum": 1218355303, "convolve": 13831655284, "mel": 2262142495},
+    "digest": "b62addbda35db1bf",
+    "varlen": {"rir": 66971882, "rir_spectrum": 202780696, "convolve": 1258928986, "mel": 646071834},
+    "throughput": {"rir": 408620437, "rir_spectrum": 1218426542, "convolve": 13830856033, "mel": 2249390259},
 }
 
 
