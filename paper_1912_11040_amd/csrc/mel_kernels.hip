@@ -308,7 +308,7 @@ __device__ inline void dft4_windowed(float2& a0, float2& a1, float2& a2, float2&
 // projection on the matrix cores, which read every power once and need no vector arithmetic, took that batch from
 // 1500 to 1080-1140 us; cepstra from a cosine table in LDS instead of global memory, 256 padded utterances from 350
 // to 134 us, and equal shares, set up from loads that are all on their way at once, to 99.  With a mixture it waits for memory:
-// 152 us for four sources of 256 utterances of 1-16 s (0.56 GB).
+// 148 us for four sources of 256 utterances of 1-16 s (0.56 GB).
 // (The first radix-16 pass on the matrix cores as well measured slower, 1350 us: products of 32-bit
 // floats there take the vector units' time.  Requesting a frame's samples a pass ahead without a mixture as well does not fit
 // the registers of four wavefronts per SIMD: 4096 utterances 1251 us.)
